@@ -344,6 +344,41 @@ mtla_status mtla_cache_fork_paged(mtla_ctx* ctx, void* cache_c, void* cache_kr, 
                                   int32_t* dst_seq_len, void* workspace, void* hip_stream);
 
 /*
+ * Page bookkeeping on the host, for callers that want the library to keep it: a
+ * page table per sequence, the number of tables that name a page, and a ring of
+ * pages nobody uses.  All arrays are the caller's HOST memory; nothing here
+ * touches a device or keeps a pointer.
+ *   table, next_table  [max_batch, max_pages], -1 = no page yet, filled from the front;
+ *   len, next_len      [max_batch] tokens per sequence
+ *   refs               [n_pages]
+ *   free_ring          [n_pages], free_count pages from free_head on (wrapping round)
+ */
+typedef struct {
+  int32_t* table;
+  int32_t* next_table;
+  int64_t* len;
+  int64_t* next_len;
+  int32_t* refs;
+  int32_t* free_ring;
+  int64_t free_head, free_count;
+  int32_t max_batch, max_pages, n_pages, page_slots, stride, max_slots;
+} mtla_page_book;
+
+/* Pages for n_new[b] (NULL: one) more tokens of sequences 0 .. batch-1; `len` is left alone.
+ * Returns the number of table entries filled, -1 for an invalid argument, -2 when the pool does
+ * not hold enough free pages (nothing is changed then). */
+int32_t mtla_pages_reserve(mtla_page_book* book, const int32_t* n_new /*host*/, int32_t batch);
+
+/* The bookkeeping side of mtla_cache_fork_paged: builds next_table / next_len for sequences that
+ * continue src_index[b] (sequences from `batch` on become empty), writes the page every
+ * destination writes to next into fresh_pages[b] (a free one, or the source's own where the
+ * destination is its only continuation), counts references, returns pages nobody names to the
+ * ring and swaps the two tables and the two length arrays in `book`.  Returns 0, -1 or -2 as
+ * above (-1, -2: tables, lengths and counts are as they were). */
+int32_t mtla_pages_fork(mtla_page_book* book, const int32_t* src_index /*host*/, int32_t batch,
+                        int32_t* fresh_pages /*host*/);
+
+/*
  * mtla_set_shared_prefix -- decoding several beams over one stored copy of what
  * they have in common (the appendix on decoding with beams of 10-50: every
  * hypothesis of an utterance starts from the same tokens).  While set, the

@@ -33,6 +33,12 @@ class mtla_layer_weights(C.Structure):
     _fields_ += [("d_model", C.c_int32), ("ln_eps", C.c_float), ("rope_base", C.c_float)]
 
 
+class mtla_page_book(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("table", "next_table", "len", "next_len", "refs", "free_ring")]
+    _fields_ += [(n, C.c_int64) for n in ("free_head", "free_count")]
+    _fields_ += [(n, C.c_int32) for n in ("max_batch", "max_pages", "n_pages", "page_slots", "stride", "max_slots")]
+
+
 class MtlaError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -74,6 +80,8 @@ SIGNATURES = {
     "mtla_prefill_chunk_attn_paged": (C.c_int, [_ctx, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32,
                                                 _vp, _vp, _vp, _vp, _vp, _vp]),
     "mtla_prefill_step_paged": (C.c_int, [_ctx] + [_vp] * 15 + [_i32] * 3 + [_vp] * 5),
+    "mtla_pages_reserve": (_i32, [C.POINTER(mtla_page_book), _vp, _i32]),
+    "mtla_pages_fork": (_i32, [C.POINTER(mtla_page_book), _vp, _i32, _vp]),
     "mtla_cache_fork_paged": (C.c_int, [_ctx] + [_vp] * 7 + [_i32] + [_vp] * 5),
     "mtla_workspace_bytes": (_sz, [_ctx]),
     "mtla_prefill_workspace_bytes": (_sz, [_ctx, _i32, _i32]),

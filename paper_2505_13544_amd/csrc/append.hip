@@ -602,7 +602,8 @@ __global__ __launch_bounds__(kBlock) void reorder_kernel(ReorderArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const size_t j = i + u * step;
-      if (j < n_c + n_k) v[u] = j < n_c ? sc[j] : sk[j - n_c];
+      const size_t jj = j < n_c + n_k ? j : n_c + n_k - 1;  // past the end: read and dropped (a guarded read sends v to scratch)
+      v[u] = jj < n_c ? sc[jj] : sk[jj - n_c];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -670,7 +671,8 @@ __global__ __launch_bounds__(kBlock) void fork_paged_kernel(ForkArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const size_t j = i + (size_t)u * step;
-      if (j < n_c + n_k) v[u] = j < n_c ? sc[j] : sk[j - n_c];
+      const size_t jj = j < n_c + n_k ? j : n_c + n_k - 1;  // past the end: read and dropped (a guarded read sends v to scratch)
+      v[u] = jj < n_c ? sc[jj] : sk[jj - n_c];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {

@@ -165,6 +165,33 @@ class Session:
         return self.ctx.device_status(self.workspace, self.stream)
 
 
+class _HostInts:
+    """Small integer arrays that a kernel reads out of pinned host memory (132 beams: 1 KB, one trip over the link in the
+    kernel instead of a copy that the kernel would have to wait for).  Arrays are handed out in turn from two
+    halves of one buffer; a half is used again only once the event recorded behind its last array has passed."""
+    PER_HALF = 32
+
+    def __init__(self, n: int, device):
+        self.n, self.device = n, device
+        self.buf = torch.empty(2 * self.PER_HALF * n, dtype=torch.int32, pin_memory=True)
+        self.host, self.addr = self.buf.numpy(), self.buf.data_ptr()
+        self.at, self.done = 0, [None, None]
+
+    def next(self, n: int):
+        """A host view of n integers (n <= the size given) and its address."""
+        i = self.at
+        half, first = divmod(i, self.PER_HALF)
+        if first == 0:
+            # everything that read the other half has been enqueued by now
+            self.done[1 - half] = torch.cuda.Event()
+            self.done[1 - half].record(torch.cuda.current_stream(self.device))
+            if self.done[half] is not None:
+                self.done[half].synchronize()
+        self.at = (i + 1) % (2 * self.PER_HALF)
+        lo = i * self.n
+        return self.host[lo:lo + n], self.addr + 4 * lo
+
+
 class PagedSession:
     """Session over paged slot storage: one pool of pages, a page table per sequence, and the bookkeeping of
     who refers to which page.  That bookkeeping is memory management, done here on the host (the lengths are
@@ -198,11 +225,21 @@ class PagedSession:
         self.workspace = torch.empty(self.ctx.workspace_bytes(), dtype=torch.uint8, device=dev)
         self.ctx.workspace_init(self.workspace, self.stream)
         self.hyp_A = self.hyp_a = self.hyp_G = self.w_uk = self.w_uv = None
-        # host side: table (-1 = no page yet), lengths, reference counts, free pages (handed out in `page_order`)
+        # host side (kept by the library's page bookkeeping): table (-1 = no page yet), lengths, reference counts, and the
+        # free pages, handed out in `page_order`
         self.h_table = np.full((max_batch, self.max_pages), -1, np.int32)
         self.h_len = np.zeros(max_batch, np.int64)
+        self._h_next = [np.empty_like(self.h_table), np.empty_like(self.h_len)]
         self.refs = np.zeros(n_pages, np.int32)
-        self.free = list(range(n_pages)) if page_order is None else [int(p) for p in page_order]
+        self._ring = np.ascontiguousarray(np.arange(n_pages) if page_order is None else page_order, dtype=np.int32)
+        n_free = len(self._ring)
+        if n_free < n_pages:
+            self._ring = np.concatenate([self._ring, np.zeros(n_pages - n_free, np.int32)])
+        at = lambda x: x.ctypes.data
+        self._book = B.mtla_page_book(at(self.h_table), at(self._h_next[0]), at(self.h_len), at(self._h_next[1]), at(self.refs),
+                                      at(self._ring), 0, n_free, max_batch, self.max_pages, n_pages, page_slots, stride,
+                                      max_slots)
+        self._picks = _HostInts(2 * max_batch, dev)
         self._alt = None
 
     @property
@@ -212,35 +249,40 @@ class PagedSession:
     set_weights = Session.set_weights
 
     # ---- pages
+    @property
+    def free(self) -> np.ndarray:
+        """The pages nobody uses, in the order they will be handed out."""
+        k = self._book
+        return self._ring[(k.free_head + np.arange(k.free_count)) % self.n_pages]
+
     def _alloc(self) -> int:
-        if not self.free:
+        k = self._book
+        if not k.free_count:
             raise RuntimeError("page pool exhausted")
-        p = self.free.pop(0)
+        p = int(self._ring[k.free_head])
+        k.free_head, k.free_count = (k.free_head + 1) % self.n_pages, k.free_count - 1
         self.refs[p] = 1
         return p
 
-    def _release(self, p: int):
-        self.refs[p] -= 1
-        assert self.refs[p] >= 0
-        if self.refs[p] == 0:
-            self.free.append(int(p))
+    def _check_pages(self, got: int) -> int:
+        if got == -2:
+            raise RuntimeError("page pool exhausted")
+        if got < 0:
+            raise IndexError("sequence or source index out of range")
+        return got
 
     def reserve(self, n_new):
         """Pages for n_new[b] more tokens of every sequence, ahead of time (a caller that replays steps as a graph
         reserves once and then steps with reserve=False)."""
-        self._reserve(n_new)
+        self._reserve(len(n_new), n_new)
 
-    def _reserve(self, n_new):
-        """Pages for n_new[b] more tokens of every sequence; uploads the table if it changed."""
-        changed = False
-        for b, n in enumerate(n_new):
-            need = -(-(-(-(int(self.h_len[b]) + int(n)) // self.stride)) // self.page_slots)
-            for k in range(min(need, self.max_pages)):
-                if self.h_table[b, k] < 0:
-                    self.h_table[b, k] = self._alloc()
-                    changed = True
-        if changed:
-            self.table.copy_(torch.from_numpy(self.h_table).to(self.device))
+    def _reserve(self, batch, n_new=None):
+        """Pages for n_new[b] (None: one) more tokens of the first `batch` sequences; uploads the table if it changed."""
+        n = None if n_new is None else np.ascontiguousarray(n_new, dtype=np.int32)
+        if self._check_pages(B.lib.mtla_pages_reserve(self._book, None if n is None else n.ctypes.data, batch)):
+            staged = torch.empty(self.h_table.shape, dtype=torch.int32, pin_memory=True)
+            staged.numpy()[:] = self.h_table
+            self.table.copy_(staged, non_blocking=True)
 
     def pages_in_use(self) -> int:
         return int((self.refs > 0).sum())
@@ -257,7 +299,7 @@ class PagedSession:
         """n_new: host integers (list / array) or None for c_new.shape[1] tokens everywhere."""
         batch, n_max = c_new.shape[0], c_new.shape[1]
         n_host = [n_max] * batch if n_new is None else [int(x) for x in n_new]
-        self._reserve(n_host)
+        self._reserve(batch, n_host)
         n_dev = None if n_new is None else torch.tensor(n_host, dtype=torch.int32, device=self.device)
         self.ctx.cache_append_paged(self.pool_c, self.pool_kr, self.tail_c, self.seq_len, self.table, c_new, kr_new, n_dev,
                                     n_max, batch, self.hyp_A, self.hyp_a, self.hyp_G, None, w_out, slot_out, self.workspace,
@@ -271,7 +313,7 @@ class PagedSession:
     def step(self, c_new, kr_new, q, q_rope, *, out=None, out_latent=None, lse=None, reserve=True):
         batch = q.shape[0]
         if reserve:
-            self._reserve([1] * batch)
+            self._reserve(batch)
         self.ctx.decode_step_paged(self.pool_c, self.pool_kr, self.tail_c, self.seq_len, self.table, c_new, kr_new,
                                    self.hyp_A, self.hyp_a, self.hyp_G, q, q_rope, self.w_uk,
                                    self.w_uv if out is not None else None, batch, out, out_latent, lse, self.workspace,
@@ -281,7 +323,7 @@ class PagedSession:
     def prefill_chunk(self, q, q_rope, c, kr, *, out, max_past_slots: int, n_new=None, w_out=None):
         batch, T = c.shape[0], c.shape[1]
         n_host = [T] * batch if n_new is None else [int(x) for x in n_new]
-        self._reserve(n_host)
+        self._reserve(batch, n_host)
         n_dev = None if n_new is None else torch.tensor(n_host, dtype=torch.int32, device=self.device)
         scratch = torch.empty(self.ctx.prefill_step_scratch_bytes(batch, T, max_past_slots), dtype=torch.uint8,
                               device=self.device)
@@ -295,37 +337,16 @@ class PagedSession:
         """Beam reordering: sequence b continues what was sequence src_index[b] (host integers).  Complete pages are
         shared; every continuation gets a page of its own for the page being written to -- the source's own, taken
         over, when it is the source's only continuation.  Sequences nobody continues give their pages back."""
-        src_index = [int(x) for x in src_index]
         batch = len(src_index)
         if self._alt is None:
             self._alt = [torch.zeros_like(self.table), torch.empty_like(self.tail_c), torch.zeros_like(self.seq_len)]
-        uses = {s: src_index.count(s) for s in set(src_index)}
-        new_table = np.full_like(self.h_table, -1)
-        new_len = np.zeros_like(self.h_len)
-        fresh = np.zeros(batch, np.int32)
-        for b, s in enumerate(src_index):
-            nxt = min(int(self.h_len[s]) // self.stride, self.max_slots - 1)
-            pw = nxt // self.page_slots
-            new_table[b, :pw] = self.h_table[s, :pw]
-            for p in new_table[b, :pw]:
-                self.refs[p] += 1
-            own = int(self.h_table[s, pw])
-            if uses[s] == 1 and own >= 0:     # take the source's page over
-                self.refs[own] += 1
-                fresh[b] = own
-            else:
-                fresh[b] = self._alloc()
-            new_table[b, pw] = fresh[b]
-            new_len[b] = self.h_len[s]
-        self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len,
-                                  torch.tensor(src_index, dtype=torch.int32, device=self.device),
-                                  torch.from_numpy(fresh).to(self.device), batch, self._alt[0], self._alt[1], self._alt[2],
-                                  self.workspace, self.stream)
-        for b in range(self.max_batch):       # the old sequences let go of their pages
-            for p in self.h_table[b]:
-                if p >= 0:
-                    self._release(int(p))
-        self.h_table, self.h_len = new_table, new_len
+        host, where = self._picks.next(2 * batch)   # sources, then the pages they will write to; the kernel reads them there
+        host[:batch] = src_index.cpu() if isinstance(src_index, torch.Tensor) else src_index
+        self._check_pages(B.lib.mtla_pages_fork(self._book, where, batch, where + 4 * batch))
+        self.h_table, self._h_next[0] = self._h_next[0], self.h_table
+        self.h_len, self._h_next[1] = self._h_next[1], self.h_len
+        self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len, where, where + 4 * batch,
+                                  batch, self._alt[0], self._alt[1], self._alt[2], self.workspace, self.stream)
         cur = [self.table, self.tail_c, self.seq_len]
         self.table, self.tail_c, self.seq_len = self._alt
         self._alt = cur
