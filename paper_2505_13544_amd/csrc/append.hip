@@ -9,6 +9,7 @@
 // the matrix cores (append_bulk_mfma_kernel, bf16 storage) or one workgroup per touched slot
 // (append_kernel, any storage), and a second tiny kernel advances seq_len once every workgroup has
 // read the old value.
+#include "absorb_f32.h"
 #include "absorb_mfma.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -120,7 +121,7 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
     cel[i] = e < r ? to_f32(crow[e]) : 0.f;
   }
   Chunk8<T> krv;
-  if (tid < dR / 8) krv.load(reinterpret_cast<const T*>(a.kr_new) + (size_t)b * dR + 8 * tid);
+  krv.load(reinterpret_cast<const T*>(a.kr_new) + (size_t)b * dR + 8 * (tid < dR / 8 ? tid : 0));  // stored by the first dR / 8 threads
   const bool ln = sizeof(TC) == 4 && a.ln_eps > 0.f;  // whole-layer call: normalise the unrounded latent first
   // [r] the latent as fp32 (normalised in the whole-layer call): the hyper-network's rows read it from
   // here instead of every thread holding its own copy of the pieces it needs (at r = 512 that copy was 64
@@ -274,6 +275,20 @@ __global__ __launch_bounds__(kBlock, sizeof(TC) == 4 ? 4 : 5) void decode_front_
   const int i = blk - ap.batch;
   const int bx = i % gx, rest = i / gx;
   absorb_mfma_block<KK, sizeof(TC) == 4>(ab, bx, rest % gy, rest / gy);  // the whole-layer call hands q, q^R and c over unrounded
+}
+
+// Front of an fp32 decode step, split the same way (the append as a launch of its own took 3.1 us and the absorption
+// behind it 5.0 us at 4 heads x 64, r = 64).
+template <int NCH, int DH4>
+__global__ __launch_bounds__(kBlock) void decode_front_f32_kernel(AppendArgs ap, AbsorbArgs ab, int gx, int gy) {
+  extern __shared__ float smem[];
+  const int blk = blockIdx.x;
+  if (blk < ap.batch) {
+    append_step_block<float, NCH>(ap, blk, smem);
+    return;
+  }
+  const int i = blk - ap.batch, rest = i / gx;
+  absorb_f32_block<DH4>(ab, i % gx, rest % gy, rest / gy, smem);
 }
 
 // One slot of a bulk append: tokens [t_lo, t_hi) of the call fold into `slot` of sequence b.
@@ -735,6 +750,26 @@ hipError_t launch_decode_front(const AppendArgs& ap, const AbsorbArgs& ab, hipSt
   MTLA_FRONT(4, 1) MTLA_FRONT(4, 2) MTLA_FRONT(4, 4)
   MTLA_FRONT(8, 1) MTLA_FRONT(8, 2) MTLA_FRONT(8, 4)
   MTLA_FRONT(16, 1) MTLA_FRONT(16, 2) MTLA_FRONT(16, 4)
+#undef MTLA_FRONT
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_decode_front_f32(const AppendArgs& ap, const AbsorbArgs& ab, hipStream_t st) {
+  const int gx = ab.r / 64 + 1, gy = ab.n_heads, gz = (ab.rows + kFrontRows - 1) / kFrontRows;
+  const dim3 grid(ap.batch + gx * gy * gz), block(kBlock);
+  const size_t append_f = (size_t)ap.d_hyper + 4 + 8 + ap.r, absorb_f = (size_t)kFrontRows * ab.d_head;
+  const size_t smem = (append_f > absorb_f ? append_f : absorb_f) * sizeof(float);
+#define MTLA_FRONT(N)                                                                                           \
+  if (ap.r == 32 * N) {                                                                                         \
+    switch (ab.d_head / 32) {                                                                                   \
+      case 1: hipLaunchKernelGGL((decode_front_f32_kernel<N, 2>), grid, block, smem, st, ap, ab, gx, gy); break;   \
+      case 2: hipLaunchKernelGGL((decode_front_f32_kernel<N, 4>), grid, block, smem, st, ap, ab, gx, gy); break;   \
+      case 4: hipLaunchKernelGGL((decode_front_f32_kernel<N, 8>), grid, block, smem, st, ap, ab, gx, gy); break;   \
+      default: hipLaunchKernelGGL((decode_front_f32_kernel<N, 0>), grid, block, smem, st, ap, ab, gx, gy); break;  \
+    }                                                                                                           \
+    return hipGetLastError();                                                                                   \
+  }
+  MTLA_FRONT(2) MTLA_FRONT(4) MTLA_FRONT(8) MTLA_FRONT(16)
 #undef MTLA_FRONT
   return hipErrorInvalidValue;
 }

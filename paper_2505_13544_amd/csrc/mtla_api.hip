@@ -87,6 +87,10 @@ PrefillLayout prefill_layout(const mtla_ctx* c, size_t rows) {
                         align_up(rows * g.d_rope * 2, 256);
     area = area > need ? area : need;
   }
+  if (g.dtype == MTLA_F32) {  // explicit keys and values in fp32
+    const size_t need = 2 * align_up(rows * nh * g.d_head * 4, 256);
+    area = area > need ? area : need;
+  }
   L.cprime = align_up(L.qcat + area, 256);
   L.part_o = align_up(L.cprime + rows * g.r * elem_size(g.dtype), 256);
   L.part_ml = align_up(L.part_o + rows * nh * g.r * 4, 256);
@@ -495,6 +499,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
   }
   if (ap && decode_front_supported(*ap, ab)) {  // append and absorb do not depend on each other: one launch
     if (!hip_ok(launch_decode_front(*ap, ab, st))) return MTLA_ERR_HIP;
+  } else if (ap && g.dtype == MTLA_F32) {
+    if (!hip_ok(launch_decode_front_f32(*ap, ab, st))) return MTLA_ERR_HIP;
   } else if (ap && ap->c_new_f32) {
     return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
   } else {
@@ -507,7 +513,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     ev.start = c->ev_start[c->prof_n];
     ev.stop = c->ev_stop[c->prof_n++];
   }
-  const hipError_t le = !use_mfma ? launch_attn_split(at, g.dtype, st, ev)
+  const hipError_t le = g.dtype == MTLA_F32 ? launch_attn_decode_f32(at, st, ev)
+                        : !use_mfma         ? launch_attn_split(at, g.dtype, st, ev)
                                   : (attn_cols_supported(at) ? launch_attn_cols(at, st, ev) : launch_attn_mfma(at, st, ev));
   if (!hip_ok(le)) return MTLA_ERR_HIP;
 
@@ -1321,8 +1328,39 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
       latent_only = false;
     }
   }
-  // the vector-ALU kernels (fp32 storage, or shapes the matrix-core kernels do not take) index a
-  // grid dimension by the row
+  if (g.dtype == MTLA_F32) {  // the un-absorbed form in fp32
+    ExplicitArgs ex;
+    ex.q = q;
+    ex.q_rope = q_rope;
+    ex.cprime = ws + L.cprime;
+    ex.kr = kr;
+    ex.w_uk = w_uk;
+    ex.w_uv = w_uv;
+    ex.seq_len = seq_lens;
+    ex.kx = ws + L.qcat;
+    ex.vx = ws + L.qcat + align_up(rows * g.n_heads * g.d_head * 4, 256);
+    ex.out = out;
+    ex.out_latent = out_latent;
+    ex.batch = batch;
+    ex.T = T;
+    ex.n_heads = g.n_heads;
+    ex.d_head = g.d_head;
+    ex.r = g.r;
+    ex.d_rope = g.d_rope;
+    ex.stride = g.stride;
+    ex.scale_log2 = c->scale * 1.4426950408889634f;
+    if (prefill_f32_supported(ex)) {
+      if (!hip_ok(launch_partial_states(ps, g.dtype, st))) return MTLA_ERR_HIP;
+      const bool timed = c->prof_n < (int)c->ev_start.size();
+      EventPair ev;
+      if (timed) {
+        ev.start = c->ev_start[c->prof_n];
+        ev.stop = c->ev_stop[c->prof_n++];
+      }
+      return hip_ok(launch_prefill_f32(ex, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
+    }
+  }
+  // the vector-ALU kernels (shapes the matrix-core kernels do not take) index a grid dimension by the row
   {
     CombineArgs probe;
     probe.r = g.r;

@@ -309,6 +309,12 @@ hipError_t launch_absorb(const AbsorbArgs& a, int dtype, hipStream_t st);
 // one-token append and matrix-core absorb of a decode step in a single launch (bf16 storage)
 bool decode_front_supported(const AppendArgs& ap, const AbsorbArgs& ab);
 hipError_t launch_decode_front(const AppendArgs& ap, const AbsorbArgs& ab, hipStream_t st);
+// the same for fp32 storage (batch of at most 65535 rows)
+hipError_t launch_decode_front_f32(const AppendArgs& ap, const AbsorbArgs& ab, hipStream_t st);
+// fp32 storage on the matrix cores: decode attention (static schedule), and the parallel form with explicit keys and values
+hipError_t launch_attn_decode_f32(const AttnArgs& a, hipStream_t st, const EventPair& ev = EventPair());
+bool prefill_f32_supported(const ExplicitArgs& a);
+hipError_t launch_prefill_f32(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 hipError_t launch_attn_split(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev = EventPair());
 // bf16 matrix-core variant of the split pass (decode addressing only)
 bool attn_mfma_supported(const AttnArgs& a);

@@ -11,6 +11,7 @@
 // contraction elements with one 16-byte load, which is also the MFMA operand
 // layout.  Every kernel issues all of its global loads before the first use:
 // at decode batch sizes these kernels are pure latency.
+#include "absorb_f32.h"
 #include "absorb_mfma.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -32,8 +33,15 @@ __global__ __launch_bounds__(kBlock) void absorb_mfma_kernel(AbsorbArgs a) {
   absorb_mfma_block<KK, QF32>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// absorb, vector ALU, fp32 result (MTLA_F32 storage, or bf16 storage feeding the
-// fp32 vector attention kernel).  grid = (ceil(E/256), n_heads, ceil(rows/8)).
+// absorb, fp32 storage: grid = (r/64 + 1, n_heads, ceil(rows/8)), body in absorb_f32.h
+template <int DH4>
+__global__ __launch_bounds__(kBlock) void absorb_f32_kernel(AbsorbArgs a) {
+  extern __shared__ float sq[];
+  absorb_f32_block<DH4>(a, blockIdx.x, blockIdx.y, blockIdx.z, sq);
+}
+
+// absorb, vector ALU, fp32 result (bf16 storage feeding the fp32 vector attention kernel).
+// grid = (ceil(E/256), n_heads, ceil(rows/8)).
 constexpr int kAbsorbRows = 8;
 template <typename T>
 __global__ __launch_bounds__(kBlock) void absorb_valu_kernel(AbsorbArgs a) {
@@ -325,13 +333,21 @@ hipError_t launch_absorb(const AbsorbArgs& a, int dtype, hipStream_t st) {
     }
     return hipGetLastError();
   }
+  if (dtype == 0) {
+    const dim3 grid(a.r / 64 + 1, a.n_heads, (a.rows + kFrontRows - 1) / kFrontRows);
+    const size_t smem = (size_t)kFrontRows * a.d_head * sizeof(float);
+    switch (a.d_head / 32) {
+      case 1: hipLaunchKernelGGL(absorb_f32_kernel<2>, grid, dim3(kBlock), smem, st, a); break;
+      case 2: hipLaunchKernelGGL(absorb_f32_kernel<4>, grid, dim3(kBlock), smem, st, a); break;
+      case 4: hipLaunchKernelGGL(absorb_f32_kernel<8>, grid, dim3(kBlock), smem, st, a); break;
+      default: hipLaunchKernelGGL(absorb_f32_kernel<0>, grid, dim3(kBlock), smem, st, a); break;
+    }
+    return hipGetLastError();
+  }
   const int E = a.r + a.d_rope;
   const dim3 grid((E + kBlock - 1) / kBlock, a.n_heads, (a.rows + kAbsorbRows - 1) / kAbsorbRows);
   const size_t smem = (size_t)kAbsorbRows * a.d_head * sizeof(float);
-  if (dtype == 0)
-    hipLaunchKernelGGL(absorb_valu_kernel<float>, grid, dim3(kBlock), smem, st, a);
-  else
-    hipLaunchKernelGGL(absorb_valu_kernel<bf16>, grid, dim3(kBlock), smem, st, a);
+  hipLaunchKernelGGL(absorb_valu_kernel<bf16>, grid, dim3(kBlock), smem, st, a);
   return hipGetLastError();
 }
 
