@@ -1,4 +1,5 @@
-"""ctypes binding of libmtla: the same names and arguments as include/mtla.h.
+"""Python binding of libmtla: the same names and arguments as include/mtla.h, through ctypes and, for the calls that a
+program makes over and over, through a native call path (csrc/pycall.cpp) that takes tensors as they are.
 
 Argument marshalling only -- every step of the path runs in the HIP kernels.
 Device buffers are passed as integer addresses (e.g. ``tensor.data_ptr()``)
@@ -117,6 +118,20 @@ for _name, (_res, _args) in SIGNATURES.items():
     _fn.restype, _fn.argtypes = _res, _args
 
 
+def _load_calls():
+    try:
+        from . import _mtla_call
+    except ImportError as e:
+        raise ImportError(f"the binding's native call path is missing beside {LIB_PATH}: build it with "
+                          "`python -m paper_2505_13544_amd.build`") from e
+    for name in SIGNATURES:   # entry points it does not know stay with ctypes
+        _mtla_call.bind(name, C.cast(getattr(lib, name), C.c_void_p).value)
+    return _mtla_call
+
+
+calls = _load_calls()
+
+
 def _p(x) -> Optional[int]:
     """Address of a device/host buffer: None, int, or anything with data_ptr()."""
     if x is None:
@@ -144,11 +159,12 @@ class Context:
                                DTYPES[dtype] if isinstance(dtype, str) else dtype, softmax_scale, page_slots, n_pages)
         self._h = _ctx()
         _check(lib.mtla_create(C.byref(self.cfg), C.byref(self._h)), "mtla_create")
+        self._ptr = self._h.value
 
     def close(self):
         if getattr(self, "_h", None):
             lib.mtla_destroy(self._h)
-            self._h = None
+            self._h = self._ptr = None
 
     __del__ = close
 
@@ -200,33 +216,26 @@ class Context:
     def cache_append_status(self, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, n_new, n_new_max,
                             batch, hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace,
                             stream=None) -> int:
-        return lib.mtla_cache_append(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(c_new),
-                                     _p(kr_new), _p(n_new), n_new_max, batch, _p(hyp_A), _p(hyp_a),
-                                     _p(hyp_G), _p(w_override), _p(w_out), _p(slot_out), _p(workspace),
-                                     _p(stream))
+        return calls.mtla_cache_append(self._ptr, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, n_new, n_new_max, batch,
+                                       hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace, stream)
 
     def decode_attn_status(self, q, q_rope, w_uk, w_uv, cache_c, cache_kr, seq_len, batch, out,
                            out_latent, lse, workspace, stream=None) -> int:
-        return lib.mtla_decode_attn(self._h, _p(q), _p(q_rope), _p(w_uk), _p(w_uv), _p(cache_c),
-                                    _p(cache_kr), _p(seq_len), batch, _p(out), _p(out_latent), _p(lse),
-                                    _p(workspace), _p(stream))
+        return calls.mtla_decode_attn(self._ptr, q, q_rope, w_uk, w_uv, cache_c, cache_kr, seq_len, batch, out, out_latent,
+                                      lse, workspace, stream)
 
     def probe_stream_read(self, buf, nbytes: int, workspace, stream=None):
         _check(lib.mtla_probe_stream_read(self._h, _p(buf), nbytes, _p(workspace), _p(stream)), "mtla_probe_stream_read")
 
     def decode_step_status(self, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, hyp_A, hyp_a, hyp_G, q,
                            q_rope, w_uk, w_uv, batch, out, out_latent, lse, workspace, stream=None) -> int:
-        return lib.mtla_decode_step(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(c_new),
-                                    _p(kr_new), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(q), _p(q_rope), _p(w_uk),
-                                    _p(w_uv), batch, _p(out), _p(out_latent), _p(lse), _p(workspace),
-                                    _p(stream))
+        return calls.mtla_decode_step(self._ptr, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, hyp_A, hyp_a, hyp_G, q,
+                                      q_rope, w_uk, w_uv, batch, out, out_latent, lse, workspace, stream)
 
     def decode_step_static_status(self, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, hyp_A, hyp_a, hyp_G, q,
                                   q_rope, w_uk, w_uv, batch, out, out_latent, lse, device_status, stream=None) -> int:
-        return lib.mtla_decode_step_static(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(c_new),
-                                           _p(kr_new), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(q), _p(q_rope), _p(w_uk),
-                                           _p(w_uv), batch, _p(out), _p(out_latent), _p(lse), _p(device_status),
-                                           _p(stream))
+        return calls.mtla_decode_step_static(self._ptr, cache_c, cache_kr, tail_c, seq_len, c_new, kr_new, hyp_A, hyp_a,
+                                             hyp_G, q, q_rope, w_uk, w_uv, batch, out, out_latent, lse, device_status, stream)
 
     def decode_step_static(self, *a, **k):
         _check(self.decode_step_static_status(*a, **k), "mtla_decode_step_static")
@@ -234,44 +243,39 @@ class Context:
     # paged storage: the same calls with the page table behind the state arguments
     def cache_append_paged_status(self, cache_c, cache_kr, tail_c, seq_len, page_table, c_new, kr_new, n_new, n_new_max,
                                   batch, hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace, stream=None) -> int:
-        return lib.mtla_cache_append_paged(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(page_table),
-                                           _p(c_new), _p(kr_new), _p(n_new), n_new_max, batch, _p(hyp_A), _p(hyp_a),
-                                           _p(hyp_G), _p(w_override), _p(w_out), _p(slot_out), _p(workspace), _p(stream))
+        return calls.mtla_cache_append_paged(self._ptr, cache_c, cache_kr, tail_c, seq_len, page_table, c_new, kr_new, n_new,
+                                             n_new_max, batch, hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace,
+                                             stream)
 
     def decode_attn_paged_status(self, q, q_rope, w_uk, w_uv, cache_c, cache_kr, seq_len, page_table, batch, out,
                                  out_latent, lse, workspace, stream=None) -> int:
-        return lib.mtla_decode_attn_paged(self._h, _p(q), _p(q_rope), _p(w_uk), _p(w_uv), _p(cache_c), _p(cache_kr),
-                                          _p(seq_len), _p(page_table), batch, _p(out), _p(out_latent), _p(lse),
-                                          _p(workspace), _p(stream))
+        return calls.mtla_decode_attn_paged(self._ptr, q, q_rope, w_uk, w_uv, cache_c, cache_kr, seq_len, page_table, batch,
+                                            out, out_latent, lse, workspace, stream)
 
     def decode_step_paged_status(self, cache_c, cache_kr, tail_c, seq_len, page_table, c_new, kr_new, hyp_A, hyp_a, hyp_G,
                                  q, q_rope, w_uk, w_uv, batch, out, out_latent, lse, workspace, stream=None) -> int:
-        return lib.mtla_decode_step_paged(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(page_table),
-                                          _p(c_new), _p(kr_new), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(q), _p(q_rope),
-                                          _p(w_uk), _p(w_uv), batch, _p(out), _p(out_latent), _p(lse), _p(workspace),
-                                          _p(stream))
+        return calls.mtla_decode_step_paged(self._ptr, cache_c, cache_kr, tail_c, seq_len, page_table, c_new, kr_new, hyp_A,
+                                            hyp_a, hyp_G, q, q_rope, w_uk, w_uv, batch, out, out_latent, lse, workspace,
+                                            stream)
 
     def prefill_chunk_attn_paged_status(self, cache_c, cache_kr, tail_prev, pos0, page_table, q, q_rope, c, kr, w, n_new,
                                         batch, T, max_past_slots, w_uk, w_uv, out, chunk_workspace, workspace,
                                         stream=None) -> int:
-        return lib.mtla_prefill_chunk_attn_paged(self._h, _p(cache_c), _p(cache_kr), _p(tail_prev), _p(pos0), _p(page_table),
-                                                 _p(q), _p(q_rope), _p(c), _p(kr), _p(w), _p(n_new), batch, T,
-                                                 max_past_slots, _p(w_uk), _p(w_uv), _p(out), _p(chunk_workspace),
-                                                 _p(workspace), _p(stream))
+        return calls.mtla_prefill_chunk_attn_paged(self._ptr, cache_c, cache_kr, tail_prev, pos0, page_table, q, q_rope, c,
+                                                   kr, w, n_new, batch, T, max_past_slots, w_uk, w_uv, out, chunk_workspace,
+                                                   workspace, stream)
 
     def prefill_step_paged_status(self, cache_c, cache_kr, tail_c, seq_len, page_table, q, q_rope, c, kr, n_new, hyp_A,
                                   hyp_a, hyp_G, w_uk, w_uv, batch, T, max_past_slots, out, w_out, scratch, workspace,
                                   stream=None) -> int:
-        return lib.mtla_prefill_step_paged(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(page_table),
-                                           _p(q), _p(q_rope), _p(c), _p(kr), _p(n_new), _p(hyp_A), _p(hyp_a), _p(hyp_G),
-                                           _p(w_uk), _p(w_uv), batch, T, max_past_slots, _p(out), _p(w_out), _p(scratch),
-                                           _p(workspace), _p(stream))
+        return calls.mtla_prefill_step_paged(self._ptr, cache_c, cache_kr, tail_c, seq_len, page_table, q, q_rope, c, kr,
+                                             n_new, hyp_A, hyp_a, hyp_G, w_uk, w_uv, batch, T, max_past_slots, out, w_out,
+                                             scratch, workspace, stream)
 
     def cache_fork_paged_status(self, cache_c, cache_kr, src_table, src_tail_c, src_seq_len, src_index, fresh_pages, batch,
                                 dst_table, dst_tail_c, dst_seq_len, workspace, stream=None) -> int:
-        return lib.mtla_cache_fork_paged(self._h, _p(cache_c), _p(cache_kr), _p(src_table), _p(src_tail_c), _p(src_seq_len),
-                                         _p(src_index), _p(fresh_pages), batch, _p(dst_table), _p(dst_tail_c),
-                                         _p(dst_seq_len), _p(workspace), _p(stream))
+        return calls.mtla_cache_fork_paged(self._ptr, cache_c, cache_kr, src_table, src_tail_c, src_seq_len, src_index,
+                                           fresh_pages, batch, dst_table, dst_tail_c, dst_seq_len, workspace, stream)
 
     def cache_append_paged(self, *a, **k): _check(self.cache_append_paged_status(*a, **k), "mtla_cache_append_paged")
     def decode_attn_paged(self, *a, **k): _check(self.decode_attn_paged_status(*a, **k), "mtla_decode_attn_paged")
@@ -281,18 +285,17 @@ class Context:
 
     def cache_reorder_status(self, src_cache_c, src_cache_kr, src_tail_c, src_seq_len, src_index, batch, dst_cache_c,
                              dst_cache_kr, dst_tail_c, dst_seq_len, workspace, stream=None) -> int:
-        return lib.mtla_cache_reorder(self._h, _p(src_cache_c), _p(src_cache_kr), _p(src_tail_c), _p(src_seq_len),
-                                      _p(src_index), batch, _p(dst_cache_c), _p(dst_cache_kr), _p(dst_tail_c),
-                                      _p(dst_seq_len), _p(workspace), _p(stream))
+        return calls.mtla_cache_reorder(self._ptr, src_cache_c, src_cache_kr, src_tail_c, src_seq_len, src_index, batch,
+                                        dst_cache_c, dst_cache_kr, dst_tail_c, dst_seq_len, workspace, stream)
 
     def cache_reorder(self, *a, **k):
         _check(self.cache_reorder_status(*a, **k), "mtla_cache_reorder")
 
     def cache_reorder_from_status(self, src_cache_c, src_cache_kr, src_tail_c, src_seq_len, src_index, batch, first_slot,
                                   dst_cache_c, dst_cache_kr, dst_tail_c, dst_seq_len, workspace, stream=None) -> int:
-        return lib.mtla_cache_reorder_from(self._h, _p(src_cache_c), _p(src_cache_kr), _p(src_tail_c), _p(src_seq_len),
-                                           _p(src_index), batch, first_slot, _p(dst_cache_c), _p(dst_cache_kr),
-                                           _p(dst_tail_c), _p(dst_seq_len), _p(workspace), _p(stream))
+        return calls.mtla_cache_reorder_from(self._ptr, src_cache_c, src_cache_kr, src_tail_c, src_seq_len, src_index, batch,
+                                             first_slot, dst_cache_c, dst_cache_kr, dst_tail_c, dst_seq_len, workspace,
+                                             stream)
 
     def cache_reorder_from(self, *a, **k):
         _check(self.cache_reorder_from_status(*a, **k), "mtla_cache_reorder_from")
@@ -303,33 +306,24 @@ class Context:
     def layer_decode_step_status(self, lw, cache_c, cache_kr, tail_c, seq_len, x, hyp_A, hyp_a, hyp_G, w_uk, w_uv,
                                  batch, y, out, scratch, workspace, stream=None) -> int:
         """lw: dict with w_q, w_qr, w_r, w_kr, w_o, d_model and optionally ln_gamma, ln_beta, ln_eps, rope_base."""
-        st = mtla_layer_weights(_p(lw["w_q"]), _p(lw["w_qr"]), _p(lw["w_r"]), _p(lw["w_kr"]), _p(lw["w_o"]),
-                                _p(lw.get("ln_gamma")), _p(lw.get("ln_beta")), lw["d_model"],
-                                lw.get("ln_eps", 0.0), lw.get("rope_base", 0.0))
-        return lib.mtla_layer_decode_step(self._h, C.byref(st), _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len),
-                                          _p(x), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(w_uk), _p(w_uv), batch, _p(y),
-                                          _p(out), _p(scratch), _p(workspace), _p(stream))
+        return calls.mtla_layer_decode_step(self._ptr, lw, cache_c, cache_kr, tail_c, seq_len, x, hyp_A, hyp_a, hyp_G, w_uk,
+                                            w_uv, batch, y, out, scratch, workspace, stream)
 
     def layer_prefill_scratch_bytes(self, d_model: int, batch: int, T: int, max_past_slots: int) -> int:
         return lib.mtla_layer_prefill_scratch_bytes(self._h, d_model, batch, T, max_past_slots)
 
     def layer_prefill_status(self, lw, cache_c, cache_kr, tail_c, seq_len, x, n_new, hyp_A, hyp_a, hyp_G, w_uk, w_uv,
                              batch, T, max_past_slots, y, scratch, workspace, stream=None) -> int:
-        st = mtla_layer_weights(_p(lw["w_q"]), _p(lw["w_qr"]), _p(lw["w_r"]), _p(lw["w_kr"]), _p(lw["w_o"]),
-                                _p(lw.get("ln_gamma")), _p(lw.get("ln_beta")), lw["d_model"],
-                                lw.get("ln_eps", 0.0), lw.get("rope_base", 0.0))
-        return lib.mtla_layer_prefill(self._h, C.byref(st), _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(x),
-                                      _p(n_new), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(w_uk), _p(w_uv), batch, T,
-                                      max_past_slots, _p(y), _p(scratch), _p(workspace), _p(stream))
+        return calls.mtla_layer_prefill(self._ptr, lw, cache_c, cache_kr, tail_c, seq_len, x, n_new, hyp_A, hyp_a, hyp_G,
+                                        w_uk, w_uv, batch, T, max_past_slots, y, scratch, workspace, stream)
 
     def layer_prefill(self, *a, **k):
         _check(self.layer_prefill_status(*a, **k), "mtla_layer_prefill")
 
     def prefill_attn_status(self, q, q_rope, c, kr, w, seq_lens, batch, T, w_uk, w_uv, out, out_latent,
                             prefill_workspace, stream=None) -> int:
-        return lib.mtla_prefill_attn(self._h, _p(q), _p(q_rope), _p(c), _p(kr), _p(w), _p(seq_lens),
-                                     batch, T, _p(w_uk), _p(w_uv), _p(out), _p(out_latent),
-                                     _p(prefill_workspace), _p(stream))
+        return calls.mtla_prefill_attn(self._ptr, q, q_rope, c, kr, w, seq_lens, batch, T, w_uk, w_uv, out, out_latent,
+                                       prefill_workspace, stream)
 
     def cache_append(self, *a, **k):
         _check(self.cache_append_status(*a, **k), "mtla_cache_append")
@@ -345,19 +339,16 @@ class Context:
 
     def prefill_step_status(self, cache_c, cache_kr, tail_c, seq_len, q, q_rope, c, kr, n_new, hyp_A, hyp_a, hyp_G,
                             w_uk, w_uv, batch, T, max_past_slots, out, w_out, scratch, workspace, stream=None) -> int:
-        return lib.mtla_prefill_step(self._h, _p(cache_c), _p(cache_kr), _p(tail_c), _p(seq_len), _p(q), _p(q_rope),
-                                     _p(c), _p(kr), _p(n_new), _p(hyp_A), _p(hyp_a), _p(hyp_G), _p(w_uk), _p(w_uv),
-                                     batch, T, max_past_slots, _p(out), _p(w_out), _p(scratch), _p(workspace),
-                                     _p(stream))
+        return calls.mtla_prefill_step(self._ptr, cache_c, cache_kr, tail_c, seq_len, q, q_rope, c, kr, n_new, hyp_A, hyp_a,
+                                       hyp_G, w_uk, w_uv, batch, T, max_past_slots, out, w_out, scratch, workspace, stream)
 
     def prefill_step(self, *a, **k):
         _check(self.prefill_step_status(*a, **k), "mtla_prefill_step")
 
     def prefill_chunk_attn_status(self, cache_c, cache_kr, tail_prev, pos0, q, q_rope, c, kr, w, n_new, batch, T,
                                   max_past_slots, w_uk, w_uv, out, chunk_workspace, workspace, stream=None) -> int:
-        return lib.mtla_prefill_chunk_attn(self._h, _p(cache_c), _p(cache_kr), _p(tail_prev), _p(pos0), _p(q),
-                                           _p(q_rope), _p(c), _p(kr), _p(w), _p(n_new), batch, T, max_past_slots,
-                                           _p(w_uk), _p(w_uv), _p(out), _p(chunk_workspace), _p(workspace), _p(stream))
+        return calls.mtla_prefill_chunk_attn(self._ptr, cache_c, cache_kr, tail_prev, pos0, q, q_rope, c, kr, w, n_new, batch,
+                                             T, max_past_slots, w_uk, w_uv, out, chunk_workspace, workspace, stream)
 
     def prefill_chunk_attn(self, *a, **k):
         _check(self.prefill_chunk_attn_status(*a, **k), "mtla_prefill_chunk_attn")

@@ -18,6 +18,20 @@ HIPCC_FLAGS = [
 ]
 
 
+PYCALL = os.path.join(HERE, "_mtla_call.so")  # native call path of the Python binding (host code, CPython API)
+
+
+def pycall_command() -> list:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    return (["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-unused-function",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", os.path.join(CSRC, "pycall.cpp")]
+            + [f"-isystem{d}" for d in cpp_extension.include_paths()] + [f"-I{sysconfig.get_paths()['include']}", "-o", PYCALL]
+            + [f"-L{d}" for d in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"])
+
+
 def hipcc() -> str:
     exe = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(exe):
@@ -26,7 +40,7 @@ def hipcc() -> str:
 
 
 def build_library(verbose: bool = True) -> str:
-    """Compile every HIP source into paper_2505_13544_amd/libmtla.so."""
+    """Compile every HIP source into paper_2505_13544_amd/libmtla.so, and the binding's native call path beside it."""
     objs = []
     obj_dir = os.path.join(HERE, "_build")
     os.makedirs(obj_dir, exist_ok=True)
@@ -38,13 +52,17 @@ def build_library(verbose: bool = True) -> str:
             print("[build]", " ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    cmd = pycall_command()
+    if verbose:
+        print("[build]", " ".join(cmd), flush=True)
+    procs.append(("pycall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if out.strip() and verbose:
             print(out)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     if verbose:
         print("[build]", " ".join(cmd), flush=True)

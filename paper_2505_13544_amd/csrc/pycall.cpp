@@ -1,0 +1,171 @@
+// Native call path of the Python binding: the library's entry points as Python functions that take tensors directly.
+//
+// A decode step passes nineteen arguments.  Turning tensors into addresses in Python and addresses into C values in
+// ctypes took 8 us of host time a call, more than the GPU needs for the step of a small model; here the same call costs
+// under 1 us.  A pointer argument is a tensor, an integer address, None (NULL), a buffer (a ctypes structure) or any
+// object with data_ptr(); the argument types come from the declarations in mtla.h.  The addresses of the functions are
+// handed in by the binding (bind), which has loaded the library: this module does not link against it.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <cstring>
+#include <exception>
+#include <tuple>
+#include <type_traits>
+#include <utility>
+
+#include "../../include/mtla.h"
+
+namespace {
+
+// What a call needs beyond its C arguments: storage for structures built from dicts, buffers to release.
+struct Hold {
+  mtla_layer_weights lw;
+  Py_buffer view;
+  bool has_view = false;
+  ~Hold() {
+    if (has_view) PyBuffer_Release(&view);
+  }
+};
+
+bool address(PyObject* o, Hold& hold, void*& out) {
+  if (o == Py_None) {
+    out = nullptr;
+    return true;
+  }
+  if (THPVariable_Check(o)) {
+    out = THPVariable_Unpack(o).data_ptr();
+    return true;
+  }
+  if (PyLong_Check(o)) {
+    out = PyLong_AsVoidPtr(o);
+    return !(out == nullptr && PyErr_Occurred());
+  }
+  if (PyObject_CheckBuffer(o) && !hold.has_view) {
+    if (PyObject_GetBuffer(o, &hold.view, PyBUF_SIMPLE) != 0) return false;
+    hold.has_view = true;
+    out = hold.view.buf;
+    return true;
+  }
+  PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);
+  if (!p) return false;
+  out = PyLong_AsVoidPtr(p);
+  Py_DECREF(p);
+  return !(out == nullptr && PyErr_Occurred());
+}
+
+bool weight(PyObject* d, const char* key, Hold& hold, const void*& out) {
+  PyObject* o = PyDict_GetItemString(d, key);
+  void* p = nullptr;
+  if (o && !address(o, hold, p)) return false;
+  out = p;
+  return true;
+}
+
+bool number(PyObject* d, const char* key, float& out) {
+  PyObject* o = PyDict_GetItemString(d, key);
+  out = 0.f;
+  if (!o || o == Py_None) return true;
+  out = (float)PyFloat_AsDouble(o);
+  return !PyErr_Occurred();
+}
+
+template <class T>
+bool convert(PyObject* o, Hold& hold, T& out) {
+  if constexpr (std::is_pointer_v<T>) {
+    if constexpr (std::is_same_v<T, const mtla_layer_weights*>) {
+      if (PyDict_Check(o)) {
+        mtla_layer_weights& w = hold.lw;
+        if (!weight(o, "w_q", hold, w.w_q) || !weight(o, "w_qr", hold, w.w_qr) || !weight(o, "w_r", hold, w.w_r) ||
+            !weight(o, "w_kr", hold, w.w_kr) || !weight(o, "w_o", hold, w.w_o) || !weight(o, "ln_gamma", hold, w.ln_gamma) ||
+            !weight(o, "ln_beta", hold, w.ln_beta) || !number(o, "ln_eps", w.ln_eps) || !number(o, "rope_base", w.rope_base))
+          return false;
+        PyObject* dm = PyDict_GetItemString(o, "d_model");
+        w.d_model = dm ? (int32_t)PyLong_AsLong(dm) : 0;
+        if (PyErr_Occurred()) return false;
+        out = &w;
+        return true;
+      }
+    }
+    void* p;
+    if (!address(o, hold, p)) return false;
+    out = reinterpret_cast<T>(p);
+    return true;
+  } else {
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) return false;
+    out = (T)v;
+    return true;
+  }
+}
+
+template <class R, class... A, size_t... I>
+PyObject* invoke(R (*fn)(A...), PyObject* const* args, Py_ssize_t n, const char* name, std::index_sequence<I...>) {
+  if (!fn) {
+    PyErr_Format(PyExc_RuntimeError, "%s: not bound", name);
+    return nullptr;
+  }
+  if (n != (Py_ssize_t)sizeof...(A)) {
+    PyErr_Format(PyExc_TypeError, "%s takes %d arguments, %d given", name, (int)sizeof...(A), (int)n);
+    return nullptr;
+  }
+  std::tuple<A...> v{};
+  Hold hold;
+  try {
+    if (!(convert(args[I], hold, std::get<I>(v)) && ...)) return nullptr;
+  } catch (const std::exception& e) {  // a tensor without storage
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
+  }
+  R rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = fn(std::get<I>(v)...);
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong((long)rc);
+}
+
+// One table row per entry point: its address once bound, and the Python function.
+#define ENTRY_POINTS(X)                                                                                              \
+  X(mtla_cache_append) X(mtla_decode_attn) X(mtla_decode_step) X(mtla_decode_step_static) X(mtla_cache_append_paged) \
+  X(mtla_decode_attn_paged) X(mtla_decode_step_paged) X(mtla_prefill_chunk_attn_paged) X(mtla_prefill_step_paged)    \
+  X(mtla_cache_fork_paged) X(mtla_prefill_attn) X(mtla_prefill_chunk_attn) X(mtla_prefill_step) X(mtla_cache_reorder) \
+  X(mtla_cache_reorder_from) X(mtla_layer_decode_step) X(mtla_layer_prefill) X(mtla_pages_reserve) X(mtla_pages_fork)
+
+#define DEFINE(NAME)                                                                                            \
+  decltype(&NAME) p_##NAME = nullptr;                                                                           \
+  template <class R, class... A>                                                                                \
+  PyObject* go_##NAME(R (*fn)(A...), PyObject* const* args, Py_ssize_t n) {                                     \
+    return invoke(fn, args, n, #NAME, std::index_sequence_for<A...>());                                         \
+  }                                                                                                             \
+  PyObject* py_##NAME(PyObject*, PyObject* const* args, Py_ssize_t n) { return go_##NAME(p_##NAME, args, n); }
+ENTRY_POINTS(DEFINE)
+#undef DEFINE
+
+// bind(name, address)
+PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (n != 2) return PyErr_Format(PyExc_TypeError, "bind(name, address)");
+  const char* name = PyUnicode_AsUTF8(args[0]);
+  void* at = PyLong_AsVoidPtr(args[1]);
+  if (!name || PyErr_Occurred()) return nullptr;
+#define SET(NAME)                                                          \
+  if (!strcmp(name, #NAME)) {                                              \
+    p_##NAME = reinterpret_cast<decltype(&NAME)>(at);                      \
+    Py_RETURN_TRUE;                                                        \
+  }
+  ENTRY_POINTS(SET)
+#undef SET
+  Py_RETURN_FALSE;
+}
+
+#define METHOD(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(py_##NAME)), METH_FASTCALL, nullptr},
+PyMethodDef methods[] = {
+    {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(bind)), METH_FASTCALL, nullptr},
+    ENTRY_POINTS(METHOD){nullptr, nullptr, 0, nullptr}};
+#undef METHOD
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_mtla_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__mtla_call(void) { return PyModule_Create(&module); }

@@ -20,6 +20,11 @@ def to_device(a: np.ndarray, dtype: str, device="cuda:0") -> torch.Tensor:
     return t if dtype == "f32" else t.to(torch.bfloat16)
 
 
+def _raw_stream(device: torch.device) -> int:
+    """The current stream of `device` as the library takes it (an address)."""
+    return torch._C._cuda_getCurrentRawStream(device.index if device.index is not None else torch.cuda.current_device())
+
+
 class Session:
     """One MTLA attention layer's device state plus the library calls."""
 
@@ -53,7 +58,7 @@ class Session:
 
     @property
     def stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return _raw_stream(self.device)
 
     def set_weights(self, *, hyp_A, hyp_G, w_uk, w_uv, hyp_a=None):
         up = lambda a: None if a is None else to_device(a, self.dtype, self.device)
@@ -76,10 +81,12 @@ class Session:
     def step(self, c_new: torch.Tensor, kr_new: torch.Tensor, q: torch.Tensor, q_rope: torch.Tensor, *,
              out=None, out_latent=None, lse=None):
         """One step of incremental inference: append the token of every sequence, then attend."""
-        batch = q.shape[0]
-        self.ctx.decode_step(self.cache_c, self.cache_kr, self.tail_c, self.seq_len, c_new, kr_new, self.hyp_A,
-                             self.hyp_a, self.hyp_G, q, q_rope, self.w_uk, self.w_uv if out is not None else None,
-                             batch, out, out_latent, lse, self.workspace, self.stream)
+        rc = B.calls.mtla_decode_step(self.ctx._ptr, self.cache_c, self.cache_kr, self.tail_c, self.seq_len, c_new, kr_new,
+                                      self.hyp_A, self.hyp_a, self.hyp_G, q, q_rope, self.w_uk,
+                                      self.w_uv if out is not None else None, len(q), out, out_latent, lse, self.workspace,
+                                      _raw_stream(self.device))
+        if rc:
+            raise B.MtlaError(rc, "mtla_decode_step")
 
     def step_static(self, c_new, kr_new, q, q_rope, *, status: torch.Tensor, out=None, out_latent=None, lse=None):
         """The same step with the library's static scratch instead of this session's workspace;
@@ -122,12 +129,15 @@ class Session:
 
     def layer_step(self, x: torch.Tensor, *, y: torch.Tensor, out=None):
         """One token per sequence through the whole attention layer: projections, step, W_O."""
-        batch = x.shape[0]
-        if self.layer_scratch is None or self.layer_scratch.numel() < self.ctx.layer_scratch_bytes(batch):
+        batch = len(x)
+        if self.layer_scratch is None or batch > self.layer_scratch_batch:
             self.layer_scratch = torch.empty(self.ctx.layer_scratch_bytes(batch), dtype=torch.uint8, device=self.device)
-        self.ctx.layer_decode_step(self.layer_w, self.cache_c, self.cache_kr, self.tail_c, self.seq_len, x, self.hyp_A,
-                                   self.hyp_a, self.hyp_G, self.w_uk, self.w_uv, batch, y, out, self.layer_scratch,
-                                   self.workspace, self.stream)
+            self.layer_scratch_batch = batch
+        rc = B.calls.mtla_layer_decode_step(self.ctx._ptr, self.layer_w, self.cache_c, self.cache_kr, self.tail_c, self.seq_len,
+                                            x, self.hyp_A, self.hyp_a, self.hyp_G, self.w_uk, self.w_uv, batch, y, out,
+                                            self.layer_scratch, self.workspace, _raw_stream(self.device))
+        if rc:
+            raise B.MtlaError(rc, "mtla_layer_decode_step")
 
     def layer_prefill(self, x: torch.Tensor, *, y: torch.Tensor, max_past_slots: int = 0, n_new=None):
         """T tokens per sequence through the whole attention layer in the parallel form, continuing from
@@ -244,7 +254,7 @@ class PagedSession:
 
     @property
     def stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return _raw_stream(self.device)
 
     set_weights = Session.set_weights
 
@@ -279,7 +289,7 @@ class PagedSession:
     def _reserve(self, batch, n_new=None):
         """Pages for n_new[b] (None: one) more tokens of the first `batch` sequences; uploads the table if it changed."""
         n = None if n_new is None else np.ascontiguousarray(n_new, dtype=np.int32)
-        if self._check_pages(B.lib.mtla_pages_reserve(self._book, None if n is None else n.ctypes.data, batch)):
+        if self._check_pages(B.calls.mtla_pages_reserve(self._book, None if n is None else n.ctypes.data, batch)):
             staged = torch.empty(self.h_table.shape, dtype=torch.int32, pin_memory=True)
             staged.numpy()[:] = self.h_table
             self.table.copy_(staged, non_blocking=True)
@@ -311,13 +321,15 @@ class PagedSession:
                                    self.seq_len, self.table, q.shape[0], out, out_latent, lse, self.workspace, self.stream)
 
     def step(self, c_new, kr_new, q, q_rope, *, out=None, out_latent=None, lse=None, reserve=True):
-        batch = q.shape[0]
+        batch = len(q)
         if reserve:
             self._reserve(batch)
-        self.ctx.decode_step_paged(self.pool_c, self.pool_kr, self.tail_c, self.seq_len, self.table, c_new, kr_new,
-                                   self.hyp_A, self.hyp_a, self.hyp_G, q, q_rope, self.w_uk,
-                                   self.w_uv if out is not None else None, batch, out, out_latent, lse, self.workspace,
-                                   self.stream)
+        rc = B.calls.mtla_decode_step_paged(self.ctx._ptr, self.pool_c, self.pool_kr, self.tail_c, self.seq_len, self.table,
+                                            c_new, kr_new, self.hyp_A, self.hyp_a, self.hyp_G, q, q_rope, self.w_uk,
+                                            self.w_uv if out is not None else None, batch, out, out_latent, lse,
+                                            self.workspace, _raw_stream(self.device))
+        if rc:
+            raise B.MtlaError(rc, "mtla_decode_step_paged")
         self.h_len[:batch] += 1
 
     def prefill_chunk(self, q, q_rope, c, kr, *, out, max_past_slots: int, n_new=None, w_out=None):
@@ -342,7 +354,7 @@ class PagedSession:
             self._alt = [torch.zeros_like(self.table), torch.empty_like(self.tail_c), torch.zeros_like(self.seq_len)]
         host, where = self._picks.next(2 * batch)   # sources, then the pages they will write to; the kernel reads them there
         host[:batch] = src_index.cpu() if isinstance(src_index, torch.Tensor) else src_index
-        self._check_pages(B.lib.mtla_pages_fork(self._book, where, batch, where + 4 * batch))
+        self._check_pages(B.calls.mtla_pages_fork(self._book, where, batch, where + 4 * batch))
         self.h_table, self._h_next[0] = self._h_next[0], self.h_table
         self.h_len, self._h_next[1] = self._h_next[1], self.h_len
         self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len, where, where + 4 * batch,
