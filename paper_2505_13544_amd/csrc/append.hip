@@ -79,14 +79,15 @@ struct Chunk8<bf16> {
 };
 template <>
 struct Chunk8<float> {
-  float4 lo, hi;
+  typedef float vec4 __attribute__((ext_vector_type(4)));  // (a float4 kept across the kernel's barriers ends up in scratch)
+  vec4 lo, hi;
   __device__ __forceinline__ void load(const float* p) {
-    lo = *reinterpret_cast<const float4*>(p);
-    hi = *reinterpret_cast<const float4*>(p + 4);
+    lo = *reinterpret_cast<const vec4*>(p);
+    hi = *reinterpret_cast<const vec4*>(p + 4);
   }
   __device__ __forceinline__ void store(float* p) const {
-    *reinterpret_cast<float4*>(p) = lo;
-    *reinterpret_cast<float4*>(p + 4) = hi;
+    *reinterpret_cast<vec4*>(p) = lo;
+    *reinterpret_cast<vec4*>(p + 4) = hi;
   }
   __device__ __forceinline__ void unpack(float (&o)[8]) const {
     o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w;
@@ -188,23 +189,35 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   }
   if (hyper) {
     // ---- Linear(c), rows y < 64 from the registers, further rows (dy > 64) straight from memory
-    for (int y0 = 0; y0 < dy; y0 += kRowsPerPass) {
-      const int yy = y0 + y;
-      float dot = 0.f;
-      if (yy < dy) {
+    auto reduce = [&](float dot, int yy, float bia) {
+      dot += __shfl_xor(dot, 1, kWave);
+      dot += __shfl_xor(dot, 2, kWave);
+      if (yy < dy && q == 0) sg[yy] = dot + bia;
+    };
+    float dot = 0.f;
+    if (y < dy) {
 #pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        float av[8], cv[8];
+        ach[i].unpack(av);
+        load8(sc_row + 8 * (q + i * kTPR), cv);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dot += av[j] * cv[j];
+      }
+    }
+    reduce(dot, y, bias);
+    for (int yy = y + kRowsPerPass; yy - y < dy; yy += kRowsPerPass) {
+      dot = 0.f;
+      if (yy < dy) {
         for (int i = 0; i < NCH; ++i) {
           float av[8], cv[8];
-          if (y0 == 0) ach[i].unpack(av);
-          else load8(A + (size_t)yy * r + 8 * (q + i * kTPR), av);
+          load8(A + (size_t)yy * r + 8 * (q + i * kTPR), av);
           load8(sc_row + 8 * (q + i * kTPR), cv);
 #pragma unroll
           for (int j = 0; j < 8; ++j) dot += av[j] * cv[j];
         }
       }
-      dot += __shfl_xor(dot, 1, kWave);
-      dot += __shfl_xor(dot, 2, kWave);
-      if (yy < dy && q == 0) sg[yy] = dot + (y0 == 0 ? bias : (ha ? to_f32(ha[yy]) : 0.f));
+      reduce(dot, yy, yy < dy && ha ? to_f32(ha[yy]) : 0.f);
     }
   }
   __syncthreads();
@@ -585,6 +598,9 @@ __global__ __launch_bounds__(kBlock) void stream_read_kernel(const uint4* __rest
 
 }  // namespace
 
+// 16 bytes in registers.  (An array of HIP's uint4 kept across a loop body's branches goes to scratch or LDS.)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // Beam reordering of the sequence state: a gather of whole sequences.  Workgroup (x, b) copies every
 // gridDim.x-th run of 256 16-byte pieces of the live rows of source sequence src_index[b] (four
 // loads in flight per thread); workgroup (0, b) also copies the tail shadow and the length.
@@ -599,10 +615,10 @@ __global__ __launch_bounds__(kBlock) void reorder_kernel(ReorderArgs a) {
   int live = len > 0 ? (len + a.stride - 1) / a.stride : 0;
   live = live < a.max_slots ? live : a.max_slots;
   const size_t row_c = (size_t)a.max_slots * a.r * a.elem, row_kr = (size_t)a.max_slots * a.d_rope * a.elem;
-  const uint4* sc = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.src_c) + src * row_c);
-  const uint4* sk = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.src_kr) + src * row_kr);
-  uint4* dc = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.dst_c) + b * row_c);
-  uint4* dk = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.dst_kr) + b * row_kr);
+  const u32x4* sc = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.src_c) + src * row_c);
+  const u32x4* sk = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.src_kr) + src * row_kr);
+  u32x4* dc = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(a.dst_c) + b * row_c);
+  u32x4* dk = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(a.dst_kr) + b * row_kr);
   // slots first_slot .. live-1 (rows are multiples of 16 bytes)
   const int first = a.first_slot < live ? a.first_slot : live;
   const size_t o_c = (size_t)first * a.r * a.elem / 16, o_k = (size_t)first * a.d_rope * a.elem / 16;
@@ -613,7 +629,7 @@ __global__ __launch_bounds__(kBlock) void reorder_kernel(ReorderArgs a) {
   const size_t n_c = (size_t)(live - first) * a.r * a.elem / 16, n_k = (size_t)(live - first) * a.d_rope * a.elem / 16;
   const size_t step = (size_t)gridDim.x * kBlock;
   for (size_t i = (size_t)blockIdx.x * kBlock + tid; i < n_c + n_k; i += 4 * step) {
-    uint4 v[4];
+    u32x4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const size_t j = i + u * step;
@@ -675,14 +691,14 @@ __global__ __launch_bounds__(kBlock) void fork_paged_kernel(ForkArgs a) {
   sp = sp < 0 ? 0 : (sp < a.src.n_pages ? sp : a.src.n_pages - 1);
   if (sp == fresh) return;           // the destination takes the source's page over
   const size_t n_c = (size_t)n_rows * a.r / 8, n_k = (size_t)n_rows * a.d_rope / 8;  // 16-byte pieces (bf16)
-  const uint4* sc = reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a.cache_c) + (size_t)sp * P * a.r);
-  const uint4* sk = reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a.cache_kr) + (size_t)sp * P * a.d_rope);
-  uint4* dc = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.cache_c) + (size_t)fresh * P * a.r);
-  uint4* dk = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.cache_kr) + (size_t)fresh * P * a.d_rope);
+  const u32x4* sc = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(a.cache_c) + (size_t)sp * P * a.r);
+  const u32x4* sk = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(a.cache_kr) + (size_t)sp * P * a.d_rope);
+  u32x4* dc = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(a.cache_c) + (size_t)fresh * P * a.r);
+  u32x4* dk = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(a.cache_kr) + (size_t)fresh * P * a.d_rope);
   constexpr int U = 8;  // pieces in flight per thread
   const size_t step = (size_t)n_parts * kBlock;
   for (size_t i = (size_t)part * kBlock + tid; i < n_c + n_k; i += U * step) {
-    uint4 v[U];
+    u32x4 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const size_t j = i + (size_t)u * step;

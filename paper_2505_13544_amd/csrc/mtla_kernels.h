@@ -150,6 +150,7 @@ struct ExplicitArgs {
   // themselves (cprime, the same rows for every head), r / d_head column slices of d_head per job, and
   // `out` is [B, T, n_heads, r].
   int n_slices = 0;
+  int unpaired = 0;        // attention launch: one row block per workgroup instead of a heavy and a light one
   float* out_latent = nullptr;  // if set (whole sequences only): also softmax . C_hat' [B, T, n_heads, r], by such a launch
 };
 

@@ -180,6 +180,11 @@ typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
 __device__ __forceinline__ void load_to_lds_16(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(src) : "memory", "m0");
 }
+// The same with the address as a wavefront-uniform base and a 32-bit byte offset per lane: a loop that only moves the
+// base pays no vector instruction for the addresses of its loads.
+__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory", "m0");
+}
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {  // until at most N of this wavefront's loads are in flight
   static_assert(N >= 0 && N <= 15, "vmcnt field");
@@ -375,7 +380,7 @@ __global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(Gemm
 // ---- attention over explicit keys and values -------------------------------------------------
 //
 // A tile is 32 columns: their keys [32][d_h] (swz_rows16), RoPE keys [32][d_R] (swz_rows16) and
-// values [32][d_h] (swz_tr), fp16, fetched two tiles ahead through three LDS buffers.
+// values [32][d_h] (swz_tr), fp16, fetched three tiles ahead through four LDS buffers.
 template <int DH, int DR>
 struct TileGeom {
   static constexpr int BN = 32, VC = DH / 8, RC = DR / 8;  // 16-byte pieces per key / value row, per RoPE key row
@@ -385,11 +390,25 @@ struct TileGeom {
   static_assert(BYTES % 1024 == 0 && K_BYTES % 1024 == 0 && R_BYTES % 1024 == 0, "1 KB per wavefront load");
 };
 
-// NW wavefronts of 32 query rows each per workgroup; grid = ceil(ceil(T / (32 NW)) / 2) * n_heads * B.
-// NW = 4 is what the launcher uses: two workgroups per CU, whose wavefronts drift apart so that one
-// multiplies while the other does softmax arithmetic.  (NW = 8, one workgroup per CU with every
-// tile serving twice the rows, halves the L2 traffic but measured 1 - 10 % slower: the two wavefronts
-// of a SIMD then walk the phases in step.)
+// <x, y> of 8 fp16 pairs, summed in fp32
+__device__ __forceinline__ float dot8(u32x4_t x, u32x4_t y, float c) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t xi = x[i], yi = y[i];  // (a bit_cast of a vector element takes element 0)
+    c = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, xi), __builtin_bit_cast(f16x2_t, yi), c, false);
+  }
+  return c;
+}
+
+// The open columns of row m are the final states of the slots that closed before it, j < (p0 + m) / s -- the same
+// columns for all heads' rows of a block up to where they end -- and the row's own running state.  That own
+// column is not a tile column: it starts the row off (reference = its logit, weight 1, output = its value), formed
+// from the row's own key and value in the layouts the queries and the output already have.  So a block of 128 rows walks
+// ((p0 + m0 + 127) / s) / 32 tiles and only the last few have a mask; with the block's own rows as masked tiles, one by
+// one, it was 128 / 32 - (128 / s) / 32 tiles more (two of the 36 a block walks on average at 4096 rows and s = 2).
+//
+// NW wavefronts of 32 query rows each per workgroup.  NW = 4 is what the launcher uses: two workgroups per CU, whose
+// wavefronts drift apart so that one multiplies while the other does softmax arithmetic.
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
 template <int DH, int DR, int NW, bool CONT, bool LAYER>
@@ -399,6 +418,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   constexpr int NT = 64 * NW, BM = 32 * NW, BN = G::BN, VC = G::VC, RC = G::RC;
   constexpr int NBUF = 4, PF = NBUF - 1;  // tiles in LDS, tiles requested ahead
   constexpr int NIK = (G::NCK + NW - 1) / NW, NIR = (G::NCR + NW - 1) / NW;  // loads per wavefront and region, at most
+  constexpr int IROWS = 64 * NW / VC;     // rows between a wavefront's chunks of a region
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * G::BYTES];
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -407,16 +427,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const int T = a.T, s = a.stride, nh = a.n_heads;
   // Workgroups are handed to the 8 XCDs in turn.  The row blocks of one (sequence, head) read the
   // same keys and values, so they are numbered to land on one XCD and meet in its L2: workgroup w of
-  // the launch takes job (w / 8) + (w % 8) * (jobs / 8), jobs ordered (sequence, head, block pair).
-  const int n_blocks = (T + BM - 1) / BM, n_pairs = (n_blocks + 1) / 2;
+  // the launch takes job (w / 8) + (w % 8) * (jobs / 8), jobs ordered (sequence, head, block or block pair).
+  const int n_blocks = (T + BM - 1) / BM, n_units = a.unpaired ? n_blocks : (n_blocks + 1) / 2;
   const unsigned jobs = gridDim.x, w = blockIdx.x;
   const unsigned job = jobs % 8 == 0 ? (w >> 3) + (w & 7) * (jobs >> 3) : w;
   // Latent-space output (a.n_slices > 0): the values are the partial states themselves, DH of their r
   // columns per job (the same rows for every head), and the output row has r columns per head.
   const int n_sl = LAYER || a.n_slices < 1 ? 1 : a.n_slices;
   const bool lat = !LAYER && a.n_slices > 0;
-  const int pair = (int)(job % (unsigned)n_pairs), sl = (int)(job / (unsigned)n_pairs % (unsigned)n_sl),
-            h = (int)(job / (unsigned)(n_pairs * n_sl) % (unsigned)nh), b = (int)(job / (unsigned)(n_pairs * n_sl * nh));
+  const int unit = (int)(job % (unsigned)n_units), sl = (int)(job / (unsigned)n_units % (unsigned)n_sl),
+            h = (int)(job / (unsigned)(n_units * n_sl) % (unsigned)nh), b = (int)(job / (unsigned)(n_units * n_sl * nh));
   const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
   // A continuing sequence has p0 tokens behind it: the final states of its first p0 / s slots are the
   // first rows of the key / value arrays (one per slot), the chunk's T rows follow at row `past`.
@@ -440,12 +460,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const uint32_t src_k = 8 * ((pk % VC) ^ swz_rows16<VC>(row_k));  // element offset inside the source row
   const uint32_t src_v = 8 * ((pk % VC) ^ swz_tr<VC>(row_k));
   const uint32_t src_r = 8 * ((pk % RC) ^ swz_rows16<RC>(row_r));
-  static_assert(NIK == 1 || (64 * NW / VC) % 16 == 0, "same swizzle for all chunks of a wavefront");
+  static_assert(NIK == 1 || IROWS % 16 == 0, "same swizzle for all chunks of a wavefront");
   static_assert(NIR == 1, "one RoPE key chunk per wavefront at most");
   int loads = 0;  // loads of this wavefront per tile
 #pragma unroll
   for (int i = 0; i < NIK; ++i) loads += wv + NW * i < G::NCK ? 2 : 0;
   loads += wv < G::NCR ? 1 : 0;
+  // byte offsets of the lane's pieces from a tile's first source row, the rows `rs` apart (1 among the slots of the past,
+  // s among the chunk-final rows)
+  uint32_t off_k = 0, off_v = 0, off_r = 0;
+  int off_rs = 0;
+  auto set_offsets = [&](int rs) {
+    off_rs = rs;
+    off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
+    off_v = 2 * ((uint32_t)(row_k * rs) * v_stride + src_v);
+    off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
+  };
   // ---- where this lane reads: key rows 16 sb + l16 (piece 4 kk + g), value rows 4g + l16/4 (+16)
   const uint32_t k_row_off = (uint32_t)(l16 * VC * 16), k_swz = (uint32_t)(swz_rows16<VC>(l16) ^ g) << 4;
   const uint32_t r_row_off = (uint32_t)(l16 * RC * 16), r_swz = (uint32_t)(swz_rows16<RC>(l16) ^ g) << 4;
@@ -453,12 +483,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const uint32_t v_row_off = (uint32_t)(v_row * VC * 16 + 8 * (l16 & 1));
   const uint32_t v_swz = (uint32_t)(swz_tr<VC>(v_row) ^ ((l16 & 3) >> 1)) << 4;
 
-  // Row block x walks x * BM / (s BN) + BM / BN tiles.  A workgroup takes block n-1-x and then block
-  // x, so every workgroup of the launch walks the same number of tiles (the middle one, if n is odd,
-  // half).
+  // Row block x walks about x * BM / (s BN) tiles.  A workgroup takes block n-1-x and then block x, so every workgroup
+  // of the launch walks the same number of tiles (the middle one, if n is odd, half); a launch that such pairs would not
+  // fill the chip with takes single blocks (a.unpaired).
   for (int pass = 0; pass < 2; ++pass) {
-    const int xb = pass == 0 ? n_blocks - 1 - pair : pair;
-    if (pass == 1 && xb >= n_blocks - 1 - pair) break;
+    const int xb = pass == 0 ? n_blocks - 1 - unit : unit;
+    if (pass == 1 && (a.unpaired || xb >= n_blocks - 1 - unit)) break;
     const int m0 = xb * BM;
     if (m0 >= len) {  // padding rows only
       const int rows = T - m0 < BM ? T - m0 : BM;
@@ -472,73 +502,98 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       }
       continue;
     }
-    // ---- the columns: shared ones, slots j < (p0 + m0) / s (a slot of the past: row j; one closed
-    // inside the chunk: the chunk's row j*s + s-1 - p0), then the block's own rows
-    const int n_sh = (p0 + m0) / s, n_sh_tiles = (n_sh + BN - 1) / BN, n_tiles = n_sh_tiles + BM / BN;
-
-    // source row of column `row` of tile t (tiles past the last one: a readable duplicate)
-    auto src_row = [&](int t, int row) -> uint32_t {
-      if (t < n_sh_tiles) {
-        const int c = BN * t + row < n_sh ? BN * t + row : n_sh - 1;
-        return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
-      }
-      const int r_ = m0 + BN * (t - n_sh_tiles) + row;
-      return (uint32_t)(past + (r_ < T ? r_ : T - 1));
+    // ---- the columns: slots j < (p0 + last row) / s (a slot of the past: row j; one closed inside the chunk: the
+    // chunk's row j*s + s-1 - p0)
+    const int m_last = (m0 + BM < len ? m0 + BM : len) - 1;
+    const int n_cols = (p0 + m_last) / s, n_tiles = (n_cols + BN - 1) / BN;
+    // source row of column c (columns past the last one: a readable duplicate)
+    auto src_row = [&](int c) -> uint32_t {
+      c = c < n_cols ? c : n_cols - 1;
+      return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
     };
     // this wavefront's part of tile t on its way into buffer t % NBUF: `loads` loads
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
     auto issue = [&](int t) {
       const uint32_t buf = lds_addr + (uint32_t)((t % NBUF) * G::BYTES);
+      const int c0 = BN * t;
+      if (c0 + BN <= n_cols && (!CONT || c0 >= j0 || c0 + BN <= j0)) {  // rows at one distance: the lanes' offsets stand
+        const int rs = CONT && c0 < j0 ? 1 : s;
+        const uint32_t row0 = CONT && c0 < j0 ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
+        if (rs != off_rs) set_offsets(rs);
+#pragma unroll
+        for (int i = 0; i < NIK; ++i)
+          if (wv + NW * i < G::NCK) {
+            const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
+            const size_t r_ = row0 + (uint32_t)(i * IROWS * rs);
+            load_to_lds_16(kx + r_ * kv_stride, off_k, buf + G::K_OFF + chunk);
+            load_to_lds_16(vx + r_ * v_stride, off_v, buf + G::V_OFF + chunk);
+          }
+        if (wv < G::NCR) load_to_lds_16(kr16 + (size_t)row0 * DR, off_r, buf + G::R_OFF + (uint32_t)(wv * 1024));
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < NIK; ++i)
         if (wv + NW * i < G::NCK) {
-          const uint32_t srow = src_row(t, row_k + i * (64 * NW / VC));
+          const uint32_t srow = src_row(c0 + row_k + i * IROWS);
           const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
           load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
           load_to_lds_16(vx + srow * v_stride + src_v, buf + G::V_OFF + chunk);
         }
-      if (wv < G::NCR) load_to_lds_16(kr16 + src_row(t, row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wv * 1024));
+      if (wv < G::NCR) load_to_lds_16(kr16 + src_row(c0 + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wv * 1024));
     };
 
-    // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt
-    u32x4_t qf[2][KQ];
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int m = m0 + 32 * wv + 16 * rt + l16;
-      const size_t row = (size_t)b * T + (m < T ? m : T - 1);
-      const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * g;
-      const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * g;
-#pragma unroll
-      for (int kk = 0; kk < KQ; ++kk) {
-        const u32x4_t raw = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk)
-                                    : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
-        // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
-        qf[rt][kk] = LAYER ? raw : bf16x8_to_f16x8(raw, a.scale_log2);
-      }
-    }
-
-    float m_ref[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    float4_t acc[2][MT];
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[rt][mt] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-    // bit 8 dt + 4 sb + v of closes_mask: row m0 + 32 dt + 16 sb + 4g + v of the block closes a chunk
-    unsigned long long closes_mask = 0;
-#pragma unroll
-    for (int i = 0; i < 8 * NW; ++i) {
-      const int c = BN * (i >> 3) + 16 * ((i >> 2) & 1) + 4 * g + (i & 3);
-      closes_mask |= (unsigned long long)((p0 + m0 + c + 1) % s == 0 ? 1u : 0u) << i;
-    }
-
-    // every wavefront is done with the buffers of the previous block (no tile load is in flight:
-    // the last tiles of a block wait for everything)
-    wait_loads_but<0>();
+    // the first tiles travel while the rows are set up.  (Every wavefront is done with the buffers of the previous block;
+    // no tile load is in flight: the last tile of a block waits for everything.)
     barrier_only();
 #pragma unroll
     for (int t = 0; t < PF; ++t)
       if (t < n_tiles) issue(t);
+
+    // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column
+    u32x4_t qf[2][KQ];
+    float4_t neg_ref[2];        // - reference of the row's weights, where the logits' sums start
+    float l_run[2];
+    float4_t acc[2][MT];
+    int bound[2];               // columns open to the lane's rows
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const int m = m0 + 32 * wv + 16 * rt + l16;
+      const int mr = m < len ? m : len - 1;
+      bound[rt] = (p0 + mr) / s;
+      const size_t row = (size_t)b * T + mr;
+      const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * g;
+      const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * g;
+      const uint32_t own = (uint32_t)(past + mr);
+      const uint16_t* kp = kx + own * kv_stride + 8 * g;
+      const uint16_t* krp = kr16 + own * DR + 8 * g;
+      const uint16_t* vp = vx + own * v_stride + 4 * g;
+      u32x4_t kd[KQ];
+      uint2 vd[MT];
+#pragma unroll
+      for (int kk = 0; kk < KQ; ++kk) {
+        qf[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
+        kd[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) vd[mt] = *reinterpret_cast<const uint2*>(vp + 16 * mt);
+      float e = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KQ; ++kk) {
+        // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
+        if (!LAYER) qf[rt][kk] = bf16x8_to_f16x8(qf[rt][kk], a.scale_log2);
+        e = dot8(kd[kk], qf[rt][kk], e);
+      }
+      e += __shfl_xor(e, 16, kWave);
+      e += __shfl_xor(e, 32, kWave);
+      neg_ref[rt] = float4_t{-e, -e, -e, -e};
+      l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        acc[rt][mt] = float4_t{f16_lo_to_f32(vd[mt].x), f16_hi_to_f32(vd[mt].x), f16_lo_to_f32(vd[mt].y), f16_hi_to_f32(vd[mt].y)};
+    }
+    // columns open to all of the wavefront's rows, and to any of them
+    const int all_below = (p0 + m0 + 32 * wv) / s;
+    const int none_from = (p0 + m0 + 32 * wv + 31) / s;
 
     for (int t = 0; t < n_tiles; ++t) {
       // tile t has landed: this wavefront's part (all but the loads of the tiles after it), then everyone's
@@ -546,34 +601,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       wait_loads_but(loads * after);
       barrier_only();
       if (t + PF < n_tiles) issue(t + PF);  // into the buffer tile t-1 was read from: every wavefront is past that
-
-      // Visibility.  A shared tile below n_sh is open to every row; the last shared tile is cut at
-      // n_sh; a tile of the block's own rows is open to row rrel at column c iff c == rrel (the row's
-      // own running state) or c < rrel and row m0 + c closes a chunk (closes_mask, set up once).
-      const bool own = t >= n_sh_tiles;
-      const int dt = t - n_sh_tiles;
-      if (own && dt > wv) continue;  // all 32 columns lie above this wavefront's rows
-      const int cbase = own ? BN * dt : BN * t;
-      const bool all_open = !own && cbase + BN <= n_sh;
-      // bit 4 sb + v of open_bits[rt]: column 16 sb + 4g + v of the tile is open to the lane's row
-      uint32_t open_bits[2] = {0xffu, 0xffu};
-      if (!all_open) {  // workgroup-uniform: five tiles per row block at most come here
-        const uint32_t closes = own ? (uint32_t)(closes_mask >> (8 * dt)) : 0xffu;
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          const int bound = own ? 32 * wv + 16 * rt + l16 : n_sh;  // columns below `bound` may be open
-          uint32_t m = 0;
-#pragma unroll
-          for (int sb = 0; sb < 2; ++sb) {
-            const int d = bound - (cbase + 16 * sb + 4 * g);  // column 4g + v of the group is below iff v < d
-            const int dd = d < 0 ? 0 : (d > 4 ? 4 : d);
-            const uint32_t lt = (1u << dd) - 1u;
-            const uint32_t eq = own ? (uint32_t)((unsigned)d < 4u) << (d & 3) : 0u;
-            m |= ((lt & (closes >> (4 * sb)) & 0xfu) | eq) << (4 * sb);
-          }
-          open_bits[rt] = m;
-        }
-      }
+      if (BN * t >= none_from) continue;    // above all of this wavefront's rows
 
       const uint32_t buf = (uint32_t)((t % NBUF) * G::BYTES);  // byte offset of the tile in `lds`
       const unsigned char* kb = lds + buf + G::K_OFF + k_row_off;
@@ -591,14 +619,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
         return u32x4_t{u0.x, u0.y, u1.x, u1.y};
       };
 
-      // ---- S^T[col, row] = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one half of the K
+      // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one half of the K
       // steps are in flight while the other half is multiplied
       constexpr int KH = KQ / 2;
       float4_t sacc[2][2];
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) sacc[rt][sb] = float4_t{0.f, 0.f, 0.f, 0.f};
       u32x4_t ka[KH][2], kc[KQ - KH][2];
 #pragma unroll
       for (int kk = 0; kk < KH; ++kk)
@@ -616,7 +640,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
 #pragma unroll
           for (int rt = 0; rt < 2; ++rt)
             sacc[rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, ka[kk][sb]),
-                                                                  __builtin_bit_cast(f16x8_t, qf[rt][kk]), sacc[rt][sb], 0, 0, 0);
+                                                                  __builtin_bit_cast(f16x8_t, qf[rt][kk]),
+                                                                  kk == 0 ? neg_ref[rt] : sacc[rt][sb], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       // the first value fragments travel while the second half is multiplied and the softmax runs
       constexpr int VPRE = MT / 2;
@@ -634,56 +659,57 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       __builtin_amdgcn_sched_barrier(0);
 
       // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
-      u32x4_t pb[2];  // per row tile: B operand of the K = 32 PV product
+      if (BN * t + BN > all_below) {  // wavefront-uniform: the last tiles only
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        float sv[2][4];
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sv[sb][v] = sacc[rt][sb][v];
-        if (!all_open) {
+        for (int rt = 0; rt < 2; ++rt) {
+          const int d = bound[rt] - (BN * t + 4 * g);
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sv[sb][v] = (open_bits[rt] >> (4 * sb + v) & 1u) ? sv[sb][v] : -INFINITY;
+            for (int v = 0; v < 4; ++v) sacc[rt][sb][v] = 16 * sb + v < d ? sacc[rt][sb][v] : -INFINITY;
         }
-        float mloc = -INFINITY;
+      }
+      // fixed reference per row (its own column's logit, re-based only when a tile tops it by more than 2^kRebase): no
+      // accumulator rescaling and no cross-lane traffic per tile.  Weights more than 2^-24 below the reference
+      // vanish in fp16; they are that much smaller than weights already summed.
+      constexpr float kRebase = 12.f;  // fp16 weights: 2^(s - reference) stays far below 65504
+      float top[2];
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
+      for (int rt = 0; rt < 2; ++rt) {
+        top[rt] = fmaxf(fmaxf(sacc[rt][0][0], sacc[rt][0][1]), sacc[rt][0][2]);
+        top[rt] = fmaxf(fmaxf(top[rt], sacc[rt][0][3]), sacc[rt][1][0]);
+        top[rt] = fmaxf(fmaxf(top[rt], sacc[rt][1][1]), sacc[rt][1][2]);
+        top[rt] = fmaxf(top[rt], sacc[rt][1][3]);
+      }
+      if (__any(fmaxf(top[0], top[1]) > kRebase)) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) mloc = fmaxf(mloc, sv[sb][v]);
-        // fixed reference per row (set at the row's first open columns, re-based only when a tile
-        // tops it by more than 2^kRebase): no accumulator rescaling and no cross-lane traffic per
-        // tile.  Weights more than 2^-24 below the reference vanish in fp16; they are that much
-        // smaller than weights already summed.
-        constexpr float kRebase = 12.f;  // fp16 weights: 2^(s - m_ref) stays far below 65504
-        if (__any(mloc - m_ref[rt] > kRebase)) {  // also true while m_ref is -inf and a column is open
-          float mt_ = fmaxf(mloc, __shfl_xor(mloc, 16, kWave));
-          mt_ = fmaxf(mt_, __shfl_xor(mt_, 32, kWave));
-          if (m_ref[rt] == -INFINITY) {
-            m_ref[rt] = mt_;
-          } else if (mt_ - m_ref[rt] > kRebase) {
-            const float alpha = __builtin_amdgcn_exp2f(m_ref[rt] - mt_);
-            m_ref[rt] = mt_;
+        for (int rt = 0; rt < 2; ++rt) {
+          float up = fmaxf(top[rt], __shfl_xor(top[rt], 16, kWave));
+          up = fmaxf(up, __shfl_xor(up, 32, kWave));
+          if (up > kRebase) {
+            const float alpha = __builtin_amdgcn_exp2f(-up);
+            neg_ref[rt] -= up;
             l_run[rt] *= alpha;
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb) sacc[rt][sb] -= up;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[rt][mt] *= alpha;
           }
         }
-        const float m_sub = m_ref[rt] == -INFINITY ? 0.f : m_ref[rt];
-        uint32_t pk2[2][2];
+      }
+      u32x4_t pb[2];  // per row tile: B operand of the K = 32 PV product
+      const f16x2_t ones = {(_Float16)1.f, (_Float16)1.f};
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-          float p[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) p[v] = __builtin_amdgcn_exp2f(sv[sb][v] - m_sub);
-          pk2[sb][0] = pack_f16x2(p[0], p[1]);
-          pk2[sb][1] = pack_f16x2(p[2], p[3]);
-          l_run[rt] += (p[0] + p[1]) + (p[2] + p[3]);  // fp32 sum; the half rounding of a weight is 2^-12 of it
-        }
+      for (int rt = 0; rt < 2; ++rt) {
         // K index 8g + e of the tile: e < 4 -> column 4g + e of its first 16, else of its second 16
-        pb[rt] = u32x4_t{pk2[0][0], pk2[0][1], pk2[1][0], pk2[1][1]};
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(sacc[rt][sb][2 * u]), __builtin_amdgcn_exp2f(sacc[rt][sb][2 * u + 1]));
+            pb[rt][2 * sb + u] = two;
+            l_run[rt] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run[rt], false);  // the weights as they are used
+          }
       }
 
       // ---- O^T[d, row] += V^T[d, col] P^T[col, row]; V^T comes out of LDS through the transposing read
@@ -740,12 +766,16 @@ hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const Eve
   const int n_blocks = (a.T + 32 * NW - 1) / (32 * NW);
   const int n_sl = a.n_slices > 0 ? a.n_slices : 1;
   if (a.n_slices > 0 && (a.q_f16 != 0 || a.n_slices * DH != a.r)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n_blocks + 1) / 2) * n_sl * a.n_heads * a.batch);  // two row blocks per workgroup
+  // Two row blocks per workgroup, unless that leaves the chip (two workgroups on each of 256 units) partly empty: then a
+  // block each, which the units run side by side.
+  ExplicitArgs x = a;
+  x.unpaired = (size_t)((n_blocks + 1) / 2) * n_sl * a.n_heads * a.batch < 512;
+  const dim3 grid((unsigned)(x.unpaired ? n_blocks : (n_blocks + 1) / 2) * n_sl * a.n_heads * a.batch);
   const bool layer = a.q_f16 != 0;  // comes with out16
   if (layer != (a.out16 != nullptr) || (layer && !a.pos0)) return hipErrorInvalidValue;
-  if (layer) launch_timed(attn_explicit_kernel<DH, DR, NW, true, true>, grid, dim3(64 * NW), 0, st, ev, a);
-  else if (a.pos0) launch_timed(attn_explicit_kernel<DH, DR, NW, true, false>, grid, dim3(64 * NW), 0, st, ev, a);
-  else launch_timed(attn_explicit_kernel<DH, DR, NW, false, false>, grid, dim3(64 * NW), 0, st, ev, a);
+  if (layer) launch_timed(attn_explicit_kernel<DH, DR, NW, true, true>, grid, dim3(64 * NW), 0, st, ev, x);
+  else if (a.pos0) launch_timed(attn_explicit_kernel<DH, DR, NW, true, false>, grid, dim3(64 * NW), 0, st, ev, x);
+  else launch_timed(attn_explicit_kernel<DH, DR, NW, false, false>, grid, dim3(64 * NW), 0, st, ev, x);
   return hipGetLastError();
 }
 
