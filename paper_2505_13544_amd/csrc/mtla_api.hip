@@ -817,6 +817,85 @@ mtla_status mtla_layer_decode_step(mtla_ctx* c, const mtla_layer_weights* lw, vo
   return hip_ok(launch_layer_out(oa, st)) ? MTLA_OK : MTLA_ERR_HIP;
 }
 
+// The front launch's record for the explicit form `ex`: whole sequences without a cache until told otherwise.
+static void front_args(const mtla_ctx* c, const ExplicitArgs& ex, const void* cc, const void* kr, const int32_t* n_new,
+                       PrefillFrontArgs& fa) {
+  ChunkStageArgs& cs = fa.cs;
+  cs.cache_c = cs.cache_kr = nullptr;
+  cs.tail_prev = nullptr;
+  cs.pos0 = nullptr;
+  cs.c = cc;
+  cs.kr = kr;
+  cs.w = nullptr;
+  cs.n_new = n_new;
+  cs.cprime = const_cast<void*>(ex.cprime);
+  cs.kr16 = ex.kr16;
+  cs.status = nullptr;
+  cs.batch = ex.batch;
+  cs.T = ex.T;
+  cs.r = ex.r;
+  cs.d_rope = ex.d_rope;
+  cs.stride = ex.stride;
+  cs.max_slots = c->cfg.max_slots;
+  cs.past_pitch = ex.past_pitch;
+  fa.w_uk = ex.w_uk;
+  fa.w_uv = ex.w_uv;
+  fa.w_kT = ex.w_kT;
+  fa.w_v16 = ex.w_v16;
+  fa.n_heads = ex.n_heads;
+  fa.d_head = ex.d_head;
+}
+
+// Event pair of the next timed launch (mtla_profile_start .. mtla_profile_read), or none.
+static EventPair next_event(mtla_ctx* c) {
+  EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
+  if (c->prof_n < (int)c->ev_start.size()) {
+    ev.start = c->ev_start[c->prof_n];
+    ev.stop = c->ev_stop[c->prof_n++];
+  }
+  return ev;
+}
+
+// The launch records of a prefill in the explicit form over scratch `ws` (chunk_layout): everything but where the
+// lengths, the merge weights and the outputs are.
+static void chunk_args(const mtla_ctx* c, const void* cache_c, const void* cache_kr, const void* q, const void* q_rope,
+                       const void* cc, const void* kr, const int32_t* n_new, int32_t batch, int32_t T, int32_t past,
+                       const void* w_uk, const void* w_uv, char* ws, void* workspace, const int32_t* page_table,
+                       ExplicitArgs& ex, PrefillFrontArgs& fa) {
+  const mtla_config& g = c->cfg;
+  const ChunkLayout L = chunk_layout(c, (size_t)batch * ((size_t)past + T));
+  ex.q = q;
+  ex.q_rope = q_rope;
+  ex.cprime = ws + L.cprime;
+  ex.kr = nullptr;
+  ex.w_uk = w_uk;
+  ex.w_uv = w_uv;
+  ex.seq_len = n_new;
+  ex.kx = ws + L.kx;
+  ex.vx = ws + L.vx;
+  ex.w_kT = ws + L.w_kT;
+  ex.w_v16 = ws + L.w_v16;
+  ex.kr16 = ws + L.kr16;
+  ex.out = nullptr;
+  ex.batch = batch;
+  ex.T = T;
+  ex.n_heads = g.n_heads;
+  ex.d_head = g.d_head;
+  ex.r = g.r;
+  ex.d_rope = g.d_rope;
+  ex.stride = g.stride;
+  ex.scale_log2 = c->scale * 1.4426950408889634f;
+  ex.past_pitch = past;
+  front_args(c, ex, cc, kr, n_new, fa);
+  fa.cs.cache_c = cache_c;
+  fa.cs.cache_kr = cache_kr;
+  fa.cs.prefix_owner = c->prefix_owner;  // mtla_set_shared_prefix: past slots of a common prompt come from their owner
+  fa.cs.prefix_slots = c->prefix_slots;
+  fa.cs.prefix_rows = g.max_batch;
+  fa.cs.pages = page_map(c, page_table);
+  fa.cs.status = reinterpret_cast<int32_t*>(workspace);
+}
+
 // Scratch of mtla_prefill_step: the saved state, the merge weights, then the scratch of the continuing prefill.
 struct PrefillStepLayout {
   size_t pos0, tail_prev, w, chunk, total;
@@ -884,24 +963,41 @@ mtla_status mtla_prefill_step_paged(mtla_ctx* c, void* cache_c, void* cache_kr, 
       return MTLA_ERR_UNSUPPORTED;
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  LayerRowsArgs prep;  // seq_len -> pos0, tail_c -> tail_prev
-  prep.seq_len = seq_len;
-  prep.tail_c = tail_c;
-  prep.pos0 = pos0;
-  prep.tail_prev = tail_prev;
-  prep.n_wo = 0;
-  prep.batch = batch;
-  prep.r = c->cfg.r;
-  if (!hip_ok(launch_layer_prefill_prep(prep, st))) return MTLA_ERR_HIP;
+  if (append_bulk_supported(ap, c->cfg.dtype)) {  // append, staging and weights in one launch
+    PrefillFrontArgs fa;
+    ExplicitArgs ex;
+    chunk_args(c, cache_c, cache_kr, q, q_rope, cc, kr, n_new, batch, T, max_past_slots, w_uk, w_uv, sc + L.chunk, workspace, page_table, ex, fa);
+    ap.w_out = w_out;
+    fa.ap = ap;
+    fa.cs.pos0 = seq_len;
+    fa.pos0_out = pos0;
+    fa.tail_next = tail_prev;
+    ex.pos0 = pos0;
+    ex.out = out;
+    ex.advance = seq_len;
+    ex.tail_c = tail_c;
+    ex.tail_next = tail_prev;
+    ex.capacity = (long long)c->cfg.max_slots * c->cfg.stride;
+    if (!hip_ok(launch_prefill_front(fa, 1, st))) return MTLA_ERR_HIP;
+    return hip_ok(launch_prefill_explicit(ex, st, next_event(c))) ? MTLA_OK : MTLA_ERR_HIP;
+  }
+  SaveStateArgs save;  // seq_len -> pos0, tail_c -> tail_prev
+  save.seq_len = seq_len;
+  save.tail_c = tail_c;
+  save.pos0 = pos0;
+  save.tail_prev = tail_prev;
+  save.batch = batch;
+  save.r = c->cfg.r;
+  if (!hip_ok(launch_save_state(save, st))) return MTLA_ERR_HIP;
   if (!hip_ok(launch_append(ap, c->cfg.dtype, st))) return MTLA_ERR_HIP;
   return mtla_prefill_chunk_attn_paged(c, cache_c, cache_kr, tail_prev, pos0, page_table, q, q_rope, cc, kr, w, n_new, batch,
                                        T, max_past_slots, w_uk, w_uv, out, sc + L.chunk, workspace, hip_stream);
 }
 
-// Scratch of a whole-layer prefill: the saved state, the projections' outputs, the merge weights, the
-// attention output as fp16, W_O as fp16, and behind them the scratch of the continuing prefill.
+// Scratch of a whole-layer prefill: the lengths before it, the tail shadows after it, the projections' outputs, the attention output
+// as fp16, W_O as fp16, and behind them the scratch of the continuing prefill.
 struct LayerPrefillLayout {
-  size_t pos0, tail_prev, rope_cs, q16, qr16, kr, c_raw, c, w, out16, w_o16, chunk, total;
+  size_t pos0, tail_next, rope_cs, q16, qr16, kr, c_raw, out16, w_o16, chunk, total;
 };
 static LayerPrefillLayout layer_prefill_layout(const mtla_ctx* c, size_t d_model, size_t batch, size_t T, size_t past) {
   const mtla_config& g = c->cfg;
@@ -914,14 +1010,12 @@ static LayerPrefillLayout layer_prefill_layout(const mtla_ctx* c, size_t d_model
     return at;
   };
   L.pos0 = take(batch * 4);
-  L.tail_prev = take(batch * g.r * 4);
+  L.tail_next = take(batch * g.r * 4);
   L.rope_cs = take(M * (g.d_rope / 2) * 8);
   L.q16 = take(M * nq * 2);
   L.qr16 = take(M * nqr * 2);
   L.kr = take(M * g.d_rope * 2);
   L.c_raw = take(M * g.r * 4);
-  L.c = take(M * g.r * 2);
-  L.w = take(M * 4);
   L.out16 = take(M * nq * 2);
   L.w_o16 = take(d_model * nq * 2);
   L.chunk = off;
@@ -955,168 +1049,82 @@ mtla_status mtla_layer_prefill(mtla_ctx* c, const mtla_layer_weights* lw, void* 
     return MTLA_ERR_INVALID_ARG;
   if (g.dtype != MTLA_BF16) return MTLA_ERR_UNSUPPORTED;
   if (lw->d_model < 32 || lw->d_model % 32 != 0 || g.r > 512) return MTLA_ERR_UNSUPPORTED;
-  const size_t M = (size_t)batch * T, rows_p = (size_t)batch * ((size_t)max_past_slots + T);
-  if (rows_p > ((size_t)1 << 24)) return MTLA_ERR_UNSUPPORTED;
+  const size_t M = (size_t)batch * T;
+  if ((size_t)batch * ((size_t)max_past_slots + T) > ((size_t)1 << 24)) return MTLA_ERR_UNSUPPORTED;
   char* sc = reinterpret_cast<char*>(scratch);
   const LayerPrefillLayout L = layer_prefill_layout(c, (size_t)lw->d_model, (size_t)batch, (size_t)T, (size_t)max_past_slots);
   const int nq = g.n_heads * g.d_head, nqr = g.n_heads * g.d_rope;
   const float scale_log2 = c->scale * 1.4426950408889634f;
   int32_t* pos0 = reinterpret_cast<int32_t*>(sc + L.pos0);
-  float* tail_prev = reinterpret_cast<float*>(sc + L.tail_prev);
-  float* w = reinterpret_cast<float*>(sc + L.w);
 
-  // ---- the four projections of x: one product each, rotation and scaling on the way out
-  GemmArgs gq;
-  gq.A = x;
-  gq.M = (int)M;
-  gq.K = lw->d_model;
-  gq.in_bf16 = 1;
-  gq.d_rope = g.d_rope;
+  // ---- the four projections of x in one launch, rotation and scaling on the way out
   RopeTableArgs rt;
-  rt.pos0 = pos0;
+  rt.pos0 = seq_len;
   rt.table = reinterpret_cast<float2*>(sc + L.rope_cs);
   rt.rows = M;
   rt.T = T;
   rt.d_rope = g.d_rope;
   for (int k = 0; k < 32; ++k)
     rt.rope_freq[k] = std::pow((double)(lw->rope_base > 0.f ? lw->rope_base : 10000.f), -2.0 * k / g.d_rope);
-  GemmArgs gqr = gq, gc = gq;
-  gq.W[0] = lw->w_q;    // q = x W_Q, times log2(e) / sqrt(d_h), fp16: what the attention multiplies
-  gq.C[0] = sc + L.q16;
-  gq.N = nq;
-  gq.epi = 0;
-  gq.scale = scale_log2;
-  gqr.W[0] = lw->w_qr;  // q^R = RoPE(x W_QR), same scaling
-  gqr.C[0] = sc + L.qr16;
-  gqr.N = nqr;
-  gqr.epi = 1;
-  gqr.scale = scale_log2;
-  gqr.rope_cs = rt.table;
-  GemmArgs gkr = gqr;   // k^R = RoPE(x W_KR), storage type (it goes into the cache): rides along with q^R when the
-  const bool kr_rides = nqr % 256 == 0;  // column blocks allow it, else it is a product of its own
-  if (kr_rides) {
-    gqr.W[1] = lw->w_kr;
-    gqr.C[1] = sc + L.kr;
-    gqr.N1 = g.d_rope;
-  } else {  // a launch with the second product only
-    gkr.W[1] = lw->w_kr;
-    gkr.C[1] = sc + L.kr;
-    gkr.N1 = g.d_rope;
-    gkr.N = 0;
-    if (!gemm_nt_supported(gkr)) return MTLA_ERR_UNSUPPORTED;
-  }
-  gc.W[0] = lw->w_r;    // x W_r in fp32, normalised next
-  gc.C[0] = sc + L.c_raw;
-  gc.N = g.r;
-  gc.epi = 3;
-  if (!gemm_nt_supported(gq) || !gemm_nt_supported(gqr) || !gemm_nt_supported(gc)) return MTLA_ERR_UNSUPPORTED;
+  GemmArgs gx;
+  gx.A = x;
+  gx.M = (int)M;
+  gx.K = lw->d_model;
+  gx.in_bf16 = 1;
+  gx.d_rope = g.d_rope;
+  gx.rope_cs = rt.table;
+  gx.n_seg = 4;
+  gx.rows.n_new = n_new;
+  gx.rows.T = T;
+  gx.seg[0] = {lw->w_q, sc + L.q16, nq, 0, scale_log2};      // q = x W_Q, times log2(e) / sqrt(d_h), fp16: what the attention multiplies
+  gx.seg[1] = {lw->w_qr, sc + L.qr16, nqr, 1, scale_log2};   // q^R = RoPE(x W_QR), same scaling
+  gx.seg[2] = {lw->w_r, sc + L.c_raw, g.r, 3, 1.f};          // x W_r in fp32, normalised by the append
+  gx.seg[3] = {lw->w_kr, sc + L.kr, g.d_rope, 2, 1.f};       // k^R = RoPE(x W_KR), storage type (it goes into the cache)
+  if (!gemm_nt_supported(gx)) return MTLA_ERR_UNSUPPORTED;
 
   // ---- the path: append (merge weights, cache), then the continuing parallel form
   AppendArgs ap;
-  const mtla_status ok = append_args(c, cache_c, cache_kr, tail_c, seq_len, sc + L.c, sc + L.kr, n_new, T, batch, hyp_A,
-                                     hyp_a, hyp_G, nullptr, w, nullptr, workspace, ap);
+  const mtla_status ok = append_args(c, cache_c, cache_kr, tail_c, seq_len, sc + L.c_raw, sc + L.kr, n_new, T, batch, hyp_A,
+                                     hyp_a, hyp_G, nullptr, nullptr, nullptr, workspace, ap);
   if (ok != MTLA_OK) return ok;
-  ap.c_merge_f32 = reinterpret_cast<const float*>(sc + L.c_raw);  // normalised in place by then
-  // only the matrix-core bulk append folds the unrounded latents; the other one would merge the rounded
-  // copies while the attention below works from the unrounded ones
-  if (!append_bulk_mfma_supported(ap, g.dtype)) return MTLA_ERR_UNSUPPORTED;
-  const ChunkLayout CL = chunk_layout(c, rows_p);
-  char* ws = sc + L.chunk;
+  ap.ln_eps = lw->ln_eps > 0.f ? lw->ln_eps : 1e-5f;
+  ap.ln_gamma = lw->ln_gamma;
+  ap.ln_beta = lw->ln_beta;
+  // only the matrix-core bulk append folds the unrounded latents
+  if (!append_bulk_supported(ap, g.dtype)) return MTLA_ERR_UNSUPPORTED;
   ExplicitArgs ex;
-  ex.q = sc + L.q16;
-  ex.q_rope = sc + L.qr16;
+  PrefillFrontArgs fa;
+  chunk_args(c, cache_c, cache_kr, sc + L.q16, sc + L.qr16, nullptr, sc + L.kr, n_new, batch, T, max_past_slots, w_uk, w_uv,
+             sc + L.chunk, workspace, nullptr, ex, fa);
+  fa.ap = ap;
+  fa.cs.pos0 = seq_len;
+  fa.pos0_out = pos0;
+  fa.tail_next = reinterpret_cast<float*>(sc + L.tail_next);
+  fa.w_o = lw->w_o;
+  fa.w_o16 = sc + L.w_o16;
+  fa.n_wo = (size_t)lw->d_model * nq;
   ex.q_f16 = 1;
-  ex.cprime = ws + CL.cprime;
-  ex.kr = nullptr;
-  ex.w_uk = w_uk;
-  ex.w_uv = w_uv;
-  ex.seq_len = n_new;
-  ex.kx = ws + CL.kx;
-  ex.vx = ws + CL.vx;
-  ex.w_kT = ws + CL.w_kT;
-  ex.w_v16 = ws + CL.w_v16;
-  ex.kr16 = ws + CL.kr16;
-  ex.out = nullptr;
   ex.out16 = sc + L.out16;
-  ex.batch = batch;
-  ex.T = T;
-  ex.n_heads = g.n_heads;
-  ex.d_head = g.d_head;
-  ex.r = g.r;
-  ex.d_rope = g.d_rope;
-  ex.stride = g.stride;
-  ex.scale_log2 = scale_log2;
   ex.pos0 = pos0;
-  ex.past_pitch = max_past_slots;
+  ex.advance = seq_len;
+  ex.tail_c = tail_c;
+  ex.tail_next = fa.tail_next;
+  ex.capacity = (long long)g.max_slots * g.stride;
   if (!prefill_explicit_supported(ex)) return MTLA_ERR_UNSUPPORTED;
   GemmArgs gy;          // y = concat_h(o_h) W_O
   gy.A = sc + L.out16;
-  gy.W[0] = sc + L.w_o16;
-  gy.C[0] = y;
   gy.M = (int)M;
-  gy.N = lw->d_model;
   gy.K = nq;
-  gy.epi = 3;
+  gy.seg[0] = {sc + L.w_o16, y, lw->d_model, 3, 1.f};
+  gy.rows.n_new = n_new;
+  gy.rows.T = T;
+  gy.rows.zeros = 1;
   if (!gemm_nt_supported(gy)) return MTLA_ERR_UNSUPPORTED;
 
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  LayerRowsArgs prep;
-  prep.seq_len = seq_len;
-  prep.tail_c = tail_c;
-  prep.pos0 = pos0;
-  prep.tail_prev = tail_prev;
-  prep.w_o = lw->w_o;
-  prep.w_o16 = sc + L.w_o16;
-  prep.n_wo = (size_t)lw->d_model * nq;
-  prep.batch = batch;
-  prep.r = g.r;
-  if (!hip_ok(launch_layer_prefill_prep(prep, st))) return MTLA_ERR_HIP;
-  if (!hip_ok(launch_rope_table(rt, st))) return MTLA_ERR_HIP;
-  if (!hip_ok(launch_gemm_nt(gq, st)) || !hip_ok(launch_gemm_nt(gqr, st)) || !hip_ok(launch_gemm_nt(gc, st)))
+  if (!hip_ok(launch_rope_table(rt, st)) || !hip_ok(launch_gemm_nt(gx, st)) || !hip_ok(launch_prefill_front(fa, 2, st)) ||
+      !hip_ok(launch_prefill_explicit(ex, st, next_event(c))))
     return MTLA_ERR_HIP;
-  if (!kr_rides && !hip_ok(launch_gemm_nt(gkr, st))) return MTLA_ERR_HIP;
-  LayerRowsArgs ln;
-  ln.raw = reinterpret_cast<const float*>(sc + L.c_raw);
-  ln.gamma = lw->ln_gamma;
-  ln.beta = lw->ln_beta;
-  ln.c = sc + L.c;
-  ln.c32 = reinterpret_cast<float*>(sc + L.c_raw);  // in place: every lane has read its elements before it writes them
-  ln.rows = M;
-  ln.r = g.r;
-  ln.eps = lw->ln_eps > 0.f ? lw->ln_eps : 1e-5f;
-  if (!hip_ok(launch_layer_norm_rows(ln, st))) return MTLA_ERR_HIP;
-  if (!hip_ok(launch_append(ap, g.dtype, st))) return MTLA_ERR_HIP;
-  ChunkStageArgs cs;
-  cs.cache_c = cache_c;
-  cs.cache_kr = cache_kr;
-  cs.tail_prev = tail_prev;
-  cs.prefix_owner = c->prefix_owner;  // mtla_set_shared_prefix: past slots of a common prompt come from their owner
-  cs.prefix_slots = c->prefix_slots;
-  cs.prefix_rows = c->cfg.max_batch;
-  cs.pos0 = pos0;
-  cs.c = sc + L.c;
-  cs.c32 = reinterpret_cast<const float*>(sc + L.c_raw);
-  cs.kr = sc + L.kr;
-  cs.w = w;
-  cs.n_new = n_new;
-  cs.cprime = ws + CL.cprime;
-  cs.kr16 = ws + CL.kr16;
-  cs.status = reinterpret_cast<int32_t*>(workspace);
-  cs.batch = batch;
-  cs.T = T;
-  cs.r = g.r;
-  cs.d_rope = g.d_rope;
-  cs.stride = g.stride;
-  cs.max_slots = g.max_slots;
-  cs.past_pitch = max_past_slots;
-  if (!hip_ok(launch_chunk_stage(cs, st))) return MTLA_ERR_HIP;
-  const bool timed = c->prof_n < (int)c->ev_start.size();
-  EventPair ev;
-  if (timed) {
-    ev.start = c->ev_start[c->prof_n];
-    ev.stop = c->ev_stop[c->prof_n++];
-  }
-  if (!hip_ok(launch_prefill_explicit(ex, st, ev))) return MTLA_ERR_HIP;
   return hip_ok(launch_gemm_nt(gy, st)) ? MTLA_OK : MTLA_ERR_HIP;
 }
 
@@ -1157,66 +1165,18 @@ mtla_status mtla_prefill_chunk_attn_paged(mtla_ctx* c, const void* cache_c, cons
   const size_t rows = (size_t)batch * ((size_t)max_past_slots + T);
   if (rows > ((size_t)1 << 24)) return MTLA_ERR_UNSUPPORTED;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  char* ws = reinterpret_cast<char*>(chunk_workspace);
-  const ChunkLayout L = chunk_layout(c, rows);
-
   ExplicitArgs ex;
-  ex.q = q;
-  ex.q_rope = q_rope;
-  ex.cprime = ws + L.cprime;
-  ex.kr = nullptr;
-  ex.w_uk = w_uk;
-  ex.w_uv = w_uv;
-  ex.seq_len = n_new;
-  ex.kx = ws + L.kx;
-  ex.vx = ws + L.vx;
-  ex.w_kT = ws + L.w_kT;
-  ex.w_v16 = ws + L.w_v16;
-  ex.kr16 = ws + L.kr16;
-  ex.out = out;
-  ex.batch = batch;
-  ex.T = T;
-  ex.n_heads = g.n_heads;
-  ex.d_head = g.d_head;
-  ex.r = g.r;
-  ex.d_rope = g.d_rope;
-  ex.stride = g.stride;
-  ex.scale_log2 = c->scale * 1.4426950408889634f;
+  PrefillFrontArgs fa;
+  chunk_args(c, cache_c, cache_kr, q, q_rope, cc, kr, n_new, batch, T, max_past_slots, w_uk, w_uv,
+             reinterpret_cast<char*>(chunk_workspace), workspace, page_table, ex, fa);
+  fa.cs.tail_prev = tail_prev;
+  fa.cs.pos0 = pos0;
+  fa.cs.w = w;
   ex.pos0 = pos0;
-  ex.past_pitch = max_past_slots;
+  ex.out = out;
   if (!prefill_explicit_supported(ex)) return MTLA_ERR_UNSUPPORTED;
-
-  ChunkStageArgs cs;
-  cs.cache_c = cache_c;
-  cs.cache_kr = cache_kr;
-  cs.tail_prev = tail_prev;
-  cs.prefix_owner = c->prefix_owner;  // mtla_set_shared_prefix: past slots of a common prompt come from their owner
-  cs.prefix_slots = c->prefix_slots;
-  cs.prefix_rows = c->cfg.max_batch;
-  cs.pages = page_map(c, page_table);
-  cs.pos0 = pos0;
-  cs.c = cc;
-  cs.kr = kr;
-  cs.w = w;
-  cs.n_new = n_new;
-  cs.cprime = ws + L.cprime;
-  cs.kr16 = ws + L.kr16;
-  cs.status = reinterpret_cast<int32_t*>(workspace);
-  cs.batch = batch;
-  cs.T = T;
-  cs.r = g.r;
-  cs.d_rope = g.d_rope;
-  cs.stride = g.stride;
-  cs.max_slots = g.max_slots;
-  cs.past_pitch = max_past_slots;
-  if (!hip_ok(launch_chunk_stage(cs, st))) return MTLA_ERR_HIP;
-  const bool timed = c->prof_n < (int)c->ev_start.size();
-  EventPair ev;
-  if (timed) {
-    ev.start = c->ev_start[c->prof_n];
-    ev.stop = c->ev_stop[c->prof_n++];
-  }
-  return hip_ok(launch_prefill_explicit(ex, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
+  if (!hip_ok(launch_prefill_front(fa, 0, st))) return MTLA_ERR_HIP;
+  return hip_ok(launch_prefill_explicit(ex, st, next_event(c))) ? MTLA_OK : MTLA_ERR_HIP;
 }
 
 mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, const void* cc,
@@ -1293,35 +1253,11 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
       }
     }
     if (prefill_explicit_supported(ex) && L.qcat + need <= L.cprime) {
-      // partial states and RoPE keys as fp16 in one pass (the staging kernel of the continuing form,
-      // with nothing in front of the rows)
-      ChunkStageArgs cs;
-      cs.cache_c = cs.cache_kr = nullptr;
-      cs.tail_prev = nullptr;
-      cs.pos0 = nullptr;
-      cs.c = cc;
-      cs.kr = kr;
-      cs.w = w;
-      cs.n_new = seq_lens;
-      cs.cprime = ws + L.cprime;
-      cs.kr16 = ex.kr16;
-      cs.status = nullptr;
-      cs.batch = batch;
-      cs.T = T;
-      cs.r = g.r;
-      cs.d_rope = g.d_rope;
-      cs.stride = g.stride;
-      cs.max_slots = g.max_slots;
-      cs.past_pitch = 0;
-      ex.kr_staged = 1;
-      if (!hip_ok(launch_chunk_stage(cs, st))) return MTLA_ERR_HIP;
-      const bool timed = c->prof_n < (int)c->ev_start.size();
-      EventPair ev;
-      if (timed) {
-        ev.start = c->ev_start[c->prof_n];
-        ev.stop = c->ev_stop[c->prof_n++];
-      }
-      if (!hip_ok(launch_prefill_explicit(ex, st, ev))) return MTLA_ERR_HIP;
+      PrefillFrontArgs fa;
+      front_args(c, ex, cc, kr, seq_lens, fa);
+      fa.cs.w = w;
+      if (!hip_ok(launch_prefill_front(fa, 0, st))) return MTLA_ERR_HIP;
+      if (!hip_ok(launch_prefill_explicit(ex, st, next_event(c)))) return MTLA_ERR_HIP;
       if (!latent_only) return MTLA_OK;
       out = nullptr;  // written; what follows reuses the scratch in stream order and fills out_latent
     } else {
@@ -1351,13 +1287,7 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
     ex.scale_log2 = c->scale * 1.4426950408889634f;
     if (prefill_f32_supported(ex)) {
       if (!hip_ok(launch_partial_states(ps, g.dtype, st))) return MTLA_ERR_HIP;
-      const bool timed = c->prof_n < (int)c->ev_start.size();
-      EventPair ev;
-      if (timed) {
-        ev.start = c->ev_start[c->prof_n];
-        ev.stop = c->ev_stop[c->prof_n++];
-      }
-      return hip_ok(launch_prefill_f32(ex, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
+      return hip_ok(launch_prefill_f32(ex, st, next_event(c))) ? MTLA_OK : MTLA_ERR_HIP;
     }
   }
   // the vector-ALU kernels (shapes the matrix-core kernels do not take) index a grid dimension by the row

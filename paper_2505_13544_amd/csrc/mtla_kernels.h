@@ -39,8 +39,6 @@ struct AppendArgs {
   int32_t* slot_out;
   int32_t* status;  // workspace header word
   int r, d_rope, d_hyper, stride, max_slots, n_new_max, batch;
-  const float* c_merge_f32 = nullptr;  // bulk append (matrix-core kernel): the same latents unrounded, [batch, n_new_max, r];
-                                       // the merge then folds these and rounds the cache row once
   int c_new_f32;    // fused decode front only: c_new holds fp32 latents (cache storage stays bf16) ...
   float ln_eps;     // ... and, if > 0, they are layer-normalised over r first (the normalisation the
   const void* ln_gamma;  //     paper applies to C = X W_r), times gamma plus beta (storage type, [r]) if given
@@ -125,25 +123,30 @@ struct CombineArgs {
 struct ExplicitArgs {
   const void* q;       // [B, T, n_heads, d_head]
   const void* q_rope;  // [B, T, n_heads, d_rope]
-  const void* cprime;  // [B, T, r] partial slot states (fp16)
-  const void* kr;      // [B, T, d_rope]
+  const void* cprime;  // [B, T, r] partial slot states (fp16; fp32 form: fp32)
+  const void* kr;      // [B, T, d_rope]  (fp32 form)
   const void* w_uk;    // [n_heads, r, d_head]
   const void* w_uv;    // [n_heads, d_head, r]
   const int32_t* seq_len;  // [B] or NULL
-  void* w_kT;          // scratch [n_heads, d_head, r] fp16: W_K^(h) with the latent index innermost
-  void* w_v16;         // scratch [n_heads, d_head, r] fp16 copy of w_uv
-  void* kr16;          // scratch [B, T, d_rope] fp16 copy of kr
+  void* w_kT;          // [n_heads, d_head, r] fp16: W_K^(h) with the latent index innermost
+  void* w_v16;         // [n_heads, d_head, r] fp16 copy of w_uv
+  void* kr16;          // [B, T, d_rope] fp16 copy of kr
   void* kx;            // scratch [B, T, n_heads, d_head] fp16
   void* vx;            // scratch [B, T, n_heads, d_head] fp16
   float* out;          // [B, T, n_heads, d_head]
   int batch, T, n_heads, d_head, r, d_rope, stride;
   float scale_log2;    // softmax_scale * log2(e)
   // Continuing sequences (a chunk of T new tokens behind pos0[b] earlier ones): cprime, kr16, kx and vx
-  // then hold past_pitch + T rows per sequence, the final states (and keys) of the slots completed
-  // before the chunk in front of the chunk's own rows.  pos0 == NULL: whole sequences, past_pitch 0.
+  // then have past_pitch + T rows per sequence, the final states (and keys) of the pos0[b] / s slots completed
+  // before the chunk and right behind them the chunk's own rows.  pos0 == NULL: whole sequences, past_pitch 0.
   const int32_t* pos0 = nullptr;
   int past_pitch = 0;
-  int kr_staged = 0;       // kr16 (and cprime) were written by the staging kernel: only the weights are converted
+  // If set, the attention launch puts the append's state in place (nothing reads the old one any more): length
+  // advance[b] = pos0[b] + new rows and tail shadow tail_c[b] = tail_next[b], where the sequence holds that many.
+  int32_t* advance = nullptr;
+  float* tail_c = nullptr;
+  const float* tail_next = nullptr;
+  long long capacity = 0;  // tokens a sequence may hold
   int q_f16 = 0;           // q and q_rope are fp16 and already carry scale_log2 (the layer's own projections)
   void* out16 = nullptr;   // if set: the output goes here as fp16 [B, T, n_heads, d_head] instead of to `out`
   // > 0 (attention launch only): the latent-space output.  The values are the partial states
@@ -154,19 +157,34 @@ struct ExplicitArgs {
   float* out_latent = nullptr;  // if set (whole sequences only): also softmax . C_hat' [B, T, n_heads, r], by such a launch
 };
 
-// C[z] = A W[z]^T on the matrix cores (see gemm_nt_kernel for the ways out).
-struct GemmArgs {
-  const void* A = nullptr;                 // [M, K]
-  const void* W[2] = {nullptr, nullptr};   // [N, K] each
-  void* C[2] = {nullptr, nullptr};         // [M, N] each
-  int M = 0, N = 0, K = 0, nz = 1;
-  int in_bf16 = 0;                         // A and W: 0 fp16, 1 bf16
-  int epi = 0;                             // 0 fp16 = scale * acc, 1 fp16 = scale * RoPE(acc), 3 fp32
+// C = A W^T on the matrix cores for up to four W that share A (see gemm_nt_kernel for the ways out).
+struct GemmSegment {
+  const void* W = nullptr;  // [N, K]
+  void* C = nullptr;        // [M, N]
+  int N = 0;
+  int epi = 0;              // 0 fp16 = scale * acc, 1 fp16 = scale * RoPE(acc), 2 bf16 = RoPE(acc), 3 fp32 = acc
   float scale = 1.f;
-  int wide = -1;                           // tile columns: -1 chosen by the launcher, 0 128, 1 256
-  int N1 = 0;                              // epi 1: columns of the second product A W[1]^T -> C[1] bf16 = RoPE(acc)
-  const float2* rope_cs = nullptr;         // epi 1: [M, d_rope / 2] (cos, sin) of every row's angles
+};
+// Which rows of A hold something: of every past + T rows the first pos0[b] / stride (slots of the past) + n_new[b] (new
+// rows).  Both arrays NULL: all rows.
+struct GemmRows {
+  const int32_t* pos0 = nullptr;
+  const int32_t* n_new = nullptr;
+  int past = 0, T = 1, stride = 1;
+  int zeros = 0;            // rows of tiles without such rows: 1 written as zeros, 0 left alone
+};
+struct GemmArgs {
+  static constexpr int kSegments = 4;
+  const void* A = nullptr;  // [M, K]
+  int M = 0, K = 0, n_seg = 1;
+  GemmSegment seg[kSegments];
+  int in_bf16 = 0;          // A and W: 0 fp16, 1 bf16
+  const float2* rope_cs = nullptr;  // epi 1, 2: [M, d_rope / 2] (cos, sin) of every row's angles
   int d_rope = 0;
+  GemmRows rows;
+  // set by the launcher; xcds: the XCDs that the row blocks are dealt to (8, or 1 for few of them)
+  int col_blocks = 0;
+  unsigned row_blocks = 0, xcds = 1;
 };
 
 struct RopeTableArgs {
@@ -185,10 +203,9 @@ struct ChunkStageArgs {
   const float* tail_prev;   // [B, r] value of the slot in progress before the chunk (read iff pos0 % s != 0)
   const int32_t* pos0;      // [B] tokens before the chunk, or NULL: whole sequences (past_pitch 0)
   const void* c;            // [B, T, r]      bf16, the chunk
-  const float* c32 = nullptr;  // the same unrounded, or NULL
   const void* kr;           // [B, T, d_rope] bf16
   const float* w;           // [B, T] merge weights
-  const int32_t* n_new;     // [B] or NULL: rows at and past n_new[b] are padding (their states are written as zeros)
+  const int32_t* n_new;     // [B] or NULL: rows at and past n_new[b] are padding (their states are not written)
   void* cprime;             // out [B, past_pitch + T, r]      fp16
   void* kr16;               // out [B, past_pitch + T, d_rope] fp16
   int32_t* status;          // sticky device status word
@@ -200,25 +217,30 @@ struct ChunkStageArgs {
   PageMap pages;         // paged storage of cache_c / cache_kr (table NULL: contiguous)
 };
 
-// Row-wise pieces of the whole-layer prefill: LayerNorm of the latent rows; saving the state the
-// chunk starts from and converting W_O.
-struct LayerRowsArgs {
-  const float* raw = nullptr;   // [rows, r] x W_r
-  const void* gamma = nullptr;  // [r] bf16 or NULL
-  const void* beta = nullptr;
-  void* c = nullptr;            // [rows, r] bf16
-  float* c32 = nullptr;         // [rows, r] the same unrounded (may be `raw` itself), or NULL
-  size_t rows = 0;
-  int r = 0;
-  float eps = 1e-5f;
-  const int32_t* seq_len = nullptr;  // prep: [batch] -> pos0
-  const float* tail_c = nullptr;     //       [batch, r] -> tail_prev
-  int32_t* pos0 = nullptr;
-  float* tail_prev = nullptr;
-  const void* w_o = nullptr;         //       [n_wo] bf16 -> w_o16 fp16
+// One launch in front of a prefill's matrix products (see prefill_front.hip).
+struct PrefillFrontArgs {
+  AppendArgs ap;             // modes 1 and 2; mode 2: c_new holds unrounded latents before their normalisation (ln_*)
+  ChunkStageArgs cs;
+  int32_t* pos0_out = nullptr;  // modes 1 and 2: [batch] tokens before the call
+  float* tail_next = nullptr;   // modes 1 and 2: [batch, r] tail shadow after the call
+  const void* w_uk = nullptr;   // [n_heads, r, d_head] -> w_kT [n_heads, d_head, r] fp16
+  const void* w_uv = nullptr;   // [n_heads, d_head, r] -> w_v16 fp16
+  void* w_kT = nullptr;
+  void* w_v16 = nullptr;
+  const void* w_o = nullptr;    // [n_wo] -> w_o16 fp16
   void* w_o16 = nullptr;
   size_t n_wo = 0;
-  int batch = 0;
+  int n_heads = 0, d_head = 0;
+  unsigned groups = 1, n_main = 0, n_conv = 0;  // set by the launcher
+};
+
+// The sequence state a continuing prefill starts from, saved in front of an append of its own.
+struct SaveStateArgs {
+  const int32_t* seq_len;  // [batch] -> pos0
+  const float* tail_c;     // [batch, r] -> tail_prev
+  int32_t* pos0;
+  float* tail_prev;
+  int batch, r;
 };
 
 // Beam search: destination sequence b continues source sequence src_index[b].
@@ -304,8 +326,12 @@ hipError_t launch_reorder(const ReorderArgs& a, hipStream_t st);
 hipError_t launch_fork_paged(const ForkArgs& a, hipStream_t st);
 hipError_t launch_stream_read(const void* p, size_t bytes, int32_t* out, int workgroups, hipStream_t st);
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t st);
-// a bulk append of these shapes runs on the matrix cores (the only bulk kernel that reads AppendArgs::c_merge_f32)
-bool append_bulk_mfma_supported(const AppendArgs& a, int dtype);
+// a bulk append of these shapes runs on the matrix cores
+bool append_bulk_supported(const AppendArgs& a, int dtype);
+hipError_t launch_append_bulk(const AppendArgs& a, hipStream_t st);
+// mode 0: merge weights given, 1: with the append, 2: with the append of unrounded latents (append_bulk_supported shapes)
+hipError_t launch_prefill_front(const PrefillFrontArgs& a, int mode, hipStream_t st);
+hipError_t launch_save_state(const SaveStateArgs& a, hipStream_t st);
 hipError_t launch_absorb(const AbsorbArgs& a, int dtype, hipStream_t st);
 // one-token append and matrix-core absorb of a decode step in a single launch (bf16 storage)
 bool decode_front_supported(const AppendArgs& ap, const AbsorbArgs& ab);
@@ -333,9 +359,6 @@ hipError_t launch_layer_front(const LayerFrontArgs& a, hipStream_t st);
 hipError_t launch_layer_out(const LayerOutArgs& a, hipStream_t st);
 bool prefill_explicit_supported(const ExplicitArgs& a);
 hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
-hipError_t launch_chunk_stage(const ChunkStageArgs& a, hipStream_t st);
-hipError_t launch_layer_norm_rows(const LayerRowsArgs& a, hipStream_t st);
-hipError_t launch_layer_prefill_prep(const LayerRowsArgs& a, hipStream_t st);
 bool gemm_nt_supported(const GemmArgs& a);
 hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st);

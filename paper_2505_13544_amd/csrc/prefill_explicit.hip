@@ -18,9 +18,7 @@
 // apart from values below 6e-5; the queries are multiplied by log2(e) / sqrt(d_h) before their one
 // rounding to half.
 //
-// Three kernels:
-//   to_f16_kernel         W_K^(h) with the contracted (latent) index innermost, like W_V^(h), and the
-//                         RoPE keys, as fp16
+// Two kernels behind the front launch (prefill_front.hip: partial states, RoPE keys and weights as fp16):
 //   gemm_nt_kernel        K = C_hat' W_K, V = C_hat' W_V for all T rows: a plain MFMA GEMM, 256 x 128
 //                         tile, operands streamed from memory straight into LDS (also the projections
 //                         of the whole-layer prefill, with rotation / scaling on the way out)
@@ -28,6 +26,8 @@
 //                         keys and values of 32 columns at a time stream from memory straight into
 //                         LDS and are shared by the four wavefronts (32 query rows each, queries in
 //                         registers)
+#include <type_traits>
+
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -42,9 +42,6 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));  // staging registers (a plain vector type: promoted reliably)
 typedef short4_t __attribute__((address_space(3))) * lds_short4_ptr;
 
-__device__ __forceinline__ uint16_t bf16_bits_to_f16_bits(uint16_t v) {
-  return __builtin_bit_cast(uint16_t, static_cast<_Float16>(__uint_as_float(uint32_t(v) << 16)));
-}
 // 8 bf16 values, each times `scale` -> 8 fp16 values
 __device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v, float scale = 1.f) {
   u32x4_t o;
@@ -52,103 +49,6 @@ __device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v, float scale = 1.f)
   for (int i = 0; i < 4; ++i)
     o[i] = pack_f16x2(__uint_as_float(v[i] << 16) * scale, __uint_as_float(v[i] & 0xffff0000u) * scale);
   return o;
-}
-
-// w_kT[h][d][n] = fp16(w_uk[h][n][d]),  w_v16[h][d][n] = fp16(w_uv[h][d][n]),  kr16 = fp16(kr)
-__global__ void to_f16_kernel(const uint16_t* w_uk, const uint16_t* w_uv, uint16_t* w_kT, uint16_t* w_v16,
-                              const uint16_t* kr, uint16_t* kr16, int n_heads, int r, int dh, size_t n_kr) {
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  const size_t n_w = (size_t)n_heads * r * dh;
-  if (idx < n_w) {
-    const int n = int(idx % r), d = int((idx / r) % dh), h = int(idx / ((size_t)r * dh));
-    w_kT[idx] = bf16_bits_to_f16_bits(w_uk[((size_t)h * r + n) * dh + d]);
-    w_v16[idx] = bf16_bits_to_f16_bits(w_uv[idx]);
-  } else if (idx - n_w < n_kr) {
-    kr16[idx - n_w] = bf16_bits_to_f16_bits(kr[idx - n_w]);
-  }
-}
-
-// Continuing sequences: the rows the key / value product and the attention read, 8 elements per thread.
-//   part 1  rows k < past_pitch of sequence b: slot k of the cache (latent and RoPE key) if k < pos0 / s,
-//           else zeros (never read as columns)
-//   part 2  the chunk's partial states: run jl holds the chunk's tokens of slot pos0 / s + jl; the first
-//           run continues the slot in progress from tail_prev when pos0 % s != 0
-//   part 3  the chunk's RoPE keys
-__global__ __launch_bounds__(kBlock) void chunk_stage_kernel(ChunkStageArgs a) {
-  const int r8 = a.r / 8, d8 = a.d_rope / 8, s = a.stride, T = a.T, past = a.past_pitch, Tp = past + T;
-  const int n_runs = (T + s - 1) / s + 1;
-  const size_t n1 = (size_t)a.batch * past * (r8 + d8), n2 = (size_t)a.batch * n_runs * r8, n3 = (size_t)a.batch * T * d8;
-  size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  const uint16_t* cache_c = reinterpret_cast<const uint16_t*>(a.cache_c);
-  const uint16_t* cache_kr = reinterpret_cast<const uint16_t*>(a.cache_kr);
-  uint16_t* cp = reinterpret_cast<uint16_t*>(a.cprime);
-  uint16_t* kr16 = reinterpret_cast<uint16_t*>(a.kr16);
-  auto start_of = [&](int b) -> int {  // tokens before the chunk, forced into what the arrays hold
-    if (!a.pos0) return 0;             // whole sequences
-    const int p0 = a.pos0[b];
-    if (p0 < 0 || p0 / s > past || p0 / s > a.max_slots) {
-      *a.status = 1;  // MTLA_ERR_INVALID_ARG
-      const int lim = past < a.max_slots ? past : a.max_slots;
-      return lim * s;
-    }
-    return p0;
-  };
-  if (idx < n1) {
-    const int piece = int(idx % (r8 + d8)), k = int(idx / (r8 + d8) % past), b = int(idx / ((size_t)(r8 + d8) * past));
-    const bool live = k < start_of(b) / s;
-    int sb = b;  // the sequence whose rows hold slot k: b itself, or the owner of a prompt it shares
-    if (a.prefix_owner && k < a.prefix_slots[b]) {
-      const int o = a.prefix_owner[b];
-      sb = o < 0 ? 0 : (o < a.prefix_rows ? o : a.prefix_rows - 1);
-    }
-    u32x4_t v = {0u, 0u, 0u, 0u};
-    const size_t src_row = live ? cache_row(a.pages, sb, k, a.max_slots) : 0;
-    if (piece < r8) {
-      if (live) v = bf16x8_to_f16x8(*reinterpret_cast<const u32x4_t*>(cache_c + src_row * a.r + 8 * piece));
-      *reinterpret_cast<u32x4_t*>(cp + ((size_t)b * Tp + k) * a.r + 8 * piece) = v;
-    } else {
-      const int pd = piece - r8;
-      if (live) v = bf16x8_to_f16x8(*reinterpret_cast<const u32x4_t*>(cache_kr + src_row * a.d_rope + 8 * pd));
-      *reinterpret_cast<u32x4_t*>(kr16 + ((size_t)b * Tp + k) * a.d_rope + 8 * pd) = v;
-    }
-    return;
-  }
-  idx -= n1;
-  if (idx < n2) {
-    const int piece = int(idx % r8), jl = int(idx / r8 % n_runs), b = int(idx / ((size_t)r8 * n_runs));
-    const int ph = start_of(b) % s;
-    int n = jl * s - ph;
-    const int n_end = n + s < T ? n + s : T;
-    float run[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (jl == 0 && ph > 0) load8(a.tail_prev + (size_t)b * a.r + 8 * piece, run);
-    if (n < 0) n = 0;
-    const bf16* c = reinterpret_cast<const bf16*>(a.c);
-    const int len = a.n_new ? a.n_new[b] : T;
-    for (; n < n_end; ++n) {
-      const size_t row = (size_t)b * T + n;
-      u32x4_t o = {0u, 0u, 0u, 0u};  // padding rows hold zeros: they meet zero weights in the tiles of live rows
-      if (n < len) {
-        float cv[8];
-        if (a.c32) load8(a.c32 + row * a.r + 8 * piece, cv);
-        else load8(c + row * a.r + 8 * piece, cv);
-        const float w = a.w[row];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          run[2 * i] += w * cv[2 * i];
-          run[2 * i + 1] += w * cv[2 * i + 1];
-          o[i] = pack_f16x2(run[2 * i], run[2 * i + 1]);
-        }
-      }
-      *reinterpret_cast<u32x4_t*>(cp + ((size_t)b * Tp + past + n) * a.r + 8 * piece) = o;
-    }
-    return;
-  }
-  idx -= n2;
-  if (idx < n3) {
-    const int pd = int(idx % d8), n = int(idx / d8 % T), b = int(idx / ((size_t)d8 * T));
-    *reinterpret_cast<u32x4_t*>(kr16 + ((size_t)b * Tp + past + n) * a.d_rope + 8 * pd) = bf16x8_to_f16x8(
-        *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.kr) + ((size_t)b * T + n) * a.d_rope + 8 * pd));
-  }
 }
 
 // ---- memory -> LDS without registers --------------------------------------------------------
@@ -208,50 +108,114 @@ __device__ __forceinline__ void barrier_only() {
 }
 
 // C[row][n] = sum_k A[row][k] W[n][k]   (A [M][K], W [N][K], C [M][N]; A and W both fp16 or both bf16,
-// K % 32 == 0, N % 8 == 0), fp32 accumulation, one of four ways out (GemmArgs::epi):
+// K % 32 == 0, N % 8 == 0), fp32 accumulation, one of three ways out (GemmSegment::epi):
 //   0  C fp16 = scale * acc                       (keys, values, queries)
-//   1  C fp16 = scale * RoPE(acc)                 (RoPE queries: row b*T + t is turned at pos0[b] + t; the
-//      cosines and sines come from a table, rope_cs[row][k]).  With N1 > 0 a second product rides
-//      along: columns N .. N + N1 - 1 are A W[1]^T, rotated the same way and stored as bf16 in C[1]
-//      ([M, N1]: the shared RoPE key, as it is stored in the cache); N is then a multiple of 128.
+//   1  C fp16 = scale * RoPE(acc), 2 the same as bf16 without the scale (RoPE queries, the shared RoPE key: row
+//      b*T + t is turned at pos0[b] + t; the cosines and sines come from a table, rope_cs[row][k])
 //   3  C fp32 = acc
-// Jobs = ceil(N/128) * ceil(M/256) * nz workgroups (z selects (W[z], C[z]): products that share A),
-// numbered so that the workgroups that read the same rows of A and of W run on one XCD.  256 x 128
-// tile; K is walked 32 at a time through three LDS stages of 24 KB.  Wavefront (wm, wn) owns a 128 x 64
-// quarter: W rows are the A operand, A rows the B operand, so a lane ends up with four consecutive
-// n of one row (two RoPE pairs).
-template <bool BF16, int EPI, int BN>  // BN = 128: four wavefronts, two workgroups per CU; 256: eight wavefronts, one
-__global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(GemmArgs a) {
+// A launch takes up to four products that share A ("segments", each with its own weights, columns and way out): a short
+// prompt's projections are one launch instead of four.
+// BM x BN tile; K is walked 32 at a time through NBUF LDS stages.  A wavefront owns a WM x WN part: W rows are the A
+// operand, A rows the B operand, so a lane ends up with four consecutive n of one row (two RoPE pairs).
+// Rows that hold nothing (GemmRows: padding of ragged sequences, slots of the past that a sequence does not have) are
+// left out: the row blocks are those of the sequences' rows in use, one after the other, so what is left over at the
+// end of the launch returns at once.  Where the caller wants zeros in such rows the blocks are the matrix's own.
+//
+// Tiles: 256 x 256 (eight wavefronts, one workgroup per CU: 1.0 PFLOP/s at K = 2048) where there are rows and columns
+// enough, smaller ones where they would leave units without work (launch_gemm picks by the work a unit gets).  129 rows
+// x 512 columns, K = 512: 17 us in two 256 x 256 tiles, 6 us in 64 x 64 ones.
+template <int BM, int BN>
+struct GemmGeom {
+  static constexpr int NWV = BM * BN >= 65536 ? 8 : 4, NT = 64 * NWV, BK = 32;
+  static constexpr int WCOLS = BN >= 128 ? BN / 64 : 2, WN = BN / WCOLS, WROWS = NWV / WCOLS, WM = BM / WROWS;
+  static constexpr int W_BYTES = BN * BK * 2, A_BYTES = BM * BK * 2, STAGE = W_BYTES + A_BYTES;
+  static constexpr int NBUF = BM >= 256 ? 3 : (BM == 128 ? 4 : 6), PF = NBUF - 1;
+  static constexpr int NLW = W_BYTES / 1024 / NWV, NLA = A_BYTES / 1024 / NWV, LOADS = NLW + NLA;  // loads per wavefront and stage
+  static constexpr int PER_CU = BM == 256 && BN == 256 ? 1 : 2;
+  static_assert(LOADS * (PF - 1) <= 15 && NLW >= 1 && NLA >= 1, "wait counts");
+};
+
+template <bool BF16, int BM, int BN>
+__global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU)) void gemm_nt_kernel(GemmArgs a) {
   typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-  constexpr int BM = 256, BK = 32, NBUF = 3, PF = NBUF - 1;
-  constexpr int NWV = 2 * BN / 64, NT = 64 * NWV, WCOLS = BN / 64;  // wavefronts: 2 row halves x BN/64 column strips
-  constexpr int W_BYTES = BN * BK * 2, A_BYTES = BM * BK * 2, STAGE = W_BYTES + A_BYTES;  // 8 or 16 KB + 16 KB
-  constexpr int NLW = W_BYTES / 1024 / NWV, NLA = A_BYTES / 1024 / NWV, LOADS = NLW + NLA;  // loads per wavefront and stage
+  using G = GemmGeom<BM, BN>;
+  constexpr int BK = G::BK, NBUF = G::NBUF, PF = G::PF, NWV = G::NWV, NT = G::NT, WN = G::WN, WM = G::WM;
+  constexpr int W_BYTES = G::W_BYTES, STAGE = G::STAGE, NLW = G::NLW, NLA = G::NLA, LOADS = G::LOADS;
+  constexpr int JM = WM / 16, IN = WN / 16;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * STAGE];
 
   const int M = a.M, K = a.K;
-  const int Nt = a.N + (EPI == 1 ? a.N1 : 0);  // all columns of the launch
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   // Job order: groups of four column blocks of the weights (1 MB at K = 512 and 128 columns, stays in
-  // L2) slowest, then the 256-row blocks of A, then the jobs of one row block inside the group; each
-  // XCD takes an eighth of that list.
-  const unsigned nz = (unsigned)a.nz;
-  const unsigned gx = (unsigned)((Nt + BN - 1) / BN), gy = (unsigned)((M + BM - 1) / BM), jobs = gridDim.x, w = blockIdx.x;
-  const unsigned job = jobs % 8 == 0 ? (w >> 3) + (w & 7) * (jobs >> 3) : w;
+  // L2) slowest, then the row blocks of A, then the jobs of one row block inside the group.  Row blocks are dealt to the
+  // eight XCDs in turn (workgroup w runs on XCD w % 8), so the workgroups that read the same rows of A run on one XCD
+  // and rows that hold nothing (ragged sequences) fall on all of them.
+  const unsigned gx = (unsigned)a.col_blocks, gy = a.row_blocks, w = blockIdx.x;
+  const unsigned nx = a.xcds, ry = (gy + nx - 1) / nx, job = w / nx;  // row blocks per XCD
   // groups of four column blocks, then one group with the blocks that are left
-  const unsigned full_jobs = (gx / 4u) * 4u * nz * gy;
+  const unsigned full_jobs = (gx / 4u) * 4u * ry;
   const bool in_full = job < full_jobs;
-  const unsigned gsz = in_full ? 4u : gx % 4u, per_group = nz * gsz * gy;
+  const unsigned gsz = in_full ? 4u : gx % 4u, per_group = gsz * ry;
   const unsigned first = in_full ? (job / per_group) * 4u : (gx / 4u) * 4u;
-  const unsigned rem = in_full ? job % per_group : job - full_jobs, inner = rem % (nz * gsz);
-  const int nb_all = (int)(first + inner / nz) * BN, rb = (int)(rem / (nz * gsz)) * BM;
-  const bool seg1 = EPI == 1 && nb_all >= a.N;  // the block belongs to the second product
-  const int z = seg1 ? 1 : (int)(inner % nz), nb = seg1 ? nb_all - a.N : nb_all, N = seg1 ? a.N1 : a.N;
+  const unsigned rem = in_full ? job % per_group : job - full_jobs;
+  const int ib = (int)(rem / gsz * nx + w % nx);  // row block
+  int rb = ib * BM, row_end = M;
+  bool work = rb < M;
+  if (a.rows.n_new || a.rows.pos0) {
+    work = false;
+    const GemmRows& q = a.rows;
+    const int Tp = q.past + q.T, n_seq = M / Tp;
+    auto used_rows = [&](int b) {
+      const int old = q.pos0 ? q.pos0[b] / q.stride : 0;
+      const int n = q.n_new ? (q.n_new[b] < q.T ? q.n_new[b] : q.T) : q.T;
+      return (old < q.past ? old : q.past) + (n > 0 ? n : 0);
+    };
+    if (q.zeros) {  // the block as it is; without rows of its own it only writes zeros
+      for (int b = rb / Tp; b < n_seq && b * Tp < rb + BM && !work; ++b) {
+        const int used = used_rows(b);
+        work = rb < b * Tp + used && used > 0;
+      }
+      if (rb >= M) return;
+    } else {        // block ib of those that the sequences use, each sequence's from its first row on
+      int before = 0;
+      for (int b0 = 0; b0 < n_seq && !work; b0 += kWave) {
+        const int used = b0 + lane < n_seq ? used_rows(b0 + lane) : 0;
+        const int n = (used + BM - 1) / BM;
+        int upto = n;  // blocks of sequences b0 .. b0 + lane
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+          const int v = __shfl_up(upto, off, kWave);
+          upto += lane >= off ? v : 0;
+        }
+        const unsigned long long here = __ballot(ib - before < upto);
+        if (here) {
+          const int at = __builtin_ctzll(here);
+          rb = (b0 + at) * Tp + (ib - before - (__shfl(upto, at, kWave) - __shfl(n, at, kWave))) * BM;
+          row_end = (b0 + at) * Tp + __shfl(used, at, kWave);
+          work = true;
+        }
+        before += __shfl(upto, kWave - 1, kWave);
+      }
+      if (!work) return;
+      rb = __builtin_amdgcn_readfirstlane(rb);
+      row_end = __builtin_amdgcn_readfirstlane(row_end);
+    }
+  } else if (!work) {
+    return;
+  }
+  // the segment the column block belongs to
+  int cb = (int)(first + rem % gsz), z = 0;
+  while (z + 1 < a.n_seg && cb >= (a.seg[z].N + BN - 1) / BN) {
+    cb -= (a.seg[z].N + BN - 1) / BN;
+    ++z;
+  }
+  const GemmSegment sg = a.seg[z];
+  const int nb = cb * BN, N = sg.N, epi = sg.epi;
   const uint16_t* A = reinterpret_cast<const uint16_t*>(a.A);
-  const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W[z]);
-  const int wn = 64 * (wv % WCOLS), wm = 128 * (wv / WCOLS);
+  const uint16_t* W = reinterpret_cast<const uint16_t*>(sg.W);
+  const int wn = WN * (wv % G::WCOLS), wm = WM * (wv / G::WCOLS);
 
   // what this thread brings in of every stage: 1 KB chunk c of a region = rows 16 c .. 16 c + 15 (4
   // pieces of 8 k each); wavefront wv fills chunks wv, wv + NWV, ..
@@ -267,7 +231,7 @@ __global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(Gemm
 #pragma unroll
   for (int i = 0; i < NLA; ++i) {
     const int row = rb + 16 * (wv + NWV * i) + prow;
-    asrc[i] = A + (size_t)(row < M ? row : M - 1) * K + psrc;
+    asrc[i] = A + (size_t)(row < row_end ? row : row_end - 1) * K + psrc;
   }
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
   auto issue = [&](int st) {  // stage st: k = 32 st ..
@@ -280,13 +244,13 @@ __global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(Gemm
   // where this lane reads: rows 16 i + l16 of a quarter, logical piece g
   const uint32_t frag_off = (uint32_t)(l16 * 64 + ((g ^ swz_rows16<4>(l16)) << 4));
 
-  float4_t acc[8][4];  // [token tile][n tile]
+  float4_t acc[JM][IN];  // [token tile][n tile]
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
+  for (int j = 0; j < JM; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[j][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < IN; ++i) acc[j][i] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int n_stages = K / BK;
+  const int n_stages = work ? K / BK : 0;
 #pragma unroll
   for (int st = 0; st < PF; ++st)
     if (st < n_stages) issue(st);
@@ -297,15 +261,15 @@ __global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(Gemm
     if (st + PF < n_stages) issue(st + PF);  // into the buffer stage st-1 was read from
     const unsigned char* wb = lds + (st % NBUF) * STAGE + wn * 64 + frag_off;
     const unsigned char* ab = lds + (st % NBUF) * STAGE + W_BYTES + wm * 64 + frag_off;
-    u32x4_t wf[4], af[8];
+    u32x4_t wf[IN], af[JM];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) wf[i] = *reinterpret_cast<const u32x4_t*>(wb + i * 1024);
+    for (int i = 0; i < IN; ++i) wf[i] = *reinterpret_cast<const u32x4_t*>(wb + i * 1024);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) af[j] = *reinterpret_cast<const u32x4_t*>(ab + j * 1024);
+    for (int j = 0; j < JM; ++j) af[j] = *reinterpret_cast<const u32x4_t*>(ab + j * 1024);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < JM; ++j)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < IN; ++i) {
         if constexpr (BF16)
           acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[i]),
                                                               __builtin_bit_cast(bf16x8_t, af[j]), acc[j][i], 0, 0, 0);
@@ -315,66 +279,57 @@ __global__ __launch_bounds__(2 * BN, BN == 128 ? 2 : 1) void gemm_nt_kernel(Gemm
       }
   }
 
-  // ---- rotation: the lane's columns n .. n+3 are two pairs of one head
-  if constexpr (EPI == 1) {
-    const int half = a.d_rope / 2;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int row = rb + wm + 16 * j + l16;
-      row = row < M ? row : M - 1;
-      const float4* cs_row = reinterpret_cast<const float4*>(a.rope_cs + (size_t)row * half);  // (cos, sin) per pair
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int jn = (nb + wn + 16 * i + 4 * g) % a.d_rope;  // element inside the head, a multiple of 4
-        const float4 cs = cs_row[jn / 4];                      // pairs jn/2 and jn/2 + 1
-        const float e0 = acc[j][i][0], e1 = acc[j][i][1], e2 = acc[j][i][2], e3 = acc[j][i][3];
-        acc[j][i] = float4_t{e0 * cs.x - e1 * cs.y, e0 * cs.y + e1 * cs.x, e2 * cs.z - e3 * cs.w, e2 * cs.w + e3 * cs.z};
-      }
-      __builtin_amdgcn_sched_barrier(0);  // one row's table entries in registers at a time
-    }
-  }
-
   // ---- the tile leaves through LDS, RP rows at a time (as many as the stage buffers hold), so that
-  // memory sees whole row segments of 256 bytes or more
-  constexpr int ES = EPI == 3 ? 4 : 2;                       // bytes per output element
-  constexpr int CS = ES * BN + 16;                           // LDS row pitch
-  constexpr int RP = NBUF * STAGE / CS >= 256 ? 256 : (NBUF * STAGE / CS >= 128 ? 128 : 64);
-  static_assert(RP * CS <= NBUF * STAGE, "the rows of a pass fit in the stage buffers");
-  constexpr int PPR = BN * ES / 16;                          // 16-byte pieces per row
-  static_assert(RP * PPR % NT == 0, "whole rounds of stores");
-  unsigned char* Cb = reinterpret_cast<unsigned char*>(a.C[z]);
-  const float sc = a.scale;
+  // memory sees whole row segments of 128 bytes or more
+  unsigned char* Cb = reinterpret_cast<unsigned char*>(sg.C);
+  const float sc = sg.scale;
   barrier_only();  // every wavefront is done with the last stage
+  auto way_out = [&](auto kind) {
+    constexpr int EPI = decltype(kind)::value;
+    constexpr int ES = EPI == 3 ? 4 : 2;                       // bytes per output element
+    constexpr int CS = ES * BN + 16;                           // LDS row pitch
+    constexpr int RP = BM >= 256 && NBUF * STAGE / CS >= 256 ? 256 : (BM >= 128 && NBUF * STAGE / CS >= 128 ? 128 : 64);
+    static_assert(RP * CS <= NBUF * STAGE && RP <= BM, "the rows of a pass fit in the stage buffers");
+    constexpr int PPR = BN * ES / 16;                          // 16-byte pieces per row
+    static_assert(RP * PPR % NT == 0, "whole rounds of stores");
 #pragma unroll
-  for (int pass = 0; pass < BM / RP; ++pass) {
+    for (int pass = 0; pass < BM / RP; ++pass) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int row = wm + 16 * j;                           // wavefront-uniform
-      if (row / RP != pass) continue;
-      unsigned char* lrow = lds + (row - RP * pass + l16) * CS;
+      for (int j = 0; j < JM; ++j) {
+        const int row = wm + 16 * j;                           // wavefront-uniform
+        if (row / RP != pass) continue;
+        unsigned char* lrow = lds + (row - RP * pass + l16) * CS;
+        const int grow = rb + row + l16 < row_end ? rb + row + l16 : row_end - 1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int col = wn + 16 * i + 4 * g;
-        if constexpr (EPI == 3) {
-          *reinterpret_cast<float4_t*>(lrow + 4 * col) = acc[j][i];
-        } else {
-          uint2 o;
-          if (seg1) o = make_uint2(pack_bf16x2(acc[j][i][0], acc[j][i][1]), pack_bf16x2(acc[j][i][2], acc[j][i][3]));
-          else o = make_uint2(pack_f16x2(sc * acc[j][i][0], sc * acc[j][i][1]), pack_f16x2(sc * acc[j][i][2], sc * acc[j][i][3]));
-          *reinterpret_cast<uint2*>(lrow + 2 * col) = o;
+        for (int i = 0; i < IN; ++i) {
+          const int col = wn + 16 * i + 4 * g;
+          float4_t o = acc[j][i];
+          if constexpr (EPI == 1 || EPI == 2) {  // rotation: the lane's columns are two pairs of one head
+            const int jn = (nb + col) % a.d_rope;              // element inside the head, a multiple of 4
+            const float4_t cs = *reinterpret_cast<const float4_t*>(a.rope_cs + (size_t)grow * (a.d_rope / 2) + jn / 2);  // (cos, sin) of both
+            o = float4_t{o[0] * cs[0] - o[1] * cs[1], o[0] * cs[1] + o[1] * cs[0], o[2] * cs[2] - o[3] * cs[3], o[2] * cs[3] + o[3] * cs[2]};
+          }
+          if constexpr (EPI == 3) *reinterpret_cast<float4_t*>(lrow + 4 * col) = o;
+          else if constexpr (EPI == 2) *reinterpret_cast<uint2*>(lrow + 2 * col) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+          else *reinterpret_cast<uint2*>(lrow + 2 * col) = make_uint2(pack_f16x2(sc * o[0], sc * o[1]), pack_f16x2(sc * o[2], sc * o[3]));
         }
+        if constexpr (EPI == 1 || EPI == 2) __builtin_amdgcn_sched_barrier(0);  // one row's table entries in registers at a time
       }
-    }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < RP * PPR / NT; ++i) {
-      const int p_ = tid + NT * i, row = p_ / PPR, c = p_ % PPR;
-      const int grow = rb + RP * pass + row, gcol = nb + c * (16 / ES);
-      if (grow < M && gcol < N)  // N is a multiple of 8
-        *reinterpret_cast<u32x4_t*>(Cb + ((size_t)grow * N + gcol) * ES) = *reinterpret_cast<const u32x4_t*>(lds + row * CS + 16 * c);
+      for (int i = 0; i < RP * PPR / NT; ++i) {
+        const int p_ = tid + NT * i, row = p_ / PPR, c = p_ % PPR;
+        const int grow = rb + RP * pass + row, gcol = nb + c * (16 / ES);
+        if (grow < row_end && gcol < N)  // N is a multiple of 8
+          *reinterpret_cast<u32x4_t*>(Cb + ((size_t)grow * N + gcol) * ES) = *reinterpret_cast<const u32x4_t*>(lds + row * CS + 16 * c);
+      }
+      if (pass + 1 < BM / RP) __syncthreads();
     }
-    if (pass + 1 < BM / RP) __syncthreads();
-  }
+  };
+  if (epi == 3) way_out(std::integral_constant<int, 3>());
+  else if (BF16 && epi == 1) way_out(std::integral_constant<int, 1>());
+  else if (BF16 && epi == 2) way_out(std::integral_constant<int, 2>());
+  else way_out(std::integral_constant<int, 0>());
 }
 
 // ---- attention over explicit keys and values -------------------------------------------------
@@ -439,11 +394,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
             h = (int)(job / (unsigned)(n_units * n_sl) % (unsigned)nh), b = (int)(job / (unsigned)(n_units * n_sl * nh));
   const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
   // A continuing sequence has p0 tokens behind it: the final states of its first p0 / s slots are the
-  // first rows of the key / value arrays (one per slot), the chunk's T rows follow at row `past`.
-  const int past = CONT ? a.past_pitch : 0, Tp = past + T;
+  // first rows of its part of the key / value arrays (one per slot), its new rows follow.
+  const int Tp = (CONT ? a.past_pitch : 0) + T;
   int p0 = CONT ? a.pos0[b] : 0;
-  if (p0 < 0 || p0 / s > past) p0 = past * s;  // out of range (reported by the staging kernel): stay inside the arrays
-  const int j0 = p0 / s;
+  if (CONT && (p0 < 0 || p0 / s > a.past_pitch)) p0 = a.past_pitch * s;  // out of range (reported by the front launch): stay inside the arrays
+  const int j0 = p0 / s, past = j0;
+  if (CONT && a.advance && unit == 0 && h == 0 && sl == 0) {
+    const long long end = (long long)a.pos0[b] + (len > 0 ? len : 0);
+    if (end <= a.capacity && len > 0) {
+      if (tid == 0) a.advance[b] = (int32_t)end;
+      for (int e = tid; e < a.r; e += NT) a.tail_c[(size_t)b * a.r + e] = a.tail_next[(size_t)b * a.r + e];
+    }
+  }
   const size_t out_stride = lat ? (size_t)nh * a.r : (size_t)nh * DH;  // elements per output row
   float* out = lat ? a.out + ((size_t)b * T * nh + h) * a.r + (size_t)sl * DH : a.out + ((size_t)b * T * nh + h) * DH;
   const uint16_t* kx = reinterpret_cast<const uint16_t*>(a.kx) + ((size_t)b * Tp * nh + h) * DH;
@@ -791,12 +753,17 @@ bool prefill_explicit_supported(const ExplicitArgs& a) {
 }
 
 bool gemm_nt_supported(const GemmArgs& a) {
-  const int n1 = a.epi == 1 ? a.N1 : 0;
-  return a.M >= 1 && (a.N >= 8 || (a.epi == 1 && a.N == 0 && a.N1 >= 8)) && a.N % 8 == 0 && a.K >= 32 && a.K % 32 == 0 && (a.nz == 1 || a.nz == 2) &&
-         (size_t)((a.N + n1 + 127) / 128) * ((a.M + 255) / 256) * a.nz < (size_t)1 << 31 &&
-         (a.epi == 0 || a.epi == 3 ||
-          (a.epi == 1 && a.nz == 1 && a.d_rope % 4 == 0 && a.d_rope >= 4 && a.rope_cs && a.N % a.d_rope == 0 &&
-           n1 % 8 == 0 && n1 >= 0 && (n1 == 0 || (a.N % 256 == 0 && n1 % a.d_rope == 0))));
+  if (a.M < 1 || a.K < 32 || a.K % 32 != 0 || a.n_seg < 1 || a.n_seg > GemmArgs::kSegments) return false;
+  size_t blocks = 0;
+  for (int i = 0; i < a.n_seg; ++i) {
+    const GemmSegment& g = a.seg[i];
+    if (g.N < 8 || g.N % 8 != 0 || !(g.epi >= 0 && g.epi <= 3)) return false;
+    if ((g.epi == 1 || g.epi == 2) && (!a.in_bf16 || a.d_rope % 4 != 0 || a.d_rope < 4 || !a.rope_cs || g.N % a.d_rope != 0)) return false;
+    blocks += (size_t)(g.N + 63) / 64;
+  }
+  if (a.rows.T < 1 || ((a.rows.n_new || a.rows.pos0) && a.M % (a.rows.past + a.rows.T) != 0)) return false;
+  const size_t n_seq = a.rows.n_new || a.rows.pos0 ? (size_t)a.M / (a.rows.past + a.rows.T) : 1;
+  return blocks * ((size_t)(a.M + 63) / 64 + n_seq + 8) < (size_t)1 << 31;
 }
 
 // (cos, sin) of pos * freq[k] for row b*T + t at position pos0[b] + t, k < d_rope / 2
@@ -818,54 +785,98 @@ hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st) {
-  if (!gemm_nt_supported(a)) return hipErrorInvalidValue;
-  const int n_all = a.N + (a.epi == 1 ? a.N1 : 0);
-  // 256-column tiles (a third less traffic into LDS per flop) when they fill: whole tiles of both products
-  const bool wide = a.wide >= 0 ? (a.wide != 0 && a.N % 256 == 0) : (a.N % 256 == 0 && (a.epi != 1 || a.N1 == 0 || a.N >= 1024));
-  const int bn = wide ? 256 : 128;
-  const dim3 grid((unsigned)((n_all + bn - 1) / bn) * (unsigned)((a.M + 255) / 256) * (unsigned)a.nz);
-#define MTLA_GEMM(BF, EP)                                                                                   \
-  if ((a.in_bf16 != 0) == BF && a.epi == EP) {                                                              \
-    if (wide) hipLaunchKernelGGL((gemm_nt_kernel<BF, EP, 256>), grid, dim3(512), 0, st, a);                 \
-    else hipLaunchKernelGGL((gemm_nt_kernel<BF, EP, 128>), grid, dim3(256), 0, st, a);                      \
+// Column blocks of a launch with tiles of bn columns (a segment starts a block of its own).
+static int gemm_col_blocks(const GemmArgs& a, int bn) {
+  int n = 0;
+  for (int i = 0; i < a.n_seg; ++i) n += (a.seg[i].N + bn - 1) / bn;
+  return n;
+}
+
+// The tile that gives the unit with the most work the least of it, and that work in units of a 256 x 256 tile's area: the
+// area of a tile weighted by how fast a unit gets through it (smaller tiles move more from L2 per product: 32768 rows x
+// 4096 columns at K = 512 took 198, 202, 232 and 368 us).  With ragged rows the number of jobs is not known here:
+// three quarters of the most, and half a round more, on average, than they fill.
+static float gemm_cost(const GemmArgs& a, int& pick) {
+  static constexpr struct { int bm, bn; float rate; } kTiles[] = {{256, 256, 1.f}, {256, 128, 0.97f}, {128, 128, 0.85f}, {64, 64, 0.54f}};
+  const bool ragged = a.rows.n_new || a.rows.pos0;
+  float best = 0.f;
+  pick = 0;
+  for (int i = 0; i < 4; ++i) {
+    const long long jobs = (long long)gemm_col_blocks(a, kTiles[i].bn) * ((a.M + kTiles[i].bm - 1) / kTiles[i].bm);
+    const float rounds = ragged && jobs > 256 ? 0.75f * (float)jobs / 256.f + 0.5f : (float)((jobs + 255) / 256);
+    const float cost = rounds * (float)(kTiles[i].bm * kTiles[i].bn) / kTiles[i].rate / 65536.f;
+    if (i == 0 || cost < best) {
+      best = cost;
+      pick = i;
+    }
   }
-  MTLA_GEMM(false, 0)
-  MTLA_GEMM(false, 3)
-  MTLA_GEMM(true, 0)
-  MTLA_GEMM(true, 1)
-  MTLA_GEMM(true, 3)
+  return best;
+}
+
+hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
+  if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
+  GemmArgs a = args;
+  int pick = 0;
+  const float whole = gemm_cost(a, pick);
+  if (a.n_seg > 1) {
+    // The narrowest product in a launch of its own if that saves more than the launch costs: 64 columns beside 3584 at
+    // 32768 rows open an eighth round of 256 x 256 tiles (67 us at K = 2048) that is half empty.
+    int least = 0;
+    for (int i = 1; i < a.n_seg; ++i)
+      if (a.seg[i].N < a.seg[least].N) least = i;
+    GemmArgs one = a, rest = a;
+    one.n_seg = 1;
+    one.seg[0] = a.seg[least];
+    rest.n_seg = a.n_seg - 1;
+    for (int i = least; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
+    int p1 = 0, p2 = 0;
+    const float launch = 0.075f * 2048.f / (float)a.K;  // 5 us
+    if (gemm_cost(one, p1) + gemm_cost(rest, p2) + launch < whole) {
+      const hipError_t e = launch_gemm_nt(rest, st);
+      return e != hipSuccess ? e : launch_gemm_nt(one, st);
+    }
+  }
+  static constexpr int kBM[] = {256, 256, 128, 64}, kBN[] = {256, 128, 128, 64};
+  a.col_blocks = gemm_col_blocks(a, kBN[pick]);
+  unsigned gy = (unsigned)((a.M + kBM[pick] - 1) / kBM[pick]);
+  if ((a.rows.n_new || a.rows.pos0) && !a.rows.zeros) {  // every sequence starts a block of its own
+    const int Tp = a.rows.past + a.rows.T;
+    gy = (unsigned)(a.M / Tp) * (unsigned)((Tp + kBM[pick] - 1) / kBM[pick]);
+  }
+  a.row_blocks = gy;
+  a.xcds = gy >= 8 ? 8 : 1;
+  const dim3 grid((unsigned)a.col_blocks * ((gy + a.xcds - 1) / a.xcds * a.xcds));
+#define MTLA_GEMM(I, BM, BN)                                                                                     \
+  if (pick == I) {                                                                                               \
+    const dim3 block(GemmGeom<BM, BN>::NT);                                                                      \
+    if (a.in_bf16) hipLaunchKernelGGL((gemm_nt_kernel<true, BM, BN>), grid, block, 0, st, a);                    \
+    else hipLaunchKernelGGL((gemm_nt_kernel<false, BM, BN>), grid, block, 0, st, a);                             \
+  }
+  MTLA_GEMM(0, 256, 256)
+  MTLA_GEMM(1, 256, 128)
+  MTLA_GEMM(2, 128, 128)
+  MTLA_GEMM(3, 64, 64)
 #undef MTLA_GEMM
   return hipGetLastError();
 }
 
-hipError_t launch_chunk_stage(const ChunkStageArgs& a, hipStream_t st) {
-  const size_t r8 = a.r / 8, d8 = a.d_rope / 8, n_runs = (a.T + a.stride - 1) / a.stride + 1;
-  const size_t n = (size_t)a.batch * a.past_pitch * (r8 + d8) + (size_t)a.batch * n_runs * r8 + (size_t)a.batch * a.T * d8;
-  hipLaunchKernelGGL(chunk_stage_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, a);
-  return hipGetLastError();
-}
-
-// partial states must already be in a.cprime (fp16 [B*T, r]); for continuing sequences (a.pos0) the
-// staging kernel has filled a.cprime and a.kr16 ([B*(past_pitch + T), ..])
+// the front launch has filled a.cprime, a.kr16 ([B*(past_pitch + T), ..]), a.w_kT and a.w_v16
 hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
-  const size_t n_w = (size_t)a.n_heads * a.r * a.d_head;
-  const size_t n_kr = (a.pos0 || a.kr_staged) ? 0 : (size_t)a.batch * a.T * a.d_rope;
-  hipLaunchKernelGGL(to_f16_kernel, dim3((unsigned)((n_w + n_kr + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
-                     reinterpret_cast<const uint16_t*>(a.w_uk), reinterpret_cast<const uint16_t*>(a.w_uv),
-                     reinterpret_cast<uint16_t*>(a.w_kT), reinterpret_cast<uint16_t*>(a.w_v16),
-                     reinterpret_cast<const uint16_t*>(a.kr), reinterpret_cast<uint16_t*>(a.kr16), a.n_heads, a.r,
-                     a.d_head, n_kr);
-  GemmArgs ga;  // K = C_hat' W_K, V = C_hat' W_V for all rows
+  GemmArgs ga;  // K = C_hat' W_K, V = C_hat' W_V for all rows that hold something
   ga.A = a.cprime;
-  ga.W[0] = a.w_kT;
-  ga.W[1] = a.w_v16;
-  ga.C[0] = a.kx;
-  ga.C[1] = a.vx;
   ga.M = a.batch * (a.past_pitch + a.T);
-  ga.N = a.n_heads * a.d_head;
   ga.K = a.r;
-  ga.nz = 2;
+  ga.n_seg = 2;
+  for (int i = 0; i < 2; ++i) {
+    ga.seg[i].W = i ? a.w_v16 : a.w_kT;
+    ga.seg[i].C = i ? a.vx : a.kx;
+    ga.seg[i].N = a.n_heads * a.d_head;
+  }
+  ga.rows.pos0 = a.pos0;
+  ga.rows.n_new = a.seq_len;
+  ga.rows.past = a.past_pitch;
+  ga.rows.T = a.T;
+  ga.rows.stride = a.stride;
   hipError_t e = launch_gemm_nt(ga, st);
   if (e != hipSuccess) return e;
   auto attend = [&](const ExplicitArgs& x, const EventPair& e) -> hipError_t {

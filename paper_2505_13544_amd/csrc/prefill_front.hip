@@ -1,0 +1,514 @@
+// What comes before the matrix products of a prefill (bf16 storage), in one launch: the append of the new tokens
+// (merge weights and cache), the rows the key / value product reads (slot states of the past and partial states
+// C_hat'[m] of the new rows, as fp16), the RoPE keys as fp16, and the weights as fp16.
+//
+//   append_bulk_kernel      mtla_cache_append of many tokens (the append alone)
+//   prefill_front_kernel    the above; MODE 0: the merge weights are given and nothing is appended (part of
+//                           mtla_prefill_attn and mtla_prefill_chunk_attn), 1: with the append, 2: with the append,
+//                           from unrounded latents that are layer-normalised first (whole-layer prefill)
+//
+// A new row's partial state is what the append of its slot holds after the row (the update rule after
+// Eq. (infer-linear)), so one pass over the latents yields both.  Appending, converting and staging in seven launches took
+// 46 us of the 227 us of six pieces of up to 510 rows (r = 512, 16 heads x 128) behind up to 3001 tokens, most of
+// it launches that wait for one another; as one launch [see FRONT_US].
+#include <type_traits>
+
+#include "mtla_device.h"
+#include "mtla_kernels.h"
+
+namespace mtla {
+
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));  // (plain vector types stay in registers)
+
+constexpr int kSlots = 16;  // slots per workgroup and pass
+
+__device__ __forceinline__ uint16_t bf16_bits_to_f16_bits(uint16_t v) {
+  return __builtin_bit_cast(uint16_t, static_cast<_Float16>(__uint_as_float(uint32_t(v) << 16)));
+}
+__device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v) {
+  u32x4_t o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t w = v[i];
+    o[i] = pack_f16x2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+  }
+  return o;
+}
+
+constexpr int kChunk = 32;  // tokens whose latents are in LDS at a time
+
+// One row of latents in LDS: bf16 as they come, or fp32 after their normalisation (LN).  The pitch is an odd multiple of
+// 16 bytes, so that 16-byte reads of 16 rows spread over all banks.
+template <int R, bool LN>
+struct AppendShared {
+  static constexpr int kPitch = R * (LN ? 4 : 2) + 16;
+  unsigned char row[kChunk][kPitch];
+  float z[4][kChunk];  // hyper-network logits of the chunk's tokens, one share per 16 rows of the hyper-network
+  __device__ __forceinline__ void values(int u, int e, float (&o)[8]) const {
+    if constexpr (LN) {
+      const float4_t lo = *reinterpret_cast<const float4_t*>(row[u] + 4 * e), hi = *reinterpret_cast<const float4_t*>(row[u] + 4 * e + 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        o[i] = lo[i];
+        o[4 + i] = hi[i];
+      }
+    } else {
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(row[u] + 2 * e);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = v[i];
+        o[2 * i] = __uint_as_float(w << 16);
+        o[2 * i + 1] = __uint_as_float(w & 0xffff0000u);
+      }
+    }
+  }
+};
+
+// Positions [pos_lo, pos_hi) of sequence b, all inside slots slot_base .. slot_base + 15; called by every thread of the
+// workgroup (barriers inside).  The latents go through LDS once, 32 tokens at a time, and serve two things:
+//   weights  Linear(c) of 16 tokens at a time is a small dense contraction D[y, token] = sum_n hyp_A[y, n] c[token, n];
+//            a wavefront owns 16 rows y (their 16 r weights stay in its registers for all tokens), dots its
+//            share with the slot's row of hyp_G, and the four shares meet in LDS
+//   merge    16 threads per slot fold w_n c_n over the slot's tokens in order, in fp32, from the tail shadow when
+//            the slot already held tokens; every partial sum is a row of C_hat' (STAGE), the last one the cache row,
+//            rounded once
+// `tail_out` takes the last slot's fp32 value.
+// A workgroup is one round trip to memory and then works out of LDS; with the rows read straight into the operand layout
+// by each wavefront, and again for the merge, 8 x 4096 tokens at r = 512 took 42 us (50 MB), now 23 us.
+template <int R, bool LN, bool STAGE>
+__device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillFrontArgs* fa, int b, int p0, int n, int slot_base,
+                                             long long pos_lo, long long pos_hi, float* tail_out, AppendShared<R, LN>& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4, q = tid & 15, j = tid >> 4;
+  const int s = a.stride, dR = a.d_rope, dy = a.d_hyper;
+  const int t0 = int(pos_lo - p0), cnt = int(pos_hi - pos_lo);  // tokens t0 .. t0 + cnt - 1 of the call
+  const size_t tok0 = (size_t)b * a.n_new_max + t0;
+  constexpr int KK = R / 32, NP = R >= 128 ? R / 128 : 1;      // a thread merges pieces q, q + 16, .. of 8 elements
+  const bool hyper = !a.w_override && 16 * wv < dy;
+  int past = 0;  // rows of cprime in front of the new ones
+  if constexpr (STAGE) past = p0 / s < fa->cs.past_pitch ? p0 / s : fa->cs.past_pitch;
+
+  // ---- requests that need nothing but the position: the wavefront's rows of hyp_A, the slot in progress
+  u32x4_t af[KK];
+  float bias[4] = {0.f, 0.f, 0.f, 0.f};
+  if (hyper) {
+    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.hyp_A) + (size_t)(16 * wv + l16) * R + 8 * g;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) af[kk] = *reinterpret_cast<const u32x4_t*>(A + 32 * kk);
+    const bf16* ha = reinterpret_cast<const bf16*>(a.hyp_a);
+    if (ha) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) bias[v] = to_f32(ha[16 * wv + 4 * g + v]);
+    }
+  }
+  const int slot = slot_base + j;
+  const long long sf = (long long)slot * s;
+  const long long lo = sf > pos_lo ? sf : pos_lo, hi = sf + s < pos_hi ? sf + s : pos_hi;
+  const bool mine = lo < hi && 8 * q < R;  // the slot is touched by this range
+  float acc[NP][8];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
+  if (mine && sf < p0) {  // the slot already holds earlier tokens
+#pragma unroll
+    for (int i = 0; i < NP; ++i) load8(a.tail_c + (size_t)b * R + 8 * (q + 16 * i), acc[i]);
+  }
+
+  for (int c0 = 0; c0 < cnt; c0 += kChunk) {
+    const int nc = cnt - c0 < kChunk ? cnt - c0 : kChunk;
+    if (c0) __syncthreads();
+    // ---- latents of the chunk: 16 threads per token, two tokens per thread, everything requested at once
+    uint2 gv[2];
+    if (hyper) {
+      const uint16_t* G = reinterpret_cast<const uint16_t*>(a.hyp_G) + 16 * wv + 4 * g;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int u = 16 * h + l16 < nc ? 16 * h + l16 : nc - 1;
+        gv[h] = *reinterpret_cast<const uint2*>(G + (size_t)((pos_lo + c0 + u) / s) * dy);
+      }
+    }
+    if constexpr (LN) {
+      constexpr int N4 = R / 64;
+      float4_t v[2][N4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int u = 16 * h + j < nc ? 16 * h + j : nc - 1;
+        const float* row = reinterpret_cast<const float*>(a.c_new) + (tok0 + c0 + u) * R;
+#pragma unroll
+        for (int i = 0; i < N4; ++i) v[h][i] = *reinterpret_cast<const float4_t*>(row + 4 * (q + 16 * i));
+      }
+      const bf16* gamma = reinterpret_cast<const bf16*>(a.ln_gamma);
+      const bf16* beta = reinterpret_cast<const bf16*>(a.ln_beta);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < N4; ++i) sum += (v[h][i][0] + v[h][i][1]) + (v[h][i][2] + v[h][i][3]);
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) sum += __shfl_xor(sum, off, kWave);
+        const float mean = sum / (float)R;
+        float sq = 0.f;
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+          v[h][i] -= mean;
+          sq += (v[h][i][0] * v[h][i][0] + v[h][i][1] * v[h][i][1]) + (v[h][i][2] * v[h][i][2] + v[h][i][3] * v[h][i][3]);
+        }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) sq += __shfl_xor(sq, off, kWave);
+        const float rstd = rsqrtf(sq / (float)R + a.ln_eps);
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+          const int e = 4 * (q + 16 * i);
+          float4_t o = v[h][i] * rstd;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (gamma) o[k] *= to_f32(gamma[e + k]);
+            if (beta) o[k] += to_f32(beta[e + k]);
+          }
+          *reinterpret_cast<float4_t*>(sh.row[16 * h + j] + 4 * e) = o;
+        }
+      }
+    } else {
+      u32x4_t v[2][NP];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int u = 16 * h + j < nc ? 16 * h + j : nc - 1;
+        const uint16_t* row = reinterpret_cast<const uint16_t*>(a.c_new) + (tok0 + c0 + u) * R;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) v[h][i] = *reinterpret_cast<const u32x4_t*>(row + (8 * q < R ? 8 * (q + 16 * i) : 0));
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+          if (8 * q < R) *reinterpret_cast<u32x4_t*>(sh.row[16 * h + j] + 16 * (q + 16 * i)) = v[h][i];
+    }
+    __syncthreads();
+
+    // ---- logits of the merge weights
+    if (hyper) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (16 * h >= nc) break;
+        float4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          if constexpr (LN) {  // unrounded latents: hi + lo bf16 planes, two matrix instructions per step
+            float v[8];
+            sh.values(16 * h + l16, 32 * kk + 8 * g, v);
+            uint32_t h0, l0, h1, l1, h2, l2, h3, l3;
+            split_bf16x2(v[0], v[1], h0, l0);
+            split_bf16x2(v[2], v[3], h1, l1);
+            split_bf16x2(v[4], v[5], h2, l2);
+            split_bf16x2(v[6], v[7], h3, l3);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]),
+                                                        __builtin_bit_cast(bf16x8_t, (u32x4_t{h0, h1, h2, h3})), d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]),
+                                                        __builtin_bit_cast(bf16x8_t, (u32x4_t{l0, l1, l2, l3})), d, 0, 0, 0);
+          } else {
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(sh.row[16 * h + l16] + 2 * (32 * kk + 8 * g));
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]), __builtin_bit_cast(bf16x8_t, v), d, 0, 0, 0);
+          }
+        }
+        // the lane holds Linear(c)[16 wv + 4 g + v] of its token
+        const float gf[4] = {__uint_as_float(gv[h].x << 16), __uint_as_float(gv[h].x & 0xffff0000u),
+                             __uint_as_float(gv[h].y << 16), __uint_as_float(gv[h].y & 0xffff0000u)};
+        float z = 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z += (d[v] + bias[v]) * gf[v];
+        z += __shfl_xor(z, 16, kWave);
+        z += __shfl_xor(z, 32, kWave);
+        if (g == 0) sh.z[wv][16 * h + l16] = z;
+      }
+    }
+    __syncthreads();
+    auto weight = [&](int u) {
+      if (a.w_override) return a.w_override[tok0 + c0 + u];
+      float z = 0.f;
+      for (int y = 0; 16 * y < dy; ++y) z += sh.z[y][u];
+      return 1.f / (1.f + expf(-z));
+    };
+    if (tid < nc && (a.w_out || a.slot_out)) {
+      if (a.w_out) a.w_out[tok0 + c0 + tid] = weight(tid);
+      if (a.slot_out) a.slot_out[tok0 + c0 + tid] = int((pos_lo + c0 + tid) / s);
+    }
+
+    // ---- temporal merge of the slot's tokens in this chunk
+    if (mine) {
+      const long long u_lo = lo - pos_lo - c0 > 0 ? lo - pos_lo - c0 : 0, u_hi = hi - pos_lo - c0 < nc ? hi - pos_lo - c0 : nc;
+      for (int u = (int)u_lo; u < (int)u_hi; ++u) {
+        const float w = weight(u);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          float v[8];
+          sh.values(u, 8 * (q + 16 * i), v);
+          u32x4_t o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[i][2 * e] += w * v[2 * e];
+            acc[i][2 * e + 1] += w * v[2 * e + 1];
+            o[e] = pack_f16x2(acc[i][2 * e], acc[i][2 * e + 1]);
+          }
+          if constexpr (STAGE) {
+            const ChunkStageArgs& cs = fa->cs;
+            *reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(cs.cprime) +
+                                        ((size_t)b * (cs.past_pitch + cs.T) + past + (size_t)(t0 + c0 + u)) * R + 8 * (q + 16 * i)) = o;
+          }
+        }
+      }
+    }
+  }
+
+  if (lo < hi) {
+    const size_t crow = cache_row(a.pages, b, slot, a.max_slots);
+    if (8 * q < R) {
+      uint16_t* out = reinterpret_cast<uint16_t*>(a.cache_c) + crow * R;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int e = 8 * (q + 16 * i);
+        *reinterpret_cast<u32x4_t*>(out + e) = u32x4_t{pack_bf16x2(acc[i][0], acc[i][1]), pack_bf16x2(acc[i][2], acc[i][3]),
+                                                       pack_bf16x2(acc[i][4], acc[i][5]), pack_bf16x2(acc[i][6], acc[i][7])};
+        if (hi == (long long)p0 + n) {  // last slot touched: remains the sequence's tail
+          float* t = tail_out + (size_t)b * R + e;
+          *reinterpret_cast<float4_t*>(t) = float4_t{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+          *reinterpret_cast<float4_t*>(t + 4) = float4_t{acc[i][4], acc[i][5], acc[i][6], acc[i][7]};
+        }
+      }
+    }
+    // RoPE key: the slot keeps the key of the newest token folded into it
+    if (q < dR / 8) {
+      const uint16_t* kr_src = reinterpret_cast<const uint16_t*>(a.kr_new) + ((size_t)b * a.n_new_max + (size_t)(hi - 1 - p0)) * dR;
+      uint16_t* kr_dst = reinterpret_cast<uint16_t*>(a.cache_kr) + crow * dR;
+      *reinterpret_cast<u32x4_t*>(kr_dst + 8 * q) = *reinterpret_cast<const u32x4_t*>(kr_src + 8 * q);
+    }
+  }
+}
+
+// Workgroup x of sequence b: slots 16 x .. of those the call touches.  The tail shadow of a sequence is read by the first
+// slot (when that slot already held tokens) and written by the last one.  With a staging launch the new one goes to
+// tail_next and is put in place by the attention launch.  An append alone has no later launch: when the shadow is
+// read, workgroup 0 takes the last slot as well, in a second pass behind a barrier, so the read precedes the write.
+template <int R, bool LN, bool STAGE>
+__device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int x, int b, AppendShared<R, LN>& sh) {
+  const int s = a.stride, p0 = a.seq_len[b];
+  int n = a.n_new ? a.n_new[b] : a.n_new_max;
+  n = n < 0 ? 0 : (n > a.n_new_max ? a.n_new_max : n);
+  if constexpr (STAGE) {
+    if (x == 0 && threadIdx.x == 0) fa->pos0_out[b] = p0;  // for the launches behind this one
+  }
+  if (n == 0) return;
+  if ((long long)p0 + n > (long long)a.max_slots * s) {   // refuse: sequence untouched
+    if (x == 0 && threadIdx.x == 0) *a.status = 3;        // MTLA_ERR_CAPACITY
+    return;
+  }
+  const long long end = (long long)p0 + n;
+  const int first_slot = p0 / s, last_slot = int((end - 1) / s);
+  const bool last_apart = !STAGE && p0 % s != 0 && last_slot - first_slot >= kSlots;  // last slot outside workgroup 0's group
+  float* tail_out = STAGE ? fa->tail_next : a.tail_c;
+  const int slot0 = first_slot + kSlots * x;
+  const long long lim = last_apart ? (long long)last_slot * s : end;  // the group's share ends here
+  const long long pos_lo = (long long)slot0 * s > p0 ? (long long)slot0 * s : p0;
+  const long long pos_hi = (long long)(slot0 + kSlots) * s < lim ? (long long)(slot0 + kSlots) * s : lim;
+  if (pos_lo < pos_hi) append_range<R, LN, STAGE>(a, fa, b, p0, n, slot0, pos_lo, pos_hi, tail_out, sh);
+  if (x == 0 && last_apart) {
+    __syncthreads();
+    append_range<R, LN, STAGE>(a, fa, b, p0, n, last_slot, (long long)last_slot * s, end, tail_out, sh);
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(kBlock) void append_bulk_kernel(AppendArgs a) {
+  __shared__ __attribute__((aligned(16))) AppendShared<R, false> sh;
+  append_block<R, false, false>(a, nullptr, blockIdx.x, blockIdx.y, sh);
+}
+
+// Tokens before the new rows, forced into what the arrays hold.
+__device__ __forceinline__ int start_of(const ChunkStageArgs& a, int b) {
+  if (!a.pos0) return 0;  // whole sequences
+  const int p0 = a.pos0[b], s = a.stride, past = a.past_pitch;
+  if (p0 < 0 || p0 / s > past || p0 / s > a.max_slots) {
+    *a.status = 1;  // MTLA_ERR_INVALID_ARG
+    const int lim = past < a.max_slots ? past : a.max_slots;
+    return lim * s;
+  }
+  return p0;
+}
+
+// 16-byte pieces: slot states and RoPE keys of the past (rows k < pos0 / s of a sequence's part of cprime and kr16), and
+// the new rows' RoPE keys behind them.  (A sequence's rows are together at the front of its part, so that the key / value
+// product meets few tiles that are only partly in use.)  Rows that hold nothing are left alone: nothing reads them.
+__device__ __forceinline__ void stage_piece(const ChunkStageArgs& a, size_t idx) {
+  const int r8 = a.r / 8, d8 = a.d_rope / 8, past = a.past_pitch, Tp = past + a.T;
+  const size_t n1 = (size_t)a.batch * past * (r8 + d8), n3 = (size_t)a.batch * a.T * d8;
+  uint16_t* cp = reinterpret_cast<uint16_t*>(a.cprime);
+  uint16_t* kr16 = reinterpret_cast<uint16_t*>(a.kr16);
+  if (idx < n1) {
+    const int piece = int(idx % (r8 + d8)), k = int(idx / (r8 + d8) % past), b = int(idx / ((size_t)(r8 + d8) * past));
+    if (k >= start_of(a, b) / a.stride) return;
+    int sb = b;  // the sequence whose rows hold slot k: b itself, or the owner of a prompt it shares
+    if (a.prefix_owner && k < a.prefix_slots[b]) {
+      const int o = a.prefix_owner[b];
+      sb = o < 0 ? 0 : (o < a.prefix_rows ? o : a.prefix_rows - 1);
+    }
+    const size_t src = cache_row(a.pages, sb, k, a.max_slots), dst = (size_t)b * Tp + k;
+    const uint16_t* from = piece < r8 ? reinterpret_cast<const uint16_t*>(a.cache_c) + src * a.r + 8 * piece
+                                      : reinterpret_cast<const uint16_t*>(a.cache_kr) + src * a.d_rope + 8 * (piece - r8);
+    uint16_t* to = piece < r8 ? cp + dst * a.r + 8 * piece : kr16 + dst * a.d_rope + 8 * (piece - r8);
+    *reinterpret_cast<u32x4_t*>(to) = bf16x8_to_f16x8(*reinterpret_cast<const u32x4_t*>(from));
+    return;
+  }
+  idx -= n1;
+  if (idx >= n3) return;
+  const int pd = int(idx % d8), m = int(idx / d8 % a.T), b = int(idx / ((size_t)d8 * a.T));
+  if (a.n_new && m >= a.n_new[b]) return;
+  *reinterpret_cast<u32x4_t*>(kr16 + ((size_t)b * Tp + start_of(a, b) / a.stride + m) * a.d_rope + 8 * pd) = bf16x8_to_f16x8(
+      *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.kr) + ((size_t)b * a.T + m) * a.d_rope + 8 * pd));
+}
+
+// Partial states from given merge weights, 8 elements per thread: run jl holds the new tokens of slot pos0 / s + jl; the
+// first run continues the slot in progress from tail_prev when pos0 % s != 0.
+__device__ __forceinline__ void stage_run(const ChunkStageArgs& a, size_t idx) {
+  const int r8 = a.r / 8, s = a.stride, T = a.T, Tp = a.past_pitch + T;
+  const int n_runs = (T + s - 1) / s + 1;
+  if (idx >= (size_t)a.batch * n_runs * r8) return;
+  const int piece = int(idx % r8), jl = int(idx / r8 % n_runs), b = int(idx / ((size_t)r8 * n_runs));
+  const int p0 = start_of(a, b), ph = p0 % s, past = p0 / s;
+  int n = jl * s - ph;
+  int n_end = n + s < T ? n + s : T;
+  float run[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (jl == 0 && ph > 0) load8(a.tail_prev + (size_t)b * a.r + 8 * piece, run);
+  if (n < 0) n = 0;
+  const int len = a.n_new ? a.n_new[b] : T;
+  n_end = n_end < len ? n_end : len;
+  for (; n < n_end; ++n) {
+    const size_t row = (size_t)b * T + n;
+    float cv[8];
+    load8(reinterpret_cast<const bf16*>(a.c) + row * a.r + 8 * piece, cv);
+    const float w = a.w[row];
+    u32x4_t o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      run[2 * i] += w * cv[2 * i];
+      run[2 * i + 1] += w * cv[2 * i + 1];
+      o[i] = pack_f16x2(run[2 * i], run[2 * i + 1]);
+    }
+    *reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(a.cprime) + ((size_t)b * Tp + past + n) * a.r + 8 * piece) = o;
+  }
+}
+
+// Weights as fp16.  W_K^(h) [r][d_h] is turned on the way (64 x 32 tiles through LDS, both sides in 16-byte pieces: read
+// an element at a time down its columns it took 10.8 us for 16 heads x 128, r = 512); W_V^(h) and W_O keep their layout.
+constexpr int kConvPieces = 4;  // 16-byte pieces per thread of the plain conversions
+__device__ __forceinline__ void convert_block(const PrefillFrontArgs& a, unsigned blk, uint16_t (*tile)[72]) {
+  const int tid = threadIdx.x, r = a.cs.r, dh = a.d_head;
+  const unsigned per_head = (unsigned)(r / 64) * (unsigned)(dh / 32), n_turn = (unsigned)a.n_heads * per_head;
+  if (blk < n_turn) {
+    const int h = int(blk / per_head), n0 = 64 * int(blk % per_head / (unsigned)(dh / 32)), d0 = 32 * int(blk % (unsigned)(dh / 32));
+    const int n = tid >> 2, d8 = 8 * (tid & 3);
+    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.w_uk) + ((size_t)h * r + n0 + n) * dh + d0 + d8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = v[i];
+      tile[d8 + 2 * i][n] = bf16_bits_to_f16_bits((uint16_t)(w & 0xffffu));
+      tile[d8 + 2 * i + 1][n] = bf16_bits_to_f16_bits((uint16_t)(w >> 16));
+    }
+    __syncthreads();
+    const int d = tid >> 3, n8 = 8 * (tid & 7);
+    *reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(a.w_kT) + ((size_t)h * dh + d0 + d) * r + n0 + n8) =
+        *reinterpret_cast<const u32x4_t*>(&tile[d][n8]);
+    return;
+  }
+  const size_t n_v = (size_t)a.n_heads * dh * r / 8, n_o = a.n_wo / 8;
+  const size_t first = (size_t)(blk - n_turn) * kBlock * kConvPieces + tid;
+#pragma unroll
+  for (int i = 0; i < kConvPieces; ++i) {
+    const size_t p = first + (size_t)i * kBlock;
+    if (p < n_v)
+      reinterpret_cast<u32x4_t*>(a.w_v16)[p] = bf16x8_to_f16x8(reinterpret_cast<const u32x4_t*>(a.w_uv)[p]);
+    else if (p < n_v + n_o)
+      reinterpret_cast<u32x4_t*>(a.w_o16)[p - n_v] = bf16x8_to_f16x8(reinterpret_cast<const u32x4_t*>(a.w_o)[p - n_v]);
+  }
+}
+
+template <int R, int MODE>
+__global__ __launch_bounds__(kBlock) void prefill_front_kernel(PrefillFrontArgs a) {
+  struct None {};
+  __shared__ __attribute__((aligned(16))) union {
+    std::conditional_t<MODE == 0, None, AppendShared<R, MODE == 2>> append;
+    uint16_t tile[32][72];
+  } sh;
+  unsigned blk = blockIdx.x;
+  if (blk < a.n_main) {  // the new rows
+    if constexpr (MODE == 0) stage_run(a.cs, (size_t)blk * kBlock + threadIdx.x);
+    else append_block<R, MODE == 2, true>(a.ap, &a, blk % a.groups, blk / a.groups, sh.append);
+    return;
+  }
+  blk -= a.n_main;
+  if (blk < a.n_conv) {
+    convert_block(a, blk, sh.tile);
+    return;
+  }
+  stage_piece(a.cs, (size_t)(blk - a.n_conv) * kBlock + threadIdx.x);
+}
+
+unsigned append_groups(const AppendArgs& a) {
+  // slots a call can touch per sequence: a partly filled first slot plus the rest
+  const int n_slots = (a.n_new_max + a.stride - 2) / a.stride + 1;
+  return (unsigned)((n_slots + kSlots - 1) / kSlots);
+}
+
+template <int MODE>
+hipError_t launch_front_mode(const PrefillFrontArgs& a, const dim3& grid, hipStream_t st) {
+  switch (a.cs.r) {
+    case 64: hipLaunchKernelGGL((prefill_front_kernel<64, MODE>), grid, dim3(kBlock), 0, st, a); break;
+    case 128: hipLaunchKernelGGL((prefill_front_kernel<128, MODE>), grid, dim3(kBlock), 0, st, a); break;
+    case 256: hipLaunchKernelGGL((prefill_front_kernel<256, MODE>), grid, dim3(kBlock), 0, st, a); break;
+    case 512: hipLaunchKernelGGL((prefill_front_kernel<512, MODE>), grid, dim3(kBlock), 0, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool append_bulk_supported(const AppendArgs& a, int dtype) {
+  return dtype != 0 && a.tail_c && a.stride <= 16 && a.d_hyper % 16 == 0 && a.d_hyper <= 64 &&
+         (a.r == 64 || a.r == 128 || a.r == 256 || a.r == 512) && a.d_rope % 8 == 0 && a.d_rope <= 128;
+}
+
+hipError_t launch_append_bulk(const AppendArgs& a, hipStream_t st) {
+  const dim3 grid(append_groups(a), a.batch);
+  switch (a.r) {
+    case 64: hipLaunchKernelGGL(append_bulk_kernel<64>, grid, dim3(kBlock), 0, st, a); break;
+    case 128: hipLaunchKernelGGL(append_bulk_kernel<128>, grid, dim3(kBlock), 0, st, a); break;
+    case 256: hipLaunchKernelGGL(append_bulk_kernel<256>, grid, dim3(kBlock), 0, st, a); break;
+    case 512: hipLaunchKernelGGL(append_bulk_kernel<512>, grid, dim3(kBlock), 0, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_front(const PrefillFrontArgs& args, int mode, hipStream_t st) {
+  PrefillFrontArgs a = args;
+  const ChunkStageArgs& cs = a.cs;
+  const size_t r8 = cs.r / 8, d8 = cs.d_rope / 8;
+  a.groups = mode == 0 ? 1 : append_groups(a.ap);
+  const size_t n_runs = (cs.T + cs.stride - 1) / cs.stride + 1;
+  const size_t main = mode == 0 ? ((size_t)cs.batch * n_runs * r8 + kBlock - 1) / kBlock : (size_t)a.groups * cs.batch;
+  const size_t plain = ((size_t)a.n_heads * a.d_head * r8 + a.n_wo / 8 + kBlock * kConvPieces - 1) / (kBlock * kConvPieces);
+  const size_t conv = (size_t)a.n_heads * (cs.r / 64) * (a.d_head / 32) + plain;
+  const size_t pieces = (size_t)cs.batch * cs.past_pitch * (r8 + d8) + (size_t)cs.batch * cs.T * d8;
+  const size_t total = main + conv + (pieces + kBlock - 1) / kBlock;
+  if (total >= (size_t)1 << 31) return hipErrorInvalidValue;
+  a.n_main = (unsigned)main;
+  a.n_conv = (unsigned)conv;
+  const dim3 grid((unsigned)total);
+  return mode == 0 ? launch_front_mode<0>(a, grid, st) : (mode == 1 ? launch_front_mode<1>(a, grid, st) : launch_front_mode<2>(a, grid, st));
+}
+
+}  // namespace mtla
