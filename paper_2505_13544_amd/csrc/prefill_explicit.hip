@@ -372,7 +372,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   constexpr int KD = DH / 32, KQ = (DH + DR) / 32, MT = DH / 16;
   constexpr int NT = 64 * NW, BM = 32 * NW, BN = G::BN, VC = G::VC, RC = G::RC;
   constexpr int NBUF = 4, PF = NBUF - 1;  // tiles in LDS, tiles requested ahead
-  constexpr int NIK = (G::NCK + NW - 1) / NW, NIR = (G::NCR + NW - 1) / NW;  // loads per wavefront and region, at most
+  constexpr int NIK = G::NCK / NW;  // loads per wavefront and region of keys or values
   constexpr int IROWS = 64 * NW / VC;     // rows between a wavefront's chunks of a region
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * G::BYTES];
 
@@ -418,26 +418,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   // of a region; lane i of it the chunk's piece i: row and (swizzled) source piece, the same for
   // all of the wavefront's chunks (they lie a multiple of 16 rows apart).
   const int pk = 64 * wv + lane;
-  const int row_k = pk / VC, row_r = pk / RC;
+  const int row_k = pk / VC;
   const uint32_t src_k = 8 * ((pk % VC) ^ swz_rows16<VC>(row_k));  // element offset inside the source row
   const uint32_t src_v = 8 * ((pk % VC) ^ swz_tr<VC>(row_k));
-  const uint32_t src_r = 8 * ((pk % RC) ^ swz_rows16<RC>(row_r));
   static_assert(NIK == 1 || IROWS % 16 == 0, "same swizzle for all chunks of a wavefront");
-  static_assert(NIR == 1, "one RoPE key chunk per wavefront at most");
-  int loads = 0;  // loads of this wavefront per tile
-#pragma unroll
-  for (int i = 0; i < NIK; ++i) loads += wv + NW * i < G::NCK ? 2 : 0;
-  loads += wv < G::NCR ? 1 : 0;
-  // byte offsets of the lane's pieces from a tile's first source row, the rows `rs` apart (1 among the slots of the past,
-  // s among the chunk-final rows)
-  uint32_t off_k = 0, off_v = 0, off_r = 0;
-  int off_rs = 0;
-  auto set_offsets = [&](int rs) {
-    off_rs = rs;
-    off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
-    off_v = 2 * ((uint32_t)(row_k * rs) * v_stride + src_v);
-    off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
-  };
+  static_assert(G::NCR <= NW, "one RoPE key chunk per wavefront at most");
+  static_assert(G::NCK % NW == 0, "whole rounds of key and value chunks");
+  // RoPE keys: fewer chunks than wavefronts at d_R = 32, where two wavefronts bring the same one, so that every wavefront
+  // has the same number of loads in flight and the waits are constants
+  constexpr int LOADS = 2 * NIK + 1;
+  const int wr = wv % G::NCR, row_r = (64 * wr + lane) / RC;
+  const uint32_t src_r = 8 * (((64 * wr + lane) % RC) ^ swz_rows16<RC>(row_r));
   // ---- where this lane reads: key rows 16 sb + l16 (piece 4 kk + g), value rows 4g + l16/4 (+16)
   const uint32_t k_row_off = (uint32_t)(l16 * VC * 16), k_swz = (uint32_t)(swz_rows16<VC>(l16) ^ g) << 4;
   const uint32_t r_row_off = (uint32_t)(l16 * RC * 16), r_swz = (uint32_t)(swz_rows16<RC>(l16) ^ g) << 4;
@@ -473,35 +464,59 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       c = c < n_cols ? c : n_cols - 1;
       return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
     };
-    // this wavefront's part of tile t on its way into buffer t % NBUF: `loads` loads
+    // this wavefront's part of tile t on its way into buffer t % NBUF: LOADS loads.  Tiles are asked for in order; while
+    // their rows are at one distance (`rs`: 1 among the slots of the past, s among the chunk-final rows) the next
+    // tile's addresses are the last one's plus a constant: uniform bases and lane offsets that stand.
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
-    auto issue = [&](int t) {
-      const uint32_t buf = lds_addr + (uint32_t)((t % NBUF) * G::BYTES);
+    int run_end = 0;              // tiles below it follow the bases as they are
+    uint64_t base_k[NIK], base_v[NIK], base_r = 0;  // (addresses)
+    uint32_t step_k = 0, step_v = 0, step_r = 0;    // bytes from a tile to the next
+    uint32_t off_k = 0, off_v = 0, off_r = 0;       // bytes from a tile's first source row to the lane's piece
+    auto start_run = [&](int t) {  // tile t begins a run of tiles whose rows are at one distance, or is one of its own
       const int c0 = BN * t;
-      if (c0 + BN <= n_cols && (!CONT || c0 >= j0 || c0 + BN <= j0)) {  // rows at one distance: the lanes' offsets stand
-        const int rs = CONT && c0 < j0 ? 1 : s;
-        const uint32_t row0 = CONT && c0 < j0 ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
-        if (rs != off_rs) set_offsets(rs);
+      const bool in_past = CONT && c0 < j0;
+      const int lim = in_past ? (j0 < n_cols ? j0 : n_cols) : n_cols;  // columns of this kind
+      run_end = lim / BN;
+      if (run_end <= t) return;
+      const int rs = in_past ? 1 : s;
+      const uint32_t row0 = in_past ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
+      off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
+      off_v = 2 * ((uint32_t)(row_k * rs) * v_stride + src_v);
+      off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
 #pragma unroll
-        for (int i = 0; i < NIK; ++i)
-          if (wv + NW * i < G::NCK) {
-            const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
-            const size_t r_ = row0 + (uint32_t)(i * IROWS * rs);
-            load_to_lds_16(kx + r_ * kv_stride, off_k, buf + G::K_OFF + chunk);
-            load_to_lds_16(vx + r_ * v_stride, off_v, buf + G::V_OFF + chunk);
-          }
-        if (wv < G::NCR) load_to_lds_16(kr16 + (size_t)row0 * DR, off_r, buf + G::R_OFF + (uint32_t)(wv * 1024));
+      for (int i = 0; i < NIK; ++i) {
+        base_k[i] = (uint64_t)(uintptr_t)kx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
+        base_v[i] = (uint64_t)(uintptr_t)vx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * v_stride;
+      }
+      base_r = (uint64_t)(uintptr_t)kr16 + 2 * (uint64_t)row0 * DR;
+      step_k = 2 * (uint32_t)(BN * rs) * kv_stride;
+      step_v = 2 * (uint32_t)(BN * rs) * v_stride;
+      step_r = 2 * (uint32_t)(BN * rs) * DR;
+    };
+    auto issue = [&](int t) {
+      const uint32_t buf = lds_addr + (uint32_t)(t % NBUF) * (uint32_t)G::BYTES;
+      if (t >= run_end) start_run(t);
+      if (t < run_end) {
+#pragma unroll
+        for (int i = 0; i < NIK; ++i) {
+          const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
+          load_to_lds_16(reinterpret_cast<const void*>(base_k[i]), off_k, buf + G::K_OFF + chunk);
+          load_to_lds_16(reinterpret_cast<const void*>(base_v[i]), off_v, buf + G::V_OFF + chunk);
+          base_k[i] += step_k;
+          base_v[i] += step_v;
+        }
+        load_to_lds_16(reinterpret_cast<const void*>(base_r), off_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
+        base_r += step_r;
         return;
       }
 #pragma unroll
-      for (int i = 0; i < NIK; ++i)
-        if (wv + NW * i < G::NCK) {
-          const uint32_t srow = src_row(c0 + row_k + i * IROWS);
-          const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
-          load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
-          load_to_lds_16(vx + srow * v_stride + src_v, buf + G::V_OFF + chunk);
-        }
-      if (wv < G::NCR) load_to_lds_16(kr16 + src_row(c0 + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wv * 1024));
+      for (int i = 0; i < NIK; ++i) {
+        const uint32_t srow = src_row(BN * t + row_k + i * IROWS);
+        const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
+        load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
+        load_to_lds_16(vx + srow * v_stride + src_v, buf + G::V_OFF + chunk);
+      }
+      load_to_lds_16(kr16 + src_row(BN * t + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
     };
 
     // the first tiles travel while the rows are set up.  (Every wavefront is done with the buffers of the previous block;
@@ -559,8 +574,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
 
     for (int t = 0; t < n_tiles; ++t) {
       // tile t has landed: this wavefront's part (all but the loads of the tiles after it), then everyone's
-      const int after = n_tiles - 1 - t < PF - 1 ? n_tiles - 1 - t : PF - 1;
-      wait_loads_but(loads * after);
+      // (the last tiles wait for everything: one wait that is too long per row block, no choice per tile)
+      if (t + PF - 1 < n_tiles) wait_loads_but<LOADS*(PF - 1)>();
+      else wait_loads_but<0>();
       barrier_only();
       if (t + PF < n_tiles) issue(t + PF);  // into the buffer tile t-1 was read from: every wavefront is past that
       if (BN * t >= none_from) continue;    // above all of this wavefront's rows
@@ -635,18 +651,27 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       // accumulator rescaling and no cross-lane traffic per tile.  Weights more than 2^-24 below the reference
       // vanish in fp16; they are that much smaller than weights already summed.
       constexpr float kRebase = 12.f;  // fp16 weights: 2^(s - reference) stays far below 65504
-      float top[2];
+      // Does any logit top it?  On the bit patterns: as integers the positive floats are in order and above all negative
+      // ones, and an integer maximum takes three operands without first quieting each.
+      int top = 0;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        top[rt] = fmaxf(fmaxf(sacc[rt][0][0], sacc[rt][0][1]), sacc[rt][0][2]);
-        top[rt] = fmaxf(fmaxf(top[rt], sacc[rt][0][3]), sacc[rt][1][0]);
-        top[rt] = fmaxf(fmaxf(top[rt], sacc[rt][1][1]), sacc[rt][1][2]);
-        top[rt] = fmaxf(top[rt], sacc[rt][1][3]);
-      }
-      if (__any(fmaxf(top[0], top[1]) > kRebase)) {
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float x = sacc[rt][sb][v];
+            top = max(top, __float_as_int(x));
+          }
+      if (__any(top > __float_as_int(kRebase))) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
-          float up = fmaxf(top[rt], __shfl_xor(top[rt], 16, kWave));
+          float up = -INFINITY;
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) up = fmaxf(up, sacc[rt][sb][v]);
+          up = fmaxf(up, __shfl_xor(up, 16, kWave));
           up = fmaxf(up, __shfl_xor(up, 32, kWave));
           if (up > kRebase) {
             const float alpha = __builtin_amdgcn_exp2f(-up);
