@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   using G = TileGeom<DH, DR>;
   constexpr int KD = DH / 32, KQ = (DH + DR) / 32, MT = DH / 16;
   constexpr int NT = 64 * NW, BM = 32 * NW, BN = G::BN, VC = G::VC, RC = G::RC;
-  constexpr int NBUF = 4, PF = NBUF - 1;  // tiles in LDS, tiles requested ahead
+  constexpr int NBUF = 4;                 // tiles in LDS: two pairs
   constexpr int NIK = G::NCK / NW;  // loads per wavefront and region of keys or values
   constexpr int IROWS = 64 * NW / VC;     // rows between a wavefront's chunks of a region
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * G::BYTES];
@@ -523,8 +523,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     // no tile load is in flight: the last tile of a block waits for everything.)
     barrier_only();
 #pragma unroll
-    for (int t = 0; t < PF; ++t)
-      if (t < n_tiles) issue(t);
+    for (int t = 0; t < 2; ++t)
+      if (n_tiles > 0) issue(t);
 
     // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column
     u32x4_t qf[2][KQ];
@@ -572,80 +572,83 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     const int all_below = (p0 + m0 + 32 * wv) / s;
     const int none_from = (p0 + m0 + 32 * wv + 31) / s;
 
-    for (int t = 0; t < n_tiles; ++t) {
-      // tile t has landed: this wavefront's part (all but the loads of the tiles after it), then everyone's
-      // (the last tiles wait for everything: one wait that is too long per row block, no choice per tile)
-      if (t + PF - 1 < n_tiles) wait_loads_but<LOADS*(PF - 1)>();
-      else wait_loads_but<0>();
+    // Two tiles per step: while one pair is multiplied the other is on its way (four buffers), one wait and one barrier for
+    // both, and the matrix products of one tile beside the softmax arithmetic of the other.
+    for (int t = 0; t < n_tiles; t += 2) {
+      wait_loads_but<0>();                  // the pair has landed: this wavefront's part, then everyone's
       barrier_only();
-      if (t + PF < n_tiles) issue(t + PF);  // into the buffer tile t-1 was read from: every wavefront is past that
+      if (t + 2 < n_tiles) {                // into the buffers the pair before was read from: every wavefront is past that
+        issue(t + 2);
+        issue(t + 3);
+      }
       if (BN * t >= none_from) continue;    // above all of this wavefront's rows
 
-      const uint32_t buf = (uint32_t)((t % NBUF) * G::BYTES);  // byte offset of the tile in `lds`
+      const uint32_t buf = (uint32_t)(t & 2) * (uint32_t)G::BYTES;  // byte offset of the pair in `lds`
       const unsigned char* kb = lds + buf + G::K_OFF + k_row_off;
       const unsigned char* rb = lds + buf + G::R_OFF + r_row_off;
       const unsigned char* vb = lds + buf + G::V_OFF + v_row_off;
-      auto read_k = [&](int kk, int sb) -> u32x4_t {  // [k | k^R] rows 16 sb + l16, elements 32 kk + 8g ..
-        return kk < KD ? *reinterpret_cast<const u32x4_t*>(kb + sb * (16 * VC * 16) + ((uint32_t)(64 * kk) ^ k_swz))
-                       : *reinterpret_cast<const u32x4_t*>(rb + sb * (16 * RC * 16) + ((uint32_t)(64 * (kk - KD)) ^ r_swz));
+      auto read_k = [&](int u, int kk, int sb) -> u32x4_t {  // tile t + u: [k | k^R] rows 16 sb + l16, elements 32 kk + 8g ..
+        return kk < KD ? *reinterpret_cast<const u32x4_t*>(kb + u * G::BYTES + sb * (16 * VC * 16) + ((uint32_t)(64 * kk) ^ k_swz))
+                       : *reinterpret_cast<const u32x4_t*>(rb + u * G::BYTES + sb * (16 * RC * 16) + ((uint32_t)(64 * (kk - KD)) ^ r_swz));
       };
-      auto read_v = [&](int mt) -> u32x4_t {  // V^T rows 16 mt + l16 (dims), columns 8g .. (K index of the PV product)
-        const unsigned char* p = vb + ((uint32_t)(32 * mt) ^ v_swz);
+      auto read_v = [&](int u, int mt) -> u32x4_t {  // V^T rows 16 mt + l16 (dims), columns 8g .. (K index of the PV product)
+        const unsigned char* p = vb + u * G::BYTES + ((uint32_t)(32 * mt) ^ v_swz);
         const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)p);
         const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 16 * VC * 16));
         const uint2 u0 = __builtin_bit_cast(uint2, v0), u1 = __builtin_bit_cast(uint2, v1);
         return u32x4_t{u0.x, u0.y, u1.x, u1.y};
       };
 
-      // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one half of the K
-      // steps are in flight while the other half is multiplied
-      constexpr int KH = KQ / 2;
-      float4_t sacc[2][2];
-      u32x4_t ka[KH][2], kc[KQ - KH][2];
+      // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one group of K
+      // steps are in flight while the group before is multiplied
+      float4_t sacc[2][2][2];  // [tile][row tile][16 columns]
+      constexpr int KG = 2, NG = 2 * KQ / KG;  // K steps per group, groups of both tiles
+      static_assert(KQ % KG == 0 || KQ % 2 == 1, "groups");
+      u32x4_t kf[2][KG][2];
+      auto read_group = [&](int i) {
 #pragma unroll
-      for (int kk = 0; kk < KH; ++kk)
+        for (int j = 0; j < KG; ++j)
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) ka[kk][sb] = read_k(kk, sb);
-      __builtin_amdgcn_sched_barrier(0);
+          for (int sb = 0; sb < 2; ++sb) {
+            const int x = i * KG + j;
+            kf[i & 1][j][sb] = read_k(x / KQ, x % KQ, sb);
+          }
+      };
+      read_group(0);
 #pragma unroll
-      for (int kk = KH; kk < KQ; ++kk)
+      for (int i = 0; i < NG; ++i) {
+        if (i + 1 < NG) read_group(i + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) kc[kk - KH][sb] = read_k(kk, sb);
-#pragma unroll
-      for (int kk = 0; kk < KH; ++kk)
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-          for (int rt = 0; rt < 2; ++rt)
-            sacc[rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, ka[kk][sb]),
-                                                                  __builtin_bit_cast(f16x8_t, qf[rt][kk]),
-                                                                  kk == 0 ? neg_ref[rt] : sacc[rt][sb], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      // the first value fragments travel while the second half is multiplied and the softmax runs
-      constexpr int VPRE = MT / 2;
-      u32x4_t vpre[VPRE];
-#pragma unroll
-      for (int mt = 0; mt < VPRE; ++mt) vpre[mt] = read_v(mt);
-#pragma unroll
-      for (int kk = KH; kk < KQ; ++kk)
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-          for (int rt = 0; rt < 2; ++rt)
-            sacc[rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kc[kk - KH][sb]),
-                                                                  __builtin_bit_cast(f16x8_t, qf[rt][kk]), sacc[rt][sb], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-
-      // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
-      if (BN * t + BN > all_below) {  // wavefront-uniform: the last tiles only
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          const int d = bound[rt] - (BN * t + 4 * g);
+        for (int j = 0; j < KG; ++j)
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sacc[rt][sb][v] = 16 * sb + v < d ? sacc[rt][sb][v] : -INFINITY;
-        }
+            for (int rt = 0; rt < 2; ++rt) {
+              const int x = i * KG + j, u = x / KQ, kk = x % KQ;
+              sacc[u][rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kf[i & 1][j][sb]),
+                                                                       __builtin_bit_cast(f16x8_t, qf[rt][kk]),
+                                                                       kk == 0 ? neg_ref[rt] : sacc[u][rt][sb], 0, 0, 0);
+            }
+      }
+      constexpr int VPRE = MT / 2;
+      u32x4_t vf[MT];  // values of the tile whose product comes next
+#pragma unroll
+      for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(0, mt);
+      __builtin_amdgcn_sched_barrier(0);
+
+      // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
+      if (BN * t + 2 * BN > all_below) {  // wavefront-uniform: the last tiles only
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) {
+            const int d = bound[rt] - (BN * (t + u) + 4 * g);
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) sacc[u][rt][sb][v] = 16 * sb + v < d ? sacc[u][rt][sb][v] : -INFINITY;
+          }
       }
       // fixed reference per row (its own column's logit, re-based only when a tile tops it by more than 2^kRebase): no
       // accumulator rescaling and no cross-lane traffic per tile.  Weights more than 2^-24 below the reference
@@ -655,22 +658,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       // ones, and an integer maximum takes three operands without first quieting each.
       int top = 0;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const float x = sacc[rt][sb][v];
-            top = max(top, __float_as_int(x));
-          }
+      for (int i = 0; i < 32; ++i) {
+        const float x = sacc[i >> 4][(i >> 3) & 1][(i >> 2) & 1][i & 3];
+        top = max(top, __float_as_int(x));
+      }
       if (__any(top > __float_as_int(kRebase))) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
           float up = -INFINITY;
 #pragma unroll
-          for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) up = fmaxf(up, sacc[rt][sb][v]);
+          for (int i = 0; i < 16; ++i) up = fmaxf(up, sacc[i >> 3][rt][(i >> 2) & 1][i & 3]);
           up = fmaxf(up, __shfl_xor(up, 16, kWave));
           up = fmaxf(up, __shfl_xor(up, 32, kWave));
           if (up > kRebase) {
@@ -678,45 +675,49 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
             neg_ref[rt] -= up;
             l_run[rt] *= alpha;
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb) sacc[rt][sb] -= up;
+            for (int i = 0; i < 4; ++i) sacc[i >> 1][rt][i & 1] -= up;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[rt][mt] *= alpha;
           }
         }
       }
-      u32x4_t pb[2];  // per row tile: B operand of the K = 32 PV product
       const f16x2_t ones = {(_Float16)1.f, (_Float16)1.f};
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
+      auto weights = [&](int u, int rt) -> u32x4_t {  // B operand of the K = 32 PV product
         // K index 8g + e of the tile: e < 4 -> column 4g + e of its first 16, else of its second 16
+        u32x4_t pb;
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(sacc[rt][sb][2 * u]), __builtin_amdgcn_exp2f(sacc[rt][sb][2 * u + 1]));
-            pb[rt][2 * sb + u] = two;
-            l_run[rt] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run[rt], false);  // the weights as they are used
-          }
-      }
-
-      // ---- O^T[d, row] += V^T[d, col] P^T[col, row]; V^T comes out of LDS through the transposing read
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4_t vpost[MT - VPRE];
-#pragma unroll
-      for (int mt = VPRE; mt < MT; ++mt) vpost[mt - VPRE] = read_v(mt);
-#pragma unroll
-      for (int mt = 0; mt < VPRE; ++mt)
+        for (int i = 0; i < 4; ++i) {
+          const float4_t& x = sacc[u][rt][i >> 1];
+          const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(x[2 * (i & 1)]), __builtin_amdgcn_exp2f(x[2 * (i & 1) + 1]));
+          pb[i] = two;
+          l_run[rt] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run[rt], false);  // the weights as they are used
+        }
+        return pb;
+      };
+      auto product = [&](int mt, const u32x4_t& v, const u32x4_t (&pb)[2]) {  // O^T[d, row] += V^T[d, col] P^T[col, row]
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
-          acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, vpre[mt]),
-                                                               __builtin_bit_cast(f16x8_t, pb[rt]), acc[rt][mt], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+          acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, v), __builtin_bit_cast(f16x8_t, pb[rt]),
+                                                               acc[rt][mt], 0, 0, 0);
+      };
+      u32x4_t pb0[2], pb1[2];
 #pragma unroll
-      for (int mt = VPRE; mt < MT; ++mt)
+      for (int rt = 0; rt < 2; ++rt) pb0[rt] = weights(0, rt);
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-          acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, vpost[mt - VPRE]),
-                                                               __builtin_bit_cast(f16x8_t, pb[rt]), acc[rt][mt], 0, 0, 0);
+      for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(0, mt);
+      // the weights of the second tile beside the first tile's product
+      pb1[0] = weights(1, 0);
+#pragma unroll
+      for (int mt = 0; mt < VPRE; ++mt) product(mt, vf[mt], pb0);
+#pragma unroll
+      for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(1, mt);
+      pb1[1] = weights(1, 1);
+#pragma unroll
+      for (int mt = VPRE; mt < MT; ++mt) product(mt, vf[mt], pb0);
+#pragma unroll
+      for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(1, mt);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) product(mt, vf[mt], pb1);
     }
 
     // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3
