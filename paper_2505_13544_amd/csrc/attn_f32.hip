@@ -37,7 +37,7 @@ __device__ __forceinline__ float col_sum(float v) {
 // read again from the cache in 64-byte pieces (the first product has just brought it into L1).
 // Bound by latency at the sizes fp32 is used for (one sequence of 128 slots, 4 heads x 64, r = 64: 49 KB): every
 // load of a tile is requested before the first product, which makes a tile one round trip.  The vector-ALU kernel
-// it replaces walked a chunk slot by slot with a cross-lane sum per head and slot: 20.6 us at that size, now 7.0.
+// it replaces walked a chunk slot by slot with a cross-lane sum per head and slot: 20.6 us at that size, now 3.9.
 // ---------------------------------------------------------------------------
 template <int R, int DR>
 __global__ __launch_bounds__(kBlock) void attn_decode_f32_kernel(AttnArgs a) {
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void attn_decode_f32_kernel(AttnArgs a) {
 // Keys (blockIdx.z = 0) and values (1) of all rows: C[m, h d_h + k] = sum_n C_hat'[m, n] W^(h)[n, k].
 // 64 x 64 tile per workgroup, the contraction 32 at a time through LDS (rows of 36 floats: the 16-byte reads of 16
 // rows spread over all banks), the next piece requested before this one is multiplied.  D = W . C_hat'^T, so a lane
-// holds four consecutive columns of its row.  2331 rows x 512 x 256, both: 1.2 GFLOP in 21 us.
+// holds four consecutive columns of its row.  2331 rows x 512 x 256, both: 1.2 GFLOP in 23 us.
 // ---------------------------------------------------------------------------
 constexpr int kGT = 64, kGK = 32, kGP = kGK + 4;
 __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
 // rows below the block, then the block's own rows under the mask (row c is open to row q iff c == q, or c < q and c
 // closes its chunk).  DV value columns per workgroup: d_head for `out`, slices of the partial states for the
 // latent-space output.  Bound by the fp32 matrix rate (256 flop per clock and unit) plus the latency of a tile.
-// Three sequences of up to 777 tokens, 8 heads x 64: 44 us; the vector-ALU kernel over absorbed queries took 353 us
+// Three sequences of up to 777 tokens, 8 heads x 64: 30 us; the vector-ALU kernel over absorbed queries took 353 us
 // (and 45 + 67 us for the absorption and the value projection, which this form does not have).
 // ---------------------------------------------------------------------------
 template <int DH, int DR, int DV, int RT>

@@ -1210,9 +1210,7 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
 
   // With many query rows per head the un-absorbed form is the cheaper one: explicit keys and
   // values for all rows (scratch inside the area the absorbed query operand would take), then
-  // attention per head.  The latent-space output, if asked for, comes from a second pass of the
-  // attention kernel over the partial states as values.
-  bool latent_only = false;  // `out` came from the explicit form, the absorbed form fills out_latent alone
+  // attention per head, the latent-space output from the same weights.
   if (g.dtype == MTLA_BF16) {
     ExplicitArgs ex;
     ex.q = q;
@@ -1241,27 +1239,13 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
     ex.stride = g.stride;
     ex.scale_log2 = c->scale * 1.4426950408889634f;
     const size_t need = 2 * kv_bytes + 2 * w_bytes + kr_bytes;
-    // The latent-space output asked for at a shape where only `out` can come from the explicit form (r not a
-    // multiple of d_head): `out` from the explicit form all the same (fp16 inside: the absorbed form's bf16
-    // operands cost `out` up to the whole 2e-2 at stride 4), then the absorbed form below for out_latent alone.
-    if (out_latent && !prefill_explicit_supported(ex)) {
-      ExplicitArgs only_out = ex;
-      only_out.out_latent = nullptr;
-      if (prefill_explicit_supported(only_out)) {
-        ex = only_out;
-        latent_only = true;
-      }
-    }
     if (prefill_explicit_supported(ex) && L.qcat + need <= L.cprime) {
       PrefillFrontArgs fa;
       front_args(c, ex, cc, kr, seq_lens, fa);
       fa.cs.w = w;
       if (!hip_ok(launch_prefill_front(fa, 0, st))) return MTLA_ERR_HIP;
       if (!hip_ok(launch_prefill_explicit(ex, st, next_event(c)))) return MTLA_ERR_HIP;
-      if (!latent_only) return MTLA_OK;
-      out = nullptr;  // written; what follows reuses the scratch in stream order and fills out_latent
-    } else {
-      latent_only = false;
+      return MTLA_OK;
     }
   }
   if (g.dtype == MTLA_F32) {  // the un-absorbed form in fp32
@@ -1339,7 +1323,7 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
   ab.out_bf16 = use_mfma ? 1 : 0;
   ab.plane = at.q_plane = rows * g.n_heads * (g.r + g.d_rope);  // two bf16 planes fill the fp32 area
   if (!hip_ok(launch_absorb(ab, g.dtype, st))) return MTLA_ERR_HIP;
-  const bool timed = !latent_only && c->prof_n < (int)c->ev_start.size();
+  const bool timed = c->prof_n < (int)c->ev_start.size();
   EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
   if (timed) {
     ev.start = c->ev_start[c->prof_n];

@@ -149,12 +149,9 @@ struct ExplicitArgs {
   long long capacity = 0;  // tokens a sequence may hold
   int q_f16 = 0;           // q and q_rope are fp16 and already carry scale_log2 (the layer's own projections)
   void* out16 = nullptr;   // if set: the output goes here as fp16 [B, T, n_heads, d_head] instead of to `out`
-  // > 0 (attention launch only): the latent-space output.  The values are the partial states
-  // themselves (cprime, the same rows for every head), r / d_head column slices of d_head per job, and
-  // `out` is [B, T, n_heads, r].
-  int n_slices = 0;
+  int n_slices = 0;        // fp32 form only, latent-space output: column slices of the partial states per head
   int unpaired = 0;        // attention launch: one row block per workgroup instead of a heavy and a light one
-  float* out_latent = nullptr;  // if set (whole sequences only): also softmax . C_hat' [B, T, n_heads, r], by such a launch
+  float* out_latent = nullptr;  // if set (whole sequences only): also softmax . C_hat' [B, T, n_heads, r]
 };
 
 // C = A W^T on the matrix cores for up to four W that share A (see gemm_nt_kernel for the ways out).
@@ -358,6 +355,8 @@ bool layer_supported(const LayerFrontArgs& a);
 hipError_t launch_layer_front(const LayerFrontArgs& a, hipStream_t st);
 hipError_t launch_layer_out(const LayerOutArgs& a, hipStream_t st);
 bool prefill_explicit_supported(const ExplicitArgs& a);
+// the attention launch where out_latent is asked for as well
+hipError_t launch_attn_latent(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 bool gemm_nt_supported(const GemmArgs& a);
 hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st);

@@ -9,7 +9,8 @@
 // query rows per head this is the cheaper form (2 (d_h + d_R) + 2 d_h flop per open (row, column)
 // pair instead of 2 (r + d_R) + 2 r), it needs neither the absorbed query operand nor the latent
 // partials, and every matrix instruction works on 16 real query rows.  The absorbed form remains
-// for decode (one row per head) and whenever the latent-space output is asked for.
+// for decode (one row per head).  The latent-space output, where it is asked for, comes from the same weights
+// (prefill_latent.hip).
 //
 // Everything between the bf16 inputs and the fp32 output is IEEE half: the partial states, the
 // keys, the values and the softmax weights each carry 11 significant bits instead of bf16's 8 (the
@@ -28,84 +29,13 @@
 //                         registers)
 #include <type_traits>
 
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
 namespace mtla {
 
 namespace {
-
-typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));  // staging registers (a plain vector type: promoted reliably)
-typedef short4_t __attribute__((address_space(3))) * lds_short4_ptr;
-
-// 8 bf16 values, each times `scale` -> 8 fp16 values
-__device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v, float scale = 1.f) {
-  u32x4_t o;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    o[i] = pack_f16x2(__uint_as_float(v[i] << 16) * scale, __uint_as_float(v[i] & 0xffff0000u) * scale);
-  return o;
-}
-
-// ---- memory -> LDS without registers --------------------------------------------------------
-//
-// Both kernels below stream their operands from memory straight into LDS: 16 bytes per lane, 64
-// lanes fill 1 KB of consecutive LDS, several tiles ahead of the one being multiplied, so no
-// register carries a tile and one barrier per tile is enough.  Rows are stored without padding;
-// each 16-byte piece j of row `row` sits at position j ^ swizzle(row), chosen per region so that
-// the reads of the matrix-core operands are free of bank conflicts:
-//   swz_rows16   ds_read_b128, 16 lanes = 16 consecutive rows, same logical piece
-//   swz_tr       transposing 8-byte reads, 32 lanes = 8 consecutive rows x 32 bytes
-// The swizzle is applied on the way in: a lane asks memory for the piece that belongs at its place.
-template <int PC>  // pieces per row (4, 8 or 16): 16 / PC rows share 256 bytes
-__device__ __forceinline__ int swz_rows16(int row) {
-  return (row / (16 / PC)) & (PC - 1);
-}
-template <int PC>
-__device__ __forceinline__ int swz_tr(int row) {
-  return ((row / (16 / PC)) & (PC / 2 - 1)) << 1;
-}
-
-typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
-
-// 64 lanes x 16 bytes from memory to 1 KB of LDS starting at byte address `lds_addr` (the same in
-// every lane); lane i's 16 bytes land at lds_addr + 16 i.  Counted by vmcnt like any load.  Written
-// as an instruction of its own so that the compiler keeps no account of it: the waits for these
-// loads are the explicit ones below, and ordinary LDS reads are not held back by loads in flight
-// into another buffer.
-__device__ __forceinline__ void load_to_lds_16(const void* src, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(src) : "memory", "m0");
-}
-// The same with the address as a wavefront-uniform base and a 32-bit byte offset per lane: a loop that only moves the
-// base pays no vector instruction for the addresses of its loads.
-__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_but() {  // until at most N of this wavefront's loads are in flight
-  static_assert(N >= 0 && N <= 15, "vmcnt field");
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_loads_but(int n) {  // wavefront-uniform n, 0 .. 15
-  switch (n) {
-#define MTLA_W(N_) case N_: wait_loads_but<N_>(); break;
-    MTLA_W(1) MTLA_W(2) MTLA_W(3) MTLA_W(4) MTLA_W(5) MTLA_W(6) MTLA_W(7) MTLA_W(8) MTLA_W(9) MTLA_W(10)
-    MTLA_W(11) MTLA_W(12) MTLA_W(13) MTLA_W(14) MTLA_W(15)
-#undef MTLA_W
-    default: wait_loads_but<0>(); break;
-  }
-}
-// workgroup barrier without a fence: callers order their own memory traffic around it
-__device__ __forceinline__ void barrier_only() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // C[row][n] = sum_k A[row][k] W[n][k]   (A [M][K], W [N][K], C [M][N]; A and W both fp16 or both bf16,
 // K % 32 == 0, N % 8 == 0), fp32 accumulation, one of three ways out (GemmSegment::epi):
@@ -345,16 +275,6 @@ struct TileGeom {
   static_assert(BYTES % 1024 == 0 && K_BYTES % 1024 == 0 && R_BYTES % 1024 == 0, "1 KB per wavefront load");
 };
 
-// <x, y> of 8 fp16 pairs, summed in fp32
-__device__ __forceinline__ float dot8(u32x4_t x, u32x4_t y, float c) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t xi = x[i], yi = y[i];  // (a bit_cast of a vector element takes element 0)
-    c = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, xi), __builtin_bit_cast(f16x2_t, yi), c, false);
-  }
-  return c;
-}
-
 // The open columns of row m are the final states of the slots that closed before it, j < (p0 + m) / s -- the same
 // columns for all heads' rows of a block up to where they end -- and the row's own running state.  That own
 // column is not a tile column: it starts the row off (reference = its logit, weight 1, output = its value), formed
@@ -380,18 +300,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int T = a.T, s = a.stride, nh = a.n_heads;
-  // Workgroups are handed to the 8 XCDs in turn.  The row blocks of one (sequence, head) read the
-  // same keys and values, so they are numbered to land on one XCD and meet in its L2: workgroup w of
-  // the launch takes job (w / 8) + (w % 8) * (jobs / 8), jobs ordered (sequence, head, block or block pair).
+  // Workgroups are handed to the 8 XCDs in turn (w % 8).  The row blocks of one (sequence, head) read the same keys and
+  // values, so they are numbered to land on one XCD and meet in its L2, and the (sequence, head) pairs are dealt to the
+  // XCDs in turn, so that long and short sequences fall on all of them.  Single blocks: those with most columns first.
   const int n_blocks = (T + BM - 1) / BM, n_units = a.unpaired ? n_blocks : (n_blocks + 1) / 2;
-  const unsigned jobs = gridDim.x, w = blockIdx.x;
-  const unsigned job = jobs % 8 == 0 ? (w >> 3) + (w & 7) * (jobs >> 3) : w;
-  // Latent-space output (a.n_slices > 0): the values are the partial states themselves, DH of their r
-  // columns per job (the same rows for every head), and the output row has r columns per head.
-  const int n_sl = LAYER || a.n_slices < 1 ? 1 : a.n_slices;
-  const bool lat = !LAYER && a.n_slices > 0;
-  const int unit = (int)(job % (unsigned)n_units), sl = (int)(job / (unsigned)n_units % (unsigned)n_sl),
-            h = (int)(job / (unsigned)(n_units * n_sl) % (unsigned)nh), b = (int)(job / (unsigned)(n_units * n_sl * nh));
+  const int per_xcd = (nh * a.batch + 7) / 8, i_xcd = (int)(blockIdx.x >> 3);
+  const int unit = a.unpaired ? i_xcd / per_xcd : i_xcd % n_units;
+  const int hb = 8 * (a.unpaired ? i_xcd % per_xcd : i_xcd / n_units) + (int)(blockIdx.x & 7);
+  if (hb >= nh * a.batch) return;
+  const int h = hb % nh, b = hb / nh;
   const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
   // A continuing sequence has p0 tokens behind it: the final states of its first p0 / s slots are the
   // first rows of its part of the key / value arrays (one per slot), its new rows follow.
@@ -399,20 +316,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   int p0 = CONT ? a.pos0[b] : 0;
   if (CONT && (p0 < 0 || p0 / s > a.past_pitch)) p0 = a.past_pitch * s;  // out of range (reported by the front launch): stay inside the arrays
   const int j0 = p0 / s, past = j0;
-  if (CONT && a.advance && unit == 0 && h == 0 && sl == 0) {
+  if (CONT && a.advance && unit == 0 && h == 0) {
     const long long end = (long long)a.pos0[b] + (len > 0 ? len : 0);
     if (end <= a.capacity && len > 0) {
       if (tid == 0) a.advance[b] = (int32_t)end;
       for (int e = tid; e < a.r; e += NT) a.tail_c[(size_t)b * a.r + e] = a.tail_next[(size_t)b * a.r + e];
     }
   }
-  const size_t out_stride = lat ? (size_t)nh * a.r : (size_t)nh * DH;  // elements per output row
-  float* out = lat ? a.out + ((size_t)b * T * nh + h) * a.r + (size_t)sl * DH : a.out + ((size_t)b * T * nh + h) * DH;
+  const size_t out_stride = (size_t)nh * DH;  // elements per output row
+  float* out = a.out + ((size_t)b * T * nh + h) * DH;
   const uint16_t* kx = reinterpret_cast<const uint16_t*>(a.kx) + ((size_t)b * Tp * nh + h) * DH;
-  const uint16_t* vx = lat ? reinterpret_cast<const uint16_t*>(a.cprime) + (size_t)b * Tp * a.r + (size_t)sl * DH
-                           : reinterpret_cast<const uint16_t*>(a.vx) + ((size_t)b * Tp * nh + h) * DH;
+  const uint16_t* vx = reinterpret_cast<const uint16_t*>(a.vx) + ((size_t)b * Tp * nh + h) * DH;
   const uint16_t* kr16 = reinterpret_cast<const uint16_t*>(a.kr16) + (size_t)b * Tp * DR;
-  const uint32_t kv_stride = (uint32_t)(nh * DH), v_stride = lat ? (uint32_t)a.r : kv_stride;
+  const uint32_t kv_stride = (uint32_t)(nh * DH);
 
   // ---- what this thread brings in of every tile.  Wavefront wv fills the 1 KB chunks wv, wv + NW, ..
   // of a region; lane i of it the chunk's piece i: row and (swizzled) source piece, the same for
@@ -470,7 +386,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
     int run_end = 0;              // tiles below it follow the bases as they are
     uint64_t base_k[NIK], base_v[NIK], base_r = 0;  // (addresses)
-    uint32_t step_k = 0, step_v = 0, step_r = 0;    // bytes from a tile to the next
+    uint32_t step_k = 0, step_r = 0;                // bytes from a tile to the next (values as keys)
     uint32_t off_k = 0, off_v = 0, off_r = 0;       // bytes from a tile's first source row to the lane's piece
     auto start_run = [&](int t) {  // tile t begins a run of tiles whose rows are at one distance, or is one of its own
       const int c0 = BN * t;
@@ -481,16 +397,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       const int rs = in_past ? 1 : s;
       const uint32_t row0 = in_past ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
       off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
-      off_v = 2 * ((uint32_t)(row_k * rs) * v_stride + src_v);
+      off_v = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_v);
       off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
 #pragma unroll
       for (int i = 0; i < NIK; ++i) {
         base_k[i] = (uint64_t)(uintptr_t)kx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
-        base_v[i] = (uint64_t)(uintptr_t)vx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * v_stride;
+        base_v[i] = (uint64_t)(uintptr_t)vx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
       }
       base_r = (uint64_t)(uintptr_t)kr16 + 2 * (uint64_t)row0 * DR;
       step_k = 2 * (uint32_t)(BN * rs) * kv_stride;
-      step_v = 2 * (uint32_t)(BN * rs) * v_stride;
       step_r = 2 * (uint32_t)(BN * rs) * DR;
     };
     auto issue = [&](int t) {
@@ -503,7 +418,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
           load_to_lds_16(reinterpret_cast<const void*>(base_k[i]), off_k, buf + G::K_OFF + chunk);
           load_to_lds_16(reinterpret_cast<const void*>(base_v[i]), off_v, buf + G::V_OFF + chunk);
           base_k[i] += step_k;
-          base_v[i] += step_v;
+          base_v[i] += step_k;
         }
         load_to_lds_16(reinterpret_cast<const void*>(base_r), off_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
         base_r += step_r;
@@ -514,7 +429,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
         const uint32_t srow = src_row(BN * t + row_k + i * IROWS);
         const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
         load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
-        load_to_lds_16(vx + srow * v_stride + src_v, buf + G::V_OFF + chunk);
+        load_to_lds_16(vx + srow * kv_stride + src_v, buf + G::V_OFF + chunk);
       }
       load_to_lds_16(kr16 + src_row(BN * t + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
     };
@@ -543,7 +458,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       const uint32_t own = (uint32_t)(past + mr);
       const uint16_t* kp = kx + own * kv_stride + 8 * g;
       const uint16_t* krp = kr16 + own * DR + 8 * g;
-      const uint16_t* vp = vx + own * v_stride + 4 * g;
+      const uint16_t* vp = vx + own * kv_stride + 4 * g;
       u32x4_t kd[KQ];
       uint2 vd[MT];
 #pragma unroll
@@ -614,6 +529,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
             kf[i & 1][j][sb] = read_k(x / KQ, x % KQ, sb);
           }
       };
+      __builtin_amdgcn_s_setprio(1);  // the stretch of matrix instructions ahead of the other wavefront's arithmetic (1 - 2 %)
       read_group(0);
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
@@ -637,6 +553,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(0, mt);
       __builtin_amdgcn_sched_barrier(0);
 
+      __builtin_amdgcn_s_setprio(0);
       // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
       if (BN * t + 2 * BN > all_below) {  // wavefront-uniform: the last tiles only
 #pragma unroll
@@ -752,13 +669,11 @@ template <int DH, int DR>
 hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
   constexpr int NW = 4;
   const int n_blocks = (a.T + 32 * NW - 1) / (32 * NW);
-  const int n_sl = a.n_slices > 0 ? a.n_slices : 1;
-  if (a.n_slices > 0 && (a.q_f16 != 0 || a.n_slices * DH != a.r)) return hipErrorInvalidValue;
   // Two row blocks per workgroup, unless that leaves the chip (two workgroups on each of 256 units) partly empty: then a
   // block each, which the units run side by side.
   ExplicitArgs x = a;
-  x.unpaired = (size_t)((n_blocks + 1) / 2) * n_sl * a.n_heads * a.batch < 512;
-  const dim3 grid((unsigned)(x.unpaired ? n_blocks : (n_blocks + 1) / 2) * n_sl * a.n_heads * a.batch);
+  x.unpaired = (size_t)((n_blocks + 1) / 2) * a.n_heads * a.batch < 512;
+  const dim3 grid((unsigned)(x.unpaired ? n_blocks : (n_blocks + 1) / 2) * ((a.n_heads * a.batch + 7) / 8 * 8));
   const bool layer = a.q_f16 != 0;  // comes with out16
   if (layer != (a.out16 != nullptr) || (layer && !a.pos0)) return hipErrorInvalidValue;
   if (layer) launch_timed(attn_explicit_kernel<DH, DR, NW, true, true>, grid, dim3(64 * NW), 0, st, ev, x);
@@ -772,8 +687,8 @@ hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const Eve
 bool prefill_explicit_supported(const ExplicitArgs& a) {
   return (a.d_head == 64 || a.d_head == 128) && (a.d_rope == 32 || a.d_rope == 64) && a.r % 64 == 0 && a.r >= 64 &&
          a.r <= 512 && a.n_heads <= 65535 && a.batch <= 65535 &&
-         (size_t)((a.T + 255) / 256) * a.n_heads * a.batch * (a.out_latent ? a.r / a.d_head : 1) < (size_t)1 << 31 &&  // workgroups of the attention launch
-         (!a.out_latent || (a.r % a.d_head == 0 && !a.pos0 && !a.q_f16)) &&
+         (size_t)((a.T + 127) / 128) * ((size_t)a.n_heads * a.batch + 7) < (size_t)1 << 31 &&  // workgroups of the attention launch
+         (!a.out_latent || ((a.r & (a.r - 1)) == 0 && !a.pos0 && !a.q_f16)) &&
          (size_t)(a.past_pitch + a.T) * a.n_heads * a.d_head < (size_t)1 << 31 &&  // 32-bit element offsets inside one sequence
          (size_t)a.batch * (a.past_pitch + a.T) < (size_t)1 << 31;                 // rows of the key / value product
 }
@@ -823,7 +738,7 @@ static int gemm_col_blocks(const GemmArgs& a, int bn) {
 // 4096 columns at K = 512 took 198, 202, 232 and 368 us).  With ragged rows the number of jobs is not known here:
 // three quarters of the most, and half a round more, on average, than they fill.
 static float gemm_cost(const GemmArgs& a, int& pick) {
-  static constexpr struct { int bm, bn; float rate; } kTiles[] = {{256, 256, 1.f}, {256, 128, 0.97f}, {128, 128, 0.85f}, {64, 64, 0.54f}};
+  static constexpr struct { int bm, bn; float rate; } kTiles[] = {{256, 256, 1.f}, {256, 128, 0.92f}, {128, 128, 0.85f}, {64, 64, 0.54f}};
   const bool ragged = a.rows.n_new || a.rows.pos0;
   float best = 0.f;
   pick = 0;
@@ -912,17 +827,7 @@ hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const 
     if (x.d_head == 128 && x.d_rope == 64) return launch_attn_explicit<128, 64>(x, st, e);
     return hipErrorInvalidValue;
   };
-  if (!a.out_latent) return attend(a, ev);
-  // The latent-space output is softmax . C_hat' with the same weights: a second pass of the same kernel
-  // whose values are the partial states, d_head of their r columns per job (the logits are formed
-  // again for every slice).  The timed launch is this one.
-  e = attend(a, EventPair());
-  if (e != hipSuccess) return e;
-  ExplicitArgs l = a;
-  l.out = a.out_latent;
-  l.out_latent = nullptr;
-  l.n_slices = a.r / a.d_head;
-  return attend(l, ev);
+  return a.out_latent ? launch_attn_latent(a, st, ev) : attend(a, ev);
 }
 
 }  // namespace mtla

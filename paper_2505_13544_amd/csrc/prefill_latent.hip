@@ -1,0 +1,410 @@
+// Parallel form with the latent-space output as well (bf16 storage, fp16 inside, gfx950): out = softmax . V and
+// out_latent = softmax . C_hat' from one set of weights.
+//
+// Beside the d_h values per column of the plain form (attn_explicit_kernel, whose notes on layouts, columns and
+// references hold here too) every column brings r latent ones, the same for all heads.  The logits are formed once: a
+// workgroup owns 128 query rows, its eight wavefronts form the weights of 16 rows each, hand them to one another through LDS
+// (as the B operand of the value product, 1 KB per 16 rows and tile), and multiply 64 rows by a quarter of the
+// d_h + r value columns each.  The weights of tile t + 1 are formed between the barrier that makes those of tile t
+// visible and the next one, so the matrix instructions of one tile cover the arithmetic of the other.
+// With a pass of the plain kernel for every d_h of the r columns (the logits formed r / d_h + 1 times: 3200 flop per pair
+// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us, now 122
+// (the outputs alone, 313 MB, are 66 at the rate of a large copy).
+#include "lds_stream.h"
+#include "mtla_device.h"
+#include "mtla_kernels.h"
+
+namespace mtla {
+
+namespace {
+
+template <int DH, int DR, int R>
+struct LatentGeom {
+  static constexpr int BN = 32, BM = 128, NW = 8;
+  static constexpr int VC = DH / 8, RC = DR / 8, CC = R / 8;                                      // 16-byte pieces per row
+  static constexpr int K_BYTES = BN * DH * 2, R_BYTES = BN * DR * 2, C_BYTES = BN * R * 2;
+  static constexpr int KT = K_BYTES + R_BYTES, VT = K_BYTES + C_BYTES;                            // one tile's keys, values
+  static constexpr int KBUF = 3, VBUF = 2;
+  static constexpr int P_BYTES = BM * BN * 2;                                                     // one tile's weights
+  static constexpr int K_OFF = 0, V_OFF = KBUF * KT, P_OFF = V_OFF + VBUF * VT, BYTES = P_OFF + 2 * P_BYTES;
+  static constexpr int NCK = K_BYTES / 1024, NCR = R_BYTES / 1024, NCC = C_BYTES / 1024;          // wavefront loads per region
+  static constexpr int NLC = NCC / NW > 0 ? NCC / NW : 1;                                         // per wavefront
+  static constexpr int NV = DH / 64, NC = R / 64;                                                 // 16-column value tiles per wavefront
+  static_assert(NCK <= NW && NCR <= NW, "one load per wavefront");
+};
+
+template <int DH, int DR, int R>
+__global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
+  using G = LatentGeom<DH, DR, R>;
+  constexpr int BN = G::BN, BM = G::BM, NT = 64 * G::NW, KD = DH / 32, KQ = (DH + DR) / 32;
+  constexpr int VC = G::VC, RC = G::RC, CC = G::CC, NV = G::NV, NC = G::NC;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[G::BYTES];
+  __shared__ float s_alpha[2][BM];  // a tile's change of a row's reference
+  __shared__ __attribute__((aligned(16))) int s_flag[2][G::NW];  // whether it has any
+  __shared__ float s_inv[BM];
+
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int jc = wv & 3, ir = wv >> 2;  // quarter of the value columns, half of the rows
+  const int T = a.T, s = a.stride, nh = a.n_heads;
+  // (sequence, head) pairs dealt to the XCDs, their blocks on one of them, those with most columns first
+  const int n_blocks = (T + BM - 1) / BM, per_xcd = (nh * a.batch + 7) / 8, i_xcd = (int)(blockIdx.x >> 3);
+  const int m0 = (n_blocks - 1 - i_xcd / per_xcd) * BM, hb = 8 * (i_xcd % per_xcd) + (int)(blockIdx.x & 7);
+  if (hb >= nh * a.batch) return;
+  const int h = hb % nh, b = hb / nh;
+  const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
+  float* out = a.out + ((size_t)b * T * nh + h) * DH;
+  float* latent = a.out_latent + ((size_t)b * T * nh + h) * R;
+  if (m0 >= len) {  // padding rows only
+    const int rows = T - m0 < BM ? T - m0 : BM;
+    constexpr int N4 = (DH + R) / 4;
+    for (int i = tid; i < rows * N4; i += NT) {
+      const size_t row = (size_t)(m0 + i / N4);
+      const int c = 4 * (i % N4);
+      *reinterpret_cast<float4_t*>(c < DH ? out + row * nh * DH + c : latent + row * nh * R + (c - DH)) = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    return;
+  }
+  const uint16_t* kx = reinterpret_cast<const uint16_t*>(a.kx) + ((size_t)b * T * nh + h) * DH;
+  const uint16_t* vx = reinterpret_cast<const uint16_t*>(a.vx) + ((size_t)b * T * nh + h) * DH;
+  const uint16_t* cx = reinterpret_cast<const uint16_t*>(a.cprime) + (size_t)b * T * R;
+  const uint16_t* kr16 = reinterpret_cast<const uint16_t*>(a.kr16) + (size_t)b * T * DR;
+  const uint32_t kv_stride = (uint32_t)(nh * DH);
+
+  const int m_last = (m0 + BM < len ? m0 + BM : len) - 1;
+  const int n_cols = m_last / s, n_tiles = (n_cols + BN - 1) / BN;
+
+  // ---- what this wavefront brings in of every tile: 1 KB pieces of each region.  Regions with fewer of them than
+  // wavefronts are brought by some twice, so that every wavefront has the same number of loads in flight.
+  const int pk = 64 * (wv % G::NCK) + lane, pr = 64 * (wv % G::NCR) + lane, pc = 64 * (wv % G::NCC) + lane;
+  const int row_k = pk / VC, row_r = pr / RC, row_c = pc / CC;
+  constexpr int C_ROWS = 64 * G::NW / CC;  // rows between a wavefront's pieces of the latent region (a multiple of 8)
+  const uint32_t src_k = 8 * ((pk % VC) ^ swz_rows16<VC>(row_k)), src_v = 8 * ((pk % VC) ^ swz_tr<VC>(row_k));
+  const uint32_t src_r = 8 * ((pr % RC) ^ swz_rows16<RC>(row_r)), src_c = 8 * ((pc % CC) ^ swz_tr<CC>(row_c));
+  const uint32_t off_k = 2 * ((uint32_t)(row_k * s) * kv_stride + src_k), off_v = 2 * ((uint32_t)(row_k * s) * kv_stride + src_v);
+  const uint32_t off_r = 2 * ((uint32_t)(row_r * s) * DR + src_r), off_c = 2 * ((uint32_t)(row_c * s) * R + src_c);
+  const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
+  const int full = n_cols / BN;            // tiles whose rows are all there, s apart
+  auto src_row = [&](int c) -> uint32_t {  // source row of column c (columns past the last one: a readable duplicate)
+    c = c < n_cols ? c : n_cols - 1;
+    return (uint32_t)(c * s + s - 1);
+  };
+  // The lane's place, out of sight of the compiler: what only a partial last tile needs is then formed there instead of
+  // being kept in registers across the loop (160 of the 256 hold the sums).
+  auto here = [&](int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  auto issue_keys = [&](int t) {  // two loads
+    const uint32_t buf = lds_addr + G::K_OFF + (uint32_t)(t % G::KBUF) * (uint32_t)G::KT;
+    const uint32_t dk = buf + (uint32_t)(wv % G::NCK) * 1024u, dr = buf + G::K_BYTES + (uint32_t)(wv % G::NCR) * 1024u;
+    if (t < full) {
+      const size_t row0 = (size_t)(BN * t) * s + s - 1;
+      load_to_lds_16(kx + row0 * kv_stride, off_k, dk);
+      load_to_lds_16(kr16 + row0 * DR, off_r, dr);
+    } else {
+      const int xk = here(pk), xr = here(pr);
+      load_to_lds_16(kx + (size_t)src_row(BN * t + xk / VC) * kv_stride + 8 * ((xk % VC) ^ swz_rows16<VC>(xk / VC)), dk);
+      load_to_lds_16(kr16 + (size_t)src_row(BN * t + xr / RC) * DR + 8 * ((xr % RC) ^ swz_rows16<RC>(xr / RC)), dr);
+    }
+  };
+  auto issue_value = [&](int t, int i) {  // load i of 1 + NLC
+    const uint32_t buf = lds_addr + G::V_OFF + (uint32_t)(t & 1) * (uint32_t)G::VT;
+    if (i == 0) {
+      const uint32_t dv = buf + (uint32_t)(wv % G::NCK) * 1024u;
+      if (t < full) {
+        load_to_lds_16(vx + ((size_t)(BN * t) * s + s - 1) * kv_stride, off_v, dv);
+      } else {
+        const int x = here(pk);
+        load_to_lds_16(vx + (size_t)src_row(BN * t + x / VC) * kv_stride + 8 * ((x % VC) ^ swz_tr<VC>(x / VC)), dv);
+      }
+    } else {
+      const uint32_t dc = buf + G::K_BYTES + (uint32_t)(wv % G::NCC + G::NW * (i - 1)) * 1024u;
+      if (t < full) {
+        load_to_lds_16(cx + ((size_t)(BN * t + C_ROWS * (i - 1)) * s + s - 1) * R, off_c, dc);
+      } else {
+        const int x = here(pc);
+        load_to_lds_16(cx + (size_t)src_row(BN * t + x / CC + C_ROWS * (i - 1)) * R + 8 * ((x % CC) ^ swz_tr<CC>(x / CC)), dc);
+      }
+    }
+  };
+  auto issue_own = [&](int k) {  // values of the block's own rows 32 k .. 32 k + 31, in the place of tile k / 2's
+    const uint32_t buf = lds_addr + G::V_OFF + (uint32_t)(k >> 1) * (uint32_t)G::VT;
+    auto own_row = [&](int row) -> size_t { return (size_t)(m0 + BN * k + row < len ? m0 + BN * k + row : len - 1); };
+    load_to_lds_16(vx + own_row(row_k) * kv_stride + src_v, buf + (uint32_t)(wv % G::NCK) * 1024u);
+#pragma unroll
+    for (int i = 0; i < G::NLC; ++i)
+      load_to_lds_16(cx + own_row(row_c + C_ROWS * i) * R + src_c, buf + G::K_BYTES + (uint32_t)(wv % G::NCC + G::NW * i) * 1024u);
+  };
+  issue_own(0);
+  issue_own(2);
+  if (n_tiles > 0) issue_keys(0);
+
+  // ---- queries of the wavefront's 16 rows (its share of the weights), and the row's own column: reference, weight 1
+  u32x4_t qf[KQ];
+  float neg_ref;  // minus the row's reference
+  float l_run;
+  const int m_own = m0 + 16 * wv + l16, m_clamp = m_own < len ? m_own : len - 1;
+  const int bound = m_clamp / s;                              // columns open to the lane's row
+  {
+    const size_t row = ((size_t)b * T + m_clamp) * nh + h;
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + row * DH + 8 * g;
+    const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + row * DR + 8 * g;
+    const uint16_t* kp = kx + (size_t)m_clamp * kv_stride + 8 * g;
+    const uint16_t* krp = kr16 + (size_t)m_clamp * DR + 8 * g;
+    u32x4_t kd[KQ];
+#pragma unroll
+    for (int kk = 0; kk < KQ; ++kk) {
+      qf[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
+      kd[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+    }
+    float e = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KQ; ++kk) {
+      qf[kk] = bf16x8_to_f16x8(qf[kk], a.scale_log2);  // logits in units of log2
+      e = dot8(kd[kk], qf[kk], e);
+    }
+    e += __shfl_xor(e, 16, kWave);
+    e += __shfl_xor(e, 32, kWave);
+    neg_ref = -e;
+    l_run = g == 0 ? 1.f : 0.f;
+  }
+  const int all_below = (m0 + 16 * wv) / s, none_from = (m0 + 16 * wv + 15) / s;  // of the rows whose weights it forms
+  const int none_rows = (m0 + 64 * ir + 63) / s;                                  // of the rows it sums
+
+  // where this lane reads: key rows 16 sb + l16 (piece 4 kk + g), value rows 4g + l16/4 (+16)
+  const uint32_t k_row_off = (uint32_t)(l16 * VC * 16), k_swz = (uint32_t)(swz_rows16<VC>(l16) ^ g) << 4;
+  const uint32_t r_row_off = (uint32_t)(l16 * RC * 16), r_swz = (uint32_t)(swz_rows16<RC>(l16) ^ g) << 4;
+  const int v_row = 4 * g + (l16 >> 2);
+  const uint32_t v_off = (uint32_t)(v_row * VC * 16 + 8 * (l16 & 1)), v_swz = (uint32_t)(swz_tr<VC>(v_row) ^ ((l16 & 3) >> 1)) << 4;
+  const uint32_t c_off = (uint32_t)(v_row * CC * 16 + 8 * (l16 & 1)), c_swz = (uint32_t)(swz_tr<CC>(v_row) ^ ((l16 & 3) >> 1)) << 4;
+
+  // The weights of tile t for the wavefront's 16 rows into LDS, as the B operand of the value product.
+  auto form_weights = [&](int t) {
+    unsigned char* dst = lds + G::P_OFF + (t & 1) * G::P_BYTES + wv * 1024 + lane * 16;
+    u32x4_t pb = {0u, 0u, 0u, 0u};
+    int flag = 0;
+    if (BN * t < none_from) {
+      const unsigned char* kb = lds + G::K_OFF + (t % G::KBUF) * G::KT + k_row_off;
+      const unsigned char* rb = lds + G::K_OFF + (t % G::KBUF) * G::KT + G::K_BYTES + r_row_off;
+      const uint32_t ks = (uint32_t)here((int)k_swz), rs = (uint32_t)here((int)r_swz);
+      float4_t sacc[2];
+      sacc[0] = sacc[1] = float4_t{neg_ref, neg_ref, neg_ref, neg_ref};
+      constexpr int KG = KQ % 3 == 0 ? 3 : 2;  // steps whose keys are read together
+#pragma unroll
+      for (int k0 = 0; k0 < KQ; k0 += KG) {
+        u32x4_t kf[KG][2];
+#pragma unroll
+        for (int k = 0; k < KG; ++k)
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb) {
+            const int kk = k0 + k;
+            if (kk < KQ)
+              kf[k][sb] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kb + sb * (16 * VC * 16) + ((uint32_t)(64 * kk) ^ ks))
+                                  : *reinterpret_cast<const u32x4_t*>(rb + sb * (16 * RC * 16) + ((uint32_t)(64 * (kk - KD)) ^ rs));
+          }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < KG; ++k)
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb)
+            if (k0 + k < KQ)
+              sacc[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kf[k][sb]),
+                                                                __builtin_bit_cast(f16x8_t, qf[k0 + k]), sacc[sb], 0, 0, 0);
+      }
+      if (BN * t + BN > all_below) {
+        const int d = bound - (BN * t + 4 * g);
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sacc[sb][v] = 16 * sb + v < d ? sacc[sb][v] : -INFINITY;
+      }
+      constexpr float kRebase = 12.f;
+      int top = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float x = sacc[i >> 2][i & 3];
+        top = max(top, __float_as_int(x));
+      }
+      if (__any(top > __float_as_int(kRebase))) {  // the rows' sums are scaled by whoever holds them, before they take this tile
+        float up = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) up = fmaxf(up, sacc[i >> 2][i & 3]);
+        up = fmaxf(up, __shfl_xor(up, 16, kWave));
+        up = fmaxf(up, __shfl_xor(up, 32, kWave));
+        float alpha = 1.f;
+        if (up > kRebase) {
+          alpha = __builtin_amdgcn_exp2f(-up);
+          neg_ref -= up;
+          l_run *= alpha;
+          sacc[0] -= up;
+          sacc[1] -= up;
+        }
+        if (g == 0) s_alpha[t & 1][16 * wv + l16] = alpha;
+        flag = 1;
+      }
+      const f16x2_t ones = {(_Float16)1.f, (_Float16)1.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4_t& x = sacc[i >> 1];
+        const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(x[2 * (i & 1)]), __builtin_amdgcn_exp2f(x[2 * (i & 1) + 1]));
+        pb[i] = two;
+        l_run = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run, false);
+      }
+    }
+    *reinterpret_cast<u32x4_t*>(dst) = pb;
+    if (lane == 0) s_flag[t & 1][wv] = flag;
+  };
+
+  // ---- sums of the wavefront's 64 rows and quarter of the columns, from the rows' own values.  These pass through LDS: read
+  // from memory in this layout (8 bytes of each of 16 rows per load) a block spent 29000 cycles here, now 13000.
+  float4_t acc[4][NV + NC];
+  auto take_own = [&](int rt0) {
+    const unsigned char* vb = lds + G::V_OFF + ir * G::VT + l16 * (VC * 16) + 8 * (g & 1);
+    const unsigned char* cb = lds + G::V_OFF + ir * G::VT + G::K_BYTES + l16 * (CC * 16) + 8 * (g & 1);
+#pragma unroll
+    for (int i = 0; i < NV + NC; ++i) {
+      const int piece = i < NV ? (2 * (NV * jc + i) + (g >> 1)) ^ swz_tr<VC>(l16) : (2 * (NC * jc + i - NV) + (g >> 1)) ^ swz_tr<CC>(l16);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint2 v = *reinterpret_cast<const uint2*>((i < NV ? vb : cb) + k * (256 * (i < NV ? VC : CC)) + 16 * piece);
+        acc[rt0 + k][i] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+  wait_loads_but<0>();
+  barrier_only();
+  take_own(0);
+  barrier_only();
+  issue_own(1);
+  issue_own(3);
+  if (n_tiles > 1) issue_keys(1);
+  if (n_tiles > 0) form_weights(0);
+  wait_loads_but<0>();
+  barrier_only();
+  take_own(2);
+  barrier_only();
+  if (n_tiles > 0)
+    for (int i = 0; i <= G::NLC; ++i) issue_value(0, i);
+  if (n_tiles > 2) issue_keys(2);
+  for (int t = 0; t < n_tiles; ++t) {
+    // values of tile t and keys of tile t + 1 have landed (keys of t + 2 may be under way), weights of tile t are written
+    if (t + 2 < n_tiles) wait_loads_but<2>();
+    else wait_loads_but<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    barrier_only();
+    // What the step brings in (values of t + 1, keys of t + 3) is asked for piece by piece between the products: all at once,
+    // the wavefronts stood at the full queue of the memory path for 600 to 900 of a step's 3750 cycles.
+    constexpr int STEPS = (NV + NC + 1) / 2;
+    auto issue_part = [&](int k) {  // part k of STEPS
+#pragma unroll
+      for (int i = 0; i <= G::NLC; ++i)
+        if (i * STEPS / (G::NLC + 1) == k && t + 1 < n_tiles) issue_value(t + 1, i);
+      if (k == STEPS - 1 && t + 3 < n_tiles) issue_keys(t + 3);
+    };
+
+    const int4 flags = *reinterpret_cast<const int4*>(&s_flag[t & 1][4 * ir]);
+    if (__builtin_amdgcn_readfirstlane(flags.x | flags.y | flags.z | flags.w)) {
+      const int f4[4] = {flags.x, flags.y, flags.z, flags.w};
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) {
+        if (!f4[rt]) continue;
+        const float alpha = s_alpha[t & 1][64 * ir + 16 * rt + l16];
+#pragma unroll
+        for (int i = 0; i < NV + NC; ++i) acc[rt][i] *= alpha;
+      }
+    }
+    // The two wavefronts of a SIMD (the two halves of the rows) take the two parts of the step in opposite order, so that the
+    // matrix instructions of one meet the arithmetic and the reads of the other.
+    if (ir == 0 && t + 1 < n_tiles) form_weights(t + 1);
+    if (BN * t < none_rows) {  // some row of this half is open to the tile
+      // ---- O^T[d, row] += V^T[d, col] P^T[col, row]: the reads of two value tiles ahead of the products of the two before
+      const unsigned char* pb_at = lds + G::P_OFF + (t & 1) * G::P_BYTES + ir * 4096 + lane * 16;
+      const unsigned char* vb = lds + G::V_OFF + (t & 1) * G::VT + v_off;
+      const unsigned char* cb = lds + G::V_OFF + (t & 1) * G::VT + G::K_BYTES + c_off;
+      const uint32_t vs = (uint32_t)here((int)v_swz), cs = (uint32_t)here((int)c_swz);
+      auto read_v = [&](int i) -> u32x4_t {
+        const unsigned char* p = i < NV ? vb + ((uint32_t)(32 * (NV * jc + i)) ^ vs) : cb + ((uint32_t)(32 * (NC * jc + i - NV)) ^ cs);
+        const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)p);
+        const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 256 * (i < NV ? VC : CC)));
+        const uint2 u0 = __builtin_bit_cast(uint2, v0), u1 = __builtin_bit_cast(uint2, v1);
+        return u32x4_t{u0.x, u0.y, u1.x, u1.y};
+      };
+      u32x4_t pb[4], vf[2][2];
+      vf[0][0] = read_v(0);
+      vf[0][1] = read_v(1);
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) pb[rt] = *reinterpret_cast<const u32x4_t*>(pb_at + rt * 1024);
+#pragma unroll
+      for (int i = 0; i < NV + NC; i += 2) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (i + 2 + k < NV + NC) vf[(i / 2 + 1) & 1][k] = read_v(i + 2 + k);
+        issue_part(i / 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (i + k < NV + NC)
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+              acc[rt][i + k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, vf[(i / 2) & 1][k]),
+                                                                      __builtin_bit_cast(f16x8_t, pb[rt]), acc[rt][i + k], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < STEPS; ++k) issue_part(k);
+    }
+    if (ir == 1 && t + 1 < n_tiles) form_weights(t + 1);
+  }
+
+  // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3
+  {
+    float l = l_run + __shfl_xor(l_run, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+    if (g == 0) s_inv[16 * wv + l16] = m_own < len ? 1.f / l : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt) {
+    const int m = m0 + 64 * ir + 16 * rt + l16;
+    if (m >= T) continue;
+    const float inv = s_inv[64 * ir + 16 * rt + l16];
+    float* po = out + (size_t)m * nh * DH + 16 * NV * jc + 4 * g;
+    float* pl = latent + (size_t)m * nh * R + 16 * NC * jc + 4 * g;
+#pragma unroll
+    for (int i = 0; i < NV + NC; ++i) {
+      const float4_t o = m < len ? acc[rt][i] * inv : float4_t{0.f, 0.f, 0.f, 0.f};  // padding rows are zeros, whatever their inputs held
+      *reinterpret_cast<float4_t*>(i < NV ? po + 16 * i : pl + 16 * (i - NV)) = o;
+    }
+  }
+}
+
+template <int DH, int DR>
+hipError_t launch_r(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
+  const dim3 grid((unsigned)((a.T + 127) / 128) * ((a.n_heads * a.batch + 7) / 8 * 8)), block(512);
+#define MTLA_CASE(RR)                                                                    \
+  if (a.r == RR) {                                                                       \
+    launch_timed(attn_latent_kernel<DH, DR, RR>, grid, block, 0, st, ev, a);             \
+    return hipGetLastError();                                                            \
+  }
+  MTLA_CASE(64)
+  MTLA_CASE(128)
+  MTLA_CASE(256)
+  MTLA_CASE(512)
+#undef MTLA_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_attn_latent(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
+  if (a.d_head == 64 && a.d_rope == 32) return launch_r<64, 32>(a, st, ev);
+  if (a.d_head == 64 && a.d_rope == 64) return launch_r<64, 64>(a, st, ev);
+  if (a.d_head == 128 && a.d_rope == 32) return launch_r<128, 32>(a, st, ev);
+  if (a.d_head == 128 && a.d_rope == 64) return launch_r<128, 64>(a, st, ev);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mtla
