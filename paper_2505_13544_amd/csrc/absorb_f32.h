@@ -46,8 +46,7 @@ __device__ __forceinline__ void absorb_f32_block(const AbsorbArgs& a, int bx, in
     } else {
       for (int i = 0; i < dh / 16; ++i) piece(*reinterpret_cast<const float4*>(w + 16 * i), i);
     }
-    dot += __shfl_xor(dot, 1, kWave);
-    dot += __shfl_xor(dot, 2, kWave);
+    dot = group_reduce<4>(dot, LaneSum());
     if (q4 == 0) qcat[(size_t)row * pitch + n] = dot * a.scale_log2;
   }
 }

@@ -10,12 +10,16 @@ namespace mtla {
 // workgroups, since a walk is a chain of load -> multiply -> store round trips (256 rows in one
 // workgroup took 17 us at batch 256); many rows (prefill): long walks that keep W_K^(h) in registers.
 __host__ __device__ constexpr int absorb_rows_per_block(int rows) { return rows >= 4096 ? 256 : 32; }
+__host__ __device__ constexpr int absorb_col_blocks(int r) { return (r + 127) / 128; }
 
 // ---------------------------------------------------------------------------
-// absorb, bf16 on the matrix cores.  Block coordinates (bx, h, bz) span (r/64 + 1, n_heads, row groups).
-// Workgroups x < r/64: wavefront w owns output columns n0 = (4x + w) * 16 of
-// head h and walks the rows 16 at a time: D[n, row] = sum_k W[n, k] q[row, k].
-// Workgroup x == r/64 copies (and scales) the RoPE query part.  The operand row is written
+// absorb, bf16 on the matrix cores.  Block coordinates (bx, h, bz) span (absorb_col_blocks(r) + 1, n_heads, row groups).
+// Workgroups x < absorb_col_blocks(r): wavefront w owns output columns n0 = (4x + w) * 32 .. + 31 of
+// head h and walks the rows 16 at a time: D[n, row] = sum_k W[n, k] q[row, k], two matrix tiles side by side.  Row i of
+// tile t is column n0 + 8 (i / 4) + 4 t + i % 4, so that a lane ends up with eight consecutive columns: it stores 16 bytes
+// per plane and a row's 64 at once (with one tile per wavefront the rows went out in pieces of 32 bytes, and the front of a
+// decode step of 256 sequences, 16 heads, r = 512 needed 1408 workgroups, more than are resident: 12.6 us, now 10.2).
+// The last workgroup of a head copies (and scales) the RoPE query part.  The operand row is written
 // as two bf16 planes, hi and lo (a.plane elements apart): the logits are then formed from an
 // almost-fp32 query at the price of a second MFMA per K step, which removes the largest
 // avoidable error of the bf16 path (rounding the absorbed query) for sequences of few slots.
@@ -37,7 +41,7 @@ __device__ __forceinline__ void absorb_mfma_block(const AbsorbArgs& a, int bx, i
   const int row_hi = row_lo + per_block < a.rows ? row_lo + per_block : a.rows;
   uint16_t* qcat = reinterpret_cast<uint16_t*>(a.qcat);
 
-  if (bx == r / 64) {  // RoPE part: qcat[row, h, r + j] = scale * q_rope[row, h, j]
+  if (bx == absorb_col_blocks(r)) {  // RoPE part: qcat[row, h, r + j] = scale * q_rope[row, h, j]
     const uint16_t* qr = reinterpret_cast<const uint16_t*>(a.q_rope);
     const int per_row = dR / 8;
     for (int idx = tid; idx < (row_hi - row_lo) * per_row; idx += kBlock) {
@@ -55,12 +59,15 @@ __device__ __forceinline__ void absorb_mfma_block(const AbsorbArgs& a, int bx, i
     return;
   }
 
-  const int n0 = (bx * kWaves + wv) * 16;
-  const uint16_t* w = reinterpret_cast<const uint16_t*>(a.w_uk) + ((size_t)h * r + n0 + l16) * DH + 8 * g;
+  const int n0 = (bx * kWaves + wv) * 32;
+  if (n0 >= r) return;
+  const uint16_t* w = reinterpret_cast<const uint16_t*>(a.w_uk) + ((size_t)h * r + n0 + 8 * (l16 >> 2) + (l16 & 3)) * DH + 8 * g;
   const uint16_t* q = reinterpret_cast<const uint16_t*>(a.q);
-  uint4 wa[KK];
+  uint4 wa[2][KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) wa[kk] = *reinterpret_cast<const uint4*>(w + 32 * kk);
+  for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) wa[nt][kk] = *reinterpret_cast<const uint4*>(w + 4 * nt * DH + 32 * kk);
   // two 16-row tiles per pass, their operands requested together
   for (int row0 = row_lo; row0 < row_hi; row0 += 32) {
     int rowt[2];
@@ -85,7 +92,7 @@ __device__ __forceinline__ void absorb_mfma_block(const AbsorbArgs& a, int bx, i
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       if (row0 + 16 * t >= row_hi) break;  // wavefront-uniform
-      float4_t acc = {0.f, 0.f, 0.f, 0.f};
+      float4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
       if constexpr (QF32) {  // hi + lo planes, two matrix instructions per K step
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
@@ -95,24 +102,30 @@ __device__ __forceinline__ void absorb_mfma_block(const AbsorbArgs& a, int bx, i
           split_bf16x2(v[2], v[3], hi.y, lo.y);
           split_bf16x2(v[4], v[5], hi.z, lo.z);
           split_bf16x2(v[6], v[7], hi.w, lo.w);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[kk]), __builtin_bit_cast(bf16x8_t, hi),
-                                                        acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[kk]), __builtin_bit_cast(bf16x8_t, lo),
-                                                        acc, 0, 0, 0);
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) {
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[nt][kk]),
+                                                              __builtin_bit_cast(bf16x8_t, hi), acc[nt], 0, 0, 0);
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[nt][kk]),
+                                                              __builtin_bit_cast(bf16x8_t, lo), acc[nt], 0, 0, 0);
+          }
         }
       } else {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[kk]),
-                                                        __builtin_bit_cast(bf16x8_t, qb[t][kk]), acc, 0, 0, 0);
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wa[nt][kk]),
+                                                              __builtin_bit_cast(bf16x8_t, qb[t][kk]), acc[nt], 0, 0, 0);
       }
-      if (validt[t]) {  // lane holds columns n0 + 4g .. + 3 of its row
-        uint32_t hi0, lo0, hi1, lo1;
-        split_bf16x2(acc[0] * a.scale_log2, acc[1] * a.scale_log2, hi0, lo0);
-        split_bf16x2(acc[2] * a.scale_log2, acc[3] * a.scale_log2, hi1, lo1);
-        uint16_t* dst = qcat + ((size_t)rowt[t] * a.n_heads + h) * E + n0 + 4 * g;
-        *reinterpret_cast<uint2*>(dst) = make_uint2(hi0, hi1);
-        *reinterpret_cast<uint2*>(dst + a.plane) = make_uint2(lo0, lo1);
+      if (validt[t]) {  // lane holds columns n0 + 8g .. + 7 of its row
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          split_bf16x2(acc[i >> 1][2 * (i & 1)] * a.scale_log2, acc[i >> 1][2 * (i & 1) + 1] * a.scale_log2, hi[i], lo[i]);
+        uint16_t* dst = qcat + ((size_t)rowt[t] * a.n_heads + h) * E + n0 + 8 * g;
+        *reinterpret_cast<uint4*>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        *reinterpret_cast<uint4*>(dst + a.plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
       }
     }
   }

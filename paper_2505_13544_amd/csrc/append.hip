@@ -43,8 +43,7 @@ __device__ __forceinline__ void hyper_linear(const T* A, const T* ha, const floa
         for (int j = 0; j < 8; ++j) dot += wv[j] * sc[8 * c8 + j];
       }
     }
-    dot += __shfl_xor(dot, 1, kWave);
-    dot += __shfl_xor(dot, 2, kWave);
+    dot = group_reduce<4>(dot, LaneSum());
     if (y < dy && q == 0) sg[y] = dot + (ha ? to_f32(ha[y]) : 0.f);
   }
 }
@@ -98,8 +97,9 @@ struct Chunk8<float> {
 // Decode step: exactly one candidate token per sequence, one workgroup per sequence.
 // Nothing but the positional branch G[slot] depends on the sequence position, so the
 // length, the latent, the old tail, the key and the thread's pieces of hyp_A are all
-// requested at once (NCH = pieces per thread of one hyp_A row, r / 32); Linear(c) is
-// finished by the time the length has arrived, and only the G row costs a second trip.
+// requested at once (NCH = pieces per thread of one hyp_A row, r / 32), and the G row as soon as the
+// length, the first to arrive, is there: it travels while Linear(c) is formed (asked for behind it, it was a
+// second trip to memory: 0.8 us of a step's 2.5 at r = 256, 1.0 of 4.9 at r = 512).
 // TC = element type of c_new: the storage type, or float when the caller's projection hands the
 // latent over unrounded (the merge and the hyper-network then see it in full precision and the cache
 // row is rounded once).
@@ -140,17 +140,17 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
       if (ha) bias = to_f32(ha[y]);
     }
   }
+  float g_pre = 0.f;  // this thread's element of the slot's row of G
+  if (hyper && dy <= kBlock && tid < dy) {
+    const int slot_c = p0 / s < a.max_slots ? p0 / s : a.max_slots - 1;  // a full sequence is refused below
+    g_pre = to_f32(reinterpret_cast<const T*>(a.hyp_G)[(size_t)slot_c * dy + tid]);
+  }
   // Layer normalisation of an unrounded latent (whole-layer call): y = (v - mean) / sqrt(var + eps),
   // two passes over the row in fp32; every thread ends up with the same mean and 1/sigma.
   float ln_mean = 0.f, ln_inv = 1.f;
   const T* ln_g = reinterpret_cast<const T*>(a.ln_gamma);
   const T* ln_b = reinterpret_cast<const T*>(a.ln_beta);
-  float g_pre = 0.f;  // ln: this thread's element of the slot's row of G, requested before the normalisation
   if (ln) {
-    if (!a.w_override && tid < dy) {
-      const int slot_c = p0 / s < a.max_slots ? p0 / s : a.max_slots - 1;  // a full sequence is refused below
-      g_pre = to_f32(reinterpret_cast<const T*>(a.hyp_G)[(size_t)slot_c * dy + tid]);
-    }
     float* lred = smem + a.d_hyper + 4;  // [8]
     float part = 0.f;
 #pragma unroll
@@ -190,8 +190,7 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   if (hyper) {
     // ---- Linear(c), rows y < 64 from the registers, further rows (dy > 64) straight from memory
     auto reduce = [&](float dot, int yy, float bia) {
-      dot += __shfl_xor(dot, 1, kWave);
-      dot += __shfl_xor(dot, 2, kWave);
+      dot = group_reduce<4>(dot, LaneSum());
       if (yy < dy && q == 0) sg[yy] = dot + bia;
     };
     float dot = 0.f;
@@ -232,7 +231,7 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   float w;
   if (hyper) {
     float z;
-    if (ln && dy <= kBlock) {  // same sum as hyper_logit, with the row already in registers
+    if (dy <= kBlock) {  // same sum as hyper_logit, with the row already in registers
       float zp = tid < dy ? sg[tid] * g_pre : 0.f;
       zp = wave_sum(zp);
       if ((tid & (kWave - 1)) == 0) red[tid >> 6] = zp;
@@ -274,11 +273,9 @@ __global__ __launch_bounds__(kBlock) void append_step_kernel(AppendArgs a) {
 // for, neither of which needs the other -- the append of the step's token (workgroups below
 // `batch`) and the absorbed queries (the rest, numbered like the absorb kernel's grid) -- in one
 // launch, so a step pays one kernel start and one round trip to memory for both.
-// At batch 256 and more a step launches more workgroups than a unit holds at once, and the kernel then
-// takes as many rounds as its registers make necessary: five workgroups per unit (96 registers; four for the
-// whole-layer call's fp32 operands, which would spill below 128).
+// Four workgroups per unit (128 registers): what a step of 256 sequences launches is then resident at once.
 template <int NCH, int KK, typename TC>
-__global__ __launch_bounds__(kBlock, sizeof(TC) == 4 ? 4 : 5) void decode_front_kernel(AppendArgs ap, AbsorbArgs ab, int gx, int gy) {
+__global__ __launch_bounds__(kBlock, 4) void decode_front_kernel(AppendArgs ap, AbsorbArgs ab, int gx, int gy) {
   extern __shared__ float smem[];
   const int blk = blockIdx.x;
   if (blk < ap.batch) {
@@ -586,7 +583,7 @@ bool decode_front_supported(const AppendArgs& ap, const AbsorbArgs& ab) {
 }
 
 hipError_t launch_decode_front(const AppendArgs& ap, const AbsorbArgs& ab, hipStream_t st) {
-  const int gx = ab.r / 64 + 1, gy = ab.n_heads;
+  const int gx = absorb_col_blocks(ab.r) + 1, gy = ab.n_heads;
   const int gz = (ab.rows + absorb_rows_per_block(ab.rows) - 1) / absorb_rows_per_block(ab.rows);
   const dim3 grid(ap.batch + gx * gy * gz), block(kBlock);
   const size_t smem = (size_t)(ap.d_hyper + 4 + 8 + ap.r) * sizeof(float);

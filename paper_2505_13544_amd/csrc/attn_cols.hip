@@ -214,8 +214,7 @@ __device__ __forceinline__ void finish_tile(const Shares<C>& sh, const uint16_t*
     constexpr float kRebase = 40.f;
     const float mloc = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
     if (__any(ws.m_ref[ht] == -INFINITY || mloc - ws.m_ref[ht] > kRebase)) {
-      float mt_ = fmaxf(mloc, __shfl_xor(mloc, 16, kWave));
-      mt_ = fmaxf(mt_, __shfl_xor(mt_, 32, kWave));
+      float mt_ = quarter_reduce(mloc, LaneMax());
       if (ws.m_ref[ht] == -INFINITY) {
         ws.m_ref[ht] = mt_;  // still -inf if nothing of the tile is visible
       } else if (mt_ - ws.m_ref[ht] > kRebase) {
@@ -379,12 +378,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     if (wv == 0) {
       const int lv = lane < B ? (a.seq_len[lane] + a.stride - 1) / a.stride : 0;
       const int nt = units_of(lv);
-      int inc = nt;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int v = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += v;
-      }
+      const int inc = wave_scan(nt);
       if (lane < B) {
         sPre[lane] = inc - nt;
         sLive[lane] = lv;
@@ -399,12 +393,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     for (int bb = b_lo; bb < b_hi; ++bb) run += units_of((a.seq_len[bb] + a.stride - 1) / a.stride);
     // inclusive scan of the threads' sums: inside each wavefront by shuffles, the wavefronts' totals
     // through LDS (two barriers instead of the sixteen of a scan in LDS over all 256 threads)
-    int inc = run;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int v = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc += v;
-    }
+    const int inc = wave_scan(run);
     if (lane == kWave - 1) sScan[kBlock - kWaves + wv] = inc;  // the wavefront's total, in the array's last entries
     __syncthreads();
     int before = 0;  // units of the wavefronts before this one
@@ -519,8 +508,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     float l_head[NHT];
 #pragma unroll
     for (int ht = 0; ht < NHT; ++ht) {
-      l_head[ht] = ws.l_run[ht] + __shfl_xor(ws.l_run[ht], 16, kWave);
-      l_head[ht] += __shfl_xor(l_head[ht], 32, kWave);
+      l_head[ht] = quarter_reduce(ws.l_run[ht], LaneSum());
     }
 #pragma unroll
     for (int ht = 0; ht < NHT; ++ht) {
@@ -674,8 +662,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_rows_kernel(AttnArgs a)
 #pragma unroll
   for (int qt = 0; qt < C::NHT; ++qt) {
     const int gi = qt / NHT, ht = qt % NHT;
-    float l_head = ws.l_run[qt] + __shfl_xor(ws.l_run[qt], 16, kWave);
-    l_head += __shfl_xor(l_head, 32, kWave);
+    const float l_head = quarter_reduce(ws.l_run[qt], LaneSum());
     const int m = m0 + gi, h = 16 * ht + l16;
     if (m < len && h < a.n_heads) {
       const size_t oh = ((size_t)b * T + m) * a.n_heads + h;

@@ -22,12 +22,10 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __bui
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 // over the four lanes that hold one column of a 16 x 16 result
 __device__ __forceinline__ float col_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, kWave));
-  return fmaxf(v, __shfl_xor(v, 32, kWave));
+  return quarter_reduce(v, LaneMax());
 }
 __device__ __forceinline__ float col_sum(float v) {
-  v += __shfl_xor(v, 16, kWave);
-  return v + __shfl_xor(v, 32, kWave);
+  return quarter_reduce(v, LaneSum());
 }
 
 // ---------------------------------------------------------------------------

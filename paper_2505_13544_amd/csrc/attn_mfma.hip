@@ -143,8 +143,7 @@ struct WaveState {
   float m_ref, l_run;  // l_run: this lane's slots only, see l_total()
   float4_t acc_o[C::MT];
   __device__ __forceinline__ float l_total() const {  // normaliser of the lane's head
-    float l = l_run + __shfl_xor(l_run, 16, kWave);
-    return l + __shfl_xor(l, 32, kWave);
+    return quarter_reduce(l_run, LaneSum());
   }
   __device__ __forceinline__ void reset() {
     m_ref = -INFINITY;
@@ -246,8 +245,7 @@ __device__ __forceinline__ void stream_tiles(TileRegs<C> (&tl)[NS], const uint4 
       constexpr float kRebase = 40.f;
       const float mloc = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
       if (__any(ws.m_ref == -INFINITY || mloc - ws.m_ref > kRebase)) {
-        float mt_ = fmaxf(mloc, __shfl_xor(mloc, 16, kWave));
-        mt_ = fmaxf(mt_, __shfl_xor(mt_, 32, kWave));
+        float mt_ = quarter_reduce(mloc, LaneMax());
         if (ws.m_ref == -INFINITY) {
           ws.m_ref = mt_;  // still -inf if the tile is dead
         } else if (mt_ - ws.m_ref > kRebase) {

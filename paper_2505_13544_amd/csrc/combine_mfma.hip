@@ -67,19 +67,6 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
   return p;
 }
 
-template <int N>  // over aligned groups of N lanes, N a power of two up to the wavefront
-__device__ __forceinline__ float group_max(float v) {
-#pragma unroll
-  for (int off = 1; off < N; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  return v;
-}
-template <int N>
-__device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int off = 1; off < N; off <<= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
-
 // grid = (runs of row tiles, n_heads)
 // RPT = rows a workgroup really fills of each 16-row tile.  16 is the dense case; 4 is for small
 // batches (decode), where the merge of the partials is the long part and wants more workgroups:
@@ -193,13 +180,13 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     if (sub >= pc.count) ml0 = make_float2(-INFINITY, 0.f);
     float mloc = ml0.x;
     for (int p = sub + TPR; p < pc.count; p += TPR) mloc = fmaxf(mloc, a.part_ml[(pb + (size_t)p * a.n_heads) * 2]);
-    const float mstar = group_max<TPR>(mloc);
+    const float mstar = group_reduce<TPR>(mloc, LaneMax());
     float lloc = sub < pc.count ? __builtin_amdgcn_exp2f(ml0.x - mstar) * ml0.y : 0.f;
     for (int p = sub + TPR; p < pc.count; p += TPR) {
       const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + (pb + (size_t)p * a.n_heads) * 2);
       lloc += __builtin_amdgcn_exp2f(ml.x - mstar) * ml.y;
     }
-    const float lstar = group_sum<TPR>(lloc);
+    const float lstar = group_reduce<TPR>(lloc, LaneSum());
 
     // ---- o~ = sum_p 2^(m_p - m*) o_p / l*
     float4_t acc[CJ];

@@ -113,12 +113,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
       for (int b0 = 0; b0 < n_seq && !work; b0 += kWave) {
         const int used = b0 + lane < n_seq ? used_rows(b0 + lane) : 0;
         const int n = (used + BM - 1) / BM;
-        int upto = n;  // blocks of sequences b0 .. b0 + lane
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-          const int v = __shfl_up(upto, off, kWave);
-          upto += lane >= off ? v : 0;
-        }
+        const int upto = wave_scan(n);  // blocks of sequences b0 .. b0 + lane
         const unsigned long long here = __ballot(ib - before < upto);
         if (here) {
           const int at = __builtin_ctzll(here);
@@ -475,8 +470,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
         if (!LAYER) qf[rt][kk] = bf16x8_to_f16x8(qf[rt][kk], a.scale_log2);
         e = dot8(kd[kk], qf[rt][kk], e);
       }
-      e += __shfl_xor(e, 16, kWave);
-      e += __shfl_xor(e, 32, kWave);
+      e = quarter_reduce(e, LaneSum());
       neg_ref[rt] = float4_t{-e, -e, -e, -e};
       l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
 #pragma unroll
@@ -585,8 +579,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
           float up = -INFINITY;
 #pragma unroll
           for (int i = 0; i < 16; ++i) up = fmaxf(up, sacc[i >> 3][rt][(i >> 2) & 1][i & 3]);
-          up = fmaxf(up, __shfl_xor(up, 16, kWave));
-          up = fmaxf(up, __shfl_xor(up, 32, kWave));
+          up = quarter_reduce(up, LaneMax());
           if (up > kRebase) {
             const float alpha = __builtin_amdgcn_exp2f(-up);
             neg_ref[rt] -= up;
@@ -640,8 +633,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-      float l = l_run[rt] + __shfl_xor(l_run[rt], 16, kWave);
-      l += __shfl_xor(l, 32, kWave);
+      const float l = quarter_reduce(l_run[rt], LaneSum());
       const int m = m0 + 32 * wv + 16 * rt + l16;
       if (m < T) {
         const bool live = m < len;  // rows past the sequence's length are zeros, whatever their inputs held

@@ -149,8 +149,7 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < N4; ++i) sum += (v[h][i][0] + v[h][i][1]) + (v[h][i][2] + v[h][i][3]);
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) sum += __shfl_xor(sum, off, kWave);
+        sum = group_reduce<16>(sum, LaneSum());
         const float mean = sum / (float)R;
         float sq = 0.f;
 #pragma unroll
@@ -158,8 +157,7 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
           v[h][i] -= mean;
           sq += (v[h][i][0] * v[h][i][0] + v[h][i][1] * v[h][i][1]) + (v[h][i][2] * v[h][i][2] + v[h][i][3] * v[h][i][3]);
         }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) sq += __shfl_xor(sq, off, kWave);
+        sq = group_reduce<16>(sq, LaneSum());
         const float rstd = rsqrtf(sq / (float)R + a.ln_eps);
 #pragma unroll
         for (int i = 0; i < N4; ++i) {
@@ -221,8 +219,7 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
         float z = 0.f;
 #pragma unroll
         for (int v = 0; v < 4; ++v) z += (d[v] + bias[v]) * gf[v];
-        z += __shfl_xor(z, 16, kWave);
-        z += __shfl_xor(z, 32, kWave);
+        z = quarter_reduce(z, LaneSum());
         if (g == 0) sh.z[wv][16 * h + l16] = z;
       }
     }

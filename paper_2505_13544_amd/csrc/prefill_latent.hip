@@ -165,8 +165,7 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       qf[kk] = bf16x8_to_f16x8(qf[kk], a.scale_log2);  // logits in units of log2
       e = dot8(kd[kk], qf[kk], e);
     }
-    e += __shfl_xor(e, 16, kWave);
-    e += __shfl_xor(e, 32, kWave);
+    e = quarter_reduce(e, LaneSum());
     neg_ref = -e;
     l_run = g == 0 ? 1.f : 0.f;
   }
@@ -231,8 +230,7 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
         float up = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 8; ++i) up = fmaxf(up, sacc[i >> 2][i & 3]);
-        up = fmaxf(up, __shfl_xor(up, 16, kWave));
-        up = fmaxf(up, __shfl_xor(up, 32, kWave));
+        up = quarter_reduce(up, LaneMax());
         float alpha = 1.f;
         if (up > kRebase) {
           alpha = __builtin_amdgcn_exp2f(-up);
@@ -361,8 +359,7 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
 
   // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3
   {
-    float l = l_run + __shfl_xor(l_run, 16, kWave);
-    l += __shfl_xor(l, 32, kWave);
+    const float l = quarter_reduce(l_run, LaneSum());
     if (g == 0) s_inv[16 * wv + l16] = m_own < len ? 1.f / l : 0.f;
   }
   __syncthreads();

@@ -311,7 +311,7 @@ void launch_combine_t(const CombineArgs& a, const dim3& grid, size_t smem, hipSt
 
 template <int KK>
 void launch_absorb_mfma_kk(const AbsorbArgs& a, hipStream_t st) {
-  const dim3 grid(a.r / 64 + 1, a.n_heads, (a.rows + absorb_rows_per_block(a.rows) - 1) / absorb_rows_per_block(a.rows));
+  const dim3 grid(absorb_col_blocks(a.r) + 1, a.n_heads, (a.rows + absorb_rows_per_block(a.rows) - 1) / absorb_rows_per_block(a.rows));
   if (a.q_f32) hipLaunchKernelGGL((absorb_mfma_kernel<KK, true>), grid, dim3(kBlock), 0, st, a);
   else hipLaunchKernelGGL((absorb_mfma_kernel<KK, false>), grid, dim3(kBlock), 0, st, a);
 }
