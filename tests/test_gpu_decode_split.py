@@ -1,0 +1,39 @@
+"""GPU parity of the decode kernel for short chunks (64 slots a step, rows and weights shared through LDS) at the edges of its
+tiles and steps, and of the front kernel's column blocks, against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_heads,r,d_rope,chunk", [(1, 64, 64, 64), (16, 64, 32, 320), (8, 256, 32, 64), (9, 128, 64, 96),
+                                                    (15, 512, 64, 128), (16, 256, 64, 32), (3, 512, 32, 320)])
+def test_slots_around_tiles_and_steps(n_heads, r, d_rope, chunk):
+    # the last step begins a tile, fills it, leaves wavefronts without a slot; chunks of half a step and of several
+    plen = np.array([1, 15, 16, 17, 63, 64, 65, 128, 129, 319, 321, 340], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name=f"split_{r}_{chunk}", batch=len(plen), d_model=96, n_heads=n_heads, d_head=64, r=r,
+                                           d_rope=d_rope, stride=1, prefix=(1, 340), steps=2, seed=60 + r + chunk)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=chunk, decode_schedule=1)
+
+
+def test_reference_moves_between_steps():
+    # logits far apart: the weights' reference moves from step to step of one chunk; chunks of one step never move theirs
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="split_far", batch=3, d_model=96, n_heads=8, d_head=64, r=256, d_rope=32, stride=1,
+                                           prefix=320, steps=1, seed=71)
+    wts = W.make_weights(wl)
+    toks = [W.make_tokens(wl, wts, b, 0, 320) for b in range(wl.batch)]
+    d = {f: H.to_device(np.stack([getattr(t, f) for t in toks]), wl.dtype) for f in ("q", "q_rope", "c", "kr")}
+    outs = []
+    for chunk in (64, 320):
+        sess = H.make_session(wl, decode_chunk=chunk, decode_schedule=1)
+        H.upload_weights(sess, wts)
+        sess.append(d["c"], d["kr"])
+        out = torch.zeros(wl.batch, wl.n_heads, wl.d_head, device="cuda")
+        sess.decode(64 * d["q"][:, -1].contiguous(), 64 * d["q_rope"][:, -1].contiguous(), out=out)
+        outs.append(out.cpu())
+    assert torch.isfinite(outs[0]).all()
+    assert (outs[0] - outs[1]).abs().max() <= H.TOL["bf16"]
