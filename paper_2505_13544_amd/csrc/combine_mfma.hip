@@ -75,15 +75,14 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
 // is fetched after the merge, when the registers of the partials are free again (single tile).
 // PF16 = the partials are normalised IEEE-half rows (o_p / l_p) from the column-split decode kernel:
 // a piece then weighs l_p 2^(m_p - m*) instead of 2^(m_p - m*).
-// PS = a few rows of very many pieces (a handful of long sequences under the balanced schedule): one row
-// per workgroup (RPT = 1), the row's pieces dealt to the four wavefronts in contiguous quarters, their
-// weighted sums added through LDS.  One round of requests instead of one per PB pieces, and four times
-// the workgroups.
+// PS = few rows, their pieces split over the wavefronts: one row per workgroup (RPT = 1), the weighted sums added through
+// LDS.  One round of requests instead of one per PB pieces, and four times the
+// workgroups, each with a quarter of the partials to bring in and to add up.
 // HF = the head is the fast grid index: the workgroups that share an XCD (and its L2) then share the
 // W_V^(h) of a few heads instead of each XCD fetching all of them.
 template <int R, int DH, int RPT, bool WKEEP, bool PF16, bool PS = false, bool HF = PS>
 __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int tiles_per_wg) {
-  static_assert(!PS || (RPT == 1 && PF16), "piece split: one row per workgroup, half partials");
+  static_assert(!PS || RPT == 1, "piece split: one row per workgroup");
   constexpr int KK = R / 32;         // K steps
   constexpr int NT = DH / 64;        // 16-row output tiles per wavefront (a quarter of d_h)
   constexpr int TPR = PS ? kWave : kBlock / RPT;  // threads merging one row (piece split: per wavefront)
@@ -93,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   // partials requested together per thread: as many as the registers allow (packed halves are cheap)
   // (small batches, four rows per workgroup: 16, so that a row of up to 16 pieces is one round of requests; the
   // headline shape has 9 or 10 pieces per row once it has decoded past 1024 tokens)
-  constexpr int PB = PS ? 12 : (WKEEP && R >= 512) ? (HF && PF16 ? 4 : 2) : ((RPT < kTileRows && (PF16 || R <= 256)) ? 16 : 8);
+  constexpr int PB = PS ? (PF16 || R <= 256 ? 12 : 8) : (WKEEP && R >= 512) ? (HF && PF16 ? 4 : 2) : ((RPT < kTileRows && (PF16 || R <= 256)) ? 16 : 8);
   __shared__ __attribute__((aligned(16))) uint16_t sA[2][kTileRows][AS];  // hi and lo planes
   __shared__ __attribute__((aligned(16))) float sRed[PS ? kWaves - 1 : 1][PS ? R : 4];  // piece split: the other wavefronts' sums
 
@@ -109,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   // weights (loads return in order, and one count asked for after the other would be a round trip each)
   const int tid0 = threadIdx.x;
   int ps_p0 = 0, ps_p1 = 0, ps_total = 0;
-  if (PS || (HF && a.n_persistent > 0)) {
+  if ((PS || HF) && a.n_persistent > 0) {
     const int row0 = PS ? t0 : RPT * t0 + tid0 / (kBlock / RPT);
     const int rc = row0 < rows ? row0 : rows - 1;
     ps_p0 = a.tile_prefix[rc];
@@ -142,15 +141,15 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     // static schedule: piece ids row*n_splits + 0 .. n_splits-1 are readable whatever the row's
     // length turns out to be, so the requests below do not wait for it
     const bool fixed_ids = a.n_persistent == 0;
-    const Pieces pc = (PS || (HF && a.n_persistent > 0 && t == t0)) ? pieces_balanced(a, row, rows, ps_p0, ps_p1, ps_total)
+    const Pieces pc = ((PS || HF) && a.n_persistent > 0 && t == t0) ? pieces_balanced(a, row, rows, ps_p0, ps_p1, ps_total)
                                                                      : pieces_of_row(a, row, rows, total_tiles);
     const int row_c = row < rows ? row : rows - 1;
     const size_t pb = (size_t)(fixed_ids ? row_c * a.n_splits : pc.first) * a.n_heads + h;  // + p * n_heads
     const int p_last = fixed_ids ? a.n_splits - 1 : (pc.count > 0 ? pc.count - 1 : 0);
-    // piece split: this wavefront's quarter of the row's pieces, [pw0, pw0 + cnt)
-    const int pq = (pc.count + kWaves - 1) / kWaves;
-    const int pw0 = PS ? wv * pq : 0;
-    const int cnt = PS ? (pc.count - pw0 < 0 ? 0 : (pc.count - pw0 < pq ? pc.count - pw0 : pq)) : pc.count;
+    // piece split: a quarter of the row's pieces where the count came first, else (requests do not wait for the count) every
+    // fourth from wv on
+    const int pq = (pc.count + kWaves - 1) / kWaves, pw0 = fixed_ids ? wv : wv * pq, ps = fixed_ids ? kWaves : 1;
+    const int cnt = !PS ? pc.count : (fixed_ids ? (pc.count - wv + kWaves - 1) / kWaves : (pc.count - pw0 < pq ? pc.count - pw0 : pq));
 
     // ---- first PB pieces: requested before anything is known about m* (any piece id that can
     // come out of pieces_of_row is readable workspace)
@@ -161,7 +160,8 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     auto request = [&](int p0) {
 #pragma unroll
       for (int i = 0; i < PB; ++i) {
-        const size_t pi = pb + (size_t)(pw0 + p0 + i < p_last ? pw0 + p0 + i : p_last) * a.n_heads;
+        const int p = PS ? pw0 + ps * (p0 + i) : p0 + i;
+        const size_t pi = pb + (size_t)(p < p_last ? p : p_last) * a.n_heads;
         mp[i] = *reinterpret_cast<const float2*>(a.part_ml + pi * 2);
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
@@ -284,6 +284,16 @@ hipError_t launch_rdh_pf(const CombineArgs& a, hipStream_t st) {
     if (a.n_persistent > 0 && rows <= 16 && a.n_persistent + rows >= 8 * rows) {
       const dim3 grid(a.n_heads, rows);
       hipLaunchKernelGGL((combine_mfma_kernel<R, DH, 1, true, true, true>), grid, dim3(kBlock), 0, st, a, 1);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (R >= 256 && !PF16) {
+    // a small decode step, at most one (row, head) per compute unit, where a row is long (r = 512) or its pieces are more
+    // than one round of requests: likewise.  With four rows per workgroup 4 sequences of 32 pieces, 16 heads, r = 512 took
+    // 10.5 us on 16 workgroups, now 7.8.  (16 sequences of 10 pieces, 8 heads, r = 256: 4.4 us either way; beyond a row and
+    // head per unit every row's own copy of W_V^(h) costs more than the merge gains.)
+    if (a.n_persistent == 0 && a.T == 0 && rows * a.n_heads <= 256 && (R == 512 || a.n_splits > 16)) {
+      hipLaunchKernelGGL((combine_mfma_kernel<R, DH, 1, true, false, true>), dim3(a.n_heads, rows), dim3(kBlock), 0, st, a, 1);
       return hipGetLastError();
     }
   }

@@ -20,6 +20,14 @@ def test_slots_around_tiles_and_steps(n_heads, r, d_rope, chunk):
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=chunk, decode_schedule=1)
 
 
+def test_more_pieces_than_one_round_of_the_merge():
+    # 29 pieces a row, dealt to the wavefronts of the combine's one-row form; rows with none, one and a few of them
+    plen = np.array([1, 33, 130, 900], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="split_pieces", batch=len(plen), d_model=96, n_heads=8, d_head=64, r=256, d_rope=32,
+                                           stride=1, prefix=(1, 900), steps=2, seed=83)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32, decode_schedule=1)
+
+
 def test_reference_moves_between_steps():
     # logits far apart: the weights' reference moves from step to step of one chunk; chunks of one step never move theirs
     wl = W.WORKLOADS["speech_bf16"].scaled(name="split_far", batch=3, d_model=96, n_heads=8, d_head=64, r=256, d_rope=32, stride=1,
