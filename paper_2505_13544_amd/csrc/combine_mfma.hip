@@ -6,12 +6,16 @@
 // Heads do not share W_V^(h), rows do, so the up-projection is a dense contraction once 16 rows
 // of one head are put side by side:
 //     out^T[d, row] = W_V^(h)[d, :] . o~[row, :]^T          (M = d_h, N = 16 rows, K = r)
-// A workgroup owns one head and a run of 16-row tiles.  Its W_V^(h) sits in registers for the
-// whole run, already in the A-operand layout of v_mfma_f32_16x16x32_bf16 (each wavefront a
-// quarter of the d_h output rows).  Per tile, 16 threads per row merge the row's partials (all
+// A workgroup owns one head and a run of 16-row tiles.  Its W_V^(h) is brought into LDS at the top, by loads that take
+// whole rows of it (straight into the A-operand layout of v_mfma_f32_16x16x32_bf16 a request touches 64 bytes of each of 16
+// rows: 128 KB took 4 us that way, beside which everything else of the kernel waited), each wavefront the quarter of the d_h
+// rows that it multiplies.  Per tile, 16 threads per row merge the row's partials (all
 // requests of up to PB pieces go out together, before the normaliser is known), write the
 // normalised latent row where the caller wants it, and park it in LDS as two bf16 planes
 // (hi + lo, an almost-fp32 value) that the four wavefronts read back as the B operand.
+// At r = 512, d_h = 128: 256 sequences, 16 heads 9.4 us, now 8.8; 1000 sequences 29.3, now 24.5; 8 sequences of 33 pieces,
+// 32 heads 9.1, now 7.0.
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -70,9 +74,7 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
 // grid = (runs of row tiles, n_heads)
 // RPT = rows a workgroup really fills of each 16-row tile.  16 is the dense case; 4 is for small
 // batches (decode), where the merge of the partials is the long part and wants more workgroups:
-// a row is then merged by a whole wavefront and three quarters of the tile's columns stay zero.
-// WKEEP = W_V^(h) is fetched once and kept in registers for the whole run of tiles; otherwise it
-// is fetched after the merge, when the registers of the partials are free again (single tile).
+// a row is then merged by a whole wavefront and the tile's other columns are copies nobody stores.
 // PF16 = the partials are normalised IEEE-half rows (o_p / l_p) from the column-split decode kernel:
 // a piece then weighs l_p 2^(m_p - m*) instead of 2^(m_p - m*).
 // PS = few rows, their pieces split over the wavefronts: one row per workgroup (RPT = 1), the weighted sums added through
@@ -80,21 +82,30 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
 // workgroups, each with a quarter of the partials to bring in and to add up.
 // HF = the head is the fast grid index: the workgroups that share an XCD (and its L2) then share the
 // W_V^(h) of a few heads instead of each XCD fetching all of them.
-template <int R, int DH, int RPT, bool WKEEP, bool PF16, bool PS = false, bool HF = PS>
+template <int R, int DH, int RPT, bool PS>
+struct CombineLds {  // [W_V^(h)][hi and lo planes of the rows][piece split: the other wavefronts' sums]
+  static constexpr int planes = DH * R * 2, red = planes + 2 * RPT * R * 2, bytes = red + (PS ? (kWaves - 1) * R * 4 : 0);
+  static_assert(bytes <= 160 * 1024, "LDS of one compute unit");
+};
+
+template <int R, int DH, int RPT, bool PF16, bool PS = false, bool HF = PS>
 __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int tiles_per_wg) {
   static_assert(!PS || RPT == 1, "piece split: one row per workgroup");
+  using L = CombineLds<R, DH, RPT, PS>;
   constexpr int KK = R / 32;         // K steps
   constexpr int NT = DH / 64;        // 16-row output tiles per wavefront (a quarter of d_h)
   constexpr int TPR = PS ? kWave : kBlock / RPT;  // threads merging one row (piece split: per wavefront)
   constexpr int CJ = R / (4 * TPR);  // float4 pieces of a latent row per thread
   static_assert(CJ >= 1, "a thread merges at least one float4 of its row");
-  constexpr int AS = R + 8;          // LDS row stride (bf16 elements)
-  // partials requested together per thread: as many as the registers allow (packed halves are cheap)
-  // (small batches, four rows per workgroup: 16, so that a row of up to 16 pieces is one round of requests; the
-  // headline shape has 9 or 10 pieces per row once it has decoded past 1024 tokens)
-  constexpr int PB = PS ? (PF16 || R <= 256 ? 12 : 8) : (WKEEP && R >= 512) ? (HF && PF16 ? 4 : 2) : ((RPT < kTileRows && (PF16 || R <= 256)) ? 16 : 8);
-  __shared__ __attribute__((aligned(16))) uint16_t sA[2][kTileRows][AS];  // hi and lo planes
-  __shared__ __attribute__((aligned(16))) float sRed[PS ? kWaves - 1 : 1][PS ? R : 4];  // piece split: the other wavefronts' sums
+  constexpr int PC = R / 8;          // 16-byte pieces of a row
+  // partials requested together per thread: what 128 registers hold, at most 16 (12 with the pieces split: 48 a row; in the
+  // dense case, whose rows have a few, 4 or 8: requests beyond a row's pieces are reloads, but not free)
+  constexpr int kFit = 128 / (CJ * (PF16 ? 2 : 4)), kMost = PS ? 12 : (RPT < kTileRows ? 16 : (R >= 512 ? 4 : 8));
+  constexpr int PB = kFit < kMost ? kFit : kMost;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  // rows in LDS: piece p of row i at place p ^ swz(i), so that 16 rows' reads of one piece spread over the banks
+  uint16_t* sA = reinterpret_cast<uint16_t*>(smem + L::planes);  // [plane][RPT][R]
+  float* sRed = reinterpret_cast<float*>(smem + L::red);         // [kWaves - 1][R]
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
@@ -116,22 +127,19 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     ps_total = a.tile_prefix[a.batch];
   }
 
-  // W_V^(h) rows wv*(d_h/4) + 16nt + l16, elements 32kk + 8g .. +7: the A operand
-  uint4 wfrag[NT][KK];
-  const uint16_t* wsrc =
-      reinterpret_cast<const uint16_t*>(a.w_uv) + ((size_t)h * DH + wv * (DH / 4) + l16) * R + 8 * g;
-  auto fetch_w = [&]() {
+  // this wavefront's d_h / 4 rows of W_V^(h), 1 KB per request
+  if (a.out) {
+    typedef const __attribute__((address_space(1))) void* global_ptr;
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    constexpr int kBytes = DH / 4 * R * 2;
+    const int uw = __builtin_amdgcn_readfirstlane(wv);
+    const uint16_t* wsrc = reinterpret_cast<const uint16_t*>(a.w_uv) + ((size_t)h * DH + uw * (DH / 4)) * R;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-        wfrag[nt][kk] = *reinterpret_cast<const uint4*>(wsrc + (size_t)16 * nt * R + 32 * kk);
-  };
-  if (WKEEP && a.out) fetch_w();
-
-  if (RPT < kTileRows) {  // tile rows no thread fills stay zero for the whole kernel
-    for (int i = tid; i < 2 * kTileRows * AS / 2; i += kBlock) reinterpret_cast<uint32_t*>(&sA[0][0][0])[i] = 0u;
-    __syncthreads();
+    for (int i = 0; i < kBytes / 1024; ++i) {
+      const int at = 64 * i + lane, row = at / PC;
+      __builtin_amdgcn_global_load_lds((global_ptr)(wsrc + row * R + 8 * ((at % PC) ^ swz_rows16<PC>(row))),
+                                       (lds_ptr)(smem + uw * kBytes + 1024 * i), 16, 0, 0);
+    }
   }
 
   const int total_tiles = (PS || HF) ? ps_total : (a.n_persistent > 0 ? a.tile_prefix[a.batch] : 0);
@@ -213,14 +221,14 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     if constexpr (PS) {  // wavefront 0 adds the other three sums to its own
       if (wv > 0) {
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) *reinterpret_cast<float4_t*>(&sRed[wv - 1][4 * sub + 4 * TPR * j]) = acc[j];
+        for (int j = 0; j < CJ; ++j) *reinterpret_cast<float4_t*>(sRed + (wv - 1) * R + 4 * sub + 4 * TPR * j) = acc[j];
       }
       __syncthreads();
       if (wv == 0) {
 #pragma unroll
         for (int w = 0; w < kWaves - 1; ++w)
 #pragma unroll
-          for (int j = 0; j < CJ; ++j) acc[j] += *reinterpret_cast<const float4_t*>(&sRed[w][4 * sub + 4 * TPR * j]);
+          for (int j = 0; j < CJ; ++j) acc[j] += *reinterpret_cast<const float4_t*>(sRed + w * R + 4 * sub + 4 * TPR * j);
       }
     }
     const float inv = pc.count > 0 ? 1.f / lstar : 0.f;  // a row with no live column gives zeros
@@ -243,23 +251,29 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
       const uint32_t h01 = pack_bf16x2(acc[j][0], acc[j][1]), h23 = pack_bf16x2(acc[j][2], acc[j][3]);
       const uint32_t l01 = pack_bf16x2(acc[j][0] - __uint_as_float(h01 << 16), acc[j][1] - __uint_as_float(h01 & 0xffff0000u));
       const uint32_t l23 = pack_bf16x2(acc[j][2] - __uint_as_float(h23 << 16), acc[j][3] - __uint_as_float(h23 & 0xffff0000u));
-      *reinterpret_cast<uint2*>(&sA[0][rr][4 * sub + 4 * TPR * j]) = make_uint2(h01, h23);
-      *reinterpret_cast<uint2*>(&sA[1][rr][4 * sub + 4 * TPR * j]) = make_uint2(l01, l23);
+      const int e = 4 * sub + 4 * TPR * j;
+      uint16_t* dst = sA + rr * R + 8 * ((e >> 3) ^ swz_rows16<PC>(rr)) + (e & 7);
+      *reinterpret_cast<uint2*>(dst) = make_uint2(h01, h23);
+      *reinterpret_cast<uint2*>(dst + RPT * R) = make_uint2(l01, l23);
     }
-    if (!WKEEP) fetch_w();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weights have landed
     __syncthreads();
 
     // ---- out^T[d, row] for this wavefront's d_h / 4 output rows
     float4_t o[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) o[nt] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const int rb = l16 % RPT;
+    const uint16_t* brow = sA + rb * R;
+    const uint16_t* wrow = reinterpret_cast<const uint16_t*>(smem) + (wv * (DH / 4) + l16) * R;  // (16 rows on, the same swizzle)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(&sA[0][l16][32 * kk + 8 * g]));
-      const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(&sA[1][l16][32 * kk + 8 * g]));
+      const int pb_ = 8 * ((4 * kk + g) ^ swz_rows16<PC>(rb)), pw = 8 * ((4 * kk + g) ^ swz_rows16<PC>(l16));
+      const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + pb_));
+      const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + RPT * R + pb_));
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, wfrag[nt][kk]);
+        const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(wrow + 16 * nt * R + pw));
         o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bh, o[nt], 0, 0, 0);
         o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bl, o[nt], 0, 0, 0);
       }
@@ -275,35 +289,36 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   }
 }
 
+template <int R, int DH, int RPT, bool PF16, bool PS = false, bool HF = PS>
+hipError_t launch_one(const CombineArgs& a, const dim3& grid, int tiles_per_wg, hipStream_t st) {
+  constexpr int smem = CombineLds<R, DH, RPT, PS>::bytes;
+  static bool attr_set = false;  // LDS above the 64 KB default needs an explicit opt-in, once
+  if (smem > 64 * 1024 && !attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>), grid, dim3(kBlock), smem, st, a, tiles_per_wg);
+  return hipGetLastError();
+}
+
 template <int R, int DH, bool PF16>
 hipError_t launch_rdh_pf(const CombineArgs& a, hipStream_t st) {
   const int rows = a.T ? a.batch * a.T : a.batch;
-  if constexpr (R >= 256 && PF16) {
-    // a handful of rows of eight or more pieces each (at most n_persistent + rows pieces exist): one row per
+  if constexpr (R >= 256) {
+    // a handful of rows of eight or more pieces each (balanced: at most n_persistent + rows pieces exist): one row per
     // workgroup, its pieces split over the wavefronts
-    if (a.n_persistent > 0 && rows <= 16 && a.n_persistent + rows >= 8 * rows) {
-      const dim3 grid(a.n_heads, rows);
-      hipLaunchKernelGGL((combine_mfma_kernel<R, DH, 1, true, true, true>), grid, dim3(kBlock), 0, st, a, 1);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (R >= 256 && !PF16) {
+    if (PF16 && a.n_persistent > 0 && rows <= 16 && a.n_persistent + rows >= 8 * rows)
+      return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
     // a small decode step, at most one (row, head) per compute unit, where a row is long (r = 512) or its pieces are more
     // than one round of requests: likewise.  With four rows per workgroup 4 sequences of 32 pieces, 16 heads, r = 512 took
-    // 10.5 us on 16 workgroups, now 7.8.  (16 sequences of 10 pieces, 8 heads, r = 256: 4.4 us either way; beyond a row and
-    // head per unit every row's own copy of W_V^(h) costs more than the merge gains.)
-    if (a.n_persistent == 0 && a.T == 0 && rows * a.n_heads <= 256 && (R == 512 || a.n_splits > 16)) {
-      hipLaunchKernelGGL((combine_mfma_kernel<R, DH, 1, true, false, true>), dim3(a.n_heads, rows), dim3(kBlock), 0, st, a, 1);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (R >= 256) {
-    if (rows <= 64) {  // small batch: four rows per workgroup, one wavefront merging each
-      const dim3 grid((rows + 3) / 4, a.n_heads);
-      // up to r = 256 the W_V fragments fit beside the partials: fetched at the top, one round trip
-      hipLaunchKernelGGL((combine_mfma_kernel<R, DH, 4, (R <= 256), PF16>), grid, dim3(kBlock), 0, st, a, 1);
-      return hipGetLastError();
-    }
+    // 10.5 us on 16 workgroups, in this form 7.8, with the weights through LDS 6.0.  (16 sequences of 10 pieces, 8 heads, r = 256: 4.4 us either way; beyond a
+    // row and head per unit every row's own copy of W_V^(h) costs more than the merge gains.)
+    if (!PF16 && a.n_persistent == 0 && a.T == 0 && rows * a.n_heads <= 256 && (R == 512 || a.n_splits > 16))
+      return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
+    if (rows <= 64)  // small batch: four rows per workgroup, one wavefront merging each
+      return launch_one<R, DH, 4, PF16>(a, dim3((rows + 3) / 4, a.n_heads), 1, st);
   }
   const int n_tiles = (rows + kTileRows - 1) / kTileRows;
   // long runs amortise the W_V^(h) fetch; short ones keep every compute unit busy
@@ -311,19 +326,11 @@ hipError_t launch_rdh_pf(const CombineArgs& a, hipStream_t st) {
   tpw = tpw < 1 ? 1 : (tpw > 8 ? 8 : tpw);
   const dim3 grid((n_tiles + (int)tpw - 1) / (int)tpw, a.n_heads);
   if constexpr (PF16) {
-    // decode over many rows, balanced schedule (a few half-size partials per row): weights requested at the
-    // top beside the counts, heads as the fast grid index
-    if (tpw == 1 && a.T == 0 && a.n_persistent > 0) {
-      hipLaunchKernelGGL((combine_mfma_kernel<R, DH, kTileRows, true, true, false, true>), dim3(a.n_heads, grid.x), dim3(kBlock),
-                         0, st, a, 1);
-      return hipGetLastError();
-    }
+    // decode over many rows, balanced schedule (a few half-size partials per row): heads as the fast grid index
+    if (tpw == 1 && a.T == 0 && a.n_persistent > 0)
+      return launch_one<R, DH, kTileRows, true, false, true>(a, dim3(a.n_heads, grid.x), 1, st);
   }
-  if (tpw == 1)
-    hipLaunchKernelGGL((combine_mfma_kernel<R, DH, kTileRows, false, PF16>), grid, dim3(kBlock), 0, st, a, 1);
-  else
-    hipLaunchKernelGGL((combine_mfma_kernel<R, DH, kTileRows, true, PF16>), grid, dim3(kBlock), 0, st, a, (int)tpw);
-  return hipGetLastError();
+  return launch_one<R, DH, kTileRows, PF16>(a, grid, (int)tpw, st);
 }
 
 template <int R, int DH>

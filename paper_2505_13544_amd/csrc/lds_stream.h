@@ -32,11 +32,13 @@ __device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v, float scale = 1.f)
 //   swz_rows16   ds_read_b128, 16 lanes = 16 consecutive rows, same logical piece
 //   swz_tr       transposing 8-byte reads, 32 lanes = 8 consecutive rows x 32 bytes
 // The swizzle is applied on the way in: a lane asks memory for the piece that belongs at its place.
-template <int PC>  // pieces per row (4, 8 or 16): 16 / PC rows share 256 bytes
+// (PC pieces per row; 16 / PC short rows share 256 bytes, rows of 16 pieces and more start at the same bank.)
+template <int PC>
 __device__ __forceinline__ int swz_rows16(int row) {
-  return (row / (16 / PC)) & (PC - 1);
+  constexpr int P = PC < 16 ? PC : 16;
+  return (row / (16 / P)) & (P - 1);
 }
-template <int PC>  // (rows of 16 pieces and more start at the same bank, whatever their length)
+template <int PC>
 __device__ __forceinline__ int swz_tr(int row) {
   constexpr int P = PC < 16 ? PC : 16;
   return ((row / (16 / P)) & (P / 2 - 1)) << 1;
