@@ -36,7 +36,10 @@ __device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v, float scale = 1.f)
 template <int PC>
 __device__ __forceinline__ int swz_rows16(int row) {
   constexpr int P = PC < 16 ? PC : 16;
-  return (row / (16 / P)) & (P - 1);
+  // A read is served 16 lanes at a time: rows 0-3 and 12-15 of one piece with 4-11 of the next.  With four pieces a row the
+  // rows' own order would put two of each such group in every bank (half of the LDS time of the matrix products).
+  const int i = row / (16 / P);
+  return (PC == 4 ? -i : i) & (P - 1);
 }
 template <int PC>
 __device__ __forceinline__ int swz_tr(int row) {

@@ -10,7 +10,7 @@
 // A new row's partial state is what the append of its slot holds after the row (the update rule after
 // Eq. (infer-linear)), so one pass over the latents yields both.  Appending, converting and staging in seven launches took
 // 46 us of the 227 us of six pieces of up to 510 rows (r = 512, 16 heads x 128) behind up to 3001 tokens, most of
-// it launches that wait for one another; as one launch [see FRONT_US].
+// it launches that wait for one another; as one launch 13.
 #include <type_traits>
 
 #include "mtla_device.h"
