@@ -2,9 +2,11 @@
 //
 // A decode step passes nineteen arguments.  Turning tensors into addresses in Python and addresses into C values in
 // ctypes took 8 us of host time a call, more than the GPU needs for the step of a small model; here the same call costs
-// under 1 us.  A pointer argument is a tensor, an integer address, None (NULL), a buffer (a ctypes structure) or any
-// object with data_ptr(); the argument types come from the declarations in mtla.h.  The addresses of the functions are
-// handed in by the binding (bind), which has loaded the library: this module does not link against it.
+// under 1 us.  A pointer argument is a tensor, an integer address, None (NULL) or any object with data_ptr().  Nothing else
+// is one: most pointers are device memory, and host memory taken for it (a numpy array, a bytes object) would be read by a
+// kernel.  Only a page book, which the library's host functions read, is a writable buffer (the ctypes structure).  The
+// argument types come from the declarations in mtla.h.  The addresses of the functions are handed in by the binding
+// (bind), which has loaded the library: this module does not link against it.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -29,7 +31,7 @@ struct Hold {
   }
 };
 
-bool address(PyObject* o, Hold& hold, void*& out) {
+bool address(PyObject* o, void*& out) {
   if (o == Py_None) {
     out = nullptr;
     return true;
@@ -42,12 +44,6 @@ bool address(PyObject* o, Hold& hold, void*& out) {
     out = PyLong_AsVoidPtr(o);
     return !(out == nullptr && PyErr_Occurred());
   }
-  if (PyObject_CheckBuffer(o) && !hold.has_view) {
-    if (PyObject_GetBuffer(o, &hold.view, PyBUF_SIMPLE) != 0) return false;
-    hold.has_view = true;
-    out = hold.view.buf;
-    return true;
-  }
   PyObject* p = PyObject_CallMethod(o, "data_ptr", nullptr);
   if (!p) return false;
   out = PyLong_AsVoidPtr(p);
@@ -55,10 +51,30 @@ bool address(PyObject* o, Hold& hold, void*& out) {
   return !(out == nullptr && PyErr_Occurred());
 }
 
-bool weight(PyObject* d, const char* key, Hold& hold, const void*& out) {
+// A structure of the caller's in host memory, by the buffer protocol (ctypes structures offer it).
+bool structure(PyObject* o, size_t bytes, Hold& hold, void*& out) {
+  if (o == Py_None) {
+    out = nullptr;
+    return true;
+  }
+  if (hold.has_view) {
+    PyErr_SetString(PyExc_TypeError, "more than one structure argument");
+    return false;
+  }
+  if (PyObject_GetBuffer(o, &hold.view, PyBUF_WRITABLE) != 0) return false;
+  hold.has_view = true;
+  if ((size_t)hold.view.len != bytes) {
+    PyErr_Format(PyExc_TypeError, "a structure of %zu bytes is needed, the buffer has %zd", bytes, hold.view.len);
+    return false;
+  }
+  out = hold.view.buf;
+  return true;
+}
+
+bool weight(PyObject* d, const char* key, const void*& out) {
   PyObject* o = PyDict_GetItemString(d, key);
   void* p = nullptr;
-  if (o && !address(o, hold, p)) return false;
+  if (o && !address(o, p)) return false;
   out = p;
   return true;
 }
@@ -77,9 +93,9 @@ bool convert(PyObject* o, Hold& hold, T& out) {
     if constexpr (std::is_same_v<T, const mtla_layer_weights*>) {
       if (PyDict_Check(o)) {
         mtla_layer_weights& w = hold.lw;
-        if (!weight(o, "w_q", hold, w.w_q) || !weight(o, "w_qr", hold, w.w_qr) || !weight(o, "w_r", hold, w.w_r) ||
-            !weight(o, "w_kr", hold, w.w_kr) || !weight(o, "w_o", hold, w.w_o) || !weight(o, "ln_gamma", hold, w.ln_gamma) ||
-            !weight(o, "ln_beta", hold, w.ln_beta) || !number(o, "ln_eps", w.ln_eps) || !number(o, "rope_base", w.rope_base))
+        if (!weight(o, "w_q", w.w_q) || !weight(o, "w_qr", w.w_qr) || !weight(o, "w_r", w.w_r) ||
+            !weight(o, "w_kr", w.w_kr) || !weight(o, "w_o", w.w_o) || !weight(o, "ln_gamma", w.ln_gamma) ||
+            !weight(o, "ln_beta", w.ln_beta) || !number(o, "ln_eps", w.ln_eps) || !number(o, "rope_base", w.rope_base))
           return false;
         PyObject* dm = PyDict_GetItemString(o, "d_model");
         w.d_model = dm ? (int32_t)PyLong_AsLong(dm) : 0;
@@ -89,7 +105,8 @@ bool convert(PyObject* o, Hold& hold, T& out) {
       }
     }
     void* p;
-    if (!address(o, hold, p)) return false;
+    const bool ok = std::is_same_v<T, mtla_page_book*> ? structure(o, sizeof(mtla_page_book), hold, p) : address(o, p);
+    if (!ok) return false;
     out = reinterpret_cast<T>(p);
     return true;
   } else {
