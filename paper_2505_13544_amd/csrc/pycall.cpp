@@ -71,19 +71,46 @@ bool structure(PyObject* o, size_t bytes, Hold& hold, void*& out) {
   return true;
 }
 
-bool weight(PyObject* d, const char* key, const void*& out) {
-  PyObject* o = PyDict_GetItemString(d, key);
+// Entry `key` of the mapping d (the layer's weights): one that is required raises KeyError if it is missing.
+struct Entry {
+  PyObject* o = nullptr;
+  ~Entry() { Py_XDECREF(o); }
+};
+bool entry(PyObject* d, const char* key, bool required, Entry& e) {
+  if (required) return (e.o = PyMapping_GetItemString(d, key)) != nullptr;
+  if (PyDict_Check(d)) {
+    e.o = PyDict_GetItemString(d, key);
+    Py_XINCREF(e.o);
+    return true;
+  }
+  return (e.o = PyObject_CallMethod(d, "get", "s", key)) != nullptr;
+}
+
+bool weight(PyObject* d, const char* key, bool required, const void*& out) {
+  Entry e;
   void* p = nullptr;
-  if (o && !address(o, p)) return false;
+  if (!entry(d, key, required, e) || (e.o && !address(e.o, p))) return false;
   out = p;
   return true;
 }
 
 bool number(PyObject* d, const char* key, float& out) {
-  PyObject* o = PyDict_GetItemString(d, key);
+  Entry e;
+  if (!entry(d, key, false, e)) return false;
   out = 0.f;
-  if (!o || o == Py_None) return true;
-  out = (float)PyFloat_AsDouble(o);
+  if (!e.o || (e.o == Py_None && !PyDict_Check(d))) return true;  // absent (None is what another mapping's get returns)
+  out = (float)PyFloat_AsDouble(e.o);
+  return !PyErr_Occurred();
+}
+
+bool layer_weights(PyObject* d, mtla_layer_weights& w) {
+  Entry dm;
+  if (!weight(d, "w_q", true, w.w_q) || !weight(d, "w_qr", true, w.w_qr) || !weight(d, "w_r", true, w.w_r) ||
+      !weight(d, "w_kr", true, w.w_kr) || !weight(d, "w_o", true, w.w_o) || !weight(d, "ln_gamma", false, w.ln_gamma) ||
+      !weight(d, "ln_beta", false, w.ln_beta) || !entry(d, "d_model", true, dm) || !number(d, "ln_eps", w.ln_eps) ||
+      !number(d, "rope_base", w.rope_base))
+    return false;
+  w.d_model = (int32_t)PyLong_AsLong(dm.o);
   return !PyErr_Occurred();
 }
 
@@ -91,23 +118,14 @@ template <class T>
 bool convert(PyObject* o, Hold& hold, T& out) {
   if constexpr (std::is_pointer_v<T>) {
     if constexpr (std::is_same_v<T, const mtla_layer_weights*>) {
-      if (PyDict_Check(o)) {
-        mtla_layer_weights& w = hold.lw;
-        if (!weight(o, "w_q", w.w_q) || !weight(o, "w_qr", w.w_qr) || !weight(o, "w_r", w.w_r) ||
-            !weight(o, "w_kr", w.w_kr) || !weight(o, "w_o", w.w_o) || !weight(o, "ln_gamma", w.ln_gamma) ||
-            !weight(o, "ln_beta", w.ln_beta) || !number(o, "ln_eps", w.ln_eps) || !number(o, "rope_base", w.rope_base))
-          return false;
-        PyObject* dm = PyDict_GetItemString(o, "d_model");
-        w.d_model = dm ? (int32_t)PyLong_AsLong(dm) : 0;
-        if (PyErr_Occurred()) return false;
-        out = &w;
-        return true;
-      }
+      if (!layer_weights(o, hold.lw)) return false;
+      out = &hold.lw;
+    } else {
+      void* p;
+      const bool ok = std::is_same_v<T, mtla_page_book*> ? structure(o, sizeof(mtla_page_book), hold, p) : address(o, p);
+      if (!ok) return false;
+      out = reinterpret_cast<T>(p);
     }
-    void* p;
-    const bool ok = std::is_same_v<T, mtla_page_book*> ? structure(o, sizeof(mtla_page_book), hold, p) : address(o, p);
-    if (!ok) return false;
-    out = reinterpret_cast<T>(p);
     return true;
   } else {
     const long long v = PyLong_AsLongLong(o);

@@ -42,3 +42,29 @@ def test_a_page_book_is_the_structure():
             B.calls.mtla_pages_reserve(book, None, 1)
     with pytest.raises(AttributeError):   # the host arrays beside it are addresses
         B.calls.mtla_pages_reserve(B.mtla_page_book(), np.zeros(4, np.int32), 1)
+
+
+def _layer_step(lw):
+    ctx = B.Context(**GOOD)
+    return ctx.layer_decode_step_status(lw, 1024, 1024, 1024, 1024, 1024, 1024, None, 1024, 1024, 1024, 0, 1024, None, 1024, 1024)
+
+
+LAYER = dict(w_q=1024, w_qr=1024, w_r=1024, w_kr=1024, w_o=1024, d_model=512)
+
+
+@pytest.mark.parametrize("key", sorted(LAYER))
+def test_a_missing_layer_weight_is_named(key):
+    with pytest.raises(KeyError, match=key):
+        _layer_step({k: v for k, v in LAYER.items() if k != key})
+
+
+def test_layer_weights_are_a_mapping():
+    from types import MappingProxyType
+    for lw in (LAYER, dict(LAYER, ln_gamma=None, ln_beta=1024, ln_eps=1e-5, rope_base=1e4), MappingProxyType(LAYER)):
+        assert _layer_step(lw) == B.MTLA_ERR_INVALID_ARG   # batch 0
+    for bad in (None, 1024, [1024], b"abcd"):             # memory that is no mapping is never read as a structure
+        with pytest.raises(TypeError):
+            _layer_step(bad)
+    for k, v in (("d_model", None), ("d_model", 512.0), ("ln_eps", None), ("rope_base", "10000")):
+        with pytest.raises(TypeError):
+            _layer_step(dict(LAYER, **{k: v}))
