@@ -25,6 +25,14 @@ def _raw_stream(device: torch.device) -> int:
     return torch._C._cuda_getCurrentRawStream(device.index if device.index is not None else torch.cuda.current_device())
 
 
+def _capturing(device: torch.device) -> bool:
+    """Whether the current stream of `device` is being captured into a graph."""
+    if device.index is None or device.index == torch.cuda.current_device():
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.device(device):
+        return torch.cuda.is_current_stream_capturing()
+
+
 class Session:
     """One MTLA attention layer's device state plus the library calls."""
 
@@ -289,10 +297,24 @@ class PagedSession:
     def _reserve(self, batch, n_new=None):
         """Pages for n_new[b] (None: one) more tokens of the first `batch` sequences; uploads the table if it changed."""
         n = None if n_new is None else np.ascontiguousarray(n_new, dtype=np.int32)
-        if self._check_pages(B.calls.mtla_pages_reserve(self._book, None if n is None else n.ctypes.data, batch)):
+        k = self._book
+        head, count = k.free_head, k.free_count
+        got = self._check_pages(B.calls.mtla_pages_reserve(k, None if n is None else n.ctypes.data, batch))
+        if not got:
+            return
+        try:
+            if _capturing(self.device):
+                raise RuntimeError("a captured step cannot take new pages (a replay would copy a table that is gone): "
+                                   "reserve() them before the capture and step with reserve=False")
             staged = torch.empty(self.h_table.shape, dtype=torch.int32, pin_memory=True)
             staged.numpy()[:] = self.h_table
             self.table.copy_(staged, non_blocking=True)
+        except BaseException:   # the device's table is the old one: so is the host's
+            taken = self._ring[(head + np.arange(got)) % self.n_pages]
+            self.h_table[np.isin(self.h_table, taken)] = -1
+            self.refs[taken] = 0
+            k.free_head, k.free_count = head, count
+            raise
 
     def pages_in_use(self) -> int:
         return int((self.refs > 0).sum())
@@ -349,6 +371,8 @@ class PagedSession:
         """Beam reordering: sequence b continues what was sequence src_index[b] (host integers).  Complete pages are
         shared; every continuation gets a page of its own for the page being written to -- the source's own, taken
         over, when it is the source's only continuation.  Sequences nobody continues give their pages back."""
+        if _capturing(self.device):
+            raise RuntimeError("fork cannot be captured: its kernel reads host memory that later forks write")
         batch = len(src_index)
         if self._alt is None:
             self._alt = [torch.zeros_like(self.table), torch.empty_like(self.tail_c), torch.zeros_like(self.seq_len)]

@@ -209,3 +209,52 @@ def test_paged_chunked_prefill_equals_contiguous(stride):
     assert worst <= H.TOL["bf16"], worst
     assert_same_state(paged, flat, lens, "after the pieces")
     assert flat.device_status() == 0 and paged.device_status() == 0
+
+
+def test_page_bookkeeping_stays_out_of_a_capture():
+    # fork and a step that needs a page are refused while the stream is captured and leave everything as it was; steps whose
+    # pages were reserved before the capture are captured, and every replay gives what eager steps give
+    B, steps, page_slots = 3, 6, 16
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="paged_capture", batch=B, d_model=64, n_heads=4, d_head=64, r=128, d_rope=32,
+                                           stride=1, prefix=16, steps=steps, seed=711)
+    wts = W.make_weights(wl)
+    toks = [W.make_tokens(wl, wts, b, 0, 16 + steps) for b in range(B)]
+    d = {f: H.to_device(np.stack([getattr(t, f) for t in toks]), wl.dtype) for f in ("q", "q_rope", "c", "kr")}
+    at = lambda f, t: d[f][:, t].contiguous()
+    tok = [(at("c", 16 + t)[:, None], at("kr", 16 + t)[:, None], at("q", 16 + t), at("q_rope", 16 + t)) for t in range(steps)]
+    sess = make_paged(wl, page_slots=page_slots, n_pages=12, seed=1)
+    H.upload_weights(sess, wts)
+    sess.append(d["c"][:, :16].contiguous(), d["kr"][:, :16].contiguous())   # ends on a page's last slot
+    out = torch.zeros(steps, B, wl.n_heads, wl.d_head, device="cuda")
+    eager = torch.zeros_like(out)
+    host = lambda: (sess.h_table.tolist(), sess.h_len.tolist(), sess.refs.tolist(), sess.free.tolist(), sess.table.data_ptr())
+    torch.cuda.synchronize()
+    for refused in (lambda: sess.fork([0] * B), lambda: sess.step(*tok[0], out=out[0]), lambda: sess.reserve([page_slots] * B)):
+        was = host()
+        with pytest.raises(RuntimeError, match="captur"):
+            with torch.cuda.graph(torch.cuda.CUDAGraph()):
+                refused()
+        assert host() == was
+    sess.fork(range(B))
+    sess.reserve([steps] * B)
+    start = [x.clone() for x in (sess.seq_len, sess.tail_c)]
+
+    def run(o):
+        for t in range(steps):
+            sess.step(*tok[t], out=o[t])
+
+    lens = sess.h_len.copy()
+    run(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    sess.h_len[:] = lens
+    with torch.cuda.graph(graph):
+        run(out)
+    for _ in range(3):
+        sess.seq_len.copy_(start[0])
+        sess.tail_c.copy_(start[1])
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+    assert sess.device_status() == 0
