@@ -378,16 +378,35 @@ class PagedSession:
             self._alt = [torch.zeros_like(self.table), torch.empty_like(self.tail_c), torch.zeros_like(self.seq_len)]
         host, where = self._picks.next(2 * batch)   # sources, then the pages they will write to; the kernel reads them there
         host[:batch] = src_index.cpu() if isinstance(src_index, torch.Tensor) else src_index
-        self._check_pages(B.calls.mtla_pages_fork(self._book, where, batch, where + 4 * batch))
+        k = self._book
+        head, count = k.free_head, k.free_count
+        self._check_pages(B.calls.mtla_pages_fork(k, where, batch, where + 4 * batch))
+        try:
+            self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len, where,
+                                      where + 4 * batch, batch, self._alt[0], self._alt[1], self._alt[2], self.workspace,
+                                      self.stream)
+        except BaseException:   # the device's state is the old one: so is the host's
+            self._undo_fork(head, count, host[batch:])
+            raise
         self.h_table, self._h_next[0] = self._h_next[0], self.h_table
         self.h_len, self._h_next[1] = self._h_next[1], self.h_len
-        self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len, where, where + 4 * batch,
-                                  batch, self._alt[0], self._alt[1], self._alt[2], self.workspace, self.stream)
         cur = [self.table, self.tail_c, self.seq_len]
         self.table, self.tail_c, self.seq_len = self._alt
         self._alt = cur
         # the kernel wrote rows 0 .. batch-1 of the new table up to the page being written to; what lies above is
         # whatever the buffer held, and is replaced (the whole table is uploaded) before an append reaches it
+
+    def _undo_fork(self, head, count, fresh):
+        """The page book as it was before a fork (head, count: its free pages then; fresh: the pages the fork gave out).  The
+        fork leaves the old table and lengths in the book's second arrays; the free pages were those it took, in the order
+        it took them, and then those left in front of what it gave back."""
+        k = self._book
+        k.table, k.next_table, k.len, k.next_len = k.next_table, k.table, k.next_len, k.len
+        self.refs[:] = np.bincount(self.h_table[self.h_table >= 0], minlength=self.n_pages)
+        taken = fresh[self.refs[fresh] == 0]
+        free = np.concatenate([taken, self.free[:count - len(taken)]])
+        k.free_head, k.free_count = head, count
+        self._ring[(head + np.arange(count)) % self.n_pages] = free
 
     def device_status(self) -> int:
         return self.ctx.device_status(self.workspace, self.stream)

@@ -75,3 +75,22 @@ def test_bookkeeping_is_refused_while_the_stream_is_captured(launches):
     assert np.array_equal(s.table.numpy()[s.h_table >= 0], s.h_table[s.h_table >= 0])
     s.fork([0, 0, 1, 3])
     assert len(launches.forks) == 1 and state(s) != was
+
+
+@pytest.mark.parametrize("n_pages", [10, 11, 24])            # the ring nearly used up, and with room
+def test_a_fork_whose_launch_fails_changes_nothing(launches, n_pages):
+    rng = np.random.default_rng(n_pages)
+    s = make(n_pages=n_pages, order=rng.permutation(n_pages))
+    grow(s, [35, 5, 0, 30])                                   # pages 2, 1, 0, 1
+    for src in ([0, 0, 1, 3], [3, 1, 0], [0, 1, 2, 3], [2, 2, 2, 2], [0]):
+        was = state(s)
+        launches.fail = RuntimeError("launch")
+        with pytest.raises(RuntimeError, match="launch"):
+            s.fork(src)
+        assert state(s) == was
+        launches.fail = None
+        s.fork(src)
+        state(s)
+        expected = [was[1][b] for b in src] + [0] * (4 - len(src))
+        assert s.h_len.tolist() == expected and launches.forks[-1][0] == src
+        grow(s, [4] * 4)
