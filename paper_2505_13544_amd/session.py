@@ -292,7 +292,9 @@ class PagedSession:
     def reserve(self, n_new):
         """Pages for n_new[b] more tokens of every sequence, ahead of time (a caller that replays steps as a graph
         reserves once and then steps with reserve=False)."""
-        self._reserve(len(n_new), n_new)
+        n_new = [int(x) for x in n_new]
+        if n_new:
+            self._reserve(len(n_new), n_new)
 
     def _reserve(self, batch, n_new=None):
         """Pages for n_new[b] (None: one) more tokens of the first `batch` sequences; uploads the table if it changed."""
@@ -373,11 +375,18 @@ class PagedSession:
         over, when it is the source's only continuation.  Sequences nobody continues give their pages back."""
         if _capturing(self.device):
             raise RuntimeError("fork cannot be captured: its kernel reads host memory that later forks write")
+        if not isinstance(src_index, list):
+            src_index = src_index.tolist() if isinstance(src_index, (np.ndarray, torch.Tensor)) else list(src_index)
         batch = len(src_index)
+        if not 0 < batch <= self.max_batch:   # (more would run over into the next forks' indices)
+            raise IndexError(f"fork of {batch} sequences in a session of {self.max_batch}")
         if self._alt is None:
             self._alt = [torch.zeros_like(self.table), torch.empty_like(self.tail_c), torch.zeros_like(self.seq_len)]
         host, where = self._picks.next(2 * batch)   # sources, then the pages they will write to; the kernel reads them there
-        host[:batch] = src_index.cpu() if isinstance(src_index, torch.Tensor) else src_index
+        try:
+            host[:batch] = src_index
+        except TypeError:                     # numbers that numpy does not take, a GPU's for instance
+            host[:batch] = [int(x) for x in src_index]
         k = self._book
         head, count = k.free_head, k.free_count
         self._check_pages(B.calls.mtla_pages_fork(k, where, batch, where + 4 * batch))

@@ -94,3 +94,30 @@ def test_a_fork_whose_launch_fails_changes_nothing(launches, n_pages):
         expected = [was[1][b] for b in src] + [0] * (4 - len(src))
         assert s.h_len.tolist() == expected and launches.forks[-1][0] == src
         grow(s, [4] * 4)
+
+
+def test_what_a_fork_and_a_reserve_take(launches):
+    s = make(n_pages=40)
+    s.reserve([])                                             # nothing to do
+    s.reserve(torch.tensor([3, 3, 3, 3]))
+    s.h_len[:] = 3
+
+    class Number:
+        def __int__(self):
+            return 1
+
+    s.fork([Number(), 0])
+    assert launches.forks.pop()[0] == [1, 0]
+    for src in ([0, 1, 1, 3], (0, 1, 1, 3), range(4), (x for x in [3, 2, 1, 0]), np.array([2, 2, 2, 2]), torch.tensor([0, 1])):
+        s.fork(src)
+        state(s)
+    assert [f[0] for f in launches.forks] == [[0, 1, 1, 3], [0, 1, 1, 3], [0, 1, 2, 3], [3, 2, 1, 0], [2, 2, 2, 2], [0, 1]]
+    was, pinned = state(s), s._picks.host.copy()
+    for bad in ([], [0] * 5, [0] * 9):                        # a pinned slot holds four sources and four pages
+        with pytest.raises(IndexError):
+            s.fork(bad)
+    assert np.array_equal(s._picks.host, pinned)
+    for bad in ([4], [-1]):
+        with pytest.raises(IndexError):
+            s.fork(bad)
+    assert state(s) == was
