@@ -792,13 +792,9 @@ hipError_t launch_rows(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   using C = MfmaCfg<R, DR, NHT>;
   constexpr size_t smem = C::tile_bytes + (size_t)kWaves * 16 * C::QS * 2;
   static_assert(smem <= 160 * 1024, "LDS budget of one compute unit");
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mfma_rows_kernel<R, DR, NHT, NS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&attn_mfma_rows_kernel<R, DR, NHT, NS>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
   const dim3 grid((a.T + C::WPT - 1) / C::WPT, a.batch);
   launch_timed(attn_mfma_rows_kernel<R, DR, NHT, NS>, grid, dim3(kBlock), smem, st, ev, a);
   return hipGetLastError();
@@ -807,13 +803,9 @@ hipError_t launch_rows(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
 template <int R, int DR, bool SH, bool PG>
 hipError_t launch_split(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   constexpr size_t smem = SplitLds<MfmaCfg<R, DR, 1>>::bytes;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_split_kernel<R, DR, SH, PG>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&attn_split_kernel<R, DR, SH, PG>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
   launch_timed(attn_split_kernel<R, DR, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
   return hipGetLastError();
 }
@@ -823,13 +815,9 @@ hipError_t launch_static(const AttnArgs& a, hipStream_t st, const EventPair& ev)
   using C = MfmaCfg<R, DR, NHT>;
   constexpr size_t smem = C::body_bytes(QL) + C::ml_bytes;
   static_assert(smem <= 160 * 1024, "LDS budget of one compute unit");
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mfma_kernel<R, DR, NHT, NS, QL, SH, PG>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&attn_mfma_kernel<R, DR, NHT, NS, QL, SH, PG>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
   launch_timed(attn_mfma_kernel<R, DR, NHT, NS, QL, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
   return hipGetLastError();
 }
@@ -841,13 +829,9 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
     if (a.prefix_owner || a.pages.table) return hipErrorInvalidValue;  // shared prefixes, pages: static schedule or the column-split kernel
     const size_t smem = C::body_bytes(QL) + C::ml_bytes + (size_t)(2 * a.batch + 1 + kBlock) * sizeof(int);
     if (smem > 160 * 1024) return hipErrorInvalidValue;
-    static bool attr_set = false;  // LDS above the 64 KB default needs an explicit opt-in, once
-    if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
+    static DeviceSet lds_allowed;
+    const hipError_t e = allow_lds(&attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, 160 * 1024, lds_allowed);
+    if (e != hipSuccess) return e;
     launch_timed(attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, dim3(a.n_persistent), dim3(kBlock), smem, st, ev, a);
     return hipGetLastError();
   }

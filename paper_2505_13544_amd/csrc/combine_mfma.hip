@@ -292,13 +292,9 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
 template <int R, int DH, int RPT, bool PF16, bool PS = false, bool HF = PS>
 hipError_t launch_one(const CombineArgs& a, const dim3& grid, int tiles_per_wg, hipStream_t st) {
   constexpr int smem = CombineLds<R, DH, RPT, PS>::bytes;
-  static bool attr_set = false;  // LDS above the 64 KB default needs an explicit opt-in, once
-  if (smem > 64 * 1024 && !attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>), grid, dim3(kBlock), smem, st, a, tiles_per_wg);
   return hipGetLastError();
 }

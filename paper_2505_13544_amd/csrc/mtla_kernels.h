@@ -4,6 +4,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "device_set.h"
+
 namespace mtla {
 
 // Paged slot storage: the cache arrays are then one pool of fixed-size pages, [n_pages, 2^shift slots, width],
@@ -316,6 +318,19 @@ inline void launch_timed(K kernel, const dim3& grid, const dim3& block, size_t s
     hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)smem, st, ev.start, ev.stop, 0, a);
   else
     hipLaunchKernelGGL(kernel, grid, block, smem, st, a);
+}
+
+// Lets `kernel` take `bytes` of dynamic LDS where that is more than the 64 KB every kernel may.  The permission belongs to
+// the device, so it is asked for once on each (`done`: a static of the launcher of that kernel).
+template <class K>
+inline hipError_t allow_lds(K kernel, size_t bytes, DeviceSet& done) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess || done.has(device)) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) done.add(device);
+  return e;
 }
 
 hipError_t launch_fill_zero(int32_t* p, int n, hipStream_t st);
