@@ -19,6 +19,7 @@ namespace mtla {
 namespace {
 
 constexpr int kMaxRPerThread = 4;  // r <= 1024 with 256 threads
+// d_hyper <= 256 (mtla_create): a thread of a workgroup holds at most one element of a row of the hyper-network's width
 
 constexpr int kTPR = 4;                 // lanes sharing one hyper-network row
 constexpr int kRowsPerPass = kBlock / kTPR;
@@ -51,8 +52,7 @@ __device__ __forceinline__ void hyper_linear(const T* A, const T* ha, const floa
 // <Linear(c), Linear(pe_j)> = sum_y sg[y] G[slot][y], reduced over the workgroup; red: [4] floats.
 template <typename T>
 __device__ __forceinline__ float hyper_logit(const float* sg, const T* Grow, float* red, int dy, int tid) {
-  float zp = 0.f;
-  for (int y = tid; y < dy; y += kBlock) zp += sg[y] * to_f32(Grow[y]);
+  float zp = tid < dy ? sg[tid] * to_f32(Grow[tid]) : 0.f;
   zp = wave_sum(zp);
   if ((tid & (kWave - 1)) == 0) red[tid >> 6] = zp;
   __syncthreads();
@@ -141,7 +141,7 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
     }
   }
   float g_pre = 0.f;  // this thread's element of the slot's row of G
-  if (hyper && dy <= kBlock && tid < dy) {
+  if (hyper && tid < dy) {
     const int slot_c = p0 / s < a.max_slots ? p0 / s : a.max_slots - 1;  // a full sequence is refused below
     g_pre = to_f32(reinterpret_cast<const T*>(a.hyp_G)[(size_t)slot_c * dy + tid]);
   }
@@ -230,16 +230,12 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   const bool continuing = (p0 - slot * s) != 0;
   float w;
   if (hyper) {
-    float z;
-    if (dy <= kBlock) {  // same sum as hyper_logit, with the row already in registers
-      float zp = tid < dy ? sg[tid] * g_pre : 0.f;
-      zp = wave_sum(zp);
-      if ((tid & (kWave - 1)) == 0) red[tid >> 6] = zp;
-      __syncthreads();
-      z = (red[0] + red[1]) + (red[2] + red[3]);
-    } else {
-      z = hyper_logit(sg, reinterpret_cast<const T*>(a.hyp_G) + (size_t)slot * dy, red, dy, tid);
-    }
+    // the sum of hyper_logit, with the row already in registers
+    float zp = tid < dy ? sg[tid] * g_pre : 0.f;
+    zp = wave_sum(zp);
+    if ((tid & (kWave - 1)) == 0) red[tid >> 6] = zp;
+    __syncthreads();
+    const float z = (red[0] + red[1]) + (red[2] + red[3]);
     w = 1.f / (1.f + expf(-z));
   } else {
     w = a.w_override[b];

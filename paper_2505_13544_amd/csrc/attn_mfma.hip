@@ -824,16 +824,19 @@ hipError_t launch_static(const AttnArgs& a, hipStream_t st, const EventPair& ev)
 
 template <int R, int DR, int NHT, int NS, bool QL>
 hipError_t launch_one(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
-  using C = MfmaCfg<R, DR, NHT>;
   if (a.n_persistent > 0) {
-    if (a.prefix_owner || a.pages.table) return hipErrorInvalidValue;  // shared prefixes, pages: static schedule or the column-split kernel
-    const size_t smem = C::body_bytes(QL) + C::ml_bytes + (size_t)(2 * a.batch + 1 + kBlock) * sizeof(int);
-    if (smem > 160 * 1024) return hipErrorInvalidValue;
-    static DeviceSet lds_allowed;
-    const hipError_t e = allow_lds(&attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, 160 * 1024, lds_allowed);
-    if (e != hipSuccess) return e;
-    launch_timed(attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, dim3(a.n_persistent), dim3(kBlock), smem, st, ev, a);
-    return hipGetLastError();
+    if constexpr (R == 64) {  // (attn_cols.hip has every other width)
+      using C = MfmaCfg<R, DR, NHT>;
+      if (a.prefix_owner || a.pages.table) return hipErrorInvalidValue;  // shared prefixes, pages: static schedule or the column-split kernel
+      const size_t smem = C::body_bytes(QL) + C::ml_bytes + (size_t)(2 * a.batch + 1 + kBlock) * sizeof(int);
+      if (smem > 160 * 1024) return hipErrorInvalidValue;
+      static DeviceSet lds_allowed;
+      const hipError_t e = allow_lds(&attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, 160 * 1024, lds_allowed);
+      if (e != hipSuccess) return e;
+      launch_timed(attn_mfma_balanced_kernel<R, DR, NHT, NS, QL>, dim3(a.n_persistent), dim3(kBlock), smem, st, ev, a);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
   }
   if (a.pages.table) return a.prefix_owner ? hipErrorInvalidValue : launch_static<R, DR, NHT, NS, QL, false, true>(a, st, ev);
   return a.prefix_owner ? launch_static<R, DR, NHT, NS, QL, true, false>(a, st, ev)
@@ -859,6 +862,14 @@ hipError_t launch_rd(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   return deep ? launch_one<R, DR, 2, kDeep, kDeepQL>(a, st, ev) : launch_one<R, DR, 2, 1, false>(a, st, ev);
 }
 
+template <int R, int DR>
+hipError_t launch_case(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
+  if (a.T == 0) return launch_rd<R, DR>(a, st, ev);
+  if constexpr (R == 64)  // (attn_cols.hip has the parallel form of every other width)
+    return a.n_heads <= 16 ? launch_rows<R, DR, 1, 2>(a, st, ev) : launch_rows<R, DR, 2, 2>(a, st, ev);
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
 
 bool attn_mfma_supported(const AttnArgs& a) {
@@ -867,11 +878,8 @@ bool attn_mfma_supported(const AttnArgs& a) {
 }
 
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
-#define MTLA_CASE(RR, DD)                                                                       \
-  if (a.r == RR && a.d_rope == DD) {                                                            \
-    if (a.T == 0) return launch_rd<RR, DD>(a, st, ev);                                              \
-    return a.n_heads <= 16 ? launch_rows<RR, DD, 1, 2>(a, st, ev) : launch_rows<RR, DD, 2, 2>(a, st, ev); \
-  }
+#define MTLA_CASE(RR, DD) \
+  if (a.r == RR && a.d_rope == DD) return launch_case<RR, DD>(a, st, ev);
   MTLA_CASE(64, 32)
   MTLA_CASE(64, 64)
   MTLA_CASE(128, 32)

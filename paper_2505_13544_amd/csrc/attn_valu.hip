@@ -1,11 +1,13 @@
-// fp32 vector-ALU attention kernels.  They carry the MTLA_F32 storage path
-// (whose 1e-5 parity bound rules out bf16 matrix-core inputs) and serve as the
-// plain fallback for shapes the matrix-core kernels do not cover.
+// fp32 vector-ALU attention kernels: the plain fallback for shapes the matrix-core kernels do not cover (bf16 storage:
+// more than 32 heads, decode and parallel form; fp32 storage: the parallel form at a d_head that attn_f32.hip has no kernel
+// for), and the partial states of every absorbed or fp32 parallel form.
 //
-//   attn_split_kernel    logits, online softmax and the latent-space weighted
+//   attn_valu_kernel     logits, online softmax and the latent-space weighted
 //                        sum over one chunk of slots, all heads of a head group
 //                        sharing each cache row                                 (Eq. (with-rope))
 //   partial_states_kernel  C_hat'[m] = running in-chunk sum of w_n c_n          (training form)
+#include <type_traits>
+
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -15,23 +17,27 @@ namespace {
 
 constexpr int kWaves = kBlock / kWave;
 
-// Live column count of a query row and the mapping from column k to a source row.
+// Live column count of a query row and the mapping from column k to a source row.  Decode addressing is bf16 storage's
+// only: attn_f32.hip decodes every fp32 shape.
+template <typename T_>
 struct RowMap {
   int b, m, live, stride, T, max_slots;
+  __device__ __forceinline__ bool decode() const { return std::is_same<T_, bf16>::value && T == 0; }
   __device__ __forceinline__ size_t src(int k) const {
-    if (T == 0) return (size_t)b * max_slots + k;                        // decode: cache slot k
+    if (decode()) return (size_t)b * max_slots + k;                        // decode: cache slot k
     const int row = (k < live - 1) ? (k * stride + stride - 1) : m;      // prefill: final state of
     return (size_t)b * T + row;                                          // chunk k, or own row
   }
 };
 
-__device__ __forceinline__ RowMap make_row_map(int row, const int32_t* seq_len, int stride, int T,
-                                               int max_slots) {
-  RowMap rm;
+template <typename T_>
+__device__ __forceinline__ RowMap<T_> make_row_map(int row, const int32_t* seq_len, int stride, int T,
+                                                   int max_slots) {
+  RowMap<T_> rm;
   rm.stride = stride;
   rm.T = T;
   rm.max_slots = max_slots;
-  if (T == 0) {
+  if (rm.decode()) {
     rm.b = row;
     rm.m = 0;
     const int len = seq_len[row];
@@ -46,7 +52,7 @@ __device__ __forceinline__ RowMap make_row_map(int row, const int32_t* seq_len, 
 }
 
 template <typename T, int R, int DR, int HG>
-__global__ __launch_bounds__(kBlock) void attn_split_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kBlock) void attn_valu_kernel(AttnArgs a) {
   constexpr int E = R + DR, RI = R / kWave;
   static_assert(R % kWave == 0 && DR <= kWave, "lane mapping");
   __shared__ float sq[HG][E];
@@ -55,7 +61,7 @@ __global__ __launch_bounds__(kBlock) void attn_split_kernel(AttnArgs a) {
 
   const int split = blockIdx.x, row = blockIdx.y, h0 = blockIdx.z * HG;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
-  const RowMap rm = make_row_map(row, a.seq_len, a.stride, a.T, a.max_slots);
+  const RowMap<T> rm = make_row_map<T>(row, a.seq_len, a.stride, a.T, a.max_slots);
   const int k0 = split * a.chunk;
   const int k1 = rm.live < k0 + a.chunk ? rm.live : k0 + a.chunk;
   if (k0 >= k1) return;
@@ -161,7 +167,6 @@ __global__ __launch_bounds__(kBlock) void partial_states_kernel(PartialStateArgs
   const int b = int(idx / ((size_t)a.r * n_chunks));
   const T* c = reinterpret_cast<const T*>(a.c);
   T* cp = reinterpret_cast<T*>(a.cprime);
-  _Float16* cp16 = reinterpret_cast<_Float16*>(a.cprime);
   float run = 0.f;
   const int n_end = (ch + 1) * a.stride < a.T ? (ch + 1) * a.stride : a.T;
   const int len = a.seq_len ? a.seq_len[b] : a.T;
@@ -169,26 +174,28 @@ __global__ __launch_bounds__(kBlock) void partial_states_kernel(PartialStateArgs
     const size_t o = ((size_t)b * a.T + n) * a.r + e;
     // padding rows hold zeros: they are multiplied by zero weights in the tiles of live rows
     run = n < len ? run + a.w[(size_t)b * a.T + n] * to_f32(c[o]) : 0.f;
-    if (a.out_f16) cp16[o] = static_cast<_Float16>(run);
-    else cp[o] = from_f32<T>(run);
+    cp[o] = from_f32<T>(run);
   }
 }
 
 template <typename T, int R, int DR>
 hipError_t launch_attn_rd(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   const int rows = a.T ? a.batch * a.T : a.batch;
-  if (a.n_heads <= 4) {
-    const dim3 grid(a.n_splits, rows, 1);
-    launch_timed(attn_split_kernel<T, R, DR, 4>, grid, dim3(kBlock), 0, st, ev, a);
-  } else {
-    const dim3 grid(a.n_splits, rows, (a.n_heads + 7) / 8);
-    launch_timed(attn_split_kernel<T, R, DR, 8>, grid, dim3(kBlock), 0, st, ev, a);
+  if constexpr (!std::is_same<T, bf16>::value) {  // (bf16 storage comes here with more than 32 heads only)
+    if (a.n_heads <= 4) {
+      const dim3 grid(a.n_splits, rows, 1);
+      launch_timed(attn_valu_kernel<T, R, DR, 4>, grid, dim3(kBlock), 0, st, ev, a);
+      return hipGetLastError();
+    }
   }
+  const dim3 grid(a.n_splits, rows, (a.n_heads + 7) / 8);
+  launch_timed(attn_valu_kernel<T, R, DR, 8>, grid, dim3(kBlock), 0, st, ev, a);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
+  if (!std::is_same<T, bf16>::value && a.T == 0) return hipErrorInvalidValue;
 #define MTLA_CASE(RR, DD) \
   if (a.r == RR && a.d_rope == DD) return launch_attn_rd<T, RR, DD>(a, st, ev);
   MTLA_CASE(64, 32)
@@ -205,7 +212,7 @@ hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st, const EventPair& ev)
 
 }  // namespace
 
-hipError_t launch_attn_split(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev) {
+hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev) {
   return dtype == 0 ? launch_attn_t<float>(a, st, ev) : launch_attn_t<bf16>(a, st, ev);
 }
 

@@ -514,7 +514,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     ev.stop = c->ev_stop[c->prof_n++];
   }
   const hipError_t le = g.dtype == MTLA_F32 ? launch_attn_decode_f32(at, st, ev)
-                        : !use_mfma         ? launch_attn_split(at, g.dtype, st, ev)
+                        : !use_mfma         ? launch_attn_valu(at, g.dtype, st, ev)
                                   : (attn_cols_supported(at) ? launch_attn_cols(at, st, ev) : launch_attn_mfma(at, st, ev));
   if (!hip_ok(le)) return MTLA_ERR_HIP;
 
@@ -1206,7 +1206,6 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
   ps.r = g.r;
   ps.stride = g.stride;
   ps.seq_len = seq_lens;
-  ps.out_f16 = 0;
 
   // With many query rows per head the un-absorbed form is the cheaper one: explicit keys and
   // values for all rows (scratch inside the area the absorbed query operand would take), then
@@ -1329,7 +1328,7 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
     ev.start = c->ev_start[c->prof_n];
     ev.stop = c->ev_stop[c->prof_n++];
   }
-  const hipError_t le = !use_mfma ? launch_attn_split(at, g.dtype, st, ev)
+  const hipError_t le = !use_mfma ? launch_attn_valu(at, g.dtype, st, ev)
                                   : (attn_cols_rows_supported(at) ? launch_attn_cols_rows(at, st, ev)
                                                                   : launch_attn_mfma(at, st, ev));
   if (!hip_ok(le)) return MTLA_ERR_HIP;

@@ -301,9 +301,8 @@ struct PartialStateArgs {
   const void* c;   // [B, T, r]
   const float* w;  // [B, T]
   const int32_t* seq_len = nullptr;  // [B] or NULL: rows at and past seq_len[b] are padding (written as zeros)
-  void* cprime;    // [B, T, r], storage type, or fp16 if out_f16
+  void* cprime;    // [B, T, r], storage type
   int batch, T, r, stride;
-  int out_f16;     // 1: write IEEE half (the explicit-form prefill works in fp16)
 };
 
 // Optional timing of one launch: the events are attached to the kernel's own dispatch, so their
@@ -354,7 +353,7 @@ hipError_t launch_decode_front_f32(const AppendArgs& ap, const AbsorbArgs& ab, h
 hipError_t launch_attn_decode_f32(const AttnArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 bool prefill_f32_supported(const ExplicitArgs& a);
 hipError_t launch_prefill_f32(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
-hipError_t launch_attn_split(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev = EventPair());
+hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev = EventPair());
 // bf16 matrix-core variant of the split pass (decode addressing only)
 bool attn_mfma_supported(const AttnArgs& a);
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st, const EventPair& ev = EventPair());

@@ -336,8 +336,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   static_assert(G::NCR <= NW, "one RoPE key chunk per wavefront at most");
   static_assert(G::NCK % NW == 0, "whole rounds of key and value chunks");
   // RoPE keys: fewer chunks than wavefronts at d_R = 32, where two wavefronts bring the same one, so that every wavefront
-  // has the same number of loads in flight and the waits are constants
-  constexpr int LOADS = 2 * NIK + 1;
+  // has the same 2 NIK + 1 loads in flight
   const int wr = wv % G::NCR, row_r = (64 * wr + lane) / RC;
   const uint32_t src_r = 8 * (((64 * wr + lane) % RC) ^ swz_rows16<RC>(row_r));
   // ---- where this lane reads: key rows 16 sb + l16 (piece 4 kk + g), value rows 4g + l16/4 (+16)
@@ -375,7 +374,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       c = c < n_cols ? c : n_cols - 1;
       return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
     };
-    // this wavefront's part of tile t on its way into buffer t % NBUF: LOADS loads.  Tiles are asked for in order; while
+    // this wavefront's part of tile t on its way into buffer t % NBUF: 2 NIK + 1 loads.  Tiles are asked for in order; while
     // their rows are at one distance (`rs`: 1 among the slots of the past, s among the chunk-final rows) the next
     // tile's addresses are the last one's plus a constant: uniform bases and lane offsets that stand.
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
