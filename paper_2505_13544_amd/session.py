@@ -27,10 +27,10 @@ def _raw_stream(device: torch.device) -> int:
 
 def _capturing(device: torch.device) -> bool:
     """Whether the current stream of `device` is being captured into a graph."""
-    if device.index is None or device.index == torch.cuda.current_device():
-        return torch.cuda.is_current_stream_capturing()
+    if device.index is None or device.index == torch._C._cuda_getDevice():
+        return torch._C._cuda_isCurrentStreamCapturing()
     with torch.cuda.device(device):
-        return torch.cuda.is_current_stream_capturing()
+        return torch._C._cuda_isCurrentStreamCapturing()
 
 
 class Session:
@@ -299,9 +299,7 @@ class PagedSession:
     def _reserve(self, batch, n_new=None):
         """Pages for n_new[b] (None: one) more tokens of the first `batch` sequences; uploads the table if it changed."""
         n = None if n_new is None else np.ascontiguousarray(n_new, dtype=np.int32)
-        k = self._book
-        head, count = k.free_head, k.free_count
-        got = self._check_pages(B.calls.mtla_pages_reserve(k, None if n is None else n.ctypes.data, batch))
+        got = self._check_pages(B.calls.mtla_pages_reserve(self._book, None if n is None else n.ctypes.data, batch))
         if not got:
             return
         try:
@@ -312,10 +310,11 @@ class PagedSession:
             staged.numpy()[:] = self.h_table
             self.table.copy_(staged, non_blocking=True)
         except BaseException:   # the device's table is the old one: so is the host's
-            taken = self._ring[(head + np.arange(got)) % self.n_pages]
+            k = self._book
+            k.free_head, k.free_count = (k.free_head - got) % self.n_pages, k.free_count + got
+            taken = self.free[:got]
             self.h_table[np.isin(self.h_table, taken)] = -1
             self.refs[taken] = 0
-            k.free_head, k.free_count = head, count
             raise
 
     def pages_in_use(self) -> int:
@@ -387,15 +386,15 @@ class PagedSession:
             host[:batch] = src_index
         except TypeError:                     # numbers that numpy does not take, a GPU's for instance
             host[:batch] = [int(x) for x in src_index]
-        k = self._book
-        head, count = k.free_head, k.free_count
-        self._check_pages(B.calls.mtla_pages_fork(k, where, batch, where + 4 * batch))
+        self._check_pages(B.calls.mtla_pages_fork(self._book, where, batch, where + 4 * batch))
         try:
-            self.ctx.cache_fork_paged(self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len, where,
-                                      where + 4 * batch, batch, self._alt[0], self._alt[1], self._alt[2], self.workspace,
-                                      self.stream)
+            rc = B.calls.mtla_cache_fork_paged(self.ctx._ptr, self.pool_c, self.pool_kr, self.table, self.tail_c, self.seq_len,
+                                               where, where + 4 * batch, batch, self._alt[0], self._alt[1], self._alt[2],
+                                               self.workspace, _raw_stream(self.device))
+            if rc:
+                raise B.MtlaError(rc, "mtla_cache_fork_paged")
         except BaseException:   # the device's state is the old one: so is the host's
-            self._undo_fork(head, count, host[batch:])
+            self._undo_fork(host[batch:])
             raise
         self.h_table, self._h_next[0] = self._h_next[0], self.h_table
         self.h_len, self._h_next[1] = self._h_next[1], self.h_len
@@ -405,17 +404,19 @@ class PagedSession:
         # the kernel wrote rows 0 .. batch-1 of the new table up to the page being written to; what lies above is
         # whatever the buffer held, and is replaced (the whole table is uploaded) before an append reaches it
 
-    def _undo_fork(self, head, count, fresh):
-        """The page book as it was before a fork (head, count: its free pages then; fresh: the pages the fork gave out).  The
-        fork leaves the old table and lengths in the book's second arrays; the free pages were those it took, in the order
-        it took them, and then those left in front of what it gave back."""
+    def _undo_fork(self, fresh):
+        """The page book as it was before a fork that gave out the pages `fresh`.  The fork leaves the old table and lengths in
+        the book's second arrays; the free pages were those it took, in the order it took them, and then what is free now
+        without what it gave back (the last of them)."""
         k = self._book
         k.table, k.next_table, k.len, k.next_len = k.next_table, k.table, k.next_len, k.len
-        self.refs[:] = np.bincount(self.h_table[self.h_table >= 0], minlength=self.n_pages)
-        taken = fresh[self.refs[fresh] == 0]
-        free = np.concatenate([taken, self.free[:count - len(taken)]])
-        k.free_head, k.free_count = head, count
-        self._ring[(head + np.arange(count)) % self.n_pages] = free
+        refs = np.bincount(self.h_table[self.h_table >= 0], minlength=self.n_pages).astype(np.int32)
+        taken = fresh[refs[fresh] == 0]
+        given = int(((refs > 0) & (self.refs == 0)).sum())
+        free = np.concatenate([taken, self.free[:k.free_count - given]])
+        self.refs[:] = refs
+        k.free_head, k.free_count = (k.free_head - len(taken)) % self.n_pages, len(free)
+        self._ring[(k.free_head + np.arange(len(free))) % self.n_pages] = free
 
     def device_status(self) -> int:
         return self.ctx.device_status(self.workspace, self.stream)

@@ -1,4 +1,6 @@
 """The host side of PagedSession without a GPU: buffers in host memory, launches replaced by records of their arguments."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -9,14 +11,15 @@ from paper_2505_13544_amd import session as S
 
 class Launches:
     def __init__(self):
-        self.capturing, self.fail, self.forks = False, None, []
+        self.capturing, self.fail, self.forks = False, 0, []
 
     def fork(self, ctx, c, kr, table, tail, lens, src, fresh, batch, *dst):
-        if self.fail:
+        if isinstance(self.fail, Exception):
             raise self.fail
-        import ctypes
-        ints = lambda at: list((ctypes.c_int32 * batch).from_address(at))
-        self.forks.append((ints(src), ints(fresh)))
+        if not self.fail:
+            ints = lambda at: list((ctypes.c_int32 * batch).from_address(at))
+            self.forks.append((ints(src), ints(fresh)))
+        return self.fail
 
 
 @pytest.fixture
@@ -34,9 +37,9 @@ def launches(monkeypatch):
     monkeypatch.setattr(torch.cuda, "Event", Event)
     monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, **k: empty(*a, **k))
     monkeypatch.setattr(S, "_raw_stream", lambda device: 0)
-    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: rec.capturing)
+    monkeypatch.setattr(torch._C, "_cuda_isCurrentStreamCapturing", lambda: rec.capturing)
     monkeypatch.setattr(B.Context, "workspace_init", lambda *a: None)
-    monkeypatch.setattr(B.Context, "cache_fork_paged", lambda self, *a: rec.fork(self, *a))
+    monkeypatch.setattr(B.calls, "mtla_cache_fork_paged", rec.fork)
     return rec
 
 
@@ -84,11 +87,11 @@ def test_a_fork_whose_launch_fails_changes_nothing(launches, n_pages):
     grow(s, [35, 5, 0, 30])                                   # pages 2, 1, 0, 1
     for src in ([0, 0, 1, 3], [3, 1, 0], [0, 1, 2, 3], [2, 2, 2, 2], [0]):
         was = state(s)
-        launches.fail = RuntimeError("launch")
-        with pytest.raises(RuntimeError, match="launch"):
-            s.fork(src)
-        assert state(s) == was
-        launches.fail = None
+        for launches.fail in (B.MTLA_ERR_HIP, TypeError("an argument")):
+            with pytest.raises((B.MtlaError, TypeError)):
+                s.fork(src)
+            assert state(s) == was
+        launches.fail = 0
         s.fork(src)
         state(s)
         expected = [was[1][b] for b in src] + [0] * (4 - len(src))
