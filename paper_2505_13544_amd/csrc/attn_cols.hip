@@ -545,7 +545,12 @@ hipError_t launch_cols(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   using C = ColCfg<R, DR, NHT>;
   constexpr bool AH = NHT == 2;  // one workgroup per CU: nothing else fills the waits of a tile step (no gain with two)
   const size_t smem = (AH ? 2 : 1) * C::park_bytes + C::s_bytes + (size_t)(2 * a.batch + 1 + kBlock) * sizeof(int);
-  if (smem > 64 * 1024) return hipErrorInvalidValue;
+  // the lists of a large batch beside the slices of two head tiles at r = 512: more than 64 KB from 1408 sequences on
+  if (smem > 64 * 1024) {
+    static DeviceSet lds_allowed;
+    const hipError_t e = allow_lds(&attn_cols_kernel<R, DR, NHT, NS, OCC, SH, PG, AH>, 160 * 1024, lds_allowed);
+    if (e != hipSuccess) return e;
+  }
   launch_timed(attn_cols_kernel<R, DR, NHT, NS, OCC, SH, PG, AH>, dim3(a.n_persistent), dim3(kBlock), smem, st, ev, a);
   return hipGetLastError();
 }

@@ -82,6 +82,16 @@ def test_balanced_schedule_many_short_sequences(n_heads):
     H.run_decode_parity(wl, prefix_lens=plen, decode_schedule=2)
 
 
+def test_balanced_schedule_lists_beside_two_head_tiles():
+    # 1500 sequences, 17 heads, r = 512: the lists of the batch and the slices of two tiles of both head tiles are more than
+    # 64 KB of LDS together
+    B = 1500
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="bal_lds", batch=B, d_model=64, n_heads=17, d_head=32, r=512, d_rope=64, stride=4,
+                                           prefix=(0, 70), steps=1, seed=19)
+    plen = np.random.default_rng(19).integers(0, 70, size=B).astype(np.int32)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_schedule=2, seqs_to_check=list(range(0, B, 83)))
+
+
 @pytest.mark.parametrize("schedule", [1, 2])
 @pytest.mark.parametrize("seed", range(8))
 def test_seeded_random_shapes_both_schedules(seed, schedule):
