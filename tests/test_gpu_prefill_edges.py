@@ -60,3 +60,35 @@ def test_plain_form_paired_blocks_and_large_products():
     # their largest tiles, with most sequences' rows left out
     lens = [640, 639, 513, 1] + [5] * 43 + [130]
     _check(lens, 6, 64, 256, 32, 2, False, which=(0, 1, 2, 3, 47))
+
+
+@pytest.mark.parametrize("bits", [14.5, 16.0])
+@pytest.mark.parametrize("latent", [False, True])
+def test_own_column_far_above_the_others(latent, bits):
+    # An even row's own key and the odd rows' keys (stride 2: the final ones) have opposite signs in one element of the RoPE
+    # part, so the row's own logit is `bits` (in units of log2) above every other column's: the other weights are subnormal
+    # fp16 numbers, and the 1536 and more of a late row are 6.6e-2 (14.5) and 2.3e-2 (16) of the normaliser.  Were they dropped
+    # from it, or from the sum of the values (the latents have a mean of one, so that it is no sum of independent ones), the
+    # outputs would be off by that share.
+    T, stride = 4096, 2
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="pf_own", batch=1, d_model=64, n_heads=2, d_head=64, r=64, d_rope=32, stride=stride,
+                                           prefix=T, steps=0, seed=977)
+    wts = W.make_weights(wl)
+    toks, _ = _prefill_inputs(wl, wts, T)
+    t, scale = toks[0], O.softmax_scale(wl.d_head)
+    c, q, kr, q_rope = H.bf16_round(t.c + 1.0), 0.0625 * t.q, np.array(t.kr), np.zeros_like(t.q_rope)
+    kr[0::2, 0], kr[1::2, 0] = 1.0, -1.0
+    q_rope[..., 0] = H.bf16_round(bits * np.log(2.0) / (2 * scale))
+    d = {f: H.to_device(x[None].astype(np.float32), wl.dtype) for f, x in (("q", q), ("q_rope", q_rope), ("c", c), ("kr", kr))}
+    _, w, out, lat = _gpu_prefill(wl, wts, d, T, np.array([T], np.int32), want_latent=latent)
+    late = np.arange(3072, T, 2)                             # of the late rows those whose own value is largest
+    weight = w[0].double().cpu().numpy()
+    rows = [0, 2, 64, 126, 128, 1022, 1024, 2050] + sorted(late[np.argsort(weight[late])[-8:]].tolist())
+    o_ref, ol_ref, _, Cp = O.prefill_attn(q, q_rope, c, kr, wts.w_uk, wts.w_uv, stride, scale, hyp_A=wts.hyp_A, hyp_a=None,
+                                          hyp_G=wts.hyp_G, rows=rows)
+    others = np.einsum("n,hnk->hk", Cp[1:T:2].mean(0), wts.w_uv)
+    for value in (o_ref[-8:], others):                       # what dropping them would cost shows
+        assert np.abs(value).max() * 1536 * 2.0 ** -bits > 2 * H.TOL["bf16"]
+    assert H.max_err(out[0, rows], o_ref) <= H.TOL["bf16"]
+    if latent:
+        H.check_latent(np.abs(lat[0, rows].cpu().numpy().astype(np.float64) - ol_ref), Cp, "bf16", "own column")
