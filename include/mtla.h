@@ -95,8 +95,8 @@ size_t mtla_cache_kr_bytes(const mtla_ctx* ctx);
 size_t mtla_page_table_bytes(const mtla_ctx* ctx); /* paged storage: int32 [max_batch, ceil(max_slots / page_slots)], else 0 */
 size_t mtla_tail_bytes(const mtla_ctx* ctx);
 size_t mtla_workspace_bytes(const mtla_ctx* ctx);
-/* Scratch for one mtla_prefill_attn call of this batch and length (absorbed
- * queries and the partial slot states C_hat' for all T rows). */
+/* Scratch for one mtla_prefill_attn call of this batch and length (keys and
+ * values or absorbed queries, and the partial slot states C_hat', of all T rows). */
 size_t mtla_prefill_workspace_bytes(const mtla_ctx* ctx, int32_t batch, int32_t T);
 
 /* Clears the workspace header (device status word).  Call once after
@@ -220,10 +220,11 @@ mtla_status mtla_decode_attn(mtla_ctx* ctx, const void* q, const void* q_rope, c
  * mtla_cache_append(n_new = NULL, n_new_max = 1, hyper-network weights) does,
  * then the step's query attends over the updated cache exactly as
  * mtla_decode_attn does.  Results are identical to the two calls in that order;
- * with bf16 storage the append and the absorption, which do not depend on each
- * other, share one kernel launch.  Arguments, layouts, ownership and errors are
- * those of the two calls (a sequence that is full is left untouched, raises
- * MTLA_ERR_CAPACITY in the workspace header, and is attended as it stands).
+ * the append and the absorption, which do not depend on each other, share one
+ * kernel launch (MTLA_F32, and MTLA_BF16 with d_head 32, 64 or 128).  Arguments,
+ * layouts, ownership and errors are those of the two calls (a sequence that is
+ * full is left untouched, raises MTLA_ERR_CAPACITY in the workspace header, and
+ * is attended as it stands).
  */
 mtla_status mtla_decode_step(mtla_ctx* ctx, void* cache_c, void* cache_kr, float* tail_c,
                              int32_t* seq_len, const void* c_new, const void* kr_new,
@@ -334,9 +335,12 @@ mtla_status mtla_prefill_step_paged(mtla_ctx* ctx, void* cache_c, void* cache_kr
  *   cache_c, cache_kr   device, the pool, read and written
  *   src_table, src_tail_c, src_seq_len   device, read only; dst_*: written for sequences 0 .. batch-1,
  *                       other arrays than the sources (reorder into a second set and swap)
- *   src_index, fresh_pages   device int32 [batch]; an index outside [0, max_batch) leaves the destination
+ *   src_index, fresh_pages   int32 [batch]; an index outside [0, max_batch) leaves the destination
  *                       untouched, a page outside [0, n_pages) is clamped; both raise MTLA_ERR_INVALID_ARG
- *                       in the workspace header (mtla_device_status)
+ *                       in the workspace header (mtla_device_status).  Device memory, or pinned host memory
+ *                       (hipHostMalloc): the kernel reads the two arrays where they are, when it runs.  Host
+ *                       memory therefore has to stand and keep its values until the kernel has run (an event
+ *                       recorded behind the call tells), and in a captured call until the last replay has.
  */
 mtla_status mtla_cache_fork_paged(mtla_ctx* ctx, void* cache_c, void* cache_kr, const int32_t* src_table,
                                   const float* src_tail_c, const int32_t* src_seq_len, const int32_t* src_index,
@@ -439,16 +443,15 @@ mtla_status mtla_set_shared_prefix(mtla_ctx* ctx, const int32_t* prefix_owner /*
  *   out_latent device float [batch, T, n_heads, r] or NULL
  *   prefill_workspace device, mtla_prefill_workspace_bytes(ctx, batch, T) bytes
  *
- * With bf16 storage and d_head in {64,128} the keys and values are formed
- * explicitly (k = C_hat' W_K^(h), v = C_hat' W_V^(h), Eq. (with-rope) before
- * absorption), which is the cheaper form for many rows per head; out_latent,
- * if asked for, comes from the same weights with the partial states C_hat' as
- * further values (r in {64,128,256,512}).  Other shapes and MTLA_F32 take the
- * absorbed form of Eq. (obsorb).  Both give the same out and
- * out_latent within the bf16 tolerance.  batch * T may not exceed 2^24;
- * MTLA_F32 storage (and bf16 shapes outside r in {128,256,512}, d_head in
- * {64,128}) is limited to batch * T <= 65535 and returns MTLA_ERR_UNSUPPORTED
- * beyond.
+ * The keys and values are formed explicitly (k = C_hat' W_K^(h), v = C_hat' W_V^(h),
+ * Eq. (with-rope) before absorption), which is the cheaper form for many rows per
+ * head: MTLA_BF16 with d_head in {64,128} (fp16 inside), MTLA_F32 with d_head in
+ * {32,64,128} (fp32 throughout, on the fp32 matrix instructions).  out_latent, if
+ * asked for, comes from the same weights with the partial states C_hat' as further
+ * values.  Other shapes take the absorbed form of Eq. (obsorb).  Both give the same
+ * out and out_latent within the storage type's tolerance.  batch * T may not exceed
+ * 2^24; MTLA_F32 storage, and MTLA_BF16 at other d_head, is limited to batch * T <=
+ * 65535 and returns MTLA_ERR_UNSUPPORTED beyond.
  */
 mtla_status mtla_prefill_attn(mtla_ctx* ctx, const void* q, const void* q_rope, const void* c,
                               const void* kr, const float* w, const int32_t* seq_lens,
