@@ -35,7 +35,9 @@ def test_ragged_small_batches_all_strides(dtype, stride):
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32)
 
 
-@pytest.mark.parametrize("r,d_rope,n_heads,d_head", [(64, 64, 3, 64), (256, 64, 12, 96), (512, 32, 9, 128)])
+# (more than 32 heads: the vector kernel)
+@pytest.mark.parametrize("r,d_rope,n_heads,d_head", [(64, 64, 3, 64), (256, 64, 12, 96), (512, 32, 9, 128), (128, 32, 33, 32),
+                                                     (512, 64, 64, 64)])
 def test_other_shapes(r, d_rope, n_heads, d_head):
     wl = W.WORKLOADS["speech_bf16"].scaled(name=f"shape_r{r}", batch=3, d_model=128, n_heads=n_heads,
                                            d_head=d_head, r=r, d_rope=d_rope, stride=2, prefix=(10, 150),
@@ -356,7 +358,7 @@ def test_state_copy_resumes_bit_identically():
 @pytest.mark.parametrize("dtype,stride,shape", [("bf16", 2, (8, 64, 256, 32)), ("bf16", 3, (6, 32, 128, 64)),
                                                ("bf16", 1, (16, 128, 512, 64)), ("f32", 2, (4, 64, 64, 32))])
 def test_decode_step_equals_append_then_attend(dtype, stride, shape):
-    """mtla_decode_step (append and absorption in one launch for bf16) against the two separate
+    """mtla_decode_step (append and absorption in one launch) against the two separate
     calls on the same inputs: caches, lengths and outputs bit for bit; and against the oracle."""
     nh, dh, r, dr = shape
     wl = W.WORKLOADS["speech_bf16"].scaled(name="fused", dtype=dtype, batch=5, d_model=nh * dh, n_heads=nh,

@@ -178,8 +178,8 @@ def test_chunked_prefill_seeded_random_shapes(case):
 
 @pytest.mark.parametrize("stride", [5, 8])
 def test_chunked_prefill_beyond_stride_4_keeps_the_documented_bound(stride):
-    # the header gives 2e-2 up to s = 4 and 2e-2 * s / 4 beyond (a cache row is the bf16 rounding of a sum of s
-    # weighted latents): the shapes of the stride tests above, at strides the random shapes leave out
+    # the header gives 2e-2 * s / 3 from s = 4 on (a cache row is the bf16 rounding of a sum of s weighted latents); these
+    # shapes, those of the stride tests above at strides the random shapes leave out, keep 2e-2 * s / 4
     wl = W.WORKLOADS["speech_bf16"].scaled(name=f"pf_chunk_s{stride}", batch=3, d_model=96, n_heads=6, d_head=64, r=128,
                                            d_rope=32, stride=stride, prefix=230, steps=0, seed=41 + stride)
     worst = _feed(wl, [230, 171, 20], [37, 1, 64, 128], tol=H.TOL["bf16"] * stride / 4)
