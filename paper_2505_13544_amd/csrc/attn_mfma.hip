@@ -35,7 +35,9 @@
 //             everything whose address does not depend on the sequence length,
 //             hardware bf16 conversion and exp2, a fixed softmax reference per
 //             wavefront instead of a running maximum (no accumulator rescaling and no
-//             cross-lane traffic on the hot path), and a single-pass merge.
+//             cross-lane traffic on the hot path), and a single-pass merge.  Up to 16
+//             heads with short chunks have a kernel of their own (attn_split_kernel), in
+//             which the wavefronts share their rows and weights through LDS instead.
 //   balanced  one persistent workgroup per compute unit.  The tiles of all
 //             sequences form one flat list that is cut into equal ranges, so
 //             ragged batches keep every compute unit streaming until the end; a

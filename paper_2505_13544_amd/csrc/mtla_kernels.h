@@ -51,8 +51,8 @@ struct AppendArgs {
 // Row source of the attention kernels.  Decode reads the cache; the prefill
 // fallback reads the per-row slot states C_hat' and the uncompressed keys.
 struct AttnArgs {
-  const void* qcat;      // [rows, n_heads, r + d_rope], pre-scaled to the log2 domain; fp32 for
-                         // the vector kernel, two bf16 planes (hi, lo) for the matrix-core kernel
+  const void* qcat;      // [rows, n_heads, r + d_rope], pre-scaled to the log2 domain; fp32 for the
+                         // vector kernel and fp32 storage, two bf16 planes (hi, lo) for bf16 matrix instructions
   size_t q_plane;        // elements between the two bf16 planes
   const void* lat;       // decode: cache_c [B, max_slots, r]; prefill: C_hat' [B, T, r]
   const void* key;       // decode: cache_kr;                  prefill: kr [B, T, d_rope]
@@ -100,7 +100,7 @@ struct AbsorbArgs {
   const void* w_uk;    // [n_heads, r, d_head]
   void* qcat;          // [rows, n_heads, r + d_rope], fp32 or bf16 (out_bf16)
   int rows, n_heads, d_head, r, d_rope;
-  int out_bf16;        // 1: bf16 hi/lo operand planes for the matrix-core kernel; 0: fp32 (vector kernel)
+  int out_bf16;        // 1: bf16 hi/lo operand planes for the bf16 matrix instructions; 0: fp32 (vector kernel, fp32 storage)
   int q_f32;           // matrix-core absorb only: q and q_rope hold fp32 (unrounded) values
   size_t plane;        // out_bf16: elements between the hi plane and the lo plane
   float scale_log2;    // softmax_scale * log2(e)

@@ -20,13 +20,13 @@
 // rounding to half.
 //
 // Two kernels behind the front launch (prefill_front.hip: partial states, RoPE keys and weights as fp16):
-//   gemm_nt_kernel        K = C_hat' W_K, V = C_hat' W_V for all T rows: a plain MFMA GEMM, 256 x 128
-//                         tile, operands streamed from memory straight into LDS (also the projections
-//                         of the whole-layer prefill, with rotation / scaling on the way out)
-//   attn_explicit_kernel  one workgroup per pair of 128-row blocks of a (head, sequence); keys, RoPE
-//                         keys and values of 32 columns at a time stream from memory straight into
-//                         LDS and are shared by the four wavefronts (32 query rows each, queries in
-//                         registers)
+//   gemm_nt_kernel        K = C_hat' W_K, V = C_hat' W_V for all T rows: a plain MFMA GEMM, its tile sized
+//                         to the rows there are, operands streamed from memory straight into LDS (also the
+//                         projections of the whole-layer prefill, with rotation / scaling on the way out)
+//   attn_explicit_kernel  one workgroup per pair of 128-row blocks of a (head, sequence), or per block where
+//                         pairs would leave units without work; keys, RoPE keys and values of 32 columns at a
+//                         time stream from memory straight into LDS and are shared by the four wavefronts
+//                         (32 query rows each, queries in registers)
 #include <type_traits>
 
 #include "lds_stream.h"
@@ -260,7 +260,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
 // ---- attention over explicit keys and values -------------------------------------------------
 //
 // A tile is 32 columns: their keys [32][d_h] (swz_rows16), RoPE keys [32][d_R] (swz_rows16) and
-// values [32][d_h] (swz_tr), fp16, fetched three tiles ahead through four LDS buffers.
+// values [32][d_h] (swz_tr), fp16; one pair of tiles is fetched while the pair before is multiplied (four LDS buffers).
 template <int DH, int DR>
 struct TileGeom {
   static constexpr int BN = 32, VC = DH / 8, RC = DR / 8;  // 16-byte pieces per key / value row, per RoPE key row
@@ -278,7 +278,10 @@ struct TileGeom {
 // one, it was 128 / 32 - (128 / s) / 32 tiles more (two of the 36 a block walks on average at 4096 rows and s = 2).
 //
 // NW wavefronts of 32 query rows each per workgroup.  NW = 4 is what the launcher uses: two workgroups per CU, whose
-// wavefronts drift apart so that one multiplies while the other does softmax arithmetic.
+// wavefronts drift apart so that one multiplies while the other does softmax arithmetic.  What bounds it is the chain
+// of a pair of tiles (operand reads, 80 matrix instructions, the arithmetic of the weights) with two wavefronts per SIMD
+// to overlap: matrix pipes busy 40 %, no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
+// us with the own rows as masked tiles and one tile per step, now 414 (830 TFLOP/s).
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
 template <int DH, int DR, int NW, bool CONT, bool LAYER>

@@ -25,9 +25,7 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = kBlock / kWave;
 
-
-
-// absorb, bf16 on the matrix cores: grid = (r/64 + 1, n_heads, row groups), body in absorb_mfma.h
+// absorb, bf16 on the matrix cores: grid = (absorb_col_blocks(r) + 1, n_heads, row groups), body in absorb_mfma.h
 template <int KK, bool QF32>
 __global__ __launch_bounds__(kBlock) void absorb_mfma_kernel(AbsorbArgs a) {
   absorb_mfma_block<KK, QF32>(a, blockIdx.x, blockIdx.y, blockIdx.z);
