@@ -35,17 +35,17 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # runs of this script, each counter scaled by its reading for a plain 256 MiB device copy
 # (profiles/decode_attention_hbm_traffic.md), as a line in the launch's algorithmic bytes (the live cache
 # rows): traffic = fixed + slope * algorithmic.  The headline workload was measured at two step counts
-# (20 and 256 steps: 7.288 MB for 4.772 MB, 7.908 MB for 5.307 MB), which fixes both numbers -- the fixed
-# part is the split partials, the query operand and first tiles requested before the length is known;
-# the other workloads were measured once, so their line goes through the origin.
-MEASURED_TRAFFIC_LINE = {"speech_bf16": (1.776e6, 1.155),
-                         "ragged_bf16": (0.0, (357175.6 + 11556.9) * 1024 / 339.5e6),
-                         "long_bf16": (0.0, (78746.6 + 8062.6) * 1024 / 75.5e6),
-                         "speech_b1024_bf16": (0.0, (306855.4 + 4164.1) * 1024 / 304.6e6)}
+# (20 and 256 steps: 7.245 MB for 4.772 MB, 8.092 MB for 5.307 MB), which fixes both numbers: an interpolation
+# between the two, since the traffic grows by whole chunks of 64 slots; the other workloads were measured once, so
+# their line goes through the origin.
+MEASURED_TRAFFIC_LINE = {"speech_bf16": (-0.313e6, 1.584),
+                         "ragged_bf16": (0.0, (357206.0 + 11557.0) * 1024 / 339.5e6),
+                         "long_bf16": (0.0, (78732.8 + 8062.6) * 1024 / 75.5e6),
+                         "speech_b1024_bf16": (0.0, (306855.8 + 4164.1) * 1024 / 304.6e6)}
 # the same for the prefill attention kernel (profiles/prefill_hbm_traffic.md); every launch of a workload
 # is the same work, so the step count does not matter
-MEASURED_PREFILL_TRAFFIC_BYTES = {"prefill_s2": 2.0 * 277890.8 * 1024 + 262147.9 * 1024,
-                                  "prefill_s4": 2.0 * 261745.8 * 1024 + 262151.1 * 1024}
+MEASURED_PREFILL_TRAFFIC_BYTES = {"prefill_s2": 2.0 * 348713.0 * 1024 + 262204.4 * 1024,
+                                  "prefill_s4": 2.0 * 294004.1 * 1024 + 262164.4 * 1024}
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix rate, published
 
 
