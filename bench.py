@@ -13,7 +13,7 @@ pieces through mtla_prefill_step), --layer (mtla_layer_decode_step, or mtla_laye
 
 Prints ONE JSON line.  `value` is
 tokens/s with all inputs resident in HBM, the K steps replayed as one HIP
-graph; the eager (one ctypes call per library entry) rate is reported beside
+graph; the eager rate (one call from Python per library entry) is reported beside
 it.  `roofline` refers to the dominant kernel (the pass over the cache slots),
 timed with HIP event pairs recorded by the library around each launch.
 """
