@@ -64,7 +64,7 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, u
 }
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {  // until at most N of this wavefront's loads are in flight
-  static_assert(N >= 0 && N <= 15, "vmcnt field");
+  static_assert(N >= 0 && N <= 63, "vmcnt field");
   if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }

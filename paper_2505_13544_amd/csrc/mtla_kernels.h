@@ -181,9 +181,11 @@ struct GemmArgs {
   const float2* rope_cs = nullptr;  // epi 1, 2: [M, d_rope / 2] (cos, sin) of every row's angles
   int d_rope = 0;
   GemmRows rows;
-  // set by the launcher; xcds: the XCDs that the row blocks are dealt to (8, or 1 for few of them)
+  // set by the launcher; xcds: the XCDs that the row blocks are dealt to (8, or 1 for few of them); stream_out: results that the
+  // caches would not hold are stored past them
   int col_blocks = 0;
   unsigned row_blocks = 0, xcds = 1;
+  int stream_out = 0;
 };
 
 struct RopeTableArgs {
@@ -375,6 +377,9 @@ hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const 
 bool gemm_nt_supported(const GemmArgs& a);
 hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st);
+// the same products as streams of 256 x 256 tiles (launch_gemm_nt picks)
+bool gemm_wide_supported(const GemmArgs& a);
+hipError_t launch_gemm_wide(const GemmArgs& a, hipStream_t st);
 hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st);
 bool combine_mfma_supported(const CombineArgs& a);  // bf16 storage; r, d_head and alignment fit
 hipError_t launch_combine_mfma(const CombineArgs& a, hipStream_t st);

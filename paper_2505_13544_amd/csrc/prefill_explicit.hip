@@ -27,6 +27,7 @@
 //                         pairs would leave units without work; keys, RoPE keys and values of 32 columns at a
 //                         time stream from memory straight into LDS and are shared by the four wavefronts
 //                         (32 query rows each, queries in registers)
+#include <cmath>
 #include <type_traits>
 
 #include "lds_stream.h"
@@ -51,9 +52,9 @@ namespace {
 // left out: the row blocks are those of the sequences' rows in use, one after the other, so what is left over at the
 // end of the launch returns at once.  Where the caller wants zeros in such rows the blocks are the matrix's own.
 //
-// Tiles: 256 x 256 (eight wavefronts, one workgroup per CU: 1.0 PFLOP/s at K = 2048) where there are rows and columns
-// enough, smaller ones where they would leave units without work (launch_gemm picks by the work a unit gets).  129 rows
-// x 512 columns, K = 512: 17 us in two 256 x 256 tiles, 6 us in 64 x 64 ones.
+// Tiles: large products go to the streams of gemm_wide.hip; here 64 x 64 to 128 x 128 for the small ones (129 rows x 512 columns,
+// K = 512: 17 us in two 256 x 256 tiles, 6 us in 64 x 64 ones), and 256 x 256 (eight wavefronts, one workgroup per CU)
+// where a contraction that is no multiple of 64 keeps a large one out of the streams.
 template <int BM, int BN>
 struct GemmGeom {
   static constexpr int NWV = BM * BN >= 65536 ? 8 : 4, NT = 64 * NWV, BK = 32;
@@ -727,22 +728,36 @@ static int gemm_col_blocks(const GemmArgs& a, int bn) {
   return n;
 }
 
-// The tile that gives the unit with the most work the least of it, and that work in units of a 256 x 256 tile's area: the
-// area of a tile weighted by how fast a unit gets through it (smaller tiles move more from L2 per product: 32768 rows x
-// 4096 columns at K = 512 took 198, 202, 232 and 368 us).  With ragged rows the number of jobs is not known here:
-// three quarters of the most, and half a round more, on average, than they fill.
+// The tile that gives the unit with the most work the least of it, and that work in units of a 256 x 256 tile of this kernel
+// (which took 24 us at K = 512 and 67 at K = 2048 with one tile a unit): the area of a tile weighted by how fast a unit gets
+// through it (smaller tiles move more from L2 per product: 32768 rows x 4096 columns at K = 512 took 198, 202, 232 and 368
+// us), and what filling and emptying a unit costs.  kWide: the streams of gemm_wide.hip, whose last round is cut smaller
+// (one round of 256, 128 and 64 jobs: 60, 35 and 23 us at K = 2048, 22, 12.5 and 9 at K = 512; below 40 jobs or so
+// the 64 x 64 tiles are as fast or faster).  With ragged rows the number of row blocks is not known here: three quarters of the
+// most, and half a block more per sequence, or half a round where blocks may hold rows of several.
+enum { kWide = 4 };
 static float gemm_cost(const GemmArgs& a, int& pick) {
   static constexpr struct { int bm, bn; float rate; } kTiles[] = {{256, 256, 1.f}, {256, 128, 0.92f}, {128, 128, 0.85f}, {64, 64, 0.54f}};
   const bool ragged = a.rows.n_new || a.rows.pos0;
+  const int n_seq = ragged ? a.M / (a.rows.past + a.rows.T) : 1;
   float best = 0.f;
   pick = 0;
   for (int i = 0; i < 4; ++i) {
     const long long jobs = (long long)gemm_col_blocks(a, kTiles[i].bn) * ((a.M + kTiles[i].bm - 1) / kTiles[i].bm);
     const float rounds = ragged && jobs > 256 ? 0.75f * (float)jobs / 256.f + 0.5f : (float)((jobs + 255) / 256);
-    const float cost = rounds * (float)(kTiles[i].bm * kTiles[i].bn) / kTiles[i].rate / 65536.f;
+    const float cost = rounds * (float)(kTiles[i].bm * kTiles[i].bn) / kTiles[i].rate / 65536.f + (i ? 0.1f : 0.f);
     if (i == 0 || cost < best) {
       best = cost;
       pick = i;
+    }
+  }
+  if (gemm_wide_supported(a)) {
+    const float blocks = ragged ? 0.75f * (float)a.M / 256.f + 0.5f * (float)n_seq : (float)((a.M + 255) / 256);
+    const float rounds = blocks * (float)gemm_col_blocks(a, 256) / 256.f, whole = floorf(rounds), left = rounds - whole;
+    const float cost = 0.9f * whole + (left == 0.f ? 0.f : left <= 0.25f ? 0.33f : left <= 0.5f ? 0.53f : 0.9f);
+    if (cost < best) {
+      best = cost;
+      pick = kWide;
     }
   }
   return best;
@@ -771,6 +786,7 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
       return e != hipSuccess ? e : launch_gemm_nt(one, st);
     }
   }
+  if (pick == kWide) return launch_gemm_wide(a, st);
   static constexpr int kBM[] = {256, 256, 128, 64}, kBN[] = {256, 128, 128, 64};
   a.col_blocks = gemm_col_blocks(a, kBN[pick]);
   unsigned gy = (unsigned)((a.M + kBM[pick] - 1) / kBM[pick]);

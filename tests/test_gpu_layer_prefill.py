@@ -97,6 +97,16 @@ def test_layer_prefill_whole_prompt(stride, n_heads, d_head, r, d_rope, d_model)
     print(f"layer prefill, stride {stride}: max abs err {worst:.2e}")
 
 
+def test_layer_prefill_streamed_products():
+    # enough rows and columns for the streamed 256 x 256 tiles in the projections (every way out) and in W_O, whose rows past a
+    # sequence's length are zeros inside a tile, at a tile's end and over whole tiles;
+    # the last column blocks of W_O have 64 columns
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="lp_wide", batch=6, d_model=1088, n_heads=16, d_head=64, r=256, d_rope=32, stride=2,
+                                           prefix=600, steps=0, seed=87)
+    worst = _feed(wl, [600, 257, 1, 599, 256, 340], [600])
+    print(f"layer prefill, streamed products: max abs err {worst:.2e}")
+
+
 @pytest.mark.parametrize("stride", [2, 3])
 def test_layer_prefill_in_pieces_with_layer_steps_between(stride):
     # pieces that end inside a slot, single-token layer steps in between, sequences running out in different pieces

@@ -62,6 +62,16 @@ def test_plain_form_paired_blocks_and_large_products():
     _check(lens, 6, 64, 256, 32, 2, False, which=(0, 1, 2, 3, 47))
 
 
+@pytest.mark.parametrize("n_heads,d_head,r,stride,lens,which", [
+    (12, 64, 512, 2, (1400, 1399, 257, 1), (1, 2, 3)),       # one round of tiles, cut into halves
+    (32, 128, 128, 3, (900, 899, 513, 1), (2, 3)),           # whole rounds and a rest; the shortest contraction
+    (18, 64, 128, 2, (769, 768, 767, 640), (0, 3)),          # columns that end inside a tile, at its half
+    (8, 64, 256, 2, (600,) * 40 + (257, 1) * 13, (39, 40, 65)),  # more sequences than lanes
+])
+def test_streamed_products(n_heads, d_head, r, stride, lens, which):
+    _check(lens, n_heads, d_head, r, 32, stride, False, which=which)
+
+
 @pytest.mark.parametrize("bits", [14.5, 16.0])
 @pytest.mark.parametrize("latent", [False, True])
 def test_own_column_far_above_the_others(latent, bits):
