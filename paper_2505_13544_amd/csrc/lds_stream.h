@@ -68,15 +68,6 @@ __device__ __forceinline__ void wait_loads_but() {  // until at most N of this w
   if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
-__device__ __forceinline__ void wait_loads_but(int n) {  // wavefront-uniform n, 0 .. 15
-  switch (n) {
-#define MTLA_W(N_) case N_: wait_loads_but<N_>(); break;
-    MTLA_W(1) MTLA_W(2) MTLA_W(3) MTLA_W(4) MTLA_W(5) MTLA_W(6) MTLA_W(7) MTLA_W(8) MTLA_W(9) MTLA_W(10)
-    MTLA_W(11) MTLA_W(12) MTLA_W(13) MTLA_W(14) MTLA_W(15)
-#undef MTLA_W
-    default: wait_loads_but<0>(); break;
-  }
-}
 // workgroup barrier without a fence: callers order their own memory traffic around it
 __device__ __forceinline__ void barrier_only() {
   asm volatile("" ::: "memory");

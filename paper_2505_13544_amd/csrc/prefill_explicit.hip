@@ -60,10 +60,14 @@ struct GemmGeom {
   static constexpr int NWV = BM * BN >= 65536 ? 8 : 4, NT = 64 * NWV, BK = 32;
   static constexpr int WCOLS = BN >= 128 ? BN / 64 : 2, WN = BN / WCOLS, WROWS = NWV / WCOLS, WM = BM / WROWS;
   static constexpr int W_BYTES = BN * BK * 2, A_BYTES = BM * BK * 2, STAGE = W_BYTES + A_BYTES;
-  static constexpr int NBUF = BM >= 256 ? 3 : (BM == 128 ? 4 : 6), PF = NBUF - 1;
+  // A small tile's stage is a chain of waits and reads for a few products: two are done behind one barrier, with constant
+  // waits.  64 x 64, K = 512 and 2048, a tile a unit or less: 5.8 and 15.6 us, now 4.8 and 10.5.  More buffers take a third
+  // workgroup from the unit and gain nothing between other kernels, where the operands come from beyond the L2.
+  static constexpr int SPB = BM >= 256 ? 1 : 2;  // stages per barrier
+  static constexpr int NBUF = BM >= 256 ? 3 : (BM == 128 ? 4 : 6), PF = NBUF - SPB;
   static constexpr int NLW = W_BYTES / 1024 / NWV, NLA = A_BYTES / 1024 / NWV, LOADS = NLW + NLA;  // loads per wavefront and stage
   static constexpr int PER_CU = BM == 256 && BN == 256 ? 1 : 2;
-  static_assert(LOADS * (PF - 1) <= 15 && NLW >= 1 && NLA >= 1, "wait counts");
+  static_assert(PF >= SPB && 2 * LOADS * SPB <= 63 && NLW >= 1 && NLA >= 1, "buffers, wait counts");
 };
 
 template <bool BF16, int BM, int BN>
@@ -180,11 +184,8 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
 #pragma unroll
   for (int st = 0; st < PF; ++st)
     if (st < n_stages) issue(st);
-  for (int st = 0; st < n_stages; ++st) {
-    const int after = n_stages - 1 - st < PF - 1 ? n_stages - 1 - st : PF - 1;
-    wait_loads_but(LOADS * after);
-    barrier_only();
-    if (st + PF < n_stages) issue(st + PF);  // into the buffer stage st-1 was read from
+  constexpr int SPB = G::SPB;
+  auto multiply = [&](int st) {
     const unsigned char* wb = lds + (st % NBUF) * STAGE + wn * 64 + frag_off;
     const unsigned char* ab = lds + (st % NBUF) * STAGE + W_BYTES + wm * 64 + frag_off;
     u32x4_t wf[IN], af[JM];
@@ -203,6 +204,26 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
           acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wf[i]),
                                                              __builtin_bit_cast(f16x8_t, af[j]), acc[j][i], 0, 0, 0);
       }
+  };
+  int st = 0;
+  for (; st + PF <= n_stages; st += SPB) {  // stages below st + PF have been asked for
+    wait_loads_but<LOADS * (PF - SPB)>();
+    barrier_only();
+#pragma unroll
+    for (int i = 0; i < SPB; ++i)
+      if (st + PF + i < n_stages) issue(st + PF + i);  // into the buffers the stages before were read from
+#pragma unroll
+    for (int i = 0; i < SPB; ++i) multiply(st + i);
+  }
+  for (; st < n_stages; st += SPB) {        // all have
+    const int left = n_stages - st;
+    if (left >= 3 * SPB) wait_loads_but<LOADS * 2 * SPB>();
+    else if (left >= 2 * SPB) wait_loads_but<LOADS * SPB>();
+    else wait_loads_but<0>();
+    barrier_only();
+#pragma unroll
+    for (int i = 0; i < SPB; ++i)
+      if (st + i < n_stages) multiply(st + i);
   }
 
   // ---- the tile leaves through LDS, RP rows at a time (as many as the stage buffers hold), so that
@@ -728,33 +749,41 @@ static int gemm_col_blocks(const GemmArgs& a, int bn) {
   return n;
 }
 
-// The tile that gives the unit with the most work the least of it, and that work in units of a 256 x 256 tile of this kernel
-// (which took 24 us at K = 512 and 67 at K = 2048 with one tile a unit): the area of a tile weighted by how fast a unit gets
-// through it (smaller tiles move more from L2 per product: 32768 rows x 4096 columns at K = 512 took 198, 202, 232 and 368
-// us), and what filling and emptying a unit costs.  kWide: the streams of gemm_wide.hip, whose last round is cut smaller
-// (one round of 256, 128 and 64 jobs: 60, 35 and 23 us at K = 2048, 22, 12.5 and 9 at K = 512; below 40 jobs or so
-// the 64 x 64 tiles are as fast or faster).  With ragged rows the number of row blocks is not known here: three quarters of the
-// most, and half a block more per sequence, or half a round where blocks may hold rows of several.
+// The tiles that take the least time, and that time (us, as measured on products of rows in use x 1024 to 4096 columns): a round is a
+// tile for each of the 256 units, `base` fills and empties them.  64 x 64 one, two, three rounds: 4.9, 7.0, 9.8 us at K = 512 and
+// 12, 20, 28 at 2048; 128 x 128 one and two: 9, 14.5 and 25, 44; the streams of gemm_wide.hip (kWide), whose last round is cut
+// into halves or quarters of a tile where that fills it: a quarter round 10 and 24, half a one 13.5 and 35, one 22 and 60, eight
+// 136 and 480.  With ragged rows the number of row blocks is not known here: three quarters of the most, and half a block more per
+// sequence, or half a round where blocks may hold rows of several.
 enum { kWide = 4 };
 static float gemm_cost(const GemmArgs& a, int& pick) {
-  static constexpr struct { int bm, bn; float rate; } kTiles[] = {{256, 256, 1.f}, {256, 128, 0.92f}, {128, 128, 0.85f}, {64, 64, 0.54f}};
+  static constexpr struct { int bm, bn; float base, round, k; } kTiles[] = {
+      {256, 256, 5.f, 4.7f, 0.028f}, {256, 128, 5.f, 2.5f, 0.0152f}, {128, 128, 3.2f, 0.5f, 0.0112f}, {64, 64, 2.2f, 0.5f, 0.004f}};
   const bool ragged = a.rows.n_new || a.rows.pos0;
-  const int n_seq = ragged ? a.M / (a.rows.past + a.rows.T) : 1;
+  const float n_seq = ragged ? (float)(a.M / (a.rows.past + a.rows.T)) : 1.f, K = (float)a.K;
+  // a ragged launch with as many jobs as this may find them all: it is not taken for less than a round
+  auto rounds_of = [&](int bm, int bn, bool packed) -> float {
+    const float cols = (float)gemm_col_blocks(a, bn), most = (float)((a.M + bm - 1) / bm);
+    if (!ragged) return cols * most / 256.f;
+    if (cols * most <= 256.f) return cols * most / 256.f;
+    return packed ? 0.75f * cols * most / 256.f + 0.5f : cols * (0.75f * (float)a.M / (float)bm + 0.5f * n_seq) / 256.f;
+  };
   float best = 0.f;
   pick = 0;
   for (int i = 0; i < 4; ++i) {
-    const long long jobs = (long long)gemm_col_blocks(a, kTiles[i].bn) * ((a.M + kTiles[i].bm - 1) / kTiles[i].bm);
-    const float rounds = ragged && jobs > 256 ? 0.75f * (float)jobs / 256.f + 0.5f : (float)((jobs + 255) / 256);
-    const float cost = rounds * (float)(kTiles[i].bm * kTiles[i].bn) / kTiles[i].rate / 65536.f + (i ? 0.1f : 0.f);
+    const float rounds = ceilf(rounds_of(kTiles[i].bm, kTiles[i].bn, a.rows.zeros));
+    float cost = kTiles[i].base + rounds * (kTiles[i].round + kTiles[i].k * K);
+    if (i == 3 && rounds > 2.f) cost += 0.6f;  // (two fit on a unit)
     if (i == 0 || cost < best) {
       best = cost;
       pick = i;
     }
   }
   if (gemm_wide_supported(a)) {
-    const float blocks = ragged ? 0.75f * (float)a.M / 256.f + 0.5f * (float)n_seq : (float)((a.M + 255) / 256);
-    const float rounds = blocks * (float)gemm_col_blocks(a, 256) / 256.f, whole = floorf(rounds), left = rounds - whole;
-    const float cost = 0.9f * whole + (left == 0.f ? 0.f : left <= 0.25f ? 0.33f : left <= 0.5f ? 0.53f : 0.9f);
+    const float rounds = rounds_of(256, 256, false), left = rounds - floorf(rounds), whole = left > 0.5f ? ceilf(rounds) : floorf(rounds);
+    float cost = 5.f + whole * (4.4f + 0.0246f * K);
+    if (left > 0.25f && left <= 0.5f) cost += 1.2f + 0.0142f * K;
+    else if (left > 0.f && left <= 0.25f) cost += 0.0097f * K;
     if (cost < best) {
       best = cost;
       pick = kWide;
@@ -769,8 +798,8 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   int pick = 0;
   const float whole = gemm_cost(a, pick);
   if (a.n_seg > 1) {
-    // The narrowest product in a launch of its own if that saves more than the launch costs: 64 columns beside 3584 at
-    // 32768 rows open an eighth round of 256 x 256 tiles (67 us at K = 2048) that is half empty.
+    // The narrowest product in a launch of its own if that saves time: 64 columns beside 3584 at 32768 rows open half a round
+    // of 256 x 256 tiles more.
     int least = 0;
     for (int i = 1; i < a.n_seg; ++i)
       if (a.seg[i].N < a.seg[least].N) least = i;
@@ -780,8 +809,7 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
     rest.n_seg = a.n_seg - 1;
     for (int i = least; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
     int p1 = 0, p2 = 0;
-    const float launch = 0.075f * 2048.f / (float)a.K;  // 5 us
-    if (gemm_cost(one, p1) + gemm_cost(rest, p2) + launch < whole) {
+    if (gemm_cost(one, p1) + gemm_cost(rest, p2) < whole) {
       const hipError_t e = launch_gemm_nt(rest, st);
       return e != hipSuccess ? e : launch_gemm_nt(one, st);
     }
