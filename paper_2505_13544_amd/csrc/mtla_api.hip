@@ -513,6 +513,17 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     ev.start = c->ev_start[c->prof_n];
     ev.stop = c->ev_stop[c->prof_n++];
   }
+  // few short sequences; a schedule or a chunk that the caller set stays what it says
+  if (c->schedule == 0 && c->chunk == c->default_chunk && (use_mfma || g.dtype == MTLA_F32)) {
+    WholeArgs wh;
+    wh.at = at;
+    wh.w_uv = w_uv;
+    wh.out = out;
+    wh.out_latent = out_latent;
+    wh.lse = lse;
+    wh.d_head = g.d_head;
+    if (attn_whole_supported(wh, g.dtype)) return hip_ok(launch_attn_whole(wh, g.dtype, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
+  }
   const hipError_t le = g.dtype == MTLA_F32 ? launch_attn_decode_f32(at, st, ev)
                         : !use_mfma         ? launch_attn_valu(at, g.dtype, st, ev)
                                   : (attn_cols_supported(at) ? launch_attn_cols(at, st, ev) : launch_attn_mfma(at, st, ev));

@@ -121,6 +121,16 @@ struct CombineArgs {
   int part_f16;                 // part_o holds normalised IEEE-half partials (matrix-core combine only)
 };
 
+// Decode attention and value up-projection of whole sequences in one launch (attn_whole.hip).
+struct WholeArgs {
+  AttnArgs at;                 // (no partials)
+  const void* w_uv = nullptr;  // [n_heads, d_head, r]
+  float* out = nullptr;        // [rows, n_heads, d_head]
+  float* out_latent = nullptr; // [rows, n_heads, r] or NULL
+  float* lse = nullptr;        // [rows, n_heads] or NULL
+  int d_head = 0;
+};
+
 // Parallel form with explicit per-head keys and values (bf16).
 struct ExplicitArgs {
   const void* q;       // [B, T, n_heads, d_head]
@@ -355,6 +365,9 @@ hipError_t launch_decode_front_f32(const AppendArgs& ap, const AbsorbArgs& ab, h
 hipError_t launch_attn_decode_f32(const AttnArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 bool prefill_f32_supported(const ExplicitArgs& a);
 hipError_t launch_prefill_f32(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
+// few short sequences: no partials, no combine (dtype: the storage type)
+bool attn_whole_supported(const WholeArgs& w, int dtype);
+hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, const EventPair& ev = EventPair());
 hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev = EventPair());
 // bf16 matrix-core variant of the split pass (decode addressing only)
 bool attn_mfma_supported(const AttnArgs& a);
