@@ -1,12 +1,13 @@
-// Decode over few short sequences (gfx950): attention, normalisation and the value up-projection of one (sequence, head) in
-// one workgroup, so that a step is two launches instead of three.
+// Decode over short sequences (gfx950): attention, normalisation and the value up-projection of a sequence and a few of its
+// heads in one workgroup, so that a step is two launches instead of three.
 //
-// A decode step at small batch is a chain of latencies: behind the front launch the split attention and the combine of its
-// partials took 4.8 to 5.3 and 4.4 to 6.0 us, most of it the launch, the first loads and the last stores of each.  Where a
-// sequence's slots are few enough for one workgroup to walk, nothing has to be combined: the workgroup ends with the head's
-// latent output in LDS and multiplies it by its W_V^(h), requested when the kernel began.  A sequence's rows are then read
-// once per head instead of once, and W_V^(h) once per sequence: the launcher's limits are where that costs what the launch
-// saves.
+// Such a step is a chain of latencies: behind the front launch the split attention and the combine of its partials took
+// 4.8 to 5.3 and 4.4 to 6.0 us at small batch, most of it the launch, the first loads and the last stores of each.  Where a
+// workgroup can walk all of a sequence's slots in the time that saves, nothing has to be combined: it ends with its heads'
+// latent outputs in LDS and multiplies them by W_V^(h).  A sequence's rows are then read once per workgroup instead of once, and
+// W_V^(h) once per sequence: the limits below are where that costs what the launch saves.
+#include <type_traits>
+
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -17,40 +18,43 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-constexpr int kWaves = kBlock / kWave;
-constexpr int kStep = 16 * kWaves;  // slots of a step
-
 // ---------------------------------------------------------------------------
-// bf16 storage.  64 slots a step: a wavefront brings 16 rows, memory -> LDS in whole rows and up to two steps ahead, forms
-// their logits, and then multiplies all 64 by a quarter of the latent columns (as attn_split_kernel does for 16
-// heads).  With one head the sixteen columns of a matrix operand are free: the even ones hold the hi plane and the odd ones the
-// lo plane of the query, of the weights (which one plane would round to 8 bits) and of the latent output before W_V^(h), each
-// at the price of one.
-// Rows straight into the operand layout, 64 bytes of each of 16 rows a request, took 1.1 us a step at r = 256, the
-// workgroup's other work half of that.
+// bf16 storage.  Every wavefront walks 16-slot tiles of its own (tile t belongs to wavefront t mod 4) with a softmax state of
+// its own; the states meet once, behind the last tile.  No barrier stands in the walk.  Tiles come memory -> LDS in whole
+// rows, one ahead of the one being multiplied (rows straight into the operand layout, 64 bytes of each of 16 rows a
+// request, took twice as long), and the logits' layout [slot, column] is the K = 16 operand of the product with the latent
+// rows as it stands.  One wavefront per SIMD issues a vector instruction every four cycles, so what is left of a tile is kept off
+// the vector ALU: a load's address is a base for the wavefront and one clamped offset, an LDS address a register and
+// a constant (the two places of a wavefront's tiles are two copies of the walk's body).
+// A head takes two of the sixteen columns of a matrix operand: the even ones hold the hi plane and the odd ones the lo plane of
+// the query, of the weights (which one plane would round to 8 bits) and of the latent output before W_V^(h), each at the
+// price of one.  So HPW heads, up to eight, cost the walk what one does: a workgroup takes one where the workgroups
+// find a compute unit each, and more where they would not.
 // SH, PG: shared prefixes and paged storage, as in attn_mfma.hip.
 // ---------------------------------------------------------------------------
-template <int R, int DR>
-struct WholeLds {
-  static constexpr int rows = kStep * R * 2, step = rows + kStep * DR * 2;  // [latent rows][RoPE keys] of a step
-  static constexpr int NB = R >= 512 ? 2 : 3;                               // steps
-  static constexpr int weights = NB * step, stats = weights + kWaves * kWave * 8, bytes = stats + 2 * kWaves * 4;
-  static_assert(bytes <= 160 * 1024 && R * 4 <= step, "LDS of one compute unit; the latent output takes a step's place");
+constexpr int kWaves = kBlock / kWave;
+
+template <int R, int DR, int HPW, int NW>
+struct WholeGeom {
+  static constexpr int tile = 16 * (R + DR) * 2;  // [latent rows][RoPE keys]
+  static constexpr int area = 2 * tile;           // a wavefront's two
+  static constexpr int bytes = NW * area;
+  // behind the walk an area holds its wavefront's sums, two planes a head, and (m, l); the first one also the planes of the result
+  static constexpr int ml = 2 * HPW * R * 4, planes = ml + 64, plane = R * 2 + 64;
+  static_assert(bytes <= 160 * 1024 && planes + 2 * HPW * plane <= area && planes % 16 == 0 && 8 * HPW <= 64, "LDS of one compute unit");
+  static constexpr int per_simd = NW / 4 * (2 * bytes <= 160 * 1024 ? 2 : 1);
 };
 
-template <int R, int DR, int DH, bool SH, bool PG>
-__global__ __launch_bounds__(kBlock, R >= 512 ? 1 : 2) void attn_whole_kernel(WholeArgs w) {
-  using L = WholeLds<R, DR>;
-  constexpr int KC = R / 32, KT = (R + DR) / 32, MW = R / 16 / kWaves, NT = DH / 64, NB = L::NB;
+template <int R, int DR, int DH, int HPW, int NW, bool SH, bool PG>
+__global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) void attn_whole_kernel(WholeArgs w) {
+  using G = WholeGeom<R, DR, HPW, NW>;
+  constexpr int KC = R / 32, KT = (R + DR) / 32, MT = R / 16, OT = DH / 16, NT = OT < NW ? 1 : OT / NW;  // NT: output tiles of a wavefront, per head
   constexpr int PC = R / 8, RC = DR / 8;  // 16-byte pieces of a row
+  static_assert(HPW <= 8, "two columns a head");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  uint2* sP = reinterpret_cast<uint2*>(smem + L::weights);  // [wavefront][lane]: weights of slots 4g .. 4g + 3
-  float* sM = reinterpret_cast<float*>(smem + L::stats);    // [wavefront]
-  float* sL = sM + kWaves;
-  float* sO = reinterpret_cast<float*>(smem);               // [R], behind the last step
 
   const AttnArgs& a = w.at;
-  const int b = blockIdx.x, h = blockIdx.y;  // an XCD takes the heads of a few sequences and reads their rows once
+  const int b = blockIdx.x, h0 = blockIdx.y * HPW;  // an XCD takes the heads of a few sequences and reads their rows once
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
@@ -65,183 +69,222 @@ __global__ __launch_bounds__(kBlock, R >= 512 ? 1 : 2) void attn_whole_kernel(Wh
     sp.dlat = (long long)(owner - b) * a.max_slots * R;
     sp.dkey = (long long)(owner - b) * a.max_slots * DR;
   }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
-  // The wavefront's 16 rows of step t (slots past `last`: a readable duplicate) on their way into place t % NB: KT loads.
-  // Piece j of row i sits at j ^ swizzle(i).
-  auto issue = [&](int t, int last) {
-    const int base = kStep * t + 16 * wv;
-    const uint32_t to = lds0 + (uint32_t)(t % NB) * (uint32_t)L::step;
-    size_t page = 0;
-    if constexpr (PG) {
-      const int s0 = base < last ? base : last;  // a page holds whole 16-slot tiles
-      int pg = load_uniform_i32(pt, s0 >> a.pages.shift);
-      pg = pg < 0 ? 0 : (pg < a.pages.n_pages ? pg : a.pages.n_pages - 1);
-      page = (size_t)pg << a.pages.shift;
-    }
-    auto one = [&](int i, int place, const uint16_t* array, long long shared, int width, uint32_t at) {
-      const int slot = base + i < last ? base + i : last;
-      const size_t row = PG ? page + (size_t)(slot & ((1 << a.pages.shift) - 1)) : (size_t)slot;
-      const uint16_t* src = array + row * width + 8 * place;
-      if constexpr (SH) {
-        if (slot < sp.n) src += shared;
+  unsigned char* area = smem + wv * G::area;
+  const uint32_t area0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem + (uint32_t)(wv * G::area);
+  auto tile_base = [&](int k) { return 16 * (wv + NW * k); };
+  // Byte offsets of the lane's 16-byte pieces in a tile of consecutive rows; piece j of row i sits at j ^ swizzle(i).
+  uint32_t at_lat[R / 32], at_key[DR / 32];
+#pragma unroll
+  for (int c = 0; c < R / 32; ++c) {
+    const int at = 64 * c + lane, i = at / PC;
+    at_lat[c] = (uint32_t)(i * R * 2 + (((at % PC) ^ swz_rows16<PC>(i)) << 4));
+  }
+#pragma unroll
+  for (int c = 0; c < DR / 32; ++c) {
+    const int at = 64 * c + lane, i = at / RC;
+    at_key[c] = (uint32_t)(i * DR * 2 + (((at % RC) ^ swz_rows16<RC>(i)) << 4));
+  }
+  // The wavefront's tile k on its way into place P: KT loads.  Slots past `last` become copies of that row's end: readable,
+  // and their weights are zero.
+  auto issue = [&](int k, int last, auto place) {
+    constexpr int P = decltype(place)::value;
+    const int base = tile_base(k);
+    const uint32_t to = area0 + (uint32_t)(P * G::tile), to_key = to + (uint32_t)(16 * R * 2);
+    if constexpr (SH) {
+      auto one = [&](uint32_t off, const uint16_t* array, long long shared, int width, uint32_t at) {
+        const int i = (int)off / (2 * width), slot = base + i < last ? base + i : last;
+        load_to_lds_16(array + (size_t)slot * width + ((int)off - i * 2 * width) / 2 + (slot < sp.n ? shared : 0), at);
+      };
+#pragma unroll
+      for (int c = 0; c < R / 32; ++c) one(at_lat[c], lat, sp.dlat, R, to + 1024u * c);
+#pragma unroll
+      for (int c = 0; c < DR / 32; ++c) one(at_key[c], key, sp.dkey, DR, to_key + 1024u * c);
+    } else {
+      const int s0 = base < last ? base : last;  // (only behind the last tile's)
+      size_t row = (size_t)s0;
+      if constexpr (PG) {  // a page holds whole 16-slot tiles
+        int pg = load_uniform_i32(pt, s0 >> a.pages.shift);
+        pg = pg < 0 ? 0 : (pg < a.pages.n_pages ? pg : a.pages.n_pages - 1);
+        row = ((size_t)pg << a.pages.shift) + (size_t)(s0 & ((1 << a.pages.shift) - 1));
       }
-      load_to_lds_16(src, at);
-    };
+      const uint32_t rows = (uint32_t)(last - s0 + 1);  // that may be read from there on
+      const uint32_t end_lat = rows * (R * 2) - 16, end_key = rows * (DR * 2) - 16;
 #pragma unroll
-    for (int c = 0; c < R / 32; ++c) {
-      const int at = 64 * c + lane, i = at / PC;
-      one(i, (at % PC) ^ swz_rows16<PC>(i), lat, sp.dlat, R, to + (uint32_t)(16 * wv * R * 2 + 1024 * c));
-    }
+      for (int c = 0; c < R / 32; ++c) load_to_lds_16(lat + row * R, at_lat[c] < end_lat ? at_lat[c] : end_lat, to + 1024u * c);
 #pragma unroll
-    for (int c = 0; c < DR / 32; ++c) {
-      const int at = 64 * c + lane, i = at / RC;
-      one(i, (at % RC) ^ swz_rows16<RC>(i), key, sp.dkey, DR, to + (uint32_t)(L::rows + 16 * wv * DR * 2 + 1024 * c));
+      for (int c = 0; c < DR / 32; ++c) load_to_lds_16(key + row * DR, at_key[c] < end_key ? at_key[c] : end_key, to_key + 1024u * c);
     }
   };
   // first rows, length (a scalar load), query and W_V^(h) are requested together
-  issue(0, a.max_slots - 1);
+  const auto place0 = std::integral_constant<int, 0>{};
+  const auto place1 = std::integral_constant<int, 1>{};
+  if (tile_base(0) < a.max_slots) issue(0, a.max_slots - 1, place0);
   const int len = load_uniform_i32(a.seq_len, b);  // nothing writes it while the kernel runs
   u32x4_t q[KT];
   {
-    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.qcat) + ((size_t)b * a.n_heads + h) * (R + DR) + 8 * g +
-                         ((l16 & 1) ? a.q_plane : 0);
+    const int h = h0 + (l16 >> 1) % HPW;
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.qcat) +
+                         ((size_t)b * a.n_heads + (h < a.n_heads ? h : a.n_heads - 1)) * (R + DR) + 8 * g + ((l16 & 1) ? a.q_plane : 0);
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) q[kk] = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
   }
   u32x4_t wf[NT][KC];
-  {
-    const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.w_uv) + ((size_t)h * DH + wv * (DH / kWaves) + l16) * R + 8 * g;
+  const int d0 = 16 * NT * wv;  // the wavefront's output columns
+  auto load_w = [&](int h) {
+    const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.w_uv) + ((size_t)(h < a.n_heads ? h : a.n_heads - 1) * DH + d0 + l16) * R + 8 * g;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
       for (int kk = 0; kk < KC; ++kk) wf[i][kk] = *reinterpret_cast<const u32x4_t*>(wp + 16 * i * R + 32 * kk);
-  }
-  const int live = (len + a.stride - 1) / a.stride, n_steps = (live + kStep - 1) / kStep;
-  const size_t oh = (size_t)b * a.n_heads + h;
-  wait_loads_but<NT * KC>();  // the first rows and the query: W_V^(h) may still travel
+  };
+  constexpr bool kEarly = 4 * (KT + MT + NT * KC) <= (G::per_simd > 1 ? 180 : 250);  // registers for W_V^(h) during the walk
+  const bool multiplies = OT >= NW || wv < OT;  // (a wavefront too many has no output columns)
+  if (kEarly && multiplies) load_w(h0);
+  const int live = (len + a.stride - 1) / a.stride, tiles = (live + 15) / 16;
+  const int mine = tiles > wv ? (tiles - wv + NW - 1) / NW : 0;
+  if (kEarly && multiplies) wait_loads_but<NT * KC>();  // the first rows and the query: W_V^(h) may still travel
+  else wait_loads_but<0>();
 #pragma unroll
-  for (int kk = 0; kk < KT; ++kk) asm volatile("" : "+v"(q[kk]));  // (and the compiler waits here, not behind the next step's loads)
-  if (n_steps > 1) issue(1, live - 1);
+  for (int kk = 0; kk < KT; ++kk) asm volatile("" : "+v"(q[kk]));  // (and the compiler waits here, not behind the next tiles' loads)
+  if (mine > 1) issue(1, live - 1, place1);
 
-  float m_ref = -INFINITY, l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
-  float4_t acc[MW];
+  float m_ref = -INFINITY, l_run = 0.f;  // of the column's head; l_run: this lane's slots only
+  float4_t acc[MT];
 #pragma unroll
-  for (int mt = 0; mt < MW; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+  for (int mt = 0; mt < MT; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-  for (int t = 0; t < n_steps; ++t) {
-    unsigned char* rows = smem + (t % NB) * L::step;
-    if (t > 0) {
-      if (NB > 2 && t + 1 < n_steps) wait_loads_but<KT>();  // the step behind it may travel on
+  const int vrow = 4 * g + (l16 >> 2);  // row of the lane's transposing reads
+  auto step = [&](int k, auto place) {
+    unsigned char* rows = area + decltype(place)::value * G::tile;
+    const int base = tile_base(k);
+    if (k > 0) {
+      if (k + 1 < mine) wait_loads_but<KT>();  // the tile behind it may travel on
       else wait_loads_but<0>();
-    } else if (live < kStep) {
-      // rows of the first step that no slot stands for may never have been written: zeros, or 0 x NaN would reach the sums
+    } else if (live < base + 16) {
+      // rows of the first tile that no slot stands for may never have been written: zeros, or 0 x NaN would reach the sums
 #pragma unroll
       for (int c = 0; c < R / 32; ++c) {
         const int at = 64 * c + lane;
-        if (16 * wv + at / PC >= live) *reinterpret_cast<u32x4_t*>(rows + 16 * wv * R * 2 + 16 * at) = u32x4_t{0u, 0u, 0u, 0u};
+        if (base + at / PC >= live) *reinterpret_cast<u32x4_t*>(rows + 16 * at) = u32x4_t{0u, 0u, 0u, 0u};
       }
     }
-    const int base = kStep * t + 16 * wv;
-    const unsigned char* xr = rows + (16 * wv + l16) * R * 2;
-    const unsigned char* kr = rows + L::rows + (16 * wv + l16) * DR * 2;
-    float4_t se = {0.f, 0.f, 0.f, 0.f}, so = se;
+    float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+    const unsigned char* xr = rows + l16 * R * 2;
+    const unsigned char* kr = rows + 16 * R * 2 + l16 * DR * 2;
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) {
       const u32x4_t x = kk < KC ? *reinterpret_cast<const u32x4_t*>(xr + (((4 * kk + g) ^ swz_rows16<PC>(l16)) << 4))
                                 : *reinterpret_cast<const u32x4_t*>(kr + (((4 * (kk - KC) + g) ^ swz_rows16<RC>(l16)) << 4));
-      float4_t& s = (kk & 1) ? so : se;
+      float4_t& s = (kk & 1) ? s1 : s0;
       s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, q[kk]), s, 0, 0, 0);
     }
     float sv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float s = se[v] + so[v];
-      sv[v] = base + 4 * g + v < live ? s + row_permuted<0xb1>(s) : -INFINITY;  // the planes' columns are neighbours
+      const float t = s0[v] + s1[v];
+      sv[v] = base + 4 * g + v < live ? t + row_permuted<0xb1>(t) : -INFINITY;  // the planes' columns are neighbours
     }
-    const float mloc = quarter_reduce(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), LaneMax());
-    if (lane == 0) sM[wv] = mloc;
-    __syncthreads();  // the maxima are there, everyone's rows too, and nobody still reads those of the step before
-    if (t + NB - 1 < n_steps && t + NB - 1 > 1) issue(t + NB - 1, live - 1);
-    const float top = fmaxf(fmaxf(sM[0], sM[1]), fmaxf(sM[2], sM[3]));
+    const float top = quarter_reduce(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), LaneMax());
     constexpr float kRebase = 40.f;
-    if (top - m_ref > kRebase) {  // uniform; true at the first step (m_ref = -inf)
-      const float alpha = __builtin_amdgcn_exp2f(m_ref - top);
-      m_ref = top;
-      l_run *= alpha;
+    if (__any(top - m_ref > kRebase)) {  // true at the first tile (m_ref = -inf)
+      if (top - m_ref > kRebase) {
+        const float alpha = __builtin_amdgcn_exp2f(m_ref - top);
+        m_ref = top;
+        l_run *= alpha;
 #pragma unroll
-      for (int mt = 0; mt < MW; ++mt) acc[mt] *= alpha;
+        for (int mt = 0; mt < MT; ++mt) acc[mt] *= alpha;
+      }
     }
     float pw[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) pw[v] = __builtin_amdgcn_exp2f(sv[v] - m_ref);
+    l_run += (pw[0] + pw[1]) + (pw[2] + pw[3]);
     uint32_t hi01, lo01, hi23, lo23;  // hi plane in the even columns, lo plane in the odd ones
     split_bf16x2(pw[0], pw[1], hi01, lo01);
     split_bf16x2(pw[2], pw[3], hi23, lo23);
-    sP[wv * kWave + lane] = (l16 & 1) ? make_uint2(lo01, lo23) : make_uint2(hi01, hi23);
-    l_run += (pw[0] + pw[1]) + (pw[2] + pw[3]);
-    if (t + 1 == n_steps) {  // last step: the wavefront's share of the normaliser
-      const float l = quarter_reduce(l_run, LaneSum());
-      if (lane == 0) sL[wv] = l;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the weights are written (loads of rows need not have landed here)
-    barrier_only();
-    const int vrow = 4 * g + (l16 >> 2);  // row of the lane's transposing reads in a 16-slot tile
+    const short4_t p = __builtin_bit_cast(short4_t, (l16 & 1) ? make_uint2(lo01, lo23) : make_uint2(hi01, hi23));
+    const unsigned char* vr = rows + vrow * R * 2 + 8 * (l16 & 1);
 #pragma unroll
-    for (int k = 0; k < kWaves / 2; ++k) {
-      const uint2 u0 = sP[(2 * k) * kWave + lane], u1 = sP[(2 * k + 1) * kWave + lane];
-      const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, u32x4_t{u0.x, u0.y, u1.x, u1.y});
-      const unsigned char* vr = rows + (32 * k + vrow) * R * 2 + 8 * (l16 & 1);
-#pragma unroll
-      for (int mt = 0; mt < MW; ++mt) {
-        const unsigned char* src = vr + ((((wv * (R / kWaves) + 16 * mt) / 8 + ((l16 & 3) >> 1)) ^ swz_rows16<PC>(vrow)) << 4);
-        const short4_t c0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
-        const short4_t c1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + 16 * R * 2));
-        const uint2 a0 = __builtin_bit_cast(uint2, c0), a1 = __builtin_bit_cast(uint2, c1);
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, u32x4_t{a0.x, a0.y, a1.x, a1.y}), pb,
-                                                          acc[mt], 0, 0, 0);
-      }
+    for (int mt = 0; mt < MT; ++mt) {
+      const short4_t c = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (lds_short4_ptr)(vr + (((2 * mt + ((l16 & 3) >> 1)) ^ swz_rows16<PC>(vrow)) << 4)));
+      acc[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(c, p, acc[mt], 0, 0, 0);
     }
+    if (k + 2 < mine) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile has been read: its place takes the one after the next
+      issue(k + 2, live - 1, place);
+    }
+  };
+  for (int k = 0; k < mine; k += 2) {
+    step(k, place0);
+    if (k + 1 < mine) step(k + 1, place1);
   }
-  __syncthreads();  // the rows have been read: sO takes their place
 
-  const float l = live > 0 ? (sL[0] + sL[1]) + (sL[2] + sL[3]) : 0.f;
-  const float inv = live > 0 ? 1.f / l : 0.f;  // a sequence without a slot gives zeros
+  // ---- the wavefronts' states side by side, each in its area
+  if (!kEarly && multiplies) load_w(h0);
+  const float l_own = quarter_reduce(l_run, LaneSum());
+  if (l16 < 2 * HPW) {  // columns 16 mt + 4g .. + 3 of head l16 / 2, from one plane of the weights
 #pragma unroll
-  for (int mt = 0; mt < MW; ++mt) {
-    float4_t o;  // columns 16 mt + 4g .. + 3 of the wavefront's quarter: the planes' columns are neighbours
-#pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = (acc[mt][v] + row_permuted<0xb1>(acc[mt][v])) * inv;
-    if (l16 == 0) {
-      const int n = wv * (R / kWaves) + 16 * mt + 4 * g;
-      *reinterpret_cast<float4_t*>(sO + n) = o;
-      if (w.out_latent) *reinterpret_cast<float4_t*>(w.out_latent + oh * R + n) = o;
-    }
+    for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<float4_t*>(area + l16 * R * 4 + 4 * (16 * mt + 4 * g)) = acc[mt];
+    if (g == 0 && !(l16 & 1)) *reinterpret_cast<float2*>(area + G::ml + 4 * l16) = make_float2(m_ref, l_own);
   }
-  if (w.lse && tid == 0) w.lse[oh] = live > 0 ? (m_ref + log2f(l)) * 0.6931471805599453f : -INFINITY;
   __syncthreads();
-  float4_t o[NT];
 #pragma unroll
-  for (int i = 0; i < NT; ++i) o[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+  for (int u = 0; u < (HPW * R / 2 + (NW * kWave) - 1) / (NW * kWave); ++u) {  // two columns a thread
+    const int at = tid + (NW * kWave) * u, hp = at / (R / 2), col = 2 * (at % (R / 2));
+    if (hp >= HPW) break;
+    const size_t oh = (size_t)b * a.n_heads + h0 + hp;
+    float2 ml[NW];
+    float ms = -INFINITY, l = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < KC; ++kk) {
-    const float4_t lo4 = *reinterpret_cast<const float4_t*>(sO + 32 * kk + 8 * g), hi4 = *reinterpret_cast<const float4_t*>(sO + 32 * kk + 8 * g + 4);
-    u32x4_t p;  // hi plane in the even columns, what it leaves of the value in the odd ones
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float e0 = i < 2 ? lo4[2 * i] : hi4[2 * i - 4], e1 = i < 2 ? lo4[2 * i + 1] : hi4[2 * i - 3];
-      uint32_t hi, lo;
-      split_bf16x2(e0, e1, hi, lo);
-      p[i] = (l16 & 1) ? lo : hi;
+    for (int i = 0; i < NW; ++i) {
+      ml[i] = *reinterpret_cast<const float2*>(smem + i * G::area + G::ml + 8 * hp);
+      ms = fmaxf(ms, ml[i].x);
     }
+    float2 o = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-      o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[i][kk]), __builtin_bit_cast(bf16x8_t, p), o[i], 0, 0, 0);
+    for (int i = 0; i < NW; ++i) {
+      const float f = live > 0 ? __builtin_amdgcn_exp2f(ml[i].x - ms) : 0.f;  // 0 for a wavefront without a tile
+      const float2 x = *reinterpret_cast<const float2*>(smem + i * G::area + (2 * hp) * R * 4 + 4 * col);
+      const float2 y = *reinterpret_cast<const float2*>(smem + i * G::area + (2 * hp + 1) * R * 4 + 4 * col);
+      l += f * ml[i].y;
+      o.x += f * (x.x + y.x);
+      o.y += f * (x.y + y.y);
+    }
+    const float inv = live > 0 ? 1.f / l : 0.f;  // a sequence without a slot gives zeros
+    o.x *= inv;
+    o.y *= inv;
+    if (h0 + hp < a.n_heads) {
+      if (w.out_latent) *reinterpret_cast<float2*>(w.out_latent + oh * R + col) = o;
+      if (w.lse && col == 0) w.lse[oh] = live > 0 ? (ms + log2f(l)) * 0.6931471805599453f : -INFINITY;
+    }
+    uint32_t hi, lo;
+    split_bf16x2(o.x, o.y, hi, lo);
+    *reinterpret_cast<uint32_t*>(smem + G::planes + 2 * hp * G::plane + 2 * col) = hi;
+    *reinterpret_cast<uint32_t*>(smem + G::planes + (2 * hp + 1) * G::plane + 2 * col) = lo;
   }
+  __syncthreads();
+  if (!multiplies) return;
 #pragma unroll
-  for (int i = 0; i < NT; ++i) {
+  for (int hp = 0; hp < HPW; ++hp) {
+    float4_t o[NT];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[i][v] += row_permuted<0xb1>(o[i][v]);
-    if (l16 == 0) *reinterpret_cast<float4_t*>(w.out + oh * DH + wv * (DH / kWaves) + 16 * i + 4 * g) = o[i];
+    for (int i = 0; i < NT; ++i) o[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* pl = smem + G::planes + (2 * hp + (l16 & 1)) * G::plane + 16 * g;
+#pragma unroll
+    for (int kk = 0; kk < KC; ++kk) {
+      const bf16x8_t p = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(pl + 64 * kk));
+#pragma unroll
+      for (int i = 0; i < NT; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[i][kk]), p, o[i], 0, 0, 0);
+    }
+    if (hp + 1 < HPW) load_w(h0 + hp + 1);
+    if (h0 + hp >= a.n_heads) break;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[i][v] += row_permuted<0xb1>(o[i][v]);
+      if (l16 == 0) *reinterpret_cast<float4_t*>(w.out + ((size_t)b * a.n_heads + h0 + hp) * DH + d0 + 16 * i + 4 * g) = o[i];
+    }
   }
 }
 
@@ -251,6 +294,8 @@ __global__ __launch_bounds__(kBlock, R >= 512 ? 1 : 2) void attn_whole_kernel(Wh
 // serves the logit and, weighted, the lane's sum of the latent columns, so a row is read once and never leaves its registers.
 // 64 slots a step, two in every lane group.
 // ---------------------------------------------------------------------------
+constexpr int kStep = 16 * kWaves;  // slots of a step
+
 template <int CTRL>
 __device__ __forceinline__ float row_rotated(float v) {  // inside 16 lanes
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + CTRL, 0xf, 0xf, true));
@@ -385,20 +430,29 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
   }
 }
 
-template <int R, int DR, int DH, bool SH, bool PG>
+template <int R, int DR, int DH, int HPW, int NW, bool SH, bool PG>
 hipError_t launch_whole(const WholeArgs& w, hipStream_t st, const EventPair& ev) {
-  constexpr size_t smem = WholeLds<R, DR>::bytes;
+  constexpr size_t smem = WholeGeom<R, DR, HPW, NW>::bytes;
   static DeviceSet lds_allowed;
-  const hipError_t e = allow_lds(&attn_whole_kernel<R, DR, DH, SH, PG>, smem, lds_allowed);
+  const hipError_t e = allow_lds(&attn_whole_kernel<R, DR, DH, HPW, NW, SH, PG>, smem, lds_allowed);
   if (e != hipSuccess) return e;
-  launch_timed(attn_whole_kernel<R, DR, DH, SH, PG>, dim3(w.at.batch, w.at.n_heads), dim3(kBlock), smem, st, ev, w);
+  launch_timed(attn_whole_kernel<R, DR, DH, HPW, NW, SH, PG>, dim3(w.at.batch, (w.at.n_heads + HPW - 1) / HPW), dim3(NW * kWave),
+               smem, st, ev, w);
   return hipGetLastError();
 }
 
-template <int R, int DR, int DH>
+template <int R, int DR, int DH, int HPW, int NW>
 hipError_t launch_form(const WholeArgs& w, hipStream_t st, const EventPair& ev) {
-  if (w.at.pages.table) return w.at.prefix_owner ? hipErrorInvalidValue : launch_whole<R, DR, DH, false, true>(w, st, ev);
-  return w.at.prefix_owner ? launch_whole<R, DR, DH, true, false>(w, st, ev) : launch_whole<R, DR, DH, false, false>(w, st, ev);
+  if (w.at.pages.table) return w.at.prefix_owner ? hipErrorInvalidValue : launch_whole<R, DR, DH, HPW, NW, false, true>(w, st, ev);
+  return w.at.prefix_owner ? launch_whole<R, DR, DH, HPW, NW, true, false>(w, st, ev) : launch_whole<R, DR, DH, HPW, NW, false, false>(w, st, ev);
+}
+
+template <int R, int DR, int DH, int NW>
+hipError_t launch_heads(const WholeArgs& w, hipStream_t st, const EventPair& ev) {
+  const size_t jobs = (size_t)w.at.n_heads * w.at.batch;
+  return jobs <= 256   ? launch_form<R, DR, DH, 1, NW>(w, st, ev)
+         : jobs <= 512 ? launch_form<R, DR, DH, 2, NW>(w, st, ev)
+                       : launch_form<R, DR, DH, 4, NW>(w, st, ev);
 }
 
 }  // namespace
@@ -406,22 +460,27 @@ hipError_t launch_form(const WholeArgs& w, hipStream_t st, const EventPair& ev) 
 bool attn_whole_supported(const WholeArgs& w, int dtype) {
   const AttnArgs& a = w.at;
   const auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  if (!w.out || !w.w_uv || a.T != 0 || a.n_persistent > 0 || !al16(w.out) || !al16(w.out_latent) || !al16(w.w_uv)) return false;
-  // Where one workgroup per (sequence, head) is the faster form, in slots a sequence may hold.  A step of 64 slots costs it 0.5 us
-  // (r = 64, fp32) to 2.0 (r = 512), what it saves are 3 to 6 us.  us a decode step, three launches / two:
+  if (!w.out || !w.w_uv || a.T != 0 || !al16(w.out) || !al16(w.out_latent) || !al16(w.w_uv)) return false;
+  // Where this is the faster form, in (sequence, head) pairs and in slots a sequence may hold: a workgroup walks a whole sequence,
+  // so the limits leave room for batches in which most are far shorter than the longest.  us a decode step, three
+  // launches / two:
   //   fp32, 8 heads x 64, r = 256, 8 sequences: 64 slots 15.9 / 9.4, 512 18.2 / 17.0, 640 18.8 / 19.3
   //   fp32, 4 heads x 64, r = 64, 1 sequence: 128 slots 10.2 / 7.1, 768 12.2 / 11.2, 1024 12.7 / 12.8
-  //   bf16, 8 heads x 64, r = 256, 16 sequences: 64 slots 12.9 / 8.9, 256 13.1 / 11.9, 384 13.2 / 13.8
-  //   bf16, 16 heads x 128, r = 512, 8 sequences: 64 slots 20.8 / 14.2, 256 21.5 / 20.6, 320 21.6 / 22.7
-  // From 256 workgroups on a unit gets a second one, at once only at r = 128 (64 sequences of 8 heads: 64 slots 11.2 / 8.7, 256 11.7 /
-  // 11.6) and in fp32; at r = 256 and 512 it waits for the first (15.5 / 15.7 at 64 slots, worse above).
+  //   bf16, 8 heads x 64, r = 128, 16 sequences: 64 slots 11.1 / 7.4, 640 12.4 / 10.5; 128: 64 slots 11.2 / 9.3, 640 18.9 / 13.9;
+  //     200 (400 workgroups of four heads): 64 slots 11.8 / 11.3, 384 19.6 / 16.5
+  //   bf16, 8 heads x 64, r = 256, 16 sequences: 64 slots 12.8 / 8.8, 256 13.1 / 10.7, 512 13.3 / 13.2, 768 13.7 / 14.6; 64: 64 slots
+  //     13.1 / 9.9, 512 18.6 / 14.5; 128: 64 slots 13.8 / 12.9, 512 21.8 / 18.8; 20 heads, 64 sequences: 64 slots 16.1 / 16.2
+  //   bf16, 8 heads x 128, r = 256, 16 sequences: 64 slots 14.0 / 9.6, 384 14.2 / 13.4, 512 14.4 / 14.3; 64: 256 15.7 / 15.1; 128: 256 20.7 / 23
+  //   bf16, 16 heads x 128, r = 512, 16 sequences: 64 slots 20.9 / 12.7, 384 23.1 / 20.1, 640 24.1 / 25.6; 32: 256 25.1 / 22.4; 48: 25.9 / 30.8
   const size_t jobs = (size_t)a.n_heads * a.batch;
   if (dtype == 0)  // fp32
     return (a.r == 64 || a.r == 128 || a.r == 256) && (a.d_rope == 32 || a.d_rope == 64) && w.d_head % 64 == 0 && jobs <= 512 &&
            a.max_slots <= (a.r == 256 ? 512 : 768);
-  const int most = a.r == 128 ? (jobs <= 256 ? 320 : 256) : 256;
-  return (a.r == 128 || a.r == 256 || a.r == 512) && ((w.d_head == 64 && a.d_rope == 32) || (w.d_head == 128 && a.d_rope == 64)) &&
-         jobs <= (a.r == 128 ? 512 : 256) && a.max_slots <= most;
+  const bool narrow = w.d_head == 64 && a.d_rope == 32, wide = w.d_head == 128 && a.d_rope == 64;
+  if (!narrow && !wide) return false;
+  if (a.r == 128) return jobs <= 1024 && a.max_slots <= (jobs <= 256 ? 768 : 640);
+  if (a.r == 256 && narrow) return jobs <= 1024 && a.max_slots <= 512;
+  return (a.r == 256 || a.r == 512) && jobs <= 512 && a.max_slots <= (jobs > 256 ? 256 : (a.r == 256 ? 448 : 384));
 }
 
 hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, const EventPair& ev) {
@@ -441,8 +500,14 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
 #undef MTLA_CASE
     return hipErrorInvalidValue;
   }
+  // r = 128, long: eight wavefronts, two per SIMD, hide more of a tile's chain than their meeting costs (16 sequences of 8 heads:
+  // 512 slots 10.5 us a step with four, 10.0 with eight; 128 slots 7.7 / 8.3.  r = 256: 512 slots 13.2 either way)
+  if (a.r == 128 && a.max_slots > 320) {
+    if (a.d_rope == 32 && w.d_head == 64) return launch_heads<128, 32, 64, 8>(w, st, ev);
+    if (a.d_rope == 64 && w.d_head == 128) return launch_heads<128, 64, 128, 8>(w, st, ev);
+  }
 #define MTLA_CASE(RR, DD, HH) \
-  if (a.r == RR && a.d_rope == DD && w.d_head == HH) return launch_form<RR, DD, HH>(w, st, ev);
+  if (a.r == RR && a.d_rope == DD && w.d_head == HH) return launch_heads<RR, DD, HH, 4>(w, st, ev);
   MTLA_CASE(128, 32, 64)
   MTLA_CASE(256, 32, 64)
   MTLA_CASE(512, 32, 64)

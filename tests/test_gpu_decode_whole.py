@@ -17,13 +17,21 @@ def _workload(dtype, n_heads, d_head, r, stride, plen, steps=2):
 
 
 @pytest.mark.parametrize("dtype,n_heads,d_head,r,stride,plen", [
-    ("bf16", 8, 64, 128, 1, (1, 14, 15, 16, 62, 63, 64, 65, 127, 128, 318)),   # 320 slots: the most there
+    ("bf16", 8, 64, 128, 1, (1, 14, 15, 16, 62, 63, 64, 65, 127, 128, 318)),      # four wavefronts, 320 slots
+    ("bf16", 8, 64, 128, 1, (1, 2, 16, 17, 127, 128, 129, 130, 255, 257, 765, 766)),  # eight, 768: the most there
     ("bf16", 21, 64, 128, 2, (1, 2, 31, 33, 126, 127, 128, 129, 300, 400, 508)),  # more than 16 heads
-    ("bf16", 8, 64, 256, 1, (1, 15, 17, 63, 65, 129, 191, 193, 254)),          # three steps in flight
-    ("bf16", 5, 128, 256, 2, (1, 3, 127, 129, 383, 510)),
-    ("bf16", 3, 64, 512, 1, (1, 64, 129, 254)),
-    ("bf16", 4, 128, 512, 1, (1, 16, 62, 63, 64, 65, 128, 129, 254)),          # two
+    ("bf16", 9, 64, 128, 1, tuple(range(1, 138, 3))),                             # two heads a workgroup, one left over
+    ("bf16", 11, 64, 128, 2, tuple(range(1, 700, 10))),                           # four, three left over; eight wavefronts
+    ("bf16", 8, 64, 256, 1, (1, 15, 17, 63, 65, 129, 191, 193, 510)),
+    ("bf16", 7, 64, 256, 1, tuple(range(2, 90, 2))),
+    ("bf16", 13, 64, 256, 3, tuple(range(1, 220, 4))),
+    ("bf16", 5, 128, 256, 2, (1, 3, 127, 129, 383, 510, 894)),
+    ("bf16", 13, 128, 256, 1, tuple(range(1, 150, 7))),
+    ("bf16", 3, 64, 512, 1, (1, 64, 129, 254, 382)),
+    ("bf16", 4, 128, 512, 1, (1, 16, 62, 63, 64, 65, 128, 129, 382)),
+    ("bf16", 15, 128, 512, 2, tuple(range(1, 160, 8))),
     ("bf16", 1, 128, 128, 3, (1, 2, 3, 4, 190, 191, 192, 193, 194)),
+    ("bf16", 18, 128, 128, 1, tuple(range(1, 400, 25))),
     ("f32", 4, 64, 64, 1, (1, 7, 8, 9, 63, 64, 65, 500, 766)),
     ("f32", 3, 128, 128, 2, (1, 15, 17, 129, 700)),                            # two passes over the output columns
     ("f32", 8, 64, 256, 1, (1, 31, 33, 64, 300, 510)),
