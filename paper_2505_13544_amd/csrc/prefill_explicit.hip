@@ -760,13 +760,16 @@ static float gemm_cost(const GemmArgs& a, int& pick) {
   static constexpr struct { int bm, bn; float base, round, k; } kTiles[] = {
       {256, 256, 5.f, 4.7f, 0.028f}, {256, 128, 5.f, 2.5f, 0.0152f}, {128, 128, 3.2f, 0.5f, 0.0112f}, {64, 64, 2.2f, 0.5f, 0.004f}};
   const bool ragged = a.rows.n_new || a.rows.pos0;
-  const float n_seq = ragged ? (float)(a.M / (a.rows.past + a.rows.T)) : 1.f, K = (float)a.K;
+  const int Tp = ragged ? a.rows.past + a.rows.T : a.M;
+  const float n_seq = ragged ? (float)(a.M / Tp) : 1.f, K = (float)a.K;
   // a ragged launch with as many jobs as this may find them all: it is not taken for less than a round
   auto rounds_of = [&](int bm, int bn, bool packed) -> float {
-    const float cols = (float)gemm_col_blocks(a, bn), most = (float)((a.M + bm - 1) / bm);
+    // (rows that are not packed: every sequence starts a block of its own, however short it is)
+    const float cols = (float)gemm_col_blocks(a, bn);
+    const float most = packed || !ragged ? (float)((a.M + bm - 1) / bm) : n_seq * (float)((Tp + bm - 1) / bm);
     if (!ragged) return cols * most / 256.f;
     if (cols * most <= 256.f) return cols * most / 256.f;
-    return packed ? 0.75f * cols * most / 256.f + 0.5f : cols * (0.75f * (float)a.M / (float)bm + 0.5f * n_seq) / 256.f;
+    return packed ? 0.75f * cols * most / 256.f + 0.5f : cols * fmaxf(0.75f * (float)a.M / (float)bm + 0.5f * n_seq, n_seq) / 256.f;
   };
   float best = 0.f;
   pick = 0;
