@@ -19,7 +19,7 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------------------
-// bf16 storage.  Every wavefront walks 16-slot tiles of its own (tile t belongs to wavefront t mod 4) with a softmax state of
+// bf16 storage.  Every wavefront walks 16-slot tiles of its own (tile t belongs to wavefront t mod NW) with a softmax state of
 // its own; the states meet once, behind the last tile.  No barrier stands in the walk.  Tiles come memory -> LDS in whole
 // rows, one ahead of the one being multiplied (rows straight into the operand layout, 64 bytes of each of 16 rows a
 // request, took twice as long), and the logits' layout [slot, column] is the K = 16 operand of the product with the latent
@@ -37,12 +37,15 @@ constexpr int kWaves = kBlock / kWave;
 template <int R, int DR, int HPW, int NW>
 struct WholeGeom {
   static constexpr int tile = 16 * (R + DR) * 2;  // [latent rows][RoPE keys]
-  static constexpr int area = 2 * tile;           // a wavefront's two
+  static constexpr int query = (2 * HPW * (R + DR) * 2 + 1023) / 1024 * 1024;  // [plane][head][R + DR], whole requests
+  static constexpr bool query_lds = R < 512;  // (its tiles fill the LDS)
+  static constexpr int area = 2 * tile + (query_lds ? query : 0);  // a wavefront's two tiles, its copy of the query
   static constexpr int bytes = NW * area;
   // behind the walk an area holds its wavefront's sums, two planes a head, and (m, l); the first one also the planes of the result
   static constexpr int ml = 2 * HPW * R * 4, planes = ml + 64, plane = R * 2 + 64;
-  static_assert(bytes <= 160 * 1024 && planes + 2 * HPW * plane <= area && planes % 16 == 0 && 8 * HPW <= 64, "LDS of one compute unit");
-  static constexpr int per_simd = NW / 4 * (2 * bytes <= 160 * 1024 ? 2 : 1);
+  static_assert(bytes <= 160 * 1024 && planes + 2 * HPW * plane <= 2 * tile && planes % 16 == 0 && 8 * HPW <= 64, "LDS of one compute unit");
+  // register budget: 256 and fewer stay clear of copies to and from the accumulation registers
+  static constexpr int per_simd = NW / 4 * (4 * NW * tile <= 160 * 1024 ? 2 : 1);
 };
 
 template <int R, int DR, int DH, int HPW, int NW, bool SH, bool PG>
@@ -115,13 +118,30 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
       for (int c = 0; c < DR / 32; ++c) load_to_lds_16(key + row * DR, at_key[c] < end_key ? at_key[c] : end_key, to_key + 1024u * c);
     }
   };
-  // first rows, length (a scalar load), query and W_V^(h) are requested together
+  // Length (a scalar load), first rows and query are requested together, then the second rows and, where there are registers for
+  // it during the walk, W_V^(h) (second rows behind W_V^(h): 16 sequences of 8 heads x 64, r = 256, 384 slots 11.1 -> 11.5 us a step).
+  constexpr bool kEarly = 4 * (KT + MT + NT * KC) <= (G::per_simd > 1 ? 180 : 250);
+  constexpr bool kNext = G::query_lds && kEarly;
   const auto place0 = std::integral_constant<int, 0>{};
   const auto place1 = std::integral_constant<int, 1>{};
+  int len;  // nothing writes it while the kernel runs
+  if constexpr (kNext) len = load_uniform_i32(a.seq_len, b);
   if (tile_base(0) < a.max_slots) issue(0, a.max_slots - 1, place0);
-  const int len = load_uniform_i32(a.seq_len, b);  // nothing writes it while the kernel runs
+  if constexpr (!kNext) len = load_uniform_i32(a.seq_len, b);
+  // Sixteen columns' fragments straight from memory are a full request for every 128 bytes of a head's query, as slow as the rows;
+  // a copy in LDS is a request or two.
   u32x4_t q[KT];
-  {
+  unsigned char* own_q = area + 2 * G::tile;
+  if constexpr (G::query_lds) {
+    constexpr int QP = HPW * (R + DR) / 8;  // 16-byte pieces of a plane
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.qcat) + ((size_t)b * a.n_heads + h0) * (R + DR);
+    const int most = (a.n_heads - h0 < HPW ? a.n_heads - h0 : HPW) * ((R + DR) / 8) - 1;  // heads there are none of: copies
+#pragma unroll
+    for (int c = 0; c < G::query / 1024; ++c) {
+      const int at = 64 * c + lane, i = at < QP ? at : at - QP;
+      load_to_lds_16(qp + (at < QP ? 0 : a.q_plane) + 8 * (i < most ? i : most), area0 + (uint32_t)(2 * G::tile) + 1024u * c);
+    }
+  } else {
     const int h = h0 + (l16 >> 1) % HPW;
     const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.qcat) +
                          ((size_t)b * a.n_heads + (h < a.n_heads ? h : a.n_heads - 1)) * (R + DR) + 8 * g + ((l16 & 1) ? a.q_plane : 0);
@@ -137,16 +157,30 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
 #pragma unroll
       for (int kk = 0; kk < KC; ++kk) wf[i][kk] = *reinterpret_cast<const u32x4_t*>(wp + 16 * i * R + 32 * kk);
   };
-  constexpr bool kEarly = 4 * (KT + MT + NT * KC) <= (G::per_simd > 1 ? 180 : 250);  // registers for W_V^(h) during the walk
   const bool multiplies = OT >= NW || wv < OT;  // (a wavefront too many has no output columns)
-  if (kEarly && multiplies) load_w(h0);
+  if (!kNext && kEarly && multiplies) load_w(h0);
   const int live = (len + a.stride - 1) / a.stride, tiles = (live + 15) / 16;
   const int mine = tiles > wv ? (tiles - wv + NW - 1) / NW : 0;
-  if (kEarly && multiplies) wait_loads_but<NT * KC>();  // the first rows and the query: W_V^(h) may still travel
-  else wait_loads_but<0>();
+  constexpr int W = kEarly ? NT * KC : 0;
+  auto wait_but_w = [&](auto others) {  // and W_V^(h)
+    if (multiplies) wait_loads_but<decltype(others)::value + W>();
+    else wait_loads_but<decltype(others)::value>();
+  };
+  const auto none = std::integral_constant<int, 0>{};
+  const auto one_tile = std::integral_constant<int, KT>{};
+  if (kNext && mine > 1) issue(1, live - 1, place1);
+  if (kNext && multiplies) load_w(h0);
+  if (kNext && mine > 1) wait_but_w(one_tile);
+  else wait_but_w(none);
+  if constexpr (G::query_lds) {
+    const unsigned char* qp = own_q + ((l16 & 1) * HPW + (l16 >> 1) % HPW) * (R + DR) * 2 + 16 * g;
 #pragma unroll
-  for (int kk = 0; kk < KT; ++kk) asm volatile("" : "+v"(q[kk]));  // (and the compiler waits here, not behind the next tiles' loads)
-  if (mine > 1) issue(1, live - 1, place1);
+    for (int kk = 0; kk < KT; ++kk) q[kk] = *reinterpret_cast<const u32x4_t*>(qp + 64 * kk);
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < KT; ++kk) asm volatile("" : "+v"(q[kk]));  // (the compiler waits here, not behind the next tile's loads)
+  }
+  if (!kNext && mine > 1) issue(1, live - 1, place1);
 
   float m_ref = -INFINITY, l_run = 0.f;  // of the column's head; l_run: this lane's slots only
   float4_t acc[MT];
@@ -157,8 +191,11 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   auto step = [&](int k, auto place) {
     unsigned char* rows = area + decltype(place)::value * G::tile;
     const int base = tile_base(k);
-    if (k > 0) {
-      if (k + 1 < mine) wait_loads_but<KT>();  // the tile behind it may travel on
+    if (kNext && k == 1) {  // W_V^(h) and the tile behind it may travel on
+      if (k + 1 < mine) wait_but_w(one_tile);
+      else wait_but_w(none);
+    } else if (k > 0) {
+      if (k + 1 < mine) wait_loads_but<KT>();
       else wait_loads_but<0>();
     } else if (live < base + 16) {
       // rows of the first tile that no slot stands for may never have been written: zeros, or 0 x NaN would reach the sums
@@ -466,12 +503,13 @@ bool attn_whole_supported(const WholeArgs& w, int dtype) {
   // launches / two:
   //   fp32, 8 heads x 64, r = 256, 8 sequences: 64 slots 15.9 / 9.4, 512 18.2 / 17.0, 640 18.8 / 19.3
   //   fp32, 4 heads x 64, r = 64, 1 sequence: 128 slots 10.2 / 7.1, 768 12.2 / 11.2, 1024 12.7 / 12.8
-  //   bf16, 8 heads x 64, r = 128, 16 sequences: 64 slots 11.1 / 7.4, 640 12.4 / 10.5; 128: 64 slots 11.2 / 9.3, 640 18.9 / 13.9;
+  //   bf16, 8 heads x 64, r = 128, 16 sequences: 64 slots 11.1 / 7.0, 640 12.5 / 10.0; 128: 64 slots 11.2 / 9.1, 640 18.7 / 13.4;
   //     200 (400 workgroups of four heads): 64 slots 11.8 / 11.3, 384 19.6 / 16.5
-  //   bf16, 8 heads x 64, r = 256, 16 sequences: 64 slots 12.8 / 8.8, 256 13.1 / 10.7, 512 13.3 / 13.2, 768 13.7 / 14.6; 64: 64 slots
-  //     13.1 / 9.9, 512 18.6 / 14.5; 128: 64 slots 13.8 / 12.9, 512 21.8 / 18.8; 20 heads, 64 sequences: 64 slots 16.1 / 16.2
-  //   bf16, 8 heads x 128, r = 256, 16 sequences: 64 slots 14.0 / 9.6, 384 14.2 / 13.4, 512 14.4 / 14.3; 64: 256 15.7 / 15.1; 128: 256 20.7 / 23
-  //   bf16, 16 heads x 128, r = 512, 16 sequences: 64 slots 20.9 / 12.7, 384 23.1 / 20.1, 640 24.1 / 25.6; 32: 256 25.1 / 22.4; 48: 25.9 / 30.8
+  //   bf16, 8 heads x 64, r = 256, 16 sequences: 64 slots 12.6 / 8.0, 256 13.1 / 10.0, 528 13.4 / 12.3, 640 13.4 / 13.1; 64: 64 slots
+  //     13.1 / 9.5, 576 18.5 / 14.8; 128: 64 slots 13.8 / 12.4, 576 22.9 / 18.9; 20 heads, 64 sequences: 64 slots 16.1 / 16.2
+  //   bf16, 8 heads x 128, r = 256, 16 sequences: 64 slots 13.8 / 8.5, 512 14.4 / 13.5; 64: 64 slots 14.5 / 11.3, 384 19.3 / 15.3; 128: 64
+  //     slots 15.4 / 17
+  //   bf16, 16 heads x 128, r = 512, 16 sequences: 64 slots 20.9 / 12.9, 384 23.0 / 20.0, 640 24.1 / 25.6; 32: 256 25.1 / 22.4; 48: 25.9 / 30.8
   const size_t jobs = (size_t)a.n_heads * a.batch;
   if (dtype == 0)  // fp32
     return (a.r == 64 || a.r == 128 || a.r == 256) && (a.d_rope == 32 || a.d_rope == 64) && w.d_head % 64 == 0 && jobs <= 512 &&
@@ -479,8 +517,9 @@ bool attn_whole_supported(const WholeArgs& w, int dtype) {
   const bool narrow = w.d_head == 64 && a.d_rope == 32, wide = w.d_head == 128 && a.d_rope == 64;
   if (!narrow && !wide) return false;
   if (a.r == 128) return jobs <= 1024 && a.max_slots <= (jobs <= 256 ? 768 : 640);
-  if (a.r == 256 && narrow) return jobs <= 1024 && a.max_slots <= 512;
-  return (a.r == 256 || a.r == 512) && jobs <= 512 && a.max_slots <= (jobs > 256 ? 256 : (a.r == 256 ? 448 : 384));
+  if (a.r == 256 && narrow) return jobs <= 1024 && a.max_slots <= (jobs <= 256 ? 640 : 576);
+  if (a.r == 256) return jobs <= 512 && a.max_slots <= (jobs > 256 ? 384 : 512);
+  return a.r == 512 && jobs <= 512 && a.max_slots <= (jobs > 256 ? 256 : 384);
 }
 
 hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, const EventPair& ev) {
@@ -500,12 +539,15 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
 #undef MTLA_CASE
     return hipErrorInvalidValue;
   }
-  // r = 128, long: eight wavefronts, two per SIMD, hide more of a tile's chain than their meeting costs (16 sequences of 8 heads:
-  // 512 slots 10.5 us a step with four, 10.0 with eight; 128 slots 7.7 / 8.3.  r = 256: 512 slots 13.2 either way)
+  // Long: eight wavefronts, two per SIMD, hide more of a tile's chain than their meeting costs (16 sequences of 8 heads, us a step
+  // with four / eight: r = 128: 128 slots 7.7 / 8.3, 512 10.5 / 10.0; r = 256: 384 slots 11.1 / 11.5, 528 12.9 / 12.3, where several
+  // heads' queries leave no room for them)
   if (a.r == 128 && a.max_slots > 320) {
     if (a.d_rope == 32 && w.d_head == 64) return launch_heads<128, 32, 64, 8>(w, st, ev);
     if (a.d_rope == 64 && w.d_head == 128) return launch_heads<128, 64, 128, 8>(w, st, ev);
   }
+  if (a.r == 256 && a.d_rope == 32 && w.d_head == 64 && a.max_slots > 448 && (size_t)a.n_heads * a.batch <= 256)
+    return launch_form<256, 32, 64, 1, 8>(w, st, ev);
 #define MTLA_CASE(RR, DD, HH) \
   if (a.r == RR && a.d_rope == DD && w.d_head == HH) return launch_heads<RR, DD, HH, 4>(w, st, ev);
   MTLA_CASE(128, 32, 64)

@@ -23,10 +23,11 @@ def _workload(dtype, n_heads, d_head, r, stride, plen, steps=2):
     ("bf16", 9, 64, 128, 1, tuple(range(1, 138, 3))),                             # two heads a workgroup, one left over
     ("bf16", 11, 64, 128, 2, tuple(range(1, 700, 10))),                           # four, three left over; eight wavefronts
     ("bf16", 8, 64, 256, 1, (1, 15, 17, 63, 65, 129, 191, 193, 510)),
+    ("bf16", 8, 64, 256, 1, (1, 31, 33, 127, 129, 255, 256, 257, 385, 638)),      # eight wavefronts, the most there
     ("bf16", 7, 64, 256, 1, tuple(range(2, 90, 2))),
     ("bf16", 13, 64, 256, 3, tuple(range(1, 220, 4))),
-    ("bf16", 5, 128, 256, 2, (1, 3, 127, 129, 383, 510, 894)),
-    ("bf16", 13, 128, 256, 1, tuple(range(1, 150, 7))),
+    ("bf16", 5, 128, 256, 2, (1, 3, 127, 129, 383, 510, 1022)),
+    ("bf16", 13, 128, 256, 1, tuple(range(1, 383, 17))),
     ("bf16", 3, 64, 512, 1, (1, 64, 129, 254, 382)),
     ("bf16", 4, 128, 512, 1, (1, 16, 62, 63, 64, 65, 128, 129, 382)),
     ("bf16", 15, 128, 512, 2, tuple(range(1, 160, 8))),
