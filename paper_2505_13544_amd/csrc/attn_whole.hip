@@ -504,7 +504,8 @@ bool attn_whole_supported(const WholeArgs& w, int dtype) {
   //   fp32, 8 heads x 64, r = 256, 8 sequences: 64 slots 15.9 / 9.4, 512 18.2 / 17.0, 640 18.8 / 19.3
   //   fp32, 4 heads x 64, r = 64, 1 sequence: 128 slots 10.2 / 7.1, 768 12.2 / 11.2, 1024 12.7 / 12.8
   //   bf16, 8 heads x 64, r = 128, 16 sequences: 64 slots 11.1 / 7.0, 640 12.5 / 10.0; 128: 64 slots 11.2 / 9.1, 640 18.7 / 13.4;
-  //     200 (400 workgroups of four heads): 64 slots 11.8 / 11.3, 384 19.6 / 16.5
+  //     240 (480 workgroups of four heads): 64 slots 12.4 / 11.3, 256 19.0 / 14.1, 384 21.1 / 19.9; 16 heads, 240 sequences: 64 slots
+  //     13.6 / 16.6
   //   bf16, 8 heads x 64, r = 256, 16 sequences: 64 slots 12.6 / 8.0, 256 13.1 / 10.0, 528 13.4 / 12.3, 640 13.4 / 13.1; 64: 64 slots
   //     13.1 / 9.5, 576 18.5 / 14.8; 128: 64 slots 13.8 / 12.4, 576 22.9 / 18.9; 20 heads, 64 sequences: 64 slots 16.1 / 16.2
   //   bf16, 8 heads x 128, r = 256, 16 sequences: 64 slots 13.8 / 8.5, 512 14.4 / 13.5; 64: 64 slots 14.5 / 11.3, 384 19.3 / 15.3; 128: 64
@@ -516,7 +517,8 @@ bool attn_whole_supported(const WholeArgs& w, int dtype) {
            a.max_slots <= (a.r == 256 ? 512 : 768);
   const bool narrow = w.d_head == 64 && a.d_rope == 32, wide = w.d_head == 128 && a.d_rope == 64;
   if (!narrow && !wide) return false;
-  if (a.r == 128) return jobs <= 1024 && a.max_slots <= (jobs <= 256 ? 768 : 640);
+  if (a.r == 128 && jobs > 1024) return narrow && jobs <= 2048 && a.max_slots <= 320;  // (two workgroups a unit)
+  if (a.r == 128) return a.max_slots <= (jobs <= 256 ? 768 : 640);
   if (a.r == 256 && narrow) return jobs <= 1024 && a.max_slots <= (jobs <= 256 ? 640 : 576);
   if (a.r == 256) return jobs <= 512 && a.max_slots <= (jobs > 256 ? 384 : 512);
   return a.r == 512 && jobs <= 512 && a.max_slots <= (jobs > 256 ? 256 : 384);

@@ -22,6 +22,7 @@ def _workload(dtype, n_heads, d_head, r, stride, plen, steps=2):
     ("bf16", 21, 64, 128, 2, (1, 2, 31, 33, 126, 127, 128, 129, 300, 400, 508)),  # more than 16 heads
     ("bf16", 9, 64, 128, 1, tuple(range(1, 138, 3))),                             # two heads a workgroup, one left over
     ("bf16", 11, 64, 128, 2, tuple(range(1, 700, 10))),                           # four, three left over; eight wavefronts
+    ("bf16", 31, 64, 128, 1, tuple(range(1, 319, 8))),                            # more workgroups than compute units
     ("bf16", 8, 64, 256, 1, (1, 15, 17, 63, 65, 129, 191, 193, 510)),
     ("bf16", 8, 64, 256, 1, (1, 31, 33, 127, 129, 255, 256, 257, 385, 638)),      # eight wavefronts, the most there
     ("bf16", 7, 64, 256, 1, tuple(range(2, 90, 2))),
