@@ -774,7 +774,14 @@ static float gemm_cost(const GemmArgs& a, int& pick) {
   float best = 0.f;
   pick = 0;
   for (int i = 0; i < 4; ++i) {
-    const float rounds = ceilf(rounds_of(kTiles[i].bm, kTiles[i].bn, a.rows.zeros));
+    float of = rounds_of(kTiles[i].bm, kTiles[i].bn, a.rows.zeros);
+    if (ragged && i < 2) {
+      // A row block's tiles are one XCD's: few blocks of many rows leave some XCDs two and others one (7 sequences of 137 to 551
+      // rows, 2112 columns, K = 1024: 14 blocks in 256 x 128 tiles 36.4 us, 22 in 128 x 128 25.8)
+      const float cols = (float)gemm_col_blocks(a, kTiles[i].bn), blocks = 256.f * of / cols;
+      if (blocks >= 8.f) of = ceilf(blocks / 8.f) * cols / 32.f;
+    }
+    const float rounds = ceilf(of);
     float cost = kTiles[i].base + rounds * (kTiles[i].round + kTiles[i].k * K);
     if (i == 3 && rounds > 2.f) cost += 0.6f;  // (two fit on a unit)
     if (i == 0 || cost < best) {
