@@ -35,10 +35,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # runs of this script, each counter scaled by its reading for a plain 256 MiB device copy
 # (profiles/decode_attention_hbm_traffic.md), as a line in the launch's algorithmic bytes (the live cache
 # rows): traffic = fixed + slope * algorithmic.  The headline workload was measured at two step counts
-# (20 and 256 steps: 7.245 MB for 4.772 MB, 8.092 MB for 5.307 MB), which fixes both numbers: an interpolation
-# between the two, since the traffic grows by whole chunks of 64 slots; the other workloads were measured once, so
+# (20 and 256 steps: 7.233 MB for 4.772 MB, 7.763 MB for 5.307 MB), which fixes both numbers; the other workloads were measured once, so
 # their line goes through the origin.
-MEASURED_TRAFFIC_LINE = {"speech_bf16": (-0.313e6, 1.584),
+MEASURED_TRAFFIC_LINE = {"speech_bf16": (2.504e6, 0.991),
                          "ragged_bf16": (0.0, (357206.0 + 11557.0) * 1024 / 339.5e6),
                          "long_bf16": (0.0, (78732.8 + 8062.6) * 1024 / 75.5e6),
                          "speech_b1024_bf16": (0.0, (306855.8 + 4164.1) * 1024 / 304.6e6)}
@@ -365,7 +364,7 @@ def main():
         "eager_ms_per_step": statistics.median(eager_ms),
         "eager_tokens_per_s": B / (statistics.median(eager_ms) * 1e-3),
         "step_effective_GBps": step_bytes / (ms_per_step * 1e-3) / 1e9,
-        "roofline": {"bound": "hbm", "kernel": "decode attention over cache slots (split pass)",
+        "roofline": {"bound": "hbm", "kernel": "decode attention over cache slots (short sequences: with the value projection)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "streaming_probe_GBps": probe_gbs,
                      "frac_of_streaming_probe": achieved / probe_gbs,
