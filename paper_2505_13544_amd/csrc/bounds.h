@@ -1,0 +1,22 @@
+// What lengths and starts out of the caller's arrays count as.  They are read on the device, where nothing can return an error
+// in front of the launch, so every kernel takes them through the functions here and all of them agree.
+#pragma once
+
+namespace mtla {
+
+// The slots in front of a sequence's new rows.  A start outside the `past` slots that the call declared counts as all of them
+// (the front launch raises the status word): no kernel leaves its arrays, and the sequence's rows are meaningless.  (As an
+// unsigned number a start below zero lies above every slot that past * stride < 2^31 tokens can have.)
+[[gnu::always_inline]] constexpr int slots_inside(int pos0, int stride, int past) {
+  const unsigned k = (unsigned)pos0 / (unsigned)stride;
+  return k < (unsigned)past ? (int)k : past;
+}
+// The tokens in front of them: the start itself, or those of the whole past.
+[[gnu::always_inline]] constexpr int start_inside(int pos0, int stride, int past) {
+  return pos0 >= 0 && (unsigned)pos0 / (unsigned)stride <= (unsigned)past ? pos0 : past * stride;
+}
+
+// The new rows of a sequence, of at most T.  A sequence's part of past + T rows then has slots_inside(..) + new_rows(..) in use.
+[[gnu::always_inline]] constexpr int new_rows(int n_new, int T) { return n_new < 0 ? 0 : (n_new < T ? n_new : T); }
+
+}  // namespace mtla

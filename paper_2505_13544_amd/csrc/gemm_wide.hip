@@ -13,6 +13,8 @@
 // PFLOP/s); 33 ragged row blocks x 4096 x 512 51 -> 42; 20 ragged row blocks 39 -> 28, of which the cut last round is 6.
 #include <type_traits>
 
+#include "bounds.h"
+#include "gemm_jobs.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -23,7 +25,7 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-constexpr int kTile = 256, kWideThreads = 512, kWideWaves = 8, kWideWgs = 256;
+constexpr int kTile = kWideTile, kWideThreads = 512, kWideWaves = 8;
 constexpr int kBK = 32, kSlots = 5;        // k of a stage, stages in LDS
 constexpr size_t kStreamOut = (size_t)128 << 20;  // half of the last-level cache
 constexpr int kPark = 4096;                // bytes a wavefront's results pass through on their way out
@@ -36,51 +38,23 @@ struct WideRows {
 __device__ __forceinline__ int used_rows(const GemmArgs& a, int b) {
   const GemmRows& q = a.rows;
   if (!q.pos0 && !q.n_new) return a.M;
-  const int old = q.pos0 ? load_uniform_i32(q.pos0, b) / q.stride : 0;
-  int n = q.n_new ? load_uniform_i32(q.n_new, b) : q.T;
-  n = n < q.T ? n : q.T;
-  return (old < q.past ? old : q.past) + (n > 0 ? n : 0);
+  return (q.pos0 ? slots_inside(load_uniform_i32(q.pos0, b), q.stride, q.past) : 0) +
+         (q.n_new ? new_rows(load_uniform_i32(q.n_new, b), q.T) : q.T);
 }
-struct WideTile {
-  int rb, row_end, nb, z;                  // first row, row behind the last, first column, segment
+struct WideLanes {  // the record, lane by lane
+  const GemmArgs& a;
+  const WideRows& r;
+  int per, pitch;
+  __device__ __forceinline__ int lane_of(int block) const { return __builtin_ctzll(__ballot(block < r.upto)); }
+  __device__ __forceinline__ int upto(int at) const { return __builtin_amdgcn_readlane(r.upto, at); }
+  __device__ __forceinline__ int blocks(int at) const { return __builtin_amdgcn_readlane(r.blocks, at); }
+  __device__ __forceinline__ int used(int at) const { return __builtin_amdgcn_readlane(r.used, at); }
+  __device__ __forceinline__ int used_rows(int b) const { return mtla::used_rows(a, b); }
 };
-// A place in the list of jobs: groups of four column blocks (the last one: what is left) slowest, then the row blocks, then the
-// blocks of the group, so that the jobs side by side on an XCD share their operands in its L2.
-struct WideWalk {
-  unsigned first, rem;                     // first column block of the group, place in the group
-  __device__ __forceinline__ unsigned size(unsigned gx) const { return gx - first < 4u ? gx - first : 4u; }
-  __device__ __forceinline__ void advance(unsigned n, unsigned gx, int n_rb) {
-    rem += n;
-    while (first + 4u < gx && rem >= 4u * (unsigned)n_rb) {
-      rem -= 4u * (unsigned)n_rb;
-      first += 4u;
-    }
-  }
-};
-__device__ __forceinline__ WideTile wide_tile(const GemmArgs& a, const WideRows& r, const WideWalk& w) {
-  const unsigned gsz = w.size((unsigned)a.col_blocks);
-  const unsigned ib = gsz == 4u ? w.rem >> 2 : (gsz == 3u ? w.rem / 3u : (gsz == 2u ? w.rem >> 1 : w.rem));
-  const int at = __builtin_ctzll(__ballot((int)ib < r.upto));
-  int block = (int)ib - (__builtin_amdgcn_readlane(r.upto, at) - __builtin_amdgcn_readlane(r.blocks, at));
-  int b = at, used = __builtin_amdgcn_readlane(r.used, at);
-  if (r.per > 1) {
-    b = at * r.per;
-    used = used_rows(a, b);
-    while (block >= (used + kTile - 1) / kTile) {
-      block -= (used + kTile - 1) / kTile;
-      used = used_rows(a, ++b);
-    }
-  }
-  WideTile t;
-  t.rb = __builtin_amdgcn_readfirstlane(b * r.pitch + block * kTile);  // (the loads' bases have to be scalars)
-  t.row_end = __builtin_amdgcn_readfirstlane(b * r.pitch + (a.rows.zeros ? r.pitch : used));
-  int cb = (int)(w.first + (w.rem - ib * gsz)), z = 0;
-  for (int n = (a.seg[0].N + kTile - 1) / kTile; z + 1 < a.n_seg && cb >= n; n = (a.seg[z].N + kTile - 1) / kTile) {
-    cb -= n;
-    ++z;
-  }
-  t.z = z;
-  t.nb = cb * kTile;
+__device__ __forceinline__ WideTile tile_at(const GemmArgs& a, const WideRows& r, const WideWalk& w) {
+  WideTile t = wide_tile(a, WideLanes{a, r, r.per, r.pitch}, w);
+  t.rb = __builtin_amdgcn_readfirstlane(t.rb);  // (the loads' bases have to be scalars)
+  t.row_end = __builtin_amdgcn_readfirstlane(t.row_end);
   return t;
 }
 
@@ -107,7 +81,7 @@ struct WideStream {
   uint64_t base_w, base_a;
 
   __device__ __forceinline__ WideTile tile(const WideWalk& w) const {
-    WideTile t = wide_tile(a, rows, w);
+    WideTile t = tile_at(a, rows, w);
     t.rb += 128 * (quad >> 1);
     t.nb += 128 * (quad & 1);
     return t;
@@ -146,7 +120,7 @@ struct WideStream {
     to_ask -= 2;
     if ((ld_st += 2) == n_st) {
       ld_st = 0;
-      ld_walk.advance(step, (unsigned)a.col_blocks, rows.n_rb);
+      ld_walk.advance(step, (unsigned)a.col_blocks, (unsigned)rows.n_rb);
     }
   }
 
@@ -329,7 +303,7 @@ struct WideStream {
       leave(cur, acc, lds + (slot == 0 ? kSlots - 1 : slot - 1) * STAGE);  // through the slot that was read last
       static_assert(JM == 8 || (BM < 256 || BN < 256), "only 256 x 256 streams have several tiles");
       stores = a.seg[cur.z].epi == 3 ? 32 : 16;
-      walk.advance(step, (unsigned)a.col_blocks, rows.n_rb);
+      walk.advance(step, (unsigned)a.col_blocks, (unsigned)rows.n_rb);
     }
   }
 };
@@ -366,51 +340,41 @@ __global__ __launch_bounds__(kWideThreads, 2) void gemm_wide_kernel(GemmArgs a) 
       }
     }
   }
+  if (rows.n_rb <= 0) return;  // no rows
 
-  // An XCD (workgroup w runs on XCD w % 8) takes an eighth of the jobs, its 32 workgroups every 32nd of them.  The jobs of
-  // a last round that would leave half of them idle or more are cut into halves or quarters.
-  const unsigned gx = (unsigned)a.col_blocks, xcd = blockIdx.x & 7u, wi = blockIdx.x >> 3, nwg = kWideWgs / 8;
-  const unsigned long long total = (unsigned long long)gx * (unsigned)rows.n_rb;
-  const unsigned lo = (unsigned)(total * xcd / 8u), n = (unsigned)(total * (xcd + 1) / 8u) - lo;
-  const unsigned left = n % nwg, cut = left == 0 ? 0 : (left <= nwg / 4 ? 4 : (left <= nwg / 2 ? 2 : 0));
-  const unsigned whole = cut ? n - left : n;
-  const int n_jobs = wi < whole ? (int)((whole - wi + nwg - 1) / nwg) : 0;
-  const bool part = cut && wi < left * cut;
+  const unsigned gx = (unsigned)a.col_blocks, n_rb = (unsigned)rows.n_rb;
+  const WideShare sh = wide_share(blockIdx.x, gx, n_rb);
   WideWalk at{0u, 0u};
-  at.advance(lo + wi, gx, rows.n_rb);
+  at.advance(sh.first, gx, n_rb);
   WideWalk part_at{0u, 0u};
-  if (part) part_at.advance(lo + whole + (cut == 4 ? wi >> 2 : wi >> 1), gx, rows.n_rb);
+  if (sh.cut) part_at.advance(sh.cut_job, gx, n_rb);
 
   WideStream<BF16, 256, 256> s{a, rows, lds, lane, wv};
   WideStream<BF16, 256, 128> s2{a, rows, lds, lane, wv};
   WideStream<BF16, 128, 128> s4{a, rows, lds, lane, wv};
   bool empty = false;
   auto begin_part = [&]() {
-    if (!part) return;
-    if (cut == 4) {
-      // (a quarter without rows: nothing to do, and none to clear either)
-      const WideTile t = wide_tile(a, rows, part_at);
-      empty = t.rb + 128 * (int)((wi & 3) >> 1) >= t.row_end || t.nb + 128 * (int)(wi & 1) >= a.seg[t.z].N;
-      if (!empty) s4.begin(part_at, 0u, (int)(wi & 3), 1);
-    } else {
-      const WideTile t = wide_tile(a, rows, part_at);
-      empty = t.nb + 128 * (int)(wi & 1) >= a.seg[t.z].N;
-      if (!empty) s2.begin(part_at, 0u, (int)(wi & 1), 1);
-    }
+    if (!sh.cut) return;
+    // (a part without rows or columns: nothing to do, and none to clear either)
+    const WideTile t = tile_at(a, rows, part_at);
+    empty = t.rb + 128 * (sh.part >> 1) >= t.row_end || t.nb + 128 * (sh.part & 1) >= a.seg[t.z].N;
+    if (empty) return;
+    if (sh.cut == 4) s4.begin(part_at, 0u, sh.part, 1);
+    else s2.begin(part_at, 0u, sh.part, 1);
   };
   auto nothing = [&]() {};
   int stores = 0;
-  if (n_jobs > 0) {
-    s.begin(at, nwg, 0, n_jobs);
-    s.run(at, n_jobs, 0, begin_part);
+  if (sh.n_jobs > 0) {
+    s.begin(at, sh.step, 0, sh.n_jobs);
+    s.run(at, sh.n_jobs, 0, begin_part);
     WideWalk last = at;
-    last.advance((unsigned)(n_jobs - 1) * nwg, gx, rows.n_rb);
-    stores = a.seg[wide_tile(a, rows, last).z].epi == 3 ? 32 : 16;
+    last.advance((unsigned)(sh.n_jobs - 1) * sh.step, gx, n_rb);
+    stores = a.seg[tile_at(a, rows, last).z].epi == 3 ? 32 : 16;
   } else {
     begin_part();
   }
-  if (!part || empty) return;
-  if (cut == 4) s4.run(part_at, 1, stores, nothing);
+  if (!sh.cut || empty) return;
+  if (sh.cut == 4) s4.run(part_at, 1, stores, nothing);
   else s2.run(part_at, 1, stores, nothing);
 }
 

@@ -30,6 +30,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "bounds.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -103,9 +104,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
     const GemmRows& q = a.rows;
     const int Tp = q.past + q.T, n_seq = M / Tp;
     auto used_rows = [&](int b) {
-      const int old = q.pos0 ? q.pos0[b] / q.stride : 0;
-      const int n = q.n_new ? (q.n_new[b] < q.T ? q.n_new[b] : q.T) : q.T;
-      return (old < q.past ? old : q.past) + (n > 0 ? n : 0);
+      return (q.pos0 ? slots_inside(q.pos0[b], q.stride, q.past) : 0) + (q.n_new ? new_rows(q.n_new[b], q.T) : q.T);
     };
     if (q.zeros) {  // the block as it is; without rows of its own it only writes zeros
       for (int b = rb / Tp; b < n_seq && b * Tp < rb + BM && !work; ++b) {
@@ -333,8 +332,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   // A continuing sequence has p0 tokens behind it: the final states of its first p0 / s slots are the
   // first rows of its part of the key / value arrays (one per slot), its new rows follow.
   const int Tp = (CONT ? a.past_pitch : 0) + T;
-  int p0 = CONT ? a.pos0[b] : 0;
-  if (CONT && (p0 < 0 || p0 / s > a.past_pitch)) p0 = a.past_pitch * s;  // out of range (reported by the front launch): stay inside the arrays
+  const int p0 = CONT ? start_inside(a.pos0[b], s, a.past_pitch) : 0;
   const int j0 = p0 / s, past = j0;
   if (CONT && a.advance && unit == 0 && h == 0) {
     const long long end = (long long)a.pos0[b] + (len > 0 ? len : 0);

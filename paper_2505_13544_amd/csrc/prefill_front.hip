@@ -13,6 +13,7 @@
 // it launches that wait for one another; as one launch 13.
 #include <type_traits>
 
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -90,7 +91,7 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
   constexpr int KK = R / 32, NP = R >= 128 ? R / 128 : 1;      // a thread merges pieces q, q + 16, .. of 8 elements
   const bool hyper = !a.w_override && 16 * wv < dy;
   int past = 0;  // rows of cprime in front of the new ones
-  if constexpr (STAGE) past = p0 / s < fa->cs.past_pitch ? p0 / s : fa->cs.past_pitch;
+  if constexpr (STAGE) past = slots_inside(p0, s, fa->cs.past_pitch);
 
   // ---- requests that need nothing but the position: the wavefront's rows of hyp_A, the slot in progress
   u32x4_t af[KK];
@@ -324,16 +325,12 @@ __global__ __launch_bounds__(kBlock) void append_bulk_kernel(AppendArgs a) {
   append_block<R, false, false>(a, nullptr, blockIdx.x, blockIdx.y, sh);
 }
 
-// Tokens before the new rows, forced into what the arrays hold.
+// Tokens before the new rows, forced into what the arrays hold (the declared past is at most the capacity).
 __device__ __forceinline__ int start_of(const ChunkStageArgs& a, int b) {
   if (!a.pos0) return 0;  // whole sequences
-  const int p0 = a.pos0[b], s = a.stride, past = a.past_pitch;
-  if (p0 < 0 || p0 / s > past || p0 / s > a.max_slots) {
-    *a.status = 1;  // MTLA_ERR_INVALID_ARG
-    const int lim = past < a.max_slots ? past : a.max_slots;
-    return lim * s;
-  }
-  return p0;
+  const int p0 = a.pos0[b], inside = start_inside(p0, a.stride, a.past_pitch);
+  if (inside != p0) *a.status = 1;  // MTLA_ERR_INVALID_ARG
+  return inside;
 }
 
 // 16-byte pieces: slot states and RoPE keys of the past (rows k < pos0 / s of a sequence's part of cprime and kr16), and

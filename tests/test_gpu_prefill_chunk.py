@@ -150,6 +150,41 @@ def test_chunk_start_outside_the_declared_past_is_reported():
     del keep, keep2
 
 
+def test_chunk_start_outside_the_declared_past_leaves_the_other_sequences_alone():
+    # At a size whose key / value product is a stream of 256 x 256 tiles over all compute units, cut by the rows in use: a start
+    # outside counts as the whole declared past, so that the other sequence's tiles are those of a call without it.
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="pf_chunk_bad_stream", batch=2, d_model=64, n_heads=16, d_head=128, r=512,
+                                           d_rope=64, stride=2, prefix=8, steps=0, seed=6)
+    past, T = 1500, 510
+    wts = W.make_weights(wl)
+    sess = H.make_session(wl, max_slots=past + T)
+    H.upload_weights(sess, wts)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    bf = lambda *s: torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16)
+    sess.cache_c.copy_(bf(*sess.cache_c.shape))
+    sess.cache_kr.copy_(bf(*sess.cache_kr.shape))
+    q, q_rope, c, kr = bf(2, T, 16, 128), bf(2, T, 16, 64), bf(2, T, 512), bf(2, T, 64)
+    tail, w = bf(2, 512).float(), torch.rand(2, T, device="cuda", generator=g)
+    ws = torch.empty(sess.ctx.prefill_chunk_workspace_bytes(2, T, past), dtype=torch.uint8, device="cuda")
+
+    def attend(starts):
+        out = torch.full((2, T, 16, 128), 9.0, device="cuda")
+        pos0 = torch.tensor(starts, dtype=torch.int32, device="cuda")
+        sess.ctx.prefill_chunk_attn(sess.cache_c, sess.cache_kr, tail, pos0, q, q_rope, c, kr, w, None, 2, T, past, sess.w_uk,
+                                    sess.w_uv, out, ws, sess.workspace, sess.stream)
+        return out, sess.device_status()
+
+    for good in (0, 1):
+        row = lambda start: [2003, start] if good == 0 else [start, 2003]
+        want, status = attend(row(2 * past))
+        assert status == 0 and torch.isfinite(want).all()
+        for start in (-4096, -1, 2 * past + 2, 2 ** 31 - 1):
+            got, status = attend(row(start))
+            assert status == 1, start
+            assert torch.equal(got[good], want[good]), start
+            assert torch.isfinite(got).all()
+
+
 @pytest.mark.parametrize("case", range(6))
 def test_chunked_prefill_seeded_random_shapes(case):
     # shapes, lengths and piece sizes drawn from a seeded generator over what the call supports
