@@ -195,7 +195,8 @@ mtla_status mtla_cache_append(mtla_ctx* ctx, void* cache_c, void* cache_kr, floa
  *   o    = o~ W_V^(h)                      -> out
  * The output projection W_O is outside this library.  The cache is read
  * once per step for all heads.  A sequence with seq_len[b] == 0 yields zeros
- * and lse = -inf.
+ * and lse = -inf.  A seq_len[b] outside [0, max_slots * s] counts as the nearer
+ * of the two: no value makes a decode call leave the sequence's own rows.
  *
  *   q          device elem  [batch, n_heads, d_head]
  *   q_rope     device elem  [batch, n_heads, d_rope]   rotated

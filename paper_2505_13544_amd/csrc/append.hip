@@ -11,6 +11,7 @@
 // read the old value.
 #include "absorb_f32.h"
 #include "absorb_mfma.h"
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -441,8 +442,7 @@ __global__ __launch_bounds__(kBlock) void reorder_kernel(ReorderArgs a) {
     return;
   }
   const int len = a.src_len[src];
-  int live = len > 0 ? (len + a.stride - 1) / a.stride : 0;
-  live = live < a.max_slots ? live : a.max_slots;
+  const int live = live_slots(len, a.stride, a.max_slots);
   const size_t row_c = (size_t)a.max_slots * a.r * a.elem, row_kr = (size_t)a.max_slots * a.d_rope * a.elem;
   const u32x4* sc = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.src_c) + src * row_c);
   const u32x4* sk = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.src_kr) + src * row_kr);
@@ -495,8 +495,7 @@ __global__ __launch_bounds__(kBlock) void fork_paged_kernel(ForkArgs a) {
     return;
   }
   const int len = a.src_len[src];
-  int live = len > 0 ? (len + a.stride - 1) / a.stride : 0;
-  live = live < a.max_slots ? live : a.max_slots;
+  const int live = live_slots(len, a.stride, a.max_slots);
   const int P = 1 << a.src.shift;
   const int next_slot = len > 0 ? len / a.stride : 0;           // the slot the next token goes into
   const int pw = (next_slot < a.max_slots ? next_slot : a.max_slots - 1) >> a.src.shift;

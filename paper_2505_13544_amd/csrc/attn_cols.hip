@@ -19,6 +19,7 @@
 // units (one per tile, after a.run_cost units per sequence for the fixed cost of starting on it) cut
 // into equal ranges, one per persistent workgroup; a workgroup emits partial number i + b for every
 // sequence b of which its range holds a tile, and the tile stream never drains between sequences.
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
   auto units_of = [&](int live) { return live > 0 ? rc + (live + kTile - 1) / kTile : 0; };
   if (B <= kWave) {
     if (wv == 0) {
-      const int lv = lane < B ? (a.seq_len[lane] + a.stride - 1) / a.stride : 0;
+      const int lv = lane < B ? live_slots(a.seq_len[lane], a.stride, a.max_slots) : 0;
       const int nt = units_of(lv);
       const int inc = wave_scan(nt);
       if (lane < B) {
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     const int per = (B + kBlock - 1) / kBlock;
     const int b_lo = tid * per, b_hi = b_lo + per < B ? b_lo + per : B;
     int run = 0;
-    for (int bb = b_lo; bb < b_hi; ++bb) run += units_of((a.seq_len[bb] + a.stride - 1) / a.stride);
+    for (int bb = b_lo; bb < b_hi; ++bb) run += units_of(live_slots(a.seq_len[bb], a.stride, a.max_slots));
     // inclusive scan of the threads' sums: inside each wavefront by shuffles, the wavefronts' totals
     // through LDS (two barriers instead of the sixteen of a scan in LDS over all 256 threads)
     const int inc = wave_scan(run);
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     {
       int acc = before + inc - run;  // units before this thread's first sequence
       for (int bb = b_lo; bb < b_hi; ++bb) {
-        const int lv = (a.seq_len[bb] + a.stride - 1) / a.stride;
+        const int lv = live_slots(a.seq_len[bb], a.stride, a.max_slots);
         sPre[bb] = acc;
         sLive[bb] = lv;
         acc += units_of(lv);

@@ -7,6 +7,7 @@
 // Operand layout of the instruction: lane = 16 k + i holds A[i, k] and B[k, i], and D[4 k + v, i] in its four results.
 // Which four elements of the contraction one instruction takes is free, as long as A and B agree: a lane loads 16
 // bytes (elements 16 c + 4 k .. + 3 of its row) and instruction j of the four that follow takes element j of every lane.
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void attn_decode_f32_kernel(AttnArgs a) {
   const float* lat = reinterpret_cast<const float*>(a.lat) + (size_t)row * a.max_slots * R;
   const float* key = reinterpret_cast<const float*>(a.key) + (size_t)row * a.max_slots * DR;
   const int k0 = split * a.chunk;
-  const int live = (len + a.stride - 1) / a.stride;
+  const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
   if (k0 >= k1) return;
 

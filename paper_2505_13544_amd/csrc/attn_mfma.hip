@@ -42,6 +42,7 @@
 //             sequences form one flat list that is cut into equal ranges, so
 //             ragged batches keep every compute unit streaming until the end; a
 //             workgroup emits one partial per sequence its range touches.
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_kernel(AttnArgs a) {
   QueryRegs<C, QL> qr;
   query_request<C, QL>(qr, reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * C::E, a.q_plane,
                        a.n_heads, ht, tid, l16, g);
-  const int live = (len + a.stride - 1) / a.stride;
+  const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
   if (k0 >= k1) return;
   query_commit<C, QL>(qr, sQ, tid);
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(kBlock) void attn_split_kernel(AttnArgs a) {
   QueryRegs<C, false> q;
   query_request<C, false>(q, reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * C::E, a.q_plane, a.n_heads, 0,
                           tid, l16, g);
-  const int live = (len + a.stride - 1) / a.stride;
+  const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
   if (k0 >= k1) return;
   t.select_live(base + l16 < k1);  // the first tile may have touched rows that were never written
@@ -615,7 +616,7 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_balanced_kernel(AttnArgs a) 
   const int per = (B + kBlock - 1) / kBlock;
   const int b_lo = tid * per, b_hi = b_lo + per < B ? b_lo + per : B;
   int run = 0;
-  for (int bb = b_lo; bb < b_hi; ++bb) run += ((a.seq_len[bb] + a.stride - 1) / a.stride + kTile - 1) / kTile;
+  for (int bb = b_lo; bb < b_hi; ++bb) run += (live_slots(a.seq_len[bb], a.stride, a.max_slots) + kTile - 1) / kTile;
   sScan[tid] = run;
   __syncthreads();
   for (int off = 1; off < kBlock; off <<= 1) {  // inclusive Hillis-Steele scan over the 256 run totals
@@ -627,7 +628,7 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_balanced_kernel(AttnArgs a) 
   {
     int acc = tid ? sScan[tid - 1] : 0;
     for (int bb = b_lo; bb < b_hi; ++bb) {
-      const int lv = (a.seq_len[bb] + a.stride - 1) / a.stride;
+      const int lv = live_slots(a.seq_len[bb], a.stride, a.max_slots);
       sPre[bb] = acc;
       sLive[bb] = lv;
       acc += (lv + kTile - 1) / kTile;

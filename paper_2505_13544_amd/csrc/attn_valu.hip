@@ -8,6 +8,7 @@
 //   partial_states_kernel  C_hat'[m] = running in-chunk sum of w_n c_n          (training form)
 #include <type_traits>
 
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -40,8 +41,7 @@ __device__ __forceinline__ RowMap<T_> make_row_map(int row, const int32_t* seq_l
   if (rm.decode()) {
     rm.b = row;
     rm.m = 0;
-    const int len = seq_len[row];
-    rm.live = (len + stride - 1) / stride;
+    rm.live = live_slots(seq_len[row], stride, max_slots);
   } else {
     rm.b = row / T;
     rm.m = row - rm.b * T;

@@ -8,6 +8,7 @@
 // W_V^(h) once per sequence: the limits below are where that costs what the launch saves.
 #include <type_traits>
 
+#include "bounds.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   };
   const bool multiplies = OT >= NW || wv < OT;  // (a wavefront too many has no output columns)
   if (!kNext && kEarly && multiplies) load_w(h0);
-  const int live = (len + a.stride - 1) / a.stride, tiles = (live + 15) / 16;
+  const int live = live_slots(len, a.stride, a.max_slots), tiles = (live + 15) / 16;
   const int mine = tiles > wv ? (tiles - wv + NW - 1) / NW : 0;
   constexpr int W = kEarly ? NT * KC : 0;
   auto wait_but_w = [&](auto others) {  // and W_V^(h)
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
       for (int c = 0; c < KC; ++c) wf[u][c] = *reinterpret_cast<const float4_t*>(wp + (size_t)32 * u * R + 32 * c);
   };
   load_w();
-  const int live = (len + a.stride - 1) / a.stride;
+  const int live = live_slots(len, a.stride, a.max_slots);
 
   float m = -INFINITY, l = 0.f;
   float4_t acc[KC];

@@ -4,6 +4,12 @@
 
 namespace mtla {
 
+// The live slots of a sequence of `len` tokens.  A length outside 0 .. max_slots * stride counts as the nearer end.
+[[gnu::always_inline]] constexpr int live_slots(int len, int stride, int max_slots) {
+  const int n = len > 0 ? (int)((unsigned)(len - 1) / (unsigned)stride) + 1 : 0;
+  return n < max_slots ? n : max_slots;
+}
+
 // The slots in front of a sequence's new rows.  A start outside the `past` slots that the call declared counts as all of them
 // (the front launch raises the status word): no kernel leaves its arrays, and the sequence's rows are meaningless.  (As an
 // unsigned number a start below zero lies above every slot that past * stride < 2^31 tokens can have.)

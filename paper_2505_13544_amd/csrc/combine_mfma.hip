@@ -15,6 +15,7 @@
 // (hi + lo, an almost-fp32 value) that the four wavefronts read back as the B operand.
 // At r = 512, d_h = 128: 256 sequences, 16 heads 9.4 us, now 8.8; 1000 sequences 29.3, now 24.5; 8 sequences of 33 pieces,
 // 32 heads 9.1, now 7.0.
+#include "bounds.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -59,7 +60,7 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
     if (row >= rows) return p;  // static: chunk c of row b is piece b * n_splits + c
     int live;
     if (a.T == 0) {
-      live = (a.seq_len[row] + a.stride - 1) / a.stride;
+      live = live_slots(a.seq_len[row], a.stride, a.max_slots);
     } else {
       const int b = row / a.T, m = row - b * a.T;
       const int len = a.seq_len ? a.seq_len[b] : a.T;

@@ -541,6 +541,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
   cb.r = g.r;
   cb.d_head = g.d_head;
   cb.stride = g.stride;
+  cb.max_slots = g.max_slots;
   cb.chunk = c->chunk;
   cb.n_splits = at.n_splits;
   cb.batch = batch;
@@ -1356,6 +1357,7 @@ mtla_status mtla_prefill_attn(mtla_ctx* c, const void* q, const void* q_rope, co
   cb.r = g.r;
   cb.d_head = g.d_head;
   cb.stride = g.stride;
+  cb.max_slots = 0;
   cb.chunk = at.chunk;
   cb.n_splits = 1;
   cb.batch = batch;

@@ -114,7 +114,7 @@ struct CombineArgs {
   float* out;         // [rows, n_heads, d_head] or NULL
   float* out_latent;  // [rows, n_heads, r] or NULL
   float* lse;         // [rows, n_heads] or NULL
-  int n_heads, r, d_head, stride, chunk, n_splits, batch, T;
+  int n_heads, r, d_head, stride, max_slots, chunk, n_splits, batch, T;  // (max_slots: decode)
   int n_persistent;             // > 0: the partials came from the balanced schedule
   const int32_t* tile_prefix;   // balanced: [batch + 1] running work units
   int run_cost = 0;             // balanced: units before a row's first tile (as the attention kernel counted)

@@ -13,6 +13,7 @@
 // at decode batch sizes these kernels are pure latency.
 #include "absorb_f32.h"
 #include "absorb_mfma.h"
+#include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(CombineArgs a) {
   } else {                   // static schedule: chunk c of row b is piece b * n_splits + c
     piece0 = row * a.n_splits;
     n_avail = a.n_splits;
-    const int live = a.T == 0 ? (len + a.stride - 1) / a.stride : (mrow < len ? mrow / a.stride + 1 : 0);
+    const int live = a.T == 0 ? live_slots(len, a.stride, a.max_slots) : (mrow < len ? mrow / a.stride + 1 : 0);
     empty = live == 0;
     nsp = (live + a.chunk - 1) / a.chunk;
   }
