@@ -106,8 +106,8 @@ mtla_status mtla_workspace_init(mtla_ctx* ctx, void* workspace /*device*/, void*
 /* Synchronises `hip_stream`, copies the sticky device status out of the
  * workspace header and clears it.  *status_out is MTLA_OK, MTLA_ERR_CAPACITY
  * (an append met a full sequence) or MTLA_ERR_INVALID_ARG (a device-side index
- * was out of range: pos0 of a continuing prefill, src_index of a reorder); the
- * last one raised wins. */
+ * was out of range: pos0 of a continuing prefill, src_index of a reorder, a
+ * length below zero in front of an append); the last one raised wins. */
 mtla_status mtla_device_status(mtla_ctx* ctx, void* workspace /*device*/, void* hip_stream,
                                int32_t* status_out /*host*/);
 
@@ -161,7 +161,9 @@ mtla_status mtla_probe_stream_read(mtla_ctx* ctx, const void* buf /*device*/, si
  * then seq_len[b] += n.  n_new_max == 1 is the decode step; larger values
  * build a prefix cache in one call.  If seq_len[b] + n > max_slots * s the
  * sequence is left untouched and MTLA_ERR_CAPACITY is raised in the
- * workspace header (see mtla_device_status).
+ * workspace header (see mtla_device_status); if seq_len[b] is below zero it is
+ * left untouched and MTLA_ERR_INVALID_ARG is raised.  Every call that appends
+ * does the same.
  *
  *   cache_c, cache_kr  device, in/out   layouts above
  *   tail_c             device, in/out   float [max_batch, r]; may be NULL for

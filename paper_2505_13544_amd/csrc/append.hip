@@ -143,7 +143,7 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   }
   float g_pre = 0.f;  // this thread's element of the slot's row of G
   if (hyper && tid < dy) {
-    const int slot_c = p0 / s < a.max_slots ? p0 / s : a.max_slots - 1;  // a full sequence is refused below
+    const int slot_c = slots_inside(p0, s, a.max_slots - 1);  // a full sequence, or a length below zero, is refused below
     g_pre = to_f32(reinterpret_cast<const T*>(a.hyp_G)[(size_t)slot_c * dy + tid]);
   }
   // Layer normalisation of an unrounded latent (whole-layer call): y = (v - mean) / sqrt(var + eps),
@@ -223,8 +223,8 @@ __device__ __forceinline__ void append_step_block(const AppendArgs& a, int b, fl
   __syncthreads();
 
   if (n < 1) return;
-  if ((long long)p0 + 1 > (long long)a.max_slots * s) {  // refuse: sequence untouched
-    if (tid == 0) *a.status = 3;                         // MTLA_ERR_CAPACITY
+  if (const int refused = append_status(p0, 1, s, a.max_slots)) {
+    if (tid == 0) *a.status = refused;
     return;
   }
   const int slot = p0 / s;
@@ -383,8 +383,8 @@ __global__ __launch_bounds__(kBlock) void append_kernel(AppendArgs a) {
   int n = a.n_new ? a.n_new[b] : a.n_new_max;
   n = n < 0 ? 0 : (n > a.n_new_max ? a.n_new_max : n);
   if (n == 0) return;
-  if ((long long)p0 + n > (long long)a.max_slots * s) {   // refuse: sequence untouched
-    if (kslot == 0 && threadIdx.x == 0) *a.status = 3;    // MTLA_ERR_CAPACITY
+  if (const int refused = append_status(p0, n, s, a.max_slots)) {
+    if (kslot == 0 && threadIdx.x == 0) *a.status = refused;
     return;
   }
   const int first_slot = p0 / s, last_slot = int(((long long)p0 + n - 1) / s);
@@ -399,7 +399,7 @@ __global__ void advance_len_kernel(AppendArgs a) {
   const int p0 = a.seq_len[b];
   int n = a.n_new ? a.n_new[b] : a.n_new_max;
   n = n < 0 ? 0 : (n > a.n_new_max ? a.n_new_max : n);
-  if ((long long)p0 + n <= (long long)a.max_slots * a.stride) a.seq_len[b] = p0 + n;
+  if (append_status(p0, n, a.stride, a.max_slots) == 0) a.seq_len[b] = p0 + n;
 }
 
 __global__ void fill_zero_kernel(int32_t* p, int n) {

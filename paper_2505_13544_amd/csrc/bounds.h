@@ -10,6 +10,12 @@ namespace mtla {
   return n < max_slots ? n : max_slots;
 }
 
+// May `n` tokens be appended to a sequence of `len`?  0, or the status that refuses them (the sequence is left untouched):
+// 1 (MTLA_ERR_INVALID_ARG) for a length below zero, 3 (MTLA_ERR_CAPACITY) for more than the capacity holds.
+[[gnu::always_inline]] constexpr int append_status(int len, int n, int stride, int max_slots) {
+  return len < 0 ? 1 : ((long long)len + n > (long long)max_slots * stride ? 3 : 0);
+}
+
 // The slots in front of a sequence's new rows.  A start outside the `past` slots that the call declared counts as all of them
 // (the front launch raises the status word): no kernel leaves its arrays, and the sequence's rows are meaningless.  (As an
 // unsigned number a start below zero lies above every slot that past * stride < 2^31 tokens can have.)

@@ -989,7 +989,7 @@ mtla_status mtla_prefill_step_paged(mtla_ctx* c, void* cache_c, void* cache_kr, 
     ex.advance = seq_len;
     ex.tail_c = tail_c;
     ex.tail_next = tail_prev;
-    ex.capacity = (long long)c->cfg.max_slots * c->cfg.stride;
+    ex.max_slots = c->cfg.max_slots;
     if (!hip_ok(launch_prefill_front(fa, 1, st))) return MTLA_ERR_HIP;
     return hip_ok(launch_prefill_explicit(ex, st, next_event(c))) ? MTLA_OK : MTLA_ERR_HIP;
   }
@@ -1121,7 +1121,7 @@ mtla_status mtla_layer_prefill(mtla_ctx* c, const mtla_layer_weights* lw, void* 
   ex.advance = seq_len;
   ex.tail_c = tail_c;
   ex.tail_next = fa.tail_next;
-  ex.capacity = (long long)g.max_slots * g.stride;
+  ex.max_slots = g.max_slots;
   if (!prefill_explicit_supported(ex)) return MTLA_ERR_UNSUPPORTED;
   GemmArgs gy;          // y = concat_h(o_h) W_O
   gy.A = sc + L.out16;

@@ -158,7 +158,7 @@ struct ExplicitArgs {
   int32_t* advance = nullptr;
   float* tail_c = nullptr;
   const float* tail_next = nullptr;
-  long long capacity = 0;  // tokens a sequence may hold
+  int max_slots = 0;       // slots a sequence may hold (with `advance`)
   int q_f16 = 0;           // q and q_rope are fp16 and already carry scale_log2 (the layer's own projections)
   void* out16 = nullptr;   // if set: the output goes here as fp16 [B, T, n_heads, d_head] instead of to `out`
   int n_slices = 0;        // fp32 form only, latent-space output: column slices of the partial states per head

@@ -335,9 +335,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const int p0 = CONT ? start_inside(a.pos0[b], s, a.past_pitch) : 0;
   const int j0 = p0 / s, past = j0;
   if (CONT && a.advance && unit == 0 && h == 0) {
-    const long long end = (long long)a.pos0[b] + (len > 0 ? len : 0);
-    if (end <= a.capacity && len > 0) {
-      if (tid == 0) a.advance[b] = (int32_t)end;
+    const int old = a.pos0[b];
+    if (len > 0 && append_status(old, len, s, a.max_slots) == 0) {  // as the append took it
+      if (tid == 0) a.advance[b] = old + len;
       for (int e = tid; e < a.r; e += NT) a.tail_c[(size_t)b * a.r + e] = a.tail_next[(size_t)b * a.r + e];
     }
   }

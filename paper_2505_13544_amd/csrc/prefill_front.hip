@@ -300,8 +300,8 @@ __device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillF
     if (x == 0 && threadIdx.x == 0) fa->pos0_out[b] = p0;  // for the launches behind this one
   }
   if (n == 0) return;
-  if ((long long)p0 + n > (long long)a.max_slots * s) {   // refuse: sequence untouched
-    if (x == 0 && threadIdx.x == 0) *a.status = 3;        // MTLA_ERR_CAPACITY
+  if (const int refused = append_status(p0, n, s, a.max_slots)) {
+    if (x == 0 && threadIdx.x == 0) *a.status = refused;
     return;
   }
   const long long end = (long long)p0 + n;

@@ -25,13 +25,16 @@ int main() {
       for (int len : {INT_MAX, INT_MAX - 1}) if (live_slots(len, s, slots) != slots) return 2;
       for (int len : {INT_MIN, INT_MIN + 1}) if (live_slots(len, s, slots) != 0) return 3;
     }
+  if (append_status(0, 1, 2, 1) != 0 || append_status(1, 1, 2, 1) != 0 || append_status(2, 1, 2, 1) != 3 || append_status(-1, 1, 2, 1) != 1 ||
+      append_status(INT_MIN, 1, 1, INT_MAX) != 1 || append_status(INT_MAX, 1, 1, INT_MAX) != 3 || append_status(INT_MAX - 1, 1, 1, INT_MAX) != 0)
+    return 5;
   return live_slots(INT_MAX, 1, INT_MAX) == INT_MAX && live_slots(INT_MAX, 16, INT_MAX / 16) == INT_MAX / 16 ? 0 : 4;
 }
 """
 
 
 @pytest.mark.skipif(not shutil.which("g++"), reason="no host compiler")
-def test_live_slots(tmp_path):
+def test_lengths(tmp_path):
     (tmp_path / "main.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", CSRC,
                     str(tmp_path / "main.cpp"), "-o", str(tmp_path / "main")], check=True)
