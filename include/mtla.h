@@ -114,7 +114,9 @@ mtla_status mtla_device_status(mtla_ctx* ctx, void* workspace /*device*/, void* 
 /* Tuning knob: number of cache slots one decode workgroup scans (a multiple
  * of 32; 0 restores the default picked at mtla_create).  The number of
  * splits per sequence is ceil(max_slots / chunk).  Must not change between
- * mtla_workspace_bytes() and the calls using that workspace. */
+ * mtla_workspace_bytes() and the calls using that workspace.  A chunk that is
+ * set, also to the default's value, holds: the form without chunks (see
+ * mtla_set_decode_schedule) is then not taken. */
 mtla_status mtla_set_decode_chunk(mtla_ctx* ctx, int32_t chunk_slots);
 int32_t mtla_get_decode_chunk(const mtla_ctx* ctx);
 
@@ -123,17 +125,27 @@ int32_t mtla_get_decode_chunk(const mtla_ctx* ctx);
  * decode_chunk slots), the low-latency choice for small batches.  2 =
  * balanced: one persistent workgroup per compute unit; the 16-slot tiles of all
  * sequences form one flat list cut into equal ranges, so ragged or large
- * batches keep every compute unit streaming.  0 = automatic (balanced once the
- * batch's slot capacity gives every compute unit at least 8 tiles). */
+ * batches keep every compute unit streaming.  0 = automatic: balanced once the
+ * batch's slot capacity gives every compute unit at least 8 tiles, else static;
+ * and, unless a chunk is set, one workgroup per sequence and one to four heads
+ * without chunks or partials, one launch less, where that is faster.  That form
+ * also exists in fp32 storage.  What decides is host-known: batch, heads, shape
+ * and the context's max_slots, not the lengths, so a context made for more
+ * slots than are ever used keeps the split form (by shape the limit lies
+ * between 256 and 768 slots and between 512 and 2048 pairs of sequence and
+ * head).  Results of the forms differ by rounding only. */
 mtla_status mtla_set_decode_schedule(mtla_ctx* ctx, int32_t schedule);
 
 /* Kernel timing for benchmarks.  After mtla_profile_start(ctx, capacity) every
- * mtla_decode_attn and mtla_prefill_attn call records a HIP event pair around
- * its dominant kernel (the attention pass over the cache slots, or over the
- * unmasked columns of the parallel form) on the call's stream, up to `capacity`
- * calls.  mtla_profile_read synchronises on the recorded events, writes the
- * elapsed milliseconds of each bracketed launch to ms_out (host, room for
- * `capacity` floats), the number of launches to *n_out, and ends profiling.
+ * call that attends (the decode calls, mtla_prefill_attn and the prefill calls
+ * that continue from a cache) records a HIP event pair around its dominant
+ * kernel (the attention pass over the cache slots, or over the unmasked columns
+ * of the parallel form) on the call's stream, up to `capacity` calls.  Where a
+ * decode call takes whole sequences without chunks (mtla_set_decode_schedule)
+ * that kernel contains the normalisation and the product with W_V as well.
+ * mtla_profile_read synchronises on the recorded events, writes the elapsed
+ * milliseconds of each bracketed launch to ms_out (host, room for `capacity`
+ * floats), the number of launches to *n_out, and ends profiling.
  * Events are host-side runtime objects; no device memory is allocated.  Do not
  * use while the stream is being captured into a HIP graph. */
 mtla_status mtla_profile_start(mtla_ctx* ctx, int32_t capacity);

@@ -18,6 +18,7 @@ struct mtla_ctx {
   float scale;           // softmax scale actually used
   int default_chunk;     // decode slots per workgroup chosen at create
   int chunk;             // current value (mtla_set_decode_chunk)
+  bool chunk_set = false;  // by the caller
   int schedule = 0;      // mtla_set_decode_schedule: 0 auto, 1 static, 2 balanced
   int n_cu = 0;          // compute units of the device, queried at the first decode call
   std::vector<hipEvent_t> ev_start, ev_stop;  // mtla_profile_start .. mtla_profile_read
@@ -271,10 +272,12 @@ mtla_status mtla_set_decode_chunk(mtla_ctx* c, int32_t chunk) {
   if (!c) return MTLA_ERR_INVALID_ARG;
   if (chunk == 0) {
     c->chunk = c->default_chunk;
+    c->chunk_set = false;
     return MTLA_OK;
   }
   if (chunk < 32 || chunk % 32) return MTLA_ERR_INVALID_ARG;
   c->chunk = chunk;
+  c->chunk_set = true;
   return MTLA_OK;
 }
 int32_t mtla_get_decode_chunk(const mtla_ctx* c) { return c ? c->chunk : 0; }
@@ -513,8 +516,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     ev.start = c->ev_start[c->prof_n];
     ev.stop = c->ev_stop[c->prof_n++];
   }
-  // few short sequences; a schedule or a chunk that the caller set stays what it says
-  if (c->schedule == 0 && c->chunk == c->default_chunk && (use_mfma || g.dtype == MTLA_F32)) {
+  // few short sequences; a schedule or a chunk that the caller set (the default's value too) stays what it says
+  if (c->schedule == 0 && !c->chunk_set && (use_mfma || g.dtype == MTLA_F32)) {
     WholeArgs wh;
     wh.at = at;
     wh.w_uv = w_uv;

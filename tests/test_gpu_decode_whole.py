@@ -89,3 +89,25 @@ def test_reference_moves_between_steps(dtype, r):
         outs.append(out.cpu())
     assert torch.isfinite(outs[0]).all()
     assert (outs[0] - outs[1]).abs().max() <= (H.TOL["bf16"] if dtype == "bf16" else 64 * H.TOL["f32"])  # (logits 64 times as large)
+
+
+@pytest.mark.parametrize("dtype,r", [("bf16", 256), ("f32", 64)])
+def test_a_chunk_set_to_the_default_value_is_set(dtype, r):
+    # the caller's chunk keeps the split form, which gives the static schedule's bits; restoring the default leaves it again
+    wl = _workload(dtype, 8, 64, r, 1, (120, 37, 64), steps=1)
+    wts = W.make_weights(wl)
+    toks = [W.make_tokens(wl, wts, b, 0, 120) for b in range(wl.batch)]
+    d = {f: H.to_device(np.stack([getattr(t, f) for t in toks]), wl.dtype) for f in ("q", "q_rope", "c", "kr")}
+    default = H.make_session(wl).ctx.get_decode_chunk()
+    outs = []
+    for chunk, schedule, restore in ((None, 0, False), (None, 1, False), (default, 0, False), (default, 0, True)):
+        sess = H.make_session(wl, decode_chunk=chunk, decode_schedule=schedule)
+        if restore:
+            sess.ctx.set_decode_chunk(0)
+        H.upload_weights(sess, wts)
+        sess.append(d["c"], d["kr"])
+        out = torch.zeros(wl.batch, wl.n_heads, wl.d_head, device="cuda")
+        sess.decode(d["q"][:, -1].contiguous(), d["q_rope"][:, -1].contiguous(), out=out)
+        outs.append(out)
+    assert not torch.equal(outs[0], outs[1])   # (two forms, two orders of summation)
+    assert torch.equal(outs[2], outs[1]) and torch.equal(outs[3], outs[0])
