@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "bounds.h"
+#include "gemm_tiles.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -740,71 +741,11 @@ hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Column blocks of a launch with tiles of bn columns (a segment starts a block of its own).
-static int gemm_col_blocks(const GemmArgs& a, int bn) {
-  int n = 0;
-  for (int i = 0; i < a.n_seg; ++i) n += (a.seg[i].N + bn - 1) / bn;
-  return n;
-}
-
-// The tiles that take the least time, and that time (us, as measured on products of rows in use x 1024 to 4096 columns): a round is a
-// tile for each of the 256 units, `base` fills and empties them.  64 x 64 one, two, three rounds: 4.9, 7.0, 9.8 us at K = 512 and
-// 12, 20, 28 at 2048; 128 x 128 one and two: 9, 14.5 and 25, 44; the streams of gemm_wide.hip (kWide), whose last round is cut
-// into halves or quarters of a tile where that fills it: a quarter round 10 and 24, half a one 13.5 and 35, one 22 and 60, eight
-// 136 and 480.  With ragged rows the number of row blocks is not known here: three quarters of the most, and half a block more per
-// sequence, or half a round where blocks may hold rows of several.
-enum { kWide = 4 };
-static float gemm_cost(const GemmArgs& a, int& pick) {
-  static constexpr struct { int bm, bn; float base, round, k; } kTiles[] = {
-      {256, 256, 5.f, 4.7f, 0.028f}, {256, 128, 5.f, 2.5f, 0.0152f}, {128, 128, 3.2f, 0.5f, 0.0112f}, {64, 64, 2.2f, 0.5f, 0.004f}};
-  const bool ragged = a.rows.n_new || a.rows.pos0;
-  const int Tp = ragged ? a.rows.past + a.rows.T : a.M;
-  const float n_seq = ragged ? (float)(a.M / Tp) : 1.f, K = (float)a.K;
-  // a ragged launch with as many jobs as this may find them all: it is not taken for less than a round
-  auto rounds_of = [&](int bm, int bn, bool packed) -> float {
-    // (rows that are not packed: every sequence starts a block of its own, however short it is)
-    const float cols = (float)gemm_col_blocks(a, bn);
-    const float most = packed || !ragged ? (float)((a.M + bm - 1) / bm) : n_seq * (float)((Tp + bm - 1) / bm);
-    if (!ragged) return cols * most / 256.f;
-    if (cols * most <= 256.f) return cols * most / 256.f;
-    return packed ? 0.75f * cols * most / 256.f + 0.5f : cols * fmaxf(0.75f * (float)a.M / (float)bm + 0.5f * n_seq, n_seq) / 256.f;
-  };
-  float best = 0.f;
-  pick = 0;
-  for (int i = 0; i < 4; ++i) {
-    float of = rounds_of(kTiles[i].bm, kTiles[i].bn, a.rows.zeros);
-    if (ragged && i < 2) {
-      // A row block's tiles are one XCD's: few blocks of many rows leave some XCDs two and others one (7 sequences of 137 to 551
-      // rows, 2112 columns, K = 1024: 14 blocks in 256 x 128 tiles 36.4 us, 22 in 128 x 128 25.8)
-      const float cols = (float)gemm_col_blocks(a, kTiles[i].bn), blocks = 256.f * of / cols;
-      if (blocks >= 8.f) of = ceilf(blocks / 8.f) * cols / 32.f;
-    }
-    const float rounds = ceilf(of);
-    float cost = kTiles[i].base + rounds * (kTiles[i].round + kTiles[i].k * K);
-    if (i == 3 && rounds > 2.f) cost += 0.6f;  // (two fit on a unit)
-    if (i == 0 || cost < best) {
-      best = cost;
-      pick = i;
-    }
-  }
-  if (gemm_wide_supported(a)) {
-    const float rounds = rounds_of(256, 256, false), left = rounds - floorf(rounds), whole = left > 0.5f ? ceilf(rounds) : floorf(rounds);
-    float cost = 5.f + whole * (4.4f + 0.0246f * K);
-    if (left > 0.25f && left <= 0.5f) cost += 1.2f + 0.0142f * K;
-    else if (left > 0.f && left <= 0.25f) cost += 0.0097f * K;
-    if (cost < best) {
-      best = cost;
-      pick = kWide;
-    }
-  }
-  return best;
-}
-
 hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
   GemmArgs a = args;
   int pick = 0;
-  const float whole = gemm_cost(a, pick);
+  const float whole = gemm_cost(a, gemm_wide_supported(a), pick);
   if (a.n_seg > 1) {
     // The narrowest product in a launch of its own if that saves time: 64 columns beside 3584 at 32768 rows open half a round
     // of 256 x 256 tiles more.
@@ -817,18 +758,18 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
     rest.n_seg = a.n_seg - 1;
     for (int i = least; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
     int p1 = 0, p2 = 0;
-    if (gemm_cost(one, p1) + gemm_cost(rest, p2) < whole) {
+    if (gemm_cost(one, gemm_wide_supported(one), p1) + gemm_cost(rest, gemm_wide_supported(rest), p2) < whole) {
       const hipError_t e = launch_gemm_nt(rest, st);
       return e != hipSuccess ? e : launch_gemm_nt(one, st);
     }
   }
   if (pick == kWide) return launch_gemm_wide(a, st);
-  static constexpr int kBM[] = {256, 256, 128, 64}, kBN[] = {256, 128, 128, 64};
-  a.col_blocks = gemm_col_blocks(a, kBN[pick]);
-  unsigned gy = (unsigned)((a.M + kBM[pick] - 1) / kBM[pick]);
+  const int bm = kGemmTiles[pick].bm;
+  a.col_blocks = gemm_col_blocks(a, kGemmTiles[pick].bn);
+  unsigned gy = (unsigned)((a.M + bm - 1) / bm);
   if ((a.rows.n_new || a.rows.pos0) && !a.rows.zeros) {  // every sequence starts a block of its own
     const int Tp = a.rows.past + a.rows.T;
-    gy = (unsigned)(a.M / Tp) * (unsigned)((Tp + kBM[pick] - 1) / kBM[pick]);
+    gy = (unsigned)(a.M / Tp) * (unsigned)((Tp + bm - 1) / bm);
   }
   a.row_blocks = gy;
   a.xcds = gy >= 8 ? 8 : 1;

@@ -1,0 +1,80 @@
+"""The rule that picks the tiles of a prefill's matrix products (csrc/gemm_tiles.h), compiled and run on the host: its estimates stand for the
+measured times that its comment gives, and it picks the faster tiles where both sides were measured."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_13544_amd", "csrc")
+
+PROGRAM = r"""
+#include "gemm_tiles.h"
+#include <cstdio>
+#include <vector>
+using namespace mtla;
+struct Args {
+  int M, K, n_seg;
+  struct { int N; } seg[4];
+  struct { const int *pos0, *n_new; int past, T, zeros; } rows;
+};
+static int some;
+Args equal(int M, int N, int K) { return Args{M, K, 1, {{N}}, {nullptr, nullptr, 0, 1, 0}}; }
+Args ragged(int n_seq, int past, int T, std::vector<int> N, int K, int zeros = 0) {
+  Args a{n_seq * (past + T), K, (int)N.size(), {}, {past ? &some : nullptr, &some, past, T, zeros}};
+  for (size_t i = 0; i < N.size(); ++i) a.seg[i].N = N[i];
+  return a;
+}
+int failed;
+void near(const char* what, float estimate, float measured) {   // the estimates choose between neighbours that lie 1.2 and more apart
+  if (std::fabs(estimate - measured) <= 0.15f * measured) return;
+  std::printf("%s: %.1f us estimated, %.1f measured\n", what, estimate, measured);
+  ++failed;
+}
+void picks(const char* what, const Args& a, int tile, bool wide = true) {
+  int pick = -1;
+  gemm_cost(a, wide, pick);
+  if (pick == tile) return;
+  std::printf("%s: tiles %d\n", what, pick);
+  ++failed;
+}
+int main() {
+  const struct { int tile, rows, cols; float us512, us2048; const char* what; } kMeasured[] = {
+      {3, 1024, 1024, 4.9f, 12.f, "64 x 64, one round"}, {3, 2048, 1024, 7.0f, 20.f, "64 x 64, two"}, {3, 3072, 1024, 9.8f, 28.f, "64 x 64, three"},
+      {2, 2048, 2048, 9.f, 25.f, "128 x 128, one round"}, {2, 4096, 2048, 14.5f, 44.f, "128 x 128, two"},
+      {kWide, 1024, 4096, 10.f, 24.f, "streams, a quarter round"}, {kWide, 2048, 4096, 13.5f, 35.f, "streams, half a round"},
+      {kWide, 4096, 4096, 22.f, 60.f, "streams, one round"}, {kWide, 32768, 4096, 136.f, 480.f, "streams, eight"}};
+  for (const auto& m : kMeasured) {
+    near(m.what, gemm_tile_cost(equal(m.rows, m.cols, 512), m.tile), m.us512);
+    near(m.what, gemm_tile_cost(equal(m.rows, m.cols, 2048), m.tile), m.us2048);
+  }
+  picks("129 rows x 512 columns", equal(129, 512, 512), 3);                     // 17 us in 256 x 256 tiles, 6
+  picks("7 sequences of up to 551 rows", ragged(7, 0, 551, {2112}, 1024), 2);   // 36.4 us in 256 x 128 tiles, 25.8
+  picks("32768 x 3584 x 2048", equal(32768, 3584, 2048), kWide);                // 452 us in 256 x 256 tiles, 378
+  picks("32768 x 4096 x 512", equal(32768, 4096, 512), kWide);                  // 171, 136
+  picks("a contraction that is no multiple of 64", equal(32768, 4096, 2080), 0, false);
+  picks("one row", equal(1, 8, 32), 3, false);
+  // two sequences of 510 new rows behind up to 1500 slots, 16 heads x 128: what the GPU's test of their starts relies on
+  picks("two chunks", ragged(2, 1500, 510, {2048, 2048}, 512), kWide);
+  // whatever the sizes, the estimate is of a tile that there is, and never grows when rows are taken away
+  for (int M : {1, 63, 64, 65, 500, 5000, 50000})
+    for (int N : {8, 64, 72, 1000, 4096})
+      for (int K : {64, 512, 4096}) {
+        int p = -1, q = -1;
+        const float a = gemm_cost(equal(M, N, K), true, p), b = gemm_cost(equal(2 * M, N, K), true, q);
+        if (p < 0 || p > kWide || !(a > 0.f) || a > b) {
+          std::printf("%d x %d x %d: %f, %f\n", M, N, K, a, b);
+          ++failed;
+        }
+      }
+  return failed ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(not shutil.which("g++"), reason="no host compiler")
+def test_estimates_stand_for_measured_times(tmp_path):
+    (tmp_path / "main.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "main")], check=True)
+    run = subprocess.run([str(tmp_path / "main")], timeout=60, capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
