@@ -516,6 +516,7 @@ bool attn_whole_supported(const WholeArgs& w, int dtype) {
   if (dtype == 0)  // fp32
     return (a.r == 64 || a.r == 128 || a.r == 256) && (a.d_rope == 32 || a.d_rope == 64) && w.d_head % 64 == 0 && jobs <= 512 &&
            a.max_slots <= (a.r == 256 ? 512 : 768);
+  // (head shapes that are built; 64 with 64 and 128 with 32 are not, and have not been measured)
   const bool narrow = w.d_head == 64 && a.d_rope == 32, wide = w.d_head == 128 && a.d_rope == 64;
   if (!narrow && !wide) return false;
   if (a.r == 128 && jobs > 1024) return narrow && jobs <= 2048 && a.max_slots <= 320;  // (two workgroups a unit)
@@ -544,7 +545,7 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
   }
   // Long: eight wavefronts, two per SIMD, hide more of a tile's chain than their meeting costs (16 sequences of 8 heads, us a step
   // with four / eight: r = 128: 128 slots 7.7 / 8.3, 512 10.5 / 10.0; r = 256: 384 slots 11.1 / 11.5, 528 12.9 / 12.3, where several
-  // heads' queries leave no room for them)
+  // heads' queries leave no room for them; not built for 128-wide heads at r = 256)
   if (a.r == 128 && a.max_slots > 320) {
     if (a.d_rope == 32 && w.d_head == 64) return launch_heads<128, 32, 64, 8>(w, st, ev);
     if (a.d_rope == 64 && w.d_head == 128) return launch_heads<128, 64, 128, 8>(w, st, ev);
