@@ -5,9 +5,9 @@
 //
 // Every cache row has exactly one writer.  A decode step (one token per sequence) is a single
 // launch of `batch` workgroups that also advances seq_len (append_step_kernel).  A bulk append
-// (prefix) runs one workgroup per (sequence, group of 16 touched slots) with the hyper-network on
-// the matrix cores (append_bulk_kernel in prefill_front.hip, bf16 storage) or one workgroup per touched slot
-// (append_kernel, any storage), and a second tiny kernel advances seq_len once every workgroup has
+// (prefix) runs one workgroup per (sequence, group of touched slots) with the hyper-network on
+// the matrix cores (append_bulk_kernel, append_bulk_f32_kernel in prefill_front.hip) or one workgroup per touched slot
+// (append_kernel, other hyper-network widths and strides), and a second tiny kernel advances seq_len once every workgroup has
 // read the old value.
 #include "absorb_f32.h"
 #include "absorb_mfma.h"
@@ -640,7 +640,7 @@ hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t st) {
   const int n_slots = (a.n_new_max + a.stride - 2) / a.stride + 1;
   const dim3 grid(n_slots, a.batch), block(kBlock);
   if (append_bulk_supported(a, dtype)) {
-    const hipError_t e = launch_append_bulk(a, st);
+    const hipError_t e = launch_append_bulk(a, dtype, st);
     if (e != hipSuccess) return e;
   } else if (dtype == 0)
     hipLaunchKernelGGL(append_kernel<float>, grid, block, smem, st, a);

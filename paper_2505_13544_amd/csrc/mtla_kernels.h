@@ -351,7 +351,7 @@ hipError_t launch_stream_read(const void* p, size_t bytes, int32_t* out, int wor
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t st);
 // a bulk append of these shapes runs on the matrix cores
 bool append_bulk_supported(const AppendArgs& a, int dtype);
-hipError_t launch_append_bulk(const AppendArgs& a, hipStream_t st);
+hipError_t launch_append_bulk(const AppendArgs& a, int dtype, hipStream_t st);
 // mode 0: merge weights given, 1: with the append, 2: with the append of unrounded latents (append_bulk_supported shapes)
 hipError_t launch_prefill_front(const PrefillFrontArgs& a, int mode, hipStream_t st);
 hipError_t launch_save_state(const SaveStateArgs& a, hipStream_t st);

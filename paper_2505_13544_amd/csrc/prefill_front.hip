@@ -287,18 +287,18 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
   }
 }
 
-// Workgroup x of sequence b: slots 16 x .. of those the call touches.  The tail shadow of a sequence is read by the first
-// slot (when that slot already held tokens) and written by the last one.  With a staging launch the new one goes to
-// tail_next and is put in place by the attention launch.  An append alone has no later launch: when the shadow is
-// read, workgroup 0 takes the last slot as well, in a second pass behind a barrier, so the read precedes the write.
-template <int R, bool LN, bool STAGE>
-__device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int x, int b, AppendShared<R, LN>& sh) {
+// Which positions workgroup x of sequence b appends: those of slots SLOTS x .. of the ones the call touches, through
+// range(p0, n, first slot, first position, behind the last one).  The tail shadow of a sequence is read by the first
+// slot (when that slot already held tokens) and written by the last one.  With a staging launch (pos0_out: takes the length
+// before the call) the new one goes to tail_next and is put in place by the attention launch.  An append alone has no later
+// launch: when the shadow is read, workgroup 0 takes the last slot as well, in a second pass behind a barrier, so the read
+// precedes the write.
+template <int SLOTS, class Range>
+__device__ __forceinline__ void append_share(const AppendArgs& a, int32_t* pos0_out, int x, int b, Range range) {
   const int s = a.stride, p0 = a.seq_len[b];
   int n = a.n_new ? a.n_new[b] : a.n_new_max;
   n = n < 0 ? 0 : (n > a.n_new_max ? a.n_new_max : n);
-  if constexpr (STAGE) {
-    if (x == 0 && threadIdx.x == 0) fa->pos0_out[b] = p0;  // for the launches behind this one
-  }
+  if (pos0_out && x == 0 && threadIdx.x == 0) pos0_out[b] = p0;  // for the launches behind this one
   if (n == 0) return;
   if (const int refused = append_status(p0, n, s, a.max_slots)) {
     if (x == 0 && threadIdx.x == 0) *a.status = refused;
@@ -306,23 +306,164 @@ __device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillF
   }
   const long long end = (long long)p0 + n;
   const int first_slot = p0 / s, last_slot = int((end - 1) / s);
-  const bool last_apart = !STAGE && p0 % s != 0 && last_slot - first_slot >= kSlots;  // last slot outside workgroup 0's group
-  float* tail_out = STAGE ? fa->tail_next : a.tail_c;
-  const int slot0 = first_slot + kSlots * x;
+  const bool last_apart = !pos0_out && p0 % s != 0 && last_slot - first_slot >= SLOTS;  // last slot outside workgroup 0's group
+  const int slot0 = first_slot + SLOTS * x;
   const long long lim = last_apart ? (long long)last_slot * s : end;  // the group's share ends here
   const long long pos_lo = (long long)slot0 * s > p0 ? (long long)slot0 * s : p0;
-  const long long pos_hi = (long long)(slot0 + kSlots) * s < lim ? (long long)(slot0 + kSlots) * s : lim;
-  if (pos_lo < pos_hi) append_range<R, LN, STAGE>(a, fa, b, p0, n, slot0, pos_lo, pos_hi, tail_out, sh);
+  const long long pos_hi = (long long)(slot0 + SLOTS) * s < lim ? (long long)(slot0 + SLOTS) * s : lim;
+  if (pos_lo < pos_hi) range(p0, n, slot0, pos_lo, pos_hi);
   if (x == 0 && last_apart) {
     __syncthreads();
-    append_range<R, LN, STAGE>(a, fa, b, p0, n, last_slot, (long long)last_slot * s, end, tail_out, sh);
+    range(p0, n, last_slot, (long long)last_slot * s, end);
   }
+}
+
+template <int R, bool LN, bool STAGE>
+__device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int x, int b, AppendShared<R, LN>& sh) {
+  float* tail_out = STAGE ? fa->tail_next : a.tail_c;
+  append_share<kSlots>(a, STAGE ? fa->pos0_out : nullptr, x, b, [&](int p0, int n, int slot0, long long pos_lo, long long pos_hi) {
+    append_range<R, LN, STAGE>(a, fa, b, p0, n, slot0, pos_lo, pos_hi, tail_out, sh);
+  });
 }
 
 template <int R>
 __global__ __launch_bounds__(kBlock) void append_bulk_kernel(AppendArgs a) {
   __shared__ __attribute__((aligned(16))) AppendShared<R, false> sh;
   append_block<R, false, false>(a, nullptr, blockIdx.x, blockIdx.y, sh);
+}
+
+// The same append in fp32 storage, on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: lane 16 k + i holds A[i, k] and
+// B[k, i]; a lane's 16 bytes are its elements for four instructions).  Eight slots per workgroup, 32 threads merge a slot;
+// 16 tokens at a time through LDS.  Bound by latency: the hyper-network's rows and the first tokens are one trip to memory,
+// then 16 tokens are r / 4 dependent matrix instructions a wavefront (2048 cycles at r = 256).  With a workgroup per slot that
+// read the hyper-network (64 KB) again for every token, three sequences of up to 777 tokens took 14.8 us, r = 256, s = 2.
+constexpr int kSlotsF32 = 8, kChunkF32 = 16;
+template <int R>
+struct AppendSharedF32 {
+  float row[kChunkF32][R + 4];
+  float z[4][kChunkF32];
+};
+template <int R>
+__device__ __forceinline__ void append_range_f32(const AppendArgs& a, int b, int p0, int n, int slot_base, long long pos_lo,
+                                                 long long pos_hi, AppendSharedF32<R>& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4, q = tid & 31, j = tid >> 5;
+  const int s = a.stride, dR = a.d_rope, dy = a.d_hyper;
+  const int t0 = int(pos_lo - p0), cnt = int(pos_hi - pos_lo);  // tokens t0 .. t0 + cnt - 1 of the call
+  const size_t tok0 = (size_t)b * a.n_new_max + t0;
+  constexpr int KK = R / 16, NP = R >= 128 ? R / 128 : 1;       // a thread merges pieces q, q + 32, .. of 4 elements
+  constexpr int NL = kChunkF32 * R / 4 / kBlock;                // 16-byte pieces of a chunk that a thread brings
+  const bool hyper = !a.w_override && 16 * wv < dy;
+
+  // ---- requests that need nothing but the position
+  float4_t af[KK], bias = {0.f, 0.f, 0.f, 0.f};
+  if (hyper) {
+    const float* A = reinterpret_cast<const float*>(a.hyp_A) + (size_t)(16 * wv + l16) * R + 4 * g;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) af[kk] = *reinterpret_cast<const float4_t*>(A + 16 * kk);
+    if (a.hyp_a) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) bias[v] = reinterpret_cast<const float*>(a.hyp_a)[16 * wv + 4 * g + v];
+    }
+  }
+  const int slot = slot_base + j;
+  const long long sf = (long long)slot * s;
+  const long long lo = sf > pos_lo ? sf : pos_lo, hi = sf + s < pos_hi ? sf + s : pos_hi;
+  const bool mine = lo < hi && 4 * q < R;  // the slot is touched by this range
+  float4_t acc[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+  if (mine && sf < p0) {  // the slot already holds earlier tokens
+#pragma unroll
+    for (int i = 0; i < NP; ++i) acc[i] = *reinterpret_cast<const float4_t*>(a.tail_c + (size_t)b * R + 4 * (q + 32 * i));
+  }
+
+  for (int c0 = 0; c0 < cnt; c0 += kChunkF32) {
+    const int nc = cnt - c0 < kChunkF32 ? cnt - c0 : kChunkF32;
+    if (c0) __syncthreads();
+    float4_t gv = {0.f, 0.f, 0.f, 0.f};
+    if (hyper) {
+      const int u = l16 < nc ? l16 : nc - 1;
+      gv = *reinterpret_cast<const float4_t*>(reinterpret_cast<const float*>(a.hyp_G) + (size_t)((pos_lo + c0 + u) / s) * dy + 16 * wv + 4 * g);
+    }
+    float4_t v[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int p = tid + i * kBlock, u = p / (R / 4), e = 4 * (p % (R / 4));
+      v[i] = *reinterpret_cast<const float4_t*>(reinterpret_cast<const float*>(a.c_new) + (tok0 + c0 + (u < nc ? u : nc - 1)) * R + e);
+    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int p = tid + i * kBlock;
+      *reinterpret_cast<float4_t*>(&sh.row[p / (R / 4)][4 * (p % (R / 4))]) = v[i];
+    }
+    __syncthreads();
+
+    // ---- logits of the merge weights
+    if (hyper) {
+      float4_t d0 = {0.f, 0.f, 0.f, 0.f}, d1 = d0;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const float4_t c = *reinterpret_cast<const float4_t*>(&sh.row[l16][16 * kk + 4 * g]);
+        d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(af[kk][0], c[0], d0, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(af[kk][1], c[1], d1, 0, 0, 0);
+        d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(af[kk][2], c[2], d0, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(af[kk][3], c[3], d1, 0, 0, 0);
+      }
+      // the lane holds Linear(c)[16 wv + 4 g + v] of its token
+      float z = 0.f;
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) z += (d0[v4] + d1[v4] + bias[v4]) * gv[v4];
+      z = quarter_reduce(z, LaneSum());
+      if (g == 0) sh.z[wv][l16] = z;
+    }
+    __syncthreads();
+    auto weight = [&](int u) {
+      if (a.w_override) return a.w_override[tok0 + c0 + u];
+      float z = 0.f;
+      for (int y = 0; 16 * y < dy; ++y) z += sh.z[y][u];
+      return 1.f / (1.f + expf(-z));
+    };
+    if (tid < nc && (a.w_out || a.slot_out)) {
+      if (a.w_out) a.w_out[tok0 + c0 + tid] = weight(tid);
+      if (a.slot_out) a.slot_out[tok0 + c0 + tid] = int((pos_lo + c0 + tid) / s);
+    }
+
+    // ---- temporal merge of the slot's tokens in this chunk
+    if (mine) {
+      const long long u_lo = lo - pos_lo - c0 > 0 ? lo - pos_lo - c0 : 0, u_hi = hi - pos_lo - c0 < nc ? hi - pos_lo - c0 : nc;
+      for (int u = (int)u_lo; u < (int)u_hi; ++u) {
+        const float w = weight(u);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) acc[i] += w * *reinterpret_cast<const float4_t*>(&sh.row[u][4 * (q + 32 * i)]);
+      }
+    }
+  }
+
+  if (lo < hi) {
+    const size_t crow = cache_row(a.pages, b, slot, a.max_slots);
+    if (4 * q < R) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int e = 4 * (q + 32 * i);
+        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(a.cache_c) + crow * R + e) = acc[i];
+        if (hi == (long long)p0 + n) *reinterpret_cast<float4_t*>(a.tail_c + (size_t)b * R + e) = acc[i];  // the sequence's tail
+      }
+    }
+    // RoPE key: the slot keeps the key of the newest token folded into it
+    if (q < dR / 4) {
+      const float* kr_src = reinterpret_cast<const float*>(a.kr_new) + ((size_t)b * a.n_new_max + (size_t)(hi - 1 - p0)) * dR;
+      *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(a.cache_kr) + crow * dR + 4 * q) = *reinterpret_cast<const float4_t*>(kr_src + 4 * q);
+    }
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(kBlock) void append_bulk_f32_kernel(AppendArgs a) {
+  __shared__ __attribute__((aligned(16))) AppendSharedF32<R> sh;
+  append_share<kSlotsF32>(a, nullptr, blockIdx.x, blockIdx.y, [&](int p0, int n, int slot0, long long pos_lo, long long pos_hi) {
+    append_range_f32<R>(a, blockIdx.y, p0, n, slot0, pos_lo, pos_hi, sh);
+  });
 }
 
 // Tokens before the new rows, forced into what the arrays hold (the declared past is at most the capacity).
@@ -450,10 +591,10 @@ __global__ __launch_bounds__(kBlock) void prefill_front_kernel(PrefillFrontArgs 
   stage_piece(a.cs, (size_t)(blk - a.n_conv) * kBlock + threadIdx.x);
 }
 
-unsigned append_groups(const AppendArgs& a) {
+unsigned append_groups(const AppendArgs& a, int slots = kSlots) {
   // slots a call can touch per sequence: a partly filled first slot plus the rest
   const int n_slots = (a.n_new_max + a.stride - 2) / a.stride + 1;
-  return (unsigned)((n_slots + kSlots - 1) / kSlots);
+  return (unsigned)((n_slots + slots - 1) / slots);
 }
 
 template <int MODE>
@@ -471,20 +612,25 @@ hipError_t launch_front_mode(const PrefillFrontArgs& a, const dim3& grid, hipStr
 }  // namespace
 
 bool append_bulk_supported(const AppendArgs& a, int dtype) {
-  return dtype != 0 && a.tail_c && a.stride <= 16 && a.d_hyper % 16 == 0 && a.d_hyper <= 64 &&
+  // fp32: rows of the hyper-network and the tail shadow are read 16 bytes at a time, which the calls do not ask of their addresses
+  const auto odd = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; };
+  if (dtype == 0 && (odd(a.hyp_A) || odd(a.hyp_G) || odd(a.tail_c))) return false;
+  return a.tail_c && a.stride <= 16 && a.d_hyper % 16 == 0 && a.d_hyper <= 64 &&
          (a.r == 64 || a.r == 128 || a.r == 256 || a.r == 512) && a.d_rope % 8 == 0 && a.d_rope <= 128;
 }
 
-hipError_t launch_append_bulk(const AppendArgs& a, hipStream_t st) {
-  const dim3 grid(append_groups(a), a.batch);
-  switch (a.r) {
-    case 64: hipLaunchKernelGGL(append_bulk_kernel<64>, grid, dim3(kBlock), 0, st, a); break;
-    case 128: hipLaunchKernelGGL(append_bulk_kernel<128>, grid, dim3(kBlock), 0, st, a); break;
-    case 256: hipLaunchKernelGGL(append_bulk_kernel<256>, grid, dim3(kBlock), 0, st, a); break;
-    case 512: hipLaunchKernelGGL(append_bulk_kernel<512>, grid, dim3(kBlock), 0, st, a); break;
-    default: return hipErrorInvalidValue;
+hipError_t launch_append_bulk(const AppendArgs& a, int dtype, hipStream_t st) {
+  const bool f32 = dtype == 0;
+  const dim3 grid(append_groups(a, f32 ? kSlotsF32 : kSlots), a.batch);
+#define MTLA_CASE(RR)                                                                             \
+  if (a.r == RR) {                                                                                \
+    if (f32) hipLaunchKernelGGL(append_bulk_f32_kernel<RR>, grid, dim3(kBlock), 0, st, a);        \
+    else hipLaunchKernelGGL(append_bulk_kernel<RR>, grid, dim3(kBlock), 0, st, a);                \
+    return hipGetLastError();                                                                     \
   }
-  return hipGetLastError();
+  MTLA_CASE(64) MTLA_CASE(128) MTLA_CASE(256) MTLA_CASE(512)
+#undef MTLA_CASE
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_prefill_front(const PrefillFrontArgs& args, int mode, hipStream_t st) {
