@@ -7,6 +7,8 @@
 // Operand layout of the instruction: lane = 16 k + i holds A[i, k] and B[k, i], and D[4 k + v, i] in its four results.
 // Which four elements of the contraction one instruction takes is free, as long as A and B agree: a lane loads 16
 // bytes (elements 16 c + 4 k .. + 3 of its row) and instruction j of the four that follow takes element j of every lane.
+#include <type_traits>
+
 #include "bounds.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -158,142 +160,180 @@ __global__ __launch_bounds__(kBlock) void attn_decode_f32_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Keys (blockIdx.z = 0) and values (1) of all rows: C[m, h d_h + k] = sum_n C_hat'[m, n] W^(h)[n, k].
-// 64 x 64 tile per workgroup, the contraction 32 at a time through LDS (rows of 36 floats: the 16-byte reads of 16
-// rows spread over all banks), the next piece requested before this one is multiplied.  D = W . C_hat'^T, so a lane
-// holds four consecutive columns of its row.  2331 rows x 512 x 256, both: 1.2 GFLOP in 23 us.
+// Keys (the first half of blockIdx.x) and values of all rows: C[m, h d_h + k] = sum_n C_hat'[m, n] W^(h)[n, k].
+// 32 rows x 64 columns per workgroup, the contraction 32 at a time through two LDS buffers and one barrier a stage; two
+// stages are on their way from memory.  D = W . C_hat'^T, so a lane holds four consecutive columns of its row.  W_V^(h) has
+// the contraction innermost and is read 16 bytes a lane (rows of 36 floats: 16 rows spread over all banks).  W_K^(h) has it
+// outermost: it stays as it is in LDS ([n][64 columns], rows of 68) and a lane picks its four elements with 4-byte reads,
+// 16 lanes side by side; turned on the way in, its 4-byte writes met 8 to a bank.
+// Bound by the fp32 matrix rate (256 flop per clock and unit) behind the first stages' trip to memory (5 us of it, all
+// workgroups at once): 1920 rows x 512 x 256, both, 1 GFLOP, 23.2 us with 64 x 64 tiles over all rows; 15.7 us now.  What counts
+// is that all units do the same: the row blocks of all sequences come first, padding last, and kKvPad keeps a fifth workgroup
+// off a unit that another one lacks (18 us without it).
 // ---------------------------------------------------------------------------
-constexpr int kGT = 64, kGK = 32, kGP = kGK + 4;
+constexpr int kGT = 64, kGK = 32, kGP = kGK + 4, kGN = kGT + 4, kKvRows = 32;
+constexpr size_t kKvPad = 12 << 10;  // LDS that a workgroup of the keys and values takes beyond its 27 KB: four per unit
 __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
-  __shared__ float sA[kGT][kGP], sW[kGT][kGP];
+  constexpr int ROWS = kKvRows, RT = ROWS / 32;                  // 16-row tiles per wavefront, and row pieces per thread
+  constexpr int W_FLOATS = kGT * kGP > kGK * kGN ? kGT * kGP : kGK * kGN;
+  __shared__ __attribute__((aligned(16))) float sA[2][ROWS][kGP], sW[2][W_FLOATS];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6, l16 = lane & 15, g = lane >> 4;
-  const int M = a.batch * a.T, N = a.n_heads * a.d_head, r = a.r, dh = a.d_head;
-  const int n0 = blockIdx.x * kGT, m0 = blockIdx.y * kGT;
-  const bool keys = blockIdx.z == 0;
-  // pieces a thread brings: two of the rows (16 bytes of the contraction), two of the weight
+  const int N = a.n_heads * a.d_head, r = a.r, dh = a.d_head;
+  const int cols = (int)gridDim.x / 2, b = blockIdx.y, m0 = blockIdx.z * ROWS;
+  const bool keys = (int)blockIdx.x < cols;
+  const int n0 = ((int)blockIdx.x - (keys ? 0 : cols)) * kGT;
+  // pieces a thread brings: RT of the rows (16 bytes of the contraction), two of the weight
   const int ar = tid >> 3, ak = 4 * (tid & 7);  // row (and row + 32), place in the contraction
-  const float* ap[2];
+  const float* ap[RT];
   const float* wp[2];
+  int w_at[2];                                   // their places in sW
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + ar + 32 * i < M ? m0 + ar + 32 * i : M - 1;
-    ap[i] = reinterpret_cast<const float*>(a.cprime) + (size_t)m * r + ak;
+  for (int i = 0; i < RT; ++i) {
+    const int m = m0 + ar + 32 * i < a.T ? m0 + ar + 32 * i : a.T - 1;
+    ap[i] = reinterpret_cast<const float*>(a.cprime) + ((size_t)b * a.T + m) * r + ak;
   }
-  const int wk = tid >> 4, wc = 4 * (tid & 15);  // keys: place in the contraction (and + 16), four columns of one head
-  if (keys) {                                    // w_uk [h][n][k]: the columns are contiguous
+  if (keys) {                                    // w_uk [h][n][k]: four columns of one head at one place of the contraction (and + 16)
+    const int wk = tid >> 4, wc = 4 * (tid & 15);
     const int c = n0 + wc < N ? n0 + wc : 0;
     const float* w = reinterpret_cast<const float*>(a.w_uk) + (size_t)(c / dh) * r * dh + c % dh;
-    wp[0] = w + (size_t)wk * dh;
-    wp[1] = w + (size_t)(wk + 16) * dh;
-  } else {                                       // w_uv [h][k][n]: the contraction is contiguous
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      wp[i] = w + (size_t)(wk + 16 * i) * dh;
+      w_at[i] = (wk + 16 * i) * kGN + wc;
+    }
+  } else {                                       // w_uv [h][k][n]
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int c = n0 + ar + 32 * i < N ? n0 + ar + 32 * i : 0;
       wp[i] = reinterpret_cast<const float*>(a.w_uv) + (size_t)c * r + ak;
+      w_at[i] = (ar + 32 * i) * kGP + ak;
     }
   }
   const size_t wstep = keys ? (size_t)kGK * dh : kGK;
-  f32x4 ra[2], rw[2];
+  f32x4 ra[2][RT], rw[2][2];                     // two stages on their way (four: no faster)
+  auto request = [&](int buf, int stage) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    ra[i] = ld4(ap[i]);
-    rw[i] = ld4(wp[i]);
-  }
-  f32x4 acc[2][2];  // [columns][rows] of the wavefront's 32 x 32 quarter
+    for (int i = 0; i < RT; ++i) ra[buf][i] = ld4(ap[i] + kGK * stage);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) rw[buf][i] = ld4(wp[i] + wstep * (size_t)stage);
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) *reinterpret_cast<f32x4*>(&sA[buf][ar + 32 * i][ak]) = ra[buf][i];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4*>(&sW[buf][w_at[i]]) = rw[buf][i];
+  };
+  const int stages = r / kGK;  // (r is a multiple of 64: an even number)
+  request(0, 0);
+  request(1, 1);
+  if (a.seq_len && m0 >= a.seq_len[b]) return;  // padding only: nothing reads its keys and values
+  f32x4 acc[2][RT];  // [columns][rows] of the wavefront's 32 x 16 RT quarter
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int cw = 32 * (wv & 1), rw0 = 32 * (wv >> 1);
-  for (int k = 0; k < r; k += kGK) {
-    if (k) __syncthreads();
+    for (int j = 0; j < RT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int cw = 32 * (wv & 1), rw0 = 16 * RT * (wv >> 1);
+  put(0);
+  __syncthreads();
+  auto walk = [&](auto KEYS) {
+    auto step = [&](int buf, int k) {
+      // the operands of the stage, then the next one into the other buffer, then the products
+      f32x4 fw[kGK / 16][2], fa[kGK / 16][RT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      *reinterpret_cast<f32x4*>(&sA[ar + 32 * i][ak]) = ra[i];
-      if (keys) {
+      for (int c = 0; c < kGK / 16; ++c) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sW[wc + j][wk + 16 * i] = rw[i][j];
-      } else {
-        *reinterpret_cast<f32x4*>(&sW[ar + 32 * i][ak]) = rw[i];
+        for (int i = 0; i < 2; ++i) {
+          if constexpr (KEYS) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fw[c][i][j] = sW[buf][(16 * c + 4 * g + j) * kGN + cw + 16 * i + l16];
+          } else {
+            fw[c][i] = ld4(&sW[buf][(cw + 16 * i + l16) * kGP + 16 * c + 4 * g]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) fa[c][i] = ld4(&sA[buf][rw0 + 16 * i + l16][16 * c + 4 * g]);
       }
+      if (k + 1 < stages) put(buf ^ 1);
+      request(buf, k + 2 < stages ? k + 2 : stages - 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < kGK / 16; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < RT; ++q) acc[i][q] = mfma4(fw[c][i][j], fa[c][q][j], acc[i][q]);
+      __syncthreads();
+    };
+    for (int k = 0; k < stages; k += 2) {
+      step(0, k);
+      step(1, k + 1);
     }
-    __syncthreads();
-    if (k + kGK < r) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ra[i] = ld4(ap[i] + k + kGK);
-        rw[i] = ld4(wp[i] + wstep * (size_t)(k / kGK + 1));
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < kGK / 16; ++c) {
-      f32x4 fw[2], fa[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fw[i] = ld4(&sW[cw + 16 * i + l16][16 * c + 4 * g]);
-        fa[i] = ld4(&sA[rw0 + 16 * i + l16][16 * c + 4 * g]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) acc[i][q] = mfma4(fw[i][j], fa[q][j], acc[i][q]);
-    }
-  }
+  };
+  if (keys) walk(std::true_type());
+  else walk(std::false_type());
   float* out = reinterpret_cast<float*>(keys ? a.kx : a.vx);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < RT; ++q) {
     const int m = m0 + rw0 + 16 * q + l16;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int n = n0 + cw + 16 * i + 4 * g;
-      if (m < M && n < N) *reinterpret_cast<f32x4*>(out + (size_t)m * N + n) = acc[i][q];
+      if (m < a.T && n < N) *reinterpret_cast<f32x4*>(out + ((size_t)b * a.T + m) * N + n) = acc[i][q];
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// Parallel form: workgroup = 16 RT query rows of one (head, sequence); its four wavefronts take the 16-column tiles in
-// turn (so that a short sequence still gives every wavefront work) and are merged at the end.  Columns: the chunk-final
-// rows below the block, then the block's own rows under the mask (row c is open to row q iff c == q, or c < q and c
+// Parallel form: workgroup = RT blocks of 16 query rows of one (head, sequence); its four wavefronts take the 16-column
+// tiles in turn (so that a short sequence still gives every wavefront work) and are merged at the end.  Columns: the
+// chunk-final rows below a block, then the block's own rows under the mask (row c is open to row q iff c == q, or c < q and c
 // closes its chunk).  DV value columns per workgroup: d_head for `out`, slices of the partial states for the
-// latent-space output.  Bound by the fp32 matrix rate (256 flop per clock and unit) plus the latency of a tile.
-// Three sequences of up to 777 tokens, 8 heads x 64: 30 us; the vector-ALU kernel over absorbed queries took 353 us
+// latent-space output.  Bound by the fp32 matrix rate (256 flop per clock and unit) plus the latency of the first tile.
+// With RT = 2 the blocks are one from either end of the sequence: the columns of the light one are among those of the heavy
+// one, so they share the tiles, and all workgroups of a sequence do the same work.  (32 rows in one piece gave some units the two
+// heaviest workgroups of the launch, 1.8 times the mean.)  A wavefront's next tile is on its way
+// while one is multiplied.
+// Three sequences of up to 777 tokens, 8 heads x 64: 29.6 us, now 22.9; the vector-ALU kernel over absorbed queries took 353 us
 // (and 45 + 67 us for the absorption and the value projection, which this form does not have).
 // ---------------------------------------------------------------------------
 template <int DH, int DR, int DV, int RT>
-__global__ __launch_bounds__(kBlock) void prefill_f32_kernel(ExplicitArgs a) {
-  constexpr int KE = (DH + DR) / 16, KC = DH / 16, NV = DV / 16, MB = 16 * RT;
-  __shared__ float s_o[kWaves][MB][DV + 4];
-  __shared__ float s_m[kWaves][MB], s_l[kWaves][MB];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6, l16 = lane & 15, g = lane >> 4;
-  const int b = blockIdx.z, h = (int)blockIdx.y % a.n_heads, slice = (int)blockIdx.y / a.n_heads;
-  const int m0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * MB;  // the blocks with most columns first
+__global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(ExplicitArgs a) {
+  constexpr int KE = (DH + DR) / 16, KC = DH / 16, NV = DV / 16;
+  __shared__ float s_o[kWaves][16][DV + 4];
+  __shared__ float s_m[kWaves][16 * RT], s_l[kWaves][16 * RT];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a tile is the same for all lanes: its branches and addresses are scalar)
+  const int b = blockIdx.y, h = (int)blockIdx.x % a.n_heads, slice = (int)blockIdx.x / a.n_heads, x = blockIdx.z;
   const bool latent = a.n_slices > 0;
   const int width = latent ? a.r : DH;                         // columns of an output row of this head
   float* out = a.out + (((size_t)b * a.T) * a.n_heads + h) * width + slice * DV;
   const size_t out_pitch = (size_t)a.n_heads * width;
   int len = a.seq_len ? a.seq_len[b] : a.T;
   len = len < a.T ? len : a.T;
-  if (m0 >= len) {  // padding
-    for (int i = tid; i < MB * DV / 4; i += kBlock) {
-      const int q = i / (DV / 4), n = 4 * (i % (DV / 4));
-      if (m0 + q < a.T) *reinterpret_cast<f32x4*>(out + (size_t)(m0 + q) * out_pitch + n) = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int n_all = (a.T + 15) / 16, n_blocks = len > 0 ? (len + 15) / 16 : 0;
+  for (int blk = n_blocks + x; blk < n_all; blk += gridDim.z) {  // blocks of padding
+    for (int i = tid; i < 16 * DV / 4; i += kBlock) {
+      const int m = 16 * blk + i / (DV / 4), n = 4 * (i % (DV / 4));
+      if (m < a.T) *reinterpret_cast<f32x4*>(out + (size_t)m * out_pitch + n) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    return;
   }
+  if (RT * x >= n_blocks) return;
+  // first rows of the blocks, from the sequence's end and from its front (the one in the middle stands alone: -1)
+  int m0[RT];
+  m0[0] = 16 * (n_blocks - 1 - x);
+  if constexpr (RT > 1) m0[1] = 2 * x + 1 < n_blocks ? 16 * x : -1;
   const size_t kpitch = (size_t)a.n_heads * DH;
   const float* kx = reinterpret_cast<const float*>(a.kx) + (size_t)b * a.T * kpitch + h * DH;
   const float* kr = reinterpret_cast<const float*>(a.kr) + (size_t)b * a.T * DR;
   const size_t vpitch = latent ? (size_t)a.r : kpitch;
   const float* vx = latent ? reinterpret_cast<const float*>(a.cprime) + (size_t)b * a.T * a.r + slice * DV
                            : reinterpret_cast<const float*>(a.vx) + (size_t)b * a.T * kpitch + h * DH;
-  // queries of the block's rows, scaled to the log2 domain
   f32x4 qf[RT][KE];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    const int m = m0 + 16 * t + l16 < len ? m0 + 16 * t + l16 : len - 1;
+    const int m_lane = (m0[t] < 0 ? 0 : m0[t]) + l16, m = m_lane < len ? m_lane : len - 1;
     const size_t qr = ((size_t)b * a.T + m) * a.n_heads + h;
     const float* q = reinterpret_cast<const float*>(a.q) + qr * DH + 4 * g;
     const float* qrope = reinterpret_cast<const float*>(a.q_rope) + qr * DR + 4 * g;
@@ -301,8 +341,6 @@ __global__ __launch_bounds__(kBlock) void prefill_f32_kernel(ExplicitArgs a) {
     for (int c = 0; c < KC; ++c) qf[t][c] = ld4(q + 16 * c);
 #pragma unroll
     for (int c = KC; c < KE; ++c) qf[t][c] = ld4(qrope + 16 * (c - KC));
-#pragma unroll
-    for (int c = 0; c < KE; ++c) qf[t][c] *= a.scale_log2;
   }
   float m[RT], l[RT];
   f32x4 acc[RT][NV];
@@ -313,52 +351,64 @@ __global__ __launch_bounds__(kBlock) void prefill_f32_kernel(ExplicitArgs a) {
 #pragma unroll
     for (int n = 0; n < NV; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const int s = a.stride, n_sh = m0 / s, sh_tiles = (n_sh + 15) / 16;
-  for (int tile = wv; tile < sh_tiles + RT; tile += kWaves) {
-    const bool shared = tile < sh_tiles;
-    const int c0 = shared ? 16 * tile : 16 * (tile - sh_tiles);  // first column of the tile: chunk index, or row of the block
-    auto src = [&](int i) {                                      // row that column c0 + i of the tile stands for
-      const int c = c0 + i;
-      if (shared) return (c < n_sh ? c : n_sh - 1) * s + s - 1;
-      return m0 + c < len ? m0 + c : len - 1;
-    };
-    const int krow = src(l16);
+  const int s = a.stride, n_sh = m0[0] / s, sh_tiles = (n_sh + 15) / 16;
+  // tiles 0 .. sh_tiles - 1: the chunk-final rows below the first block; behind them every block's own rows
+  const int tiles = sh_tiles + (RT > 1 && m0[RT - 1] < 0 ? RT - 1 : RT);
+  auto src = [&](int tile, int i) {  // row that column i of a tile stands for
+    if (tile < sh_tiles) {
+      const int c = 16 * tile + i;
+      return (c < n_sh ? c : n_sh - 1) * s + s - 1;
+    }
+    const int own = (tile == sh_tiles ? m0[0] : m0[RT - 1]) + i;
+    return own < len ? own : len - 1;
+  };
+  struct Tile {
+    f32x4 k[KE];
+    float v[NV][4];
+  };
+  auto request = [&](Tile& t, int tile) {
+    const int krow = src(tile, l16);
     const float* kp = kx + (size_t)krow * kpitch + 4 * g;
     const float* krp = kr + (size_t)krow * DR + 4 * g;
-    f32x4 kf[KE];
 #pragma unroll
-    for (int c = 0; c < KC; ++c) kf[c] = ld4(kp + 16 * c);
+    for (int c = 0; c < KC; ++c) t.k[c] = ld4(kp + 16 * c);
 #pragma unroll
-    for (int c = KC; c < KE; ++c) kf[c] = ld4(krp + 16 * (c - KC));
-    float vf[NV][4];
+    for (int c = KC; c < KE; ++c) t.k[c] = ld4(krp + 16 * (c - KC));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float* vp = vx + (size_t)src(4 * g + v) * vpitch + l16;
+      const float* vp = vx + (size_t)src(tile, 4 * g + v) * vpitch + l16;
 #pragma unroll
-      for (int n = 0; n < NV; ++n) vf[n][v] = vp[16 * n];
+      for (int n = 0; n < NV; ++n) t.v[n][v] = vp[16 * n];
     }
+  };
+  auto multiply = [&](const Tile& tl, int tile) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      if (!shared && c0 > 16 * t + 15) continue;  // wholly above the rows
+      const int own = sh_tiles + t, open_sh = m0[t] < 0 ? 0 : m0[t] / s;  // the block's own tile; its open chunks
+      if (tile != own && (tile >= sh_tiles || 16 * tile >= open_sh)) continue;
       f32x4 s_a = {0.f, 0.f, 0.f, 0.f}, s_b = s_a;
 #pragma unroll
       for (int c = 0; c < KE; ++c) {
-        s_a = mfma4(kf[c][0], qf[t][c][0], s_a);
-        s_b = mfma4(kf[c][1], qf[t][c][1], s_b);
-        s_a = mfma4(kf[c][2], qf[t][c][2], s_a);
-        s_b = mfma4(kf[c][3], qf[t][c][3], s_b);
+        s_a = mfma4(tl.k[c][0], qf[t][c][0], s_a);
+        s_b = mfma4(tl.k[c][1], qf[t][c][1], s_b);
+        s_a = mfma4(tl.k[c][2], qf[t][c][2], s_a);
+        s_b = mfma4(tl.k[c][3], qf[t][c][3], s_b);
       }
       float p[4];
-      float mt = -INFINITY;
+      if (tile != own) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int c = c0 + 4 * g + v, q = 16 * t + l16;
-        const bool open = shared ? c < n_sh : (c == q || (c < q && (m0 + c + 1) % s == 0));
-        p[v] = open ? s_a[v] + s_b[v] : -INFINITY;
-        mt = fmaxf(mt, p[v]);
+        for (int v = 0; v < 4; ++v) p[v] = 16 * tile + 4 * g + v < open_sh ? s_a[v] + s_b[v] : -INFINITY;
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int c = 4 * g + v;
+          const bool open = (c == l16) | ((c < l16) & ((m0[t] + c + 1) % s == 0));
+          p[v] = open ? s_a[v] + s_b[v] : -INFINITY;
+        }
       }
+      const float mt = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
       const float mn = fmaxf(m[t], col_max(mt));
-      const float ref = mn == -INFINITY ? 0.f : mn;  // no open column so far
+      const float ref = mn == -INFINITY ? 0.f : mn;  // (every logit so far overflowed)
       const float alpha = __builtin_amdgcn_exp2f(m[t] - ref);
       l[t] *= alpha;
 #pragma unroll
@@ -368,14 +418,33 @@ __global__ __launch_bounds__(kBlock) void prefill_f32_kernel(ExplicitArgs a) {
       }
       m[t] = mn;
 #pragma unroll
-      for (int n = 0; n < NV; ++n) {
-        acc[t][n] *= alpha;
+      for (int n = 0; n < NV; ++n) acc[t][n] *= alpha;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[t][n] = mfma4(vf[n][v], p[v], acc[t][n]);
-      }
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int n = 0; n < NV; ++n) acc[t][n] = mfma4(tl.v[n][v], p[v], acc[t][n]);
+    }
+  };
+  // (a request past the last tile repeats the last one)
+  if (wv < tiles) {
+    Tile ta, tb;
+    request(ta, wv);
+#pragma unroll
+    for (int t = 0; t < RT; ++t)  // to the log2 domain, behind the first request
+#pragma unroll
+      for (int c = 0; c < KE; ++c) qf[t][c] *= a.scale_log2;
+    for (int tile = wv;;) {
+      const int second = tile + kWaves, third = tile + 2 * kWaves;
+      request(tb, second < tiles ? second : tiles - 1);
+      multiply(ta, tile);
+      if (second >= tiles) break;
+      request(ta, third < tiles ? third : tiles - 1);
+      multiply(tb, second);
+      if (third >= tiles) break;
+      tile = third;
     }
   }
-  // ---- merge the wavefronts
+  // ---- merge the wavefronts, 16 rows at a time
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
     const float lt = col_sum(l[t]);
@@ -383,33 +452,39 @@ __global__ __launch_bounds__(kBlock) void prefill_f32_kernel(ExplicitArgs a) {
       s_m[wv][16 * t + l16] = m[t];
       s_l[wv][16 * t + l16] = lt;
     }
-#pragma unroll
-    for (int n = 0; n < NV; ++n) *reinterpret_cast<f32x4*>(&s_o[wv][16 * t + l16][16 * n + 4 * g]) = acc[t][n];
   }
-  __syncthreads();
-  for (int i = tid; i < MB * DV / 4; i += kBlock) {
-    const int q = i / (DV / 4), n = 4 * (i % (DV / 4));
-    if (m0 + q >= a.T) continue;
-    float ms = s_m[0][q];  // a row's own column is always open, so the maximum over the wavefronts is finite
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][q]);
-    float ls = 0.f;
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < RT; ++t) {
+    if (m0[t] < 0) break;
+    if (t) __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float f = __builtin_amdgcn_exp2f(s_m[w][q] - ms);
-      ls += f * s_l[w][q];
-      o += *reinterpret_cast<f32x4*>(&s_o[w][q][n]) * f;
+    for (int n = 0; n < NV; ++n) *reinterpret_cast<f32x4*>(&s_o[wv][l16][16 * n + 4 * g]) = acc[t][n];
+    __syncthreads();
+    for (int i = tid; i < 16 * DV / 4; i += kBlock) {
+      const int qt = i / (DV / 4), q = 16 * t + qt, n = 4 * (i % (DV / 4));
+      if (m0[t] + qt >= a.T) continue;
+      float ms = s_m[0][q];  // a row's own column is always open, so the maximum over the wavefronts is finite
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][q]);
+      float ls = 0.f;
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float f = __builtin_amdgcn_exp2f(s_m[w][q] - ms);
+        ls += f * s_l[w][q];
+        o += *reinterpret_cast<f32x4*>(&s_o[w][qt][n]) * f;
+      }
+      o *= 1.f / ls;
+      if (m0[t] + qt >= len) o = f32x4{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4*>(out + (size_t)(m0[t] + qt) * out_pitch + n) = o;
     }
-    o *= 1.f / ls;
-    if (m0 + q >= len) o = f32x4{0.f, 0.f, 0.f, 0.f};
-    *reinterpret_cast<f32x4*>(out + (size_t)(m0 + q) * out_pitch + n) = o;
   }
 }
 
 template <int DH, int DR, int DV, int RT>
 void launch_prefill_rows(const ExplicitArgs& a, int slices, hipStream_t st, const EventPair& ev) {
-  const dim3 grid((a.T + 16 * RT - 1) / (16 * RT), a.n_heads * slices, a.batch);
+  const unsigned blocks = (a.T + 15) / 16;
+  const dim3 grid(a.n_heads * slices, a.batch, (blocks + RT - 1) / RT);
   launch_timed(prefill_f32_kernel<DH, DR, DV, RT>, grid, dim3(kBlock), 0, st, ev, a);
 }
 
@@ -442,8 +517,8 @@ bool prefill_f32_supported(const ExplicitArgs& a) {
 hipError_t launch_prefill_f32(const ExplicitArgs& args, hipStream_t st, const EventPair& ev) {
   ExplicitArgs a = args;
   a.n_slices = 0;
-  const dim3 grid((a.n_heads * a.d_head + kGT - 1) / kGT, (a.batch * a.T + kGT - 1) / kGT, 2);
-  hipLaunchKernelGGL(kv_f32_kernel, grid, dim3(kBlock), 0, st, a);
+  const unsigned cols = (a.n_heads * a.d_head + kGT - 1) / kGT;
+  hipLaunchKernelGGL(kv_f32_kernel, dim3(2 * cols, a.batch, (a.T + kKvRows - 1) / kKvRows), dim3(kBlock), kKvPad, st, a);
 #define MTLA_CASE(HH, DD, RT)                                                                        \
   if (a.d_head == HH && a.d_rope == DD) {                                                            \
     launch_prefill_rows<HH, DD, HH, RT>(a, 1, st, ev);                                               \

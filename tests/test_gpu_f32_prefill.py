@@ -1,0 +1,67 @@
+"""fp32 storage: the bulk append on the matrix cores and the parallel form, at the edges of their tiles (16 rows or columns, 8
+slots and 16 tokens per append workgroup, 32 x 64 key / value tiles, a block from either end of a sequence), against the
+float64 oracle.  Bound: the fp32 tolerance of the other tests, which is for values of order 1, times the largest value: an output is
+a mean of values under weights whose relative error is that of their logit, a sum of at most 576 products."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import mtla_oracle as O
+from tests import harness as H
+from tests.test_gpu_prefill import _gpu_prefill, _prefill_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,lens,heads,d_head,r,d_rope,stride", [
+    (1, (1, 0, 1), 4, 64, 64, 32, 2),             # one row
+    (16, (16, 15, 1), 4, 64, 64, 32, 1),          # one block: no second one
+    (17, (17, 16, 2), 8, 64, 128, 32, 2),         # one row in the second block
+    (33, (33, 32, 31), 3, 64, 256, 64, 3),        # three blocks: the middle one alone; columns of the product not a multiple of 64
+    (65, (65, 64, 48), 8, 64, 256, 32, 4),
+    (130, (130, 97, 0), 4, 32, 512, 64, 16),      # an empty sequence, the widest latent, the longest stride of the matrix-core append
+    (81, (81, 17, 80), 2, 128, 64, 64, 2),        # one block a workgroup
+    (40, (40, 39, 5), 4, 64, 64, 32, 17),         # stride beyond the matrix-core append
+])
+def test_rows_at_the_edges(T, lens, heads, d_head, r, d_rope, stride):
+    wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_edges", batch=3, d_model=64, n_heads=heads, d_head=d_head, r=r, d_rope=d_rope,
+                                        stride=stride, prefix=T, steps=0, seed=5 + T)
+    wts = W.make_weights(wl)
+    toks, d = _prefill_inputs(wl, wts, T)
+    sess, w, out, lat = _gpu_prefill(wl, wts, d, T, np.array(lens, np.int32))
+    ob = H.OracleBatch.new(wl, wts)
+    for b, n in enumerate(lens):
+        w_ref, _ = ob.append(b, toks[b].c[:n], toks[b].kr[:n])
+        if n:
+            assert np.abs(w[b, :n].cpu().numpy() - w_ref).max() <= H.TOL_W
+            o_ref, ol_ref, _, _ = O.prefill_attn(toks[b].q[:n], toks[b].q_rope[:n], toks[b].c[:n], toks[b].kr[:n], wts.w_uk, wts.w_uv,
+                                                stride, O.softmax_scale(d_head), hyp_A=wts.hyp_A, hyp_a=None, hyp_G=wts.hyp_G)
+            assert H.max_err(out[b, :n], o_ref) <= H.TOL["f32"] * max(1.0, np.abs(o_ref).max())
+            assert H.max_err(lat[b, :n], ol_ref) <= H.TOL["f32"] * max(1.0, np.abs(ol_ref).max())
+        assert torch.all(out[b, n:] == 0) and torch.all(lat[b, n:] == 0)
+    H.check_cache(sess, ob)
+    assert sess.seq_len.cpu().tolist() == list(lens) and sess.device_status() == 0
+
+
+@pytest.mark.parametrize("stride,pieces", [(2, (3, 40, 1, 17)), (1, (7, 8, 9, 33)), (5, (81, 2, 90)), (16, (130, 1, 140)), (20, (41, 60))])
+def test_bulk_append_continues(stride, pieces):
+    # pieces that end inside a slot, in and behind the first group of eight slots; equal to the appends token by token up to the
+    # order of the logit's sum
+    n = sum(pieces)
+    wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_pieces", batch=2, d_model=64, r=128, stride=stride, prefix=n, steps=0, seed=9)
+    wts = W.make_weights(wl)
+    toks = [W.make_tokens(wl, wts, b, 0, n) for b in range(2)]
+    sess = H.make_session(wl)
+    H.upload_weights(sess, wts)
+    ob = H.OracleBatch.new(wl, wts)
+    t = 0
+    for k, m in enumerate(pieces):
+        cut = lambda f: H.to_device(np.stack([getattr(x, f)[t:t + m] for x in toks]), "f32")
+        w = torch.zeros(2, m, device="cuda")
+        sess.append(cut("c"), cut("kr"), w_out=w)
+        for b in range(2):
+            w_ref, _ = ob.append(b, toks[b].c[t:t + m], toks[b].kr[t:t + m])
+            assert np.abs(w[b].cpu().numpy() - w_ref).max() <= H.TOL_W
+        t += m
+        H.check_cache(sess, ob, what=f"piece {k}")
