@@ -87,7 +87,9 @@ const char* mtla_last_hip_error(void);
  *             from the fp32 sum instead of once per folded token.  Part of the
  *             sequence state, like the caches and seq_len.
  *   workspace decode scratch (absorbed queries, split partials) behind a
- *             256-byte header holding the device status word.
+ *             256-byte header holding the device status word and the counters
+ *             of decode steps that run as one launch (zeros between launches).
+ *             Like the scratch behind it, for one decode call at a time.
  * Cache bytes per token are (r + d_rope) * sizeof(elem) / s, the paper's
  * KV-cache accounting (end of the section on decoupled RoPE). */
 size_t mtla_cache_c_bytes(const mtla_ctx* ctx);
@@ -99,8 +101,8 @@ size_t mtla_workspace_bytes(const mtla_ctx* ctx);
  * values or absorbed queries, and the partial slot states C_hat', of all T rows). */
 size_t mtla_prefill_workspace_bytes(const mtla_ctx* ctx, int32_t batch, int32_t T);
 
-/* Clears the workspace header (device status word).  Call once after
- * allocating a workspace, before its first use.  Enqueues a fill kernel. */
+/* Clears the workspace header (device status word, step counters).  Call once
+ * after allocating a workspace, before its first use.  Enqueues a fill kernel. */
 mtla_status mtla_workspace_init(mtla_ctx* ctx, void* workspace /*device*/, void* hip_stream);
 
 /* Synchronises `hip_stream`, copies the sticky device status out of the

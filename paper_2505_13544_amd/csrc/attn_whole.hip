@@ -8,6 +8,7 @@
 // W_V^(h) once per sequence: the limits below are where that costs what the launch saves.
 #include <type_traits>
 
+#include "append_step.h"
 #include "bounds.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
@@ -339,8 +340,21 @@ __device__ __forceinline__ float row_rotated(float v) {  // inside 16 lanes
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + CTRL, 0xf, 0xf, true));
 }
 
-template <int R, int DR>
-__global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) {
+// DH > 0: the whole step as one launch (heads of that width).  Every workgroup of a sequence forms the token's slot and its own head's
+// query for itself, with the sums in the order of append_step_block and absorb_f32_block; nobody waits for anybody: the sequence's
+// workgroups count themselves when they have read its state, and the last one writes it.
+template <int R, int DR, int DH>
+struct StepSharedF32 {
+  float query[R + DR];         // the absorbed query
+  float row[R + DR];           // the token's slot after it
+  float append[256 + 12 + R];  // AppendStep's
+  float q[DH];
+  int32_t arrival;
+};
+struct NoShared {};
+
+template <int R, int DR, int DH>
+__global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(std::conditional_t<DH == 0, WholeArgs, WholeStepArgs> w) {
   constexpr int E = R + DR, KC = R / 32, KE = E / 32;
   __shared__ __attribute__((aligned(16))) float sO[kWaves][R];
   __shared__ float sM[kWaves], sL[kWaves];
@@ -350,8 +364,27 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
   const int sl = lane >> 3, q8 = lane & 7;
   const float* lat = reinterpret_cast<const float*>(a.lat) + (size_t)b * a.max_slots * R + 4 * q8;
   const float* key = reinterpret_cast<const float*>(a.key) + (size_t)b * a.max_slots * DR + 4 * q8;
-  const int len = a.seq_len[b];
+  __shared__ __attribute__((aligned(16))) std::conditional_t<DH == 0, NoShared, StepSharedF32<R, DR, DH == 0 ? 64 : DH>> sh;
+  int len = *const_cast<const volatile int32_t*>(a.seq_len + b);  // (read once: the step's last workgroup writes it)
+  int slot = -1;                                                  // that the step's token goes into, if it takes one
   float4_t x[2][KE], q[KE], wf[2][KC];
+  AppendStep<float, R / 32> st;  // (DH > 0)
+  constexpr int QN = DH == 0 ? 1 : R / 64, QK = DH == 0 ? 1 : DH / 16;
+  float4_t wk[QN][QK], qs = {0.f, 0.f, 0.f, 0.f};
+  float qr = 0.f;
+  int arrival = 0;
+  const int q4 = tid & 3;
+  if constexpr (DH != 0) {  // four lanes share a column of the absorbed query, 64 columns at a time
+    st.request(w.ap, b, tid);
+#pragma unroll
+    for (int u = 0; u < QN; ++u)
+#pragma unroll
+      for (int i = 0; i < QK; ++i)
+        wk[u][i] = *reinterpret_cast<const float4_t*>(reinterpret_cast<const float*>(w.w_uk) + ((size_t)h * R + 64 * u + (tid >> 2)) * DH + 16 * i + 4 * q4);
+    const size_t bh = (size_t)b * a.n_heads + h;
+    if (tid < DH / 4) qs = *reinterpret_cast<const float4_t*>(reinterpret_cast<const float*>(w.q) + bh * DH + 4 * tid);
+    if (tid < DR) qr = reinterpret_cast<const float*>(w.q_rope)[bh * DR + tid];
+  }
   auto load_rows = [&](int s0, int last) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -362,9 +395,11 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
     }
   };
   load_rows(0, a.max_slots - 1);
-  const float* qp = reinterpret_cast<const float*>(a.qcat) + ((size_t)b * a.n_heads + h) * E + 4 * q8;
+  if constexpr (DH == 0) {
+    const float* qp = reinterpret_cast<const float*>(a.qcat) + ((size_t)b * a.n_heads + h) * E + 4 * q8;
 #pragma unroll
-  for (int c = 0; c < KE; ++c) q[c] = *reinterpret_cast<const float4_t*>(qp + 32 * c);
+    for (int c = 0; c < KE; ++c) q[c] = *reinterpret_cast<const float4_t*>(qp + 32 * c);
+  }
   // W_V^(h): eight lanes share an output column, 64 columns at a time
   const float* wp = reinterpret_cast<const float*>(w.w_uv) + ((size_t)h * w.d_head + (tid >> 3)) * R + 4 * q8;
   auto load_w = [&]() {
@@ -374,7 +409,42 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
       for (int c = 0; c < KC; ++c) wf[u][c] = *reinterpret_cast<const float4_t*>(wp + (size_t)32 * u * R + 32 * c);
   };
   load_w();
+  if constexpr (DH != 0) {
+    st.request_slot(w.ap, tid, len);
+    if (tid < DH / 4) *reinterpret_cast<float4_t*>(&sh.q[4 * tid]) = qs;
+    if (tid < DR) sh.query[R + tid] = qr * w.scale_log2;
+    const float wt = st.weight(w.ap, b, tid, sh.append);  // (barriers inside: sh.q is there behind it)
+#pragma unroll
+    for (int u = 0; u < QN; ++u) {  // as absorb_f32_block forms it
+      float dot = 0.f;
+#pragma unroll
+      for (int i = 0; i < QK; ++i) {
+        const float4_t y = *reinterpret_cast<const float4_t*>(&sh.q[16 * i + 4 * q4]);
+        dot += wk[u][i][0] * y[0] + wk[u][i][1] * y[1] + wk[u][i][2] * y[2] + wk[u][i][3] * y[3];
+      }
+      dot = group_reduce<4>(dot, LaneSum());
+      if (q4 == 0) sh.query[64 * u + (tid >> 2)] = dot * w.scale_log2;
+    }
+    if (append_status(len, 1, a.stride, a.max_slots) == 0) {
+      slot = len / a.stride;
+      const bool continuing = len != slot * a.stride;
+#pragma unroll
+      for (int i = 0; i < kMaxRPerThread; ++i) {
+        const int e = tid + i * kBlock;
+        if (e < R) sh.row[e] = (continuing ? st.told[i] : 0.f) + wt * st.cel[i];
+      }
+      if (tid < DR / 8) st.krv.store(&sh.row[R + 8 * tid]);
+    }
+    len += slot >= 0 ? 1 : 0;
+    __syncthreads();
+    // Behind here the workgroup reads no more of what the step changes (a row of the slot that is on its way is dropped).
+    if (tid == kBlock - kWave) arrival = __hip_atomic_fetch_add(w.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int c = 0; c < KE; ++c) q[c] = *reinterpret_cast<const float4_t*>(&sh.query[4 * q8 + 32 * c]);
+  }
   const int live = live_slots(len, a.stride, a.max_slots);
+  // the last row that memory holds: not yet the token's slot, whose row comes out of LDS
+  const int last = DH != 0 && slot > 0 ? slot - 1 : (live > 0 ? live - 1 : 0);
 
   float m = -INFINITY, l = 0.f;
   float4_t acc[KC];
@@ -383,6 +453,14 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
   auto step = [&](int s0) {
     float s[2];
     bool ok[2];
+    if constexpr (DH != 0) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (s0 + 16 * wv + 8 * u + sl == slot) {
+#pragma unroll
+          for (int c = 0; c < KE; ++c) x[u][c] = *reinterpret_cast<const float4_t*>(&sh.row[4 * q8 + 32 * c]);
+        }
+    }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       float4_t d4 = {0.f, 0.f, 0.f, 0.f};
@@ -411,9 +489,12 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
   if (live > 0) {
     step(0);
     for (int s0 = kStep; s0 < live; s0 += kStep) {
-      load_rows(s0, live - 1);
+      load_rows(s0, last);
       step(s0);
     }
+  }
+  if constexpr (DH != 0) {
+    if (tid == kBlock - kWave) sh.arrival = arrival;
   }
   // over the wavefront's eight lane groups
   auto over_slots = [&](float v) {
@@ -433,6 +514,23 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(WholeArgs w) 
     sL[wv] = l;
   }
   __syncthreads();
+  if constexpr (DH != 0) {
+    if (sh.arrival == (int)gridDim.y - 1) {
+      const AppendArgs& ap = w.ap;
+      if (slot >= 0) {
+        const size_t crow = (size_t)b * a.max_slots + slot;
+        for (int e = tid; e < R; e += kBlock) {
+          reinterpret_cast<float*>(ap.cache_c)[crow * R + e] = sh.row[e];
+          if (ap.tail_c) ap.tail_c[(size_t)b * R + e] = sh.row[e];
+        }
+        if (tid < DR) reinterpret_cast<float*>(ap.cache_kr)[crow * DR + tid] = sh.row[R + tid];
+        if (tid == 0) ap.seq_len[b] = len;
+      } else if (tid == 0) {
+        *ap.status = append_status(len, 1, a.stride, a.max_slots);
+      }
+      if (tid == 0) __hip_atomic_store(w.arrived + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
   const size_t oh = (size_t)b * a.n_heads + h;
   const float ms = fmaxf(fmaxf(sM[0], sM[1]), fmaxf(sM[2], sM[3]));
   float f[kWaves], ls = 0.f;
@@ -531,7 +629,7 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
   if (dtype == 0) {
 #define MTLA_CASE(RR, DD)                                                                                          \
   if (a.r == RR && a.d_rope == DD) {                                                                               \
-    launch_timed(attn_whole_f32_kernel<RR, DD>, dim3(a.batch, a.n_heads), dim3(kBlock), 0, st, ev, w);              \
+    launch_timed(attn_whole_f32_kernel<RR, DD, 0>, dim3(a.batch, a.n_heads), dim3(kBlock), 0, st, ev, w);           \
     return hipGetLastError();                                                                                      \
   }
     MTLA_CASE(64, 32)
@@ -560,6 +658,40 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
   MTLA_CASE(128, 64, 128)
   MTLA_CASE(256, 64, 128)
   MTLA_CASE(512, 64, 128)
+#undef MTLA_CASE
+  return hipErrorInvalidValue;
+}
+
+bool attn_step_supported(const WholeStepArgs& w, int dtype) {
+  // fp32 storage, one workgroup a unit.  us a step, two launches / one: 4 heads x 64, r = 64, one sequence of 128 slots 7.2 / 6.5 (as eager
+  // calls, where the host's part of two launches is what counts, 9.1 / 6.4); 8 heads x 64, 8 sequences, r = 256: 32 slots 9.3 / 9.4, 450 16.9 /
+  // 16.7.  In bf16, where every workgroup of a sequence would read 32 KB of the hyper-network and its head's 32 KB of W_K for itself, it was
+  // built and gains nothing: 16 sequences of 8 heads x 64, r = 256: 150 slots 9.2 / 10.0, 528 12.2 / 12.6; r = 128: 20 slots 7.0 / 6.7, 200 8.3 / 8.6.
+  const AttnArgs& a = w.at;
+  const AppendArgs& ap = w.ap;
+  return dtype == 0 && attn_whole_supported(w, dtype) && (w.d_head == 64 || w.d_head == 128) && (size_t)a.n_heads * a.batch <= 256 &&
+         a.batch <= kStepArrivals && ap.tail_c && !ap.w_override && !ap.n_new && !ap.w_out && !ap.slot_out;
+}
+
+hipError_t launch_attn_step(const WholeStepArgs& w, hipStream_t st, const EventPair& ev) {
+  const AttnArgs& a = w.at;
+#define MTLA_CASE(RR, DD, HH)                                                                                      \
+  if (a.r == RR && a.d_rope == DD && w.d_head == HH) {                                                             \
+    launch_timed(attn_whole_f32_kernel<RR, DD, HH>, dim3(a.batch, a.n_heads), dim3(kBlock), 0, st, ev, w);          \
+    return hipGetLastError();                                                                                      \
+  }
+  MTLA_CASE(64, 32, 64)
+  MTLA_CASE(64, 64, 64)
+  MTLA_CASE(128, 32, 64)
+  MTLA_CASE(128, 64, 64)
+  MTLA_CASE(256, 32, 64)
+  MTLA_CASE(256, 64, 64)
+  MTLA_CASE(64, 32, 128)
+  MTLA_CASE(64, 64, 128)
+  MTLA_CASE(128, 32, 128)
+  MTLA_CASE(128, 64, 128)
+  MTLA_CASE(256, 32, 128)
+  MTLA_CASE(256, 64, 128)
 #undef MTLA_CASE
   return hipErrorInvalidValue;
 }

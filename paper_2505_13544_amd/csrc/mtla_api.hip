@@ -500,6 +500,30 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     at.part_f16 = combine_mfma_supported(probe) ? 1 : 0;
     at.run_cost = kRunCost;
   }
+  const bool timed = c->prof_n < (int)c->ev_start.size();
+  EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
+  if (timed) {
+    ev.start = c->ev_start[c->prof_n];
+    ev.stop = c->ev_stop[c->prof_n++];
+  }
+  // few short sequences; a schedule or a chunk that the caller set (the default's value too) stays what it says
+  WholeStepArgs wh;
+  wh.at = at;
+  wh.w_uv = w_uv;
+  wh.out = out;
+  wh.out_latent = out_latent;
+  wh.lse = lse;
+  wh.d_head = g.d_head;
+  const bool whole = c->schedule == 0 && !c->chunk_set && (use_mfma || g.dtype == MTLA_F32) && attn_whole_supported(wh, g.dtype);
+  if (whole && ap && ap->status == reinterpret_cast<int32_t*>(workspace)) {  // (not the static scratch, whose header nobody clears)
+    wh.ap = *ap;
+    wh.q = q;
+    wh.q_rope = q_rope;
+    wh.w_uk = w_uk;
+    wh.scale_log2 = ab.scale_log2;
+    wh.arrived = reinterpret_cast<int32_t*>(ws) + kArrivalWord;
+    if (attn_step_supported(wh, g.dtype)) return hip_ok(launch_attn_step(wh, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
+  }
   if (ap && decode_front_supported(*ap, ab)) {  // append and absorb do not depend on each other: one launch
     if (!hip_ok(launch_decode_front(*ap, ab, st))) return MTLA_ERR_HIP;
   } else if (ap && g.dtype == MTLA_F32) {
@@ -510,23 +534,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     if (ap && !hip_ok(launch_append(*ap, g.dtype, st))) return MTLA_ERR_HIP;
     if (!hip_ok(launch_absorb(ab, g.dtype, st))) return MTLA_ERR_HIP;
   }
-  const bool timed = c->prof_n < (int)c->ev_start.size();
-  EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
-  if (timed) {
-    ev.start = c->ev_start[c->prof_n];
-    ev.stop = c->ev_stop[c->prof_n++];
-  }
-  // few short sequences; a schedule or a chunk that the caller set (the default's value too) stays what it says
-  if (c->schedule == 0 && !c->chunk_set && (use_mfma || g.dtype == MTLA_F32)) {
-    WholeArgs wh;
-    wh.at = at;
-    wh.w_uv = w_uv;
-    wh.out = out;
-    wh.out_latent = out_latent;
-    wh.lse = lse;
-    wh.d_head = g.d_head;
-    if (attn_whole_supported(wh, g.dtype)) return hip_ok(launch_attn_whole(wh, g.dtype, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
-  }
+  if (whole) return hip_ok(launch_attn_whole(wh, g.dtype, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
   const hipError_t le = g.dtype == MTLA_F32 ? launch_attn_decode_f32(at, st, ev)
                         : !use_mfma         ? launch_attn_valu(at, g.dtype, st, ev)
                                   : (attn_cols_supported(at) ? launch_attn_cols(at, st, ev) : launch_attn_mfma(at, st, ev));

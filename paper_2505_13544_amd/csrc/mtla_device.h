@@ -7,7 +7,8 @@ namespace mtla {
 
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kBlock = 256;        // threads per workgroup in the VALU kernels (4 waves)
-constexpr int kHeaderBytes = 256;  // workspace header; int32[0] is the sticky device status
+constexpr int kHeaderBytes = 256;  // workspace header, cleared once: int32[0] is the sticky device status,
+constexpr int kArrivalWord = 8;    // from here on the counters of a decode step in one launch (zeros between launches)
 
 // Storage element types.  bf16 is carried as its 16-bit pattern.
 struct bf16 {

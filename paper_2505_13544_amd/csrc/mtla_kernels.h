@@ -131,6 +131,17 @@ struct WholeArgs {
   int d_head = 0;
 };
 
+// The whole decode step in that launch: append and absorption as well (fp32 storage).
+constexpr int kStepArrivals = 56;  // (the header's words from kArrivalWord on)
+struct WholeStepArgs : WholeArgs {
+  AppendArgs ap;
+  const void* q = nullptr;       // as AbsorbArgs
+  const void* q_rope = nullptr;
+  const void* w_uk = nullptr;
+  float scale_log2 = 0.f;
+  int32_t* arrived = nullptr;    // [kStepArrivals] workgroups of a sequence that have read its state; zeros between launches
+};
+
 // Parallel form with explicit per-head keys and values (bf16).
 struct ExplicitArgs {
   const void* q;       // [B, T, n_heads, d_head]
@@ -368,6 +379,9 @@ hipError_t launch_prefill_f32(const ExplicitArgs& a, hipStream_t st, const Event
 // few short sequences: no partials, no combine (dtype: the storage type)
 bool attn_whole_supported(const WholeArgs& w, int dtype);
 hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, const EventPair& ev = EventPair());
+// ... and the whole decode step of fp32 storage
+bool attn_step_supported(const WholeStepArgs& w, int dtype);
+hipError_t launch_attn_step(const WholeStepArgs& w, hipStream_t st, const EventPair& ev = EventPair());
 hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t st, const EventPair& ev = EventPair());
 // bf16 matrix-core variant of the split pass (decode addressing only)
 bool attn_mfma_supported(const AttnArgs& a);
