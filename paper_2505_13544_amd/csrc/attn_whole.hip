@@ -150,17 +150,23 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) q[kk] = *reinterpret_cast<const u32x4_t*>(qp + 32 * kk);
   }
-  u32x4_t wf[NT][KC];
+  // W_V^(h) of this many heads is in registers or on its way: the first one's from the top, the others' from where the walk's sums
+  // leave theirs.  Head after head through the same registers, the kernel ended in a trip to memory for each: us a step, before and
+  // now, 8 heads x 64, r = 256, 250 slots: 64 sequences (two heads a workgroup) 11.5 / 10.8, 128 (four) 14.9 / 13.5; 8 heads x 128, r = 256,
+  // 64 sequences 12.6 / 11.1.  (r = 512, whose registers are full of sums: one, 18.0 against 18.25 with two.)
+  constexpr int HA0 = (G::per_simd > 1 ? 144 : 0) / (4 * NT * KC), HA = HA0 < 1 ? 1 : (HA0 < HPW ? HA0 : HPW);
+  u32x4_t wf[HA][NT][KC];
   const int d0 = 16 * NT * wv;  // the wavefront's output columns
-  auto load_w = [&](int h) {
+  auto load_w = [&](int hp) {
+    const int h = h0 + hp;
     const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.w_uv) + ((size_t)(h < a.n_heads ? h : a.n_heads - 1) * DH + d0 + l16) * R + 8 * g;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int kk = 0; kk < KC; ++kk) wf[i][kk] = *reinterpret_cast<const u32x4_t*>(wp + 16 * i * R + 32 * kk);
+      for (int kk = 0; kk < KC; ++kk) wf[hp % HA][i][kk] = *reinterpret_cast<const u32x4_t*>(wp + 16 * i * R + 32 * kk);
   };
   const bool multiplies = OT >= NW || wv < OT;  // (a wavefront too many has no output columns)
-  if (!kNext && kEarly && multiplies) load_w(h0);
+  if (!kNext && kEarly && multiplies) load_w(0);
   const int live = live_slots(len, a.stride, a.max_slots), tiles = (live + 15) / 16;
   const int mine = tiles > wv ? (tiles - wv + NW - 1) / NW : 0;
   constexpr int W = kEarly ? NT * KC : 0;
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   const auto none = std::integral_constant<int, 0>{};
   const auto one_tile = std::integral_constant<int, KT>{};
   if (kNext && mine > 1) issue(1, live - 1, place1);
-  if (kNext && multiplies) load_w(h0);
+  if (kNext && multiplies) load_w(0);
   if (kNext && mine > 1) wait_but_w(one_tile);
   else wait_but_w(none);
   if constexpr (G::query_lds) {
@@ -260,12 +266,16 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   }
 
   // ---- the wavefronts' states side by side, each in its area
-  if (!kEarly && multiplies) load_w(h0);
+  if (!kEarly && multiplies) load_w(0);
   const float l_own = quarter_reduce(l_run, LaneSum());
   if (l16 < 2 * HPW) {  // columns 16 mt + 4g .. + 3 of head l16 / 2, from one plane of the weights
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<float4_t*>(area + l16 * R * 4 + 4 * (16 * mt + 4 * g)) = acc[mt];
     if (g == 0 && !(l16 & 1)) *reinterpret_cast<float2*>(area + G::ml + 4 * l16) = make_float2(m_ref, l_own);
+  }
+  if (multiplies) {
+#pragma unroll
+    for (int hp = 1; hp < HA; ++hp) load_w(hp);
   }
   __syncthreads();
 #pragma unroll
@@ -314,9 +324,9 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
     for (int kk = 0; kk < KC; ++kk) {
       const bf16x8_t p = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(pl + 64 * kk));
 #pragma unroll
-      for (int i = 0; i < NT; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[i][kk]), p, o[i], 0, 0, 0);
+      for (int i = 0; i < NT; ++i) o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[hp % HA][i][kk]), p, o[i], 0, 0, 0);
     }
-    if (hp + 1 < HPW) load_w(h0 + hp + 1);
+    if (hp + HA < HPW) load_w(hp + HA);
     if (h0 + hp >= a.n_heads) break;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
