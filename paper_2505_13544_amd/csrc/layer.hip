@@ -102,11 +102,11 @@ __global__ __launch_bounds__(kBlock) void layer_front_kernel(LayerFrontArgs a) {
     if (is_key) n0 -= nqr;
     const int n_out = is_key ? a.d_rope : nqr;
     const int pos = mine ? a.seq_len[tok] : 0;  // 0-based position of the token this step appends
-    const auto freq = a.rope_freq[((n0 + n2) % a.d_rope) / 2];
+    const float2 cs = rope_angle(pos, a.rope_freq[((n0 + n2) % a.d_rope) / 2]);
     float2 o = tile_sum(linear_tile(reinterpret_cast<const uint16_t*>(is_key ? a.w_kr : a.w_qr), n_out, x, a.batch, K, n0, tok0,
                                     l16, g, st), s_red, tid, wv, l16, g);
     if (mine) {
-      rope_pair(o.x, o.y, pos, freq);
+      o = rope_turn(o, cs);
       if (is_key)  // the key goes into the cache: storage type
         *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(a.kr) + (size_t)tok * n_out + n0 + n2) = pack_bf16x2(o.x, o.y);
       else

@@ -1081,21 +1081,16 @@ mtla_status mtla_layer_prefill(mtla_ctx* c, const mtla_layer_weights* lw, void* 
   int32_t* pos0 = reinterpret_cast<int32_t*>(sc + L.pos0);
 
   // ---- the four projections of x in one launch, rotation and scaling on the way out
-  RopeTableArgs rt;
-  rt.pos0 = seq_len;
-  rt.table = reinterpret_cast<float2*>(sc + L.rope_cs);
-  rt.rows = M;
-  rt.T = T;
-  rt.d_rope = g.d_rope;
-  for (int k = 0; k < 32; ++k)
-    rt.rope_freq[k] = std::pow((double)(lw->rope_base > 0.f ? lw->rope_base : 10000.f), -2.0 * k / g.d_rope);
   GemmArgs gx;
   gx.A = x;
   gx.M = (int)M;
   gx.K = lw->d_model;
   gx.in_bf16 = 1;
   gx.d_rope = g.d_rope;
-  gx.rope_cs = rt.table;
+  gx.rope_cs = reinterpret_cast<float2*>(sc + L.rope_cs);
+  gx.rope_pos0 = seq_len;
+  for (int k = 0; k < 32; ++k)
+    gx.rope_freq[k] = std::pow((double)(lw->rope_base > 0.f ? lw->rope_base : 10000.f), -2.0 * k / g.d_rope);
   gx.n_seg = 4;
   gx.rows.n_new = n_new;
   gx.rows.T = T;
@@ -1145,7 +1140,7 @@ mtla_status mtla_layer_prefill(mtla_ctx* c, const mtla_layer_weights* lw, void* 
   if (!gemm_nt_supported(gy)) return MTLA_ERR_UNSUPPORTED;
 
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  if (!hip_ok(launch_rope_table(rt, st)) || !hip_ok(launch_gemm_nt(gx, st)) || !hip_ok(launch_prefill_front(fa, 2, st)) ||
+  if (!hip_ok(launch_gemm_nt(gx, st)) || !hip_ok(launch_prefill_front(fa, 2, st)) ||
       !hip_ok(launch_prefill_explicit(ex, st, next_event(c))))
     return MTLA_ERR_HIP;
   return hip_ok(launch_gemm_nt(gy, st)) ? MTLA_OK : MTLA_ERR_HIP;

@@ -137,17 +137,23 @@ __device__ __forceinline__ int wave_scan(int v) {
 __device__ __forceinline__ float wave_sum(float v) { return group_reduce<kWave>(v, LaneSum()); }
 __device__ __forceinline__ float wave_max(float v) { return group_reduce<kWave>(v, LaneMax()); }
 
-// The pair (a, b) = elements (2k, 2k+1) of a d-wide vector, turned by pos * freq, freq = base^(-2k/d)
-// (a double, from the host: positions reach tens of thousands of radians, so the product and its
-// reduction to [-pi, pi] are done in double; sine and cosine of the reduced angle in float).
-__device__ __forceinline__ void rope_pair(float& a, float& b, int pos, double freq) {
-  double ang = (double)pos * freq;
-  ang -= 6.283185307179586476925 * rint(ang * 0.15915494309189533577);
-  float sn, cs;
-  sincosf((float)ang, &sn, &cs);
-  const float ra = a * cs - b * sn, rb = a * sn + b * cs;
-  a = ra;
-  b = rb;
+// (cos, sin) of pos * freq, freq = base^(-2k/d) (a double, from the host: positions reach tens of thousands of radians, so the
+// product and its reduction to a quarter turn are done in double).  Taylor series in float from there: what they leave out is
+// below 2e-9 at pi / 4.  Some forty instructions without a branch, where the library's pair of any argument is several hundred
+// that a cold launch fetches first (a short prompt's projections 9.1 us with the library's pair, 8.6 with this one); largest error against 64 bits over 200000 positions
+// 6.9e-8, the library's behind a reduction to a whole turn 1.3e-7.
+__device__ __forceinline__ float2 rope_angle(int pos, double freq) {
+  const double ang = (double)pos * freq, q = rint(ang * 0.63661977236758134308);
+  const float x = (float)fma(q, -1.57079632679489661923, ang), z = x * x;
+  const float sp = fmaf(z, fmaf(z, fmaf(z, 1.f / 362880, -1.f / 5040), 1.f / 120), -1.f / 6);
+  const float cp = fmaf(z, fmaf(z, fmaf(z, fmaf(z, -1.f / 3628800, 1.f / 40320), -1.f / 720), 1.f / 24), -0.5f);
+  const float sn = fmaf(x * z, sp, x), cs = fmaf(z, cp, 1.f);
+  const int k = (int)q;  // quarter turns
+  const float c = (k & 1) ? sn : cs, s = (k & 1) ? cs : sn;
+  return make_float2(((k + 1) & 2) ? -c : c, (k & 2) ? -s : s);
 }
+
+// A pair of elements (2k, 2k + 1) of a vector, turned by that angle.
+__device__ __forceinline__ float2 rope_turn(float2 v, float2 cs) { return make_float2(v.x * cs.x - v.y * cs.y, v.x * cs.y + v.y * cs.x); }
 
 }  // namespace mtla

@@ -199,14 +199,19 @@ struct GemmArgs {
   int M = 0, K = 0, n_seg = 1;
   GemmSegment seg[kSegments];
   int in_bf16 = 0;          // A and W: 0 fp16, 1 bf16
-  const float2* rope_cs = nullptr;  // epi 1, 2: [M, d_rope / 2] (cos, sin) of every row's angles
+  // epi 1, 2: row b * rows.T + t is turned at position rope_pos0[b] + t (NULL: t) by rope_freq[k] = base^(-2k / d_rope); rope_cs is
+  // room for a table of these angles, [M, d_rope / 2], that the launcher fills where the tiles do not compute their own
+  float2* rope_cs = nullptr;
+  const int32_t* rope_pos0 = nullptr;
+  double rope_freq[32] = {};
   int d_rope = 0;
   GemmRows rows;
-  // set by the launcher; xcds: the XCDs that the row blocks are dealt to (8, or 1 for few of them); stream_out: results that the
+  // set by the launcher; rope_ready: the table is filled; xcds: the XCDs that the row blocks are dealt to (8, or 1 for few of them); stream_out: results that the
   // caches would not hold are stored past them
   int col_blocks = 0;
   unsigned row_blocks = 0, xcds = 1;
   int stream_out = 0;
+  int rope_ready = 0;
 };
 
 struct RopeTableArgs {
@@ -214,7 +219,7 @@ struct RopeTableArgs {
   float2* table;         // [rows, d_rope / 2]
   size_t rows;
   int T, d_rope;
-  double rope_freq[32];  // base^(-2k / d_rope)
+  double rope_freq[32];
 };
 
 // Rows of a continuing prefill, in front of the key / value product: slot states of the past out of the cache, the
@@ -402,7 +407,6 @@ bool prefill_explicit_supported(const ExplicitArgs& a);
 hipError_t launch_attn_latent(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 bool gemm_nt_supported(const GemmArgs& a);
-hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st);
 // the same products as streams of 256 x 256 tiles (launch_gemm_nt picks)
 bool gemm_wide_supported(const GemmArgs& a);

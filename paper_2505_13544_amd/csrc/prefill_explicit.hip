@@ -44,7 +44,7 @@ namespace {
 // K % 32 == 0, N % 8 == 0), fp32 accumulation, one of three ways out (GemmSegment::epi):
 //   0  C fp16 = scale * acc                       (keys, values, queries)
 //   1  C fp16 = scale * RoPE(acc), 2 the same as bf16 without the scale (RoPE queries, the shared RoPE key: row
-//      b*T + t is turned at pos0[b] + t; the cosines and sines come from a table, rope_cs[row][k])
+//      b*T + t is turned at pos0[b] + t; 64 x 64 tiles form the cosines and sines they need, the larger ones read a table, rope_cs[row][k])
 //   3  C fp32 = acc
 // A launch takes up to four products that share A ("segments", each with its own weights, columns and way out): a short
 // prompt's projections are one launch instead of four.
@@ -69,6 +69,11 @@ struct GemmGeom {
   static constexpr int NBUF = BM >= 256 ? 3 : (BM == 128 ? 4 : 6), PF = NBUF - SPB;
   static constexpr int NLW = W_BYTES / 1024 / NWV, NLA = A_BYTES / 1024 / NWV, LOADS = NLW + NLA;  // loads per wavefront and stage
   static constexpr int PER_CU = BM == 256 && BN == 256 ? 1 : 2;
+  // Tiles of 64 rows form their angles while their first operands are on the way: a row is a lane, a frequency a wavefront's.  A
+  // launch that writes a table first is 3 us of a short prompt's; the layer over 129 tokens 35.5, now 34.5 us, 1000 tokens 46.0,
+  // now 44.4.  (Where the larger tiles pay there are thousands of rows: each would be turned once per column block, and the table's
+  // launch is 6 us of 1280.)
+  static constexpr bool OWN_ANGLES = BM == 64 && BN == 64;
   static_assert(PF >= SPB && 2 * LOADS * SPB <= 63 && NLW >= 1 && NLA >= 1, "buffers, wait counts");
 };
 
@@ -79,6 +84,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
   constexpr int BK = G::BK, NBUF = G::NBUF, PF = G::PF, NWV = G::NWV, NT = G::NT, WN = G::WN, WM = G::WM;
   constexpr int W_BYTES = G::W_BYTES, STAGE = G::STAGE, NLW = G::NLW, NLA = G::NLA, LOADS = G::LOADS;
   constexpr int JM = WM / 16, IN = WN / 16;
+  constexpr bool kAngles = BF16 && G::OWN_ANGLES;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * STAGE];
 
   const int M = a.M, K = a.K;
@@ -100,6 +106,15 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
   const int ib = (int)(rem / gsz * nx + w % nx);  // row block
   int rb = ib * BM, row_end = M;
   bool work = rb < M;
+  double freq[kAngles ? 32 / NWV : 1];  // asked for here: behind the first operands each would be a wait of its own
+  int start = 0;                        // of the block's sequence, where the rows are told apart
+  if constexpr (kAngles) {
+#pragma unroll
+    for (int i = 0; i < 32 / NWV; ++i) {
+      freq[i] = a.rope_freq[wv + NWV * i];
+      asm volatile("" : "+s"(freq[i]));
+    }
+  }
   if (a.rows.n_new || a.rows.pos0) {
     work = false;
     const GemmRows& q = a.rows;
@@ -117,6 +132,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
       int before = 0;
       for (int b0 = 0; b0 < n_seq && !work; b0 += kWave) {
         const int used = b0 + lane < n_seq ? used_rows(b0 + lane) : 0;
+        const int from = kAngles && a.rope_pos0 && b0 + lane < n_seq ? a.rope_pos0[b0 + lane] : 0;
         const int n = (used + BM - 1) / BM;
         const int upto = wave_scan(n);  // blocks of sequences b0 .. b0 + lane
         const unsigned long long here = __ballot(ib - before < upto);
@@ -124,6 +140,7 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
           const int at = __builtin_ctzll(here);
           rb = (b0 + at) * Tp + (ib - before - (__shfl(upto, at, kWave) - __shfl(n, at, kWave))) * BM;
           row_end = (b0 + at) * Tp + __shfl(used, at, kWave);
+          start = __shfl(from, at, kWave);
           work = true;
         }
         before += __shfl(upto, kWave - 1, kWave);
@@ -184,6 +201,24 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
 #pragma unroll
   for (int st = 0; st < PF; ++st)
     if (st < n_stages) issue(st);
+  float2 turn[kAngles ? 32 / NWV : 1];  // lane: row; the wavefronts take the frequencies in turn
+#pragma unroll
+  for (float2& t : turn) t = make_float2(1.f, 0.f);
+  if constexpr (kAngles) {
+    if (work && (epi == 1 || epi == 2) && !a.rope_ready) {
+      const int T = a.rows.T, row = rb + lane;
+      int pos = start + row % T;
+      if (!a.rows.n_new && !a.rows.pos0 && a.rope_pos0) {  // rows of several sequences (scalar loads: none that waits for the operands)
+        for (int b = rb / T; b * T < rb + BM && b * T < M; ++b) {
+          start = load_uniform_i32(a.rope_pos0, b);
+          if (row >= b * T) pos = start + row - b * T;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 32 / NWV; ++i)
+        if (wv + NWV * i < a.d_rope / 2) turn[i] = rope_angle(pos, freq[i]);
+    }
+  }
   constexpr int SPB = G::SPB;
   auto multiply = [&](int st) {
     const unsigned char* wb = lds + (st % NBUF) * STAGE + wn * 64 + frag_off;
@@ -231,6 +266,19 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
   unsigned char* Cb = reinterpret_cast<unsigned char*>(sg.C);
   const float sc = sg.scale;
   barrier_only();  // every wavefront is done with the last stage
+  constexpr int kAnglesAt = BM * (4 * BN + 16);  // behind the rows on their way out: [two pairs of a head][row]
+  static_assert(!kAngles || kAnglesAt + 16 * 16 * BM <= NBUF * STAGE, "the angles fit in the stage buffers");
+  const bool own_angles = kAngles && (epi == 1 || epi == 2) && !a.rope_ready;
+  if constexpr (kAngles) {
+    if (own_angles) {
+#pragma unroll
+      for (int i = 0; i < 32 / NWV; ++i) {
+        const int k = wv + NWV * i;
+        if (k < a.d_rope / 2) *reinterpret_cast<float2*>(lds + kAnglesAt + ((k >> 1) * BM + lane) * 16 + 8 * (k & 1)) = turn[i];
+      }
+      __syncthreads();
+    }
+  }
   auto way_out = [&](auto kind) {
     constexpr int EPI = decltype(kind)::value;
     constexpr int ES = EPI == 3 ? 4 : 2;                       // bytes per output element
@@ -253,7 +301,9 @@ __global__ __launch_bounds__((GemmGeom<BM, BN>::NT), (GemmGeom<BM, BN>::PER_CU))
           float4_t o = acc[j][i];
           if constexpr (EPI == 1 || EPI == 2) {  // rotation: the lane's columns are two pairs of one head
             const int jn = (nb + col) % a.d_rope;              // element inside the head, a multiple of 4
-            const float4_t cs = *reinterpret_cast<const float4_t*>(a.rope_cs + (size_t)grow * (a.d_rope / 2) + jn / 2);  // (cos, sin) of both
+            float4_t cs;                                       // (cos, sin) of both
+            if (own_angles) cs = *reinterpret_cast<const float4_t*>(lds + kAnglesAt + (jn / 4 * BM + row + l16) * 16);
+            else cs = *reinterpret_cast<const float4_t*>(a.rope_cs + (size_t)grow * (a.d_rope / 2) + jn / 2);
             o = float4_t{o[0] * cs[0] - o[1] * cs[1], o[0] * cs[1] + o[1] * cs[0], o[2] * cs[2] - o[3] * cs[3], o[2] * cs[3] + o[3] * cs[2]};
           }
           if constexpr (EPI == 3) *reinterpret_cast<float4_t*>(lrow + 4 * col) = o;
@@ -714,7 +764,7 @@ bool gemm_nt_supported(const GemmArgs& a) {
   for (int i = 0; i < a.n_seg; ++i) {
     const GemmSegment& g = a.seg[i];
     if (g.N < 8 || g.N % 8 != 0 || !(g.epi >= 0 && g.epi <= 3)) return false;
-    if ((g.epi == 1 || g.epi == 2) && (!a.in_bf16 || a.d_rope % 4 != 0 || a.d_rope < 4 || !a.rope_cs || g.N % a.d_rope != 0)) return false;
+    if ((g.epi == 1 || g.epi == 2) && (!a.in_bf16 || a.d_rope % 4 != 0 || a.d_rope < 4 || a.d_rope > 64 || !a.rope_cs || g.N % a.d_rope != 0)) return false;
     blocks += (size_t)(g.N + 63) / 64;
   }
   if (a.rows.T < 1 || ((a.rows.n_new || a.rows.pos0) && a.M % (a.rows.past + a.rows.T) != 0)) return false;
@@ -730,20 +780,35 @@ __global__ __launch_bounds__(kBlock) void rope_table_kernel(RopeTableArgs a) {
   const size_t row = idx / half;
   const int k = int(idx % half), b = int(row / a.T);
   const int pos = (a.pos0 ? a.pos0[b] : 0) + int(row - (size_t)b * a.T);
-  float cs = 1.f, sn = 0.f;
-  rope_pair(cs, sn, pos, a.rope_freq[k]);  // (1, 0) turned by the angle
-  a.table[idx] = make_float2(cs, sn);
+  a.table[idx] = rope_angle(pos, a.rope_freq[k]);
 }
 
-hipError_t launch_rope_table(const RopeTableArgs& a, hipStream_t st) {
+namespace {
+
+hipError_t launch_rope_table(const GemmArgs& g, hipStream_t st) {
+  RopeTableArgs a;
+  a.pos0 = g.rope_pos0;
+  a.table = g.rope_cs;
+  a.rows = (size_t)g.M;
+  a.T = g.rows.T;
+  a.d_rope = g.d_rope;
+  for (int k = 0; k < 32; ++k) a.rope_freq[k] = g.rope_freq[k];
   const size_t n = a.rows * (a.d_rope / 2);
   hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, a);
   return hipGetLastError();
 }
 
+}  // namespace
+
 hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
   GemmArgs a = args;
+  bool turned = false;
+  for (int i = 0; i < a.n_seg; ++i) turned = turned || a.seg[i].epi == 1 || a.seg[i].epi == 2;
+  auto table = [&]() {
+    a.rope_ready = 1;
+    return launch_rope_table(a, st);
+  };
   int pick = 0;
   const float whole = gemm_cost(a, gemm_wide_supported(a), pick);
   if (a.n_seg > 1) {
@@ -759,9 +824,15 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
     for (int i = least; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
     int p1 = 0, p2 = 0;
     if (gemm_cost(one, gemm_wide_supported(one), p1) + gemm_cost(rest, gemm_wide_supported(rest), p2) < whole) {
-      const hipError_t e = launch_gemm_nt(rest, st);
+      hipError_t e = turned && !a.rope_ready ? table() : hipSuccess;  // one for both
+      one.rope_ready = rest.rope_ready = a.rope_ready;
+      if (e == hipSuccess) e = launch_gemm_nt(rest, st);
       return e != hipSuccess ? e : launch_gemm_nt(one, st);
     }
+  }
+  if (turned && !a.rope_ready && (pick == kWide || kGemmTiles[pick].bm != 64)) {
+    const hipError_t e = table();
+    if (e != hipSuccess) return e;
   }
   if (pick == kWide) return launch_gemm_wide(a, st);
   const int bm = kGemmTiles[pick].bm;
