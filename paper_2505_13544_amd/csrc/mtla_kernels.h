@@ -258,7 +258,8 @@ struct PrefillFrontArgs {
   void* w_o16 = nullptr;
   size_t n_wo = 0;
   int n_heads = 0, d_head = 0;
-  unsigned groups = 1, n_main = 0, n_conv = 0;  // set by the launcher
+  unsigned groups = 1, n_main = 0, n_conv = 0;  // set by the launcher, as
+  int group_slots = 1;                          // slots of a workgroup
 };
 
 // The sequence state a continuing prefill starts from, saved in front of an append of its own.

@@ -1,8 +1,8 @@
-// What comes before the matrix products of a prefill (bf16 storage), in one launch: the append of the new tokens
+// What comes before the matrix products of a prefill (bf16 storage but for the append alone), in one launch: the append of the new tokens
 // (merge weights and cache), the rows the key / value product reads (slot states of the past and partial states
 // C_hat'[m] of the new rows, as fp16), the RoPE keys as fp16, and the weights as fp16.
 //
-//   append_bulk_kernel      mtla_cache_append of many tokens (the append alone)
+//   append_bulk_kernel      mtla_cache_append of many tokens (the append alone); append_bulk_f32_kernel the same in fp32 storage
 //   prefill_front_kernel    the above; MODE 0: the merge weights are given and nothing is appended (part of
 //                           mtla_prefill_attn and mtla_prefill_chunk_attn), 1: with the append, 2: with the append,
 //                           from unrounded latents that are layer-normalised first (whole-layer prefill)
@@ -25,8 +25,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));  // (plain vector types stay in registers)
 
-constexpr int kSlots = 16;  // slots per workgroup and pass
-
 __device__ __forceinline__ uint16_t bf16_bits_to_f16_bits(uint16_t v) {
   return __builtin_bit_cast(uint16_t, static_cast<_Float16>(__uint_as_float(uint32_t(v) << 16)));
 }
@@ -40,7 +38,9 @@ __device__ __forceinline__ u32x4_t bf16x8_to_f16x8(u32x4_t v) {
   return o;
 }
 
+constexpr int kMaxHyper = 64;  // rows of the hyper-network
 constexpr int kChunk = 32;  // tokens whose latents are in LDS at a time
+constexpr int kChunkSlots = 16, kTurns = 2;  // threads side by side merge 16 slots at a time; a chunk touches at most 32 (17 from a stride of 2)
 
 // One row of latents in LDS: bf16 as they come, or fp32 after their normalisation (LN).  The pitch is an odd multiple of
 // 16 bytes, so that 16-byte reads of 16 rows spread over all banks.
@@ -48,7 +48,11 @@ template <int R, bool LN>
 struct AppendShared {
   static constexpr int kPitch = R * (LN ? 4 : 2) + 16;
   unsigned char row[kChunk][kPitch];
-  float z[4][kChunk];  // hyper-network logits of the chunk's tokens, one share per 16 rows of the hyper-network
+  float z[kChunk][4];  // hyper-network logits of the chunk's tokens, a share per wavefront
+  float w[4][kChunk];  // merge weights, a copy per wavefront
+  float bias[2][kMaxHyper];               // of the hyper-network; zeros, for all wavefronts but one
+  uint16_t g[kChunk][kMaxHyper + 8];      // the tokens' rows of hyp_G
+  u32x4_t kr[kTurns][kChunkSlots][16];    // the slots' new RoPE keys, 16 bytes a thread
   __device__ __forceinline__ void values(int u, int e, float (&o)[8]) const {
     if constexpr (LN) {
       const float4_t lo = *reinterpret_cast<const float4_t*>(row[u] + 4 * e), hi = *reinterpret_cast<const float4_t*>(row[u] + 4 * e + 16);
@@ -69,70 +73,107 @@ struct AppendShared {
   }
 };
 
-// Positions [pos_lo, pos_hi) of sequence b, all inside slots slot_base .. slot_base + 15; called by every thread of the
+// A wavefront's part of hyp_A: k = 32 (KW wv + i) .. + 31 of rows 16 t .. 16 t + 15, as matrix operands; zeros where there are none.
+template <int R>
+struct HyperRows {
+  static constexpr int KK = R / 32, KW = KK < 4 ? 1 : KK / 4, YT = kMaxHyper / 16;
+  u32x4_t f[YT][KW];
+  uint32_t bias = 0;  // bf16, element threadIdx.x
+  __device__ __forceinline__ void load(const AppendArgs& a) {
+    if (a.w_override) return;
+    const int tid = threadIdx.x, l16 = tid & 15, g = (tid & (kWave - 1)) >> 4, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (a.hyp_a && tid < a.d_hyper) bias = reinterpret_cast<const uint16_t*>(a.hyp_a)[tid];
+    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.hyp_A) + (size_t)l16 * R + 32 * KW * wv + 8 * g;
+#pragma unroll
+    for (int t = 0; t < YT; ++t)
+#pragma unroll
+      for (int i = 0; i < KW; ++i) {
+        f[t][i] = u32x4_t{0u, 0u, 0u, 0u};
+        if (16 * t < a.d_hyper && KW * wv < KK) f[t][i] = *reinterpret_cast<const u32x4_t*>(A + (size_t)16 * t * R + 32 * i);
+      }
+  }
+};
+
+// Positions [pos_lo, pos_hi) of sequence b, which begin with a slot or with the call; called by every thread of the
 // workgroup (barriers inside).  The latents go through LDS once, 32 tokens at a time, and serve two things:
 //   weights  Linear(c) of 16 tokens at a time is a small dense contraction D[y, token] = sum_n hyp_A[y, n] c[token, n];
-//            a wavefront owns 16 rows y (their 16 r weights stay in its registers for all tokens), dots its
+//            a wavefront takes a quarter of n for all rows y (their weights stay in its registers for all tokens), dots its
 //            share with the slot's row of hyp_G, and the four shares meet in LDS
 //   merge    16 threads per slot fold w_n c_n over the slot's tokens in order, in fp32, from the tail shadow when
 //            the slot already held tokens; every partial sum is a row of C_hat' (STAGE), the last one the cache row,
 //            rounded once
 // `tail_out` takes the last slot's fp32 value.
-// A workgroup is one round trip to memory and then works out of LDS; with the rows read straight into the operand layout
-// by each wavefront, and again for the merge, 8 x 4096 tokens at r = 512 took 42 us (50 MB), now 23 us.
+// A workgroup is one round trip to memory and then works out of LDS, while the next chunk's latents travel (LN: its registers are
+// full of the fp32 ones); with the rows read straight into the operand layout by each wavefront, and again for the merge,
+// 8 x 4096 tokens at r = 512 took 42 us (50 MB); with a workgroup per 16 slots and rows of hyp_A a wavefront, which has every wavefront
+// read (and, unrounded, split) all latents of the chunk, 25.5 us, now 21.6; five prompts of up to 1531 tokens, s = 3, one chunk a
+// workgroup, 12.9 and 8.9; the whole layer's front launch over 8 x 4096 tokens 51.5 and 44.  What is left is latency: the
+// lengths 2.4 us, the weights and latents 2 to 5, then logits, weights and merge 1.3 + 0.5 + 1.3 a chunk.
 template <int R, bool LN, bool STAGE>
-__device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillFrontArgs* fa, int b, int p0, int n, int slot_base,
-                                             long long pos_lo, long long pos_hi, float* tail_out, AppendShared<R, LN>& sh) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+__device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillFrontArgs* fa, int b, int p0, int n, long long pos_lo,
+                                             long long pos_hi, float* tail_out, const HyperRows<R>& hr, AppendShared<R, LN>& sh) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4, q = tid & 15, j = tid >> 4;
   const int s = a.stride, dR = a.d_rope, dy = a.d_hyper;
   const int t0 = int(pos_lo - p0), cnt = int(pos_hi - pos_lo);  // tokens t0 .. t0 + cnt - 1 of the call
   const size_t tok0 = (size_t)b * a.n_new_max + t0;
-  constexpr int KK = R / 32, NP = R >= 128 ? R / 128 : 1;      // a thread merges pieces q, q + 16, .. of 8 elements
-  const bool hyper = !a.w_override && 16 * wv < dy;
+  constexpr int NP = R >= 128 ? R / 128 : 1;                   // a thread merges pieces q, q + 16, .. of 8 elements
+  constexpr int KW = HyperRows<R>::KW, YT = HyperRows<R>::YT;
+  const bool hyper = !a.w_override;
   int past = 0;  // rows of cprime in front of the new ones
   if constexpr (STAGE) past = slots_inside(p0, s, fa->cs.past_pitch);
 
-  // ---- requests that need nothing but the position: the wavefront's rows of hyp_A, the slot in progress
-  u32x4_t af[KK];
-  float bias[4] = {0.f, 0.f, 0.f, 0.f};
-  if (hyper) {
-    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.hyp_A) + (size_t)(16 * wv + l16) * R + 8 * g;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) af[kk] = *reinterpret_cast<const u32x4_t*>(A + 32 * kk);
-    const bf16* ha = reinterpret_cast<const bf16*>(a.hyp_a);
-    if (ha) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) bias[v] = to_f32(ha[16 * wv + 4 * g + v]);
-    }
-  }
-  const int slot = slot_base + j;
-  const long long sf = (long long)slot * s;
-  const long long lo = sf > pos_lo ? sf : pos_lo, hi = sf + s < pos_hi ? sf + s : pos_hi;
-  const bool mine = lo < hi && 8 * q < R;  // the slot is touched by this range
-  float acc[NP][8];
+  const int slot0 = int(pos_lo / s);
+  float acc[NP][8];  // of slots slot0 + j, + 16, ..
 #pragma unroll
   for (int i = 0; i < NP; ++i)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
-  if (mine && sf < p0) {  // the slot already holds earlier tokens
+  if (j == 0 && 8 * q < R && (long long)slot0 * s < p0) {  // the slot already holds earlier tokens
 #pragma unroll
     for (int i = 0; i < NP; ++i) load8(a.tail_c + (size_t)b * R + 8 * (q + 16 * i), acc[i]);
   }
 
+  // What a chunk takes from memory, on its way to LDS while the one before is folded: latents, 16 threads per token and two tokens per
+  // thread; rows of hyp_G, 8 threads per token; the thread's slots' new keys (a slot keeps the key of the newest token folded into it).
+  // Nothing else is loaded in the loop: waiting for it would be waiting for these.
+  u32x4_t cv[LN ? 1 : 2][LN ? 1 : NP], krv[kTurns];
+  uint2 gv[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
+  float given = 0.f;  // merge weight of token lane % 32
+  auto request = [&](int c0) {
+    const int nc = cnt - c0 < kChunk ? cnt - c0 : kChunk;
+    if constexpr (!LN) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int u = 16 * h + j < nc ? 16 * h + j : nc - 1;
+        const uint16_t* row = reinterpret_cast<const uint16_t*>(a.c_new) + (tok0 + c0 + u) * R;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) cv[h][i] = *reinterpret_cast<const u32x4_t*>(row + (8 * q < R ? 8 * (q + 16 * i) : 0));
+      }
+    }
+    const int u_w = lane & (kChunk - 1);
+    if (a.w_override) given = a.w_override[tok0 + c0 + (u_w < nc ? u_w : nc - 1)];
+    const long long first = pos_lo + c0, end = first + nc;
+    if (hyper && 8 * (tid & 7) < dy) {
+      const int u = tid >> 3 < nc ? tid >> 3 : nc - 1;
+      const uint16_t* G = reinterpret_cast<const uint16_t*>(a.hyp_G) + (size_t)((first + u) / s) * dy + 8 * (tid & 7);
+      gv[0] = *reinterpret_cast<const uint2*>(G);
+      gv[1] = *reinterpret_cast<const uint2*>(G + 4);
+    }
+    const int slot_c = int(first / s), slot_t = slot_c + ((j - (slot_c - slot0)) & (kChunkSlots - 1));
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+      const long long sf = (long long)(slot_t + kChunkSlots * t) * s, hi = sf + s < pos_hi ? sf + s : pos_hi;
+      if (q < dR / 8 && sf < end && hi <= end)
+        krv[t] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.kr_new) +
+                                                   ((size_t)b * a.n_new_max + (size_t)(hi - 1 - p0)) * dR + 8 * q);
+    }
+  };
+  request(0);
+  if (tid < 2 * kMaxHyper) sh.bias[tid / kMaxHyper][tid % kMaxHyper] = __uint_as_float(hr.bias << 16);  // (0 from 64 on: dy <= 64)
   for (int c0 = 0; c0 < cnt; c0 += kChunk) {
     const int nc = cnt - c0 < kChunk ? cnt - c0 : kChunk;
     if (c0) __syncthreads();
-    // ---- latents of the chunk: 16 threads per token, two tokens per thread, everything requested at once
-    uint2 gv[2];
-    if (hyper) {
-      const uint16_t* G = reinterpret_cast<const uint16_t*>(a.hyp_G) + 16 * wv + 4 * g;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int u = 16 * h + l16 < nc ? 16 * h + l16 : nc - 1;
-        gv[h] = *reinterpret_cast<const uint2*>(G + (size_t)((pos_lo + c0 + u) / s) * dy);
-      }
-    }
     if constexpr (LN) {
       constexpr int N4 = R / 64;
       float4_t v[2][N4];
@@ -173,74 +214,98 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
         }
       }
     } else {
-      u32x4_t v[2][NP];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int u = 16 * h + j < nc ? 16 * h + j : nc - 1;
-        const uint16_t* row = reinterpret_cast<const uint16_t*>(a.c_new) + (tok0 + c0 + u) * R;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) v[h][i] = *reinterpret_cast<const u32x4_t*>(row + (8 * q < R ? 8 * (q + 16 * i) : 0));
-      }
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int i = 0; i < NP; ++i)
-          if (8 * q < R) *reinterpret_cast<u32x4_t*>(sh.row[16 * h + j] + 16 * (q + 16 * i)) = v[h][i];
+          if (8 * q < R) *reinterpret_cast<u32x4_t*>(sh.row[16 * h + j] + 16 * (q + 16 * i)) = cv[h][i];
     }
+    *reinterpret_cast<uint2*>(&sh.g[tid >> 3][8 * (tid & 7)]) = gv[0];
+    *reinterpret_cast<uint2*>(&sh.g[tid >> 3][8 * (tid & 7) + 4]) = gv[1];
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) sh.kr[t][j][q] = krv[t];
+    float wt = given;
+    if (c0 + kChunk < cnt) request(c0 + kChunk);
     __syncthreads();
 
     // ---- logits of the merge weights
     if (hyper) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        if (16 * h >= nc) break;
-        float4_t d = {0.f, 0.f, 0.f, 0.f};
+        float4_t d[YT];
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          if constexpr (LN) {  // unrounded latents: hi + lo bf16 planes, two matrix instructions per step
-            float v[8];
-            sh.values(16 * h + l16, 32 * kk + 8 * g, v);
-            uint32_t h0, l0, h1, l1, h2, l2, h3, l3;
-            split_bf16x2(v[0], v[1], h0, l0);
-            split_bf16x2(v[2], v[3], h1, l1);
-            split_bf16x2(v[4], v[5], h2, l2);
-            split_bf16x2(v[6], v[7], h3, l3);
-            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]),
-                                                        __builtin_bit_cast(bf16x8_t, (u32x4_t{h0, h1, h2, h3})), d, 0, 0, 0);
-            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]),
-                                                        __builtin_bit_cast(bf16x8_t, (u32x4_t{l0, l1, l2, l3})), d, 0, 0, 0);
-          } else {
-            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(sh.row[16 * h + l16] + 2 * (32 * kk + 8 * g));
-            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kk]), __builtin_bit_cast(bf16x8_t, v), d, 0, 0, 0);
+        for (int t = 0; t < YT; ++t) d[t] = float4_t{0.f, 0.f, 0.f, 0.f};
+        if (KW * wv < R / 32) {
+#pragma unroll
+          for (int i = 0; i < KW; ++i) {
+            const int e = 32 * (KW * wv + i) + 8 * g;
+            u32x4_t hi, lo;
+            if constexpr (LN) {  // unrounded latents: hi + lo bf16 planes, two matrix instructions per step
+              float v[8];
+              sh.values(16 * h + l16, e, v);
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                uint32_t a0, a1;
+                split_bf16x2(v[2 * k], v[2 * k + 1], a0, a1);
+                hi[k] = a0;
+                lo[k] = a1;
+              }
+            } else {
+              hi = *reinterpret_cast<const u32x4_t*>(sh.row[16 * h + l16] + 2 * e);
+            }
+#pragma unroll
+            for (int t = 0; t < YT; ++t)
+              d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, hi), d[t], 0, 0, 0);
+            if constexpr (LN) {
+#pragma unroll
+              for (int t = 0; t < YT; ++t)
+                d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, lo), d[t], 0, 0, 0);
+            }
           }
         }
-        // the lane holds Linear(c)[16 wv + 4 g + v] of its token
-        const float gf[4] = {__uint_as_float(gv[h].x << 16), __uint_as_float(gv[h].x & 0xffff0000u),
-                             __uint_as_float(gv[h].y << 16), __uint_as_float(gv[h].y & 0xffff0000u)};
+        // the lane holds its share of Linear(c)[16 t + 4 g + v] of its token
         float z = 0.f;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) z += (d[v] + bias[v]) * gf[v];
+        for (int t = 0; t < YT; ++t) {
+          d[t] += *reinterpret_cast<const float4_t*>(sh.bias[wv == 0 ? 0 : 1] + 16 * t + 4 * g);
+          const uint2 w = *reinterpret_cast<const uint2*>(&sh.g[16 * h + l16][16 * t + 4 * g]);
+          z += d[t][0] * __uint_as_float(w.x << 16) + d[t][1] * __uint_as_float(w.x & 0xffff0000u);
+          z += d[t][2] * __uint_as_float(w.y << 16) + d[t][3] * __uint_as_float(w.y & 0xffff0000u);
+        }
         z = quarter_reduce(z, LaneSum());
-        if (g == 0) sh.z[wv][16 * h + l16] = z;
+        if (g == 0) sh.z[16 * h + l16][wv] = z;
       }
     }
     __syncthreads();
-    auto weight = [&](int u) {
-      if (a.w_override) return a.w_override[tok0 + c0 + u];
-      float z = 0.f;
-      for (int y = 0; 16 * y < dy; ++y) z += sh.z[y][u];
-      return 1.f / (1.f + expf(-z));
-    };
+    const int u_w = lane & (kChunk - 1);
+    if (hyper) {
+      const float4_t z = *reinterpret_cast<const float4_t*>(sh.z[u_w]);
+      wt = 1.f / (1.f + expf(-((z[0] + z[1]) + (z[2] + z[3]))));
+    }
+    sh.w[wv][u_w] = wt;
+    __builtin_amdgcn_wave_barrier();  // (the wavefront's own copy)
     if (tid < nc && (a.w_out || a.slot_out)) {
-      if (a.w_out) a.w_out[tok0 + c0 + tid] = weight(tid);
+      if (a.w_out) a.w_out[tok0 + c0 + tid] = wt;
       if (a.slot_out) a.slot_out[tok0 + c0 + tid] = int((pos_lo + c0 + tid) / s);
     }
 
-    // ---- temporal merge of the slot's tokens in this chunk
-    if (mine) {
-      const long long u_lo = lo - pos_lo - c0 > 0 ? lo - pos_lo - c0 : 0, u_hi = hi - pos_lo - c0 < nc ? hi - pos_lo - c0 : nc;
-      for (int u = (int)u_lo; u < (int)u_hi; ++u) {
-        const float w = weight(u);
+    // ---- temporal merge of the slots' tokens in this chunk
+    const long long first = pos_lo + c0, end = first + nc;
+    const int slot_c = int(first / s), slot_t = slot_c + ((j - (slot_c - slot0)) & (kChunkSlots - 1));
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+      const int slot = slot_t + kChunkSlots * t;
+      const long long sf = (long long)slot * s, hi = sf + s < pos_hi ? sf + s : pos_hi;
+      if (sf >= end) break;
+      if (sf >= first && (t || c0)) {  // begins here (the first chunk's: above)
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
+      }
+      const int u_lo = sf > first ? int(sf - first) : 0, u_hi = hi < end ? int(hi - first) : nc;
+      for (int u = u_lo; 8 * q < R && u < u_hi; ++u) {
+        const float w = sh.w[wv][u];
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
           float v[8];
@@ -259,44 +324,39 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
           }
         }
       }
-    }
-  }
-
-  if (lo < hi) {
-    const size_t crow = cache_row(a.pages, b, slot, a.max_slots);
-    if (8 * q < R) {
-      uint16_t* out = reinterpret_cast<uint16_t*>(a.cache_c) + crow * R;
+      if (hi > end) break;  // goes on in the next chunk
+      const size_t crow = cache_row(a.pages, b, slot, a.max_slots);
+      if (8 * q < R) {
+        uint16_t* out = reinterpret_cast<uint16_t*>(a.cache_c) + crow * R;
 #pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        const int e = 8 * (q + 16 * i);
-        *reinterpret_cast<u32x4_t*>(out + e) = u32x4_t{pack_bf16x2(acc[i][0], acc[i][1]), pack_bf16x2(acc[i][2], acc[i][3]),
-                                                       pack_bf16x2(acc[i][4], acc[i][5]), pack_bf16x2(acc[i][6], acc[i][7])};
-        if (hi == (long long)p0 + n) {  // last slot touched: remains the sequence's tail
-          float* t = tail_out + (size_t)b * R + e;
-          *reinterpret_cast<float4_t*>(t) = float4_t{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-          *reinterpret_cast<float4_t*>(t + 4) = float4_t{acc[i][4], acc[i][5], acc[i][6], acc[i][7]};
+        for (int i = 0; i < NP; ++i) {
+          const int e = 8 * (q + 16 * i);
+          *reinterpret_cast<u32x4_t*>(out + e) = u32x4_t{pack_bf16x2(acc[i][0], acc[i][1]), pack_bf16x2(acc[i][2], acc[i][3]),
+                                                         pack_bf16x2(acc[i][4], acc[i][5]), pack_bf16x2(acc[i][6], acc[i][7])};
+          if (hi == (long long)p0 + n) {  // last slot touched: remains the sequence's tail
+            float* to = tail_out + (size_t)b * R + e;
+            *reinterpret_cast<float4_t*>(to) = float4_t{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+            *reinterpret_cast<float4_t*>(to + 4) = float4_t{acc[i][4], acc[i][5], acc[i][6], acc[i][7]};
+          }
         }
       }
-    }
-    // RoPE key: the slot keeps the key of the newest token folded into it
-    if (q < dR / 8) {
-      const uint16_t* kr_src = reinterpret_cast<const uint16_t*>(a.kr_new) + ((size_t)b * a.n_new_max + (size_t)(hi - 1 - p0)) * dR;
-      uint16_t* kr_dst = reinterpret_cast<uint16_t*>(a.cache_kr) + crow * dR;
-      *reinterpret_cast<u32x4_t*>(kr_dst + 8 * q) = *reinterpret_cast<const u32x4_t*>(kr_src + 8 * q);
+      if (q < dR / 8) *reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(a.cache_kr) + crow * dR + 8 * q) = sh.kr[t][j][q];
     }
   }
 }
 
-// Which positions workgroup x of sequence b appends: those of slots SLOTS x .. of the ones the call touches, through
+// Which positions workgroup x of sequence b appends: those of slots `slots` x .. of the ones the call touches, through
 // range(p0, n, first slot, first position, behind the last one).  The tail shadow of a sequence is read by the first
 // slot (when that slot already held tokens) and written by the last one.  With a staging launch (pos0_out: takes the length
 // before the call) the new one goes to tail_next and is put in place by the attention launch.  An append alone has no later
 // launch: when the shadow is read, workgroup 0 takes the last slot as well, in a second pass behind a barrier, so the read
 // precedes the write.
-template <int SLOTS, class Range>
-__device__ __forceinline__ void append_share(const AppendArgs& a, int32_t* pos0_out, int x, int b, Range range) {
-  const int s = a.stride, p0 = a.seq_len[b];
-  int n = a.n_new ? a.n_new[b] : a.n_new_max;
+// `first` requests what does not depend on the lengths; it travels with them.
+template <class First, class Range>
+__device__ __forceinline__ void append_share(const AppendArgs& a, int slots, int32_t* pos0_out, int x, int b, First first, Range range) {
+  const int s = a.stride, p0 = load_uniform_i32(a.seq_len, b);
+  int n = a.n_new ? load_uniform_i32(a.n_new, b) : a.n_new_max;
+  first();
   n = n < 0 ? 0 : (n > a.n_new_max ? a.n_new_max : n);
   if (pos0_out && x == 0 && threadIdx.x == 0) pos0_out[b] = p0;  // for the launches behind this one
   if (n == 0) return;
@@ -306,30 +366,32 @@ __device__ __forceinline__ void append_share(const AppendArgs& a, int32_t* pos0_
   }
   const long long end = (long long)p0 + n;
   const int first_slot = p0 / s, last_slot = int((end - 1) / s);
-  const bool last_apart = !pos0_out && p0 % s != 0 && last_slot - first_slot >= SLOTS;  // last slot outside workgroup 0's group
-  const int slot0 = first_slot + SLOTS * x;
+  const bool last_apart = !pos0_out && p0 % s != 0 && last_slot - first_slot >= slots;  // last slot outside workgroup 0's group
+  const long long slot0 = first_slot + (long long)slots * x;
   const long long lim = last_apart ? (long long)last_slot * s : end;  // the group's share ends here
-  const long long pos_lo = (long long)slot0 * s > p0 ? (long long)slot0 * s : p0;
-  const long long pos_hi = (long long)(slot0 + SLOTS) * s < lim ? (long long)(slot0 + SLOTS) * s : lim;
-  if (pos_lo < pos_hi) range(p0, n, slot0, pos_lo, pos_hi);
+  const long long pos_lo = slot0 * s > p0 ? slot0 * s : p0;
+  const long long pos_hi = (slot0 + slots) * s < lim ? (slot0 + slots) * s : lim;
+  if (pos_lo < pos_hi) range(p0, n, pos_lo, pos_hi);
   if (x == 0 && last_apart) {
     __syncthreads();
-    range(p0, n, last_slot, (long long)last_slot * s, end);
+    range(p0, n, (long long)last_slot * s, end);
   }
 }
 
 template <int R, bool LN, bool STAGE>
-__device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int x, int b, AppendShared<R, LN>& sh) {
+__device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int slots, int x, int b,
+                                             AppendShared<R, LN>& sh) {
   float* tail_out = STAGE ? fa->tail_next : a.tail_c;
-  append_share<kSlots>(a, STAGE ? fa->pos0_out : nullptr, x, b, [&](int p0, int n, int slot0, long long pos_lo, long long pos_hi) {
-    append_range<R, LN, STAGE>(a, fa, b, p0, n, slot0, pos_lo, pos_hi, tail_out, sh);
+  HyperRows<R> hr;
+  append_share(a, slots, STAGE ? fa->pos0_out : nullptr, x, b, [&]() { hr.load(a); }, [&](int p0, int n, long long pos_lo, long long pos_hi) {
+    append_range<R, LN, STAGE>(a, fa, b, p0, n, pos_lo, pos_hi, tail_out, hr, sh);
   });
 }
 
 template <int R>
-__global__ __launch_bounds__(kBlock) void append_bulk_kernel(AppendArgs a) {
+__global__ __launch_bounds__(kBlock, 2) void append_bulk_kernel(AppendArgs a, int slots) {
   __shared__ __attribute__((aligned(16))) AppendShared<R, false> sh;
-  append_block<R, false, false>(a, nullptr, blockIdx.x, blockIdx.y, sh);
+  append_block<R, false, false>(a, nullptr, slots, blockIdx.y, blockIdx.x, sh);
 }
 
 // The same append in fp32 storage, on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: lane 16 k + i holds A[i, k] and
@@ -461,8 +523,8 @@ __device__ __forceinline__ void append_range_f32(const AppendArgs& a, int b, int
 template <int R>
 __global__ __launch_bounds__(kBlock) void append_bulk_f32_kernel(AppendArgs a) {
   __shared__ __attribute__((aligned(16))) AppendSharedF32<R> sh;
-  append_share<kSlotsF32>(a, nullptr, blockIdx.x, blockIdx.y, [&](int p0, int n, int slot0, long long pos_lo, long long pos_hi) {
-    append_range_f32<R>(a, blockIdx.y, p0, n, slot0, pos_lo, pos_hi, sh);
+  append_share(a, kSlotsF32, nullptr, blockIdx.x, blockIdx.y, []() {}, [&](int p0, int n, long long pos_lo, long long pos_hi) {
+    append_range_f32<R>(a, blockIdx.y, p0, n, int(pos_lo / a.stride), pos_lo, pos_hi, sh);
   });
 }
 
@@ -571,7 +633,7 @@ __device__ __forceinline__ void convert_block(const PrefillFrontArgs& a, unsigne
 }
 
 template <int R, int MODE>
-__global__ __launch_bounds__(kBlock) void prefill_front_kernel(PrefillFrontArgs a) {
+__global__ __launch_bounds__(kBlock, 2) void prefill_front_kernel(PrefillFrontArgs a) {
   struct None {};
   __shared__ __attribute__((aligned(16))) union {
     std::conditional_t<MODE == 0, None, AppendShared<R, MODE == 2>> append;
@@ -580,7 +642,7 @@ __global__ __launch_bounds__(kBlock) void prefill_front_kernel(PrefillFrontArgs 
   unsigned blk = blockIdx.x;
   if (blk < a.n_main) {  // the new rows
     if constexpr (MODE == 0) stage_run(a.cs, (size_t)blk * kBlock + threadIdx.x);
-    else append_block<R, MODE == 2, true>(a.ap, &a, blk % a.groups, blk / a.groups, sh.append);
+    else append_block<R, MODE == 2, true>(a.ap, &a, a.group_slots, blk / (unsigned)a.cs.batch, blk % (unsigned)a.cs.batch, sh.append);
     return;
   }
   blk -= a.n_main;
@@ -591,10 +653,18 @@ __global__ __launch_bounds__(kBlock) void prefill_front_kernel(PrefillFrontArgs 
   stage_piece(a.cs, (size_t)(blk - a.n_conv) * kBlock + threadIdx.x);
 }
 
-unsigned append_groups(const AppendArgs& a, int slots = kSlots) {
-  // slots a call can touch per sequence: a partly filled first slot plus the rest
-  const int n_slots = (a.n_new_max + a.stride - 2) / a.stride + 1;
-  return (unsigned)((n_slots + slots - 1) / slots);
+// slots a call can touch per sequence: a partly filled first slot plus the rest
+int touched_slots(const AppendArgs& a) { return (a.n_new_max + a.stride - 2) / a.stride + 1; }
+
+// Slots of a workgroup (bf16): a chunk of tokens, or as many chunks as leave the chip one round of two workgroups a unit, the next
+// chunk's latents on their way (each fetches the weights of the hyper-network, at r = 512 twice a chunk's latents, and waits
+// for the lengths).  r = 512, s = 2, 8 x 4096 tokens, 1024 chunks: one a workgroup 23.0, two 21.6, four 27 us; the layer's
+// front launch 48.4, 44.2, 57.
+int group_slots(const AppendArgs& a) {
+  constexpr size_t kRound = 512;
+  const int one = a.stride < kChunk ? kChunk / a.stride : 1;
+  const size_t groups = (size_t)(((a.n_new_max + a.stride - 1) / a.stride + one - 1) / one) * a.batch;
+  return one * (int)((groups + kRound - 1) / kRound);
 }
 
 template <int MODE>
@@ -621,11 +691,12 @@ bool append_bulk_supported(const AppendArgs& a, int dtype) {
 
 hipError_t launch_append_bulk(const AppendArgs& a, int dtype, hipStream_t st) {
   const bool f32 = dtype == 0;
-  const dim3 grid(append_groups(a, f32 ? kSlotsF32 : kSlots), a.batch);
+  const int slots = f32 ? kSlotsF32 : group_slots(a);
+  const unsigned groups = (unsigned)((touched_slots(a) + slots - 1) / slots);  // bf16: the sequences' last ones, which may be empty, start last
 #define MTLA_CASE(RR)                                                                             \
   if (a.r == RR) {                                                                                \
-    if (f32) hipLaunchKernelGGL(append_bulk_f32_kernel<RR>, grid, dim3(kBlock), 0, st, a);        \
-    else hipLaunchKernelGGL(append_bulk_kernel<RR>, grid, dim3(kBlock), 0, st, a);                \
+    if (f32) hipLaunchKernelGGL(append_bulk_f32_kernel<RR>, dim3(groups, a.batch), dim3(kBlock), 0, st, a);        \
+    else hipLaunchKernelGGL(append_bulk_kernel<RR>, dim3(a.batch, groups), dim3(kBlock), 0, st, a, slots);         \
     return hipGetLastError();                                                                     \
   }
   MTLA_CASE(64) MTLA_CASE(128) MTLA_CASE(256) MTLA_CASE(512)
@@ -637,7 +708,10 @@ hipError_t launch_prefill_front(const PrefillFrontArgs& args, int mode, hipStrea
   PrefillFrontArgs a = args;
   const ChunkStageArgs& cs = a.cs;
   const size_t r8 = cs.r / 8, d8 = cs.d_rope / 8;
-  a.groups = mode == 0 ? 1 : append_groups(a.ap);
+  if (mode != 0) {
+    a.group_slots = group_slots(a.ap);
+    a.groups = (unsigned)((touched_slots(a.ap) + a.group_slots - 1) / a.group_slots);
+  }
   const size_t n_runs = (cs.T + cs.stride - 1) / cs.stride + 1;
   const size_t main = mode == 0 ? ((size_t)cs.batch * n_runs * r8 + kBlock - 1) / kBlock : (size_t)a.groups * cs.batch;
   const size_t plain = ((size_t)a.n_heads * a.d_head * r8 + a.n_wo / 8 + kBlock * kConvPieces - 1) / (kBlock * kConvPieces);
