@@ -180,7 +180,7 @@ __device__ __forceinline__ void publish_share(const SliceRegs<C>& t, const QSlic
 // Second half, after the workgroup barrier: the four shares are summed (same order in every
 // wavefront, so all four hold identical logits), the softmax weights are formed and the PV
 // product adds this wavefront's output columns.  vmask[ht] bit v says whether slot 4g + v of the
-// tile is visible to query tile ht.
+// tile is visible to query tile ht; WHOLE: all are.
 template <class C>
 struct Shares {  // the four wavefronts' shares of a tile's logits, as this lane reads them
   float4_t s[C::NHT][kWaves];
@@ -194,7 +194,7 @@ __device__ __forceinline__ void read_shares(Shares<C>& sh, const float4_t* sSb, 
     for (int w = 0; w < kWaves; ++w) sh.s[ht][w] = sSr[(w * C::NHT + ht) * kWave];
 }
 
-template <class C>
+template <class C, bool WHOLE = false>
 __device__ __forceinline__ void finish_tile(const Shares<C>& sh, const uint16_t* sTw, const uint32_t (&vmask)[C::NHT],
                                             ColState<C>& ws, int lane, int l16, int g) {
   short4_t pb[C::NHT];
@@ -206,7 +206,7 @@ __device__ __forceinline__ void finish_tile(const Shares<C>& sh, const uint16_t*
     // ---- softmax weights; lane holds query column l16 of query tile ht and slots 4g .. 4g+3
     float sv[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sv[v] = (vmask[ht] >> v & 1u) ? s[v] : -INFINITY;
+    for (int v = 0; v < 4; ++v) sv[v] = WHOLE || (vmask[ht] >> v & 1u) ? s[v] : -INFINITY;
     // Weights are taken relative to a reference m_ref fixed at the first live tile, so the hot
     // path needs no cross-lane traffic at all: the four lanes that share a query column keep
     // their own partial normaliser (summed at the end), and the tile maximum is only formed on
@@ -324,7 +324,7 @@ __device__ __forceinline__ void stream_cols_ahead(SliceRegs<C> (&tl)[NS], const 
   // and the product with the slice.  Whether a step publishes is fixed where it is written, not
   // tested inside it: the compiler counts the loads in flight along every path, and a refill that
   // may or may not have been issued would make every wait in the loop one for "all of them".
-  auto step = [&](auto st_, auto publishes_, int j) __attribute__((always_inline)) {
+  auto step = [&](auto st_, auto publishes_, auto whole_, int j) __attribute__((always_inline)) {
     constexpr int st = decltype(st_)::value;
     const int par = (sb0 ^ j) & 1;
     __syncthreads();  // all four shares of tile j are in LDS
@@ -337,16 +337,17 @@ __device__ __forceinline__ void stream_cols_ahead(SliceRegs<C> (&tl)[NS], const 
     for (int v = 0; v < 4; ++v) vm |= (base0 + j * kTile + 4 * g + v < k1 ? 1u : 0u) << v;
 #pragma unroll
     for (int ht = 0; ht < C::NHT; ++ht) vmask[ht] = vm;
-    finish_tile<C>(sh, sTw + par * kPark, vmask, ws, lane, l16, g);
+    finish_tile<C, decltype(whole_)::value>(sh, sTw + par * kPark, vmask, ws, lane, l16, g);
   };
   static_assert(NS == 2, "two stages");
   publish(std::integral_constant<int, 0>{}, 0);
   for (int it = 0; it < n_iter - 1; ++it) {
-    step(std::integral_constant<int, 0>{}, std::true_type{}, NS * it);
-    step(std::integral_constant<int, 1>{}, std::true_type{}, NS * it + 1);
+    step(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, NS * it);
+    step(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, NS * it + 1);
   }
-  step(std::integral_constant<int, 0>{}, std::true_type{}, n_all - 2);
-  step(std::integral_constant<int, 1>{}, std::false_type{}, n_all - 1);
+  // The run's end lies in these two; a mask in the others was part of every tile's chain (8 x 8192 slots, 32 heads: 25.0, now 24.8 us).
+  step(std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{}, n_all - 2);
+  step(std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{}, n_all - 1);
   sbuf = (sb0 ^ n_all) & 1;
 }
 
