@@ -177,8 +177,13 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   const auto none = std::integral_constant<int, 0>{};
   const auto one_tile = std::integral_constant<int, KT>{};
   if (kNext && mine > 1) issue(1, live - 1, place1);
-  if (kNext && multiplies) load_w(0);
-  if (kNext && mine > 1) wait_but_w(one_tile);
+  // Loads come back in the order they were asked for, 64 bytes a clock and unit.  With eight wavefronts the first head's W_V^(h) goes
+  // out behind the third tile, if the wavefront has one (16 sequences of 8 heads x 64, r = 256, 512 slots 12.1, now 11.54 us a step;
+  // 128 sequences, r = 128, 512 slots 12.1 and 11.1).  With four, one on a SIMD, it is too late there (r = 256, 350 slots 10.7 and 11.0).
+  const bool late = kNext && NW == 8 && mine > 2;
+  if (kNext && multiplies && !late) load_w(0);
+  if (late) wait_loads_but<KT>();
+  else if (kNext && mine > 1) wait_but_w(one_tile);
   else wait_but_w(none);
   if constexpr (G::query_lds) {
     const unsigned char* qp = own_q + ((l16 & 1) * HPW + (l16 >> 1) % HPW) * (R + DR) * 2 + 16 * g;
@@ -199,7 +204,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   auto step = [&](int k, auto place) {
     unsigned char* rows = area + decltype(place)::value * G::tile;
     const int base = tile_base(k);
-    if (kNext && k == 1) {  // W_V^(h) and the tile behind it may travel on
+    if (kNext && (k == 1 || (k == 2 && late))) {  // W_V^(h) and the tile behind it may travel on
       if (k + 1 < mine) wait_but_w(one_tile);
       else wait_but_w(none);
     } else if (k > 0) {
@@ -261,6 +266,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
     if (k + 2 < mine) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile has been read: its place takes the one after the next
       issue(k + 2, live - 1, place);
+      if (late && k == 0 && multiplies) load_w(0);
     }
   };
   for (int k = 0; k < mine; k += 2) {
