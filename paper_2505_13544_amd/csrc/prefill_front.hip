@@ -267,6 +267,7 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
         float z = 0.f;
 #pragma unroll
         for (int t = 0; t < YT; ++t) {
+          if (16 * t >= dy) break;  // (rows that there are not: of an infinite latent their products are not numbers)
           d[t] += *reinterpret_cast<const float4_t*>(sh.bias[wv == 0 ? 0 : 1] + 16 * t + 4 * g);
           const uint2 w = *reinterpret_cast<const uint2*>(&sh.g[16 * h + l16][16 * t + 4 * g]);
           z += d[t][0] * __uint_as_float(w.x << 16) + d[t][1] * __uint_as_float(w.x & 0xffff0000u);

@@ -49,3 +49,26 @@ def test_one_call_of_many_tokens_equals_several(stride, r, d_rope, batch, given)
     for a, b in ((one.cache_c, some.cache_c), (one.cache_kr, some.cache_kr)):
         assert torch.equal(a[:batch][live], b[:batch][live])
     assert torch.equal(one.tail_c[:batch], some.tail_c[:batch])
+
+
+@pytest.mark.parametrize("r", [64, 128, 256, 512])
+@pytest.mark.parametrize("d_hyper", [16, 32, 48, 64])
+def test_infinite_latents_saturate_the_weight(r, d_hyper):
+    # An infinite element whose column of hyp_A is positive, under positive rows of hyp_G: the logit is that infinity, the weight 1
+    # or 0, also where the hyper-network has fewer rows than the matrix operands; the other tokens' weights are finite.
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="append_inf", batch=2, d_model=64, r=r, d_hyper=d_hyper, stride=2, prefix=40, steps=0)
+    sess = H.make_session(wl)
+    H.upload_weights(sess, W.make_weights(wl))
+    g = torch.Generator(device="cuda").manual_seed(r + d_hyper)
+    c = torch.randn(2, 40, r, generator=g, device="cuda").bfloat16()
+    kr = torch.randn(2, 40, wl.d_rope, generator=g, device="cuda").bfloat16()
+    col = r - 3
+    sess.hyp_A[:, col] = 0.5
+    sess.hyp_G.abs_().add_(0.01)
+    c[0, 3, col] = float("inf")
+    c[1, 33, col] = float("-inf")
+    w = torch.full((2, 40), -1.0, device="cuda")
+    sess.append(c, kr, w_out=w)
+    assert w[0, 3] == 1 and w[1, 33] == 0
+    w[0, 3], w[1, 33] = 0.5, 0.5
+    assert torch.all((w >= 0) & (w <= 1))
