@@ -73,23 +73,29 @@ struct AppendShared {
   }
 };
 
-// A wavefront's part of hyp_A: k = 32 (KW wv + i) .. + 31 of rows 16 t .. 16 t + 15, as matrix operands; zeros where there are none.
-template <int R>
+// A wavefront's part of hyp_A, as matrix operands: k = k0 + 32 i .. + 31 of rows y0 + 16 t .. + 15; zeros where there are none.
+template <int R, bool LN>
 struct HyperRows {
-  static constexpr int KK = R / 32, KW = KK < 4 ? 1 : KK / 4, YT = kMaxHyper / 16;
+  // A quarter of k for all rows saves the wavefronts three quarters of the reads (and, unrounded, of the splitting) of a chunk's
+  // latents and costs them four sums instead of one.  Narrow rounded latents are cheaper read by all, 16 rows a wavefront: append of 16
+  // x 2080 tokens, s = 2, by quarters / by rows: r = 64 8.7 / 7.9 us, 128 9.2 / 8.4, 256 11.4 / 11.0, 512 19.3 / 19.4; the layer over them, r = 256: 160.7 / 162.2.
+  static constexpr bool kByRow = R == 64 || (!LN && R <= 256);
+  static constexpr int KW = kByRow ? R / 32 : R / 128, YT = kByRow ? 1 : kMaxHyper / 16;
+  static __device__ __forceinline__ int y0(int wv) { return kByRow ? 16 * wv : 0; }
+  static __device__ __forceinline__ int k0(int wv) { return kByRow ? 0 : 32 * KW * wv; }
   u32x4_t f[YT][KW];
   uint32_t bias = 0;  // bf16, element threadIdx.x
   __device__ __forceinline__ void load(const AppendArgs& a) {
     if (a.w_override) return;
     const int tid = threadIdx.x, l16 = tid & 15, g = (tid & (kWave - 1)) >> 4, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (a.hyp_a && tid < a.d_hyper) bias = reinterpret_cast<const uint16_t*>(a.hyp_a)[tid];
-    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.hyp_A) + (size_t)l16 * R + 32 * KW * wv + 8 * g;
+    const uint16_t* A = reinterpret_cast<const uint16_t*>(a.hyp_A) + (size_t)(y0(wv) + l16) * R + k0(wv) + 8 * g;
 #pragma unroll
     for (int t = 0; t < YT; ++t)
 #pragma unroll
       for (int i = 0; i < KW; ++i) {
         f[t][i] = u32x4_t{0u, 0u, 0u, 0u};
-        if (16 * t < a.d_hyper && KW * wv < KK) f[t][i] = *reinterpret_cast<const u32x4_t*>(A + (size_t)16 * t * R + 32 * i);
+        if (y0(wv) + 16 * t < a.d_hyper) f[t][i] = *reinterpret_cast<const u32x4_t*>(A + (size_t)16 * t * R + 32 * i);
       }
   }
 };
@@ -97,8 +103,8 @@ struct HyperRows {
 // Positions [pos_lo, pos_hi) of sequence b, which begin with a slot or with the call; called by every thread of the
 // workgroup (barriers inside).  The latents go through LDS once, 32 tokens at a time, and serve two things:
 //   weights  Linear(c) of 16 tokens at a time is a small dense contraction D[y, token] = sum_n hyp_A[y, n] c[token, n];
-//            a wavefront takes a quarter of n for all rows y (their weights stay in its registers for all tokens), dots its
-//            share with the slot's row of hyp_G, and the four shares meet in LDS
+//            a wavefront takes a quarter of n for all rows y, or 16 rows and all n (their weights stay in its registers for all
+//            tokens), dots its share with the slot's row of hyp_G, and the four shares meet in LDS
 //   merge    16 threads per slot fold w_n c_n over the slot's tokens in order, in fp32, from the tail shadow when
 //            the slot already held tokens; every partial sum is a row of C_hat' (STAGE), the last one the cache row,
 //            rounded once
@@ -111,14 +117,16 @@ struct HyperRows {
 // lengths 2.4 us, the weights and latents 2 to 5, then logits, weights and merge 1.3 + 0.5 + 1.3 a chunk.
 template <int R, bool LN, bool STAGE>
 __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillFrontArgs* fa, int b, int p0, int n, long long pos_lo,
-                                             long long pos_hi, float* tail_out, const HyperRows<R>& hr, AppendShared<R, LN>& sh) {
+                                             long long pos_hi, float* tail_out, const HyperRows<R, LN>& hr, AppendShared<R, LN>& sh) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4, q = tid & 15, j = tid >> 4;
   const int s = a.stride, dR = a.d_rope, dy = a.d_hyper;
   const int t0 = int(pos_lo - p0), cnt = int(pos_hi - pos_lo);  // tokens t0 .. t0 + cnt - 1 of the call
   const size_t tok0 = (size_t)b * a.n_new_max + t0;
   constexpr int NP = R >= 128 ? R / 128 : 1;                   // a thread merges pieces q, q + 16, .. of 8 elements
-  constexpr int KW = HyperRows<R>::KW, YT = HyperRows<R>::YT;
+  using Hyper = HyperRows<R, LN>;
+  constexpr int KW = Hyper::KW, YT = Hyper::YT;
+  const int y0 = Hyper::y0(wv), k0 = Hyper::k0(wv);
   const bool hyper = !a.w_override;
   int past = 0;  // rows of cprime in front of the new ones
   if constexpr (STAGE) past = slots_inside(p0, s, fa->cs.past_pitch);
@@ -235,43 +243,41 @@ __device__ __forceinline__ void append_range(const AppendArgs& a, const PrefillF
         float4_t d[YT];
 #pragma unroll
         for (int t = 0; t < YT; ++t) d[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-        if (KW * wv < R / 32) {
 #pragma unroll
-          for (int i = 0; i < KW; ++i) {
-            const int e = 32 * (KW * wv + i) + 8 * g;
-            u32x4_t hi, lo;
-            if constexpr (LN) {  // unrounded latents: hi + lo bf16 planes, two matrix instructions per step
-              float v[8];
-              sh.values(16 * h + l16, e, v);
+        for (int i = 0; i < KW; ++i) {
+          const int e = k0 + 32 * i + 8 * g;
+          u32x4_t hi, lo;
+          if constexpr (LN) {  // unrounded latents: hi + lo bf16 planes, two matrix instructions per step
+            float v[8];
+            sh.values(16 * h + l16, e, v);
 #pragma unroll
-              for (int k = 0; k < 4; ++k) {
-                uint32_t a0, a1;
-                split_bf16x2(v[2 * k], v[2 * k + 1], a0, a1);
-                hi[k] = a0;
-                lo[k] = a1;
-              }
-            } else {
-              hi = *reinterpret_cast<const u32x4_t*>(sh.row[16 * h + l16] + 2 * e);
+            for (int k = 0; k < 4; ++k) {
+              uint32_t a0, a1;
+              split_bf16x2(v[2 * k], v[2 * k + 1], a0, a1);
+              hi[k] = a0;
+              lo[k] = a1;
             }
+          } else {
+            hi = *reinterpret_cast<const u32x4_t*>(sh.row[16 * h + l16] + 2 * e);
+          }
+#pragma unroll
+          for (int t = 0; t < YT; ++t)
+            d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, hi), d[t], 0, 0, 0);
+          if constexpr (LN) {
 #pragma unroll
             for (int t = 0; t < YT; ++t)
-              d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, hi), d[t], 0, 0, 0);
-            if constexpr (LN) {
-#pragma unroll
-              for (int t = 0; t < YT; ++t)
-                d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, lo), d[t], 0, 0, 0);
-            }
+              d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, hr.f[t][i]), __builtin_bit_cast(bf16x8_t, lo), d[t], 0, 0, 0);
           }
         }
-        // the lane holds its share of Linear(c)[16 t + 4 g + v] of its token
+        // the lane holds its share of Linear(c)[y0 + 16 t + 4 g + v] of its token
         float z = 0.f;
 #pragma unroll
         for (int t = 0; t < YT; ++t) {
-          if (16 * t >= dy) break;  // (rows that there are not: of an infinite latent their products are not numbers)
-          d[t] += *reinterpret_cast<const float4_t*>(sh.bias[wv == 0 ? 0 : 1] + 16 * t + 4 * g);
-          const uint2 w = *reinterpret_cast<const uint2*>(&sh.g[16 * h + l16][16 * t + 4 * g]);
-          z += d[t][0] * __uint_as_float(w.x << 16) + d[t][1] * __uint_as_float(w.x & 0xffff0000u);
-          z += d[t][2] * __uint_as_float(w.y << 16) + d[t][3] * __uint_as_float(w.y & 0xffff0000u);
+          d[t] += *reinterpret_cast<const float4_t*>(sh.bias[Hyper::kByRow || wv == 0 ? 0 : 1] + y0 + 16 * t + 4 * g);
+          const uint2 w = *reinterpret_cast<const uint2*>(&sh.g[16 * h + l16][y0 + 16 * t + 4 * g]);
+          const float part = (d[t][0] * __uint_as_float(w.x << 16) + d[t][1] * __uint_as_float(w.x & 0xffff0000u)) +
+                             (d[t][2] * __uint_as_float(w.y << 16) + d[t][3] * __uint_as_float(w.y & 0xffff0000u));
+          z += y0 + 16 * t < dy ? part : 0.f;  // (rows that there are not: of an infinite latent their products are not numbers)
         }
         z = quarter_reduce(z, LaneSum());
         if (g == 0) sh.z[16 * h + l16][wv] = z;
@@ -383,7 +389,7 @@ template <int R, bool LN, bool STAGE>
 __device__ __forceinline__ void append_block(const AppendArgs& a, const PrefillFrontArgs* fa, int slots, int x, int b,
                                              AppendShared<R, LN>& sh) {
   float* tail_out = STAGE ? fa->tail_next : a.tail_c;
-  HyperRows<R> hr;
+  HyperRows<R, LN> hr;
   append_share(a, slots, STAGE ? fa->pos0_out : nullptr, x, b, [&]() { hr.load(a); }, [&](int p0, int n, long long pos_lo, long long pos_hi) {
     append_range<R, LN, STAGE>(a, fa, b, p0, n, pos_lo, pos_hi, tail_out, hr, sh);
   });
@@ -657,15 +663,17 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_front_kernel(PrefillFrontAr
 // slots a call can touch per sequence: a partly filled first slot plus the rest
 int touched_slots(const AppendArgs& a) { return (a.n_new_max + a.stride - 2) / a.stride + 1; }
 
-// Slots of a workgroup (bf16): a chunk of tokens, or as many chunks as leave the chip one round of two workgroups a unit, the next
-// chunk's latents on their way (each fetches the weights of the hyper-network, at r = 512 twice a chunk's latents, and waits
-// for the lengths).  r = 512, s = 2, 8 x 4096 tokens, 1024 chunks: one a workgroup 23.0, two 21.6, four 27 us; the layer's
-// front launch 48.4, 44.2, 57.
+// Slots of a workgroup (bf16): a chunk of tokens, or as many chunks as leave the chip one round of the workgroups that fit on its
+// units (by their registers: four at r = 64 and 128, three at 256, two at 512), the next chunk's latents on their way: each
+// fetches the weights of the hyper-network, at r = 512 twice a chunk's latents, and waits for the lengths.  us with one / two / three
+// chunks a workgroup, s = 2, over 8 x 4096 tokens, 1024 chunks, and 16 x 2080, 1040: r = 64 7.3 / 7.9 / 10.7 and 7.9 / 8.0 / 10.8, 128 7.8 / 8.3
+// and 9.6 / 8.4, 256 11.3 / 10.5 / 12.5 and 12.7 / 11.0 / 12.7, 512 19.2 / 17.2 / 19.4 and 21.6 / 19.3 / 19.4; 12 x 2048, 768 chunks: 256 9.1 / 10.0, 512
+// 15.6 / 15.6; 32 x 2048, 2048 chunks: 64 10.8 / 10.4, 256 18.8 / 18.0 / 17.0, 512 31.8 / 28.6 / 29.2, four 25.7.
 int group_slots(const AppendArgs& a) {
-  constexpr size_t kRound = 512;
+  const size_t round = 256 * (a.r <= 128 ? 4 : (a.r == 256 ? 3 : 2));
   const int one = a.stride < kChunk ? kChunk / a.stride : 1;
   const size_t groups = (size_t)(((a.n_new_max + a.stride - 1) / a.stride + one - 1) / one) * a.batch;
-  return one * (int)((groups + kRound - 1) / kRound);
+  return one * (int)((groups + round - 1) / round);
 }
 
 template <int MODE>
