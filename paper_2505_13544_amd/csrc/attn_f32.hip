@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kBlock) void attn_decode_f32_kernel(AttnArgs a) {
 // Bound by the fp32 matrix rate (256 flop per clock and unit) behind the first stages' trip to memory (5 us of it, all
 // workgroups at once): 1920 rows x 512 x 256, both, 1 GFLOP, 23.2 us with 64 x 64 tiles over all rows; 15.7 us now.  What counts
 // is that all units do the same: the row blocks of all sequences come first, padding last, and kKvPad keeps a fifth workgroup
-// off a unit that another one lacks (18 us without it).
+// off a unit that another one lacks (18 us without it).  Sequences without padding, or short ones, are one sequence to it (launch_prefill_f32).
 // ---------------------------------------------------------------------------
 constexpr int kGT = 64, kGK = 32, kGP = kGK + 4, kGN = kGT + 4, kKvRows = 32;
 constexpr size_t kKvPad = 12 << 10;  // LDS that a workgroup of the keys and values takes beyond its 27 KB: four per unit
@@ -517,8 +517,21 @@ bool prefill_f32_supported(const ExplicitArgs& a) {
 hipError_t launch_prefill_f32(const ExplicitArgs& args, hipStream_t st, const EventPair& ev) {
   ExplicitArgs a = args;
   a.n_slices = 0;
-  const unsigned cols = (a.n_heads * a.d_head + kGT - 1) / kGT;
-  hipLaunchKernelGGL(kv_f32_kernel, dim3(2 * cols, a.batch, (a.T + kKvRows - 1) / kKvRows), dim3(kBlock), kKvPad, st, a);
+  // Rows of the product: blocks of their own for every sequence skip its padding and waste half a block at its end.  us of the call, 8
+  // heads x 64, r = 256, a block's own / all rows as one: 600 sequences of 5 tokens 130 / 59, 90 of 33 54 / 41, 90 of up to 33 40 / 38, 60 of
+  // up to 50 38.5 / 38.5, 46 of up to 64 33.8 / 36.4, 3 of 500 to 777 39.7 / 42.0.
+  ExplicitArgs kv = a;
+  if ((!a.seq_len || a.T <= 56) && (size_t)a.batch * a.T <= (size_t)65535 * kKvRows) {
+    kv.T = a.batch * a.T;
+    kv.batch = 1;
+    kv.seq_len = nullptr;
+  }
+  // Of a ragged launch about half of the blocks are padding: kKvPad where the others are a round of four a unit.  Without / with it: 3
+  // sequences of 500 to 777 tokens (1200 workgroups) 41.6 / 39.7, 15 of up to 200 (1680) 34.1 / 32.6, 30 of up to 100 (1920) 32.9 / 33.8, 4 of 100 to
+  // 1024 (2048) 66.5 / 68.5.
+  const dim3 kv_grid(2 * ((a.n_heads * a.d_head + kGT - 1) / kGT), kv.batch, (kv.T + kKvRows - 1) / kKvRows);
+  const size_t pad = kv.seq_len && (size_t)kv_grid.x * kv_grid.y * kv_grid.z <= 1792 ? kKvPad : 0;
+  hipLaunchKernelGGL(kv_f32_kernel, kv_grid, dim3(kBlock), pad, st, kv);
 #define MTLA_CASE(HH, DD, RT)                                                                        \
   if (a.d_head == HH && a.d_rope == DD) {                                                            \
     launch_prefill_rows<HH, DD, HH, RT>(a, 1, st, ev);                                               \

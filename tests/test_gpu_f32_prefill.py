@@ -65,3 +65,34 @@ def test_bulk_append_continues(stride, pieces):
             assert np.abs(w[b].cpu().numpy() - w_ref).max() <= H.TOL_W
         t += m
         H.check_cache(sess, ob, what=f"piece {k}")
+
+
+@pytest.mark.parametrize("batch,T,lens", [
+    (40, 5, None), (40, 5, "ragged"),    # blocks of the key / value product over several sequences
+    (7, 56, "ragged"), (7, 57, "ragged"),  # the longest that are one sequence to it; a sequence's own blocks
+    (5, 65, None), (33, 1, None),
+])
+def test_rows_of_several_sequences_in_a_block(batch, T, lens):
+    wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_short", batch=batch, d_model=64, n_heads=3, d_head=64, r=128, d_rope=32, stride=2,
+                                        prefix=T, steps=0, seed=60 + T)
+    wts = W.make_weights(wl)
+    g = np.random.default_rng(batch + T)
+    n = np.full(batch, T, np.int32) if lens is None else g.integers(0, T + 1, batch).astype(np.int32)
+    toks, d = _prefill_inputs(wl, wts, T)
+    w = torch.rand(batch, T, device="cuda", generator=torch.Generator(device="cuda").manual_seed(T))
+    sess = H.make_session(wl)
+    H.upload_weights(sess, wts)
+    out = torch.empty(batch, T, wl.n_heads, wl.d_head, device="cuda")
+    lat = torch.empty(batch, T, wl.n_heads, wl.r, device="cuda")
+    keep = sess.prefill(d["q"], d["q_rope"], d["c"], d["kr"], w, out=out, out_latent=lat,
+                        seq_lens=None if lens is None else torch.from_numpy(n).cuda())
+    torch.cuda.synchronize()
+    del keep
+    for b in range(batch):
+        m = int(n[b])
+        assert torch.all(out[b, m:] == 0) and torch.all(lat[b, m:] == 0)
+        if m:
+            o_ref, ol_ref, _, _ = O.prefill_attn(toks[b].q[:m], toks[b].q_rope[:m], toks[b].c[:m], toks[b].kr[:m], wts.w_uk, wts.w_uv,
+                                                 wl.stride, O.softmax_scale(wl.d_head), w=w[b, :m].cpu().numpy())
+            assert H.max_err(out[b, :m], o_ref) <= H.TOL["f32"] * max(1.0, np.abs(o_ref).max())
+            assert H.max_err(lat[b, :m], ol_ref) <= H.TOL["f32"] * max(1.0, np.abs(ol_ref).max())
