@@ -293,13 +293,17 @@ __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
 // latent-space output.  Bound by the fp32 matrix rate (256 flop per clock and unit) plus the latency of the first tile.
 // With RT = 2 the blocks are one from either end of the sequence: the columns of the light one are among those of the heavy
 // one, so they share the tiles, and all workgroups of a sequence do the same work.  (32 rows in one piece gave some units the two
-// heaviest workgroups of the launch, 1.8 times the mean.)  A wavefront's next tile is on its way
-// while one is multiplied.
+// heaviest workgroups of the launch, 1.8 times the mean.)  AHEAD: a wavefront's next tile is on its way while one is multiplied.  Heads of
+// 128, one block a workgroup, have no registers for that with two workgroups a unit: there the next tile's keys are asked for when this one's
+// have been multiplied, the values in front of the keys' product.  us of the call, 8 heads, r = 256, s = 2, ahead with one workgroup a unit / so: 8
+// prompts of 512 tokens 128 / 107, 12 of 777 333 / 272, 10 of 128 (640 workgroups) 42.1 / 39.6; 4 heads, 3 of 700 (528) 52.0 / 52.8, with s = 1
+// 60.9 / 69.8; 8 heads, one of 700 (352) 36.9 / 41.2: kAheadMost.  (Beyond it one prompt of 4096 alone is slower so, 343 / 355.)
 // Three sequences of up to 777 tokens, 8 heads x 64: 29.6 us, now 22.9; the vector-ALU kernel over absorbed queries took 353 us
 // (and 45 + 67 us for the absorption and the value projection, which this form does not have).
 // ---------------------------------------------------------------------------
-template <int DH, int DR, int DV, int RT>
-__global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(ExplicitArgs a) {
+constexpr size_t kAheadMost = 576;  // workgroups of a launch over heads of 128
+template <int DH, int DR, int DV, int RT, bool AHEAD>
+__global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_kernel(ExplicitArgs a) {
   constexpr int KE = (DH + DR) / 16, KC = DH / 16, NV = DV / 16;
   __shared__ float s_o[kWaves][16][DV + 4];
   __shared__ float s_m[kWaves][16 * RT], s_l[kWaves][16 * RT];
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(
     f32x4 k[KE];
     float v[NV][4];
   };
-  auto request = [&](Tile& t, int tile) {
+  auto request_k = [&](Tile& t, int tile) {
     const int krow = src(tile, l16);
     const float* kp = kx + (size_t)krow * kpitch + 4 * g;
     const float* krp = kr + (size_t)krow * DR + 4 * g;
@@ -374,6 +378,8 @@ __global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(
     for (int c = 0; c < KC; ++c) t.k[c] = ld4(kp + 16 * c);
 #pragma unroll
     for (int c = KC; c < KE; ++c) t.k[c] = ld4(krp + 16 * (c - KC));
+  };
+  auto request_v = [&](Tile& t, int tile) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float* vp = vx + (size_t)src(tile, 4 * g + v) * vpitch + l16;
@@ -381,7 +387,7 @@ __global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(
       for (int n = 0; n < NV; ++n) t.v[n][v] = vp[16 * n];
     }
   };
-  auto multiply = [&](const Tile& tl, int tile) {
+  auto multiply = [&](const Tile& tl, int tile, auto&& behind_keys) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int own = sh_tiles + t, open_sh = m0[t] < 0 ? 0 : m0[t] / s;  // the block's own tile; its open chunks
@@ -394,6 +400,7 @@ __global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(
         s_a = mfma4(tl.k[c][2], qf[t][c][2], s_a);
         s_b = mfma4(tl.k[c][3], qf[t][c][3], s_b);
       }
+      behind_keys();
       float p[4];
       if (tile != own) {
 #pragma unroll
@@ -426,22 +433,48 @@ __global__ __launch_bounds__(kBlock, DH == 128 ? 1 : 2) void prefill_f32_kernel(
     }
   };
   // (a request past the last tile repeats the last one)
-  if (wv < tiles) {
-    Tile ta, tb;
-    request(ta, wv);
+  auto to_log2 = [&]() {  // behind the first request
 #pragma unroll
-    for (int t = 0; t < RT; ++t)  // to the log2 domain, behind the first request
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int c = 0; c < KE; ++c) qf[t][c] *= a.scale_log2;
-    for (int tile = wv;;) {
-      const int second = tile + kWaves, third = tile + 2 * kWaves;
-      request(tb, second < tiles ? second : tiles - 1);
-      multiply(ta, tile);
-      if (second >= tiles) break;
-      request(ta, third < tiles ? third : tiles - 1);
-      multiply(tb, second);
-      if (third >= tiles) break;
-      tile = third;
+  };
+  if constexpr (AHEAD) {
+    auto request = [&](Tile& t, int tile) {
+      request_k(t, tile);
+      request_v(t, tile);
+    };
+    auto nothing = [&]() {};
+    if (wv < tiles) {
+      Tile ta, tb;
+      request(ta, wv);
+      to_log2();
+      for (int tile = wv;;) {
+        const int second = tile + kWaves, third = tile + 2 * kWaves;
+        request(tb, second < tiles ? second : tiles - 1);
+        multiply(ta, tile, nothing);
+        if (second >= tiles) break;
+        request(ta, third < tiles ? third : tiles - 1);
+        multiply(tb, second, nothing);
+        if (third >= tiles) break;
+        tile = third;
+      }
+    }
+  } else {
+    static_assert(RT == 1, "one block: its keys are multiplied once a tile");
+    if (wv < tiles) {
+      Tile tl;
+      request_k(tl, wv);
+      to_log2();
+      for (int tile = wv; tile < tiles; tile += kWaves) {
+        request_v(tl, tile);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(tl, tile, [&]() {
+          __builtin_amdgcn_sched_barrier(0);
+          request_k(tl, tile + kWaves < tiles ? tile + kWaves : tiles - 1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      }
     }
   }
   // ---- merge the wavefronts, 16 rows at a time
@@ -485,7 +518,8 @@ template <int DH, int DR, int DV, int RT>
 void launch_prefill_rows(const ExplicitArgs& a, int slices, hipStream_t st, const EventPair& ev) {
   const unsigned blocks = (a.T + 15) / 16;
   const dim3 grid(a.n_heads * slices, a.batch, (blocks + RT - 1) / RT);
-  launch_timed(prefill_f32_kernel<DH, DR, DV, RT>, grid, dim3(kBlock), 0, st, ev, a);
+  if (RT > 1 || (size_t)grid.x * grid.y * grid.z <= kAheadMost) launch_timed(prefill_f32_kernel<DH, DR, DV, RT, true>, grid, dim3(kBlock), 0, st, ev, a);
+  else launch_timed(prefill_f32_kernel<DH, DR, DV, RT, RT != 1>, grid, dim3(kBlock), 0, st, ev, a);
 }
 
 }  // namespace

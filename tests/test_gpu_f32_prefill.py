@@ -22,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (65, (65, 64, 48), 8, 64, 256, 32, 4),
     (130, (130, 97, 0), 4, 32, 512, 64, 16),      # an empty sequence, the widest latent, the longest stride of the matrix-core append
     (81, (81, 17, 80), 2, 128, 64, 64, 2),        # one block a workgroup
+    (500, (500, 479, 3), 8, 128, 128, 32, 2),     # heads of 128: more workgroups than have their next tile ahead (24 x 32)
+    (290, (290, 273, 16), 16, 128, 64, 64, 1),    # 48 x 19
     (40, (40, 39, 5), 4, 64, 64, 32, 17),         # stride beyond the matrix-core append
 ])
 def test_rows_at_the_edges(T, lens, heads, d_head, r, d_rope, stride):
