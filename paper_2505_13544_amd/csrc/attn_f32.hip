@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
       for (int n = 0; n < NV; ++n) t.v[n][v] = vp[16 * n];
     }
   };
-  auto multiply = [&](const Tile& tl, int tile, auto&& behind_keys) {
+  auto multiply = [&](Tile& tl, int tile, auto&& behind_keys) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int own = sh_tiles + t, open_sh = m0[t] < 0 ? 0 : m0[t] / s;  // the block's own tile; its open chunks
@@ -405,6 +405,12 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
       if (tile != own) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) p[v] = 16 * tile + 4 * g + v < open_sh ? s_a[v] + s_b[v] : -INFINITY;
+        if (t > 0 && 16 * tile + 16 > open_sh) {  // the heavy block's columns: of an infinite value a weight of zero makes no number
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int n = 0; n < NV; ++n) tl.v[n][v] = 16 * tile + 4 * g + v < open_sh ? tl.v[n][v] : 0.f;
+        }
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {

@@ -98,3 +98,29 @@ def test_rows_of_several_sequences_in_a_block(batch, T, lens):
                                                  wl.stride, O.softmax_scale(wl.d_head), w=w[b, :m].cpu().numpy())
             assert H.max_err(out[b, :m], o_ref) <= H.TOL["f32"] * max(1.0, np.abs(o_ref).max())
             assert H.max_err(lat[b, :m], ol_ref) <= H.TOL["f32"] * max(1.0, np.abs(ol_ref).max())
+
+
+@pytest.mark.parametrize("stride,at,d_head", [(2, 163, 64), (3, 141, 64), (5, 150, 32), (16, 163, 64)])
+def test_infinite_latents_leave_the_rows_far_before_them_alone(stride, at, d_head):
+    # An infinite element of a token's latent: rows of blocks of 16 that end before it are what they are without it, also where their
+    # tile of closed chunks is shared with a block behind it.
+    T = 300
+    wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_inf", batch=1, d_model=64, n_heads=2, d_head=d_head, r=128, d_rope=32, stride=stride,
+                                        prefix=T, steps=0, seed=90 + stride)
+    wts = W.make_weights(wl)
+    _, d = _prefill_inputs(wl, wts, T)
+    w = torch.rand(1, T, device="cuda", generator=torch.Generator(device="cuda").manual_seed(stride))
+    sess = H.make_session(wl)
+    H.upload_weights(sess, wts)
+
+    def attend():
+        out, lat = (torch.empty(1, T, wl.n_heads, n, device="cuda") for n in (wl.d_head, wl.r))
+        keep = sess.prefill(d["q"], d["q_rope"], d["c"], d["kr"], w, out=out, out_latent=lat)
+        torch.cuda.synchronize()
+        del keep
+        return out, lat
+
+    want = attend()
+    d["c"][0, at, 5] = float("inf")
+    for got, ref in zip(attend(), want):
+        assert torch.equal(got[:, :at // 16 * 16], ref[:, :at // 16 * 16])
