@@ -690,14 +690,22 @@ hipError_t launch_attn_whole(const WholeArgs& w, int dtype, hipStream_t st, cons
 }
 
 bool attn_step_supported(const WholeStepArgs& w, int dtype) {
-  // fp32 storage, one workgroup a unit.  us a step, two launches / one: 4 heads x 64, r = 64, one sequence of 128 slots 7.2 / 6.5 (as eager
-  // calls, where the host's part of two launches is what counts, 9.1 / 6.4); 8 heads x 64, 8 sequences, r = 256: 32 slots 9.3 / 9.4, 450 16.9 /
-  // 16.7.  In bf16, where every workgroup of a sequence would read 32 KB of the hyper-network and its head's 32 KB of W_K for itself, it was
-  // built and gains nothing: 16 sequences of 8 heads x 64, r = 256: 150 slots 9.2 / 10.0, 528 12.2 / 12.6; r = 128: 20 slots 7.0 / 6.7, 200 8.3 / 8.6.
+  // fp32 storage.  Every workgroup reads the hyper-network and its head's W_K for itself, and a sequence's meet at its counter: one
+  // launch loses where they are many, more so of many heads and wide weights.  us a replayed step of 24 / 200 slots, two launches -> one:
+  //   4 heads x 64, r = 64, 8 sequences 6.6 -> 5.7 / 7.8 -> 6.9, 48: 6.7 -> 6.2 / 8.1 -> 7.5, 64: 6.8 -> 7.1 / 8.2 -> 8.6
+  //   8 heads x 64, r = 256, 16: 9.3 -> 9.3 / 12.6 -> 12.2, 24: 9.3 -> 10.1 / 12.7 -> 13.2; r = 128, 24: 7.6 -> 7.8 / 9.5 -> 9.6
+  //   32 heads x 64, r = 64, 3: 6.7 -> 6.5 / 8.0 -> 7.7, 4: 6.6 -> 6.7 / 8.0 -> 8.0, 8: 6.8 -> 8.2 / 8.1 -> 9.5
+  //   32 heads x 128, r = 128, 2: 7.9 -> 7.9 / 9.5 -> 9.7, 3: 7.9 -> 8.3 / 9.5 -> 10.1
+  //   8 heads x 128, r = 256, 1: 9.7 -> 10.3 / 12.8 -> 13.6; 32 heads, 8: 13.4 -> 17.9 / 16.9 -> 21.1 (not taken, not built)
+  // As eager calls, where the host's part of two launches is what counts, one gains more (the first line 9.1 -> 6.4 / 9.0 -> 7.6).  In
+  // bf16, 32 KB of the hyper-network and of W_K a workgroup, it was built and gains nothing: 16 sequences of 8 heads x 64, r = 256:
+  // 150 slots 9.2 / 10.0, 528 12.2 / 12.6; r = 128: 20 slots 7.0 / 6.7, 200 8.3 / 8.6.
   const AttnArgs& a = w.at;
   const AppendArgs& ap = w.ap;
-  return dtype == 0 && attn_whole_supported(w, dtype) && (w.d_head == 64 || w.d_head == 128) && (size_t)a.n_heads * a.batch <= 256 &&
-         a.batch <= kStepArrivals && ap.tail_c && !ap.w_override && !ap.n_new && !ap.w_out && !ap.slot_out;
+  const int weight = a.r * w.d_head;  // elements of a head's W_K
+  const size_t most = a.n_heads <= 4 ? 192 : (a.n_heads <= 8 ? 128 : (weight <= 8192 ? 96 : 64));
+  return dtype == 0 && attn_whole_supported(w, dtype) && (w.d_head == 64 || w.d_head == 128) && weight <= 16384 &&
+         (size_t)a.n_heads * a.batch <= most && a.batch <= kStepArrivals && ap.tail_c && !ap.w_override && !ap.n_new && !ap.w_out && !ap.slot_out;
 }
 
 hipError_t launch_attn_step(const WholeStepArgs& w, hipStream_t st, const EventPair& ev) {
@@ -717,8 +725,6 @@ hipError_t launch_attn_step(const WholeStepArgs& w, hipStream_t st, const EventP
   MTLA_CASE(64, 64, 128)
   MTLA_CASE(128, 32, 128)
   MTLA_CASE(128, 64, 128)
-  MTLA_CASE(256, 32, 128)
-  MTLA_CASE(256, 64, 128)
 #undef MTLA_CASE
   return hipErrorInvalidValue;
 }

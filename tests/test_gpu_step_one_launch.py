@@ -32,6 +32,8 @@ def _pair(batch, heads, d_head, r, d_rope, stride, slots, lens, seed=3):
     (2, 8, 128, 256, 64, 3, 130, (191, 384)),                  # the second one fills up on the way
     (5, 3, 64, 128, 64, 4, 40, (1, 63, 64, 65, 160)),          # the last is full from the start
     (56, 4, 64, 64, 32, 2, 20, tuple(i % 39 for i in range(56))),
+    (2, 8, 128, 128, 64, 3, 130, (191, 384)),                  # heads of 128 (at r = 256: two launches)
+    (56, 3, 64, 64, 32, 2, 20, tuple(i % 39 for i in range(56))),  # as many sequences as there are counters
     (57, 4, 64, 64, 32, 2, 20, tuple(i % 39 for i in range(57))),  # one more than there are counters: two launches
 ])
 def test_equals_append_then_attend(batch, heads, d_head, r, d_rope, stride, slots, lens):
