@@ -231,13 +231,21 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
     float sv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float t = s0[v] + s1[v], both = t + row_permuted<0xb1>(t);  // the planes' columns are neighbours
-      sv[v] = 4 * g + v < live - base ? both : -INFINITY;
+      const float t = s0[v] + s1[v];
+      // The planes' columns are neighbours.  At r = 512, whose sums are in the accumulation registers, a branch: as selects the walk lost, us a
+      // step, select / branch: 12 heads x 128, 4 sequences of 345 slots 18.2 / 17.5, behind a shared prefix 20.8 / 18.8; 20 heads x 64, 4 of 336
+      // 17.2 / 16.4 and 19.8 / 18.1; 16 heads x 128, 16 of 384 22.6 / 22.6.
+      if constexpr (R == 512) {
+        sv[v] = base + 4 * g + v < live ? t + row_permuted<0xb1>(t) : -INFINITY;
+      } else {
+        const float both = t + row_permuted<0xb1>(t);
+        sv[v] = 4 * g + v < live - base ? both : -INFINITY;
+      }
     }
     const float top = quarter_reduce(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), LaneMax());
     constexpr float kRebase = 40.f;
     if (__any(top - m_ref > kRebase)) {  // true at the first tile (m_ref = -inf)
-      // Selects, and nothing to scale at the first tile: as branches of the lanes these and the mask above were part of every tile's
+      // Selects, and nothing to scale at the first tile: as branches of the lanes these (and, below r = 512, the mask above) were part of every tile's
       // chain (r = 256, 8 heads x 64, 350 slots 11.05, now 10.74 us a step; r = 128, 600 slots 9.99 and 9.62).
       const bool moves = top - m_ref > kRebase;
       if (k > 0) {
