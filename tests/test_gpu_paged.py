@@ -258,3 +258,30 @@ def test_page_bookkeeping_stays_out_of_a_capture():
         torch.cuda.synchronize()
         assert torch.equal(out, eager)
     assert sess.device_status() == 0
+
+
+@pytest.mark.parametrize("n_heads,r,batch,max_slots,page_slots", [(8, 128, 5, 640, 16), (11, 128, 64, 400, 64), (8, 256, 7, 500, 16)])
+def test_whole_sequence_walk_of_eight_wavefronts(n_heads, r, batch, max_slots, page_slots):
+    # the walk that asks for the value weight behind its third tile (sequences of more than 256 slots), over pages and over own
+    # rows, bit for bit (own rows: test_gpu_decode_whole.py)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="paged_late", batch=batch, d_model=64, n_heads=n_heads, d_head=64, r=r, d_rope=32,
+                                           stride=1, prefix=1, steps=0, seed=r + n_heads)
+    wts = W.make_weights(wl, max_slots=max_slots)
+    g = torch.Generator(device="cuda").manual_seed(r)
+    bf = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    lens = np.random.default_rng(n_heads).integers(max_slots // 3, max_slots - 2, batch).astype(np.int32)
+    lens[:3] = 255, 256, max_slots - 2
+    flat = H.make_session(wl, max_slots=max_slots)
+    paged = make_paged(wl, page_slots=page_slots, n_pages=batch * -(-max_slots // page_slots), max_slots=max_slots, seed=r)
+    c, kr = bf(batch, max_slots, r), bf(batch, max_slots, 32)
+    for s, n in ((flat, torch.from_numpy(lens).cuda()), (paged, lens)):
+        H.upload_weights(s, wts)
+        s.append(c, kr, n_new=n)
+    for _ in range(2):
+        token = bf(batch, 1, r), bf(batch, 1, 32), bf(batch, n_heads, 64), bf(batch, n_heads, 32)
+        out = [torch.empty(batch, n_heads, 64, device="cuda") for _ in range(2)]
+        flat.step(*token, out=out[0])
+        paged.step(*token, out=out[1])
+        assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
+    assert_same_state(paged, flat, lens + 2, "after two steps")
+    assert flat.device_status() == 0 and paged.device_status() == 0

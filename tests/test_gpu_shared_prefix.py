@@ -226,3 +226,37 @@ def test_chunked_prefill_reads_the_cached_prompt_from_its_owner(stride):
             worst = max(worst, H.max_err(outs[0][b, t], o_ref))
     print(f"chunked prefill over a shared prompt, stride {stride}: max abs err {worst:.2e}")
     assert worst <= H.TOL[dtype]
+
+
+@pytest.mark.parametrize("n_heads,r,batch,max_slots", [(8, 128, 5, 640), (11, 128, 64, 400), (8, 256, 7, 500)])
+def test_whole_sequence_walk_of_eight_wavefronts(n_heads, r, batch, max_slots):
+    # the walk that asks for the value weight behind its third tile (sequences of more than 256 slots): prompts that end before,
+    # in and behind that tile, from one stored copy and from own rows, bit for bit (own rows: test_gpu_decode_whole.py)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="shared_prefix_late", batch=batch, d_model=64, n_heads=n_heads, d_head=64, r=r, d_rope=32,
+                                           stride=1, prefix=1, steps=0, seed=r + n_heads)
+    wts = W.make_weights(wl, max_slots=max_slots)
+    g = torch.Generator(device="cuda").manual_seed(r)
+    bf = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    rng = np.random.default_rng(n_heads)
+    n_pre = [0] + [int(x) for x in rng.integers(200, max_slots - 40, batch - 1)]
+    lens = [max_slots - 3] + [min(p + int(x), max_slots - 2) for p, x in zip(n_pre[1:], rng.integers(0, 60, batch - 1))]
+    lens[1], lens[-1] = 255, 256   # one tile less than a third one for every wavefront, and the first token of it
+    n_pre[1], n_pre[-1] = 250, 256
+    own, shared = H.make_session(wl, max_slots=max_slots), H.make_session(wl, max_slots=max_slots)
+    c, kr = bf(batch, max_slots, r), bf(batch, max_slots, 32)
+    for s in (own, shared):
+        H.upload_weights(s, wts)
+        s.cache_c.copy_(c)
+        s.cache_kr.copy_(kr)
+        s.seq_len.copy_(torch.tensor(lens, dtype=torch.int32))
+    for b in range(1, batch):
+        own.cache_c[b, :n_pre[b]], own.cache_kr[b, :n_pre[b]] = c[0, :n_pre[b]], kr[0, :n_pre[b]]
+        shared.cache_c[b, :n_pre[b]], shared.cache_kr[b, :n_pre[b]] = float("nan"), float("nan")
+    shared.share_prefix(torch.zeros(batch, dtype=torch.int32, device="cuda"), torch.tensor(n_pre, dtype=torch.int32, device="cuda"))
+    for _ in range(2):
+        token = bf(batch, 1, r), bf(batch, 1, 32), bf(batch, n_heads, 64), bf(batch, n_heads, 32)
+        out = [torch.empty(batch, n_heads, 64, device="cuda") for _ in range(2)]
+        own.step(*token, out=out[0])
+        shared.step(*token, out=out[1])
+        assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
+    assert own.device_status() == 0 and shared.device_status() == 0
