@@ -402,11 +402,11 @@ __global__ __launch_bounds__(kBlock, 2) void append_bulk_kernel(AppendArgs a, in
 }
 
 // The same append in fp32 storage, on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: lane 16 k + i holds A[i, k] and
-// B[k, i]; a lane's 16 bytes are its elements for four instructions).  Eight slots per workgroup, 32 threads merge a slot;
+// B[k, i]; a lane's 16 bytes are its elements for four instructions).  32 threads merge a slot, eight at most per workgroup;
 // 16 tokens at a time through LDS.  Bound by latency: the hyper-network's rows and the first tokens are one trip to memory,
 // then 16 tokens are r / 4 dependent matrix instructions a wavefront (2048 cycles at r = 256).  With a workgroup per slot that
 // read the hyper-network (64 KB) again for every token, three sequences of up to 777 tokens took 14.8 us, r = 256, s = 2.
-constexpr int kSlotsF32 = 8, kChunkF32 = 16;
+constexpr int kSlotsF32 = 8, kChunkF32 = 16;  // the most slots of a workgroup, tokens at a time
 template <int R>
 struct AppendSharedF32 {
   float row[kChunkF32][R + 4];
@@ -528,9 +528,9 @@ __device__ __forceinline__ void append_range_f32(const AppendArgs& a, int b, int
 }
 
 template <int R>
-__global__ __launch_bounds__(kBlock) void append_bulk_f32_kernel(AppendArgs a) {
+__global__ __launch_bounds__(kBlock) void append_bulk_f32_kernel(AppendArgs a, int slots) {
   __shared__ __attribute__((aligned(16))) AppendSharedF32<R> sh;
-  append_share(a, kSlotsF32, nullptr, blockIdx.x, blockIdx.y, []() {}, [&](int p0, int n, long long pos_lo, long long pos_hi) {
+  append_share(a, slots, nullptr, blockIdx.x, blockIdx.y, []() {}, [&](int p0, int n, long long pos_lo, long long pos_hi) {
     append_range_f32<R>(a, blockIdx.y, p0, n, int(pos_lo / a.stride), pos_lo, pos_hi, sh);
   });
 }
@@ -676,6 +676,17 @@ int group_slots(const AppendArgs& a) {
   return one * (int)((groups + round - 1) / round);
 }
 
+// fp32: 16 tokens' slots, twice that of launches with more than two such workgroups a unit.  A workgroup's chunks follow one another, and
+// with eight slots whatever the stride a long one's are many.  us of 1 / 2 / 4 / 8 slots: r = 256, 3 sequences of 700 to 777 tokens, s = 2
+// 21.2 / 14.9 / 12.3 / 10.1, s = 4 15.5 / 12.5 / 10.4 / 13.3; 16 of 1000, s = 4 53.7 / 31.9 / 20.5 / 18.5, s = 8 32.5 / 20.9 / 19.8 / 24.6, s = 16 23.4 / 24.4 /
+// 34.3 / 60.3; weights given, 8 of 259, s = 16 8.9 / 10.6 / 14.8 / 23.1.
+int group_slots_f32(const AppendArgs& a) {
+  const int one = a.stride < kChunkF32 ? kChunkF32 / a.stride : 1;
+  const size_t groups = (size_t)((touched_slots(a) + one - 1) / one) * a.batch;
+  const int n = one > 1 && groups > 512 ? 2 * one : one;
+  return n < kSlotsF32 ? n : kSlotsF32;
+}
+
 template <int MODE>
 hipError_t launch_front_mode(const PrefillFrontArgs& a, const dim3& grid, hipStream_t st) {
   switch (a.cs.r) {
@@ -700,11 +711,11 @@ bool append_bulk_supported(const AppendArgs& a, int dtype) {
 
 hipError_t launch_append_bulk(const AppendArgs& a, int dtype, hipStream_t st) {
   const bool f32 = dtype == 0;
-  const int slots = f32 ? kSlotsF32 : group_slots(a);
+  const int slots = f32 ? group_slots_f32(a) : group_slots(a);
   const unsigned groups = (unsigned)((touched_slots(a) + slots - 1) / slots);  // bf16: the sequences' last ones, which may be empty, start last
 #define MTLA_CASE(RR)                                                                             \
   if (a.r == RR) {                                                                                \
-    if (f32) hipLaunchKernelGGL(append_bulk_f32_kernel<RR>, dim3(groups, a.batch), dim3(kBlock), 0, st, a);        \
+    if (f32) hipLaunchKernelGGL(append_bulk_f32_kernel<RR>, dim3(groups, a.batch), dim3(kBlock), 0, st, a, slots); \
     else hipLaunchKernelGGL(append_bulk_kernel<RR>, dim3(a.batch, groups), dim3(kBlock), 0, st, a, slots);         \
     return hipGetLastError();                                                                     \
   }

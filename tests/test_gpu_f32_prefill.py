@@ -69,6 +69,31 @@ def test_bulk_append_continues(stride, pieces):
         H.check_cache(sess, ob, what=f"piece {k}")
 
 
+@pytest.mark.parametrize("stride,batch", [(1, 40), (3, 40), (4, 3), (4, 40), (8, 40), (16, 40)])
+def test_bulk_append_groups_of_slots(stride, batch):
+    # one call, whose workgroups take one to eight slots by the stride and the number of them, and pieces of 15 tokens: the same bits
+    wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_groups", batch=batch, d_model=64, n_heads=1, d_head=64, r=64, d_rope=32, stride=stride,
+                                        prefix=230, steps=0, seed=stride)
+    wts = W.make_weights(wl)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    c, kr = (torch.randn(batch, 230, n, generator=g, device="cuda") for n in (wl.r, wl.d_rope))
+    sess, w = [H.make_session(wl) for _ in range(2)], [torch.zeros(batch, 230, device="cuda") for _ in range(2)]
+    for s, x, step in zip(sess, w, (225, 15)):
+        H.upload_weights(s, wts)
+        for a, e in [(0, 5)] + [(t, min(t + step, 230)) for t in range(5, 230, step)]:
+            piece = torch.zeros(batch, e - a, device="cuda")
+            s.append(c[:, a:e].contiguous(), kr[:, a:e].contiguous(), w_out=piece)
+            x[:, a:e] = piece
+        assert s.device_status() == 0
+    n = -(-230 // stride)
+    assert torch.equal(w[0], w[1]) and torch.equal(sess[0].tail_c, sess[1].tail_c)
+    assert torch.equal(sess[0].cache_c[:, :n], sess[1].cache_c[:, :n]) and torch.equal(sess[0].cache_kr[:, :n], sess[1].cache_kr[:, :n])
+    ob = H.OracleBatch.new(wl, wts)
+    for b in range(0, batch, 13):
+        w_ref, _ = ob.append(b, c[b].cpu().numpy(), kr[b].cpu().numpy())
+        assert np.abs(w[0][b].cpu().numpy() - w_ref).max() <= H.TOL_W
+
+
 @pytest.mark.parametrize("batch,T,lens", [
     (40, 5, None), (40, 5, "ragged"),    # blocks of the key / value product over several sequences
     (7, 56, "ragged"), (7, 57, "ragged"),  # the longest that are one sequence to it; a sequence's own blocks
