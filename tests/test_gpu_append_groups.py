@@ -29,9 +29,10 @@ def _append(wl, wts, start, pieces, c, kr, lens, given):
 
 
 @pytest.mark.parametrize("stride,r,d_rope,batch,given", [(1, 64, 32, 17, False), (2, 512, 64, 16, False), (3, 128, 32, 16, False),
-                                                         (5, 256, 64, 16, True), (16, 64, 32, 18, False), (2, 64, 32, 3, False)])
+                                                         (5, 256, 64, 16, True), (16, 64, 32, 18, False), (2, 64, 32, 3, False),
+                                                         (1, 512, 64, 3, False), (1, 128, 32, 3, True)])
 def test_one_call_of_many_tokens_equals_several(stride, r, d_rope, batch, given):
-    start, T = 37, 2080  # from inside a slot (stride 1: none); more than one chunk a workgroup from 8 sequences on
+    start, T = 37, 2080  # from inside a slot (stride 1: none, and of 3 sequences 16 slots a workgroup); more than one chunk a workgroup from 8 sequences on
     wl = W.WORKLOADS["speech_bf16"].scaled(name="append_groups", batch=batch, d_model=64, r=r, d_rope=d_rope, stride=stride,
                                            prefix=start + T, steps=0, seed=40 + stride)
     wts = W.make_weights(wl)
