@@ -687,8 +687,10 @@ int group_slots(const AppendArgs& a) {
 // fp32: 16 tokens' slots, twice that of launches with more than two such workgroups a unit.  A workgroup's chunks follow one another, and
 // with eight slots whatever the stride a long one's are many.  us of 1 / 2 / 4 / 8 slots: r = 256, 3 sequences of 700 to 777 tokens, s = 2
 // 21.2 / 14.9 / 12.3 / 10.1, s = 4 15.5 / 12.5 / 10.4 / 13.3; 16 of 1000, s = 4 53.7 / 31.9 / 20.5 / 18.5, s = 8 32.5 / 20.9 / 19.8 / 24.6, s = 16 23.4 / 24.4 /
-// 34.3 / 60.3; weights given, 8 of 259, s = 16 8.9 / 10.6 / 14.8 / 23.1.
+// 34.3 / 60.3; weights given, 8 of 259, s = 16 8.9 / 10.6 / 14.8 / 23.1.  A sequence's last slot apart from workgroup 0's is a second pass of
+// its own (append_share): two chunks that one workgroup can take stay together (7 sequences of 22 tokens, s = 4 12.9, apart 14.9).
 int group_slots_f32(const AppendArgs& a) {
+  if (touched_slots(a) <= kSlotsF32 && a.n_new_max <= 2 * kChunkF32) return kSlotsF32;
   const int one = a.stride < kChunkF32 ? kChunkF32 / a.stride : 1;
   const size_t groups = (size_t)((touched_slots(a) + one - 1) / one) * a.batch;
   const int n = one > 1 && groups > 512 ? 2 * one : one;

@@ -71,14 +71,15 @@ def test_bulk_append_continues(stride, pieces):
 
 @pytest.mark.parametrize("stride,batch", [(1, 40), (3, 40), (4, 3), (4, 40), (8, 40), (16, 40)])
 def test_bulk_append_groups_of_slots(stride, batch):
-    # one call, whose workgroups take one to eight slots by the stride and the number of them, and pieces of 15 tokens: the same bits
+    # one call, whose workgroups take one to eight slots by the stride and the number of them, and pieces of 25 tokens (up to two chunks of
+    # one workgroup): the same bits
     wl = W.WORKLOADS["tiny_f32"].scaled(name="f32_groups", batch=batch, d_model=64, n_heads=1, d_head=64, r=64, d_rope=32, stride=stride,
                                         prefix=230, steps=0, seed=stride)
     wts = W.make_weights(wl)
     g = torch.Generator(device="cuda").manual_seed(batch)
     c, kr = (torch.randn(batch, 230, n, generator=g, device="cuda") for n in (wl.r, wl.d_rope))
     sess, w = [H.make_session(wl) for _ in range(2)], [torch.zeros(batch, 230, device="cuda") for _ in range(2)]
-    for s, x, step in zip(sess, w, (225, 15)):
+    for s, x, step in zip(sess, w, (225, 25)):
         H.upload_weights(s, wts)
         for a, e in [(0, 5)] + [(t, min(t + step, 230)) for t in range(5, 230, step)]:
             piece = torch.zeros(batch, e - a, device="cuda")
