@@ -13,6 +13,22 @@ constexpr GemmTile kGemmTiles[] = {
     {256, 256, 5.f, 4.7f, 0.028f}, {256, 128, 5.f, 2.5f, 0.0152f}, {128, 128, 3.2f, 0.5f, 0.0112f}, {64, 64, 2.2f, 0.5f, 0.004f}};
 enum { kWide = 4 };
 
+// Tiles that form the angles of the rows they turn (why these: GemmGeom); the others read them from a table.
+constexpr bool gemm_own_angles(int bm, int bn) { return bm == 64 && bn == 64; }
+
+// Products with turned rows (ways out 1 and 2).  A row's position is its place in its sequence, found from where that begins: sequences
+// are their new rows alone, and with lengths a block of rows is one sequence's.
+template <class Args>
+bool gemm_turns(const Args& a) {
+  for (int i = 0; i < a.n_seg; ++i)
+    if (a.seg[i].epi == 1 || a.seg[i].epi == 2) return true;
+  return false;
+}
+template <class Args>
+bool gemm_turned_rows_supported(const Args& a) {
+  return !gemm_turns(a) || (!a.rows.pos0 && a.rows.past == 0 && !a.rows.zeros && a.rows.T >= 1);
+}
+
 // Column blocks of a launch with tiles of bn columns (a segment starts a block of its own).
 template <class Args>
 int gemm_col_blocks(const Args& a, int bn) {

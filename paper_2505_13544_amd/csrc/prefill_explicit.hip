@@ -73,7 +73,7 @@ struct GemmGeom {
   // launch that writes a table first is 3 us of a short prompt's; the layer over 129 tokens 35.5, now 34.5 us, 1000 tokens 46.0,
   // now 44.4.  (Where the larger tiles pay there are thousands of rows: each would be turned once per column block, and the table's
   // launch is 6 us of 1280.)
-  static constexpr bool OWN_ANGLES = BM == 64 && BN == 64;
+  static constexpr bool OWN_ANGLES = gemm_own_angles(BM, BN);
   static_assert(PF >= SPB && 2 * LOADS * SPB <= 63 && NLW >= 1 && NLA >= 1, "buffers, wait counts");
 };
 
@@ -767,6 +767,7 @@ bool gemm_nt_supported(const GemmArgs& a) {
     if ((g.epi == 1 || g.epi == 2) && (!a.in_bf16 || a.d_rope % 4 != 0 || a.d_rope < 4 || a.d_rope > 64 || !a.rope_cs || g.N % a.d_rope != 0)) return false;
     blocks += (size_t)(g.N + 63) / 64;
   }
+  if (!gemm_turned_rows_supported(a)) return false;
   if (a.rows.T < 1 || ((a.rows.n_new || a.rows.pos0) && a.M % (a.rows.past + a.rows.T) != 0)) return false;
   const size_t n_seq = a.rows.n_new || a.rows.pos0 ? (size_t)a.M / (a.rows.past + a.rows.T) : 1;
   return blocks * ((size_t)(a.M + 63) / 64 + n_seq + 8) < (size_t)1 << 31;
@@ -803,8 +804,7 @@ hipError_t launch_rope_table(const GemmArgs& g, hipStream_t st) {
 hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
   GemmArgs a = args;
-  bool turned = false;
-  for (int i = 0; i < a.n_seg; ++i) turned = turned || a.seg[i].epi == 1 || a.seg[i].epi == 2;
+  const bool turned = gemm_turns(a);
   auto table = [&]() {
     a.rope_ready = 1;
     return launch_rope_table(a, st);
@@ -830,7 +830,7 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
       return e != hipSuccess ? e : launch_gemm_nt(one, st);
     }
   }
-  if (turned && !a.rope_ready && (pick == kWide || kGemmTiles[pick].bm != 64)) {
+  if (turned && !a.rope_ready && (pick == kWide || !gemm_own_angles(kGemmTiles[pick].bm, kGemmTiles[pick].bn))) {
     const hipError_t e = table();
     if (e != hipSuccess) return e;
   }

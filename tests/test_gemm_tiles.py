@@ -15,11 +15,11 @@ PROGRAM = r"""
 using namespace mtla;
 struct Args {
   int M, K, n_seg;
-  struct { int N; } seg[4];
+  struct { int N, epi; } seg[4];
   struct { const int *pos0, *n_new; int past, T, zeros; } rows;
 };
 static int some;
-Args equal(int M, int N, int K) { return Args{M, K, 1, {{N}}, {nullptr, nullptr, 0, 1, 0}}; }
+Args equal(int M, int N, int K) { return Args{M, K, 1, {{N, 0}}, {nullptr, nullptr, 0, 1, 0}}; }
 Args ragged(int n_seq, int past, int T, std::vector<int> N, int K, int zeros = 0) {
   Args a{n_seq * (past + T), K, (int)N.size(), {}, {past ? &some : nullptr, &some, past, T, zeros}};
   for (size_t i = 0; i < N.size(); ++i) a.seg[i].N = N[i];
@@ -67,6 +67,19 @@ int main() {
           ++failed;
         }
       }
+  // rows that are turned: new rows of sequences alone, in blocks of one sequence each
+  auto turned = [&](const char* what, Args a, int epi, bool taken) {
+    a.seg[a.n_seg - 1].epi = epi;
+    if (gemm_turned_rows_supported(a) == taken) return;
+    std::printf("turned rows, %s\n", what);
+    ++failed;
+  };
+  turned("all rows", equal(100, 64, 64), 1, true);
+  turned("lengths", ragged(3, 0, 40, {512, 64}, 64), 2, true);
+  turned("rows behind a past", ragged(3, 5, 40, {512, 64}, 64), 2, false);
+  turned("blocks of several sequences", ragged(3, 0, 40, {512, 64}, 64, 1), 1, false);
+  turned("none turned", ragged(3, 5, 40, {512, 64}, 64, 1), 3, true);
+  for (int i = 0; i < kWide; ++i) failed += gemm_own_angles(kGemmTiles[i].bm, kGemmTiles[i].bn) != (i == 3);
   return failed ? 1 : 0;
 }
 """
