@@ -144,7 +144,9 @@ mtla_status mtla_set_decode_schedule(mtla_ctx* ctx, int32_t schedule);
  * kernel (the attention pass over the cache slots, or over the unmasked columns
  * of the parallel form) on the call's stream, up to `capacity` calls.  Where a
  * decode call takes whole sequences without chunks (mtla_set_decode_schedule)
- * that kernel contains the normalisation and the product with W_V as well.
+ * that kernel contains the normalisation and the product with W_V as well, and
+ * in a decode step of fp32 storage that is one launch (few heads and short
+ * sequences) the append and the absorption of the query too.
  * mtla_profile_read synchronises on the recorded events, writes the elapsed
  * milliseconds of each bracketed launch to ms_out (host, room for `capacity`
  * floats), the number of launches to *n_out, and ends profiling.

@@ -551,7 +551,7 @@ hipError_t launch_attn_decode_f32(const AttnArgs& a, hipStream_t st, const Event
 
 bool prefill_f32_supported(const ExplicitArgs& a) {
   return (a.d_head == 32 || a.d_head == 64 || a.d_head == 128) && (a.d_rope == 32 || a.d_rope == 64) && a.r % 64 == 0 &&
-         a.batch <= 65535 && (size_t)a.batch * a.T <= 65535u;  // the rows of the key / value product are a grid dimension
+         a.batch <= 65535 && (size_t)a.batch * a.T <= 65535u;  // (the call refuses more rows of fp32 storage, as the interface states)
 }
 
 hipError_t launch_prefill_f32(const ExplicitArgs& args, hipStream_t st, const EventPair& ev) {

@@ -500,6 +500,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     at.part_f16 = combine_mfma_supported(probe) ? 1 : 0;
     at.run_cost = kRunCost;
   }
+  const bool front = ap && decode_front_supported(*ap, ab);
+  if (ap && ap->c_new_f32 && !front && g.dtype != MTLA_F32) return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
   const bool timed = c->prof_n < (int)c->ev_start.size();
   EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
   if (timed) {
@@ -524,12 +526,10 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     wh.arrived = reinterpret_cast<int32_t*>(ws) + kArrivalWord;
     if (attn_step_supported(wh, g.dtype)) return hip_ok(launch_attn_step(wh, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
   }
-  if (ap && decode_front_supported(*ap, ab)) {  // append and absorb do not depend on each other: one launch
+  if (front) {  // append and absorb do not depend on each other: one launch
     if (!hip_ok(launch_decode_front(*ap, ab, st))) return MTLA_ERR_HIP;
   } else if (ap && g.dtype == MTLA_F32) {
     if (!hip_ok(launch_decode_front_f32(*ap, ab, st))) return MTLA_ERR_HIP;
-  } else if (ap && ap->c_new_f32) {
-    return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
   } else {
     if (ap && !hip_ok(launch_append(*ap, g.dtype, st))) return MTLA_ERR_HIP;
     if (!hip_ok(launch_absorb(ab, g.dtype, st))) return MTLA_ERR_HIP;

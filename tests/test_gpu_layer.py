@@ -9,6 +9,7 @@ import torch
 
 import workloads as W
 from oracle import mtla_oracle as O
+from paper_2505_13544_amd.binding import MtlaError
 from tests import harness as H
 
 pytestmark = pytest.mark.gpu
@@ -105,3 +106,18 @@ def test_layer_rope_positions_far_out():
         for b in range(2):
             kr_ref = O.rope(lw.w_kr.astype(np.float64) @ xs[b, t].astype(np.float64), p0 + t)
             assert np.abs(kr_gpu[b] - kr_ref).max() <= 2.0 ** -8 * np.abs(kr_ref).max() + 1e-6
+
+
+def test_a_refused_step_uses_up_no_timing():
+    # more heads than the matrix-core decode takes: the layer's step is refused, and the events of a profile stay for the calls behind it
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="layer_refused", batch=2, d_model=64, n_heads=33, d_head=32, r=64, d_rope=32, stride=2,
+                                           prefix=1, steps=0)
+    wts = W.make_weights(wl, max_slots=4)
+    lw = W.make_layer_weights(wl, wts)
+    sess = H.make_session(wl, max_slots=4)
+    H.upload_weights(sess, wts)
+    sess.set_layer_weights(w_q=lw.w_q, w_qr=lw.w_qr, w_r=lw.w_r, w_kr=lw.w_kr, w_o=lw.w_o)
+    sess.ctx.profile_start(4)
+    with pytest.raises(MtlaError):
+        sess.layer_step(torch.zeros(2, 64, dtype=torch.bfloat16, device="cuda"), y=torch.empty(2, 64, device="cuda"))
+    assert len(sess.ctx.profile_read()) == 0
