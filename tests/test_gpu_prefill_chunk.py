@@ -174,14 +174,24 @@ def test_chunk_start_outside_the_declared_past_leaves_the_other_sequences_alone(
                                     sess.w_uv, out, ws, sess.workspace, sess.stream)
         return out, sess.device_status()
 
+    def differences(x, y):  # where, for the message of a failure: the spans of every index, and spans of the scratch more than 1 MB apart
+        at = (x != y).nonzero().cpu()
+        if at.shape[1] > 1:
+            return f"{len(at)} values, (row, head, column) {at.min(0).values.tolist()} to {at.max(0).values.tolist()}, first {at[:4].tolist()}"
+        at, ends = at[:, 0], []
+        for i in (torch.diff(at) > 1 << 20).nonzero()[:, 0].tolist():
+            ends += [int(at[i]), int(at[i + 1])]
+        return f"scratch bytes {[int(at[0])] + ends + [int(at[-1])] if len(at) else []} of {len(x)}"
+
     for good in (0, 1):
         row = lambda start: [2003, start] if good == 0 else [start, 2003]
         want, status = attend(row(2 * past))
+        scratch = ws.clone()
         assert status == 0 and torch.isfinite(want).all()
         for start in (-4096, -1, 2 * past + 2, 2 ** 31 - 1):
             got, status = attend(row(start))
             assert status == 1, start
-            assert torch.equal(got[good], want[good]), start
+            assert torch.equal(got[good], want[good]), (start, differences(got[good], want[good]), differences(ws, scratch))
             assert torch.isfinite(got).all()
 
 
