@@ -439,7 +439,7 @@ __global__ __launch_bounds__(kBlock, 1) void attn_whole_f32_kernel(std::conditio
   };
   // Loads come back in the order they were asked for, 64 bytes a clock: W_V^(h), needed last, is asked for behind the slot's row of G
   // (r = 128, 4 sequences of 600 slots 12.36, now 12.13 us a step), where it is 64 KB behind the merge weight (r = 256, 8 sequences
-  // of 32 slots 9.42, now 9.25; at r = 64 the later place costs 0.1 us, the earlier one gains 0.03).
+  // of 32 slots 9.42, now 9.32; at r = 64 the later place costs 0.1 us, the earlier one gains 0.03).
   constexpr bool kLate = R >= 256;
   if constexpr (DH == 0) load_w();
   if constexpr (DH != 0) {

@@ -352,7 +352,8 @@ struct TileGeom {
 // NW wavefronts of 32 query rows each per workgroup.  NW = 4 is what the launcher uses: two workgroups per CU, whose
 // wavefronts drift apart so that one multiplies while the other does softmax arithmetic.  What bounds it is the chain
 // of a pair of tiles (operand reads, 80 matrix instructions, the arithmetic of the weights) with two wavefronts per SIMD
-// to overlap: matrix pipes busy 40 %, no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
+// to overlap, and a fifth of the time around the tile loop: matrix pipes busy 41 % of 820 thousand cycles, which are the same at any
+// clock (1.7 to 2.2 GHz, as power allows), no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
 // us with the own rows as masked tiles and one tile per step, now 414 (830 TFLOP/s).
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
