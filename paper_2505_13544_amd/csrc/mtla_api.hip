@@ -500,8 +500,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     at.part_f16 = combine_mfma_supported(probe) ? 1 : 0;
     at.run_cost = kRunCost;
   }
-  const bool front = ap && decode_front_supported(*ap, ab);
-  if (ap && ap->c_new_f32 && !front && g.dtype != MTLA_F32) return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
+  if (ap && ap->c_new_f32 && g.dtype != MTLA_F32 && !decode_front_supported(*ap, ab)) return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
   const bool timed = c->prof_n < (int)c->ev_start.size();
   EventPair ev;  // attached to the dispatch itself: the kernel's own begin and end
   if (timed) {
@@ -526,7 +525,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     wh.arrived = reinterpret_cast<int32_t*>(ws) + kArrivalWord;
     if (attn_step_supported(wh, g.dtype)) return hip_ok(launch_attn_step(wh, st, ev)) ? MTLA_OK : MTLA_ERR_HIP;
   }
-  if (front) {  // append and absorb do not depend on each other: one launch
+  if (ap && decode_front_supported(*ap, ab)) {  // append and absorb do not depend on each other: one launch
     if (!hip_ok(launch_decode_front(*ap, ab, st))) return MTLA_ERR_HIP;
   } else if (ap && g.dtype == MTLA_F32) {
     if (!hip_ok(launch_decode_front_f32(*ap, ab, st))) return MTLA_ERR_HIP;
