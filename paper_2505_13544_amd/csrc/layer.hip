@@ -8,11 +8,15 @@
 //   layer_out_kernel     y = concat_h(o_h) W_O (Eq. (softmax))
 // Weights are output-major, [out_features, d_in], so that the contracted index is innermost for both
 // operands of `D[n, token] = sum_k W[n, k] x[token, k]` (v_mfma_f32_16x16x32_bf16: W rows are the A
-// operand, token rows the B operand).  At decode batch sizes these are weight-streaming kernels: a
-// workgroup owns 16 outputs for 16 tokens, its four wavefronts a quarter of the contraction each, operands straight
-// from memory into the operand layout (the token rows come out of L2 for every workgroup after the first); the four
-// sums meet in LDS.  With one wavefront per tile walking the whole contraction, front and output took 4.0 and 4.3 us
-// at d_model = 512, batch 11, of which it spent half waiting for its own requests: now 3.7 and 3.6.
+// operand, token rows the B operand).  A workgroup owns TN x 16 outputs for TM x 16 tokens, its wavefronts a share of the
+// contraction each, so that nothing is fetched twice inside a workgroup and no barrier is needed before their sums meet.
+//
+// Operands go memory -> LDS -> operand layout, through a ring of the wavefront's own.  Straight into the operand layout the
+// neighbouring lanes of a load are 16 rows, and a unit takes such a load one lane a cycle: 38 GB/s whatever is in flight.  With four
+// neighbouring lanes to 64 bytes of a row it takes 115 (both with all units at it, operands in the L2s).
+#include <type_traits>
+
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -21,149 +25,242 @@ namespace mtla {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
 
-// A wavefront's share of one 16 x 16 tile: its quarter of the K steps (K % 32 == 0), D[n0 + 4g + v, tok0 + l16] for v = 0..3.
-// Rows past the ends are clamped (their results are never stored).  The operands of kBatch K steps are requested together,
-// so that a contraction of 1024 costs one round trip to memory.
-constexpr int kBatch = 8;
-struct Steps {
-  int lo, hi;  // in elements
+// TM x 16 tokens by TN x 16 outputs a workgroup of NW wavefronts, each with a ring of D K steps (of 32).  F32: x is fp32 and enters as
+// bf16 hi + lo planes (two matrix instructions a step).
+template <int TM_, int TN_, int NW_, int D_, bool F32_>
+struct LayerTile {
+  static constexpr int TM = TM_, TN = TN_, NW = NW_, D = D_, NT = 64 * NW_, kTiles = TM_ * TN_;
+  static constexpr bool F32 = F32_;
+  static constexpr int XL = F32_ ? 2 : 1, LOADS = TN_ + TM_ * XL;  // loads (1 KB) of 16 tokens, of a step
+  static constexpr int STAGE = 1024 * LOADS, LDS = NW_ * D_ * STAGE;
+  static constexpr int CH = kTiles < 4 ? kTiles : 4;               // 16 x 16 tiles summed at a time
+  static constexpr int kRow = 17;                                  // floats per output row: a column of four rows apart lies in other banks
+  static constexpr int SUMS = NW_ * CH * 16 * kRow * 4;
+  static constexpr int BYTES = LDS > SUMS ? LDS : SUMS;
+  static_assert(kTiles % CH == 0 && D_ >= 3 && LOADS * (D_ - 2) <= 63 && BYTES <= 160 * 1024, "rounds, wait counts, LDS");
 };
-__device__ __forceinline__ Steps steps_of(int K, int wv) {
-  const int per = 32 * ((K / 32 + 3) / 4), lo = wv * per;
-  return Steps{lo, lo + per < K ? lo + per : K};
+
+template <int N, class F>
+__device__ __forceinline__ void each_down(F f) {  // f(N), f(N - 1), .. f(0)
+  f(std::integral_constant<int, N>());
+  if constexpr (N > 0) each_down<N - 1>(f);
 }
-__device__ __forceinline__ float4_t linear_tile(const uint16_t* W, int n_out, const uint16_t* x, int n_tok, int K,
-                                                int n0, int tok0, int l16, int g, const Steps& st) {
-  const int n = n0 + l16 < n_out ? n0 + l16 : n_out - 1, t = tok0 + l16 < n_tok ? tok0 + l16 : n_tok - 1;
-  const uint16_t* wp = W + (size_t)n * K + 8 * g;
-  const uint16_t* xp = x + (size_t)t * K + 8 * g;
-  float4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = st.lo; k0 < st.hi; k0 += 32 * kBatch) {
-    uint4 wf[kBatch], xf[kBatch];
+
+// A wavefront's share of the contraction, `n` K steps from element `lo` on: acc[i][j] = D[n_j + 4g + v, tok_i + l16], v = 0..3.
+// Addresses: the tiles' first rows (wb; xb of the first token tile), and from there the lane's 16 bytes (w_at, x_at); `ring`: this
+// wavefront's part of the LDS.
+template <class C>
+__device__ __forceinline__ void contract(float4_t (&acc)[C::TM][C::TN], const unsigned char* const (&wb)[C::TN], uint32_t w_at, const unsigned char* xb,
+                                         const uint32_t (&x_at)[C::TM][C::XL], int lo, int n, const unsigned char* ring, int l16, int g) {
+  constexpr int TM = C::TM, TN = C::TN, D = C::D, LOADS = C::LOADS;
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
-      if (k0 + 16 * kBatch * half < st.hi)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = kBatch / 2 * half; i < kBatch / 2 * (half + 1); ++i) {
-          const int k = k0 + 32 * i < st.hi ? k0 + 32 * i : k0;  // past the end: a harmless reload
-          wf[i] = *reinterpret_cast<const uint4*>(wp + k);
-          xf[i] = *reinterpret_cast<const uint4*>(xp + k);
+    for (int j = 0; j < TN; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const uint32_t ring_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)ring;
+  auto issue = [&](int step) {
+    const size_t k = (size_t)(lo + 32 * step);
+    const uint32_t at = ring_addr + (uint32_t)(step % D) * C::STAGE;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) load_to_lds_16(wb[j] + 2 * k, w_at, at + j * 1024);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int u = 0; u < C::XL; ++u)
+        load_to_lds_16(xb + (C::F32 ? 4 : 2) * k, x_at[i][u], at + (TN + C::XL * i + u) * 1024);
+  };
+  const uint32_t w_off = (uint32_t)(l16 * 64 + ((g ^ swz_rows16<4>(l16)) << 4));
+  const uint32_t x_swz = (uint32_t)swz_rows16<8>(l16);
+  auto multiply = [&](int step) {
+    const unsigned char* at = ring + (step % D) * C::STAGE;
+    u32x4_t wf[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wf[j] = *reinterpret_cast<const u32x4_t*>(at + j * 1024 + w_off);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const unsigned char* xt = at + (TN + C::XL * i) * 1024;
+      if constexpr (C::F32) {
+        const float4_t a = *reinterpret_cast<const float4_t*>(xt + l16 * 128 + (((2 * g) ^ x_swz) << 4));
+        const float4_t b = *reinterpret_cast<const float4_t*>(xt + l16 * 128 + (((2 * g + 1) ^ x_swz) << 4));
+        uint4 hi, lw;
+        split_bf16x2(a[0], a[1], hi.x, lw.x);
+        split_bf16x2(a[2], a[3], hi.y, lw.y);
+        split_bf16x2(b[0], b[1], hi.z, lw.z);
+        split_bf16x2(b[2], b[3], hi.w, lw.w);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[j]), __builtin_bit_cast(bf16x8_t, hi), acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[j]), __builtin_bit_cast(bf16x8_t, lw), acc[i][j], 0, 0, 0);
         }
+      } else {
+        const u32x4_t xf = *reinterpret_cast<const u32x4_t*>(xt + w_off);
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i)
-      if (k0 + 32 * i < st.hi)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[i]), __builtin_bit_cast(bf16x8_t, xf[i]),
-                                                      acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-// The four wavefronts' shares of a tile, summed; threads below 128 get outputs 2p, 2p + 1 (p = tid / 16) of token tid % 16.
-constexpr int kRow = 17;  // floats per output row: a column of four rows apart lies in other banks
-__device__ __forceinline__ float2 tile_sum(const float4_t& d, float (*s_red)[16 * kRow], int tid, int wv, int l16, int g) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v) s_red[wv][(4 * g + v) * kRow + l16] = d[v];
-  __syncthreads();
-  float2 o = make_float2(0.f, 0.f);
-  if (tid < 128) {
-    const int at = 2 * (tid >> 4) * kRow + (tid & 15);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      o.x += s_red[w][at];
-      o.y += s_red[w][at + kRow];
-    }
-  }
-  return o;
-}
-
-// grid = (tiles, ceil(batch / 16)), tiles = (n_h d_h + n_h d_R + d_R + r) / 16 in the order q, q^R, k^R, c.
-__global__ __launch_bounds__(kBlock) void layer_front_kernel(LayerFrontArgs a) {
-  __shared__ float s_red[4][16 * kRow];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tok0 = 16 * blockIdx.y, K = a.d_model;
-  const int tok = tok0 + (tid & 15), n2 = 2 * (tid >> 4);  // what the thread stores: outputs n2, n2 + 1 of the tile
-  const bool mine = tid < 128 && tok < a.batch;
-  const uint16_t* x = reinterpret_cast<const uint16_t*>(a.x);
-  const Steps st = steps_of(K, wv);
-  const int nq = a.n_heads * a.d_head, nqr = a.n_heads * a.d_rope;
-  int n0 = 16 * blockIdx.x;
-  if (n0 < nq) {  // ---- q
-    const float2 o = tile_sum(linear_tile(reinterpret_cast<const uint16_t*>(a.w_q), nq, x, a.batch, K, n0, tok0, l16, g, st),
-                              s_red, tid, wv, l16, g);
-    if (mine) *reinterpret_cast<float2*>(a.q + (size_t)tok * nq + n0 + n2) = o;
-    return;
-  }
-  n0 -= nq;
-  if (n0 < nqr + a.d_rope) {  // ---- q^R (per head) and k^R (one shared head): rotated at the token's position
-    const bool is_key = n0 >= nqr;
-    if (is_key) n0 -= nqr;
-    const int n_out = is_key ? a.d_rope : nqr;
-    const int pos = mine ? a.seq_len[tok] : 0;  // 0-based position of the token this step appends
-    const float2 cs = rope_angle(pos, a.rope_freq[((n0 + n2) % a.d_rope) / 2]);
-    float2 o = tile_sum(linear_tile(reinterpret_cast<const uint16_t*>(is_key ? a.w_kr : a.w_qr), n_out, x, a.batch, K, n0, tok0,
-                                    l16, g, st), s_red, tid, wv, l16, g);
-    if (mine) {
-      o = rope_turn(o, cs);
-      if (is_key)  // the key goes into the cache: storage type
-        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(a.kr) + (size_t)tok * n_out + n0 + n2) = pack_bf16x2(o.x, o.y);
-      else
-        *reinterpret_cast<float2*>(a.q_rope + (size_t)tok * n_out + n0 + n2) = o;
-    }
-    return;
-  }
-  // ---- c = x W_r, before its normalisation (which the step's append does, where the whole row meets)
-  n0 -= nqr + a.d_rope;
-  const float2 o = tile_sum(linear_tile(reinterpret_cast<const uint16_t*>(a.w_r), a.r, x, a.batch, K, n0, tok0, l16, g, st), s_red,
-                            tid, wv, l16, g);
-  if (mine) *reinterpret_cast<float2*>(a.c + (size_t)tok * a.r + n0 + n2) = o;
-}
-
-// y[token, n] = sum_k o[token, k] W_O[n, k]; o is fp32 and enters as bf16 hi + lo planes (two matrix
-// instructions per step), so that only the weights' own rounding is left.  grid = (ceil(d_model / 16), ceil(batch / 16)).
-__global__ __launch_bounds__(kBlock) void layer_out_kernel(LayerOutArgs a) {
-  __shared__ float s_red[4][16 * kRow];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tok0 = 16 * blockIdx.y, n0 = 16 * blockIdx.x, K = a.k;
-  const int n = n0 + l16 < a.d_model ? n0 + l16 : a.d_model - 1;
-  const int t = tok0 + l16 < a.batch ? tok0 + l16 : a.batch - 1;
-  const uint16_t* wp = reinterpret_cast<const uint16_t*>(a.w_o) + (size_t)n * K + 8 * g;
-  const float* op = a.o + (size_t)t * K + 8 * g;
-  const Steps st = steps_of(K, wv);
-  float4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = st.lo; k0 < st.hi; k0 += 32 * kBatch) {  // three 16-byte loads per step
-    uint4 wf[kBatch];
-    float4_t o0[kBatch], o1[kBatch];
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-      if (k0 + 16 * kBatch * half < st.hi)
-#pragma unroll
-        for (int i = kBatch / 2 * half; i < kBatch / 2 * (half + 1); ++i) {
-          const int k = k0 + 32 * i < st.hi ? k0 + 32 * i : k0;
-          wf[i] = *reinterpret_cast<const uint4*>(wp + k);
-          o0[i] = *reinterpret_cast<const float4_t*>(op + k);
-          o1[i] = *reinterpret_cast<const float4_t*>(op + k + 4);
-        }
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i)
-      if (k0 + 32 * i < st.hi) {
-        uint4 hi, lo;
-        split_bf16x2(o0[i][0], o0[i][1], hi.x, lo.x);
-        split_bf16x2(o0[i][2], o0[i][3], hi.y, lo.y);
-        split_bf16x2(o1[i][0], o1[i][1], hi.z, lo.z);
-        split_bf16x2(o1[i][2], o1[i][3], hi.w, lo.w);
-        const bf16x8_t w8 = __builtin_bit_cast(bf16x8_t, wf[i]);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w8, __builtin_bit_cast(bf16x8_t, hi), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w8, __builtin_bit_cast(bf16x8_t, lo), acc, 0, 0, 0);
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[j]), __builtin_bit_cast(bf16x8_t, xf), acc[i][j], 0, 0, 0);
       }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s)
+    if (s < n) issue(s);
+  int s = 0;
+  for (; s + D - 1 < n; ++s) {  // steps below s + D - 1 have been asked for
+    wait_loads_but<LOADS * (D - 2)>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the step before has been read
+    issue(s + D - 1);
+    multiply(s);
   }
-  const float2 y = tile_sum(acc, s_red, tid, wv, l16, g);
-  const int tok = tok0 + (tid & 15), n2 = n0 + 2 * (tid >> 4);
-  if (tid < 128 && tok < a.batch && n2 < a.d_model)  // d_model is even
-    *reinterpret_cast<float2*>(a.y + (size_t)tok * a.d_model + n2) = y;
+  each_down<D - 2>([&](auto left) {  // all have; so many behind this one
+    constexpr int kLeft = decltype(left)::value;
+    if (kLeft >= n) return;
+    wait_loads_but<LOADS * kLeft>();
+    multiply(s++);
+  });
+}
+// Byte offset of the 16 bytes a lane brings in, of rows of K elements (they land at position `lane` of the KB; the swizzle spreads
+// the reads over the banks): bf16, row lane / 4 of 16; fp32, row lane / 8 of the half u.
+__device__ __forceinline__ uint32_t piece16(int lane, int row, int K) { return 2 * (uint32_t)row * (uint32_t)K + 16 * (uint32_t)((lane & 3) ^ swz_rows16<4>(lane >> 2)); }
+__device__ __forceinline__ uint32_t piece32(int lane, int u, int row, int K) {
+  return 4 * (uint32_t)row * (uint32_t)K + 16 * (uint32_t)((lane & 7) ^ swz_rows16<8>(8 * u + (lane >> 3)));
+}
+
+// The wavefronts' shares of a workgroup's tiles, summed: out(tile, outputs 2p and 2p + 1, p, token).
+template <class C, class Out>
+__device__ __forceinline__ void sum_tiles(const float4_t (&acc)[C::TM][C::TN], unsigned char* lds, int tid, int wv, int l16, int g, Out out) {
+  constexpr int kRow = C::kRow;
+  typedef float Tile[16 * kRow];
+  Tile* s_red = reinterpret_cast<Tile*>(lds);  // [wavefront][CH]
+  const int p = tid & 7, t = (tid >> 3) & 15;  // consecutive lanes: consecutive outputs of a token
+#pragma unroll
+  for (int rnd = 0; rnd < C::kTiles / C::CH; ++rnd) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C::CH; ++c) {
+      const int at = rnd * C::CH + c;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s_red[wv * C::CH + c][(4 * g + v) * kRow + l16] = acc[at / C::TN][at % C::TN][v];
+    }
+    __syncthreads();
+    for (int c = tid >> 7; c < C::CH; c += C::NT / 128) {
+      float2 o = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < C::NW; ++w) {
+        o.x += s_red[w * C::CH + c][2 * p * kRow + t];
+        o.y += s_red[w * C::CH + c][2 * p * kRow + t + kRow];
+      }
+      out(rnd * C::CH + c, o, p, t);
+    }
+  }
+}
+
+// The K steps of wavefront wv: first one, how many.
+template <int NW>
+__device__ __forceinline__ int2 steps_of(int K, int wv) {
+  const int all = K / 32, per = (all + NW - 1) / NW, lo = wv * per;
+  return make_int2(lo, lo >= all ? 0 : (lo + per < all ? per : all - lo));
+}
+
+// Workgroup w runs on XCD w % 8: the token blocks of one block of outputs are numbered to follow one another on one XCD, so that its
+// L2 reads the weights once.  (x: block of outputs, y: of tokens; of nx x ny)
+__device__ __forceinline__ int2 layer_job(unsigned w, unsigned ny) { return make_int2((int)((w >> 3) / ny * 8 + (w & 7)), (int)((w >> 3) % ny)); }
+inline unsigned layer_grid(unsigned nx, unsigned ny) { return (nx + 7) / 8 * 8 * ny; }
+
+// Where 16 outputs of the projections belong: tiles in the order q, q^R, k^R, c.
+struct FrontTile {
+  const uint16_t* W;  // rows of the product it is part of
+  int n0, kind;       // first output in that product; 0 q, 1 q^R, 2 k^R, 3 c
+};
+__device__ __forceinline__ FrontTile front_tile(const LayerFrontArgs& a, int tile) {
+  const int nq = a.n_heads * a.d_head, nqr = a.n_heads * a.d_rope;
+  int n0 = 16 * tile;
+  if (n0 < nq) return FrontTile{reinterpret_cast<const uint16_t*>(a.w_q), n0, 0};
+  n0 -= nq;
+  if (n0 < nqr) return FrontTile{reinterpret_cast<const uint16_t*>(a.w_qr), n0, 1};
+  n0 -= nqr;
+  if (n0 < a.d_rope) return FrontTile{reinterpret_cast<const uint16_t*>(a.w_kr), n0, 2};
+  return FrontTile{reinterpret_cast<const uint16_t*>(a.w_r), n0 - a.d_rope, 3};
+}
+
+// Jobs (layer_job): ceil(tiles / TN) x ceil(batch / (16 TM)), tiles = (n_h d_h + n_h d_R + d_R + r) / 16.
+template <class C>
+__global__ __launch_bounds__(C::NT) void layer_front_kernel(LayerFrontArgs a) {
+  constexpr int TM = C::TM, TN = C::TN;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 job = layer_job(blockIdx.x, (unsigned)(a.batch + 16 * TM - 1) / (16 * TM));
+  const int tok0 = 16 * TM * job.y, K = a.d_model;
+  const int tiles = (a.n_heads * (a.d_head + a.d_rope) + a.d_rope + a.r) / 16, tile0 = TN * job.x;
+  if (tile0 >= tiles) return;
+  const unsigned char* wb[TN];
+  uint32_t x_at[TM][1];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const FrontTile f = front_tile(a, tile0 + j < tiles ? tile0 + j : tiles - 1);
+    wb[j] = reinterpret_cast<const unsigned char*>(f.W + (size_t)f.n0 * K);
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {  // tokens past the batch: clamped, never stored
+    const int t = 16 * i + (lane >> 2), last = a.batch - 1 - tok0;
+    x_at[i][0] = piece16(lane, t < last ? t : last, K);
+  }
+  const unsigned char* xb = reinterpret_cast<const unsigned char*>(a.x) + 2 * (size_t)tok0 * K;
+  const int2 st = steps_of<C::NW>(K, wv);
+  float4_t acc[TM][TN];
+  contract<C>(acc, wb, piece16(lane, lane >> 2, K), xb, x_at, 32 * st.x, st.y, lds + wv * (C::D * C::STAGE), l16, g);
+  sum_tiles<C>(acc, lds, tid, wv, l16, g, [&](int at, float2 o, int p, int t) {
+    const int tok = tok0 + 16 * (at / TN) + t, tile = tile0 + at % TN;
+    if (tok >= a.batch || tile >= tiles) return;
+    const FrontTile f = front_tile(a, tile);
+    const int n = f.n0 + 2 * p;
+    if (f.kind == 1 || f.kind == 2)  // rotated at the 0-based position of the token this step appends
+      o = rope_turn(o, rope_angle(a.seq_len[tok], a.rope_freq[(n % a.d_rope) / 2]));
+    if (f.kind == 2)  // the key goes into the cache: storage type
+      *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(a.kr) + (size_t)tok * a.d_rope + n) = pack_bf16x2(o.x, o.y);
+    else if (f.kind == 0)
+      *reinterpret_cast<float2*>(a.q + (size_t)tok * (a.n_heads * a.d_head) + n) = o;
+    else if (f.kind == 1)
+      *reinterpret_cast<float2*>(a.q_rope + (size_t)tok * (a.n_heads * a.d_rope) + n) = o;
+    else  // c = x W_r, before its normalisation (which the step's append does, where the whole row meets)
+      *reinterpret_cast<float2*>(a.c + (size_t)tok * a.r + n) = o;
+  });
+}
+
+// y[token, n] = sum_k o[token, k] W_O[n, k]; o is fp32 and enters as bf16 hi + lo planes, so that only the weights' own
+// rounding is left.  Jobs: ceil(d_model / (16 TN)) x ceil(batch / (16 TM)).
+template <class C>
+__global__ __launch_bounds__(C::NT) void layer_out_kernel(LayerOutArgs a) {
+  constexpr int TM = C::TM, TN = C::TN;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 job = layer_job(blockIdx.x, (unsigned)(a.batch + 16 * TM - 1) / (16 * TM));
+  const int tok0 = 16 * TM * job.y, n0 = 16 * TN * job.x, K = a.k;
+  if (n0 >= a.d_model) return;
+  const unsigned char* wb[TN];
+  uint32_t o_at[TM][2];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {  // (d_model is a multiple of 32)
+    const int n = n0 + 16 * j < a.d_model ? n0 + 16 * j : a.d_model - 16;
+    wb[j] = reinterpret_cast<const unsigned char*>(a.w_o) + 2 * (size_t)n * K;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = 16 * i + 8 * u + (lane >> 3), last = a.batch - 1 - tok0;
+      o_at[i][u] = piece32(lane, u, t < last ? t : last, K);
+    }
+  const unsigned char* ob = reinterpret_cast<const unsigned char*>(a.o) + 4 * (size_t)tok0 * K;
+  const int2 st = steps_of<C::NW>(K, wv);
+  float4_t acc[TM][TN];
+  contract<C>(acc, wb, piece16(lane, lane >> 2, K), ob, o_at, 32 * st.x, st.y, lds + wv * (C::D * C::STAGE), l16, g);
+  sum_tiles<C>(acc, lds, tid, wv, l16, g, [&](int at, float2 y, int p, int t) {
+    const int tok = tok0 + 16 * (at / TN) + t, n = n0 + 16 * (at % TN) + 2 * p;
+    if (tok < a.batch && n < a.d_model)  // d_model is even
+      *reinterpret_cast<float2*>(a.y + (size_t)tok * a.d_model + n) = y;
+  });
 }
 
 // The state a continuing prefill starts from, in front of an append of its own.
@@ -186,15 +283,50 @@ bool layer_supported(const LayerFrontArgs& a) {
          a.d_rope <= 64 && a.r % 16 == 0 && a.batch <= 16 * 65535;
 }
 
-hipError_t launch_layer_front(const LayerFrontArgs& a, hipStream_t st) {
+template <class C>
+hipError_t layer_front_as(const LayerFrontArgs& a, hipStream_t st) {
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&layer_front_kernel<C>, C::BYTES, lds_allowed);
+  if (e != hipSuccess) return e;
   const int tiles = (a.n_heads * (a.d_head + a.d_rope) + a.d_rope + a.r) / 16;
-  hipLaunchKernelGGL(layer_front_kernel, dim3(tiles, (a.batch + 15) / 16), dim3(kBlock), 0, st, a);
+  hipLaunchKernelGGL(layer_front_kernel<C>, dim3(layer_grid((tiles + C::TN - 1) / C::TN, (a.batch + 16 * C::TM - 1) / (16 * C::TM))), dim3(C::NT), C::BYTES, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_layer_out(const LayerOutArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(layer_out_kernel, dim3((a.d_model + 15) / 16, (a.batch + 15) / 16), dim3(kBlock), 0, st, a);
+template <class C>
+hipError_t layer_out_as(const LayerOutArgs& a, hipStream_t st) {
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&layer_out_kernel<C>, C::BYTES, lds_allowed);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(layer_out_kernel<C>, dim3(layer_grid((a.d_model / 16 + C::TN - 1) / C::TN, (a.batch + 16 * C::TM - 1) / (16 * C::TM))), dim3(C::NT), C::BYTES, st, a);
   return hipGetLastError();
+}
+
+// A workgroup's tokens and outputs: a 16 x 16 tile each as long as that leaves no more of them than the chip holds at once; beyond, a larger
+// tile fetches less (a unit is at the rate of its loads) and has fewer sums to meet.  us a launch, weights in turn out of three sets:
+//   projections  B = 16, d_model 2048 (228 tiles)   1 x 1 tiles 4.9, 2 x 2 6.2      output  B = 32, 2048 (256)   1 x 1 4.4, 1 x 2 5.2
+//                B = 32, 2048 (456)     1 x 1 6.7, 2 x 1 5.7, 2 x 2 7.0                     B = 256, 512 (512)   1 x 1 3.3, 1 x 2 3.0
+//                B = 100, 1024 (798)    1 x 1 5.2, 2 x 2 4.6, 4 x 4 10                      B = 64, 4096 (1024)  1 x 2 16, 2 x 2 13, 2 x 4 16
+//                B = 64, 4096 (1680)    2 x 2 20, 4 x 4 24                                  B = 256, 2048 (2048) 2 x 2 12.2, 2 x 4 10.1, 4 x 4 15.5
+//                B = 256, 2048 (3648)   2 x 2 17.7, 4 x 4 15.7                              B = 189, 4096 (3072) 2 x 4 32, 4 x 4 26.9
+// (Operands straight into the registers, 1 x 1 tiles: 6.2, 9.8, 9.3, 51.6, 54.5; 8.0, 5.1, 43.9, 44.2, 125.6.)
+hipError_t launch_layer_front(const LayerFrontArgs& a, hipStream_t st) {
+  const int token_tiles = (a.batch + 15) / 16;
+  const long long tiles = (long long)(a.n_heads * (a.d_head + a.d_rope) + a.d_rope + a.r) / 16 * token_tiles;
+  if (token_tiles == 1 || tiles <= 400) return layer_front_as<LayerTile<1, 1, 4, 4, false>>(a, st);
+  if (tiles <= 600) return layer_front_as<LayerTile<2, 1, 4, 4, false>>(a, st);
+  if (tiles <= 2000) return layer_front_as<LayerTile<2, 2, 4, 4, false>>(a, st);
+  return layer_front_as<LayerTile<4, 4, 4, 3, false>>(a, st);
+}
+
+hipError_t launch_layer_out(const LayerOutArgs& a, hipStream_t st) {
+  const int token_tiles = (a.batch + 15) / 16;
+  const long long tiles = (long long)((a.d_model + 15) / 16) * token_tiles;
+  if (tiles <= 300) return layer_out_as<LayerTile<1, 1, 8, 3, true>>(a, st);
+  if (token_tiles == 1 || tiles <= 600) return layer_out_as<LayerTile<1, 2, 8, 3, true>>(a, st);
+  if (tiles <= 1200) return layer_out_as<LayerTile<2, 2, 8, 3, true>>(a, st);
+  if (tiles <= 2600) return layer_out_as<LayerTile<2, 4, 4, 3, true>>(a, st);
+  return layer_out_as<LayerTile<4, 4, 4, 3, true>>(a, st);
 }
 
 }  // namespace mtla

@@ -67,6 +67,20 @@ def test_layer_step_every_token(stride, batch, d_model, n_heads, d_head, r, d_ro
     _run(wl, T, set(range(T)), list(range(batch)))
 
 
+@pytest.mark.parametrize("batch,d_model,n_heads,r", [(17, 96, 4, 64),     # one K step for three of four wavefronts, none for the last
+                                                     (100, 512, 8, 256),  # projections 2 x 1 tiles a workgroup, the last block half empty
+                                                     (161, 512, 8, 256),  # 2 x 2; output 1 x 2
+                                                     (500, 512, 8, 256),  # 4 x 4 over 66 tiles; output 2 x 2
+                                                     (500, 736, 4, 64),   # 2 x 2; output 2 x 4 over 46 tiles
+                                                     (1000, 736, 8, 128)])  # 4 x 4 both
+def test_layer_step_many_sequences(batch, d_model, n_heads, r):
+    # every tile of launch_layer_front and launch_layer_out; sequences at the edges of their token blocks
+    T = 5
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="layer_many", batch=batch, d_model=d_model, n_heads=n_heads, r=r, prefix=T, steps=0, stride=2, seed=77)
+    seqs = sorted({b for b in (0, 1, 15, 16, 31, 32, 63, 64, 99, 130, 255, 511, batch - 2, batch - 1) if b < batch})
+    _run(wl, T, {1, T - 1}, seqs)
+
+
 def test_layer_step_affine_layer_norm_and_other_constants():
     # LayerNorm with scale and shift, a larger epsilon, another RoPE base
     T = 15
