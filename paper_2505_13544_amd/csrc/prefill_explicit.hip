@@ -365,6 +365,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   constexpr int NBUF = 4;                 // tiles in LDS: two pairs
   constexpr int NIK = G::NCK / NW;  // loads per wavefront and region of keys or values
   constexpr int IROWS = 64 * NW / VC;     // rows between a wavefront's chunks of a region
+  constexpr int kOwn = 2 * G::BYTES / NW; // a wavefront's part of a pair of buffers
+  static_assert(1024 * (KQ + KD) <= kOwn, "sixteen rows' queries and values fit");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NBUF * G::BYTES];
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -503,53 +505,77 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       load_to_lds_16(kr16 + src_row(BN * t + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
     };
 
-    // the first tiles travel while the rows are set up.  (Every wavefront is done with the buffers of the previous block;
-    // no tile load is in flight: the last tile of a block waits for everything.)
+    // the first tiles travel while the rows are set up.  (Every wavefront is done with the buffers of the previous block, its
+    // rows on their way out included; no tile load is in flight: the last tile of a block waits for everything.)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     barrier_only();
 #pragma unroll
     for (int t = 0; t < 2; ++t)
       if (n_tiles > 0) issue(t);
 
-    // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column
+    // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column.
+    // They come in with four neighbouring lanes to 64 bytes of a row and change places through the wavefront's part of the buffers
+    // that the second pair of tiles will take: in the operand layout neighbouring lanes are 16 rows, which a unit's address path takes one
+    // lane a cycle (66 cycles a load, 10 thousand a block; now 2.5).  Stores likewise, see below.
     u32x4_t qf[2][KQ];
     float4_t neg_ref[2];        // - reference of the row's weights, where the logits' sums start
     float l_run[2];
     float4_t acc[2][MT];
     int bound[2];               // columns open to the lane's rows
+    {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));              // (what depends on it is formed here, not kept in registers over the tile loop)
+      const int qr = ln >> 2, qc = ln & 3;      // row and 16 bytes of the 64 that a load brings of it
+      u32x4_t qd[2][KQ], kd[2][KQ], vd[2][KD];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int m = m0 + 32 * wv + 16 * rt + l16;
-      const int mr = m < len ? m : len - 1;
-      bound[rt] = (p0 + mr) / s;
-      const size_t row = (size_t)b * T + mr;
-      const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * g;
-      const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * g;
-      const uint32_t own = (uint32_t)(past + mr);
-      const uint16_t* kp = kx + own * kv_stride + 8 * g;
-      const uint16_t* krp = kr16 + own * DR + 8 * g;
-      const uint16_t* vp = vx + own * kv_stride + 4 * g;
-      u32x4_t kd[KQ];
-      uint2 vd[MT];
+      for (int rt = 0; rt < 2; ++rt) {
+        const int m = m0 + 32 * wv + 16 * rt + qr, mr = m < len ? m : len - 1;
+        const size_t row = (size_t)b * T + mr;
+        const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * qc;
+        const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * qc;
+        const uint32_t own = (uint32_t)(past + mr);
+        const uint16_t* kp = kx + own * kv_stride + 8 * qc;
+        const uint16_t* krp = kr16 + own * DR + 8 * qc;
+        const uint16_t* vp = vx + own * kv_stride + 8 * qc;
 #pragma unroll
-      for (int kk = 0; kk < KQ; ++kk) {
-        qf[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
-        kd[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+        for (int kk = 0; kk < KQ; ++kk) {
+          qd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
+          kd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+        }
+#pragma unroll
+        for (int kk = 0; kk < KD; ++kk) vd[rt][kk] = *reinterpret_cast<const u32x4_t*>(vp + 32 * kk);
       }
+      unsigned char* own_lds = lds + 2 * G::BYTES + wv * kOwn;  // [query pieces | value pieces][row][64 bytes]
+      unsigned char* to = own_lds + qr * 64 + ((qc ^ swz_rows16<4>(qr)) << 4);
+      const unsigned char* from = own_lds + l16 * 64;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) vd[mt] = *reinterpret_cast<const uint2*>(vp + 16 * mt);
-      float e = 0.f;
+      for (int rt = 0; rt < 2; ++rt) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int m = m0 + 32 * wv + 16 * rt + l16;
+        bound[rt] = (p0 + (m < len ? m : len - 1)) / s;
+        float e = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < KQ; ++kk) {
-        // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
-        if (!LAYER) qf[rt][kk] = bf16x8_to_f16x8(qf[rt][kk], a.scale_log2);
-        e = dot8(kd[kk], qf[rt][kk], e);
+        for (int kk = 0; kk < KQ; ++kk) {
+          // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
+          if (!LAYER) qd[rt][kk] = bf16x8_to_f16x8(qd[rt][kk], a.scale_log2);
+          e = dot8(kd[rt][kk], qd[rt][kk], e);
+          *reinterpret_cast<u32x4_t*>(to + 1024 * kk) = qd[rt][kk];
+        }
+#pragma unroll
+        for (int kk = 0; kk < KD; ++kk) *reinterpret_cast<u32x4_t*>(to + 1024 * (KQ + kk)) = vd[rt][kk];
+        e = group_reduce<4>(e, LaneSum());
+        e = __int_as_float(__builtin_amdgcn_ds_bpermute(16 * l16, __float_as_int(e)));  // of row l16: lane 4 l16
+        neg_ref[rt] = float4_t{-e, -e, -e, -e};
+        l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4_t*>(from + 1024 * kk + ((g ^ swz_rows16<4>(l16)) << 4));
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {  // dims 16 mt + 4g ..
+          const uint2 v = *reinterpret_cast<const uint2*>(from + 1024 * (KQ + (mt >> 1)) + (((2 * (mt & 1) + (g >> 1)) ^ swz_rows16<4>(l16)) << 4) + 8 * (g & 1));
+          acc[rt][mt] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
+        }
       }
-      e = quarter_reduce(e, LaneSum());
-      neg_ref[rt] = float4_t{-e, -e, -e, -e};
-      l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        acc[rt][mt] = float4_t{f16_lo_to_f32(vd[mt].x), f16_hi_to_f32(vd[mt].x), f16_lo_to_f32(vd[mt].y), f16_hi_to_f32(vd[mt].y)};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the barrier behind which those buffers are filled
     }
     // columns open to all of the wavefront's rows, and to any of them
     const int all_below = (p0 + m0 + 32 * wv) / s;
@@ -704,28 +730,36 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       for (int mt = 0; mt < MT; ++mt) product(mt, vf[mt], pb1);
     }
 
-    // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3
+    // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3.  The rows leave through LDS, whole
+    // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path), in the wavefront's part of the pair
+    // of buffers that the last step did not read: every wavefront is past the step before it.
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    unsigned char* leave = lds + (n_tiles > 0 ? (~(n_tiles - 1) & 2) : 0) * G::BYTES + wv * kOwn;
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
+      constexpr int ES = LAYER ? 2 : 4, RB = DH * ES, PPR = RB / 16;  // bytes of a row, 16-byte pieces; piece j of row i sits at j ^ (i % 16), in RB
+      static_assert(16 * RB <= kOwn && PPR >= 8, "the rows fit");
       const float l = quarter_reduce(l_run[rt], LaneSum());
-      const int m = m0 + 32 * wv + 16 * rt + l16;
-      if (m < T) {
-        const bool live = m < len;  // rows past the sequence's length are zeros, whatever their inputs held
-        const float inv = live ? 1.f / l : 0.f;
+      const int mt0 = m0 + 32 * wv + 16 * rt;
+      const bool live = mt0 + (ln & 15) < len;  // rows past the sequence's length are zeros, whatever their inputs held
+      const float inv = live ? 1.f / l : 0.f;
+      constexpr int SW = PPR < 16 ? PPR - 1 : 15;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[rt][mt] = live ? acc[rt][mt] * inv : float4_t{0.f, 0.f, 0.f, 0.f};
-        if constexpr (LAYER) {
-          uint16_t* po = reinterpret_cast<uint16_t*>(a.out16) + (((size_t)b * T + m) * nh + h) * DH + 4 * g;
+      for (int mt = 0; mt < MT; ++mt) {
+        const float4_t o = live ? acc[rt][mt] * inv : float4_t{0.f, 0.f, 0.f, 0.f};
+        if constexpr (LAYER)
+          *reinterpret_cast<uint2*>(leave + (ln & 15) * RB + (((2 * mt + ((ln >> 5) & 1)) ^ (ln & SW)) << 4) + 8 * ((ln >> 4) & 1)) = make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
+        else
+          *reinterpret_cast<float4_t*>(leave + (ln & 15) * RB + (((4 * mt + (ln >> 4)) ^ (ln & SW)) << 4)) = o;
+      }
+      unsigned char* out_rows = LAYER ? reinterpret_cast<unsigned char*>(a.out16) + (((size_t)b * T + mt0) * nh + h) * RB
+                                      : reinterpret_cast<unsigned char*>(out) + (size_t)mt0 * out_stride * 4;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const float4_t o = acc[rt][mt];
-            *reinterpret_cast<uint2*>(po + 16 * mt) = make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
-          }
-        } else {
-          float* po = out + (size_t)m * out_stride + 4 * g;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<float4_t*>(po + 16 * mt) = acc[rt][mt];
-        }
+      for (int i = 0; i < 16 * PPR / 64; ++i) {
+        const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(leave + row * RB + ((c ^ (row & SW)) << 4));
+        if (mt0 + row < T) *reinterpret_cast<u32x4_t*>(out_rows + (size_t)row * out_stride * ES + 16 * c) = v;
       }
     }
   }  // pass
