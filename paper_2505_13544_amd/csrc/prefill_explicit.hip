@@ -23,13 +23,13 @@
 //   gemm_nt_kernel        K = C_hat' W_K, V = C_hat' W_V for all T rows: a plain MFMA GEMM, its tile sized
 //                         to the rows there are, operands streamed from memory straight into LDS (also the
 //                         projections of the whole-layer prefill, with rotation / scaling on the way out)
-//   attn_explicit_kernel  one workgroup per pair of 128-row blocks of a (head, sequence), or per block where
-//                         pairs would leave units without work; keys, RoPE keys and values of 32 columns at a
+//   attn_explicit_kernel  one workgroup per block of 128 rows of a (head, sequence), in the order of attn_blocks.h; keys, RoPE keys and values of 32 columns at a
 //                         time stream from memory straight into LDS and are shared by the four wavefronts
 //                         (32 query rows each, queries in registers)
 #include <cmath>
 #include <type_traits>
 
+#include "attn_blocks.h"
 #include "bounds.h"
 #include "gemm_tiles.h"
 #include "lds_stream.h"
@@ -352,8 +352,8 @@ struct TileGeom {
 // NW wavefronts of 32 query rows each per workgroup.  NW = 4 is what the launcher uses: two workgroups per CU, whose
 // wavefronts drift apart so that one multiplies while the other does softmax arithmetic.  What bounds it is the chain
 // of a pair of tiles (operand reads, 80 matrix instructions, the arithmetic of the weights) with two wavefronts per SIMD
-// to overlap, and a fifth of the time around the tile loop: matrix pipes busy 41 % of 820 thousand cycles, which are the same at any
-// clock (1.7 to 2.2 GHz, as power allows), no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
+// to overlap, and what lies around the tile loop: matrix pipes busy 41 % (at 820 thousand cycles, the same at any
+// clock from 1.7 to 2.2 GHz, as power allows), no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
 // us with the own rows as masked tiles and one tile per step, now 414 (830 TFLOP/s).
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
@@ -373,22 +373,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int T = a.T, s = a.stride, nh = a.n_heads;
-  // Workgroups are handed to the 8 XCDs in turn (w % 8).  The row blocks of one (sequence, head) read the same keys and
-  // values, so they are numbered to land on one XCD and meet in its L2, and the (sequence, head) pairs are dealt to the
-  // XCDs in turn, so that long and short sequences fall on all of them.  Single blocks: those with most columns first.
-  const int n_blocks = (T + BM - 1) / BM, n_units = a.unpaired ? n_blocks : (n_blocks + 1) / 2;
-  const int per_xcd = (nh * a.batch + 7) / 8, i_xcd = (int)(blockIdx.x >> 3);
-  const int unit = a.unpaired ? i_xcd / per_xcd : i_xcd % n_units;
-  const int hb = 8 * (a.unpaired ? i_xcd % per_xcd : i_xcd / n_units) + (int)(blockIdx.x & 7);
+  const int n_blocks = (T + BM - 1) / BM;
+  const AttnBlock job = attn_block(blockIdx.x, nh * a.batch, n_blocks, a.group);
+  const int hb = __builtin_amdgcn_readfirstlane(job.pair);
   if (hb >= nh * a.batch) return;
   const int h = hb % nh, b = hb / nh;
   const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
   // A continuing sequence has p0 tokens behind it: the final states of its first p0 / s slots are the
   // first rows of its part of the key / value arrays (one per slot), its new rows follow.
   const int Tp = (CONT ? a.past_pitch : 0) + T;
-  const int p0 = CONT ? start_inside(a.pos0[b], s, a.past_pitch) : 0;
+  const int p0 = CONT ? __builtin_amdgcn_readfirstlane(start_inside(a.pos0[b], s, a.past_pitch)) : 0;
   const int j0 = p0 / s, past = j0;
-  if (CONT && a.advance && unit == 0 && h == 0) {
+  if (CONT && a.advance && job.block == 0 && h == 0) {
     const int old = a.pos0[b];
     if (len > 0 && append_status(old, len, s, a.max_slots) == 0) {  // as the append took it
       if (tid == 0) a.advance[b] = old + len;
@@ -423,357 +419,347 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   const uint32_t v_row_off = (uint32_t)(v_row * VC * 16 + 8 * (l16 & 1));
   const uint32_t v_swz = (uint32_t)(swz_tr<VC>(v_row) ^ ((l16 & 3) >> 1)) << 4;
 
-  // Row block x walks about x * BM / (s BN) tiles.  A workgroup takes block n-1-x and then block x, so every workgroup
-  // of the launch walks the same number of tiles (the middle one, if n is odd, half); a launch that such pairs would not
-  // fill the chip with takes single blocks (a.unpaired).
-  for (int pass = 0; pass < 2; ++pass) {
-    const int xb = pass == 0 ? n_blocks - 1 - unit : unit;
-    if (pass == 1 && (a.unpaired || xb >= n_blocks - 1 - unit)) break;
-    const int m0 = xb * BM;
-    if (m0 >= len) {  // padding rows only
-      const int rows = T - m0 < BM ? T - m0 : BM;
-      for (int i = tid; i < rows * (DH / 4); i += NT) {
-        const size_t row = (size_t)(m0 + i / (DH / 4));
-        if constexpr (LAYER)
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out16) + (((size_t)b * T + row) * nh + h) * DH + 4 * (i % (DH / 4))) =
-              make_uint2(0u, 0u);
-        else
-          *reinterpret_cast<float4_t*>(out + row * out_stride + 4 * (i % (DH / 4))) = float4_t{0.f, 0.f, 0.f, 0.f};
-      }
-      continue;
+  const int m0 = __builtin_amdgcn_readfirstlane(job.block) * BM;
+  if (m0 >= len) {  // padding rows only
+    const int rows = T - m0 < BM ? T - m0 : BM;
+    for (int i = tid; i < rows * (DH / 4); i += NT) {
+      const size_t row = (size_t)(m0 + i / (DH / 4));
+      if constexpr (LAYER)
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out16) + (((size_t)b * T + row) * nh + h) * DH + 4 * (i % (DH / 4))) =
+            make_uint2(0u, 0u);
+      else
+        *reinterpret_cast<float4_t*>(out + row * out_stride + 4 * (i % (DH / 4))) = float4_t{0.f, 0.f, 0.f, 0.f};
     }
-    // ---- the columns: slots j < (p0 + last row) / s (a slot of the past: row j; one closed inside the chunk: the
-    // chunk's row j*s + s-1 - p0)
-    const int m_last = (m0 + BM < len ? m0 + BM : len) - 1;
-    const int n_cols = (p0 + m_last) / s, n_tiles = (n_cols + BN - 1) / BN;
-    // source row of column c (columns past the last one: a readable duplicate)
-    auto src_row = [&](int c) -> uint32_t {
-      c = c < n_cols ? c : n_cols - 1;
-      return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
-    };
-    // this wavefront's part of tile t on its way into buffer t % NBUF: 2 NIK + 1 loads.  Tiles are asked for in order; while
-    // their rows are at one distance (`rs`: 1 among the slots of the past, s among the chunk-final rows) the next
-    // tile's addresses are the last one's plus a constant: uniform bases and lane offsets that stand.
-    const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
-    int run_end = 0;              // tiles below it follow the bases as they are
-    uint64_t base_k[NIK], base_v[NIK], base_r = 0;  // (addresses)
-    uint32_t step_k = 0, step_r = 0;                // bytes from a tile to the next (values as keys)
-    uint32_t off_k = 0, off_v = 0, off_r = 0;       // bytes from a tile's first source row to the lane's piece
-    auto start_run = [&](int t) {  // tile t begins a run of tiles whose rows are at one distance, or is one of its own
-      const int c0 = BN * t;
-      const bool in_past = CONT && c0 < j0;
-      const int lim = in_past ? (j0 < n_cols ? j0 : n_cols) : n_cols;  // columns of this kind
-      run_end = lim / BN;
-      if (run_end <= t) return;
-      const int rs = in_past ? 1 : s;
-      const uint32_t row0 = in_past ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
-      off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
-      off_v = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_v);
-      off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
+    return;
+  }
+  // ---- the columns: slots j < (p0 + last row) / s (a slot of the past: row j; one closed inside the chunk: the
+  // chunk's row j*s + s-1 - p0)
+  const int m_last = (m0 + BM < len ? m0 + BM : len) - 1;
+  const int n_cols = (p0 + m_last) / s, n_tiles = (n_cols + BN - 1) / BN;
+  // source row of column c (columns past the last one: a readable duplicate)
+  auto src_row = [&](int c) -> uint32_t {
+    c = c < n_cols ? c : n_cols - 1;
+    return (uint32_t)(c < j0 ? c : past + c * s + s - 1 - p0);
+  };
+  // this wavefront's part of tile t on its way into buffer t % NBUF: 2 NIK + 1 loads.  Tiles are asked for in order; while
+  // their rows are at one distance (`rs`: 1 among the slots of the past, s among the chunk-final rows) the next
+  // tile's addresses are the last one's plus a constant: uniform bases and lane offsets that stand.
+  const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_byte_ptr)lds;
+  int run_end = 0;              // tiles below it follow the bases as they are
+  uint64_t base_k[NIK], base_v[NIK];              // (addresses)
+  uint32_t at_r = 0;                              // of the RoPE keys' array (its bytes stay below 2^32)
+  uint32_t step_k = 0, step_r = 0;                // bytes from a tile to the next (values as keys)
+  uint32_t off_k = 0, off_v = 0, off_r = 0;       // bytes from a tile's first source row to the lane's piece
+  auto start_run = [&](int t) {  // tile t begins a run of tiles whose rows are at one distance, or is one of its own
+    const int c0 = BN * t;
+    const bool in_past = CONT && c0 < j0;
+    const int lim = in_past ? (j0 < n_cols ? j0 : n_cols) : n_cols;  // columns of this kind
+    run_end = lim / BN;
+    if (run_end <= t) return;
+    const int rs = in_past ? 1 : s;
+    const uint32_t row0 = in_past ? (uint32_t)c0 : (uint32_t)(past + c0 * s + s - 1 - p0);
+    off_k = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_k);
+    off_v = 2 * ((uint32_t)(row_k * rs) * kv_stride + src_v);
+    off_r = 2 * ((uint32_t)(row_r * rs) * DR + src_r);
+#pragma unroll
+    for (int i = 0; i < NIK; ++i) {
+      base_k[i] = (uint64_t)(uintptr_t)kx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
+      base_v[i] = (uint64_t)(uintptr_t)vx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
+    }
+    at_r = 2 * row0 * DR;
+    step_k = 2 * (uint32_t)(BN * rs) * kv_stride;
+    step_r = 2 * (uint32_t)(BN * rs) * DR;
+  };
+  auto issue = [&](int t) {
+    const uint32_t buf = lds_addr + (uint32_t)(t % NBUF) * (uint32_t)G::BYTES;
+    if (t >= run_end) start_run(t);
+    if (t < run_end) {
 #pragma unroll
       for (int i = 0; i < NIK; ++i) {
-        base_k[i] = (uint64_t)(uintptr_t)kx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
-        base_v[i] = (uint64_t)(uintptr_t)vx + 2 * (uint64_t)(row0 + (uint32_t)(i * IROWS * rs)) * kv_stride;
-      }
-      base_r = (uint64_t)(uintptr_t)kr16 + 2 * (uint64_t)row0 * DR;
-      step_k = 2 * (uint32_t)(BN * rs) * kv_stride;
-      step_r = 2 * (uint32_t)(BN * rs) * DR;
-    };
-    auto issue = [&](int t) {
-      const uint32_t buf = lds_addr + (uint32_t)(t % NBUF) * (uint32_t)G::BYTES;
-      if (t >= run_end) start_run(t);
-      if (t < run_end) {
-#pragma unroll
-        for (int i = 0; i < NIK; ++i) {
-          const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
-          load_to_lds_16(reinterpret_cast<const void*>(base_k[i]), off_k, buf + G::K_OFF + chunk);
-          load_to_lds_16(reinterpret_cast<const void*>(base_v[i]), off_v, buf + G::V_OFF + chunk);
-          base_k[i] += step_k;
-          base_v[i] += step_k;
-        }
-        load_to_lds_16(reinterpret_cast<const void*>(base_r), off_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
-        base_r += step_r;
-        return;
-      }
-#pragma unroll
-      for (int i = 0; i < NIK; ++i) {
-        const uint32_t srow = src_row(BN * t + row_k + i * IROWS);
         const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
-        load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
-        load_to_lds_16(vx + srow * kv_stride + src_v, buf + G::V_OFF + chunk);
+        load_to_lds_16(reinterpret_cast<const void*>(base_k[i]), off_k, buf + G::K_OFF + chunk);
+        load_to_lds_16(reinterpret_cast<const void*>(base_v[i]), off_v, buf + G::V_OFF + chunk);
+        base_k[i] += step_k;
+        base_v[i] += step_k;
       }
-      load_to_lds_16(kr16 + src_row(BN * t + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
+      load_to_lds_16(reinterpret_cast<const unsigned char*>(kr16) + at_r, off_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
+      at_r += step_r;
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < NIK; ++i) {
+      const uint32_t srow = src_row(BN * t + row_k + i * IROWS);
+      const uint32_t chunk = (uint32_t)((wv + NW * i) * 1024);
+      load_to_lds_16(kx + srow * kv_stride + src_k, buf + G::K_OFF + chunk);
+      load_to_lds_16(vx + srow * kv_stride + src_v, buf + G::V_OFF + chunk);
+    }
+    load_to_lds_16(kr16 + src_row(BN * t + row_r) * DR + src_r, buf + G::R_OFF + (uint32_t)(wr * 1024));
+  };
+
+  // the first tiles travel while the rows are set up
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+    if (n_tiles > 0) issue(t);
+
+  // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column.
+  // They come in with four neighbouring lanes to 64 bytes of a row and change places through the wavefront's part of the buffers
+  // that the second pair of tiles will take: in the operand layout neighbouring lanes are 16 rows, which a unit's address path takes one
+  // lane a cycle (66 cycles a load, 10 thousand a block; now 2.5).  Stores likewise, see below.
+  u32x4_t qf[2][KQ];
+  float4_t neg_ref[2];        // - reference of the row's weights, where the logits' sums start
+  float l_run[2];
+  float4_t acc[2][MT];
+  int bound[2];               // columns open to the lane's rows
+  {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));              // (what depends on it is formed here, not kept in registers over the tile loop)
+    const int qr = ln >> 2, qc = ln & 3;      // row and 16 bytes of the 64 that a load brings of it
+    u32x4_t qd[2][KQ], kd[2][KQ], vd[2][KD];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const int m = m0 + 32 * wv + 16 * rt + qr, mr = m < len ? m : len - 1;
+      const size_t row = (size_t)b * T + mr;
+      const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * qc;
+      const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * qc;
+      const uint32_t own = (uint32_t)(past + mr);
+      const uint16_t* kp = kx + own * kv_stride + 8 * qc;
+      const uint16_t* krp = kr16 + own * DR + 8 * qc;
+      const uint16_t* vp = vx + own * kv_stride + 8 * qc;
+#pragma unroll
+      for (int kk = 0; kk < KQ; ++kk) {
+        qd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
+        kd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+      }
+#pragma unroll
+      for (int kk = 0; kk < KD; ++kk) vd[rt][kk] = *reinterpret_cast<const u32x4_t*>(vp + 32 * kk);
+    }
+    unsigned char* own_lds = lds + 2 * G::BYTES + wv * kOwn;  // [query pieces | value pieces][row][64 bytes]
+    unsigned char* to = own_lds + qr * 64 + ((qc ^ swz_rows16<4>(qr)) << 4);
+    const unsigned char* from = own_lds + l16 * 64;
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int m = m0 + 32 * wv + 16 * rt + l16;
+      bound[rt] = (p0 + (m < len ? m : len - 1)) / s;
+      float e = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KQ; ++kk) {
+        // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
+        if (!LAYER) qd[rt][kk] = bf16x8_to_f16x8(qd[rt][kk], a.scale_log2);
+        e = dot8(kd[rt][kk], qd[rt][kk], e);
+        *reinterpret_cast<u32x4_t*>(to + 1024 * kk) = qd[rt][kk];
+      }
+#pragma unroll
+      for (int kk = 0; kk < KD; ++kk) *reinterpret_cast<u32x4_t*>(to + 1024 * (KQ + kk)) = vd[rt][kk];
+      e = group_reduce<4>(e, LaneSum());
+      e = __int_as_float(__builtin_amdgcn_ds_bpermute(16 * l16, __float_as_int(e)));  // of row l16: lane 4 l16
+      neg_ref[rt] = float4_t{-e, -e, -e, -e};
+      l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
+#pragma unroll
+      for (int kk = 0; kk < KQ; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4_t*>(from + 1024 * kk + ((g ^ swz_rows16<4>(l16)) << 4));
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {  // dims 16 mt + 4g ..
+        const uint2 v = *reinterpret_cast<const uint2*>(from + 1024 * (KQ + (mt >> 1)) + (((2 * (mt & 1) + (g >> 1)) ^ swz_rows16<4>(l16)) << 4) + 8 * (g & 1));
+        acc[rt][mt] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the barrier behind which those buffers are filled
+  }
+  // columns open to all of the wavefront's rows, and to any of them
+  const int all_below = (p0 + m0 + 32 * wv) / s;
+  const int none_from = (p0 + m0 + 32 * wv + 31) / s;
+
+  // Two tiles per step: while one pair is multiplied the other is on its way (four buffers), one wait and one barrier for
+  // both, and the matrix products of one tile beside the softmax arithmetic of the other.
+  for (int t = 0; t < n_tiles; t += 2) {
+    wait_loads_but<0>();                  // the pair has landed: this wavefront's part, then everyone's
+    barrier_only();
+    if (t + 2 < n_tiles) {                // into the buffers the pair before was read from: every wavefront is past that
+      issue(t + 2);
+      issue(t + 3);
+    }
+    if (BN * t >= none_from) continue;    // above all of this wavefront's rows
+
+    const uint32_t buf = (uint32_t)(t & 2) * (uint32_t)G::BYTES;  // byte offset of the pair in `lds`
+    const unsigned char* kb = lds + buf + G::K_OFF + k_row_off;
+    const unsigned char* rb = lds + buf + G::R_OFF + r_row_off;
+    const unsigned char* vb = lds + buf + G::V_OFF + v_row_off;
+    auto read_k = [&](int u, int kk, int sb) -> u32x4_t {  // tile t + u: [k | k^R] rows 16 sb + l16, elements 32 kk + 8g ..
+      return kk < KD ? *reinterpret_cast<const u32x4_t*>(kb + u * G::BYTES + sb * (16 * VC * 16) + ((uint32_t)(64 * kk) ^ k_swz))
+                     : *reinterpret_cast<const u32x4_t*>(rb + u * G::BYTES + sb * (16 * RC * 16) + ((uint32_t)(64 * (kk - KD)) ^ r_swz));
+    };
+    auto read_v = [&](int u, int mt) -> u32x4_t {  // V^T rows 16 mt + l16 (dims), columns 8g .. (K index of the PV product)
+      const unsigned char* p = vb + u * G::BYTES + ((uint32_t)(32 * mt) ^ v_swz);
+      const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)p);
+      const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 16 * VC * 16));
+      const uint2 u0 = __builtin_bit_cast(uint2, v0), u1 = __builtin_bit_cast(uint2, v1);
+      return u32x4_t{u0.x, u0.y, u1.x, u1.y};
     };
 
-    // the first tiles travel while the rows are set up.  (Every wavefront is done with the buffers of the previous block, its
-    // rows on their way out included; no tile load is in flight: the last tile of a block waits for everything.)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    barrier_only();
+    // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one group of K
+    // steps are in flight while the group before is multiplied
+    float4_t sacc[2][2][2];  // [tile][row tile][16 columns]
+    constexpr int KG = 2, NG = 2 * KQ / KG;  // K steps per group, groups of both tiles
+    static_assert(KQ % KG == 0 || KQ % 2 == 1, "groups");
+    u32x4_t kf[2][KG][2];
+    auto read_group = [&](int i) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      if (n_tiles > 0) issue(t);
-
-    // ---- queries of this wavefront's 32 rows: B operand, lane = row l16 of row tile rt; the row's own column.
-    // They come in with four neighbouring lanes to 64 bytes of a row and change places through the wavefront's part of the buffers
-    // that the second pair of tiles will take: in the operand layout neighbouring lanes are 16 rows, which a unit's address path takes one
-    // lane a cycle (66 cycles a load, 10 thousand a block; now 2.5).  Stores likewise, see below.
-    u32x4_t qf[2][KQ];
-    float4_t neg_ref[2];        // - reference of the row's weights, where the logits' sums start
-    float l_run[2];
-    float4_t acc[2][MT];
-    int bound[2];               // columns open to the lane's rows
-    {
-      int ln = lane;
-      asm volatile("" : "+v"(ln));              // (what depends on it is formed here, not kept in registers over the tile loop)
-      const int qr = ln >> 2, qc = ln & 3;      // row and 16 bytes of the 64 that a load brings of it
-      u32x4_t qd[2][KQ], kd[2][KQ], vd[2][KD];
+      for (int j = 0; j < KG; ++j)
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        const int m = m0 + 32 * wv + 16 * rt + qr, mr = m < len ? m : len - 1;
-        const size_t row = (size_t)b * T + mr;
-        const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * qc;
-        const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * qc;
-        const uint32_t own = (uint32_t)(past + mr);
-        const uint16_t* kp = kx + own * kv_stride + 8 * qc;
-        const uint16_t* krp = kr16 + own * DR + 8 * qc;
-        const uint16_t* vp = vx + own * kv_stride + 8 * qc;
-#pragma unroll
-        for (int kk = 0; kk < KQ; ++kk) {
-          qd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
-          kd[rt][kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
+        for (int sb = 0; sb < 2; ++sb) {
+          const int x = i * KG + j;
+          kf[i & 1][j][sb] = read_k(x / KQ, x % KQ, sb);
         }
+    };
+    __builtin_amdgcn_s_setprio(1);  // the stretch of matrix instructions ahead of the other wavefront's arithmetic (1 - 2 %)
+    read_group(0);
 #pragma unroll
-        for (int kk = 0; kk < KD; ++kk) vd[rt][kk] = *reinterpret_cast<const u32x4_t*>(vp + 32 * kk);
-      }
-      unsigned char* own_lds = lds + 2 * G::BYTES + wv * kOwn;  // [query pieces | value pieces][row][64 bytes]
-      unsigned char* to = own_lds + qr * 64 + ((qc ^ swz_rows16<4>(qr)) << 4);
-      const unsigned char* from = own_lds + l16 * 64;
+    for (int i = 0; i < NG; ++i) {
+      if (i + 1 < NG) read_group(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        __builtin_amdgcn_sched_barrier(0);
-        const int m = m0 + 32 * wv + 16 * rt + l16;
-        bound[rt] = (p0 + (m < len ? m : len - 1)) / s;
-        float e = 0.f;
+      for (int j = 0; j < KG; ++j)
 #pragma unroll
-        for (int kk = 0; kk < KQ; ++kk) {
-          // logits come out in units of log2: log2(e) / sqrt(d_h) folded in
-          if (!LAYER) qd[rt][kk] = bf16x8_to_f16x8(qd[rt][kk], a.scale_log2);
-          e = dot8(kd[rt][kk], qd[rt][kk], e);
-          *reinterpret_cast<u32x4_t*>(to + 1024 * kk) = qd[rt][kk];
-        }
+        for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-        for (int kk = 0; kk < KD; ++kk) *reinterpret_cast<u32x4_t*>(to + 1024 * (KQ + kk)) = vd[rt][kk];
-        e = group_reduce<4>(e, LaneSum());
-        e = __int_as_float(__builtin_amdgcn_ds_bpermute(16 * l16, __float_as_int(e)));  // of row l16: lane 4 l16
-        neg_ref[rt] = float4_t{-e, -e, -e, -e};
-        l_run[rt] = g == 0 ? 1.f : 0.f;  // the four lanes of a row sum their own columns' weights
-#pragma unroll
-        for (int kk = 0; kk < KQ; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4_t*>(from + 1024 * kk + ((g ^ swz_rows16<4>(l16)) << 4));
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {  // dims 16 mt + 4g ..
-          const uint2 v = *reinterpret_cast<const uint2*>(from + 1024 * (KQ + (mt >> 1)) + (((2 * (mt & 1) + (g >> 1)) ^ swz_rows16<4>(l16)) << 4) + 8 * (g & 1));
-          acc[rt][mt] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
-        }
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the barrier behind which those buffers are filled
-    }
-    // columns open to all of the wavefront's rows, and to any of them
-    const int all_below = (p0 + m0 + 32 * wv) / s;
-    const int none_from = (p0 + m0 + 32 * wv + 31) / s;
-
-    // Two tiles per step: while one pair is multiplied the other is on its way (four buffers), one wait and one barrier for
-    // both, and the matrix products of one tile beside the softmax arithmetic of the other.
-    for (int t = 0; t < n_tiles; t += 2) {
-      wait_loads_but<0>();                  // the pair has landed: this wavefront's part, then everyone's
-      barrier_only();
-      if (t + 2 < n_tiles) {                // into the buffers the pair before was read from: every wavefront is past that
-        issue(t + 2);
-        issue(t + 3);
-      }
-      if (BN * t >= none_from) continue;    // above all of this wavefront's rows
-
-      const uint32_t buf = (uint32_t)(t & 2) * (uint32_t)G::BYTES;  // byte offset of the pair in `lds`
-      const unsigned char* kb = lds + buf + G::K_OFF + k_row_off;
-      const unsigned char* rb = lds + buf + G::R_OFF + r_row_off;
-      const unsigned char* vb = lds + buf + G::V_OFF + v_row_off;
-      auto read_k = [&](int u, int kk, int sb) -> u32x4_t {  // tile t + u: [k | k^R] rows 16 sb + l16, elements 32 kk + 8g ..
-        return kk < KD ? *reinterpret_cast<const u32x4_t*>(kb + u * G::BYTES + sb * (16 * VC * 16) + ((uint32_t)(64 * kk) ^ k_swz))
-                       : *reinterpret_cast<const u32x4_t*>(rb + u * G::BYTES + sb * (16 * RC * 16) + ((uint32_t)(64 * (kk - KD)) ^ r_swz));
-      };
-      auto read_v = [&](int u, int mt) -> u32x4_t {  // V^T rows 16 mt + l16 (dims), columns 8g .. (K index of the PV product)
-        const unsigned char* p = vb + u * G::BYTES + ((uint32_t)(32 * mt) ^ v_swz);
-        const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)p);
-        const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 16 * VC * 16));
-        const uint2 u0 = __builtin_bit_cast(uint2, v0), u1 = __builtin_bit_cast(uint2, v1);
-        return u32x4_t{u0.x, u0.y, u1.x, u1.y};
-      };
-
-      // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one group of K
-      // steps are in flight while the group before is multiplied
-      float4_t sacc[2][2][2];  // [tile][row tile][16 columns]
-      constexpr int KG = 2, NG = 2 * KQ / KG;  // K steps per group, groups of both tiles
-      static_assert(KQ % KG == 0 || KQ % 2 == 1, "groups");
-      u32x4_t kf[2][KG][2];
-      auto read_group = [&](int i) {
-#pragma unroll
-        for (int j = 0; j < KG; ++j)
-#pragma unroll
-          for (int sb = 0; sb < 2; ++sb) {
-            const int x = i * KG + j;
-            kf[i & 1][j][sb] = read_k(x / KQ, x % KQ, sb);
+          for (int rt = 0; rt < 2; ++rt) {
+            const int x = i * KG + j, u = x / KQ, kk = x % KQ;
+            sacc[u][rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kf[i & 1][j][sb]),
+                                                                     __builtin_bit_cast(f16x8_t, qf[rt][kk]),
+                                                                     kk == 0 ? neg_ref[rt] : sacc[u][rt][sb], 0, 0, 0);
           }
-      };
-      __builtin_amdgcn_s_setprio(1);  // the stretch of matrix instructions ahead of the other wavefront's arithmetic (1 - 2 %)
-      read_group(0);
+    }
+    constexpr int VPRE = MT / 2;
+    u32x4_t vf[MT];  // values of the tile whose product comes next
 #pragma unroll
-      for (int i = 0; i < NG; ++i) {
-        if (i + 1 < NG) read_group(i + 1);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(0, mt);
+    __builtin_amdgcn_sched_barrier(0);
+
+    __builtin_amdgcn_s_setprio(0);
+    // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
+    if (BN * t + 2 * BN > all_below) {  // wavefront-uniform: the last tiles only
 #pragma unroll
-        for (int j = 0; j < KG; ++j)
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+          const int d = bound[rt] - (BN * (t + u) + 4 * g);
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt) {
-              const int x = i * KG + j, u = x / KQ, kk = x % KQ;
-              sacc[u][rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kf[i & 1][j][sb]),
-                                                                       __builtin_bit_cast(f16x8_t, qf[rt][kk]),
-                                                                       kk == 0 ? neg_ref[rt] : sacc[u][rt][sb], 0, 0, 0);
-            }
-      }
-      constexpr int VPRE = MT / 2;
-      u32x4_t vf[MT];  // values of the tile whose product comes next
+            for (int v = 0; v < 4; ++v) sacc[u][rt][sb][v] = 16 * sb + v < d ? sacc[u][rt][sb][v] : -INFINITY;
+        }
+    }
+    // fixed reference per row (its own column's logit, re-based only when a tile tops it by more than 2^kRebase): no
+    // accumulator rescaling and no cross-lane traffic per tile.  Weights more than 2^-24 below the reference
+    // vanish in fp16; they are that much smaller than weights already summed.
+    constexpr float kRebase = 12.f;  // fp16 weights: 2^(s - reference) stays far below 65504
+    // Does any logit top it?  On the bit patterns: as integers the positive floats are in order and above all negative
+    // ones, and an integer maximum takes three operands without first quieting each.
+    int top = 0;
 #pragma unroll
-      for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(0, mt);
-      __builtin_amdgcn_sched_barrier(0);
-
-      __builtin_amdgcn_s_setprio(0);
-      // ---- softmax weights: lane holds row l16 of row tile rt and columns 16 sb + 4g + v
-      if (BN * t + 2 * BN > all_below) {  // wavefront-uniform: the last tiles only
+    for (int i = 0; i < 32; ++i) {
+      const float x = sacc[i >> 4][(i >> 3) & 1][(i >> 2) & 1][i & 3];
+      top = max(top, __float_as_int(x));
+    }
+    if (__any(top > __float_as_int(kRebase))) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+      for (int rt = 0; rt < 2; ++rt) {
+        float up = -INFINITY;
 #pragma unroll
-          for (int rt = 0; rt < 2; ++rt) {
-            const int d = bound[rt] - (BN * (t + u) + 4 * g);
+        for (int i = 0; i < 16; ++i) up = fmaxf(up, sacc[i >> 3][rt][(i >> 2) & 1][i & 3]);
+        up = quarter_reduce(up, LaneMax());
+        if (up > kRebase) {
+          const float alpha = __builtin_amdgcn_exp2f(-up);
+          neg_ref[rt] -= up;
+          l_run[rt] *= alpha;
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb)
+          for (int i = 0; i < 4; ++i) sacc[i >> 1][rt][i & 1] -= up;
 #pragma unroll
-              for (int v = 0; v < 4; ++v) sacc[u][rt][sb][v] = 16 * sb + v < d ? sacc[u][rt][sb][v] : -INFINITY;
-          }
-      }
-      // fixed reference per row (its own column's logit, re-based only when a tile tops it by more than 2^kRebase): no
-      // accumulator rescaling and no cross-lane traffic per tile.  Weights more than 2^-24 below the reference
-      // vanish in fp16; they are that much smaller than weights already summed.
-      constexpr float kRebase = 12.f;  // fp16 weights: 2^(s - reference) stays far below 65504
-      // Does any logit top it?  On the bit patterns: as integers the positive floats are in order and above all negative
-      // ones, and an integer maximum takes three operands without first quieting each.
-      int top = 0;
-#pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        const float x = sacc[i >> 4][(i >> 3) & 1][(i >> 2) & 1][i & 3];
-        top = max(top, __float_as_int(x));
-      }
-      if (__any(top > __float_as_int(kRebase))) {
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          float up = -INFINITY;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) up = fmaxf(up, sacc[i >> 3][rt][(i >> 2) & 1][i & 3]);
-          up = quarter_reduce(up, LaneMax());
-          if (up > kRebase) {
-            const float alpha = __builtin_amdgcn_exp2f(-up);
-            neg_ref[rt] -= up;
-            l_run[rt] *= alpha;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sacc[i >> 1][rt][i & 1] -= up;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[rt][mt] *= alpha;
-          }
+          for (int mt = 0; mt < MT; ++mt) acc[rt][mt] *= alpha;
         }
       }
-      const f16x2_t ones = {(_Float16)1.f, (_Float16)1.f};
-      auto weights = [&](int u, int rt) -> u32x4_t {  // B operand of the K = 32 PV product
-        // K index 8g + e of the tile: e < 4 -> column 4g + e of its first 16, else of its second 16
-        u32x4_t pb;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4_t& x = sacc[u][rt][i >> 1];
-          const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(x[2 * (i & 1)]), __builtin_amdgcn_exp2f(x[2 * (i & 1) + 1]));
-          pb[i] = two;
-          l_run[rt] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run[rt], false);  // the weights as they are used
-        }
-        return pb;
-      };
-      auto product = [&](int mt, const u32x4_t& v, const u32x4_t (&pb)[2]) {  // O^T[d, row] += V^T[d, col] P^T[col, row]
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-          acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, v), __builtin_bit_cast(f16x8_t, pb[rt]),
-                                                               acc[rt][mt], 0, 0, 0);
-      };
-      u32x4_t pb0[2], pb1[2];
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) pb0[rt] = weights(0, rt);
-#pragma unroll
-      for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(0, mt);
-      // the weights of the second tile beside the first tile's product
-      pb1[0] = weights(1, 0);
-#pragma unroll
-      for (int mt = 0; mt < VPRE; ++mt) product(mt, vf[mt], pb0);
-#pragma unroll
-      for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(1, mt);
-      pb1[1] = weights(1, 1);
-#pragma unroll
-      for (int mt = VPRE; mt < MT; ++mt) product(mt, vf[mt], pb0);
-#pragma unroll
-      for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(1, mt);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) product(mt, vf[mt], pb1);
     }
+    const f16x2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    auto weights = [&](int u, int rt) -> u32x4_t {  // B operand of the K = 32 PV product
+      // K index 8g + e of the tile: e < 4 -> column 4g + e of its first 16, else of its second 16
+      u32x4_t pb;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4_t& x = sacc[u][rt][i >> 1];
+        const uint32_t two = pack_f16x2(__builtin_amdgcn_exp2f(x[2 * (i & 1)]), __builtin_amdgcn_exp2f(x[2 * (i & 1) + 1]));
+        pb[i] = two;
+        l_run[rt] = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, two), ones, l_run[rt], false);  // the weights as they are used
+      }
+      return pb;
+    };
+    auto product = [&](int mt, const u32x4_t& v, const u32x4_t (&pb)[2]) {  // O^T[d, row] += V^T[d, col] P^T[col, row]
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+        acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, v), __builtin_bit_cast(f16x8_t, pb[rt]),
+                                                             acc[rt][mt], 0, 0, 0);
+    };
+    u32x4_t pb0[2], pb1[2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) pb0[rt] = weights(0, rt);
+#pragma unroll
+    for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(0, mt);
+    // the weights of the second tile beside the first tile's product
+    pb1[0] = weights(1, 0);
+#pragma unroll
+    for (int mt = 0; mt < VPRE; ++mt) product(mt, vf[mt], pb0);
+#pragma unroll
+    for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(1, mt);
+    pb1[1] = weights(1, 1);
+#pragma unroll
+    for (int mt = VPRE; mt < MT; ++mt) product(mt, vf[mt], pb0);
+#pragma unroll
+    for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(1, mt);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) product(mt, vf[mt], pb1);
+  }
 
-    // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3.  The rows leave through LDS, whole
-    // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path), in the wavefront's part of the pair
-    // of buffers that the last step did not read: every wavefront is past the step before it.
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    unsigned char* leave = lds + (n_tiles > 0 ? (~(n_tiles - 1) & 2) : 0) * G::BYTES + wv * kOwn;
+  // ---- normalise and store: lane holds row l16 of row tile rt, output dims 16 mt + 4g .. +3.  The rows leave through LDS, whole
+  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path), in the wavefront's part of the pair
+  // of buffers that the last step did not read: every wavefront is past the step before it.
+  int ln = lane;
+  asm volatile("" : "+v"(ln));
+  unsigned char* leave = lds + (n_tiles > 0 ? (~(n_tiles - 1) & 2) : 0) * G::BYTES + wv * kOwn;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      constexpr int ES = LAYER ? 2 : 4, RB = DH * ES, PPR = RB / 16;  // bytes of a row, 16-byte pieces; piece j of row i sits at j ^ (i % 16), in RB
-      static_assert(16 * RB <= kOwn && PPR >= 8, "the rows fit");
-      const float l = quarter_reduce(l_run[rt], LaneSum());
-      const int mt0 = m0 + 32 * wv + 16 * rt;
-      const bool live = mt0 + (ln & 15) < len;  // rows past the sequence's length are zeros, whatever their inputs held
-      const float inv = live ? 1.f / l : 0.f;
-      constexpr int SW = PPR < 16 ? PPR - 1 : 15;
+  for (int rt = 0; rt < 2; ++rt) {
+    constexpr int ES = LAYER ? 2 : 4, RB = DH * ES, PPR = RB / 16;  // bytes of a row, 16-byte pieces; piece j of row i sits at j ^ (i % 16), in RB
+    static_assert(16 * RB <= kOwn && PPR >= 8, "the rows fit");
+    const float l = quarter_reduce(l_run[rt], LaneSum());
+    const int mt0 = m0 + 32 * wv + 16 * rt;
+    const bool live = mt0 + (ln & 15) < len;  // rows past the sequence's length are zeros, whatever their inputs held
+    const float inv = live ? 1.f / l : 0.f;
+    constexpr int SW = PPR < 16 ? PPR - 1 : 15;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const float4_t o = live ? acc[rt][mt] * inv : float4_t{0.f, 0.f, 0.f, 0.f};
-        if constexpr (LAYER)
-          *reinterpret_cast<uint2*>(leave + (ln & 15) * RB + (((2 * mt + ((ln >> 5) & 1)) ^ (ln & SW)) << 4) + 8 * ((ln >> 4) & 1)) = make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
-        else
-          *reinterpret_cast<float4_t*>(leave + (ln & 15) * RB + (((4 * mt + (ln >> 4)) ^ (ln & SW)) << 4)) = o;
-      }
-      unsigned char* out_rows = LAYER ? reinterpret_cast<unsigned char*>(a.out16) + (((size_t)b * T + mt0) * nh + h) * RB
-                                      : reinterpret_cast<unsigned char*>(out) + (size_t)mt0 * out_stride * 4;
-#pragma unroll
-      for (int i = 0; i < 16 * PPR / 64; ++i) {
-        const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(leave + row * RB + ((c ^ (row & SW)) << 4));
-        if (mt0 + row < T) *reinterpret_cast<u32x4_t*>(out_rows + (size_t)row * out_stride * ES + 16 * c) = v;
-      }
+    for (int mt = 0; mt < MT; ++mt) {
+      const float4_t o = live ? acc[rt][mt] * inv : float4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (LAYER)
+        *reinterpret_cast<uint2*>(leave + (ln & 15) * RB + (((2 * mt + ((ln >> 5) & 1)) ^ (ln & SW)) << 4) + 8 * ((ln >> 4) & 1)) = make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
+      else
+        *reinterpret_cast<float4_t*>(leave + (ln & 15) * RB + (((4 * mt + (ln >> 4)) ^ (ln & SW)) << 4)) = o;
     }
-  }  // pass
+    unsigned char* out_rows = LAYER ? reinterpret_cast<unsigned char*>(a.out16) + (((size_t)b * T + mt0) * nh + h) * RB
+                                    : reinterpret_cast<unsigned char*>(out) + (size_t)mt0 * out_stride * 4;
+#pragma unroll
+    for (int i = 0; i < 16 * PPR / 64; ++i) {
+      const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(leave + row * RB + ((c ^ (row & SW)) << 4));
+      if (mt0 + row < T) *reinterpret_cast<u32x4_t*>(out_rows + (size_t)row * out_stride * ES + 16 * c) = v;
+    }
+  }
 }
 
 template <int DH, int DR>
 hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
   constexpr int NW = 4;
-  const int n_blocks = (a.T + 32 * NW - 1) / (32 * NW);
-  // Two row blocks per workgroup, unless that leaves the chip (two workgroups on each of 256 units) partly empty: then a
-  // block each, which the units run side by side.
+  static_assert(32 * NW == kAttnRows, "rows of a block");
+  const int n_blocks = (a.T + kAttnRows - 1) / kAttnRows, pairs = a.n_heads * a.batch;
   ExplicitArgs x = a;
-  x.unpaired = (size_t)((n_blocks + 1) / 2) * a.n_heads * a.batch < 512;
-  const dim3 grid((unsigned)(x.unpaired ? n_blocks : (n_blocks + 1) / 2) * ((a.n_heads * a.batch + 7) / 8 * 8));
+  x.group = attn_group(pairs, DH);
+  const dim3 grid((unsigned)n_blocks * (unsigned)(attn_pairs(pairs) * kXcds));
   const bool layer = a.q_f16 != 0;  // comes with out16
   if (layer != (a.out16 != nullptr) || (layer && !a.pos0)) return hipErrorInvalidValue;
   if (layer) launch_timed(attn_explicit_kernel<DH, DR, NW, true, true>, grid, dim3(64 * NW), 0, st, ev, x);
