@@ -43,6 +43,7 @@
 //             ragged batches keep every compute unit streaming until the end; a
 //             workgroup emits one partial per sequence its range touches.
 #include "bounds.h"
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -51,9 +52,6 @@ namespace mtla {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef short4_t __attribute__((address_space(3))) * lds_short4_ptr;
 
 constexpr int kWaves = kBlock / kWave;
 constexpr int kTile = 16;  // slots per wavefront tile
@@ -447,41 +445,49 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// static schedule, short chunks, up to 16 heads: one workgroup per (chunk, sequence) takes 64 slots a step, each wavefront
-// the logits of its own 16 and then the value product of a quarter of the latent columns over all 64.
-// A decode step at small batch is a chain of latencies, not of bytes: with each wavefront taking its slots through both
-// contractions (attn_mfma_kernel) the four results had to be merged through LDS, 1.1 us behind 1.2 us of contractions.
-// Here the rows and weights meet in LDS and every wavefront ends up with finished columns.  Two barriers a step: one behind
-// the wavefronts' maxima (all weights are taken relative to one reference per head), one behind the weights and rows.
-// 16 sequences x 512 slots, 8 heads, r = 256: 5.9 us, now 5.1.
+// static schedule, short chunks: one workgroup per (chunk, sequence) takes 64 slots a step.  With one head tile a wavefront forms the
+// logits of its own 16 slots, with two those of 32 slots and one head tile; then every wavefront takes the value product of a quarter of
+// the latent columns over all 64.  A decode step at small batch is a chain of latencies, not of bytes: with each wavefront taking its
+// slots through both contractions the four results had to be merged through LDS, 1.1 us behind 1.2 us of contractions.
+// Two barriers a step: one behind the wavefronts' maxima (all weights are taken relative to one reference per head), one behind the weights.
+// Rows and query come memory -> LDS, four neighbouring lanes to 64 bytes of a row, and the sums leave through LDS in whole lines: straight to
+// and from the operand layouts the address path of the unit takes a load or store one lane a cycle, 66 cycles each, and each wavefront fetched the
+// query for itself.  us a step: 31 sequences of 640 slots, 20 heads x 128, r = 512 38.0, now 30.5; 7 of 700, 32 heads (whole layer) 52.3 and 38.0; 16
+// of 750, 16 heads, r = 512 24.3 and 20.4; 79 of 195, 16 heads x 64, r = 256 19.3 and 17.6.
 // ---------------------------------------------------------------------------
-template <class C>
-struct SplitLds {
-  static constexpr size_t rows = (size_t)kWaves * kTile * C::TS * 2;
-  static constexpr size_t weights = (size_t)kWaves * kWave * 8;
-  static constexpr size_t bytes = rows + weights + (size_t)2 * kWaves * 16 * 4;
+template <int R, int DR, int NHT>
+struct SplitGeom {
+  static constexpr int KC = R / 32, KT = (R + DR) / 32, HP = 16 * NHT, MW = R / 16 / kWaves;
+  static constexpr int TILE = KT * 1024;                              // 16 slots: [K step][slot][64 bytes], pieces swizzled
+  static constexpr int ROWS = kWaves * TILE, Q = NHT * 2 * KT * 1024;  // query: [head tile][plane][K step][head][64 bytes]
+  static constexpr int OUT = HP * R * 4;                              // the sums on their way out, in place of the rows
+  static constexpr int BODY = ROWS > OUT ? ROWS : OUT;
+  static constexpr int WEIGHTS = kWaves * NHT * kWave * 8;
+  static constexpr int BYTES = BODY + Q + WEIGHTS + 2 * kWaves * HP * 4;
+  static constexpr int PER_CU = 2 * BYTES <= 160 * 1024 ? 2 : 1;
+  static_assert(BYTES <= 160 * 1024, "LDS budget of one compute unit");
 };
 
-template <int R, int DR, bool SH, bool PG>
-__global__ __launch_bounds__(kBlock) void attn_split_kernel(AttnArgs a) {
-  using C = MfmaCfg<R, DR, 1>;
-  constexpr int MW = C::MT / kWaves;  // output column tiles of one wavefront
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  uint16_t* sT = reinterpret_cast<uint16_t*>(smem);
-  uint2* sP = reinterpret_cast<uint2*>(smem + SplitLds<C>::rows);  // [wavefront][lane]: weights of slots 4g .. 4g + 3, head l16
-  float* sM = reinterpret_cast<float*>(smem + SplitLds<C>::rows + SplitLds<C>::weights);  // [kWaves][16]
-  float* sL = sM + kWaves * 16;
+template <int R, int DR, int NHT, bool SH, bool PG>
+__global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_split_kernel(AttnArgs a) {
+  using G = SplitGeom<R, DR, NHT>;
+  constexpr int KC = G::KC, KT = G::KT, E = R + DR, HP = G::HP, MW = G::MW;
+  constexpr int GROUPS = kWaves / NHT;  // of wavefronts that share a head tile's slots
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  unsigned char* sQ = smem + G::BODY;
+  uint2* sP = reinterpret_cast<uint2*>(sQ + G::Q);  // [slot tile][head tile][lane]: weights of slots 4g .. 4g + 3, head l16
+  float* sM = reinterpret_cast<float*>(sQ + G::Q + G::WEIGHTS);  // [group][HP]
+  float* sL = sM + kWaves * HP;
 
   const int split = blockIdx.x, b = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int k0 = split * a.chunk;
   const uint16_t* lat = reinterpret_cast<const uint16_t*>(a.lat) + (PG ? 0 : (size_t)b * a.max_slots * R);
   const uint16_t* key = reinterpret_cast<const uint16_t*>(a.key) + (PG ? 0 : (size_t)b * a.max_slots * DR);
-  const PageRow pr{PG ? a.pages.table + (size_t)b * a.pages.max_pages : nullptr, a.pages.shift, a.pages.n_pages};
 
-  // length, query and first tile are requested together, as in attn_mfma_kernel
-  const int len = a.seq_len[b];
+  // length, first rows and query are requested together, as in attn_mfma_kernel
   SharedPrefix sp{0, 0, 0};
   if constexpr (SH) {
     int owner = a.prefix_owner[b], n = a.prefix_slots[b];
@@ -490,99 +496,190 @@ __global__ __launch_bounds__(kBlock) void attn_split_kernel(AttnArgs a) {
     sp.dlat = (long long)(owner - b) * a.max_slots * R;
     sp.dkey = (long long)(owner - b) * a.max_slots * DR;
   }
-  const Cols cm{C::kStep, 0, 0, 0};
-  int base = k0 + wv * kTile;
-  TileRegs<C> t;
-  load_tile<C, SH, PG>(t, lat, key, base, a.max_slots - 1, l16, g, cm, sp, pr);
-  QueryRegs<C, false> q;
-  query_request<C, false>(q, reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * C::E, a.q_plane, a.n_heads, 0,
-                          tid, l16, g);
-  const int live = live_slots(len, a.stride, a.max_slots);
-  const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
-  if (k0 >= k1) return;
-  t.select_live(base + l16 < k1);  // the first tile may have touched rows that were never written
-
-  float m_ref = -INFINITY, l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
-  float4_t acc[MW];
+  const int len = load_uniform_i32(a.seq_len, b);  // nothing writes it while the kernel runs
+  const int in_row = lane >> 2, piece = (lane & 3) ^ swz_rows16<4>(in_row);  // what a lane brings in: 16 bytes of that row's 64
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
+  // the wavefront's 16 slots from `base` on; slots past `last` become copies of that one
+  auto issue_rows = [&](int base, int last) {
+    const uint32_t to = lds0 + (uint32_t)(wv * G::TILE);
+    const int s0 = base < last ? base : last, slot = base + in_row < last ? base + in_row : last;
+    if constexpr (SH) {
+      const uint16_t* lr = lat + (size_t)slot * R + 8 * piece + (slot < sp.n ? sp.dlat : 0);
+      const uint16_t* kr = key + (size_t)slot * DR + 8 * piece + (slot < sp.n ? sp.dkey : 0);
 #pragma unroll
-  for (int mt = 0; mt < MW; ++mt) acc[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
-  uint16_t* row = sT + (wv * kTile + l16) * C::TS + 8 * g;
-  const uint16_t* trow = sT + (4 * g + (l16 >> 2)) * C::TS + wv * (R / kWaves) + 4 * (l16 & 3);
-
-  for (int s0 = k0; s0 < k1; s0 += C::kStep, base += C::kStep) {
-    // ---- logits S^T[slot, head] of the wavefront's tile (log2 units), one chain per query plane
-    float4_t sh = {0.f, 0.f, 0.f, 0.f}, sl = {0.f, 0.f, 0.f, 0.f};
+      for (int kk = 0; kk < KT; ++kk) load_to_lds_16(kk < KC ? lr + 32 * kk : kr + 32 * (kk - KC), to + 1024u * kk);
+    } else {
+      size_t row = (size_t)s0;
+      if constexpr (PG) {  // a page holds whole 16-slot tiles
+        int pg = load_uniform_i32(a.pages.table + (size_t)b * a.pages.max_pages, s0 >> a.pages.shift);
+        pg = pg < 0 ? 0 : (pg < a.pages.n_pages ? pg : a.pages.n_pages - 1);
+        row = ((size_t)pg << a.pages.shift) + (size_t)(s0 & ((1 << a.pages.shift) - 1));
+      }
+      const uint32_t i = (uint32_t)(slot - s0), at_lat = i * (R * 2) + 16 * piece, at_key = i * (DR * 2) + 16 * piece;
 #pragma unroll
-    for (int kk = 0; kk < C::KT; ++kk) {
-      const bf16x8_t x = __builtin_bit_cast(bf16x8_t, kk < C::KC ? t.xc[kk < C::KC ? kk : 0] : t.xr[kk < C::KC ? 0 : kk - C::KC]);
-      sh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, q.r[kk]), sh, 0, 0, 0);
-      sl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, q.r[C::KT + kk]), sl, 0, 0, 0);
-    }
-    float sv[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sv[v] = (base + 4 * g + v < k1) ? sh[v] + sl[v] : -INFINITY;
-    const float mloc = quarter_reduce(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), LaneMax());
-    if (g == 0) sM[wv * 16 + l16] = mloc;
-    __syncthreads();  // the maxima are there, and nobody still reads the rows and weights of the step before
-    // ---- rows out, the next step's in
-#pragma unroll
-    for (int kk = 0; kk < C::KC; ++kk) *reinterpret_cast<uint4*>(row + 32 * kk) = t.xc[kk];
-    if (s0 + C::kStep < k1) load_tile<C, SH, PG>(t, lat, key, base + C::kStep, k1 - 1, l16, g, cm, sp, pr);
-    // ---- reference (fixed at the first step, moved when a step tops it by 2^40), weights as bf16
-    float top = sM[l16];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) top = fmaxf(top, sM[w * 16 + l16]);
-    constexpr float kRebase = 40.f;
-    if (__any(top - m_ref > kRebase)) {  // the same decision in every wavefront; true at the first step (m_ref = -inf)
-      if (top - m_ref > kRebase) {
-        const float alpha = __builtin_amdgcn_exp2f(m_ref - top);
-        m_ref = top;
-        l_run *= alpha;
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt) acc[mt] *= alpha;
+      for (int kk = 0; kk < KT; ++kk) {
+        if (kk < KC) load_to_lds_16(lat + row * R + 32 * kk, at_lat, to + 1024u * kk);
+        else load_to_lds_16(key + row * DR + 32 * (kk - KC), at_key, to + 1024u * kk);
       }
     }
-    float pw[4];
+  };
+  issue_rows(k0 + wv * kTile, a.max_slots - 1);
+  {
+    const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * E;
+    uint32_t at_q[NHT];  // heads past the last one: copies of it, never stored
 #pragma unroll
-    for (int v = 0; v < 4; ++v) pw[v] = __builtin_amdgcn_exp2f(sv[v] - m_ref);
-    const uint32_t p01 = pack_bf16x2(pw[0], pw[1]), p23 = pack_bf16x2(pw[2], pw[3]);
-    sP[wv * kWave + lane] = make_uint2(p01, p23);
-    l_run += (__uint_as_float(p01 << 16) + __uint_as_float(p01 & 0xffff0000u)) +
-             (__uint_as_float(p23 << 16) + __uint_as_float(p23 & 0xffff0000u));
-    if (s0 + C::kStep >= k1) {  // last step: the wavefront's share of the normaliser
+    for (int ht = 0; ht < NHT; ++ht) {
+      const int h = 16 * ht + in_row < a.n_heads ? 16 * ht + in_row : a.n_heads - 1;
+      at_q[ht] = (uint32_t)(h * E * 2 + 16 * piece);
+    }
+    constexpr int PER = (2 * KT + kWaves - 1) / kWaves;  // a wavefront's share of a head tile's pieces
+#pragma unroll
+    for (int ht = 0; ht < NHT; ++ht)
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int c = wv + kWaves * i < 2 * KT ? wv + kWaves * i : 2 * KT - 1;  // (a few twice)
+        const int plane = c >= KT ? 1 : 0, kk = c - plane * KT;
+        load_to_lds_16(q + (plane ? a.q_plane : 0) + 32 * kk, at_q[ht], lds0 + (uint32_t)(G::BODY + (ht * 2 * KT + c) * 1024));
+      }
+  }
+  const int live = live_slots(len, a.stride, a.max_slots);
+  const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
+
+  const int hq = NHT == 2 ? wv & 1 : 0, grp = NHT == 2 ? wv >> 1 : wv;  // head tile and slot tiles NHT grp .. of the wavefront's logits
+  float m_ref[NHT], l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
+  float4_t acc[NHT][MW];
+#pragma unroll
+  for (int ht = 0; ht < NHT; ++ht) {
+    m_ref[ht] = -INFINITY;
+#pragma unroll
+    for (int mt = 0; mt < MW; ++mt) acc[ht][mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  const uint32_t frag = (uint32_t)(l16 * 64 + ((g ^ swz_rows16<4>(l16)) << 4));
+  const int vrow = 4 * g + (l16 >> 2);  // row of the lane's transposing reads
+
+  wait_loads_but<0>();
+  if (k0 >= k1) return;  // (nothing of this workgroup is on its way into LDS any more)
+  for (int s0 = k0; s0 < k1; s0 += kWaves * kTile) {
+    if (s0 > k0) {  // (chunks of more than 64 slots: set by the caller)
+      __syncthreads();
+      issue_rows(s0 + wv * kTile, k1 - 1);
+      wait_loads_but<0>();
+    } else if (k1 < s0 + (wv + 1) * kTile) {
+      // rows of the first step that no slot stands for may never have been written: zeros, or 0 x NaN would reach the sums
+      if (s0 + wv * kTile + in_row >= k1)
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) *reinterpret_cast<u32x4_t*>(smem + wv * G::TILE + 1024 * kk + 16 * lane) = u32x4_t{0u, 0u, 0u, 0u};
+    }
+    __syncthreads();  // rows and query are there
+    // ---- logits S^T[slot, head] (log2 units), one chain per query plane
+    float4_t sh[NHT], sl[NHT];
+#pragma unroll
+    for (int u = 0; u < NHT; ++u) sh[u] = sl[u] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* xr = smem + NHT * grp * G::TILE + frag;
+    const unsigned char* qr = sQ + hq * (2 * KT * 1024) + frag;
+#pragma unroll
+    for (int kk = 0; kk < KT; ++kk) {
+      const u32x4_t qh = *reinterpret_cast<const u32x4_t*>(qr + 1024 * kk), ql = *reinterpret_cast<const u32x4_t*>(qr + 1024 * (KT + kk));
+#pragma unroll
+      for (int u = 0; u < NHT; ++u) {
+        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(xr + u * G::TILE + 1024 * kk));
+        sh[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, qh), sh[u], 0, 0, 0);
+        sl[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, ql), sl[u], 0, 0, 0);
+      }
+    }
+    float sv[NHT][4], mloc = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < NHT; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        sv[u][v] = (s0 + (NHT * grp + u) * kTile + 4 * g + v < k1) ? sh[u][v] + sl[u][v] : -INFINITY;
+        mloc = fmaxf(mloc, sv[u][v]);
+      }
+    mloc = quarter_reduce(mloc, LaneMax());
+    if (g == 0) sM[grp * HP + 16 * hq + l16] = mloc;
+    __syncthreads();
+    // ---- reference (fixed at the first step, moved when a step tops it by 2^40), weights as bf16
+    constexpr float kRebase = 40.f;
+#pragma unroll
+    for (int ht = 0; ht < NHT; ++ht) {
+      float top = sM[16 * ht + l16];
+#pragma unroll
+      for (int w = 1; w < GROUPS; ++w) top = fmaxf(top, sM[w * HP + 16 * ht + l16]);
+      if (__any(top - m_ref[ht] > kRebase)) {  // the same decision in every wavefront; true at the first step (m_ref = -inf)
+        if (top - m_ref[ht] > kRebase) {
+          const float alpha = __builtin_amdgcn_exp2f(m_ref[ht] - top);
+          m_ref[ht] = top;
+          if (ht == hq) l_run *= alpha;
+#pragma unroll
+          for (int mt = 0; mt < MW; ++mt) acc[ht][mt] *= alpha;
+        }
+      }
+    }
+    const float ref = NHT == 2 && hq == 1 ? m_ref[NHT - 1] : m_ref[0];
+#pragma unroll
+    for (int u = 0; u < NHT; ++u) {
+      float pw[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) pw[v] = __builtin_amdgcn_exp2f(sv[u][v] - ref);
+      const uint32_t p01 = pack_bf16x2(pw[0], pw[1]), p23 = pack_bf16x2(pw[2], pw[3]);
+      sP[((NHT * grp + u) * NHT + hq) * kWave + lane] = make_uint2(p01, p23);
+      l_run += (__uint_as_float(p01 << 16) + __uint_as_float(p01 & 0xffff0000u)) +
+               (__uint_as_float(p23 << 16) + __uint_as_float(p23 & 0xffff0000u));
+    }
+    if (s0 + kWaves * kTile >= k1) {  // last step: the wavefront's share of the normaliser
       const float l = quarter_reduce(l_run, LaneSum());
-      if (g == 0) sL[wv * 16 + l16] = l;
+      if (g == 0) sL[grp * HP + 16 * hq + l16] = l;
     }
     __syncthreads();
     // ---- O^T[col, head] += C_hat^T[col, slot] P^T[slot, head]: a lane's eight slots of a K step are 4g .. + 3 of two tiles
 #pragma unroll
     for (int k = 0; k < kWaves / 2; ++k) {
-      const uint2 u0 = sP[(2 * k) * kWave + lane], u1 = sP[(2 * k + 1) * kWave + lane];
-      const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, make_uint4(u0.x, u0.y, u1.x, u1.y));
+      bf16x8_t pb[NHT];
 #pragma unroll
-      for (int mt = 0; mt < MW; ++mt) {
-        const uint16_t* src = trow + (32 * k) * C::TS + 16 * mt;
+      for (int ht = 0; ht < NHT; ++ht) {
+        const uint2 u0 = sP[((2 * k) * NHT + ht) * kWave + lane], u1 = sP[((2 * k + 1) * NHT + ht) * kWave + lane];
+        pb[ht] = __builtin_bit_cast(bf16x8_t, make_uint4(u0.x, u0.y, u1.x, u1.y));
+      }
+#pragma unroll
+      for (int mt = 0; mt < MW; ++mt) {  // latent columns 16 (MW wv + mt) ..: half of a K step's 32
+        const int ct = MW * wv + mt;
+        const unsigned char* src = smem + 2 * k * G::TILE + 1024 * (ct >> 1) + vrow * 64 + 8 * (l16 & 1) +
+                                   (((2 * (ct & 1) + ((l16 & 3) >> 1)) ^ swz_rows16<4>(vrow)) << 4);
         const short4_t c0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
-        const short4_t c1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + 16 * C::TS));
+        const short4_t c1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + G::TILE));
         const uint2 a0 = __builtin_bit_cast(uint2, c0), a1 = __builtin_bit_cast(uint2, c1);
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(a0.x, a0.y, a1.x, a1.y)), pb,
-                                                          acc[mt], 0, 0, 0);
+        const bf16x8_t ct8 = __builtin_bit_cast(bf16x8_t, make_uint4(a0.x, a0.y, a1.x, a1.y));
+#pragma unroll
+        for (int ht = 0; ht < NHT; ++ht) acc[ht][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct8, pb[ht], acc[ht][mt], 0, 0, 0);
       }
     }
   }
 
-  if (l16 < a.n_heads) {  // lane holds head l16, columns 16 mt + 4g .. + 3 of its quarter
-    const size_t ph = ((size_t)b * a.n_splits + split) * a.n_heads + l16;
-    float* po = a.part_o + ph * R + wv * (R / kWaves) + 4 * g;
+  // ---- the partial of all heads, one run of memory: lane holds head 16 ht + l16, columns 16 mt + 4g .. + 3 of its quarter; piece j (16
+  // bytes) of head i sits at j ^ (i % 16)
+  __syncthreads();  // the rows have been read
 #pragma unroll
-    for (int mt = 0; mt < MW; ++mt) *reinterpret_cast<float4_t*>(po + 16 * mt) = acc[mt];
-    if (wv == 0 && g == 0) {
-      float l = sL[l16];
+  for (int ht = 0; ht < NHT; ++ht)
 #pragma unroll
-      for (int w = 1; w < kWaves; ++w) l += sL[w * 16 + l16];
-      a.part_ml[ph * 2 + 0] = m_ref;
-      a.part_ml[ph * 2 + 1] = l;
-    }
+    for (int mt = 0; mt < MW; ++mt)
+      *reinterpret_cast<float4_t*>(smem + (16 * ht + l16) * (R * 4) + (((4 * (MW * wv + mt) + g) ^ l16) << 4)) = acc[ht][mt];
+  __syncthreads();
+  const size_t ph = ((size_t)b * a.n_splits + split) * a.n_heads;
+  float* po = a.part_o + ph * R;
+  for (int at = tid; at < a.n_heads * (R / 4); at += kBlock) {
+    const int h = at / (R / 4), j = at % (R / 4);
+    *reinterpret_cast<float4_t*>(po + 4 * (size_t)at) = *reinterpret_cast<const float4_t*>(smem + h * (R * 4) + ((j ^ (h & 15)) << 4));
+  }
+  if (tid < a.n_heads) {
+    float l = sL[tid];
+#pragma unroll
+    for (int w = 1; w < GROUPS; ++w) l += sL[w * HP + tid];
+    a.part_ml[(ph + tid) * 2 + 1] = l;
+  }
+  if (wv == 0 && g == 0) {
+#pragma unroll
+    for (int ht = 0; ht < NHT; ++ht)
+      if (16 * ht + l16 < a.n_heads) a.part_ml[(ph + 16 * ht + l16) * 2] = m_ref[ht];
   }
 }
 
@@ -803,13 +900,13 @@ hipError_t launch_rows(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   return hipGetLastError();
 }
 
-template <int R, int DR, bool SH, bool PG>
+template <int R, int DR, int NHT, bool SH, bool PG>
 hipError_t launch_split(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
-  constexpr size_t smem = SplitLds<MfmaCfg<R, DR, 1>>::bytes;
+  constexpr size_t smem = SplitGeom<R, DR, NHT>::BYTES;
   static DeviceSet lds_allowed;
-  const hipError_t e = allow_lds(&attn_split_kernel<R, DR, SH, PG>, smem, lds_allowed);
+  const hipError_t e = allow_lds(&attn_split_kernel<R, DR, NHT, SH, PG>, smem, lds_allowed);
   if (e != hipSuccess) return e;
-  launch_timed(attn_split_kernel<R, DR, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
+  launch_timed(attn_split_kernel<R, DR, NHT, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
   return hipGetLastError();
 }
 
@@ -846,8 +943,7 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
                         : launch_static<R, DR, NHT, NS, QL, false, false>(a, st, ev);
 }
 
-// Pipeline depth: a wavefront that will see only a tile or two (decode at small batch) gets the
-// short single-stage code with the query in registers (up to 16 heads: attn_split_kernel); long runs keep several tiles in flight
+// Pipeline depth: a workgroup that will see only a step or two (decode at small batch) is attn_split_kernel's; long runs keep several tiles in flight
 // per wavefront, which is what it takes to cover HBM latency with four wavefronts per compute
 // unit.
 template <int R, int DR>
@@ -857,12 +953,13 @@ hipError_t launch_rd(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   const int nht = a.n_heads <= 16 ? 1 : 2;
   const int tiles_per_wave = a.chunk / (kTile * (kWaves / nht));
   const bool deep = a.n_persistent > 0 || tiles_per_wave >= 2 * kDeep;
-  if (nht == 1) {
-    if (deep) return launch_one<R, DR, 1, kDeep, kDeepQL>(a, st, ev);
-    if (a.pages.table) return a.prefix_owner ? hipErrorInvalidValue : launch_split<R, DR, false, true>(a, st, ev);
-    return a.prefix_owner ? launch_split<R, DR, true, false>(a, st, ev) : launch_split<R, DR, false, false>(a, st, ev);
+  if (deep) return nht == 1 ? launch_one<R, DR, 1, kDeep, kDeepQL>(a, st, ev) : launch_one<R, DR, 2, kDeep, kDeepQL>(a, st, ev);
+  if (a.pages.table) {
+    if (a.prefix_owner) return hipErrorInvalidValue;
+    return nht == 1 ? launch_split<R, DR, 1, false, true>(a, st, ev) : launch_split<R, DR, 2, false, true>(a, st, ev);
   }
-  return deep ? launch_one<R, DR, 2, kDeep, kDeepQL>(a, st, ev) : launch_one<R, DR, 2, 1, false>(a, st, ev);
+  if (a.prefix_owner) return nht == 1 ? launch_split<R, DR, 1, true, false>(a, st, ev) : launch_split<R, DR, 2, true, false>(a, st, ev);
+  return nht == 1 ? launch_split<R, DR, 1, false, false>(a, st, ev) : launch_split<R, DR, 2, false, false>(a, st, ev);
 }
 
 template <int R, int DR>

@@ -20,6 +20,16 @@ def test_slots_around_tiles_and_steps(n_heads, r, d_rope, chunk):
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=chunk, decode_schedule=1)
 
 
+@pytest.mark.parametrize("n_heads,r,d_rope,chunk", [(17, 64, 32, 64), (32, 128, 64, 96), (24, 256, 32, 160), (31, 256, 64, 32),
+                                                    (32, 512, 64, 64), (20, 512, 32, 96)])
+def test_two_head_tiles(n_heads, r, d_rope, chunk):
+    # more than sixteen heads: a wavefront's logits are those of one head tile and two of a step's four slot tiles
+    plen = np.array([1, 15, 17, 32, 33, 48, 63, 64, 65, 97, 161, 200], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name=f"split2_{r}_{chunk}", batch=len(plen), d_model=96, n_heads=n_heads, d_head=64, r=r,
+                                           d_rope=d_rope, stride=1, prefix=(1, 200), steps=2, seed=60 + r + chunk)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=chunk, decode_schedule=1)
+
+
 def test_more_pieces_than_one_round_of_the_merge():
     # 29 pieces a row, dealt to the wavefronts of the combine's one-row form; rows with none, one and a few of them
     plen = np.array([1, 33, 130, 900], np.int32)
