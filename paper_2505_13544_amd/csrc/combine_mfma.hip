@@ -28,7 +28,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTileRows = 16;
-constexpr int kWaves = kBlock / kWave;
 
 struct Pieces {
   int first, count;
@@ -78,14 +77,15 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
 // a row is then merged by a whole wavefront and the tile's other columns are copies nobody stores.
 // PF16 = the partials are normalised IEEE-half rows (o_p / l_p) from the column-split decode kernel:
 // a piece then weighs l_p 2^(m_p - m*) instead of 2^(m_p - m*).
-// PS = few rows, their pieces split over the wavefronts: one row per workgroup (RPT = 1), the weighted sums added through
-// LDS.  One round of requests instead of one per PB pieces, and four times the
+// PS = few rows, their pieces split over the wavefronts (at r = 128 and 64 over halves and quarters of them: a lane takes four
+// columns): one row per workgroup (RPT = 1), the weighted sums added through LDS.  One round of requests instead of one per PB pieces, and four times the
 // workgroups, each with a quarter of the partials to bring in and to add up.
 // HF = the head is the fast grid index: the workgroups that share an XCD (and its L2) then share the
 // W_V^(h) of a few heads instead of each XCD fetching all of them.
 template <int R, int DH, int RPT, bool PS>
-struct CombineLds {  // [W_V^(h)][hi and lo planes of the rows][piece split: the other wavefronts' sums]
-  static constexpr int planes = DH * R * 2, red = planes + 2 * RPT * R * 2, bytes = red + (PS ? (kWaves - 1) * R * 4 : 0);
+struct CombineLds {  // [W_V^(h)][hi and lo planes of the rows][piece split: the other groups' sums]
+  static constexpr int TPR = !PS ? kBlock / RPT : (R / 4 < kWave ? R / 4 : kWave), groups = PS ? kBlock / TPR : 1;  // threads merging one row
+  static constexpr int planes = DH * R * 2, red = planes + 2 * RPT * R * 2, bytes = red + (groups - 1) * R * 4;
   static_assert(bytes <= 160 * 1024, "LDS of one compute unit");
 };
 
@@ -95,7 +95,8 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   using L = CombineLds<R, DH, RPT, PS>;
   constexpr int KK = R / 32;         // K steps
   constexpr int NT = DH / 64;        // 16-row output tiles per wavefront (a quarter of d_h)
-  constexpr int TPR = PS ? kWave : kBlock / RPT;  // threads merging one row (piece split: per wavefront)
+  constexpr int TPR = L::TPR;        // threads merging one row (piece split: a group of NG)
+  constexpr int NG = L::groups;
   constexpr int CJ = R / (4 * TPR);  // float4 pieces of a latent row per thread
   static_assert(CJ >= 1, "a thread merges at least one float4 of its row");
   constexpr int PC = R / 8;          // 16-byte pieces of a row
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // rows in LDS: piece p of row i at place p ^ swz(i), so that 16 rows' reads of one piece spread over the banks
   uint16_t* sA = reinterpret_cast<uint16_t*>(smem + L::planes);  // [plane][RPT][R]
-  float* sRed = reinterpret_cast<float*>(smem + L::red);         // [kWaves - 1][R]
+  float* sRed = reinterpret_cast<float*>(smem + L::red);         // [NG - 1][R]
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
@@ -145,6 +146,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
 
   const int total_tiles = (PS || HF) ? ps_total : (a.n_persistent > 0 ? a.tile_prefix[a.batch] : 0);
   const int rr = PS ? 0 : tid / TPR, sub = tid % TPR;  // merge phase: TPR threads per row
+  const int grp = PS ? tid / TPR : 0;                  // ... or, of one row, NG groups of as many
   for (int t = t0; t < t1; ++t) {
     const int row = RPT * t + rr;
     // static schedule: piece ids row*n_splits + 0 .. n_splits-1 are readable whatever the row's
@@ -155,10 +157,10 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     const int row_c = row < rows ? row : rows - 1;
     const size_t pb = (size_t)(fixed_ids ? row_c * a.n_splits : pc.first) * a.n_heads + h;  // + p * n_heads
     const int p_last = fixed_ids ? a.n_splits - 1 : (pc.count > 0 ? pc.count - 1 : 0);
-    // piece split: a quarter of the row's pieces where the count came first, else (requests do not wait for the count) every
-    // fourth from wv on
-    const int pq = (pc.count + kWaves - 1) / kWaves, pw0 = fixed_ids ? wv : wv * pq, ps = fixed_ids ? kWaves : 1;
-    const int cnt = !PS ? pc.count : (fixed_ids ? (pc.count - wv + kWaves - 1) / kWaves : (pc.count - pw0 < pq ? pc.count - pw0 : pq));
+    // piece split: a group's share of the row's pieces where the count came first, else (requests do not wait for the count) every
+    // NG-th from its own number on
+    const int pq = (pc.count + NG - 1) / NG, pw0 = fixed_ids ? grp : grp * pq, ps = fixed_ids ? NG : 1;
+    const int cnt = !PS ? pc.count : (fixed_ids ? (pc.count - grp + NG - 1) / NG : (pc.count - pw0 < pq ? pc.count - pw0 : pq));
 
     // ---- first PB pieces: requested before anything is known about m* (any piece id that can
     // come out of pieces_of_row is readable workspace)
@@ -219,15 +221,15 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
         }
       }
     }
-    if constexpr (PS) {  // wavefront 0 adds the other three sums to its own
-      if (wv > 0) {
+    if constexpr (PS) {  // group 0 adds the other sums to its own
+      if (grp > 0) {
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) *reinterpret_cast<float4_t*>(sRed + (wv - 1) * R + 4 * sub + 4 * TPR * j) = acc[j];
+        for (int j = 0; j < CJ; ++j) *reinterpret_cast<float4_t*>(sRed + (grp - 1) * R + 4 * sub + 4 * TPR * j) = acc[j];
       }
       __syncthreads();
-      if (wv == 0) {
+      if (grp == 0) {
 #pragma unroll
-        for (int w = 0; w < kWaves - 1; ++w)
+        for (int w = 0; w < NG - 1; ++w)
 #pragma unroll
           for (int j = 0; j < CJ; ++j) acc[j] += *reinterpret_cast<const float4_t*>(sRed + w * R + 4 * sub + 4 * TPR * j);
       }
@@ -235,7 +237,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     const float inv = pc.count > 0 ? 1.f / lstar : 0.f;  // a row with no live column gives zeros
 #pragma unroll
     for (int j = 0; j < CJ; ++j) acc[j] *= inv;
-    if (row < rows && (!PS || wv == 0)) {
+    if (row < rows && (!PS || grp == 0)) {
       const size_t oh = (size_t)row * a.n_heads + h;
       if (a.out_latent) {
 #pragma unroll
@@ -247,15 +249,17 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     if (!a.out) continue;
 
     // ---- park the row as hi + lo bf16 planes
+    if (!PS || grp == 0) {
 #pragma unroll
-    for (int j = 0; j < (!PS || wv == 0 ? CJ : 0); ++j) {
-      const uint32_t h01 = pack_bf16x2(acc[j][0], acc[j][1]), h23 = pack_bf16x2(acc[j][2], acc[j][3]);
-      const uint32_t l01 = pack_bf16x2(acc[j][0] - __uint_as_float(h01 << 16), acc[j][1] - __uint_as_float(h01 & 0xffff0000u));
-      const uint32_t l23 = pack_bf16x2(acc[j][2] - __uint_as_float(h23 << 16), acc[j][3] - __uint_as_float(h23 & 0xffff0000u));
-      const int e = 4 * sub + 4 * TPR * j;
-      uint16_t* dst = sA + rr * R + 8 * ((e >> 3) ^ swz_rows16<PC>(rr)) + (e & 7);
-      *reinterpret_cast<uint2*>(dst) = make_uint2(h01, h23);
-      *reinterpret_cast<uint2*>(dst + RPT * R) = make_uint2(l01, l23);
+      for (int j = 0; j < CJ; ++j) {
+        const uint32_t h01 = pack_bf16x2(acc[j][0], acc[j][1]), h23 = pack_bf16x2(acc[j][2], acc[j][3]);
+        const uint32_t l01 = pack_bf16x2(acc[j][0] - __uint_as_float(h01 << 16), acc[j][1] - __uint_as_float(h01 & 0xffff0000u));
+        const uint32_t l23 = pack_bf16x2(acc[j][2] - __uint_as_float(h23 << 16), acc[j][3] - __uint_as_float(h23 & 0xffff0000u));
+        const int e = 4 * sub + 4 * TPR * j;
+        uint16_t* dst = sA + rr * R + 8 * ((e >> 3) ^ swz_rows16<PC>(rr)) + (e & 7);
+        *reinterpret_cast<uint2*>(dst) = make_uint2(h01, h23);
+        *reinterpret_cast<uint2*>(dst + RPT * R) = make_uint2(l01, l23);
+      }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weights have landed
     __syncthreads();
@@ -303,17 +307,19 @@ hipError_t launch_one(const CombineArgs& a, const dim3& grid, int tiles_per_wg, 
 template <int R, int DH, bool PF16>
 hipError_t launch_rdh_pf(const CombineArgs& a, hipStream_t st) {
   const int rows = a.T ? a.batch * a.T : a.batch;
+  // a handful of rows of eight or more pieces each (balanced: at most n_persistent + rows pieces exist): one row per
+  // workgroup, its pieces split over the wavefronts
+  if (PF16 && a.n_persistent > 0 && rows <= 16 && a.n_persistent + rows >= 8 * rows)
+    return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
+  // a small decode step, at most one (row, head) per compute unit, where a row is long (r = 512) or its pieces are more
+  // than one round of requests: likewise.  With four rows per workgroup 4 sequences of 32 pieces, 16 heads, r = 512 took
+  // 10.5 us on 16 workgroups, in this form 7.8, with the weights through LDS 6.0.  (16 sequences of 10 pieces, 8 heads, r = 256: 4.4 us either way; beyond a
+  // row and head per unit every row's own copy of W_V^(h) costs more than the merge gains.)  Narrow latents have sixteen rows a
+  // workgroup else: us a step, 8 heads x 64, r = 128: 1 sequence of 16 pieces 11.1 / 10.7, 1 of 96 28.3 / 21.1, 4 of 141 30.0 / 17.0; 16 heads, 16
+  // of 24 16.9 / 13.0; r = 64: 1 of 63 16.2 / 10.9, but 4 of 16 10.4 / 10.6.
+  if (!PF16 && a.n_persistent == 0 && a.T == 0 && rows * a.n_heads <= 256 && (R == 512 || a.n_splits > (R == 128 ? 8 : 16)))
+    return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
   if constexpr (R >= 256) {
-    // a handful of rows of eight or more pieces each (balanced: at most n_persistent + rows pieces exist): one row per
-    // workgroup, its pieces split over the wavefronts
-    if (PF16 && a.n_persistent > 0 && rows <= 16 && a.n_persistent + rows >= 8 * rows)
-      return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
-    // a small decode step, at most one (row, head) per compute unit, where a row is long (r = 512) or its pieces are more
-    // than one round of requests: likewise.  With four rows per workgroup 4 sequences of 32 pieces, 16 heads, r = 512 took
-    // 10.5 us on 16 workgroups, in this form 7.8, with the weights through LDS 6.0.  (16 sequences of 10 pieces, 8 heads, r = 256: 4.4 us either way; beyond a
-    // row and head per unit every row's own copy of W_V^(h) costs more than the merge gains.)
-    if (!PF16 && a.n_persistent == 0 && a.T == 0 && rows * a.n_heads <= 256 && (R == 512 || a.n_splits > 16))
-      return launch_one<R, DH, 1, PF16, true>(a, dim3(a.n_heads, rows), 1, st);
     if (rows <= 64)  // small batch: four rows per workgroup, one wavefront merging each
       return launch_one<R, DH, 4, PF16>(a, dim3((rows + 3) / 4, a.n_heads), 1, st);
   }

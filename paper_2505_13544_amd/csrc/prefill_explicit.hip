@@ -551,6 +551,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       }
 #pragma unroll
       for (int kk = 0; kk < KD; ++kk) *reinterpret_cast<u32x4_t*>(to + 1024 * (KQ + kk)) = vd[rt][kk];
+      __builtin_amdgcn_wave_barrier();
       e = group_reduce<4>(e, LaneSum());
       e = __int_as_float(__builtin_amdgcn_ds_bpermute(16 * l16, __float_as_int(e)));  // of row l16: lane 4 l16
       neg_ref[rt] = float4_t{-e, -e, -e, -e};
@@ -741,6 +742,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       else
         *reinterpret_cast<float4_t*>(leave + (ln & 15) * RB + (((4 * mt + (ln >> 4)) ^ (ln & SW)) << 4)) = o;
     }
+    __builtin_amdgcn_wave_barrier();
     unsigned char* out_rows = LAYER ? reinterpret_cast<unsigned char*>(a.out16) + (((size_t)b * T + mt0) * nh + h) * RB
                                     : reinterpret_cast<unsigned char*>(out) + (size_t)mt0 * out_stride * 4;
 #pragma unroll

@@ -38,6 +38,15 @@ def test_more_pieces_than_one_round_of_the_merge():
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32, decode_schedule=1)
 
 
+@pytest.mark.parametrize("r,schedule", [(64, 1), (128, 1), (128, 2)])
+def test_pieces_dealt_to_parts_of_a_wavefront(r, schedule):
+    # narrow latents: sixteen groups (r = 64) or eight (r = 128) merge a row; rows with none, one, a few and all of 29 pieces
+    plen = np.array([1, 33, 130, 900], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name=f"split_narrow_{r}_{schedule}", batch=len(plen), d_model=96, n_heads=8, d_head=64, r=r, d_rope=32,
+                                           stride=1, prefix=(1, 900), steps=2, seed=84)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32 if schedule == 1 else 64, decode_schedule=schedule)
+
+
 def test_reference_moves_between_steps():
     # logits far apart: the weights' reference moves from step to step of one chunk; chunks of one step never move theirs
     wl = W.WORKLOADS["speech_bf16"].scaled(name="split_far", batch=3, d_model=96, n_heads=8, d_head=64, r=256, d_rope=32, stride=1,
