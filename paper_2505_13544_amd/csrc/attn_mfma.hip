@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
   const uint16_t* lat = reinterpret_cast<const uint16_t*>(a.lat) + (PG ? 0 : (size_t)b * a.max_slots * R);
   const uint16_t* key = reinterpret_cast<const uint16_t*>(a.key) + (PG ? 0 : (size_t)b * a.max_slots * DR);
 
-  // length, first rows and query are requested together, as in attn_mfma_kernel
+  const int len = load_uniform_i32(a.seq_len, b);  // nothing writes it while the kernel runs
   SharedPrefix sp{0, 0, 0};
   if constexpr (SH) {
     int owner = a.prefix_owner[b], n = a.prefix_slots[b];
@@ -496,7 +496,6 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
     sp.dlat = (long long)(owner - b) * a.max_slots * R;
     sp.dkey = (long long)(owner - b) * a.max_slots * DR;
   }
-  const int len = load_uniform_i32(a.seq_len, b);  // nothing writes it while the kernel runs
   const int in_row = lane >> 2, piece = (lane & 3) ^ swz_rows16<4>(in_row);  // what a lane brings in: 16 bytes of that row's 64
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
   // the wavefront's 16 slots from `base` on; slots past `last` become copies of that one
@@ -523,7 +522,6 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
       }
     }
   };
-  issue_rows(k0 + wv * kTile, a.max_slots - 1);
   {
     const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * E;
     uint32_t at_q[NHT];  // heads past the last one: copies of it, never stored
@@ -544,6 +542,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
   }
   const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
+  if (k0 < k1) issue_rows(k0 + wv * kTile, k1 - 1);
 
   const int hq = NHT == 2 ? wv & 1 : 0, grp = NHT == 2 ? wv >> 1 : wv;  // head tile and slot tiles NHT grp .. of the wavefront's logits
   float m_ref[NHT], l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
@@ -564,11 +563,6 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
       __syncthreads();
       issue_rows(s0 + wv * kTile, k1 - 1);
       wait_loads_but<0>();
-    } else if (k1 < s0 + (wv + 1) * kTile) {
-      // rows of the first step that no slot stands for may never have been written: zeros, or 0 x NaN would reach the sums
-      if (s0 + wv * kTile + in_row >= k1)
-#pragma unroll
-        for (int kk = 0; kk < KC; ++kk) *reinterpret_cast<u32x4_t*>(smem + wv * G::TILE + 1024 * kk + 16 * lane) = u32x4_t{0u, 0u, 0u, 0u};
     }
     __syncthreads();  // rows and query are there
     // ---- logits S^T[slot, head] (log2 units), one chain per query plane

@@ -403,6 +403,22 @@ mtla_status mtla_cache_append(mtla_ctx* c, void* cache_c, void* cache_kr, float*
                                  hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace, hip_stream);
 }
 
+// Tiles of 16 slots (as many as the session holds) from which the balanced schedule is the faster one.  It has a fixed cost, the scan
+// of the lengths and a cold start of every persistent workgroup, some 5 us of a step beside a chunk a workgroup; against it stand the rounds of
+// workgroups that the chunks come to, which are two a unit at r = 256, one with two head tiles or r = 512.  us a step, chunks / balanced:
+//   r = 128   12 heads, 50 x 1000 slots (3200 tiles) 14.4 / 18.3, 16 heads, 100 x 1000 (6400) 17.8 / 21.0, 200 x 1000 (12800) 27.7 / 27.9
+//   r = 256   8 heads, 40 x 1000 (2560) 16.8 / 18.9, 16 heads, 100 x 500 (3200) 20.6 / 22.6, 8 heads, 16 x 5000 (5024) 20.5 / 20.4; 20 heads, 31 x
+//             450 (899) 18.8 / 20.2, 31 x 525 (1054, d_head 128) 22.9 / 20.9, 32 heads x 64, 20 x 900 (1160) 21.0 / 21.0
+//   r = 512   16 heads, 32 x 400 (832) 23.9 / 27.2, 32 x 650 (1344) 28.0 / 28.2, 64 x 600 (2432) 34.5 / 31.4; 32 heads, 31 x 500 (992) 28.8 /
+//             31.2, 20 heads, 31 x 640 (1294) 30.6 / 27.5
+static long long balanced_from(const mtla_config& g, int n_cu) {
+  const bool two = g.n_heads > 16;
+  if (g.r == 128) return 24LL * n_cu;
+  if (g.r == 256 && !two) return 16LL * n_cu;
+  if (g.r == 256 || g.r == 512) return two ? 9LL * n_cu / 2 : 11LL * n_cu / 2;
+  return 8LL * n_cu;
+}
+
 // Attention of one decode step; `ap` (may be NULL) is the append of the step's token that has to
 // come first.
 static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q, const void* q_rope,
@@ -467,9 +483,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
         return MTLA_ERR_HIP;
       c->n_cu = n < kMaxPersistent ? n : kMaxPersistent;
     }
-    // balanced pays off once every persistent workgroup has a run of tiles to stream
     const long long cap_tiles = (long long)batch * ((g.max_slots + 15) / 16);
-    if (c->schedule == 2 || cap_tiles >= 8LL * c->n_cu) {
+    if (c->schedule == 2 || cap_tiles >= balanced_from(g, c->n_cu)) {
       at.n_persistent = c->n_cu;
       if (attn_cols_supported(at)) {
         const int n = c->n_cu * attn_cols_workgroups_per_cu(at);
