@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kBlock, 4) void decode_front_kernel(AppendArgs ap, 
   }
   const int i = blk - ap.batch;
   const int bx = i % gx, rest = i / gx;
-  absorb_mfma_block<KK, sizeof(TC) == 4>(ab, bx, rest % gy, rest / gy);  // the whole-layer call hands q, q^R and c over unrounded
+  absorb_mfma_block<KK, sizeof(TC) == 4>(ab, bx, rest % gy, rest / gy, reinterpret_cast<unsigned char*>(smem));  // the whole-layer call hands q, q^R and c over unrounded
 }
 
 // Front of an fp32 decode step, split the same way (the append as a launch of its own took 3.1 us and the absorption
@@ -412,9 +412,10 @@ hipError_t launch_decode_front(const AppendArgs& ap, const AbsorbArgs& ab, hipSt
   const int gx = absorb_col_blocks(ab.r) + 1, gy = ab.n_heads;
   const int gz = (ab.rows + absorb_rows_per_block(ab.rows) - 1) / absorb_rows_per_block(ab.rows);
   const dim3 grid(ap.batch + gx * gy * gz), block(kBlock);
-  const size_t smem = AppendStep<bf16, 1>::floats(ap) * sizeof(float);
+  const size_t append = AppendStep<bf16, 1>::floats(ap) * sizeof(float);
 #define MTLA_FRONT(N, K)                                                                                \
   if (ap.r == 32 * N && ab.d_head == 32 * K) {                                                          \
+    const size_t absorb = ap.c_new_f32 ? AbsorbLds<K, true>::bytes : AbsorbLds<K, false>::bytes, smem = append > absorb ? append : absorb; \
     if (ap.c_new_f32)                                                                                   \
       hipLaunchKernelGGL((decode_front_kernel<N, K, float>), grid, block, smem, st, ap, ab, gx, gy);    \
     else                                                                                                \

@@ -29,7 +29,8 @@ constexpr int kWaves = kBlock / kWave;
 // absorb, bf16 on the matrix cores: grid = (absorb_col_blocks(r) + 1, n_heads, row groups), body in absorb_mfma.h
 template <int KK, bool QF32>
 __global__ __launch_bounds__(kBlock) void absorb_mfma_kernel(AbsorbArgs a) {
-  absorb_mfma_block<KK, QF32>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+  extern __shared__ float sq[];
+  absorb_mfma_block<KK, QF32>(a, blockIdx.x, blockIdx.y, blockIdx.z, reinterpret_cast<unsigned char*>(sq));
 }
 
 // absorb, fp32 storage: grid = (r/64 + 1, n_heads, ceil(rows/8)), body in absorb_f32.h
@@ -308,11 +309,19 @@ void launch_combine_t(const CombineArgs& a, const dim3& grid, size_t smem, hipSt
   hipLaunchKernelGGL((combine_kernel<T, 0, INLINE>), grid, dim3(kBlock), smem, st, a);
 }
 
-template <int KK>
-void launch_absorb_mfma_kk(const AbsorbArgs& a, hipStream_t st) {
+template <int KK, bool QF32>
+hipError_t launch_absorb_mfma_as(const AbsorbArgs& a, hipStream_t st) {
   const dim3 grid(absorb_col_blocks(a.r) + 1, a.n_heads, (a.rows + absorb_rows_per_block(a.rows) - 1) / absorb_rows_per_block(a.rows));
-  if (a.q_f32) hipLaunchKernelGGL((absorb_mfma_kernel<KK, true>), grid, dim3(kBlock), 0, st, a);
-  else hipLaunchKernelGGL((absorb_mfma_kernel<KK, false>), grid, dim3(kBlock), 0, st, a);
+  constexpr size_t smem = AbsorbLds<KK, QF32>::bytes;
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&absorb_mfma_kernel<KK, QF32>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((absorb_mfma_kernel<KK, QF32>), grid, dim3(kBlock), smem, st, a);
+  return hipGetLastError();
+}
+template <int KK>
+hipError_t launch_absorb_mfma_kk(const AbsorbArgs& a, hipStream_t st) {
+  return a.q_f32 ? launch_absorb_mfma_as<KK, true>(a, st) : launch_absorb_mfma_as<KK, false>(a, st);
 }
 
 }  // namespace
@@ -320,17 +329,16 @@ void launch_absorb_mfma_kk(const AbsorbArgs& a, hipStream_t st) {
 hipError_t launch_absorb(const AbsorbArgs& a, int dtype, hipStream_t st) {
   if (a.out_bf16) {  // bf16 storage, matrix-core operand
     switch (a.d_head / 32) {
-      case 1: launch_absorb_mfma_kk<1>(a, st); break;
-      case 2: launch_absorb_mfma_kk<2>(a, st); break;
-      case 3: launch_absorb_mfma_kk<3>(a, st); break;
-      case 4: launch_absorb_mfma_kk<4>(a, st); break;
-      case 5: launch_absorb_mfma_kk<5>(a, st); break;
-      case 6: launch_absorb_mfma_kk<6>(a, st); break;
-      case 7: launch_absorb_mfma_kk<7>(a, st); break;
-      case 8: launch_absorb_mfma_kk<8>(a, st); break;
+      case 1: return launch_absorb_mfma_kk<1>(a, st);
+      case 2: return launch_absorb_mfma_kk<2>(a, st);
+      case 3: return launch_absorb_mfma_kk<3>(a, st);
+      case 4: return launch_absorb_mfma_kk<4>(a, st);
+      case 5: return launch_absorb_mfma_kk<5>(a, st);
+      case 6: return launch_absorb_mfma_kk<6>(a, st);
+      case 7: return launch_absorb_mfma_kk<7>(a, st);
+      case 8: return launch_absorb_mfma_kk<8>(a, st);
       default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
   }
   if (dtype == 0) {
     const dim3 grid(a.r / 64 + 1, a.n_heads, (a.rows + kFrontRows - 1) / kFrontRows);
