@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmtla.so")
-SOURCES = ["mtla_api.hip", "append.hip", "attn_valu.hip", "attn_f32.hip", "attn_mfma.hip", "attn_cols.hip", "attn_whole.hip", "proj.hip", "combine_mfma.hip", "prefill_front.hip", "prefill_explicit.hip", "gemm_wide.hip", "prefill_latent.hip", "layer.hip", "pages.hip"]
+SOURCES = ["mtla_api.hip", "append.hip", "attn_valu.hip", "attn_f32.hip", "attn_mfma.hip", "attn_cols.hip", "attn_whole.hip", "proj.hip", "combine_mfma.hip", "prefill_front.hip", "prefill_explicit.hip", "gemm_wide.hip", "gemm_ring.hip", "prefill_latent.hip", "layer.hip", "pages.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-fno-gpu-rdc", "-Wall", "-Wno-unused-function",

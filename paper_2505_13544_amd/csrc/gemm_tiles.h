@@ -37,6 +37,24 @@ int gemm_col_blocks(const Args& a, int bn) {
   return n;
 }
 
+// Small products (gemm_ring.hip): 16 x 16 tiles of outputs, as many as the sequences may have.  Up to kRingSmall of them one a workgroup,
+// up to kRingMedium two, beyond four.  us of a whole layer over short prompts, without / with them for all its products up to 2000 tiles:
+// 8 heads x 64, r = 256, 33 tokens 31.9 / 26.7, 129 (594 tiles) 33.4 / 28.0, 257 (1122) 34.2 / 31.1, 400 (1650) 36.0 / 33.8; 16 x 128, r = 512,
+// 17 tokens 49.9 / 36.0, 64 (912) 52.1 / 40.6, 129 (2052) 52.0 / 50.1; 32 x 128, 33 tokens (1260) 70.4 / 58.6.  Up to 3000 tiles: 400 tokens of
+// the first 34.0, but 2 x 300 36.6 / 38.6, 200 of the second 53.3 / 56.7, 100 of the third 75.9 / 81.2.
+constexpr int kRingSmall = 400, kRingMedium = 600, kRingMost = 2000;
+template <class Args>
+long long gemm_ring_tiles(const Args& a) {
+  const bool ragged = (a.rows.n_new || a.rows.pos0) && !a.rows.zeros;
+  const int Tp = a.rows.past + a.rows.T;
+  const long long rows = ragged ? (long long)(a.M / Tp) * ((Tp + 15) / 16) : ((long long)a.M + 15) / 16;
+  return rows * gemm_col_blocks(a, 16);
+}
+template <class Args>
+bool gemm_ring_pays(const Args& a) {
+  return gemm_ring_tiles(a) <= kRingMost;
+}
+
 // The time of a product in tiles i, as measured on rows in use x 1024 to 4096 columns.  A round is a tile for each of the 256
 // units.  us at K = 512 / 2048: 64 x 64 one round 4.9 / 12, two 7.0 / 20, three 9.8 / 28; 128 x 128 one 9 / 25, two 14.5 / 44; the
 // streams, whose last round is cut into halves or quarters of a tile where that fills it: a quarter round 10 / 24, half a one

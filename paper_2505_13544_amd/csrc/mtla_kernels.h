@@ -409,6 +409,8 @@ hipError_t launch_attn_latent(const ExplicitArgs& a, hipStream_t st, const Event
 hipError_t launch_prefill_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev = EventPair());
 bool gemm_nt_supported(const GemmArgs& a);
 hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st);
+// the same products in tiles of 16 x 16 outputs and a few of them (launch_gemm_nt picks)
+hipError_t launch_gemm_ring(const GemmArgs& a, hipStream_t st);
 // the same products as streams of 256 x 256 tiles (launch_gemm_nt picks)
 bool gemm_wide_supported(const GemmArgs& a);
 hipError_t launch_gemm_wide(const GemmArgs& a, hipStream_t st);

@@ -826,6 +826,7 @@ hipError_t launch_rope_table(const GemmArgs& g, hipStream_t st) {
 
 hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
+  if (gemm_ring_pays(args)) return launch_gemm_ring(args, st);
   GemmArgs a = args;
   const bool turned = gemm_turns(a);
   auto table = [&]() {

@@ -97,6 +97,17 @@ def test_layer_prefill_whole_prompt(stride, n_heads, d_head, r, d_rope, d_model)
     print(f"layer prefill, stride {stride}: max abs err {worst:.2e}")
 
 
+@pytest.mark.parametrize("lens,pieces,n_heads,d_model", [([1], [1], 2, 32),             # 16 x 16 tiles; one K step: three wavefronts without
+                                                         ([17, 3, 33], [17, 16], 4, 96),  # row blocks of one row, of none; three K steps
+                                                         ([33, 5, 31], [33], 4, 160),   # 32 x 16 tiles, five K steps over four wavefronts
+                                                         ([64, 33, 1, 49], [64], 8, 128)])  # 32 x 32
+def test_layer_prefill_small_products(lens, pieces, n_heads, d_model):
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="lp_small", batch=len(lens), d_model=d_model, n_heads=n_heads, d_head=64, r=64, d_rope=32, stride=2,
+                                           prefix=max(lens), steps=0, seed=88)
+    worst = _feed(wl, lens, pieces)
+    print(f"layer prefill, small products: max abs err {worst:.2e}")
+
+
 def test_layer_prefill_streamed_products():
     # enough rows and columns for the streamed 256 x 256 tiles in the projections (every way out) and in W_O, whose rows past a
     # sequence's length are zeros inside a tile, at a tile's end and over whole tiles;
