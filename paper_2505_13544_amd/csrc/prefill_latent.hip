@@ -8,8 +8,12 @@
 // d_h + r value columns each.  The weights of tile t + 1 are formed between the barrier that makes those of tile t
 // visible and the next one, so the matrix instructions of one tile cover the arithmetic of the other.
 // With a pass of the plain kernel for every d_h of the r columns (the logits formed r / d_h + 1 times: 3200 flop per pair
-// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us, now 122
+// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us; in one pass 122, and now 113 with
+// the rows leaving by whole lines, the queries and own keys coming by 64 bytes of a row, and the blocks ordered as the plain form's
 // (the outputs alone, 313 MB, are 66 at the rate of a large copy).
+#include <type_traits>
+
+#include "attn_blocks.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
@@ -49,8 +53,9 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   const int jc = wv & 3, ir = wv >> 2;  // quarter of the value columns, half of the rows
   const int T = a.T, s = a.stride, nh = a.n_heads;
   // (sequence, head) pairs dealt to the XCDs, their blocks on one of them, those with most columns first
-  const int n_blocks = (T + BM - 1) / BM, per_xcd = (nh * a.batch + 7) / 8, i_xcd = (int)(blockIdx.x >> 3);
-  const int m0 = (n_blocks - 1 - i_xcd / per_xcd) * BM, hb = 8 * (i_xcd % per_xcd) + (int)(blockIdx.x & 7);
+  const int n_blocks = (T + BM - 1) / BM;
+  const AttnBlock mine = attn_block(blockIdx.x, nh * a.batch, n_blocks, a.group);
+  const int m0 = mine.block * BM, hb = mine.pair;
   if (hb >= nh * a.batch) return;
   const int h = hb % nh, b = hb / nh;
   const int len = a.seq_len ? (a.seq_len[b] < T ? a.seq_len[b] : T) : T;
@@ -147,12 +152,17 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   float l_run;
   const int m_own = m0 + 16 * wv + l16, m_clamp = m_own < len ? m_own : len - 1;
   const int bound = m_clamp / s;                              // columns open to the lane's row
+  // Read from memory by 64 bytes of 4 rows to 16 neighbouring lanes (the operand's layout, 16 rows, is 66 cycles of the unit's address path a
+  // load, 12 loads a wavefront, this one 24).  In this layout the row's own logit is formed as well; the queries then change lanes in the
+  // wavefront's place among the weights.
   {
-    const size_t row = ((size_t)b * T + m_clamp) * nh + h;
-    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + row * DH + 8 * g;
-    const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + row * DR + 8 * g;
-    const uint16_t* kp = kx + (size_t)m_clamp * kv_stride + 8 * g;
-    const uint16_t* krp = kr16 + (size_t)m_clamp * DR + 8 * g;
+    const int ln = here(lane), m_load = m0 + 16 * wv + (ln >> 2);
+    const int m_from = m_load < len ? m_load : len - 1;
+    const size_t row = ((size_t)b * T + m_from) * nh + h;
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + row * DH + 8 * (ln & 3);
+    const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + row * DR + 8 * (ln & 3);
+    const uint16_t* kp = kx + (size_t)m_from * kv_stride + 8 * (ln & 3);
+    const uint16_t* krp = kr16 + (size_t)m_from * DR + 8 * (ln & 3);
     u32x4_t kd[KQ];
 #pragma unroll
     for (int kk = 0; kk < KQ; ++kk) {
@@ -165,9 +175,22 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       qf[kk] = bf16x8_to_f16x8(qf[kk], a.scale_log2);  // logits in units of log2
       e = dot8(kd[kk], qf[kk], e);
     }
-    e = quarter_reduce(e, LaneSum());
-    neg_ref = -e;
+    e += __shfl_xor(e, 1);
+    e += __shfl_xor(e, 2);
+    neg_ref = -__shfl(e, 4 * (ln & 15));
     l_run = g == 0 ? 1.f : 0.f;
+    unsigned char* turn = lds + G::P_OFF + wv * 1024;
+#pragma unroll
+    for (int kk = 0; kk < KQ; kk += 2) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (kk + k < KQ) *reinterpret_cast<u32x4_t*>(turn + k * G::P_BYTES + (ln >> 2) * 64 + (((ln & 3) ^ swz_rows16<4>(ln >> 2)) << 4)) = qf[kk + k];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (kk + k < KQ) qf[kk + k] = *reinterpret_cast<const u32x4_t*>(turn + k * G::P_BYTES + (ln & 15) * 64 + (((ln >> 4) ^ swz_rows16<4>(ln & 15)) << 4));
+      __builtin_amdgcn_wave_barrier();
+    }
   }
   const int all_below = (m0 + 16 * wv) / s, none_from = (m0 + 16 * wv + 15) / s;  // of the rows whose weights it forms
   const int none_rows = (m0 + 64 * ir + 63) / s;                                  // of the rows it sums
@@ -357,33 +380,52 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
     if (ir == 1 && t + 1 < n_tiles) form_weights(t + 1);
   }
 
-  // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3
+  // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3.  The rows leave through LDS, up to whole
+  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path, 320 of them a block).
   {
     const float l = quarter_reduce(l_run, LaneSum());
     if (g == 0) s_inv[16 * wv + l16] = m_own < len ? 1.f / l : 0.f;
   }
   __syncthreads();
+  const int ln = here(lane);
+  unsigned char* leave = lds + wv * (1024 * (NV + NC));
+  static_assert(8 * 1024 * (NV + NC) <= G::BYTES, "the rows fit");
 #pragma unroll
   for (int rt = 0; rt < 4; ++rt) {
-    const int m = m0 + 64 * ir + 16 * rt + l16;
-    if (m >= T) continue;
-    const float inv = s_inv[64 * ir + 16 * rt + l16];
-    float* po = out + (size_t)m * nh * DH + 16 * NV * jc + 4 * g;
-    float* pl = latent + (size_t)m * nh * R + 16 * NC * jc + 4 * g;
+    const int mt0 = m0 + 64 * ir + 16 * rt;
+    if (mt0 >= T) break;
+    const bool live = mt0 + (ln & 15) < len;  // padding rows are zeros, whatever their inputs held
+    const float inv = s_inv[64 * ir + 16 * rt + (ln & 15)];
+    auto leave_rows = [&](auto n_tag, int first, unsigned char* area, unsigned char* to, size_t to_row) {  // N tiles of 16 columns from `first` on
+      constexpr int N = decltype(n_tag)::value, PPR = 4 * N, SW = PPR < 16 ? PPR - 1 : 15;  // piece j of row i sits at j ^ (i & SW)
 #pragma unroll
-    for (int i = 0; i < NV + NC; ++i) {
-      const float4_t o = m < len ? acc[rt][i] * inv : float4_t{0.f, 0.f, 0.f, 0.f};  // padding rows are zeros, whatever their inputs held
-      *reinterpret_cast<float4_t*>(i < NV ? po + 16 * i : pl + 16 * (i - NV)) = o;
-    }
+      for (int i = 0; i < N; ++i)
+        *reinterpret_cast<float4_t*>(area + (ln & 15) * (16 * PPR) + (((4 * i + (ln >> 4)) ^ (ln & SW)) << 4)) =
+            live ? acc[rt][first + i] * inv : float4_t{0.f, 0.f, 0.f, 0.f};
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(area + row * (16 * PPR) + ((c ^ (row & SW)) << 4));
+        if (mt0 + row < T) *reinterpret_cast<u32x4_t*>(to + row * to_row + 16 * c) = v;
+      }
+      __builtin_amdgcn_wave_barrier();
+    };
+    leave_rows(std::integral_constant<int, NV>(), 0, leave, reinterpret_cast<unsigned char*>(out + (size_t)mt0 * nh * DH + 16 * NV * jc), (size_t)nh * DH * 4);
+    leave_rows(std::integral_constant<int, NC>(), NV, leave + 1024 * NV, reinterpret_cast<unsigned char*>(latent + (size_t)mt0 * nh * R + 16 * NC * jc), (size_t)nh * R * 4);
   }
 }
 
 template <int DH, int DR>
 hipError_t launch_r(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
-  const dim3 grid((unsigned)((a.T + 127) / 128) * ((a.n_heads * a.batch + 7) / 8 * 8)), block(512);
+  static_assert(kAttnRows == LatentGeom<DH, DR, 64>::BM, "rows of a block");
+  const int pairs = a.n_heads * a.batch;
+  ExplicitArgs x = a;
+  x.group = attn_group(pairs, DH);
+  const dim3 grid((unsigned)((a.T + kAttnRows - 1) / kAttnRows) * (unsigned)(attn_pairs(pairs) * kXcds)), block(512);
 #define MTLA_CASE(RR)                                                                    \
   if (a.r == RR) {                                                                       \
-    launch_timed(attn_latent_kernel<DH, DR, RR>, grid, block, 0, st, ev, a);             \
+    launch_timed(attn_latent_kernel<DH, DR, RR>, grid, block, 0, st, ev, x);             \
     return hipGetLastError();                                                            \
   }
   MTLA_CASE(64)
