@@ -8,8 +8,9 @@
 // d_h + r value columns each.  The weights of tile t + 1 are formed between the barrier that makes those of tile t
 // visible and the next one, so the matrix instructions of one tile cover the arithmetic of the other.
 // With a pass of the plain kernel for every d_h of the r columns (the logits formed r / d_h + 1 times: 3200 flop per pair
-// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us; in one pass 122, and now 113 with
-// the rows leaving by whole lines, the queries and own keys coming by 64 bytes of a row, and the blocks ordered as the plain form's
+// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us; in one pass 122, and now 110 with
+// the rows leaving by whole lines, the queries, own keys and own values coming by 64 bytes of a row and more, all in flight at once, and
+// the blocks ordered as the plain form's
 // (the outputs alone, 313 MB, are 66 at the rate of a large copy).
 #include <type_traits>
 
@@ -134,17 +135,12 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       }
     }
   };
-  auto issue_own = [&](int k) {  // values of the block's own rows 32 k .. 32 k + 31, in the place of tile k / 2's
-    const uint32_t buf = lds_addr + G::V_OFF + (uint32_t)(k >> 1) * (uint32_t)G::VT;
-    auto own_row = [&](int row) -> size_t { return (size_t)(m0 + BN * k + row < len ? m0 + BN * k + row : len - 1); };
-    load_to_lds_16(vx + own_row(row_k) * kv_stride + src_v, buf + (uint32_t)(wv % G::NCK) * 1024u);
-#pragma unroll
-    for (int i = 0; i < G::NLC; ++i)
-      load_to_lds_16(cx + own_row(row_c + C_ROWS * i) * R + src_c, buf + G::K_BYTES + (uint32_t)(wv % G::NCC + G::NW * i) * 1024u);
-  };
-  issue_own(0);
-  issue_own(2);
-  if (n_tiles > 0) issue_keys(0);
+  if (n_tiles > 0) {
+    issue_keys(0);
+    for (int i = 0; i <= G::NLC; ++i) issue_value(0, i);
+    if (n_tiles > 1) issue_keys(1);
+    if (n_tiles > 2) issue_keys(2);
+  }
 
   // ---- queries of the wavefront's 16 rows (its share of the weights), and the row's own column: reference, weight 1
   u32x4_t qf[KQ];
@@ -152,6 +148,17 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   float l_run;
   const int m_own = m0 + 16 * wv + l16, m_clamp = m_own < len ? m_own : len - 1;
   const int bound = m_clamp / s;                              // columns open to the lane's row
+  // The values of the wavefront's 64 rows, a quarter of the columns, all asked for at once: piece `at` of them is 16 bytes of row
+  // at / (two pieces a tile).
+  u32x4_t own_v[2 * NV], own_c[2 * NC];
+  auto load_own = [&](auto& own, const uint16_t* from, uint32_t stride, int ln) {
+    constexpr int N = sizeof(own) / 32;  // tiles of 16 columns
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) {
+      const int at = 64 * i + ln, m = m0 + 64 * ir + at / (2 * N);
+      own[i] = *reinterpret_cast<const u32x4_t*>(from + (size_t)(m < len ? m : len - 1) * stride + 16 * N * jc + 8 * (at % (2 * N)));
+    }
+  };
   // Read from memory by 64 bytes of 4 rows to 16 neighbouring lanes (the operand's layout, 16 rows, is 66 cycles of the unit's address path a
   // load, 12 loads a wavefront, this one 24).  In this layout the row's own logit is formed as well; the queries then change lanes in the
   // wavefront's place among the weights.
@@ -169,6 +176,9 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       qf[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(qp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(qrp + 32 * (kk - KD));
       kd[kk] = kk < KD ? *reinterpret_cast<const u32x4_t*>(kp + 32 * kk) : *reinterpret_cast<const u32x4_t*>(krp + 32 * (kk - KD));
     }
+    load_own(own_v, vx, kv_stride, ln);
+    load_own(own_c, cx, R, ln);
+    asm volatile("" ::: "memory");
     float e = 0.f;
 #pragma unroll
     for (int kk = 0; kk < KQ; ++kk) {
@@ -278,38 +288,42 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
     if (lane == 0) s_flag[t & 1][wv] = flag;
   };
 
-  // ---- sums of the wavefront's 64 rows and quarter of the columns, from the rows' own values.  These pass through LDS: read
-  // from memory in this layout (8 bytes of each of 16 rows per load) a block spent 29000 cycles here, now 13000.
+  // ---- sums of the wavefront's 64 rows and quarter of the columns, from the rows' own values.  They change lanes in the wavefront's part
+  // of the second tile's place, 16 rows at a time: read from memory in the sums' layout (8 bytes of each of 16 rows per load) a
+  // block spent 29000 cycles here, brought to LDS by the block, half the rows after the other, 13000.
   float4_t acc[4][NV + NC];
-  auto take_own = [&](int rt0) {
-    const unsigned char* vb = lds + G::V_OFF + ir * G::VT + l16 * (VC * 16) + 8 * (g & 1);
-    const unsigned char* cb = lds + G::V_OFF + ir * G::VT + G::K_BYTES + l16 * (CC * 16) + 8 * (g & 1);
+  unsigned char* own_place = lds + G::V_OFF + G::VT + wv * (512 * (NV + NC));
+  static_assert(G::NW * 512 * (NV + NC) <= G::VT, "16 rows of every wavefront");
+  auto take_own = [&](auto& own, int rt, int first, unsigned char* place) {
+    constexpr int N = sizeof(own) / 32, PPR = 2 * N;
+    const int ln = here(lane);
+    if constexpr (N == 1) {
+      const int row = (ln >> 1) & 15;  // a load holds two row tiles
+      if ((ln >> 5) == (rt & 1)) *reinterpret_cast<u32x4_t*>(place + row * 32 + (((ln & 1) ^ swz_rows16<2>(row)) << 4)) = own[rt >> 1];
+    } else {
 #pragma unroll
-    for (int i = 0; i < NV + NC; ++i) {
-      const int piece = i < NV ? (2 * (NV * jc + i) + (g >> 1)) ^ swz_tr<VC>(l16) : (2 * (NC * jc + i - NV) + (g >> 1)) ^ swz_tr<CC>(l16);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const uint2 v = *reinterpret_cast<const uint2*>((i < NV ? vb : cb) + k * (256 * (i < NV ? VC : CC)) + 16 * piece);
-        acc[rt0 + k][i] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
+      for (int i = 0; i < N / 2; ++i) {
+        const int at = 64 * i + ln, row = at / PPR;
+        *reinterpret_cast<u32x4_t*>(place + row * (16 * PPR) + (((at % PPR) ^ swz_rows16<PPR>(row)) << 4)) = own[rt * (N / 2) + i];
       }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    const int row = ln & 15;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint2 v = *reinterpret_cast<const uint2*>(place + row * (16 * PPR) + (((2 * i + (ln >> 5)) ^ swz_rows16<PPR>(row)) << 4) + 8 * ((ln >> 4) & 1));
+      acc[rt][first + i] = float4_t{f16_lo_to_f32(v.x), f16_hi_to_f32(v.x), f16_lo_to_f32(v.y), f16_hi_to_f32(v.y)};
+    }
+    __builtin_amdgcn_wave_barrier();
   };
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt) {
+    take_own(own_v, rt, 0, own_place);
+    take_own(own_c, rt, NV, own_place + 512 * NV);
+  }
   wait_loads_but<0>();
   barrier_only();
-  take_own(0);
-  barrier_only();
-  issue_own(1);
-  issue_own(3);
-  if (n_tiles > 1) issue_keys(1);
   if (n_tiles > 0) form_weights(0);
-  wait_loads_but<0>();
-  barrier_only();
-  take_own(2);
-  barrier_only();
-  if (n_tiles > 0)
-    for (int i = 0; i <= G::NLC; ++i) issue_value(0, i);
-  if (n_tiles > 2) issue_keys(2);
   for (int t = 0; t < n_tiles; ++t) {
     // values of tile t and keys of tile t + 1 have landed (keys of t + 2 may be under way), weights of tile t are written
     if (t + 2 < n_tiles) wait_loads_but<2>();
