@@ -4,7 +4,7 @@
 
 namespace mtla {
 
-constexpr int kAttnRows = 128;  // query rows of a block
+constexpr int kAttnRows = 128;  // query rows of a block; of a small one half
 constexpr int kXcds = 8;        // workgroup w runs on XCD w % 8
 
 // Pairs of an XCD, and how many of them are side by side (`group`).  A group's blocks go out heaviest first (a block walks the columns
@@ -17,6 +17,19 @@ constexpr int kXcds = 8;        // workgroup w runs on XCD w % 8
 constexpr int attn_group(int pairs, int d_head) {
   const int per = attn_pairs(pairs), about = d_head <= 64 ? 8 : 4, groups = per / about > 1 ? per / about : 1;
   return (per + groups - 1) / groups;
+}
+
+// Rows of a block of the plain form.  Where a unit has one block of 128 or none, the heaviest one's chain is the pass, and half the rows
+// in each wavefront shorten it (every pair of tiles is still read by all wavefronts, so with more blocks than that the LDS is what they
+// wait for).  us a pass, 128 rows / 64: 2048 tokens, 8 heads x 128 (128 blocks of 128 rows) 55.3 / 48.6, 16 heads (256) 60.4 / 55.4, 24 heads (384) 71.6
+// / 68.7, but 3 of 1024 (384) 60.4 / 61.7 and 2 of 2048 (512) 75.6 / 77.5; d_head 64, whose blocks take half the LDS: 4096 x 8 heads (256) 57.3 / 49.1, 2 of
+// 3072 (384) 56.1 / 51.3, 32 of 256 (512) 40.1 / 38.7, s = 1, 1024 blocks 127.7 / 146.6.  Behind tokens of a cache all blocks are heavy: 2 of 512, 16 x 128
+// (128) 50.7 / 45.0, 8 of 128 (128) 117.4 / 114.0, 12 of 128 (192) 150.0 / 159.2; d_head 64, 16 of 128 (128) 63.2 / 55.6, 32 of 128 (256) 81.8 / 79.5.
+// And up to 64 rows the other half of a block would be empty: 64 prompts of 64, 16 x 128 78.4 / 73.6; 48 behind a cache 307 / 299.
+[[gnu::always_inline]] constexpr int attn_rows(int T, int pairs, int d_head, bool behind) {
+  constexpr int kUnits = 256;
+  const long long blocks = (long long)((T + kAttnRows - 1) / kAttnRows) * pairs;
+  return T <= kAttnRows / 2 || blocks <= (d_head <= 64 ? 2 : 1) * (behind ? kUnits / 2 : kUnits) ? kAttnRows / 2 : kAttnRows;
 }
 
 struct AttnBlock {

@@ -349,7 +349,8 @@ struct TileGeom {
 // ((p0 + m0 + 127) / s) / 32 tiles and only the last few have a mask; with the block's own rows as masked tiles, one by
 // one, it was 128 / 32 - (128 / s) / 32 tiles more (two of the 36 a block walks on average at 4096 rows and s = 2).
 //
-// NW wavefronts of 32 query rows each per workgroup.  NW = 4 is what the launcher uses: two workgroups per CU, whose
+// NW wavefronts of 32 query rows each per workgroup (RT = 2 tiles of 16; of 16 where attn_rows takes half a block).  NW = 4 is what the
+// launcher uses: two workgroups per CU, whose
 // wavefronts drift apart so that one multiplies while the other does softmax arithmetic.  What bounds it is the chain
 // of a pair of tiles (operand reads, 80 matrix instructions, the arithmetic of the weights) with two wavefronts per SIMD
 // to overlap, and what lies around the tile loop: matrix pipes busy 41 % (at 820 thousand cycles, the same at any
@@ -357,11 +358,11 @@ struct TileGeom {
 // us with the own rows as masked tiles and one tile per step, now 414 (830 TFLOP/s).
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
-template <int DH, int DR, int NW, bool CONT, bool LAYER>
+template <int DH, int DR, int NW, bool CONT, bool LAYER, int RT>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel(ExplicitArgs a) {
   using G = TileGeom<DH, DR>;
   constexpr int KD = DH / 32, KQ = (DH + DR) / 32, MT = DH / 16;
-  constexpr int NT = 64 * NW, BM = 32 * NW, BN = G::BN, VC = G::VC, RC = G::RC;
+  constexpr int NT = 64 * NW, BM = 16 * RT * NW, BN = G::BN, VC = G::VC, RC = G::RC;
   constexpr int NBUF = 4;                 // tiles in LDS: two pairs
   constexpr int NIK = G::NCK / NW;  // loads per wavefront and region of keys or values
   constexpr int IROWS = 64 * NW / VC;     // rows between a wavefront's chunks of a region
@@ -505,19 +506,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   // They come in with four neighbouring lanes to 64 bytes of a row and change places through the wavefront's part of the buffers
   // that the second pair of tiles will take: in the operand layout neighbouring lanes are 16 rows, which a unit's address path takes one
   // lane a cycle (66 cycles a load, 10 thousand a block; now 2.5).  Stores likewise, see below.
-  u32x4_t qf[2][KQ];
-  float4_t neg_ref[2];        // - reference of the row's weights, where the logits' sums start
-  float l_run[2];
-  float4_t acc[2][MT];
-  int bound[2];               // columns open to the lane's rows
+  u32x4_t qf[RT][KQ];
+  float4_t neg_ref[RT];        // - reference of the row's weights, where the logits' sums start
+  float l_run[RT];
+  float4_t acc[RT][MT];
+  int bound[RT];               // columns open to the lane's rows
   {
     int ln = lane;
     asm volatile("" : "+v"(ln));              // (what depends on it is formed here, not kept in registers over the tile loop)
     const int qr = ln >> 2, qc = ln & 3;      // row and 16 bytes of the 64 that a load brings of it
-    u32x4_t qd[2][KQ], kd[2][KQ], vd[2][KD];
+    u32x4_t qd[RT][KQ], kd[RT][KQ], vd[RT][KD];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int m = m0 + 32 * wv + 16 * rt + qr, mr = m < len ? m : len - 1;
+    for (int rt = 0; rt < RT; ++rt) {
+      const int m = m0 + 16 * RT * wv + 16 * rt + qr, mr = m < len ? m : len - 1;
       const size_t row = (size_t)b * T + mr;
       const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (row * nh + h) * DH + 8 * qc;
       const uint16_t* qrp = reinterpret_cast<const uint16_t*>(a.q_rope) + (row * nh + h) * DR + 8 * qc;
@@ -537,9 +538,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     unsigned char* to = own_lds + qr * 64 + ((qc ^ swz_rows16<4>(qr)) << 4);
     const unsigned char* from = own_lds + l16 * 64;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
       __builtin_amdgcn_sched_barrier(0);
-      const int m = m0 + 32 * wv + 16 * rt + l16;
+      const int m = m0 + 16 * RT * wv + 16 * rt + l16;
       bound[rt] = (p0 + (m < len ? m : len - 1)) / s;
       float e = 0.f;
 #pragma unroll
@@ -567,8 +568,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the barrier behind which those buffers are filled
   }
   // columns open to all of the wavefront's rows, and to any of them
-  const int all_below = (p0 + m0 + 32 * wv) / s;
-  const int none_from = (p0 + m0 + 32 * wv + 31) / s;
+  const int all_below = (p0 + m0 + 16 * RT * wv) / s;
+  const int none_from = (p0 + m0 + 16 * RT * wv + 16 * RT - 1) / s;
 
   // Two tiles per step: while one pair is multiplied the other is on its way (four buffers), one wait and one barrier for
   // both, and the matrix products of one tile beside the softmax arithmetic of the other.
@@ -599,7 +600,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
 
     // ---- S^T[col, row] - reference = [k | k^R][col, :] . [q | q^R][row, :]: the reads of one group of K
     // steps are in flight while the group before is multiplied
-    float4_t sacc[2][2][2];  // [tile][row tile][16 columns]
+    float4_t sacc[2][RT][2];  // [tile][row tile][16 columns]
     constexpr int KG = 2, NG = 2 * KQ / KG;  // K steps per group, groups of both tiles
     static_assert(KQ % KG == 0 || KQ % 2 == 1, "groups");
     u32x4_t kf[2][KG][2];
@@ -623,7 +624,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-          for (int rt = 0; rt < 2; ++rt) {
+          for (int rt = 0; rt < RT; ++rt) {
             const int x = i * KG + j, u = x / KQ, kk = x % KQ;
             sacc[u][rt][sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, kf[i & 1][j][sb]),
                                                                      __builtin_bit_cast(f16x8_t, qf[rt][kk]),
@@ -642,7 +643,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
+        for (int rt = 0; rt < RT; ++rt) {
           const int d = bound[rt] - (BN * (t + u) + 4 * g);
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb)
@@ -658,13 +659,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     // ones, and an integer maximum takes three operands without first quieting each.
     int top = 0;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const float x = sacc[i >> 4][(i >> 3) & 1][(i >> 2) & 1][i & 3];
+    for (int i = 0; i < 16 * RT; ++i) {
+      const float x = sacc[i / (8 * RT)][(i >> 3) % RT][(i >> 2) & 1][i & 3];
       top = max(top, __float_as_int(x));
     }
     if (__any(top > __float_as_int(kRebase))) {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
+      for (int rt = 0; rt < RT; ++rt) {
         float up = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 16; ++i) up = fmaxf(up, sacc[i >> 3][rt][(i >> 2) & 1][i & 3]);
@@ -693,15 +694,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
       }
       return pb;
     };
-    auto product = [&](int mt, const u32x4_t& v, const u32x4_t (&pb)[2]) {  // O^T[d, row] += V^T[d, col] P^T[col, row]
+    auto product = [&](int mt, const u32x4_t& v, const u32x4_t (&pb)[RT]) {  // O^T[d, row] += V^T[d, col] P^T[col, row]
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
         acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, v), __builtin_bit_cast(f16x8_t, pb[rt]),
                                                              acc[rt][mt], 0, 0, 0);
     };
-    u32x4_t pb0[2], pb1[2];
+    u32x4_t pb0[RT], pb1[RT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) pb0[rt] = weights(0, rt);
+    for (int rt = 0; rt < RT; ++rt) pb0[rt] = weights(0, rt);
 #pragma unroll
     for (int mt = VPRE; mt < MT; ++mt) vf[mt] = read_v(0, mt);
     // the weights of the second tile beside the first tile's product
@@ -710,7 +711,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
     for (int mt = 0; mt < VPRE; ++mt) product(mt, vf[mt], pb0);
 #pragma unroll
     for (int mt = 0; mt < VPRE; ++mt) vf[mt] = read_v(1, mt);
-    pb1[1] = weights(1, 1);
+    if constexpr (RT == 2) pb1[1] = weights(1, 1);
 #pragma unroll
     for (int mt = VPRE; mt < MT; ++mt) product(mt, vf[mt], pb0);
 #pragma unroll
@@ -726,11 +727,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_explicit_kernel
   asm volatile("" : "+v"(ln));
   unsigned char* leave = lds + (n_tiles > 0 ? (~(n_tiles - 1) & 2) : 0) * G::BYTES + wv * kOwn;
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
     constexpr int ES = LAYER ? 2 : 4, RB = DH * ES, PPR = RB / 16;  // bytes of a row, 16-byte pieces; piece j of row i sits at j ^ (i % 16), in RB
     static_assert(16 * RB <= kOwn && PPR >= 8, "the rows fit");
     const float l = quarter_reduce(l_run[rt], LaneSum());
-    const int mt0 = m0 + 32 * wv + 16 * rt;
+    const int mt0 = m0 + 16 * RT * wv + 16 * rt;
     const bool live = mt0 + (ln & 15) < len;  // rows past the sequence's length are zeros, whatever their inputs held
     const float inv = live ? 1.f / l : 0.f;
     constexpr int SW = PPR < 16 ? PPR - 1 : 15;
@@ -758,15 +759,21 @@ template <int DH, int DR>
 hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
   constexpr int NW = 4;
   static_assert(32 * NW == kAttnRows, "rows of a block");
-  const int n_blocks = (a.T + kAttnRows - 1) / kAttnRows, pairs = a.n_heads * a.batch;
+  const int pairs = a.n_heads * a.batch, rows = attn_rows(a.T, pairs, DH, a.past_pitch > 0);
+  const int n_blocks = (a.T + rows - 1) / rows;
   ExplicitArgs x = a;
   x.group = attn_group(pairs, DH);
   const dim3 grid((unsigned)n_blocks * (unsigned)(attn_pairs(pairs) * kXcds));
   const bool layer = a.q_f16 != 0;  // comes with out16
   if (layer != (a.out16 != nullptr) || (layer && !a.pos0)) return hipErrorInvalidValue;
-  if (layer) launch_timed(attn_explicit_kernel<DH, DR, NW, true, true>, grid, dim3(64 * NW), 0, st, ev, x);
-  else if (a.pos0) launch_timed(attn_explicit_kernel<DH, DR, NW, true, false>, grid, dim3(64 * NW), 0, st, ev, x);
-  else launch_timed(attn_explicit_kernel<DH, DR, NW, false, false>, grid, dim3(64 * NW), 0, st, ev, x);
+  auto launch = [&](auto cont, auto lay) {
+    constexpr bool C = decltype(cont)::value, L = decltype(lay)::value;
+    if (rows == kAttnRows / 2) launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 1>, grid, dim3(64 * NW), 0, st, ev, x);
+    else launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 2>, grid, dim3(64 * NW), 0, st, ev, x);
+  };
+  if (layer) launch(std::true_type(), std::true_type());
+  else if (a.pos0) launch(std::true_type(), std::false_type());
+  else launch(std::false_type(), std::false_type());
   return hipGetLastError();
 }
 

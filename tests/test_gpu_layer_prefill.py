@@ -108,6 +108,14 @@ def test_layer_prefill_small_products(lens, pieces, n_heads, d_model):
     print(f"layer prefill, small products: max abs err {worst:.2e}")
 
 
+def test_layer_prefill_blocks_of_128_rows():
+    # enough row blocks behind a cache for 128 rows each; the first piece takes blocks of 64
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="lp_rows", batch=5, d_model=64, n_heads=32, d_head=64, r=64, d_rope=32, stride=2, prefix=332, steps=0,
+                                           seed=89)
+    worst = _feed(wl, [332, 190, 23, 331, 260], [70, 130, 132])
+    print(f"layer prefill, blocks of 128 rows: max abs err {worst:.2e}")
+
+
 def test_layer_prefill_streamed_products():
     # enough rows and columns for the streamed 256 x 256 tiles in the projections (every way out) and in W_O, whose rows past a
     # sequence's length are zeros inside a tile, at a tile's end and over whole tiles;

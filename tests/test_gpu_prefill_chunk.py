@@ -91,6 +91,15 @@ def test_chunked_prefill_other_shapes_with_decode_steps_between(n_heads, d_head,
     print(f"chunk / decode / chunk, stride {stride}: max abs err {worst:.2e}")
 
 
+@pytest.mark.parametrize("n_heads,d_head,r,d_rope", [(32, 64, 64, 32), (16, 128, 128, 64)])
+def test_chunked_prefill_blocks_of_128_rows(n_heads, d_head, r, d_rope):
+    # enough blocks behind a cache for 128 rows each: pieces of 130 and of 132 rows; the first, of 70, takes blocks of 64
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="pf_chunk_rows", batch=5, d_model=64, n_heads=n_heads, d_head=d_head, r=r, d_rope=d_rope, stride=2,
+                                           prefix=332, steps=0, seed=77)
+    worst = _feed(wl, [332, 190, 23, 331, 260], [70, 130, 132])
+    print(f"chunked prefill, {n_heads} heads x {d_head}: max abs err {worst:.2e}")
+
+
 def test_chunked_prefill_full_size_sampled_rows():
     # the prefill workload (batch 8, T = 4096, 16 heads x 128, r = 512, s = 2) in pieces of 1024, one sequence
     # shorter; the oracle evaluates sampled rows of two sequences, among them the first and last of every piece

@@ -55,6 +55,16 @@ def test_plain_form(n_heads, d_head, r, d_rope, stride, lens):
     _check(lens, n_heads, d_head, r, d_rope, stride, False)
 
 
+@pytest.mark.parametrize("n_heads,d_head,r,d_rope,stride,lens,which", [
+    (32, 128, 256, 64, 2, (64, 65, 66, 127, 130, 255, 256, 257), (1, 3, 4, 6, 7)),  # as above, with enough blocks for 128 rows each
+    (32, 64, 64, 32, 1, (32, 33, 64, 65, 128, 129, 160, 1), (1, 4, 5, 6)),
+    (8, 128, 128, 64, 2, (64, 63, 1) + (64,) * 37, (0, 1, 2, 39)),                  # many, but of 64 rows: one small block
+])
+def test_plain_form_rows_of_a_block(n_heads, d_head, r, d_rope, stride, lens, which):
+    lens = lens if d_head == 128 else lens + tuple(reversed(lens))
+    _check(lens, n_heads, d_head, r, d_rope, stride, False, which=which)
+
+
 def test_plain_form_paired_blocks_and_large_products():
     # more than 512 pairs of row blocks, an odd number of blocks (the last one has no partner); the key and value products take
     # their largest tiles, with most sequences' rows left out
