@@ -157,9 +157,33 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   constexpr int HA0 = (G::per_simd > 1 ? 144 : 0) / (4 * NT * KC), HA = HA0 < 1 ? 1 : (HA0 < HPW ? HA0 : HPW);
   u32x4_t wf[HA][NT][KC];
   const int d0 = 16 * NT * wv;  // the wavefront's output columns
+  // It comes with four neighbouring lanes to 64 bytes of a row and changes lanes behind the walk, in the last of the wavefront's area: in
+  // the operand's layout, sixteen rows to sixteen lanes, a load is 66 cycles of the unit's address path, which the walk's rows wait for, this
+  // one 24.  Where the walk fills that path or W_V^(h) is 64 KB; elsewhere the change costs more (us a step, operand's layout / changed: r = 256,
+  // 8 heads x 64, 16 sequences of 528 slots, eight wavefronts 11.59 / 11.44; 16 x 128, 8 of 400, 12.47 / 12.02, 16 of 300 11.44 / 11.14; but 8 x 64 on four
+  // wavefronts, 350 slots, 10.75 / 10.91, two heads a workgroup 10.46 / 10.94, r = 128 9.15 / 9.38, r = 512 17.8 / 18.1).
+  constexpr bool kTurn = R == 256 && HPW == 1 && (NW == 8 || DH == 128);
+  static_assert(!kTurn || G::planes + 2 * HPW * G::plane + KC * 1024 <= 2 * G::tile, "behind the sums and planes");
+  const int w_row = kTurn ? lane >> 2 : l16, w_piece = kTurn ? lane & 3 : g;
+  auto turn_w = [&](int hp) {
+    if constexpr (kTurn) {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      unsigned char* at = area + 2 * G::tile - KC * 1024;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) *reinterpret_cast<u32x4_t*>(at + 1024 * kk + (ln >> 2) * 64 + (((ln & 3) ^ swz_rows16<4>(ln >> 2)) << 4)) = wf[hp % HA][i][kk];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) wf[hp % HA][i][kk] = *reinterpret_cast<const u32x4_t*>(at + 1024 * kk + (ln & 15) * 64 + (((ln >> 4) ^ swz_rows16<4>(ln & 15)) << 4));
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  };
   auto load_w = [&](int hp) {
     const int h = h0 + hp;
-    const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.w_uv) + ((size_t)(h < a.n_heads ? h : a.n_heads - 1) * DH + d0 + l16) * R + 8 * g;
+    const uint16_t* wp = reinterpret_cast<const uint16_t*>(w.w_uv) + ((size_t)(h < a.n_heads ? h : a.n_heads - 1) * DH + d0 + w_row) * R + 8 * w_piece;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -293,6 +317,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
   if (multiplies) {
 #pragma unroll
     for (int hp = 1; hp < HA; ++hp) load_w(hp);
+    if (kEarly) turn_w(0);  // (landed during the walk)
   }
   __syncthreads();
 #pragma unroll
@@ -336,6 +361,7 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
     float4_t o[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) o[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    if (!kEarly || hp > 0) turn_w(hp);
     const unsigned char* pl = smem + G::planes + (2 * hp + (l16 & 1)) * G::plane + 16 * g;
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
