@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "bounds.h"
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -298,14 +299,57 @@ __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
 // have been multiplied, the values in front of the keys' product.  us of the call, 8 heads, r = 256, s = 2, ahead with one workgroup a unit / so: 8
 // prompts of 512 tokens 128 / 107, 12 of 777 333 / 272, 10 of 128 (640 workgroups) 42.1 / 39.6; 4 heads, 3 of 700 (528) 52.0 / 52.8, with s = 1
 // 60.9 / 69.8; 8 heads, one of 700 (352) 36.9 / 41.2: kAheadMost.  (Beyond it one prompt of 4096 alone is slower so, 343 / 355.)
-// Three sequences of up to 777 tokens, 8 heads x 64: 29.6 us, now 22.9; the vector-ALU kernel over absorbed queries took 353 us
+// With RT = 2 queries and tiles come in as whole rows, 16 bytes a lane, and change lanes in the wavefront's part of LDS: loaded straight into
+// the operands' layout (16 rows for neighbours; the values 4 bytes a lane) a tile keeps the address path of the unit for some 650 cycles
+// beside its 1280 of products, four wavefronts side by side.  us of the append and the parallel form, 8 heads x 64, r = 256: 3 prompts of 500 to 777 tokens
+// 49.6 -> 46.2, 2 of up to 900 with the latent output 92.2 -> 82.7; 4 heads, r = 64, 4 of 1024 40.5 -> 37.8.  Heads of 128 load as before: the
+// turns lengthen the chain of a wavefront that has its SIMD for itself (4 heads, 3 of 700, s = 1 70.3 / 75.5; 8 heads, 200 of 16 70.0 / 73.9; one
+// of 4096 365 / 339 though).
+// Three sequences of up to 777 tokens, 8 heads x 64: the vector-ALU kernel over absorbed queries took 353 us
 // (and 45 + 67 us for the absorption and the value projection, which this form does not have).
 // ---------------------------------------------------------------------------
+// 16 rows of COLS floats on their way: load i of a lane is piece 64 i + lane of them, 16 bytes each.
+template <int COLS>
+struct RowsF32 {
+  static constexpr int N = COLS / 16, PPR = COLS / 4, RS = kWave / PPR;  // loads, pieces a row, rows a load
+  f32x4 f[N];
+  // row i is the one min(i, last) steps behind `first`
+  __device__ __forceinline__ void request(int lane, const float* first, size_t step, int last) {
+    const int row0 = lane / PPR, col = 4 * (lane % PPR);
+    if (last >= 15) {
+      const float* p = first + (size_t)(uint32_t)row0 * step + col;
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[i] = ld4(p + (size_t)(RS * i) * step);
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[i] = ld4(first + (size_t)(uint32_t)(row0 + RS * i < last ? row0 + RS * i : last) * step + col);
+    }
+  }
+  // In LDS piece j of row i sits at j ^ swz_rows16(i).  A load's rows and a lane's pieces differ in bits of their own, so that either's places
+  // are one exclusive or from the first.
+  __device__ __forceinline__ void put(int lane, unsigned char* to) const {
+    const int row0 = lane / PPR, at = row0 * (COLS * 4) + 16 * ((lane % PPR) ^ swz_rows16<PPR>(row0));
+#pragma unroll
+    for (int i = 0; i < N; ++i) *reinterpret_cast<f32x4*>(to + (at ^ (16 * swz_rows16<PPR>(RS * i))) + RS * i * (COLS * 4)) = f[i];
+  }
+  static __device__ __forceinline__ f32x4 operand(const unsigned char* from, int lane, int c) {  // columns 16 c + 4 (lane / 16) .. + 3 of row lane % 16
+    const int row = lane & 15, at = row * (COLS * 4) + 16 * ((lane >> 4) ^ swz_rows16<PPR>(row));
+    return *reinterpret_cast<const f32x4*>(from + (at ^ (64 * c)));
+  }
+  __device__ __forceinline__ void put_plain(int lane, float (*to)[COLS + 4]) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) *reinterpret_cast<f32x4*>(&to[lane / PPR + RS * i][4 * (lane % PPR)]) = f[i];
+  }
+};
+
 constexpr size_t kAheadMost = 576;  // workgroups of a launch over heads of 128
 template <int DH, int DR, int DV, int RT, bool AHEAD>
 __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_kernel(ExplicitArgs a) {
   constexpr int KE = (DH + DR) / 16, KC = DH / 16, NV = DV / 16;
-  __shared__ float s_o[kWaves][16][DV + 4];
+  // the wavefronts' values (rows of DV + 4, so that 4-byte reads of four rows spread over the banks), in the end their sums; their keys
+  constexpr bool kTurned = RT > 1;
+  __shared__ __attribute__((aligned(16))) float s_o[kWaves][16][DV + 4];
+  __shared__ __attribute__((aligned(16))) float s_k[kTurned ? kWaves : 1][kTurned ? 16 * (DH + DR) : 4];
   __shared__ float s_m[kWaves][16 * RT], s_l[kWaves][16 * RT];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a tile is the same for all lanes: its branches and addresses are scalar)
@@ -335,16 +379,18 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
   const float* vx = latent ? reinterpret_cast<const float*>(a.cprime) + (size_t)b * a.T * a.r + slice * DV
                            : reinterpret_cast<const float*>(a.vx) + (size_t)b * a.T * kpitch + h * DH;
   f32x4 qf[RT][KE];
+  if constexpr (!kTurned) {
 #pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    const int m_lane = (m0[t] < 0 ? 0 : m0[t]) + l16, m = m_lane < len ? m_lane : len - 1;
-    const size_t qr = ((size_t)b * a.T + m) * a.n_heads + h;
-    const float* q = reinterpret_cast<const float*>(a.q) + qr * DH + 4 * g;
-    const float* qrope = reinterpret_cast<const float*>(a.q_rope) + qr * DR + 4 * g;
+    for (int t = 0; t < RT; ++t) {
+      const int m_lane = (m0[t] < 0 ? 0 : m0[t]) + l16, m = m_lane < len ? m_lane : len - 1;
+      const size_t qr = ((size_t)b * a.T + m) * a.n_heads + h;
+      const float* q = reinterpret_cast<const float*>(a.q) + qr * DH + 4 * g;
+      const float* qrope = reinterpret_cast<const float*>(a.q_rope) + qr * DR + 4 * g;
 #pragma unroll
-    for (int c = 0; c < KC; ++c) qf[t][c] = ld4(q + 16 * c);
+      for (int c = 0; c < KC; ++c) qf[t][c] = ld4(q + 16 * c);
 #pragma unroll
-    for (int c = KC; c < KE; ++c) qf[t][c] = ld4(qrope + 16 * (c - KC));
+      for (int c = KC; c < KE; ++c) qf[t][c] = ld4(qrope + 16 * (c - KC));
+    }
   }
   float m[RT], l[RT];
   f32x4 acc[RT][NV];
@@ -445,7 +491,61 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
 #pragma unroll
       for (int c = 0; c < KE; ++c) qf[t][c] *= a.scale_log2;
   };
-  if constexpr (AHEAD) {
+  if constexpr (kTurned) {
+    unsigned char* lds_k = reinterpret_cast<unsigned char*>(s_k[wv]);
+    unsigned char* lds_r = lds_k + 16 * DH * 4;
+    float (*lds_v)[DV + 4] = s_o[wv];
+    RowsF32<DH> next_k;
+    RowsF32<DR> next_r;
+    RowsF32<DV> next_v;
+    auto request = [&](int tile) {
+      const bool shared = tile < sh_tiles;
+      const int first = shared ? src(tile, 0) : (tile == sh_tiles ? m0[0] : m0[RT - 1]), step = shared ? s : 1;
+      const int last = shared ? n_sh - 1 - 16 * tile : len - 1 - first;
+      next_k.request(lane, kx + (size_t)first * kpitch, step * kpitch, last);
+      next_r.request(lane, kr + (size_t)first * DR, (size_t)step * DR, last);
+      next_v.request(lane, vx + (size_t)first * vpitch, step * vpitch, last);
+    };
+    auto operand = [&](int c) { return c < KC ? RowsF32<DH>::operand(lds_k, lane, c) : RowsF32<DR>::operand(lds_r, lane, c - KC); };
+    if (wv < tiles) {
+      RowsF32<DH> q[RT];
+      RowsF32<DR> q_rope[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int first = m0[t] < 0 ? 0 : m0[t];
+        const size_t row = ((size_t)b * a.T + first) * a.n_heads + h;
+        q[t].request(lane, reinterpret_cast<const float*>(a.q) + row * DH, kpitch, len - 1 - first);
+        q_rope[t].request(lane, reinterpret_cast<const float*>(a.q_rope) + row * DR, (size_t)a.n_heads * DR, len - 1 - first);
+      }
+      request(wv);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        q[t].put(lane, lds_k);
+        q_rope[t].put(lane, lds_r);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < KE; ++c) qf[t][c] = operand(c);
+        __builtin_amdgcn_wave_barrier();
+      }
+      to_log2();
+      for (int tile = wv; tile < tiles; tile += kWaves) {
+        Tile tl;
+        next_k.put(lane, lds_k);
+        next_r.put(lane, lds_r);
+        next_v.put_plain(lane, lds_v);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < KE; ++c) tl.k[c] = operand(c);
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) tl.v[n][v] = lds_v[4 * g + v][16 * n + l16];
+        __builtin_amdgcn_wave_barrier();
+        if (tile + kWaves < tiles) request(tile + kWaves);
+        multiply(tl, tile, []() {});
+      }
+    }
+  } else if constexpr (AHEAD) {
     auto request = [&](Tile& t, int tile) {
       request_k(t, tile);
       request_v(t, tile);

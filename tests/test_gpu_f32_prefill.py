@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
     (33, (33, 32, 31), 3, 64, 256, 64, 3),        # three blocks: the middle one alone; columns of the product not a multiple of 64
     (65, (65, 64, 48), 8, 64, 256, 32, 4),
     (130, (130, 97, 0), 4, 32, 512, 64, 16),      # an empty sequence, the widest latent, the longest stride of the matrix-core append
+    (49, (49, 47, 34), 2, 32, 64, 32, 1),         # the narrowest rows: eight of them a load
     (81, (81, 17, 80), 2, 128, 64, 64, 2),        # one block a workgroup
     (500, (500, 479, 3), 8, 128, 128, 32, 2),     # heads of 128: more workgroups than have their next tile ahead (24 x 32)
     (290, (290, 273, 16), 16, 128, 64, 64, 1),    # 48 x 19
