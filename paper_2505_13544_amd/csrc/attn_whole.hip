@@ -388,11 +388,6 @@ __global__ __launch_bounds__(NW * kWave, (WholeGeom<R, DR, HPW, NW>::per_simd)) 
 // ---------------------------------------------------------------------------
 constexpr int kStep = 16 * kWaves;  // slots of a step
 
-template <int CTRL>
-__device__ __forceinline__ float row_rotated(float v) {  // inside 16 lanes
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + CTRL, 0xf, 0xf, true));
-}
-
 // DH > 0: the whole step as one launch (heads of that width).  Every workgroup of a sequence forms the token's slot and its own head's
 // query for itself, with the sums in the order of append_step_block and absorb_f32_block; nobody waits for anybody: the sequence's
 // workgroups count themselves when they have read its state, and the last one writes it.

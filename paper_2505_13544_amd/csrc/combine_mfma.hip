@@ -8,13 +8,15 @@
 //     out^T[d, row] = W_V^(h)[d, :] . o~[row, :]^T          (M = d_h, N = 16 rows, K = r)
 // A workgroup owns one head and a run of 16-row tiles.  Its W_V^(h) is brought into LDS at the top, by loads that take
 // whole rows of it (straight into the A-operand layout of v_mfma_f32_16x16x32_bf16 a request touches 64 bytes of each of 16
-// rows: 128 KB took 4 us that way, beside which everything else of the kernel waited), each wavefront the quarter of the d_h
+// rows: 128 KB took 4 us that way, beside which everything else of the kernel waited), each wavefront the share of the d_h
 // rows that it multiplies.  Per tile, 16 threads per row merge the row's partials (all
 // requests of up to PB pieces go out together, before the normaliser is known), write the
 // normalised latent row where the caller wants it, and park it in LDS as two bf16 planes
-// (hi + lo, an almost-fp32 value) that the four wavefronts read back as the B operand.
+// (hi + lo, an almost-fp32 value) that the wavefronts read back as the B operand.
 // At r = 512, d_h = 128: 256 sequences, 16 heads 9.4 us, now 8.8; 1000 sequences 29.3, now 24.5; 8 sequences of 33 pieces,
-// 32 heads 9.1, now 7.0.
+// 32 heads 9.1, now 7.0.  There the 128 KB leave a unit one workgroup: with eight wavefronts, two a SIMD, to cover each other's waits, and fewer
+// products one behind the other, a step of 256 sequences of 512 to 4096 slots' tokens, 16 heads, took 85.3 us, now 84.1; 200 of 300, 33.8, now 32.7; 8 heads,
+// 128 of 2000, 43.3, now 42.2; 8 of 32768, s = 4, 32 heads, 37.1, now 36.2.
 #include "bounds.h"
 #include "lds_stream.h"
 #include "mtla_device.h"
@@ -79,22 +81,24 @@ __device__ __forceinline__ Pieces pieces_of_row(const CombineArgs& a, int row, i
 // a piece then weighs l_p 2^(m_p - m*) instead of 2^(m_p - m*).
 // PS = few rows, their pieces split over the wavefronts (at r = 128 and 64 over halves and quarters of them: a lane takes four
 // columns): one row per workgroup (RPT = 1), the weighted sums added through LDS.  One round of requests instead of one per PB pieces, and four times the
-// workgroups, each with a quarter of the partials to bring in and to add up.
+// workgroups, each wavefront with its share of the partials to bring in and to add up.
 // HF = the head is the fast grid index: the workgroups that share an XCD (and its L2) then share the
 // W_V^(h) of a few heads instead of each XCD fetching all of them.
+// NW = wavefronts: eight where the weights leave a unit one workgroup (four rows a workgroup are merged by a wavefront each).
 template <int R, int DH, int RPT, bool PS>
 struct CombineLds {  // [W_V^(h)][hi and lo planes of the rows][piece split: the other groups' sums]
-  static constexpr int TPR = !PS ? kBlock / RPT : (R / 4 < kWave ? R / 4 : kWave), groups = PS ? kBlock / TPR : 1;  // threads merging one row
+  static constexpr int NW = R == 512 && DH == 128 && (PS || RPT == 16) ? 8 : 4, threads = NW * kWave;
+  static constexpr int TPR = !PS ? threads / RPT : (R / 4 < kWave ? R / 4 : kWave), groups = PS ? threads / TPR : 1;  // threads merging one row
   static constexpr int planes = DH * R * 2, red = planes + 2 * RPT * R * 2, bytes = red + (groups - 1) * R * 4;
   static_assert(bytes <= 160 * 1024, "LDS of one compute unit");
 };
 
 template <int R, int DH, int RPT, bool PF16, bool PS = false, bool HF = PS>
-__global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int tiles_per_wg) {
+__global__ __launch_bounds__((CombineLds<R, DH, RPT, PS>::threads)) void combine_mfma_kernel(CombineArgs a, int tiles_per_wg) {
   static_assert(!PS || RPT == 1, "piece split: one row per workgroup");
   using L = CombineLds<R, DH, RPT, PS>;
   constexpr int KK = R / 32;         // K steps
-  constexpr int NT = DH / 64;        // 16-row output tiles per wavefront (a quarter of d_h)
+  constexpr int DW = DH / L::NW, NT = DW / 16;  // output dims of a wavefront, 16-row tiles
   constexpr int TPR = L::TPR;        // threads merging one row (piece split: a group of NG)
   constexpr int NG = L::groups;
   constexpr int CJ = R / (4 * TPR);  // float4 pieces of a latent row per thread
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   constexpr int PC = R / 8;          // 16-byte pieces of a row
   // partials requested together per thread: what 128 registers hold, at most 16 (12 with the pieces split: 48 a row; in the
   // dense case, whose rows have a few, 4 or 8: requests beyond a row's pieces are reloads, but not free)
-  constexpr int kFit = 128 / (CJ * (PF16 ? 2 : 4)), kMost = PS ? 12 : (RPT < kTileRows ? 16 : (R >= 512 ? 4 : 8));
+  constexpr int kFit = 128 / (CJ * (PF16 ? 2 : 4)), kMost = PS ? 48 / L::NW : (RPT < kTileRows ? 16 : (R >= 512 ? 4 : 8));
   constexpr int PB = kFit < kMost ? kFit : kMost;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // rows in LDS: piece p of row i at place p ^ swz(i), so that 16 rows' reads of one piece spread over the banks
@@ -122,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   const int tid0 = threadIdx.x;
   int ps_p0 = 0, ps_p1 = 0, ps_total = 0;
   if ((PS || HF) && a.n_persistent > 0) {
-    const int row0 = PS ? t0 : RPT * t0 + tid0 / (kBlock / RPT);
+    const int row0 = PS ? t0 : RPT * t0 + tid0 / TPR;
     const int rc = row0 < rows ? row0 : rows - 1;
     ps_p0 = a.tile_prefix[rc];
     ps_p1 = a.tile_prefix[rc + 1];
@@ -133,9 +137,9 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
   if (a.out) {
     typedef const __attribute__((address_space(1))) void* global_ptr;
     typedef __attribute__((address_space(3))) void* lds_ptr;
-    constexpr int kBytes = DH / 4 * R * 2;
+    constexpr int kBytes = DW * R * 2;
     const int uw = __builtin_amdgcn_readfirstlane(wv);
-    const uint16_t* wsrc = reinterpret_cast<const uint16_t*>(a.w_uv) + ((size_t)h * DH + uw * (DH / 4)) * R;
+    const uint16_t* wsrc = reinterpret_cast<const uint16_t*>(a.w_uv) + ((size_t)h * DH + uw * DW) * R;
 #pragma unroll
     for (int i = 0; i < kBytes / 1024; ++i) {
       const int at = 64 * i + lane, row = at / PC;
@@ -264,29 +268,46 @@ __global__ __launch_bounds__(kBlock) void combine_mfma_kernel(CombineArgs a, int
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weights have landed
     __syncthreads();
 
-    // ---- out^T[d, row] for this wavefront's d_h / 4 output rows
+    // ---- out^T[d, row] for this wavefront's output dims
     float4_t o[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) o[nt] = float4_t{0.f, 0.f, 0.f, 0.f};
-    const int rb = l16 % RPT;
-    const uint16_t* brow = sA + rb * R;
-    const uint16_t* wrow = reinterpret_cast<const uint16_t*>(smem) + (wv * (DH / 4) + l16) * R;  // (16 rows on, the same swizzle)
+    const uint16_t* wrow = reinterpret_cast<const uint16_t*>(smem) + (wv * DW + l16) * R;  // (16 rows on, the same swizzle)
+    if constexpr (RPT <= 8) {  // the hi planes in columns 0 to 7, the lo planes in the others: one product, half the reads
+      const int rb = l16 % RPT;
+      const uint16_t* brow = sA + rb * R + (l16 >> 3) * RPT * R;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const int pb_ = 8 * ((4 * kk + g) ^ swz_rows16<PC>(rb)), pw = 8 * ((4 * kk + g) ^ swz_rows16<PC>(l16));
-      const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + pb_));
-      const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + RPT * R + pb_));
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8_t b = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + 8 * ((4 * kk + g) ^ swz_rows16<PC>(rb))));
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(wrow + 16 * nt * R + pw));
-        o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bh, o[nt], 0, 0, 0);
-        o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bl, o[nt], 0, 0, 0);
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(wrow + 16 * nt * R + 8 * ((4 * kk + g) ^ swz_rows16<PC>(l16))));
+          o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, b, o[nt], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[nt][v] += row_rotated<8>(o[nt][v]);
+    } else {
+      const uint16_t* brow = sA + l16 * R;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const int at = 8 * ((4 * kk + g) ^ swz_rows16<PC>(l16));
+        const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + at));
+        const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(brow + RPT * R + at));
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8_t wa = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(wrow + 16 * nt * R + at));
+          o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bh, o[nt], 0, 0, 0);
+          o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, bl, o[nt], 0, 0, 0);
+        }
       }
     }
-    // lane holds row l16 of the tile, output dims wv*(d_h/4) + 16nt + 4g .. +3
+    // lane holds row l16 of the tile, output dims wv * DW + 16nt + 4g .. +3
     const int orow = RPT * t + l16;
     if (l16 < RPT && orow < rows) {
-      float* dst = a.out + ((size_t)orow * a.n_heads + h) * DH + wv * (DH / 4) + 4 * g;
+      float* dst = a.out + ((size_t)orow * a.n_heads + h) * DH + wv * DW + 4 * g;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<float4_t*>(dst + 16 * nt) = o[nt];
     }
@@ -300,7 +321,7 @@ hipError_t launch_one(const CombineArgs& a, const dim3& grid, int tiles_per_wg, 
   static DeviceSet lds_allowed;
   const hipError_t e = allow_lds(&combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>, smem, lds_allowed);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>), grid, dim3(kBlock), smem, st, a, tiles_per_wg);
+  hipLaunchKernelGGL((combine_mfma_kernel<R, DH, RPT, PF16, PS, HF>), grid, dim3(CombineLds<R, DH, RPT, PS>::threads), smem, st, a, tiles_per_wg);
   return hipGetLastError();
 }
 

@@ -116,6 +116,10 @@ __device__ __forceinline__ float group_reduce(float v, Op op) {
   }
   return v;
 }
+template <int CTRL>
+__device__ __forceinline__ float row_rotated(float v) {  // inside 16 lanes
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + CTRL, 0xf, 0xf, true));
+}
 // Over the four lanes l16, l16 + 16, + 32, + 48 (the lanes that share a row or column of a matrix tile).
 template <class Op>
 __device__ __forceinline__ float quarter_reduce(float v, Op op) {

@@ -47,6 +47,15 @@ def test_pieces_dealt_to_parts_of_a_wavefront(r, schedule):
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32 if schedule == 1 else 64, decode_schedule=schedule)
 
 
+@pytest.mark.parametrize("batch,schedule", [(1, 2), (3, 1), (16, 2), (65, 1), (67, 2)])
+def test_wide_merge_of_eight_wavefronts(batch, schedule):
+    # r = 512 with heads of 128: a row a workgroup and sixteen, the last tile nearly empty, rows with no and with more than one round of pieces
+    plen = np.array([400, 1, 65] * 23, np.int32)[:batch]
+    wl = W.WORKLOADS["speech_bf16"].scaled(name=f"merge8_{batch}", batch=batch, d_model=96, n_heads=3, d_head=128, r=512, d_rope=64, stride=1,
+                                           prefix=(1, 400), steps=1, seed=85)
+    H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=32 if schedule == 1 else 64, decode_schedule=schedule)
+
+
 def test_reference_moves_between_steps():
     # logits far apart: the weights' reference moves from step to step of one chunk; chunks of one step never move theirs
     wl = W.WORKLOADS["speech_bf16"].scaled(name="split_far", batch=3, d_model=96, n_heads=8, d_head=64, r=256, d_rope=32, stride=1,
