@@ -8,9 +8,9 @@
 // d_h + r value columns each.  The weights of tile t + 1 are formed between the barrier that makes those of tile t
 // visible and the next one, so the matrix instructions of one tile cover the arithmetic of the other.
 // With a pass of the plain kernel for every d_h of the r columns (the logits formed r / d_h + 1 times: 3200 flop per pair
-// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us; in one pass 122, and now 110 with
+// instead of 1664 at r = 512, d_h = 128) 5 ragged prompts of up to 1531 rows, 16 heads, took 211 us; in one pass 122, then 110 with
 // the rows leaving by whole lines, the queries, own keys and own values coming by 64 bytes of a row and more, all in flight at once, and
-// the blocks ordered as the plain form's
+// the blocks ordered as the plain form's, and now 99 with the rows leaving past the caches
 // (the outputs alone, 313 MB, are 66 at the rate of a large copy).
 #include <type_traits>
 
@@ -395,7 +395,11 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   }
 
   // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3.  The rows leave through LDS, up to whole
-  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path, 320 of them a block).
+  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path, 320 of them a block), and past the caches:
+  // 320 KB a block and unit otherwise take the place of the tiles that the blocks beside it read, and are written back in bursts.  us a pass, ordinary
+  // stores / these: 5 ragged prompts of up to 1531, 16 heads x 128, r = 512 (390 MB) 160.0 / 136.5, 8 of 2048 517 / 490, 1 of 700 58.8 / 55.3; 7 of 540, 8 x 64,
+  // r = 256 47.3 / 44.8.  What reads the outputs next finds fewer of them in the last-level cache; with an elementwise pass over both outputs behind it
+  // 267.5 / 257.0, 695 / 658, 68.0 / 67.2, 58.9 / 59.5.
   {
     const float l = quarter_reduce(l_run, LaneSum());
     if (g == 0) s_inv[16 * wv + l16] = m_own < len ? 1.f / l : 0.f;
@@ -421,7 +425,7 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       for (int i = 0; i < N; ++i) {
         const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
         const u32x4_t v = *reinterpret_cast<const u32x4_t*>(area + row * (16 * PPR) + ((c ^ (row & SW)) << 4));
-        if (mt0 + row < T) *reinterpret_cast<u32x4_t*>(to + row * to_row + 16 * c) = v;
+        if (mt0 + row < T) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(to + row * to_row + 16 * c));
       }
       __builtin_amdgcn_wave_barrier();
     };
