@@ -27,7 +27,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kTile = kWideTile, kWideThreads = 512, kWideWaves = 8;
 constexpr int kBK = 32, kSlots = 5;        // k of a stage, stages in LDS
-constexpr size_t kStreamOut = (size_t)128 << 20;  // half of the last-level cache
 constexpr int kPark = 4096;                // bytes a wavefront's results pass through on their way out
 
 // Where the rows are, the same for every job of the launch.  Lane i stands for sequences i * per .. + per - 1: the blocks of

@@ -112,3 +112,21 @@ def test_own_column_far_above_the_others(latent, bits):
     assert H.max_err(out[0, rows], o_ref) <= H.TOL["bf16"]
     if latent:
         H.check_latent(np.abs(lat[0, rows].cpu().numpy().astype(np.float64) - ol_ref), Cp, "bf16", "own column")
+
+
+def test_outputs_past_the_caches():
+    # 172 MB of outputs in one call, which leave past the caches, and the sequences one at a time, whose 34 MB do not: a row's sums are the
+    # same but for the references of the blocks of rows it is in, a tenth of the bound on any row; blocks cut by a sequence's end and by T
+    B, T, nh, dh = 5, 2105, 32, 128
+    lens = np.array([T, T - 1, 17, 0, 1040], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="streamed", batch=B, d_model=64, n_heads=nh, d_head=dh, r=128, d_rope=64, stride=4, prefix=1, steps=0, seed=5)
+    wts = W.make_weights(wl, max_slots=-(-T // 4))
+    g = torch.Generator(device="cuda").manual_seed(8)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
+    d = dict(q=n(B, T, nh, dh), q_rope=n(B, T, nh, 64), c=n(B, T, 128), kr=n(B, T, 64))
+    _, _, out, _ = _gpu_prefill(wl, wts, d, T, lens, want_latent=False)
+    for b in range(B):
+        one = {k: v[b:b + 1].contiguous() for k, v in d.items()}
+        _, _, ref, _ = _gpu_prefill(wl.scaled(batch=1), wts, one, T, lens[b:b + 1], want_latent=False)
+        assert torch.isfinite(out[b]).all() and (out[b] - ref[0]).abs().max() <= H.TOL["bf16"] / 10
+        assert torch.all(out[b, lens[b]:] == 0)
