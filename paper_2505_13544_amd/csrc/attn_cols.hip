@@ -20,6 +20,7 @@
 // into equal ranges, one per persistent workgroup; a workgroup emits partial number i + b for every
 // sequence b of which its range holds a tile, and the tile stream never drains between sequences.
 #include "bounds.h"
+#include "lds_stream.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -120,14 +121,68 @@ __device__ __forceinline__ void load_query_tile(uint4 (&hi)[C::KQ], uint4 (&lo)[
   lo[C::KC] = make_uint4(rl.x & m, rl.y & m, rl.z & m, rl.w & m);
 }
 
-// decode: query tile ht = heads 16 ht .. 16 ht + 15 of the sequence whose operand rows start at qbase
+// decode: query tile ht = heads 16 ht .. 16 ht + 15 of the sequence whose operand rows start at qbase.  They come by 64 bytes of a row to four
+// neighbouring lanes and change lanes in the wavefront's parked slice's place (turn_query): in the operand's layout, 16 rows for neighbours, a load is
+// 66 cycles of the unit's address path, this one 24, and at a workgroup's start 40 to 80 of them (and in front of a unit's second
+// workgroup as many again) stood before the first tile.  With the partials by whole pieces (below), us of 8 steps: 8 sequences of 32768, s = 4, 32 heads, r = 512
+// 288.1 -> 279.9; 16 heads, 64 of 1200 254.8 -> 244.5, 256 of 512 to 4096 673.2 -> 669.6; r = 128, 8 heads, 1024 of 1000 387.8 -> 369.0, 16 heads, 200 of
+// 2000, s = 1 307.2 -> 291.0; r = 256, 20 heads, 100 of 1000 217.4 -> 215.4; r = 512, 20 heads, 31 of 1300 230.3 -> 231.8.
 template <class C>
 __device__ __forceinline__ void load_query_slice(QSlice<C>& q, const uint16_t* qbase, size_t plane, int n_heads,
-                                                 int l16, int g, int wv) {
+                                                 int lane, int wv) {
+  asm volatile("" : "+v"(lane));  // (what depends on it is formed here, not kept in registers through the stream)
+  const int piece = lane & 3;
 #pragma unroll
   for (int ht = 0; ht < C::NHT; ++ht) {
-    const int h = 16 * ht + l16 < n_heads ? 16 * ht + l16 : n_heads - 1;  // padded heads: never stored
+    const int head = 16 * ht + (lane >> 2), h = head < n_heads ? head : n_heads - 1;  // padded heads: never stored
+    const uint16_t* qhead = qbase + (size_t)h * C::E;
+    const uint16_t* src = qhead + wv * C::RW + 8 * piece;
+    const uint16_t* rs = qhead + C::R + wv * C::DRW + (8 * piece < C::DRW ? 8 * piece : 0);
+#pragma unroll
+    for (int kk = 0; kk < C::KQ; ++kk) {
+      const uint16_t* from = kk < C::KC ? src + 32 * kk : rs;
+      q.hi[ht][kk] = *reinterpret_cast<const uint4*>(from);
+      q.lo[ht][kk] = *reinterpret_cast<const uint4*>(from + plane);
+    }
+  }
+}
+// ... straight into the operands' layout: for the runs behind a workgroup's first, whose queries travel beside a stream and would change lanes with
+// nothing beside them (two head tiles: 20 heads, r = 512, 128 of 150 to 1200 turned 283.5, so 280.3)
+template <class C>
+__device__ __forceinline__ void load_query_direct(QSlice<C>& q, const uint16_t* qbase, size_t plane, int n_heads,
+                                                  int l16, int g, int wv) {
+#pragma unroll
+  for (int ht = 0; ht < C::NHT; ++ht) {
+    const int h = 16 * ht + l16 < n_heads ? 16 * ht + l16 : n_heads - 1;
     load_query_tile<C>(q.hi[ht], q.lo[ht], qbase + (size_t)h * C::E, plane, g, wv);
+  }
+}
+template <class C>
+__device__ __forceinline__ void turn_query(QSlice<C>& q, uint16_t* sTw, int lane) {
+  constexpr int N = 2 * C::KQ, kFit = kTile * C::TS * 2 / 1024;  // operands of a query tile, and how many have a place
+  static_assert(kFit >= 1, "an operand fits");
+  asm volatile("" : "+v"(lane));
+  const int l16 = lane & 15, g = lane >> 4;
+  unsigned char* place = reinterpret_cast<unsigned char*>(sTw);
+  unsigned char* to = place + (lane >> 2) * 64 + (((lane & 3) ^ swz_rows16<4>(lane >> 2)) << 4);
+  const unsigned char* from = place + l16 * 64 + ((g ^ swz_rows16<4>(l16)) << 4);
+#pragma unroll
+  for (int ht = 0; ht < C::NHT; ++ht) {
+    auto operand = [&](int i) -> uint4& { return i < C::KQ ? q.hi[ht][i < C::KQ ? i : 0] : q.lo[ht][i < C::KQ ? 0 : i - C::KQ]; };
+#pragma unroll
+    for (int i0 = 0; i0 < N; i0 += kFit) {
+#pragma unroll
+      for (int i = i0; i < (i0 + kFit < N ? i0 + kFit : N); ++i) *reinterpret_cast<uint4*>(to + 1024 * (i - i0)) = operand(i);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = i0; i < (i0 + kFit < N ? i0 + kFit : N); ++i) operand(i) = *reinterpret_cast<const uint4*>(from + 1024 * (i - i0));
+      __builtin_amdgcn_wave_barrier();
+    }
+    const uint32_t m = 8 * g < C::DRW ? 0xffffffffu : 0u;  // (lanes without a RoPE column hold copies)
+    uint4& rh = q.hi[ht][C::KC];
+    uint4& rl = q.lo[ht][C::KC];
+    rh = make_uint4(rh.x & m, rh.y & m, rh.z & m, rh.w & m);
+    rl = make_uint4(rl.x & m, rl.y & m, rl.z & m, rl.w & m);
   }
 }
 
@@ -478,10 +533,11 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
     // run from the later ones inside the tile loop, so every wait for a query register there is sized
     // for the first run; with the query requested after the tiles that was "everything in flight",
     // the tile requested a moment ago included (one tile of prefetch instead of NS).
-    load_query_slice<C>(q, q_all + (size_t)cur.b * a.n_heads * C::E, a.q_plane, a.n_heads, l16, g, wv);
+    load_query_slice<C>(q, q_all + (size_t)cur.b * a.n_heads * C::E, a.q_plane, a.n_heads, lane, wv);
 #pragma unroll
     for (int st = 0; st < NS; ++st)
       load_slice<C, SH, PG>(tl[st], lat, key, cur.k0 + st * kTile, cur.k1 - 1, l16, g, wv, cur.sp, pr_cur);
+    turn_query<C>(q, sTw, lane);
   }
   int sbuf = 0;
   while (true) {
@@ -498,15 +554,18 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
       nx.last = nxt.k1 - 1;
       nx.sp = nxt.sp;
       nx.pr = pages_of(nxt.b);
-      load_query_slice<C>(qn, q_all + (size_t)nxt.b * a.n_heads * C::E, a.q_plane, a.n_heads, l16, g, wv);
+      load_query_direct<C>(qn, q_all + (size_t)nxt.b * a.n_heads * C::E, a.q_plane, a.n_heads, l16, g, wv);
     }
     ColState<C> ws;
     ws.reset();
     if constexpr (AH) stream_cols_ahead<C, NS, SH, PG>(tl, q, sTw, sS, lat, key, cur.k0, cur.k1, nx, lane, l16, g, wv, sbuf, ws, cur.sp, pr_cur);
     else stream_cols<C, NS, SH, PG>(tl, q, sTw, sS, lat, key, cur.k0, cur.k1, nx, lane, l16, g, wv, sbuf, ws, cur.sp, pr_cur);
 
-    // ---- this wavefront's columns of the run's partial: lane holds head l16, columns 16mt + 4g .. +3
+    // ---- this wavefront's columns of the run's partial: lane holds head l16, columns 16mt + 4g .. +3.  They leave through the parked slice's
+    // place, 16 bytes a lane and the heads' columns as runs of memory (as they stand a store is 32 bytes of each of 16 rows).
     const size_t piece = (size_t)blockIdx.x + cur.b;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
     float l_head[NHT];
 #pragma unroll
     for (int ht = 0; ht < NHT; ++ht) {
@@ -515,24 +574,34 @@ __global__ __launch_bounds__(kBlock, OCC) void attn_cols_kernel(AttnArgs a) {
 #pragma unroll
     for (int ht = 0; ht < NHT; ++ht) {
       const int h = 16 * ht + l16;
-      if (h < a.n_heads) {
-        if (a.part_f16) {  // normalised by the run's own sum: a convex combination of cache rows, safe in half
-          const float inv = l_head[ht] > 0.f ? 1.f / l_head[ht] : 0.f;
-          uint16_t* ph = reinterpret_cast<uint16_t*>(a.part_o) + (piece * a.n_heads + h) * R + wv * C::RW + 4 * g;
+      if (a.part_f16) {  // normalised by the run's own sum: a convex combination of cache rows, safe in half
+        constexpr int PPR = C::RW / 8;  // 16-byte pieces of a head's columns; piece j of head i sits at j ^ (i & (PPR - 1))
+        static_assert(16 * C::RW <= kTile * C::TS, "a head tile's columns fit");
+        unsigned char* place = reinterpret_cast<unsigned char*>(sTw);
+        const float inv = l_head[ht] > 0.f ? 1.f / l_head[ht] : 0.f;
 #pragma unroll
-          for (int mt = 0; mt < C::MT; ++mt) {
-            const float4_t o = ws.acc_o[ht][mt] * inv;
-            *reinterpret_cast<uint2*>(ph + 16 * mt) = make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
-          }
-        } else {
-          float* po = a.part_o + (piece * a.n_heads + h) * R + wv * C::RW + 4 * g;
+        for (int mt = 0; mt < C::MT; ++mt) {
+          const float4_t o = ws.acc_o[ht][mt] * inv;
+          *reinterpret_cast<uint2*>(place + (ln & 15) * (16 * PPR) + (((2 * mt + (ln >> 5)) ^ (ln & (PPR - 1))) << 4) + 8 * ((ln >> 4) & 1)) =
+              make_uint2(pack_f16x2(o[0], o[1]), pack_f16x2(o[2], o[3]));
+        }
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-          for (int mt = 0; mt < C::MT; ++mt) *reinterpret_cast<float4_t*>(po + 16 * mt) = ws.acc_o[ht][mt];
+        for (int i = 0; i < 16 * PPR / kWave; ++i) {
+          const int at = kWave * i + ln, row = at / PPR, c = at % PPR;
+          const uint4 v = *reinterpret_cast<const uint4*>(place + row * (16 * PPR) + ((c ^ (row & (PPR - 1))) << 4));
+          if (16 * ht + row < a.n_heads)
+            *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.part_o) + (piece * a.n_heads + 16 * ht + row) * R + wv * C::RW + 8 * c) = v;
         }
-        if (wv == 0 && g == 0) {
-          a.part_ml[(piece * a.n_heads + h) * 2 + 0] = ws.m_ref[ht];
-          a.part_ml[(piece * a.n_heads + h) * 2 + 1] = l_head[ht];
-        }
+        __builtin_amdgcn_wave_barrier();
+      } else if (h < a.n_heads) {
+        float* po = a.part_o + (piece * a.n_heads + h) * R + wv * C::RW + 4 * g;
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt) *reinterpret_cast<float4_t*>(po + 16 * mt) = ws.acc_o[ht][mt];
+      }
+      if (h < a.n_heads && wv == 0 && g == 0) {
+        a.part_ml[(piece * a.n_heads + h) * 2 + 0] = ws.m_ref[ht];
+        a.part_ml[(piece * a.n_heads + h) * 2 + 1] = l_head[ht];
       }
     }
     if (!more) break;
