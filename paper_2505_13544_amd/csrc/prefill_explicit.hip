@@ -353,9 +353,10 @@ struct TileGeom {
 // launcher uses: two workgroups per CU, whose
 // wavefronts drift apart so that one multiplies while the other does softmax arithmetic.  What bounds it is the chain
 // of a pair of tiles (operand reads, 80 matrix instructions, the arithmetic of the weights) with two wavefronts per SIMD
-// to overlap, and what lies around the tile loop: matrix pipes busy 41 % (at 820 thousand cycles, the same at any
-// clock from 1.7 to 2.2 GHz, as power allows), no bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
-// us with the own rows as masked tiles and one tile per step, now 414 (830 TFLOP/s).
+// to overlap, and what lies around the tile loop: matrix pipes busy 45 % (at 750 thousand cycles, the same at any
+// clock from 1.7 to 2.2 GHz, as power allows), 2 % bank conflicts.  8 sequences x 4096 rows, 16 heads x 128, s = 2 (0.344 TFLOP): 460
+// us with the own rows as masked tiles and one tile per step, 414 with two blocks a workgroup and operands' loads in the operand's layout (820 thousand
+// cycles), now 391 (879 TFLOP/s).
 // CONT: the sequences continue from a cache (a.pos0, a.past_pitch); whole sequences are compiled without it.
 // LAYER: the whole-layer prefill's operands (queries already fp16 and scaled, output as fp16 for W_O).
 template <int DH, int DR, int NW, bool CONT, bool LAYER, int RT>
