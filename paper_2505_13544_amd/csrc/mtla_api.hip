@@ -10,6 +10,7 @@
 #include <new>
 #include <vector>
 
+#include "decode_schedule.h"
 #include "mtla_device.h"
 #include "mtla_kernels.h"
 
@@ -117,17 +118,6 @@ ChunkLayout chunk_layout(const mtla_ctx* c, size_t rows) {
   return L;
 }
 
-int pick_chunk(const mtla_config& g) {
-  // About two workgroups per compute unit (256 CUs) when every sequence is full; a workgroup's
-  // four wavefronts take 16-slot tiles round-robin, so chunks are multiples of 64 slots.
-  const long long total = (long long)g.max_batch * g.max_slots;
-  long long chunk = (total + 511) / 512;
-  chunk = (chunk + 63) / 64 * 64;
-  if (chunk < 64) chunk = 64;
-  if (chunk > 1024) chunk = 1024;
-  return (int)chunk;
-}
-
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Paged storage (cfg.page_slots > 0): table entries per sequence, and the map the kernels follow.
@@ -202,7 +192,7 @@ mtla_status mtla_create(const mtla_config* cfg, mtla_ctx** out) {
   if (!c) return MTLA_ERR_INVALID_ARG;
   c->cfg = g;
   c->scale = g.softmax_scale > 0.f ? g.softmax_scale : 1.0f / std::sqrt((float)g.d_head);
-  c->default_chunk = c->chunk = pick_chunk(g);
+  c->default_chunk = c->chunk = decode_chunk(g.max_batch, g.max_slots);
   *out = c;
   return MTLA_OK;
 }
@@ -403,22 +393,6 @@ mtla_status mtla_cache_append(mtla_ctx* c, void* cache_c, void* cache_kr, float*
                                  hyp_A, hyp_a, hyp_G, w_override, w_out, slot_out, workspace, hip_stream);
 }
 
-// Tiles of 16 slots (as many as the session holds) from which the balanced schedule is the faster one.  It has a fixed cost, the scan
-// of the lengths and a cold start of every persistent workgroup, some 5 us of a step beside a chunk a workgroup; against it stand the rounds of
-// workgroups that the chunks come to, which are two a unit at r = 256, one with two head tiles or r = 512.  us a step, chunks / balanced:
-//   r = 128   12 heads, 50 x 1000 slots (3200 tiles) 14.4 / 18.3, 16 heads, 100 x 1000 (6400) 17.8 / 21.0, 200 x 1000 (12800) 27.7 / 27.9
-//   r = 256   8 heads, 40 x 1000 (2560) 16.8 / 18.9, 16 heads, 100 x 500 (3200) 20.6 / 22.6, 8 heads, 16 x 5000 (5024) 20.5 / 20.4; 20 heads, 31 x
-//             450 (899) 18.8 / 20.2, 31 x 525 (1054, d_head 128) 22.9 / 20.9, 32 heads x 64, 20 x 900 (1160) 21.0 / 21.0
-//   r = 512   16 heads, 32 x 400 (832) 23.9 / 27.2, 32 x 650 (1344) 28.0 / 28.2, 64 x 600 (2432) 34.5 / 31.4; 32 heads, 31 x 500 (992) 28.8 /
-//             31.2, 20 heads, 31 x 640 (1294) 30.6 / 27.5
-static long long balanced_from(const mtla_config& g, int n_cu) {
-  const bool two = g.n_heads > 16;
-  if (g.r == 128) return 24LL * n_cu;
-  if (g.r == 256 && !two) return 16LL * n_cu;
-  if (g.r == 256 || g.r == 512) return two ? 9LL * n_cu / 2 : 11LL * n_cu / 2;
-  return 8LL * n_cu;
-}
-
 // Attention of one decode step; `ap` (may be NULL) is the append of the step's token that has to
 // come first.
 static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q, const void* q_rope,
@@ -475,6 +449,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
   const bool use_mfma = g.dtype == MTLA_BF16 && attn_mfma_supported(at);
   ab.out_bf16 = use_mfma ? 1 : 0;
   ab.plane = at.q_plane = (size_t)g.max_batch * g.n_heads * (g.r + g.d_rope);  // two bf16 planes fill the fp32 area
+  DecodeSchedule schedule = kDecodeChunks;
   if (use_mfma && c->schedule != 1 && batch <= kBalancedMaxBatch) {
     if (c->n_cu == 0) {  // first decode call on this context: ask the device once
       int dev = 0, n = 0;
@@ -483,8 +458,8 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
         return MTLA_ERR_HIP;
       c->n_cu = n < kMaxPersistent ? n : kMaxPersistent;
     }
-    const long long cap_tiles = (long long)batch * ((g.max_slots + 15) / 16);
-    if (c->schedule == 2 || cap_tiles >= balanced_from(g, c->n_cu)) {
+    schedule = c->schedule == 2 ? kDecodeBalanced : decode_schedule(g.r, g.n_heads, batch, g.max_slots, c->chunk, c->chunk_set, c->n_cu);
+    if (schedule != kDecodeChunks) {
       at.n_persistent = c->n_cu;
       if (attn_cols_supported(at)) {
         const int n = c->n_cu * attn_cols_workgroups_per_cu(at);
@@ -504,7 +479,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     at.prefix_rows = g.max_batch;
   }
   at.part_f16 = 0;
-  if (use_mfma && attn_cols_supported(at)) {  // half-size partials if the matrix-core combine will read them
+  if (use_mfma && attn_cols_supported(at)) {  // half-size partials if the schedule takes them and the matrix-core combine will read them
     CombineArgs probe;
     probe.r = g.r;
     probe.d_head = g.d_head;
@@ -512,7 +487,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     probe.out = out;
     probe.out_latent = out_latent;
     probe.w_uv = w_uv;
-    at.part_f16 = combine_mfma_supported(probe) ? 1 : 0;
+    at.part_f16 = schedule == kDecodeBalanced && combine_mfma_supported(probe) ? 1 : 0;
     at.run_cost = kRunCost;
   }
   if (ap && ap->c_new_f32 && g.dtype != MTLA_F32 && !decode_front_supported(*ap, ab)) return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents
