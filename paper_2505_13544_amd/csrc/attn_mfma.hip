@@ -455,11 +455,15 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_kernel(AttnArgs a) {
 // query for itself.  us a step: 31 sequences of 640 slots, 20 heads x 128, r = 512 38.0, now 30.5; 7 of 700, 32 heads (whole layer) 52.3 and 38.0; 16
 // of 750, 16 heads, r = 512 24.3 and 20.4; 79 of 195, 16 heads x 64, r = 256 19.3 and 17.6.
 // ---------------------------------------------------------------------------
-template <int R, int DR, int NHT>
+// Chunks of more than one step: where two workgroups a unit still fit (r = 64 and 128) a step's rows travel while the step before is multiplied
+// into a second place (DB), and the query stays in registers.  us a step, rows asked for at the step's top / so, 8 sequences of 1024 slots: r = 128, 8 heads, chunks of
+// 128 12.2 / 11.8, of 320 14.6 / 13.6, 32 heads, of 160 14.8 / 13.8; r = 64, 16 heads, of 320 13.1 / 12.4.
+template <int R, int DR, int NHT, bool DB>
 struct SplitGeom {
   static constexpr int KC = R / 32, KT = (R + DR) / 32, HP = 16 * NHT, MW = R / 16 / kWaves;
   static constexpr int TILE = KT * 1024;                              // 16 slots: [K step][slot][64 bytes], pieces swizzled
-  static constexpr int ROWS = kWaves * TILE, Q = NHT * 2 * KT * 1024;  // query: [head tile][plane][K step][head][64 bytes]
+  static constexpr int STEP = kWaves * TILE, ROWS = (DB ? 2 : 1) * STEP;
+  static constexpr int Q = NHT * 2 * KT * 1024;                       // query: [head tile][plane][K step][head][64 bytes]
   static constexpr int OUT = HP * R * 4;                              // the sums on their way out, in place of the rows
   static constexpr int BODY = ROWS > OUT ? ROWS : OUT;
   static constexpr int WEIGHTS = kWaves * NHT * kWave * 8;
@@ -468,9 +472,9 @@ struct SplitGeom {
   static_assert(BYTES <= 160 * 1024, "LDS budget of one compute unit");
 };
 
-template <int R, int DR, int NHT, bool SH, bool PG>
-__global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_split_kernel(AttnArgs a) {
-  using G = SplitGeom<R, DR, NHT>;
+template <int R, int DR, int NHT, bool DB, bool SH, bool PG>
+__global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void attn_split_kernel(AttnArgs a) {
+  using G = SplitGeom<R, DR, NHT, DB>;
   constexpr int KC = G::KC, KT = G::KT, E = R + DR, HP = G::HP, MW = G::MW;
   constexpr int GROUPS = kWaves / NHT;  // of wavefronts that share a head tile's slots
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -498,9 +502,9 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
   }
   const int in_row = lane >> 2, piece = (lane & 3) ^ swz_rows16<4>(in_row);  // what a lane brings in: 16 bytes of that row's 64
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
-  // the wavefront's 16 slots from `base` on; slots past `last` become copies of that one
-  auto issue_rows = [&](int base, int last) {
-    const uint32_t to = lds0 + (uint32_t)(wv * G::TILE);
+  // the wavefront's 16 slots from `base` on, into the step's place; slots past `last` become copies of that one
+  auto issue_rows = [&](int base, int last, uint32_t step_at) {
+    const uint32_t to = lds0 + step_at + (uint32_t)(wv * G::TILE);
     const int s0 = base < last ? base : last, slot = base + in_row < last ? base + in_row : last;
     if constexpr (SH) {
       const uint16_t* lr = lat + (size_t)slot * R + 8 * piece + (slot < sp.n ? sp.dlat : 0);
@@ -542,7 +546,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
   }
   const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
-  if (k0 < k1) issue_rows(k0 + wv * kTile, k1 - 1);
+  if (k0 < k1) issue_rows(k0 + wv * kTile, k1 - 1, 0);
 
   const int hq = NHT == 2 ? wv & 1 : 0, grp = NHT == 2 ? wv >> 1 : wv;  // head tile and slot tiles NHT grp .. of the wavefront's logits
   float m_ref[NHT], l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
@@ -558,22 +562,30 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
 
   wait_loads_but<0>();
   if (k0 >= k1) return;  // (nothing of this workgroup is on its way into LDS any more)
+  const unsigned char* qr = sQ + hq * (2 * KT * 1024) + frag;
+  u32x4_t qf[DB ? 2 * KT : 1];  // the query, where it is read more than once
+  if constexpr (DB) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2 * KT; ++i) qf[i] = *reinterpret_cast<const u32x4_t*>(qr + 1024 * i);
+  }
+  uint32_t step_at = 0;  // this step's rows in LDS
   for (int s0 = k0; s0 < k1; s0 += kWaves * kTile) {
-    if (s0 > k0) {  // (chunks of more than 64 slots: set by the caller)
+    if (!DB && s0 > k0) {
       __syncthreads();
-      issue_rows(s0 + wv * kTile, k1 - 1);
-      wait_loads_but<0>();
+      issue_rows(s0 + wv * kTile, k1 - 1, 0);
     }
-    __syncthreads();  // rows and query are there
+    if (s0 > k0) wait_loads_but<0>();
+    if (!DB || (NHT > 1 && s0 > k0)) __syncthreads();  // rows and query are there (with one head tile the rows are the wavefront's own)
     // ---- logits S^T[slot, head] (log2 units), one chain per query plane
     float4_t sh[NHT], sl[NHT];
 #pragma unroll
     for (int u = 0; u < NHT; ++u) sh[u] = sl[u] = float4_t{0.f, 0.f, 0.f, 0.f};
-    const unsigned char* xr = smem + NHT * grp * G::TILE + frag;
-    const unsigned char* qr = sQ + hq * (2 * KT * 1024) + frag;
+    const unsigned char* xr = smem + step_at + NHT * grp * G::TILE + frag;
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) {
-      const u32x4_t qh = *reinterpret_cast<const u32x4_t*>(qr + 1024 * kk), ql = *reinterpret_cast<const u32x4_t*>(qr + 1024 * (KT + kk));
+      const u32x4_t qh = DB ? qf[DB ? kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * kk);
+      const u32x4_t ql = DB ? qf[DB ? KT + kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * (KT + kk));
 #pragma unroll
       for (int u = 0; u < NHT; ++u) {
         const bf16x8_t x = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(xr + u * G::TILE + 1024 * kk));
@@ -591,7 +603,8 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
       }
     mloc = quarter_reduce(mloc, LaneMax());
     if (g == 0) sM[grp * HP + 16 * hq + l16] = mloc;
-    __syncthreads();
+    __syncthreads();  // the maxima are there, and nobody reads the rows of the step before
+    if (DB && s0 + kWaves * kTile < k1) issue_rows(s0 + kWaves * kTile + wv * kTile, k1 - 1, (uint32_t)G::STEP - step_at);
     // ---- reference (fixed at the first step, moved when a step tops it by 2^40), weights as bf16
     constexpr float kRebase = 40.f;
 #pragma unroll
@@ -628,6 +641,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
     // ---- O^T[col, head] += C_hat^T[col, slot] P^T[slot, head]: a lane's eight slots of a K step are 4g .. + 3 of two tiles
 #pragma unroll
     for (int k = 0; k < kWaves / 2; ++k) {
+      if (DB && k > 0 && s0 + 2 * kTile * k >= k1) break;  // (weights of zero)
       bf16x8_t pb[NHT];
 #pragma unroll
       for (int ht = 0; ht < NHT; ++ht) {
@@ -637,7 +651,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
 #pragma unroll
       for (int mt = 0; mt < MW; ++mt) {  // latent columns 16 (MW wv + mt) ..: half of a K step's 32
         const int ct = MW * wv + mt;
-        const unsigned char* src = smem + 2 * k * G::TILE + 1024 * (ct >> 1) + vrow * 64 + 8 * (l16 & 1) +
+        const unsigned char* src = smem + step_at + 2 * k * G::TILE + 1024 * (ct >> 1) + vrow * 64 + 8 * (l16 & 1) +
                                    (((2 * (ct & 1) + ((l16 & 3) >> 1)) ^ swz_rows16<4>(vrow)) << 4);
         const short4_t c0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
         const short4_t c1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + G::TILE));
@@ -647,22 +661,29 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT>::PER_CU)) void attn_
         for (int ht = 0; ht < NHT; ++ht) acc[ht][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct8, pb[ht], acc[ht][mt], 0, 0, 0);
       }
     }
+    if (DB) step_at = (uint32_t)G::STEP - step_at;
   }
 
   // ---- the partial of all heads, one run of memory: lane holds head 16 ht + l16, columns 16 mt + 4g .. + 3 of its quarter; piece j (16
-  // bytes) of head i sits at j ^ (i % 16)
-  __syncthreads();  // the rows have been read
-#pragma unroll
-  for (int ht = 0; ht < NHT; ++ht)
-#pragma unroll
-    for (int mt = 0; mt < MW; ++mt)
-      *reinterpret_cast<float4_t*>(smem + (16 * ht + l16) * (R * 4) + (((4 * (MW * wv + mt) + g) ^ l16) << 4)) = acc[ht][mt];
-  __syncthreads();
+  // bytes) of head i sits at j ^ (i % 16).  (Of a quarter of 16 columns a wavefront has one store a head tile: as it stands.)
   const size_t ph = ((size_t)b * a.n_splits + split) * a.n_heads;
   float* po = a.part_o + ph * R;
-  for (int at = tid; at < a.n_heads * (R / 4); at += kBlock) {
-    const int h = at / (R / 4), j = at % (R / 4);
-    *reinterpret_cast<float4_t*>(po + 4 * (size_t)at) = *reinterpret_cast<const float4_t*>(smem + h * (R * 4) + ((j ^ (h & 15)) << 4));
+  if constexpr (MW == 1) {
+#pragma unroll
+    for (int ht = 0; ht < NHT; ++ht)
+      if (16 * ht + l16 < a.n_heads) *reinterpret_cast<float4_t*>(po + (size_t)(16 * ht + l16) * R + 16 * wv + 4 * g) = acc[ht][0];
+  } else {
+    __syncthreads();  // the rows have been read
+#pragma unroll
+    for (int ht = 0; ht < NHT; ++ht)
+#pragma unroll
+      for (int mt = 0; mt < MW; ++mt)
+        *reinterpret_cast<float4_t*>(smem + (16 * ht + l16) * (R * 4) + (((4 * (MW * wv + mt) + g) ^ l16) << 4)) = acc[ht][mt];
+    __syncthreads();
+    for (int at = tid; at < a.n_heads * (R / 4); at += kBlock) {
+      const int h = at / (R / 4), j = at % (R / 4);
+      *reinterpret_cast<float4_t*>(po + 4 * (size_t)at) = *reinterpret_cast<const float4_t*>(smem + h * (R * 4) + ((j ^ (h & 15)) << 4));
+    }
   }
   if (tid < a.n_heads) {
     float l = sL[tid];
@@ -894,14 +915,21 @@ hipError_t launch_rows(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
   return hipGetLastError();
 }
 
+template <int R, int DR, int NHT, bool DB, bool SH, bool PG>
+hipError_t launch_split_as(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
+  constexpr size_t smem = SplitGeom<R, DR, NHT, DB>::BYTES;
+  static DeviceSet lds_allowed;
+  const hipError_t e = allow_lds(&attn_split_kernel<R, DR, NHT, DB, SH, PG>, smem, lds_allowed);
+  if (e != hipSuccess) return e;
+  launch_timed(attn_split_kernel<R, DR, NHT, DB, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
+  return hipGetLastError();
+}
 template <int R, int DR, int NHT, bool SH, bool PG>
 hipError_t launch_split(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
-  constexpr size_t smem = SplitGeom<R, DR, NHT>::BYTES;
-  static DeviceSet lds_allowed;
-  const hipError_t e = allow_lds(&attn_split_kernel<R, DR, NHT, SH, PG>, smem, lds_allowed);
-  if (e != hipSuccess) return e;
-  launch_timed(attn_split_kernel<R, DR, NHT, SH, PG>, dim3(a.n_splits, a.batch), dim3(kBlock), smem, st, ev, a);
-  return hipGetLastError();
+  if constexpr (R <= 128) {
+    if (a.chunk > kTile * kWaves) return launch_split_as<R, DR, NHT, true, SH, PG>(a, st, ev);
+  }
+  return launch_split_as<R, DR, NHT, false, SH, PG>(a, st, ev);
 }
 
 template <int R, int DR, int NHT, int NS, bool QL, bool SH, bool PG>

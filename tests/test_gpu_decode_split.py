@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import workloads as W
+from paper_2505_13544_amd.session import PagedSession, Session
 from tests import harness as H
 
 pytestmark = pytest.mark.gpu
@@ -28,6 +29,41 @@ def test_two_head_tiles(n_heads, r, d_rope, chunk):
     wl = W.WORKLOADS["speech_bf16"].scaled(name=f"split2_{r}_{chunk}", batch=len(plen), d_model=96, n_heads=n_heads, d_head=64, r=r,
                                            d_rope=d_rope, stride=1, prefix=(1, 200), steps=2, seed=60 + r + chunk)
     H.run_decode_parity(wl, prefix_lens=plen, decode_chunk=chunk, decode_schedule=1)
+
+
+@pytest.mark.parametrize("n_heads,r,d_rope,chunk", [(16, 64, 64, 192), (8, 128, 32, 160), (16, 128, 64, 320), (17, 64, 32, 160), (32, 128, 32, 160),
+                                                    (20, 128, 64, 128)])
+def test_rows_that_travel_a_step_ahead(n_heads, r, d_rope, chunk):
+    # narrow latents, chunks of several steps: two places for rows in turn, whose last step may hold up to 32 slots; the same over pages
+    # and over one stored copy of the first 100 slots, bit for bit; rows that no sequence holds are no numbers
+    lens = np.array([100, 1, 63, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 225, 320, 321, 350], np.int32)
+    B, slots, shared_slots = len(lens), 352, 100
+    wl = W.WORKLOADS["speech_bf16"].scaled(name=f"ahead_{r}_{chunk}", batch=B, d_model=96, n_heads=n_heads, d_head=64, r=r, d_rope=d_rope, stride=1,
+                                           prefix=(1, 350), steps=2, seed=90 + r + chunk)
+    H.run_decode_parity(wl, prefix_lens=lens, decode_chunk=chunk, decode_schedule=1)
+    kw = dict(n_heads=n_heads, d_head=64, r=r, d_rope=d_rope, d_hyper=64, stride=1, max_batch=B, max_slots=slots, dtype="bf16", decode_chunk=chunk,
+              decode_schedule=1)
+    flat, paged, shared = Session(**kw), PagedSession(page_slots=32, n_pages=B * slots // 32, **kw), Session(**kw)
+    g = torch.Generator(device="cuda").manual_seed(r + chunk)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    c, kr = n(B, 350, r), n(B, 350, d_rope)
+    c[:, :shared_slots], kr[:, :shared_slots] = c[:1, :shared_slots].clone(), kr[:1, :shared_slots].clone()
+    wts = W.make_weights(wl, max_slots=slots)
+    outs = []
+    for s in (flat, paged, shared):
+        H.upload_weights(s, wts)
+        for cache in (s.pool_c, s.pool_kr) if s is paged else (s.cache_c, s.cache_kr):
+            cache.fill_(float("nan"))
+        s.append(c, kr, n_new=lens.tolist() if s is paged else torch.from_numpy(lens).cuda())
+    shared.share_prefix(torch.zeros(B, dtype=torch.int32, device="cuda"), torch.from_numpy(np.minimum(lens, shared_slots)).cuda())
+    shared.cache_c[1:, :shared_slots] = float("nan")
+    q, q_rope = n(B, n_heads, 64), n(B, n_heads, d_rope)
+    for s in (flat, paged, shared):
+        out = torch.empty(B, n_heads, 64, device="cuda")
+        s.decode(q, q_rope, out=out)
+        outs.append(out)
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
 def test_more_pieces_than_one_round_of_the_merge():
