@@ -111,4 +111,35 @@ float gemm_cost(const Args& a, bool wide_supported, int& pick) {
   return best;
 }
 
+// What a call becomes: the small products; or tiles, with the narrowest product in a launch of its own if that saves time (64 columns
+// beside 3584 at 32768 rows open half a round of 256 x 256 tiles more).  `part`: of a call that was split.  A part is tiles whatever its size:
+// that is what its time was compared as, and the small products of 64 columns beside thousands of rows read every row for few of them
+// and form every angle anew (us of that part, 64 x 64 tiles / 32 x 32 of the small products: 8000 rows, K = 1536 12.9 / 35.6; K = 4096 28.2 / 79.3).
+struct GemmPlan {
+  bool ring;
+  int pick, alone;  // tile; the product by itself or -1
+};
+template <class Args>
+void gemm_without(const Args& a, int alone, Args& one, Args& rest) {
+  one = rest = a;
+  one.n_seg = 1;
+  one.seg[0] = a.seg[alone];
+  rest.n_seg = a.n_seg - 1;
+  for (int i = alone; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
+}
+template <class Args, class Wide>
+GemmPlan gemm_plan(const Args& a, bool part, Wide wide_supported) {
+  GemmPlan p{!part && gemm_ring_pays(a), 0, -1};
+  if (p.ring) return p;
+  const float whole = gemm_cost(a, wide_supported(a), p.pick);
+  if (a.n_seg < 2) return p;
+  int least = 0, p1 = 0, p2 = 0;
+  for (int i = 1; i < a.n_seg; ++i)
+    if (a.seg[i].N < a.seg[least].N) least = i;
+  Args one, rest;
+  gemm_without(a, least, one, rest);
+  if (gemm_cost(one, wide_supported(one), p1) + gemm_cost(rest, wide_supported(rest), p2) < whole) p.alone = least;
+  return p;
+}
+
 }  // namespace mtla

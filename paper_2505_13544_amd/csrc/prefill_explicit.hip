@@ -842,38 +842,24 @@ hipError_t launch_rope_table(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-}  // namespace
-
-hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
-  if (!gemm_nt_supported(args)) return hipErrorInvalidValue;
-  if (gemm_ring_pays(args)) return launch_gemm_ring(args, st);
+hipError_t launch_gemm(const GemmArgs& args, bool part, hipStream_t st) {
   GemmArgs a = args;
+  const GemmPlan plan = gemm_plan(a, part, gemm_wide_supported);
+  if (plan.ring) return launch_gemm_ring(a, st);
   const bool turned = gemm_turns(a);
   auto table = [&]() {
     a.rope_ready = 1;
     return launch_rope_table(a, st);
   };
-  int pick = 0;
-  const float whole = gemm_cost(a, gemm_wide_supported(a), pick);
-  if (a.n_seg > 1) {
-    // The narrowest product in a launch of its own if that saves time: 64 columns beside 3584 at 32768 rows open half a round
-    // of 256 x 256 tiles more.
-    int least = 0;
-    for (int i = 1; i < a.n_seg; ++i)
-      if (a.seg[i].N < a.seg[least].N) least = i;
-    GemmArgs one = a, rest = a;
-    one.n_seg = 1;
-    one.seg[0] = a.seg[least];
-    rest.n_seg = a.n_seg - 1;
-    for (int i = least; i + 1 < a.n_seg; ++i) rest.seg[i] = a.seg[i + 1];
-    int p1 = 0, p2 = 0;
-    if (gemm_cost(one, gemm_wide_supported(one), p1) + gemm_cost(rest, gemm_wide_supported(rest), p2) < whole) {
-      hipError_t e = turned && !a.rope_ready ? table() : hipSuccess;  // one for both
-      one.rope_ready = rest.rope_ready = a.rope_ready;
-      if (e == hipSuccess) e = launch_gemm_nt(rest, st);
-      return e != hipSuccess ? e : launch_gemm_nt(one, st);
-    }
+  if (plan.alone >= 0) {
+    GemmArgs one, rest;
+    gemm_without(a, plan.alone, one, rest);
+    hipError_t e = turned && !a.rope_ready ? table() : hipSuccess;  // one for both
+    one.rope_ready = rest.rope_ready = a.rope_ready;
+    if (e == hipSuccess) e = launch_gemm(rest, true, st);
+    return e != hipSuccess ? e : launch_gemm(one, true, st);
   }
+  const int pick = plan.pick;
   if (turned && !a.rope_ready && (pick == kWide || !gemm_own_angles(kGemmTiles[pick].bm, kGemmTiles[pick].bn))) {
     const hipError_t e = table();
     if (e != hipSuccess) return e;
@@ -901,6 +887,12 @@ hipError_t launch_gemm_nt(const GemmArgs& args, hipStream_t st) {
   MTLA_GEMM(3, 64, 64)
 #undef MTLA_GEMM
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t st) {
+  return gemm_nt_supported(a) ? launch_gemm(a, false, st) : hipErrorInvalidValue;
 }
 
 // the front launch has filled a.cprime, a.kr16 ([B*(past_pitch + T), ..]), a.w_kT and a.w_v16

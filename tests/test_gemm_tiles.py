@@ -79,6 +79,27 @@ int main() {
   turned("rows behind a past", ragged(3, 5, 40, {512, 64}, 64), 2, false);
   turned("blocks of several sequences", ragged(3, 0, 40, {512, 64}, 64, 1), 1, false);
   turned("none turned", ragged(3, 5, 40, {512, 64}, 64, 1), 3, true);
+  // the product that is launched by itself, and its parts, which are tiles however few they have: a layer's q, q^R, c and k^R
+  auto wide = [](const Args&) { return true; };
+  auto splits = [&](const char* what, const Args& a, int alone, int tile) {
+    const GemmPlan whole = gemm_plan(a, false, wide);
+    bool good = !whole.ring && whole.alone == alone;
+    if (good && alone >= 0) {
+      Args one, rest;
+      gemm_without(a, alone, one, rest);
+      const GemmPlan p = gemm_plan(one, true, wide), q = gemm_plan(rest, true, wide);
+      good = one.n_seg == 1 && rest.n_seg == a.n_seg - 1 && one.seg[0].N == a.seg[alone].N && !p.ring && p.pick == tile && p.alone < 0 && !q.ring;
+      for (int i = 0; i < rest.n_seg; ++i) good = good && rest.seg[i].N == a.seg[i + (i >= alone)].N;
+    }
+    if (good) return;
+    std::printf("%s: ring %d, alone %d\n", what, whole.ring, whole.alone);
+    ++failed;
+  };
+  auto layer = [](int n_seq, int T, int heads, int d_head, int r) { return ragged(n_seq, 0, T, {heads * d_head, heads * d_head / 2, r, d_head / 2}, heads * d_head); };
+  splits("2 x 4000 rows, 12 heads x 128", layer(2, 4000, 12, 128, 256), 3, 3);   // 2000 tiles of 16 x 16: 12.9 us in 64 x 64, 35.6 as small products
+  splits("6000 rows, 16 heads x 128", layer(1, 6000, 16, 128, 512), 3, 3);       // 14.4, 33.5
+  splits("2 x 4000 rows, 32 heads x 128", layer(2, 4000, 32, 128, 512), 3, 3);   // 28.2, 79.3
+  splits("1000 rows, 8 heads x 64", layer(1, 1000, 8, 64, 256), -1, 0);
   for (int i = 0; i < kWide; ++i) failed += gemm_own_angles(kGemmTiles[i].bm, kGemmTiles[i].bn) != (i == 3);
   return failed ? 1 : 0;
 }
