@@ -17,20 +17,23 @@ enum DecodeSchedule { kDecodeChunks, kDecodeBalanced, kDecodeBalancedF32 };
 // The schedule of a call of `batch` sequences of up to `max_slots` slots; `chunk_set`: by the caller.
 // The balanced one has a fixed cost, the scan of the lengths and a cold start of every persistent workgroup, some 5 us of a step beside a
 // chunk a workgroup.  Below 8 tiles of 16 slots a unit partials are fp32: with them it is the faster one only where a chunk's workgroup has a unit for
-// itself (two head tiles, r = 512) and there are some sequences.  Beyond, chunks are the faster ones at r = 128 and, with one head tile, r = 256, as
-// long as the unit with most of them has not much more than its even share.  (The chunk is made for the session's sequences: a call of some of
-// them has chunks as long, but fewer.)  us a step, chunks / balanced, by the slots that the fullest unit has beyond its share; sequences
-// of the call / the session x slots:
-//   r = 128, 8 heads   112 / 112 x 1024 (64) 17.6 / 21.3, 256 / 256 x 1024 (0) 24.9 / 29.1, 24 / 128 x 2048 (320) 15.9 / 19.0, 36 / 256 x 1024 (368)
-//                      15.7 / 16.5, 112 / 224 x 1024 (448) 21.9 / 21.3, 14 / 28 x 8192 (448) 21.6 / 20.6, 90 / 512 x 1024 (664) 21.1 / 20.2, 6 / 64 x 8192 (832) 19.6 / 16.6
-//   r = 128, 20 heads  112 / 112 x 1024 (64) 24.2 / 30.5, 56 / 224 x 1024 (224) 20.2 / 21.8, 3 / 14 x 16384 (256) 19.4 / 20.3, 32 / 224 x 1024 (320) 19.2 / 18.3,
-//                      40 / 512 x 1024 (864) 27.8 / 19.5
+// itself (two head tiles, r = 512) and there are some sequences.  us a step, chunks / balanced, all sequences of a session: r = 512, 20 and 32 heads,
+// 24 x 1000 (1512 tiles) 31.7 / 30.4 and 35.8 / 33.9, 12 x 2600 33.0 / 31.0 and 38.9 / 33.4, 8 x 2600 29.9 / 29.1 and 32.2 / 30.9, 16 x 1024 (1024 tiles) 24.9 /
+// 28.4 and 27.6 / 30.7, 2 x 12000 33.8 / 37.3 and 36.3 / 38.5; 16 heads, 24 x 1000 28.8 / 29.0; r = 256, 32 heads x 64, 24 x 1000 23.2 / 24.4.
+//
+// Beyond, chunks are the faster ones at r = 128 and, with one head tile, r = 256, within three limits.
+// `most`: the slots that the fullest unit has beyond its even share.  (The chunk is made for the session's sequences: a call of some of them has
+// chunks as long, but fewer.)  us a step, chunks / balanced, by these slots; sequences of the call / the session x slots:
+//   r = 128, 8 heads   112 / 112 x 1024 (64) 17.6 / 21.3, 24 / 128 x 2048 (320) 15.9 / 19.0, 36 / 256 x 1024 (368) 15.7 / 16.5, 112 / 224 x 1024 (448) 21.9 / 21.3,
+//                      14 / 28 x 8192 (448) 21.6 / 20.6, 90 / 512 x 1024 (664) 21.1 / 20.2, 6 / 64 x 8192 (832) 19.6 / 16.6
+//   r = 128, 20 heads  112 / 112 x 1024 (64) 24.2 / 30.5, 56 / 224 x 1024 (224) 20.2 / 21.8, 32 / 224 x 1024 (320) 19.2 / 18.3, 40 / 512 x 1024 (864) 27.8 / 19.5
 //   r = 256, 8 heads   64 / 64 x 1024 (0) 19.6 / 22.5, 128 / 128 x 1024 (0) 25.2 / 27.1, 32 / 128 x 1024 (128) 18.8 / 18.9, 40 / 160 x 1024 (160) 20.4 / 19.5, 96 / 96 x 1024
 //                      (192) 26.8 / 24.7, 24 / 128 x 2048 (320) 24.0 / 21.7, 6 / 64 x 8192 (832) 31.3 / 20.6
 //   r = 256, 32 heads x 128, 32 / 32 x 1024 (0) 29.6 / 26.4; r = 512, 16 heads, 32 / 32 x 1024 (0) 31.8 / 29.1
-// and in fp32, all sequences of a session: r = 512, 20 and 32 heads, 24 x 1000 (1512 tiles) 31.7 / 30.4 and 35.8 / 33.9, 12 x 2600 33.0 / 31.0 and 38.9 / 33.4, 8 x
-// 2600 29.9 / 29.1 and 32.2 / 30.9, 16 x 1024 (1024 tiles) 24.9 / 28.4 and 27.6 / 30.7, 2 x 12000 33.8 / 37.3 and 36.3 / 38.5; 16 heads, 24 x 1000 28.8 / 29.0; r = 256, 32 heads
-// x 64, 24 x 1000 23.2 / 24.4.
+// The chunk's length: r = 256, 8 heads, chunks of 256 (256 x 512) 25.5 / 28.2, of 384 (256 x 768) 37.3 / 32.9, of 768 52.5 / 48.3.  At r = 128 lengths that are all
+// alike gain with any chunk (of 512, 24.9 / 29.0, of 1024 36.9 / 41.2), but where they range from nothing to the most, two chunks a unit: of 320 17.5 / 20.7
+// (64 x 2560) and 16.5 / 19.1 (16 x 10240), of 384 21.0 / 21.1 and 21.0 / 20.0, of 1024 32.3 / 30.1 and 31.7 / 28.6.
+// With two head tiles the chunks of a sequence, lengths from nothing to the most, 20 heads: two (256 x 512) 24.8 / 28.4, eight (64 x 2048) 24.1 / 23.6, 32 (16 x 8192) 26.6 / 22.9.
 // A chunk that the caller set may be far from any of these: there the fixed border.
 constexpr DecodeSchedule decode_schedule(int r, int n_heads, int batch, int max_slots, int chunk, bool chunk_set, int n_cu) {
   const long long tiles = batch * ((max_slots + 15LL) / 16);
@@ -38,8 +41,10 @@ constexpr DecodeSchedule decode_schedule(int r, int n_heads, int batch, int max_
   if (tiles < 8LL * n_cu) return two && r == 512 && batch >= 8 && 2 * tiles >= 9LL * n_cu && !chunk_set ? kDecodeBalancedF32 : kDecodeChunks;
   const int most = r == 128 ? (two ? 300 : 400) : (r == 256 && !two ? 128 : -1);
   if (chunk_set || most < 0) return kDecodeBalanced;
-  const long long chunks = batch * ((max_slots + chunk - 1LL) / chunk), on_a_unit = (chunks + n_cu - 1) / n_cu;
-  return on_a_unit * chunk - (long long)batch * max_slots / n_cu > most ? kDecodeBalanced : kDecodeChunks;
+  const long long of_a_sequence = (max_slots + chunk - 1LL) / chunk, on_a_unit = (batch * of_a_sequence + n_cu - 1) / n_cu;
+  const int longest = r == 256 ? 256 : (two || on_a_unit == 1 ? 512 : 320);
+  const bool chunks = chunk <= longest && (!two || of_a_sequence <= 8) && on_a_unit * chunk - (long long)batch * max_slots / n_cu <= most;
+  return chunks ? kDecodeChunks : kDecodeBalanced;
 }
 
 }  // namespace mtla

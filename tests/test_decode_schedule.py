@@ -31,14 +31,15 @@ def takes(rule, r, heads, batch, max_batch, max_slots, n_cu=256):
 
 # r, heads, sequences of the call, of the session, slots, us a step in chunks and balanced (256 units, heads of 64 but where 16 or 32 at r >= 256: 128)
 MEASURED = [
-    (128, 8, 32, 32, 1024, 12.8, 16.4), (128, 8, 100, 100, 1000, 17.2, 20.0), (128, 8, 112, 112, 1024, 17.6, 21.3), (128, 8, 256, 256, 1024, 24.9, 29.1),
-    (128, 8, 128, 256, 1024, 18.8, 22.1), (128, 8, 24, 128, 2048, 15.9, 19.0), (128, 8, 36, 256, 1024, 15.7, 16.5), (128, 8, 2, 14, 16384, 15.6, 19.5),
+    (128, 8, 32, 32, 1024, 12.8, 16.4), (128, 8, 100, 100, 1000, 17.2, 20.0), (128, 8, 112, 112, 1024, 17.6, 21.3), (128, 8, 256, 256, 640, 19.9, 24.9),
+    (128, 8, 128, 256, 1024, 18.8, 22.1), (128, 8, 24, 128, 2048, 15.9, 19.0), (128, 8, 36, 256, 1024, 15.7, 16.5), (128, 8, 2, 14, 16384, 15.6, 19.5), (128, 8, 256, 256, 512, 18.5, 23.3),
     (128, 8, 14, 28, 8192, 21.6, 20.6), (128, 8, 448, 448, 512, 31.9, 28.7), (128, 8, 90, 512, 1024, 21.1, 20.2), (128, 8, 40, 512, 1024, 19.8, 16.7),
     (128, 8, 6, 64, 8192, 19.6, 16.6), (128, 16, 208, 208, 1024, 31.4, 27.9), (128, 20, 112, 112, 1024, 24.2, 30.5), (128, 20, 56, 224, 1024, 20.2, 21.8),
-    (128, 20, 3, 14, 16384, 19.4, 20.3), (128, 20, 64, 256, 1024, 21.4, 22.9), (128, 20, 32, 224, 1024, 19.2, 18.3), (128, 20, 36, 256, 1024, 20.6, 18.7),
+    (128, 20, 256, 256, 1024, 33.1, 46.9), (128, 20, 64, 256, 1024, 21.4, 22.9), (128, 20, 16, 16, 8192, 26.6, 22.9), (128, 20, 32, 224, 1024, 19.2, 18.3), (128, 20, 36, 256, 1024, 20.6, 18.7),
     (128, 20, 40, 512, 1024, 27.8, 19.5), (128, 32, 6, 64, 8192, 27.6, 20.2),
     (256, 8, 32, 32, 1024, 16.1, 18.7), (256, 8, 64, 64, 1024, 19.6, 22.5), (256, 8, 100, 100, 1000, 23.4, 25.0), (256, 8, 128, 128, 1024, 25.2, 27.1),
     (256, 8, 4, 16, 8192, 18.1, 20.1), (256, 8, 2, 8, 16384, 19.2, 23.5), (256, 16, 32, 128, 1024, 20.2, 21.8), (256, 16, 100, 100, 1000, 26.3, 28.3),
+    (256, 8, 256, 256, 768, 37.2, 32.9), (256, 8, 256, 256, 1504, 52.0, 46.8), (256, 16, 256, 256, 2048, 66.8, 45.6), (256, 8, 256, 256, 512, 25.5, 28.2),
     (256, 8, 96, 96, 1024, 26.8, 24.7), (256, 8, 40, 160, 1024, 20.4, 19.5), (256, 8, 160, 160, 1024, 33.7, 29.9), (256, 8, 24, 128, 2048, 24.0, 21.7),
     (256, 8, 40, 512, 1024, 30.9, 19.0), (256, 8, 90, 512, 1024, 32.6, 25.1), (256, 8, 6, 64, 8192, 31.3, 20.6), (256, 16, 40, 512, 1024, 36.4, 22.6),
     (256, 32, 32, 32, 1024, 29.6, 26.4), (256, 32, 100, 100, 1000, 47.8, 35.2), (256, 20, 40, 512, 1024, 46.7, 24.4),
