@@ -299,11 +299,13 @@ __global__ __launch_bounds__(kBlock) void kv_f32_kernel(ExplicitArgs a) {
 // have been multiplied, the values in front of the keys' product.  us of the call, 8 heads, r = 256, s = 2, ahead with one workgroup a unit / so: 8
 // prompts of 512 tokens 128 / 107, 12 of 777 333 / 272, 10 of 128 (640 workgroups) 42.1 / 39.6; 4 heads, 3 of 700 (528) 52.0 / 52.8, with s = 1
 // 60.9 / 69.8; 8 heads, one of 700 (352) 36.9 / 41.2: kAheadMost.  (Beyond it one prompt of 4096 alone is slower so, 343 / 355.)
-// With RT = 2 queries and tiles come in as whole rows, 16 bytes a lane, and change lanes in the wavefront's part of LDS: loaded straight into
+// TURNED (RT = 2): queries and tiles come in as whole rows, 16 bytes a lane, and change lanes in the wavefront's part of LDS: loaded straight into
 // the operands' layout (16 rows for neighbours; the values 4 bytes a lane) a tile keeps the address path of the unit for some 650 cycles
 // beside its 1280 of products, four wavefronts side by side.  us of the append and the parallel form, 8 heads x 64, r = 256: 3 prompts of 500 to 777 tokens
-// 49.6 -> 46.2, 2 of up to 900 with the latent output 92.2 -> 82.7; 4 heads, r = 64, 4 of 1024 40.5 -> 37.8.  Heads of 128 load as before: the
-// turns lengthen the chain of a wavefront that has its SIMD for itself (4 heads, 3 of 700, s = 1 70.3 / 75.5; 8 heads, 200 of 16 70.0 / 73.9; one
+// 49.6 -> 46.2, 2 of up to 900 with the latent output 92.2 -> 82.7; 4 heads, r = 64, 4 of 1024 40.5 -> 37.8.  A launch of at most a workgroup a unit loads as before
+// where it has more than 300 columns or hardly any (20 rows, 4 heads 29.8 / 30.3), and so do heads of 128: the
+// turns lengthen the chain of a wavefront that has its SIMD for itself (4 heads, 3 of 700, s = 1 70.3 / 75.5; 4 heads x 64, r = 64, s = 1, one of 2000 (252 workgroups)
+// 66.9 / 73.1, of 1000 45.6 / 48.5, of 500 36.2 / 37.2, but of 200 30.1 / 29.9, and 3 of 777 (300) 57.2 / 54.1; 8 heads x 128, 200 of 16 70.0 / 73.9; one
 // of 4096 365 / 339 though).
 // Three sequences of up to 777 tokens, 8 heads x 64: the vector-ALU kernel over absorbed queries took 353 us
 // (and 45 + 67 us for the absorption and the value projection, which this form does not have).
@@ -343,13 +345,12 @@ struct RowsF32 {
 };
 
 constexpr size_t kAheadMost = 576;  // workgroups of a launch over heads of 128
-template <int DH, int DR, int DV, int RT, bool AHEAD>
+template <int DH, int DR, int DV, int RT, bool AHEAD, bool TURNED>
 __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_kernel(ExplicitArgs a) {
   constexpr int KE = (DH + DR) / 16, KC = DH / 16, NV = DV / 16;
   // the wavefronts' values (rows of DV + 4, so that 4-byte reads of four rows spread over the banks), in the end their sums; their keys
-  constexpr bool kTurned = RT > 1;
   __shared__ __attribute__((aligned(16))) float s_o[kWaves][16][DV + 4];
-  __shared__ __attribute__((aligned(16))) float s_k[kTurned ? kWaves : 1][kTurned ? 16 * (DH + DR) : 4];
+  __shared__ __attribute__((aligned(16))) float s_k[TURNED ? kWaves : 1][TURNED ? 16 * (DH + DR) : 4];
   __shared__ float s_m[kWaves][16 * RT], s_l[kWaves][16 * RT];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), l16 = lane & 15, g = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a tile is the same for all lanes: its branches and addresses are scalar)
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
   const float* vx = latent ? reinterpret_cast<const float*>(a.cprime) + (size_t)b * a.T * a.r + slice * DV
                            : reinterpret_cast<const float*>(a.vx) + (size_t)b * a.T * kpitch + h * DH;
   f32x4 qf[RT][KE];
-  if constexpr (!kTurned) {
+  if constexpr (!TURNED) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int m_lane = (m0[t] < 0 ? 0 : m0[t]) + l16, m = m_lane < len ? m_lane : len - 1;
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(kBlock, AHEAD && RT == 1 ? 1 : 2) void prefill_f32_
 #pragma unroll
       for (int c = 0; c < KE; ++c) qf[t][c] *= a.scale_log2;
   };
-  if constexpr (kTurned) {
+  if constexpr (TURNED) {
     unsigned char* lds_k = reinterpret_cast<unsigned char*>(s_k[wv]);
     unsigned char* lds_r = lds_k + 16 * DH * 4;
     float (*lds_v)[DV + 4] = s_o[wv];
@@ -624,8 +625,14 @@ template <int DH, int DR, int DV, int RT>
 void launch_prefill_rows(const ExplicitArgs& a, int slices, hipStream_t st, const EventPair& ev) {
   const unsigned blocks = (a.T + 15) / 16;
   const dim3 grid(a.n_heads * slices, a.batch, (blocks + RT - 1) / RT);
-  if (RT > 1 || (size_t)grid.x * grid.y * grid.z <= kAheadMost) launch_timed(prefill_f32_kernel<DH, DR, DV, RT, true>, grid, dim3(kBlock), 0, st, ev, a);
-  else launch_timed(prefill_f32_kernel<DH, DR, DV, RT, RT != 1>, grid, dim3(kBlock), 0, st, ev, a);
+  const size_t n = (size_t)grid.x * grid.y * grid.z;
+  if constexpr (RT > 1) {
+    if (n <= 256 && (a.T <= 32 || a.T > (long long)300 * a.stride)) launch_timed(prefill_f32_kernel<DH, DR, DV, RT, true, false>, grid, dim3(kBlock), 0, st, ev, a);
+    else launch_timed(prefill_f32_kernel<DH, DR, DV, RT, true, true>, grid, dim3(kBlock), 0, st, ev, a);
+  } else {
+    if (n <= kAheadMost) launch_timed(prefill_f32_kernel<DH, DR, DV, RT, true, false>, grid, dim3(kBlock), 0, st, ev, a);
+    else launch_timed(prefill_f32_kernel<DH, DR, DV, RT, false, false>, grid, dim3(kBlock), 0, st, ev, a);
+  }
 }
 
 }  // namespace

@@ -22,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (65, (65, 64, 48), 8, 64, 256, 32, 4),
     (130, (130, 97, 0), 4, 32, 512, 64, 16),      # an empty sequence, the widest latent, the longest stride of the matrix-core append
     (49, (49, 47, 34), 2, 32, 64, 32, 1),         # the narrowest rows: eight of them a load
+    (641, (641, 16, 333), 2, 64, 64, 32, 1),      # few workgroups and many columns: operands as they are multiplied
+    (322, (322, 321, 0), 4, 32, 128, 32, 1),
+    (32, (32, 17, 1), 4, 64, 64, 32, 2),          # hardly any rows: likewise
     (81, (81, 17, 80), 2, 128, 64, 64, 2),        # one block a workgroup
     (500, (500, 479, 3), 8, 128, 128, 32, 2),     # heads of 128: more workgroups than have their next tile ahead (24 x 32)
     (290, (290, 273, 16), 16, 128, 64, 64, 1),    # 48 x 19
