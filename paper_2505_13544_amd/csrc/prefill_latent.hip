@@ -439,7 +439,7 @@ hipError_t launch_r(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) 
   static_assert(kAttnRows == LatentGeom<DH, DR, 64>::BM, "rows of a block");
   const int pairs = a.n_heads * a.batch;
   ExplicitArgs x = a;
-  x.group = attn_group(pairs, DH);
+  x.group = attn_group(pairs, DH, false);
   const dim3 grid((unsigned)((a.T + kAttnRows - 1) / kAttnRows) * (unsigned)(attn_pairs(pairs) * kXcds)), block(512);
 #define MTLA_CASE(RR)                                                                    \
   if (a.r == RR) {                                                                       \
