@@ -28,13 +28,15 @@ constexpr bool attn_at_once(int rows, int pairs, int n_blocks, int d_head) { ret
 // in each wavefront shorten it (every pair of tiles is still read by all wavefronts, so with more blocks than that the LDS is what they
 // wait for).  us a pass, 128 rows / 64: 2048 tokens, 8 heads x 128 (128 blocks of 128 rows) 55.3 / 48.6, 16 heads (256) 60.4 / 55.4, 24 heads (384) 71.6
 // / 68.7, but 3 of 1024 (384) 60.4 / 61.7 and 2 of 2048 (512) 75.6 / 77.5; d_head 64, whose blocks take half the LDS: 4096 x 8 heads (256) 57.3 / 49.1, 2 of
-// 3072 (384) 56.1 / 51.3, 32 of 256 (512) 40.1 / 38.7, s = 1, 1024 blocks 127.7 / 146.6.  Behind tokens of a cache all blocks are heavy: 2 of 512, 16 x 128
-// (128) 50.7 / 45.0, 8 of 128 (128) 117.4 / 114.0, 12 of 128 (192) 150.0 / 159.2; d_head 64, 16 of 128 (128) 63.2 / 55.6, 32 of 128 (256) 81.8 / 79.5.
+// 3072 (384) 56.1 / 51.3, 32 of 256 (512) 40.1 / 38.7, 8 of 500, 20 heads, s = 1 (640) 53.9 / 52.3, 5 of 900, 16 heads, s = 2
+// (640) 50.7 / 51.3, of 225 to 900 45.6 / 44.2, but 5 of 2000 (640) 59.8 / 62.0, s = 1, 1024 blocks 127.7 / 146.6.  Behind `past` slots of a cache all blocks are heavy: 2 of 512, 16 x 128
+// (128) 50.7 / 45.0, 8 of 128 (128) 117.4 / 114.0, 12 of 128 (192) 150.0 / 159.2; d_head 64, 16 of 128 (128) 63.2 / 55.6, 32 of 128 (256) 81.8 / 79.5, of 65 64.0 / 65.4; the longer the
+// past, the more of the pass is those reads: behind 4000 slots, 8 x 64, times of 64 rows over those of 128 at 128, 160, 192 and 256 blocks 0.90, 0.99, 1.03 and 1.03.
 // And up to 64 rows the other half of a block would be empty: 64 prompts of 64, 16 x 128 78.4 / 73.6; 48 behind a cache 307 / 299.
-[[gnu::always_inline]] constexpr int attn_rows(int T, int pairs, int d_head, bool behind) {
-  constexpr int kUnits = 256;
+[[gnu::always_inline]] constexpr int attn_rows(int T, int pairs, int d_head, int past) {
   const long long blocks = (long long)((T + kAttnRows - 1) / kAttnRows) * pairs;
-  return T <= kAttnRows / 2 || blocks <= (d_head <= 64 ? 2 : 1) * (behind ? kUnits / 2 : kUnits) ? kAttnRows / 2 : kAttnRows;
+  const int most = d_head <= 64 ? (past == 0 ? (T <= 1100 ? 640 : 512) : (past <= 2048 ? 240 : 160)) : (past == 0 ? 256 : 128);
+  return T <= kAttnRows / 2 || blocks <= most ? kAttnRows / 2 : kAttnRows;
 }
 
 struct AttnBlock {

@@ -768,7 +768,7 @@ template <int DH, int DR>
 hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) {
   constexpr int NW = 4;
   static_assert(32 * NW == kAttnRows, "rows of a block");
-  const int pairs = a.n_heads * a.batch, rows = attn_rows(a.T, pairs, DH, a.past_pitch > 0);
+  const int pairs = a.n_heads * a.batch, rows = attn_rows(a.T, pairs, DH, a.past_pitch);
   const int n_blocks = (a.T + rows - 1) / rows;
   ExplicitArgs x = a;
   x.group = attn_group(pairs, DH, attn_at_once(rows, pairs, n_blocks, DH));

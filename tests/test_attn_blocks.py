@@ -61,3 +61,14 @@ def test_one_group_where_all_blocks_are_there_at_once(blocks, lens, heads, d_hea
     B, T = lens
     rows = blocks.rows_of(T, B * heads, d_head, 0)
     assert bool(blocks.at_once(rows, B * heads, -(-T // rows), d_head)) == one_group
+
+
+# prompts, rows of each, heads, d_head, slots of a past, and the rows of a block that were the faster ones
+@pytest.mark.parametrize("B,T,heads,d_head,past,rows", [
+    (1, 2048, 8, 128, 0, 64), (1, 2048, 16, 128, 0, 64), (3, 1024, 16, 128, 0, 128), (2, 2048, 16, 128, 0, 128), (64, 64, 16, 128, 0, 64),
+    (64, 65, 16, 128, 0, 128), (1, 4096, 8, 64, 0, 64), (2, 3072, 8, 64, 0, 64), (32, 256, 8, 64, 0, 64), (8, 500, 20, 64, 0, 64), (8, 1100, 8, 64, 0, 64), (5, 2000, 8, 64, 0, 128), (4, 4096, 8, 64, 0, 128),
+    (2, 512, 16, 128, 1000, 64), (8, 128, 16, 128, 4000, 64), (12, 128, 16, 128, 1000, 128), (48, 64, 16, 128, 4000, 64),
+    (16, 128, 8, 64, 4000, 64), (32, 65, 8, 64, 4000, 128), (24, 128, 8, 64, 4000, 128), (16, 256, 8, 64, 4000, 128), (28, 128, 8, 64, 1000, 64),
+    (32, 65, 8, 64, 1000, 128)])
+def test_rows_of_a_block(blocks, B, T, heads, d_head, past, rows):
+    assert blocks.rows_of(T, B * heads, d_head, past) == rows
