@@ -39,6 +39,16 @@ constexpr bool attn_at_once(int rows, int pairs, int n_blocks, int d_head) { ret
   return T <= kAttnRows / 2 || blocks <= most ? kAttnRows / 2 : kAttnRows;
 }
 
+// Whether a unit is kept to two blocks of 128 rows (heads of 64 and their registers leave room for three).  With a few more blocks than two a unit all are
+// there from the start, and the unit that got three heavy ones is last; two at a time, the third goes to whoever is done.  It shows where a block
+// walks many columns.  us a pass, three / two a unit: one prompt of 4000, 20 heads (640 blocks), s = 1 116.6 / 111.5, s = 2 79.4 / 76.4, s = 4 61.7 / 64.8; of 4700, 16 heads (592), s = 4 61.2
+// / 59.9; 2 of 3200, 16 heads (800), s = 1 105.1 / 98.9, s = 4 60.3 / 62.7; 2 of 1900, 20 heads (600), s = 2 57.0 / 56.1; 5 of 900, 16 heads (640), s = 1 58.7 / 60.0; beyond, 2 of 4000,
+// 20 heads (1280) 106.9 / 110.1.
+[[gnu::always_inline]] constexpr bool attn_two_a_unit(int rows, int pairs, int n_blocks, int T, int s, int d_head, int past) {
+  const long long blocks = (long long)pairs * n_blocks;
+  return rows == kAttnRows && d_head <= 64 && past == 0 && blocks > 512 && blocks <= (s <= 2 ? 800 : 600) && T >= 950LL * s;
+}
+
 struct AttnBlock {
   int pair, block;  // pair: head + n_heads * sequence; may be past the last one
 };

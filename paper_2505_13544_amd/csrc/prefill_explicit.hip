@@ -777,12 +777,13 @@ hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const Eve
   // 77.2 / 75.5 and 92.0 / 93.1.
   x.stream_out = !a.out16 && (size_t)a.batch * a.T * a.n_heads * DH * 4 > kStreamOut;
   const dim3 grid((unsigned)n_blocks * (unsigned)(attn_pairs(pairs) * kXcds));
+  const size_t more_lds = attn_two_a_unit(rows, pairs, n_blocks, a.T, a.stride, DH, a.past_pitch) ? 20 * 1024 : 0;  // (three of 60 KB do not fit)
   const bool layer = a.q_f16 != 0;  // comes with out16
   if (layer != (a.out16 != nullptr) || (layer && !a.pos0)) return hipErrorInvalidValue;
   auto launch = [&](auto cont, auto lay) {
     constexpr bool C = decltype(cont)::value, L = decltype(lay)::value;
-    if (rows == kAttnRows / 2) launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 1>, grid, dim3(64 * NW), 0, st, ev, x);
-    else launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 2>, grid, dim3(64 * NW), 0, st, ev, x);
+    if (rows == kAttnRows / 2) launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 1>, grid, dim3(64 * NW), more_lds, st, ev, x);
+    else launch_timed(attn_explicit_kernel<DH, DR, NW, C, L, 2>, grid, dim3(64 * NW), more_lds, st, ev, x);
   };
   if (layer) launch(std::true_type(), std::true_type());
   else if (a.pos0) launch(std::true_type(), std::false_type());

@@ -12,6 +12,7 @@ SOURCE = """
 extern "C" int group_of(int pairs, int d_head, int at_once) { return mtla::attn_group(pairs, d_head, at_once); }
 extern "C" int at_once(int rows, int pairs, int n_blocks, int d_head) { return mtla::attn_at_once(rows, pairs, n_blocks, d_head); }
 extern "C" int rows_of(int T, int pairs, int d_head, int past) { return mtla::attn_rows(T, pairs, d_head, past); }
+extern "C" int two_a_unit(int rows, int pairs, int n_blocks, int T, int s, int d_head, int past) { return mtla::attn_two_a_unit(rows, pairs, n_blocks, T, s, d_head, past); }
 extern "C" void block_of(unsigned w, int pairs, int n_blocks, int group, int* out) {
   const mtla::AttnBlock b = mtla::attn_block(w, pairs, n_blocks, group);
   out[0] = b.pair;
@@ -72,3 +73,12 @@ def test_one_group_where_all_blocks_are_there_at_once(blocks, lens, heads, d_hea
     (32, 65, 8, 64, 1000, 128)])
 def test_rows_of_a_block(blocks, B, T, heads, d_head, past, rows):
     assert blocks.rows_of(T, B * heads, d_head, past) == rows
+
+
+@pytest.mark.parametrize("B,T,heads,s,d_head,two", [(1, 4000, 20, 1, 64, True), (1, 4000, 20, 2, 64, True), (1, 4000, 20, 4, 64, False), (1, 4700, 16, 4, 64, True), (2, 3200, 16, 1, 64, True),
+                                                    (2, 1900, 20, 2, 64, True), (5, 900, 16, 1, 64, False), (2, 4000, 20, 2, 64, False), (1, 4000, 20, 1, 128, False),
+                                                    (1, 4000, 8, 1, 64, False)])
+def test_two_blocks_a_unit(blocks, B, T, heads, s, d_head, two):
+    rows = blocks.rows_of(T, B * heads, d_head, 0)
+    assert bool(blocks.two_a_unit(rows, B * heads, -(-T // rows), T, s, d_head, 0)) == two
+    assert not blocks.two_a_unit(rows, B * heads, -(-T // rows), T, s, d_head, 1)
