@@ -395,11 +395,8 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   }
 
   // ---- normalise and store: lane holds row l16 of row tile rt, output columns 16 i + 4g .. +3.  The rows leave through LDS, up to whole
-  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path, 320 of them a block), and past the caches:
-  // 320 KB a block and unit otherwise take the place of the tiles that the blocks beside it read, and are written back in bursts.  us a pass, ordinary
-  // stores / these: 5 ragged prompts of up to 1531, 16 heads x 128, r = 512 (390 MB) 160.0 / 136.5, 8 of 2048 517 / 490, 1 of 700 58.8 / 55.3; 7 of 540, 8 x 64,
-  // r = 256 47.3 / 44.8.  What reads the outputs next finds fewer of them in the last-level cache; with an elementwise pass over both outputs behind it
-  // 267.5 / 257.0, 695 / 658, 68.0 / 67.2, 58.9 / 59.5.
+  // lines at a time (as they stand, a store is 64 bytes of 16 rows, 67 cycles of the address path, 320 of them a block), and past the caches where the
+  // launcher says so: 320 KB a block and unit otherwise take the place of the tiles that the blocks beside it read, and are written back in bursts.
   {
     const float l = quarter_reduce(l_run, LaneSum());
     if (g == 0) s_inv[16 * wv + l16] = m_own < len ? 1.f / l : 0.f;
@@ -425,7 +422,14 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
       for (int i = 0; i < N; ++i) {
         const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
         const u32x4_t v = *reinterpret_cast<const u32x4_t*>(area + row * (16 * PPR) + ((c ^ (row & SW)) << 4));
-        if (mt0 + row < T) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(to + row * to_row + 16 * c));
+        if (mt0 + row < T) {
+          if (a.stream_out) {  // (as a store of its own kind: the compiler makes one of two that differ in a hint)
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(to, 0, 16 * (int)to_row, 0x00027000);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, row * (int)to_row + 16 * c, 0, 2 /* nt */);
+          } else {
+            *reinterpret_cast<u32x4_t*>(to + (size_t)row * to_row + 16 * c) = v;
+          }
+        }
       }
       __builtin_amdgcn_wave_barrier();
     };
@@ -440,6 +444,13 @@ hipError_t launch_r(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) 
   const int pairs = a.n_heads * a.batch;
   ExplicitArgs x = a;
   x.group = attn_group(pairs, DH, false);
+  // Outputs past the caches: few bytes, which take the place of the tiles for nothing, and more than the caches hold; between them whoever reads the
+  // outputs next would wait for what the call gains.  us alone and with an elementwise pass over both outputs behind it, ordinary / past the caches: 16 heads x 128,
+  // r = 512, one of 409 (16 MB) 56.4 / 54.8 and 63.7 / 62.0, one of 1228 (48 MB) 82.2 / 80.7 and 98.5 / 100.1, 4 of 409 (64 MB) 64.4 / 62.9 and 84.5 / 85.5, 4 of 1024 (160 MB)
+  // 112.5 / 112.8 and 171.5 / 179.0, 4 of 321 to 1280 (200 MB) 124.4 / 116.9 and 209.2 / 198.1, 4 of 1920 (300 MB) 253.6 / 233.4 and 363.9 / 347.3; 8 x 64, r = 256, one
+  // of 1638 (16 MB) 62.2 / 59.9 and 72.2 / 70.3, 4 of 819 (32 MB) 54.9 / 52.6 and 65.4 / 64.8, 4 of 1228 (48 MB) 64.5 / 62.9 and 79.9 / 81.6.
+  const size_t out_bytes = (size_t)a.batch * a.T * a.n_heads * (DH + a.r) * 4;
+  x.stream_out = out_bytes <= (size_t)32 << 20 || out_bytes > (size_t)192 << 20;
   const dim3 grid((unsigned)((a.T + kAttnRows - 1) / kAttnRows) * (unsigned)(attn_pairs(pairs) * kXcds)), block(512);
 #define MTLA_CASE(RR)                                                                    \
   if (a.r == RR) {                                                                       \

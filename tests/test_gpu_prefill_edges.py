@@ -130,3 +130,20 @@ def test_outputs_past_the_caches():
         _, _, ref, _ = _gpu_prefill(wl.scaled(batch=1), wts, one, T, lens[b:b + 1], want_latent=False)
         assert torch.isfinite(out[b]).all() and (out[b] - ref[0]).abs().max() <= H.TOL["bf16"] / 10
         assert torch.all(out[b, lens[b]:] == 0)
+
+
+def test_latent_outputs_of_medium_size():
+    # 43 MB of outputs in one call, which stay in the caches, and the sequences one at a time, whose 14 MB leave past them: the same blocks
+    B, T, nh, dh = 3, 700, 16, 64
+    lens = np.array([T, 0, 129], np.int32)
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="medium", batch=B, d_model=64, n_heads=nh, d_head=dh, r=256, d_rope=32, stride=3, prefix=1, steps=0, seed=6)
+    wts = W.make_weights(wl, max_slots=-(-T // 3))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
+    d = dict(q=n(B, T, nh, dh), q_rope=n(B, T, nh, 32), c=n(B, T, 256), kr=n(B, T, 32))
+    _, _, out, lat = _gpu_prefill(wl, wts, d, T, lens, want_latent=True)
+    for b in range(B):
+        one = {k: v[b:b + 1].contiguous() for k, v in d.items()}
+        _, _, ref, ref_lat = _gpu_prefill(wl.scaled(batch=1), wts, one, T, lens[b:b + 1], want_latent=True)
+        assert torch.equal(out[b], ref[0]) and torch.equal(lat[b], ref_lat[0])
+        assert torch.isfinite(lat[b]).all() and torch.all(lat[b, lens[b]:] == 0) and torch.all(out[b, lens[b]:] == 0)
