@@ -455,9 +455,13 @@ __global__ __launch_bounds__(kBlock) void attn_mfma_kernel(AttnArgs a) {
 // query for itself.  us a step: 31 sequences of 640 slots, 20 heads x 128, r = 512 38.0, now 30.5; 7 of 700, 32 heads (whole layer) 52.3 and 38.0; 16
 // of 750, 16 heads, r = 512 24.3 and 20.4; 79 of 195, 16 heads x 64, r = 256 19.3 and 17.6.
 // ---------------------------------------------------------------------------
-// Chunks of more than one step: where two workgroups a unit still fit (r = 64 and 128) a step's rows travel while the step before is multiplied
-// into a second place (DB), and the query stays in registers.  us a step, rows asked for at the step's top / so, 8 sequences of 1024 slots: r = 128, 8 heads, chunks of
-// 128 12.2 / 11.8, of 320 14.6 / 13.6, 32 heads, of 160 14.8 / 13.8; r = 64, 16 heads, of 320 13.1 / 12.4.
+// Chunks of more than one step: where two workgroups a unit still fit (r = 128, and 64 with two head tiles) a step's rows travel while the step before is
+// multiplied into a second place (DB), and the query stays in registers.  us a step, rows asked for at the step's top / so, 8 sequences of 1024 slots: r = 128, 8 heads,
+// chunks of 128 12.2 / 11.8, of 320 14.6 / 13.6, 32 heads, of 160 14.8 / 13.8.
+// r = 64 and one head tile (OPS): three loads of rows and six of the query a wavefront are not worth the way through LDS.  They go straight into the operands' layout,
+// the first rows before the length is known, the next step's behind the maxima's barrier, and only the latents are put into LDS for the
+// value product.  us a step, through LDS / so: 16 heads, 8 sequences of 1024 in chunks of 320 12.4 / 12.3, 4 heads, 4 in chunks of 64 10.74 / 10.66 (16 heads,
+// 32 in chunks of 64 13.0 / 13.3).
 template <int R, int DR, int NHT, bool DB>
 struct SplitGeom {
   static constexpr int KC = R / 32, KT = (R + DR) / 32, HP = 16 * NHT, MW = R / 16 / kWaves;
@@ -477,6 +481,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
   using G = SplitGeom<R, DR, NHT, DB>;
   constexpr int KC = G::KC, KT = G::KT, E = R + DR, HP = G::HP, MW = G::MW;
   constexpr int GROUPS = kWaves / NHT;  // of wavefronts that share a head tile's slots
+  constexpr bool OPS = R == 64 && NHT == 1, QR = DB || OPS;  // operands straight into registers; the query stays in registers
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* sQ = smem + G::BODY;
   uint2* sP = reinterpret_cast<uint2*>(sQ + G::Q);  // [slot tile][head tile][lane]: weights of slots 4g .. 4g + 3, head l16
@@ -500,7 +505,8 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
     sp.dlat = (long long)(owner - b) * a.max_slots * R;
     sp.dkey = (long long)(owner - b) * a.max_slots * DR;
   }
-  const int in_row = lane >> 2, piece = (lane & 3) ^ swz_rows16<4>(in_row);  // what a lane brings in: 16 bytes of that row's 64
+  const int in_row = OPS ? l16 : lane >> 2, piece = OPS ? g : (lane & 3) ^ swz_rows16<4>(in_row);  // what a lane brings in: 16 bytes of that row's 64
+  u32x4_t own[OPS ? KT : 1];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
   // the wavefront's 16 slots from `base` on, into the step's place; slots past `last` become copies of that one
   auto issue_rows = [&](int base, int last, uint32_t step_at) {
@@ -510,7 +516,11 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
       const uint16_t* lr = lat + (size_t)slot * R + 8 * piece + (slot < sp.n ? sp.dlat : 0);
       const uint16_t* kr = key + (size_t)slot * DR + 8 * piece + (slot < sp.n ? sp.dkey : 0);
 #pragma unroll
-      for (int kk = 0; kk < KT; ++kk) load_to_lds_16(kk < KC ? lr + 32 * kk : kr + 32 * (kk - KC), to + 1024u * kk);
+      for (int kk = 0; kk < KT; ++kk) {
+        const uint16_t* from = kk < KC ? lr + 32 * kk : kr + 32 * (kk - KC);
+        if constexpr (OPS) own[kk] = *reinterpret_cast<const u32x4_t*>(from);
+        else load_to_lds_16(from, to + 1024u * kk);
+      }
     } else {
       size_t row = (size_t)s0;
       if constexpr (PG) {  // a page holds whole 16-slot tiles
@@ -521,12 +531,22 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
       const uint32_t i = (uint32_t)(slot - s0), at_lat = i * (R * 2) + 16 * piece, at_key = i * (DR * 2) + 16 * piece;
 #pragma unroll
       for (int kk = 0; kk < KT; ++kk) {
-        if (kk < KC) load_to_lds_16(lat + row * R + 32 * kk, at_lat, to + 1024u * kk);
-        else load_to_lds_16(key + row * DR + 32 * (kk - KC), at_key, to + 1024u * kk);
+        const uint16_t* from = kk < KC ? lat + row * R + 32 * kk : key + row * DR + 32 * (kk - KC);
+        if constexpr (OPS) own[kk] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(from) + (kk < KC ? at_lat : at_key));
+        else load_to_lds_16(from, kk < KC ? at_lat : at_key, to + 1024u * kk);
       }
     }
   };
-  {
+  u32x4_t qf[QR ? 2 * KT : 1];  // the query, where it is read more than once
+  if constexpr (OPS) {
+    issue_rows(k0 + wv * kTile, a.max_slots - 1, 0);
+    const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qcat) + ((size_t)b * a.n_heads + (l16 < a.n_heads ? l16 : a.n_heads - 1)) * E + 8 * g;
+#pragma unroll
+    for (int kk = 0; kk < KT; ++kk) {
+      qf[kk] = *reinterpret_cast<const u32x4_t*>(q + 32 * kk);
+      qf[QR ? KT + kk : 0] = *reinterpret_cast<const u32x4_t*>(q + a.q_plane + 32 * kk);
+    }
+  } else {
     const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qcat) + (size_t)b * a.n_heads * E;
     uint32_t at_q[NHT];  // heads past the last one: copies of it, never stored
 #pragma unroll
@@ -546,7 +566,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
   }
   const int live = live_slots(len, a.stride, a.max_slots);
   const int k1 = live < k0 + a.chunk ? live : k0 + a.chunk;
-  if (k0 < k1) issue_rows(k0 + wv * kTile, k1 - 1, 0);
+  if (!OPS && k0 < k1) issue_rows(k0 + wv * kTile, k1 - 1, 0);
 
   const int hq = NHT == 2 ? wv & 1 : 0, grp = NHT == 2 ? wv >> 1 : wv;  // head tile and slot tiles NHT grp .. of the wavefront's logits
   float m_ref[NHT], l_run = 0.f;  // m_ref: the same in all wavefronts; l_run: this lane's slots only
@@ -560,10 +580,15 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
   const uint32_t frag = (uint32_t)(l16 * 64 + ((g ^ swz_rows16<4>(l16)) << 4));
   const int vrow = 4 * g + (l16 >> 2);  // row of the lane's transposing reads
 
-  wait_loads_but<0>();
+  if (!OPS) wait_loads_but<0>();
   if (k0 >= k1) return;  // (nothing of this workgroup is on its way into LDS any more)
+  if constexpr (OPS) {  // the first rows were asked for before the length was known: those past it may never have been written
+    if (k0 + wv * kTile + l16 >= k1) {
+#pragma unroll
+      for (int kk = 0; kk < KT; ++kk) own[kk] = u32x4_t{0u, 0u, 0u, 0u};
+    }
+  }
   const unsigned char* qr = sQ + hq * (2 * KT * 1024) + frag;
-  u32x4_t qf[DB ? 2 * KT : 1];  // the query, where it is read more than once
   if constexpr (DB) {
     __syncthreads();
 #pragma unroll
@@ -571,12 +596,12 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
   }
   uint32_t step_at = 0;  // this step's rows in LDS
   for (int s0 = k0; s0 < k1; s0 += kWaves * kTile) {
-    if (!DB && s0 > k0) {
+    if (!DB && !OPS && s0 > k0) {
       __syncthreads();
       issue_rows(s0 + wv * kTile, k1 - 1, 0);
     }
-    if (s0 > k0) wait_loads_but<0>();
-    if (!DB || (NHT > 1 && s0 > k0)) __syncthreads();  // rows and query are there (with one head tile the rows are the wavefront's own)
+    if (!OPS && s0 > k0) wait_loads_but<0>();
+    if (!QR || (NHT > 1 && s0 > k0)) __syncthreads();  // rows and query are there (with one head tile the rows are the wavefront's own)
     // ---- logits S^T[slot, head] (log2 units), one chain per query plane
     float4_t sh[NHT], sl[NHT];
 #pragma unroll
@@ -584,11 +609,11 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
     const unsigned char* xr = smem + step_at + NHT * grp * G::TILE + frag;
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) {
-      const u32x4_t qh = DB ? qf[DB ? kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * kk);
-      const u32x4_t ql = DB ? qf[DB ? KT + kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * (KT + kk));
+      const u32x4_t qh = QR ? qf[QR ? kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * kk);
+      const u32x4_t ql = QR ? qf[QR ? KT + kk : 0] : *reinterpret_cast<const u32x4_t*>(qr + 1024 * (KT + kk));
 #pragma unroll
       for (int u = 0; u < NHT; ++u) {
-        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(xr + u * G::TILE + 1024 * kk));
+        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, OPS ? own[OPS ? kk : 0] : *reinterpret_cast<const u32x4_t*>(xr + u * G::TILE + 1024 * kk));
         sh[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, qh), sh[u], 0, 0, 0);
         sl[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, ql), sl[u], 0, 0, 0);
       }
@@ -604,7 +629,11 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
     mloc = quarter_reduce(mloc, LaneMax());
     if (g == 0) sM[grp * HP + 16 * hq + l16] = mloc;
     __syncthreads();  // the maxima are there, and nobody reads the rows of the step before
-    if (DB && s0 + kWaves * kTile < k1) issue_rows(s0 + kWaves * kTile + wv * kTile, k1 - 1, (uint32_t)G::STEP - step_at);
+    if constexpr (OPS) {  // the rows' latents to where the value products read them
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk) *reinterpret_cast<u32x4_t*>(smem + wv * G::TILE + 1024 * kk + frag) = own[kk];
+    }
+    if ((DB || OPS) && s0 + kWaves * kTile < k1) issue_rows(s0 + kWaves * kTile + wv * kTile, k1 - 1, (uint32_t)G::STEP - step_at);
     // ---- reference (fixed at the first step, moved when a step tops it by 2^40), weights as bf16
     constexpr float kRebase = 40.f;
 #pragma unroll
@@ -641,7 +670,7 @@ __global__ __launch_bounds__(kBlock, (SplitGeom<R, DR, NHT, DB>::PER_CU)) void a
     // ---- O^T[col, head] += C_hat^T[col, slot] P^T[slot, head]: a lane's eight slots of a K step are 4g .. + 3 of two tiles
 #pragma unroll
     for (int k = 0; k < kWaves / 2; ++k) {
-      if (DB && k > 0 && s0 + 2 * kTile * k >= k1) break;  // (weights of zero)
+      if (QR && k > 0 && s0 + 2 * kTile * k >= k1) break;  // (weights of zero)
       bf16x8_t pb[NHT];
 #pragma unroll
       for (int ht = 0; ht < NHT; ++ht) {
@@ -926,7 +955,7 @@ hipError_t launch_split_as(const AttnArgs& a, hipStream_t st, const EventPair& e
 }
 template <int R, int DR, int NHT, bool SH, bool PG>
 hipError_t launch_split(const AttnArgs& a, hipStream_t st, const EventPair& ev) {
-  if constexpr (R <= 128) {
+  if constexpr (R == 128 || (R == 64 && NHT == 2)) {
     if (a.chunk > kTile * kWaves) return launch_split_as<R, DR, NHT, true, SH, PG>(a, st, ev);
   }
   return launch_split_as<R, DR, NHT, false, SH, PG>(a, st, ev);
