@@ -175,7 +175,7 @@ struct ExplicitArgs {
   int q_f16 = 0;           // q and q_rope are fp16 and already carry scale_log2 (the layer's own projections)
   void* out16 = nullptr;   // if set: the output goes here as fp16 [B, T, n_heads, d_head] instead of to `out`
   int n_slices = 0;        // fp32 form only, latent-space output: column slices of the partial states per head
-  int stream_out = 0;      // attention launch: the outputs go past the caches, set by the launcher
+  int stream_out = 0;      // attention launch: `out` goes past the caches, set by the launcher
   int group = 1;           // attention launch: (sequence, head) pairs side by side (attn_blocks.h), set by the launcher
   float* out_latent = nullptr;  // if set (whole sequences only): also softmax . C_hat' [B, T, n_heads, r]
 };

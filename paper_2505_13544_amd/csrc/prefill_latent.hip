@@ -38,7 +38,7 @@ struct LatentGeom {
   static_assert(NCK <= NW && NCR <= NW, "one load per wavefront");
 };
 
-template <int DH, int DR, int R>
+template <int DH, int DR, int R, bool STREAM>
 __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
   using G = LatentGeom<DH, DR, R>;
   constexpr int BN = G::BN, BM = G::BM, NT = 64 * G::NW, KD = DH / 32, KQ = (DH + DR) / 32;
@@ -423,12 +423,9 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
         const int at = 64 * i + ln, row = at / PPR, c = at % PPR;
         const u32x4_t v = *reinterpret_cast<const u32x4_t*>(area + row * (16 * PPR) + ((c ^ (row & SW)) << 4));
         if (mt0 + row < T) {
-          if (a.stream_out) {  // (as a store of its own kind: the compiler makes one of two that differ in a hint)
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(to, 0, 16 * (int)to_row, 0x00027000);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rs, row * (int)to_row + 16 * c, 0, 2 /* nt */);
-          } else {
-            *reinterpret_cast<u32x4_t*>(to + (size_t)row * to_row + 16 * c) = v;
-          }
+          u32x4_t* at_row = reinterpret_cast<u32x4_t*>(to + row * to_row + 16 * c);
+          if constexpr (STREAM) __builtin_nontemporal_store(v, at_row);
+          else *at_row = v;
         }
       }
       __builtin_amdgcn_wave_barrier();
@@ -444,17 +441,18 @@ hipError_t launch_r(const ExplicitArgs& a, hipStream_t st, const EventPair& ev) 
   const int pairs = a.n_heads * a.batch;
   ExplicitArgs x = a;
   x.group = attn_group(pairs, DH, false);
-  // Outputs past the caches: few bytes, which take the place of the tiles for nothing, and more than the caches hold; between them whoever reads the
-  // outputs next would wait for what the call gains.  us alone and with an elementwise pass over both outputs behind it, ordinary / past the caches: 16 heads x 128,
-  // r = 512, one of 409 (16 MB) 56.4 / 54.8 and 63.7 / 62.0, one of 1228 (48 MB) 82.2 / 80.7 and 98.5 / 100.1, 4 of 409 (64 MB) 64.4 / 62.9 and 84.5 / 85.5, 4 of 1024 (160 MB)
-  // 112.5 / 112.8 and 171.5 / 179.0, 4 of 321 to 1280 (200 MB) 124.4 / 116.9 and 209.2 / 198.1, 4 of 1920 (300 MB) 253.6 / 233.4 and 363.9 / 347.3; 8 x 64, r = 256, one
-  // of 1638 (16 MB) 62.2 / 59.9 and 72.2 / 70.3, 4 of 819 (32 MB) 54.9 / 52.6 and 65.4 / 64.8, 4 of 1228 (48 MB) 64.5 / 62.9 and 79.9 / 81.6.
+  // Outputs past the caches, but for those of medium size: with them whoever reads the outputs next would wait for what the call gains.  us alone and with an
+  // elementwise pass over both outputs behind it, ordinary / past the caches: 16 heads x 128, r = 512, one of 409 (16 MB) 56.4 / 53.8 and 63.7 / 61.9, one of 1228 (48 MB) 82.7 / 80.3
+  // and 98.4 / 100.3, 4 of 409 (64 MB) 63.6 / 62.3 and 83.6 / 85.5, 4 of 614 (96 MB) 85.2 / 83.4 and 120.8 / 116.5, 4 of 1920 (300 MB) 253.6 / 219.4 and 363.9 / 333.4; 12 x 128,
+  // r = 256, 4 of 910 (64 MB) 77.1 / 74.2 and 97.6 / 98.5, 4 of 1820 (128 MB) 139.4 / 134.2 and 191.2 / 186.1; 8 x 64, 4 of 819 (32 MB) 54.9 / 52.2 and 65.4 / 64.9, 4 of 1228
+  // (48 MB) 64.2 / 62.5 and 79.5 / 80.4.
   const size_t out_bytes = (size_t)a.batch * a.T * a.n_heads * (DH + a.r) * 4;
-  x.stream_out = out_bytes <= (size_t)32 << 20 || out_bytes > (size_t)192 << 20;
+  const bool stream = out_bytes <= (size_t)32 << 20 || out_bytes > (size_t)80 << 20;
   const dim3 grid((unsigned)((a.T + kAttnRows - 1) / kAttnRows) * (unsigned)(attn_pairs(pairs) * kXcds)), block(512);
 #define MTLA_CASE(RR)                                                                    \
   if (a.r == RR) {                                                                       \
-    launch_timed(attn_latent_kernel<DH, DR, RR>, grid, block, 0, st, ev, x);             \
+    if (stream) launch_timed(attn_latent_kernel<DH, DR, RR, true>, grid, block, 0, st, ev, x); \
+    else launch_timed(attn_latent_kernel<DH, DR, RR, false>, grid, block, 0, st, ev, x); \
     return hipGetLastError();                                                            \
   }
   MTLA_CASE(64)
