@@ -13,7 +13,7 @@ constexpr int kXcds = 8;        // workgroup w runs on XCD w % 8
 // of 1287 to 2574 rows, 8 heads x 128, s = 2, 115 -> 99 us a pass; 3 of 3000, 16 x 64, 103 -> 85), and all pairs in one group had the heavy
 // blocks of all in step: 8 prompts of 2048, 16 heads x 128, groups of 2, 4, 8, 16: 235, 228, 234, 245 us (4096: 555, 556, 568, 588; 1024: 111, 106,
 // 113, 116); 8 of 4096, 8 x 64, s = 1, groups of 4 and 8: 237 and 230.  Groups are as equal as whole pairs allow (72 pairs at d_head 128: 5 and 4).
-// `at_once`: blocks of 128 rows, heads of 128, and no more of them than the chip holds side by side: there is no next round for a group to
+// `at_once`: blocks of 128 rows, heads of 128, no cache in front of them (behind one all blocks are heavy), and no more of them than the chip holds side by side: there is no next round for a group to
 // meet, and all heavy ones first leave a unit's second place to a light one.  Groups / one: 8 of 6 to 257, 16 heads (384 blocks) 55.3 / 51.6, 5 of 700, 16 heads
 // (480) 72.1 / 69.4, 8 of 10 to 400, 12 heads (384) 48.0 / 46.4, 8 of 400, 16 heads (512) 67.9 / 66.6; but 8 of 1000, 12 heads (768) 81.4 / 86.0, and with
 // blocks of 64, one of 1000, 16 heads (256) 48.9 / 52.4.  (d_head 64, three on a unit: no difference up to 1024 blocks.)
@@ -22,7 +22,9 @@ constexpr int attn_group(int pairs, int d_head, bool at_once) {
   const int per = attn_pairs(pairs), about = d_head <= 64 ? 8 : 4, groups = per / about > 1 && !at_once ? per / about : 1;
   return (per + groups - 1) / groups;
 }
-constexpr bool attn_at_once(int rows, int pairs, int n_blocks, int d_head) { return rows == kAttnRows && d_head > 64 && (long long)pairs * n_blocks <= 512; }
+constexpr bool attn_at_once(int rows, int pairs, int n_blocks, int d_head, int past) {
+  return rows == kAttnRows && d_head > 64 && past == 0 && (long long)pairs * n_blocks <= 512;
+}
 
 // Rows of a block of the plain form.  Where a unit has one block of 128 or none, the heaviest one's chain is the pass, and half the rows
 // in each wavefront shorten it (every pair of tiles is still read by all wavefronts, so with more blocks than that the LDS is what they

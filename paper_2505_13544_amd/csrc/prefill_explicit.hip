@@ -771,7 +771,7 @@ hipError_t launch_attn_explicit(const ExplicitArgs& a, hipStream_t st, const Eve
   const int pairs = a.n_heads * a.batch, rows = attn_rows(a.T, pairs, DH, a.past_pitch);
   const int n_blocks = (a.T + rows - 1) / rows;
   ExplicitArgs x = a;
-  x.group = attn_group(pairs, DH, attn_at_once(rows, pairs, n_blocks, DH));
+  x.group = attn_group(pairs, DH, attn_at_once(rows, pairs, n_blocks, DH, a.past_pitch));
   // Outputs past the caches where what reads them next would hardly find them there.  us a pass, ordinary / past the caches, alone and with an elementwise
   // pass over them behind it: 8 prompts of 4096, 16 heads x 128 (268 MB) 556 / 548 and 636 / 635, of 2400 (157 MB) 290 / 278 and 344 / 342; 8 of 1000, 12 heads (49 MB)
   // 77.2 / 75.5 and 92.0 / 93.1.

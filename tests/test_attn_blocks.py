@@ -10,7 +10,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "attn_blocks.h"
 extern "C" int group_of(int pairs, int d_head, int at_once) { return mtla::attn_group(pairs, d_head, at_once); }
-extern "C" int at_once(int rows, int pairs, int n_blocks, int d_head) { return mtla::attn_at_once(rows, pairs, n_blocks, d_head); }
+extern "C" int at_once(int rows, int pairs, int n_blocks, int d_head, int past) { return mtla::attn_at_once(rows, pairs, n_blocks, d_head, past); }
 extern "C" int rows_of(int T, int pairs, int d_head, int past) { return mtla::attn_rows(T, pairs, d_head, past); }
 extern "C" int two_a_unit(int rows, int pairs, int n_blocks, int T, int s, int d_head, int past) { return mtla::attn_two_a_unit(rows, pairs, n_blocks, T, s, d_head, past); }
 extern "C" void block_of(unsigned w, int pairs, int n_blocks, int group, int* out) {
@@ -61,7 +61,8 @@ def test_pairs_side_by_side(blocks, pairs, d_head, group):
 def test_one_group_where_all_blocks_are_there_at_once(blocks, lens, heads, d_head, one_group):
     B, T = lens
     rows = blocks.rows_of(T, B * heads, d_head, 0)
-    assert bool(blocks.at_once(rows, B * heads, -(-T // rows), d_head)) == one_group
+    assert bool(blocks.at_once(rows, B * heads, -(-T // rows), d_head, 0)) == one_group
+    assert not blocks.at_once(rows, B * heads, -(-T // rows), d_head, 1)
 
 
 # prompts, rows of each, heads, d_head, slots of a past, and the rows of a block that were the faster ones
