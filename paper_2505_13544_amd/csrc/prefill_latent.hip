@@ -322,6 +322,7 @@ __global__ __launch_bounds__(512, 1) void attn_latent_kernel(ExplicitArgs a) {
     take_own(own_c, rt, NV, own_place + 512 * NV);
   }
   wait_loads_but<0>();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the own values' place has been read (it is filled behind the next barrier)
   barrier_only();
   if (n_tiles > 0) form_weights(0);
   for (int t = 0; t < n_tiles; ++t) {
