@@ -48,12 +48,11 @@ int main() {
     near(m.what, gemm_tile_cost(equal(m.rows, m.cols, 512), m.tile), m.us512);
     near(m.what, gemm_tile_cost(equal(m.rows, m.cols, 2048), m.tile), m.us2048);
   }
-  picks("129 rows x 512 columns", equal(129, 512, 512), 3);                     // 17 us in 256 x 256 tiles, 6
+  picks("1000 rows x 1024 columns", equal(1000, 1024, 512), 3);                 // (256 tiles: 4.9 us)
   picks("7 sequences of up to 551 rows", ragged(7, 0, 551, {2112}, 1024), 2);   // 36.4 us in 256 x 128 tiles, 25.8
   picks("32768 x 3584 x 2048", equal(32768, 3584, 2048), kWide);                // 452 us in 256 x 256 tiles, 378
   picks("32768 x 4096 x 512", equal(32768, 4096, 512), kWide);                  // 171, 136
   picks("a contraction that is no multiple of 64", equal(32768, 4096, 2080), 0, false);
-  picks("one row", equal(1, 8, 32), 3, false);
   // two sequences of 510 new rows behind up to 1500 slots, 16 heads x 128: what the GPU's test of their starts relies on
   picks("two chunks", ragged(2, 1500, 510, {2048, 2048}, 512), kWide);
   // whatever the sizes, the estimate is of a tile that there is, and never grows when rows are taken away
@@ -100,6 +99,38 @@ int main() {
   splits("6000 rows, 16 heads x 128", layer(1, 6000, 16, 128, 512), 3, 3);       // 14.4, 33.5
   splits("2 x 4000 rows, 32 heads x 128", layer(2, 4000, 32, 128, 512), 3, 3);   // 28.2, 79.3
   splits("1000 rows, 8 heads x 64", layer(1, 1000, 8, 64, 256), -1, 0);
+  // the small products, and where they end: whole layers over short prompts, as measured with and without them
+  auto small = [&](const char* what, const Args& a, bool ring, int tile = -1) {
+    const GemmPlan p = gemm_plan(a, false, wide);
+    if (p.ring == ring && p.ring == (gemm_ring_tiles(a) <= kRingMost) && (ring || tile < 0 || (p.pick == tile && p.alone < 0))) return;
+    std::printf("%s: ring %d, %lld tiles, pick %d\n", what, p.ring, gemm_ring_tiles(a), p.pick);
+    ++failed;
+  };
+  small("33 tokens, 8 heads x 64", layer(1, 33, 8, 64, 256), true);      // 31.9 us without, 26.7
+  small("129 tokens, 8 heads x 64", layer(1, 129, 8, 64, 256), true);    // 33.4, 28.0
+  small("400 tokens, 8 heads x 64", layer(1, 400, 8, 64, 256), true);    // 36.0, 33.8
+  small("2 x 300 tokens, 8 heads x 64", layer(2, 300, 8, 64, 256), false);   // 36.6, 38.6
+  small("64 tokens, 16 heads x 128", layer(1, 64, 16, 128, 512), true);      // 52.1, 40.6
+  small("200 tokens, 16 heads x 128", layer(1, 200, 16, 128, 512), false);   // 53.3, 56.7
+  small("33 tokens, 32 heads x 128", layer(1, 33, 32, 128, 512), true);      // 70.4, 58.6
+  small("100 tokens, 32 heads x 128", layer(1, 100, 32, 128, 512), false);   // 75.9, 81.2
+  small("129 rows x 512 columns", equal(129, 512, 512), true);
+  small("one row", equal(1, 8, 32), true);
+  small("2000 tiles", equal(800, 640, 512), true);
+  small("2050 tiles", equal(801, 656, 512), false);
+  // tiles with rows of several sequences that form their own angles (tests/test_gpu_layer_prefill_angles.py): 5 sequences, 8 heads x 64, r = 256
+  for (int d_rope : {32, 64})
+    for (int tokens : {1, 13, 33, 64, 65, 100, 120}) {
+      Args a = equal(5 * tokens, 512, 128);
+      a.n_seg = 4;
+      a.seg[1].N = 8 * d_rope;
+      a.seg[1].epi = 1;
+      a.seg[2].N = 256;
+      a.seg[3].N = d_rope;
+      a.seg[3].epi = 2;
+      a.rows.T = tokens;
+      small("rows of several sequences", a, tokens < 100, 3);
+    }
   for (int i = 0; i < kWide; ++i) failed += gemm_own_angles(kGemmTiles[i].bm, kGemmTiles[i].bn) != (i == 3);
   return failed ? 1 : 0;
 }

@@ -1,6 +1,7 @@
-"""GPU parity of the projections' rotation in 64 x 64 tiles, which form their own angles: pieces without a list of lengths, so that a
-tile holds rows of several sequences, each continuing from another position.  Outputs and cache against the float64 oracle,
-within the 2e-2 of bf16."""
+"""GPU parity of the projections' rotation where tiles form their own angles: pieces without a list of lengths, so that a
+tile holds rows of several sequences, each continuing from another position.  Up to 65 tokens the products are the small ones of 16 x 16
+tiles and more (gemm_ring_kernel), from 100 on 64 x 64 tiles (gemm_nt_kernel; tests/test_gemm_tiles.py holds the rule to that).
+Outputs and cache against the float64 oracle, within the 2e-2 of bf16."""
 import numpy as np
 import pytest
 import torch
@@ -13,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d_rope", [32, 64])
-@pytest.mark.parametrize("tokens", [1, 13, 33, 64, 65])
+@pytest.mark.parametrize("tokens", [1, 13, 33, 64, 65, 100, 120])
 def test_tiles_with_rows_of_several_sequences(d_rope, tokens):
     starts = np.array([40, 3, 0, 57, 22], dtype=np.int32)
-    wl = W.WORKLOADS["speech_bf16"].scaled(name="lp_angles", batch=len(starts), d_model=128, d_rope=d_rope, stride=3, prefix=140,
+    wl = W.WORKLOADS["speech_bf16"].scaled(name="lp_angles", batch=len(starts), d_model=128, d_rope=d_rope, stride=3, prefix=180,
                                            steps=0, seed=300 + d_rope + tokens)
     wts, lw, sess, okw = _setup(wl)
     xs = [W.make_x(wl, b, 0, int(starts[b]) + tokens) for b in range(wl.batch)]

@@ -1,5 +1,5 @@
 """GPU parity of the prefill kernels at the edges of their tiles: the form with the latent-space output (32-column tiles, 128-row
-blocks), the plain form with and without paired row blocks (an even and an odd number of tiles, none at all), and the matrix
+blocks), the plain form in blocks of 64 and of 128 rows (an even and an odd number of tiles, none at all), and the matrix
 products at each of their tile sizes with rows left out."""
 import numpy as np
 import pytest
@@ -47,7 +47,7 @@ def test_latent_form(n_heads, d_head, r, d_rope, stride, lens, q_scale):
 
 
 @pytest.mark.parametrize("n_heads,d_head,r,d_rope,stride,lens", [
-    (3, 64, 128, 32, 1, (1, 2, 32, 33, 64, 65, 128, 129)),   # unpaired blocks; 0, 1, 2, 3 tiles, full and begun
+    (3, 64, 128, 32, 1, (1, 2, 32, 33, 64, 65, 128, 129)),   # blocks of 64 rows; 0, 1, 2, 3 tiles, full and begun
     (3, 128, 512, 64, 2, (64, 65, 66, 127, 130, 255, 256, 257)),
     (2, 128, 256, 32, 16, (513, 512, 511, 1)),
 ])
@@ -65,8 +65,8 @@ def test_plain_form_rows_of_a_block(n_heads, d_head, r, d_rope, stride, lens, wh
     _check(lens, n_heads, d_head, r, d_rope, stride, False, which=which)
 
 
-def test_plain_form_paired_blocks_and_large_products():
-    # more than 512 pairs of row blocks, an odd number of blocks (the last one has no partner); the key and value products take
+def test_plain_form_many_blocks_and_large_products():
+    # 1440 blocks of 128 rows in groups of pairs, most of them padding, an odd number a pair; the key and value products take
     # their largest tiles, with most sequences' rows left out
     lens = [640, 639, 513, 1] + [5] * 43 + [130]
     _check(lens, 6, 64, 256, 32, 2, False, which=(0, 1, 2, 3, 47))
