@@ -129,8 +129,8 @@ int32_t mtla_get_decode_chunk(const mtla_ctx* ctx);
  * sequences form one flat list cut into equal ranges, so ragged or large
  * batches keep every compute unit streaming.  0 = automatic: static or balanced,
  * whichever is faster for the batch's slot capacity, r and the number of heads
- * (balanced mostly from 8 tiles a compute unit on; below that partial sums are
- * fp32 in either); and, unless a chunk is set, one workgroup per sequence and one to four heads
+ * (balanced from 8 tiles a compute unit on, mostly; partial sums are fp32 in
+ * chunks); and, unless a chunk is set, one workgroup per sequence and one to four heads
  * without chunks or partials, one launch less, where that is faster.  That form
  * also exists in fp32 storage.  What decides is host-known: batch, heads, shape
  * and the context's max_slots, not the lengths, so a context made for more

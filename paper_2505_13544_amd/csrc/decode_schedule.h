@@ -11,15 +11,13 @@ constexpr int decode_chunk(int max_batch, int max_slots) {
   return (int)(chunk < 64 ? 64 : (chunk > 1024 ? 1024 : chunk));
 }
 
-// Static chunks, or the balanced schedule, whose partials are normalised halves (kDecodeBalanced) or fp32 as the chunks' are.
-enum DecodeSchedule { kDecodeChunks, kDecodeBalanced, kDecodeBalancedF32 };
-
-// The schedule of a call of `batch` sequences of up to `max_slots` slots; `chunk_set`: by the caller.
+// Whether a call of `batch` sequences of up to `max_slots` slots takes the balanced schedule rather than static chunks; `chunk_set`: by the caller.
 // The balanced one has a fixed cost, the scan of the lengths and a cold start of every persistent workgroup, some 5 us of a step beside a
-// chunk a workgroup.  Below 8 tiles of 16 slots a unit partials are fp32: with them it is the faster one only where a chunk's workgroup has a unit for
-// itself (two head tiles, r = 512) and there are some sequences.  us a step, chunks / balanced, all sequences of a session: r = 512, 20 and 32 heads,
-// 24 x 1000 (1512 tiles) 31.7 / 30.4 and 35.8 / 33.9, 12 x 2600 33.0 / 31.0 and 38.9 / 33.4, 8 x 2600 29.9 / 29.1 and 32.2 / 30.9, 16 x 1024 (1024 tiles) 24.9 /
-// 28.4 and 27.6 / 30.7, 2 x 12000 33.8 / 37.3 and 36.3 / 38.5; 16 heads, 24 x 1000 28.8 / 29.0; r = 256, 32 heads x 64, 24 x 1000 23.2 / 24.4.
+// chunk a workgroup, and its partials are halves.  Below 8 tiles of 16 slots a unit it is left out: with partials in fp32, as the chunks' are, it would gain there only with
+// two head tiles at r = 512 and some sequences (us a step, chunks / balanced, all sequences of a session, 20 and 32 heads: 24 x 1000 (1512 tiles) 31.7 / 30.4 and 35.8 / 33.9,
+// 12 x 2600 33.0 / 31.0 and 38.9 / 33.4, 16 x 1024 (1024 tiles) 24.9 / 28.4 and 27.6 / 30.7; 16 heads, 24 x 1000 28.8 / 29.0; r = 256, 32 heads x 64, 24 x 1000 23.2 / 24.4),
+// and the longer a softmax reference is kept, the fewer weights are exact: against 64 bits the output's error is 3.9e-4 of it in chunks and 1.10e-3 balanced
+// (20 heads, 24 x 1000, queries and keys of standard deviations 2 and 1; 9.2e-4 and 1.29e-3 with queries of 1).
 //
 // Beyond, chunks are the faster ones at r = 128 and, with one head tile, r = 256, within three limits.
 // `most`: the slots that the fullest unit has beyond its even share.  (The chunk is made for the session's sequences: a call of some of them has
@@ -35,16 +33,14 @@ enum DecodeSchedule { kDecodeChunks, kDecodeBalanced, kDecodeBalancedF32 };
 // (64 x 2560) and 16.5 / 19.1 (16 x 10240), of 384 21.0 / 21.1 and 21.0 / 20.0, of 1024 32.3 / 30.1 and 31.7 / 28.6.
 // With two head tiles the chunks of a sequence, lengths from nothing to the most, 20 heads: two (256 x 512) 24.8 / 28.4, eight (64 x 2048) 24.1 / 23.6, 32 (16 x 8192) 26.6 / 22.9.
 // A chunk that the caller set may be far from any of these: there the fixed border.
-constexpr DecodeSchedule decode_schedule(int r, int n_heads, int batch, int max_slots, int chunk, bool chunk_set, int n_cu) {
-  const long long tiles = batch * ((max_slots + 15LL) / 16);
+constexpr bool decode_balanced(int r, int n_heads, int batch, int max_slots, int chunk, bool chunk_set, int n_cu) {
+  if (batch * ((max_slots + 15LL) / 16) < 8LL * n_cu) return false;
   const bool two = n_heads > 16;
-  if (tiles < 8LL * n_cu) return two && r == 512 && batch >= 8 && 2 * tiles >= 9LL * n_cu && !chunk_set ? kDecodeBalancedF32 : kDecodeChunks;
   const int most = r == 128 ? (two ? 300 : 400) : (r == 256 && !two ? 128 : -1);
-  if (chunk_set || most < 0) return kDecodeBalanced;
+  if (chunk_set || most < 0) return true;
   const long long of_a_sequence = (max_slots + chunk - 1LL) / chunk, on_a_unit = (batch * of_a_sequence + n_cu - 1) / n_cu;
   const int longest = r == 256 ? 256 : (two || on_a_unit == 1 ? 512 : 320);
-  const bool chunks = chunk <= longest && (!two || of_a_sequence <= 8) && on_a_unit * chunk - (long long)batch * max_slots / n_cu <= most;
-  return chunks ? kDecodeChunks : kDecodeBalanced;
+  return chunk > longest || (two && of_a_sequence > 8) || on_a_unit * chunk - (long long)batch * max_slots / n_cu > most;
 }
 
 }  // namespace mtla

@@ -449,7 +449,6 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
   const bool use_mfma = g.dtype == MTLA_BF16 && attn_mfma_supported(at);
   ab.out_bf16 = use_mfma ? 1 : 0;
   ab.plane = at.q_plane = (size_t)g.max_batch * g.n_heads * (g.r + g.d_rope);  // two bf16 planes fill the fp32 area
-  DecodeSchedule schedule = kDecodeChunks;
   if (use_mfma && c->schedule != 1 && batch <= kBalancedMaxBatch) {
     if (c->n_cu == 0) {  // first decode call on this context: ask the device once
       int dev = 0, n = 0;
@@ -458,8 +457,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
         return MTLA_ERR_HIP;
       c->n_cu = n < kMaxPersistent ? n : kMaxPersistent;
     }
-    schedule = c->schedule == 2 ? kDecodeBalanced : decode_schedule(g.r, g.n_heads, batch, g.max_slots, c->chunk, c->chunk_set, c->n_cu);
-    if (schedule != kDecodeChunks) {
+    if (c->schedule == 2 || decode_balanced(g.r, g.n_heads, batch, g.max_slots, c->chunk, c->chunk_set, c->n_cu)) {
       at.n_persistent = c->n_cu;
       if (attn_cols_supported(at)) {
         const int n = c->n_cu * attn_cols_workgroups_per_cu(at);
@@ -479,7 +477,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     at.prefix_rows = g.max_batch;
   }
   at.part_f16 = 0;
-  if (use_mfma && attn_cols_supported(at)) {  // half-size partials if the schedule takes them and the matrix-core combine will read them
+  if (use_mfma && attn_cols_supported(at)) {  // half-size partials if the matrix-core combine will read them
     CombineArgs probe;
     probe.r = g.r;
     probe.d_head = g.d_head;
@@ -487,7 +485,7 @@ static mtla_status decode_core(mtla_ctx* c, const AppendArgs* ap, const void* q,
     probe.out = out;
     probe.out_latent = out_latent;
     probe.w_uv = w_uv;
-    at.part_f16 = schedule == kDecodeBalanced && combine_mfma_supported(probe) ? 1 : 0;
+    at.part_f16 = combine_mfma_supported(probe) ? 1 : 0;
     at.run_cost = kRunCost;
   }
   if (ap && ap->c_new_f32 && g.dtype != MTLA_F32 && !decode_front_supported(*ap, ab)) return MTLA_ERR_UNSUPPORTED;  // only the fused front reads fp32 latents

@@ -1,5 +1,5 @@
 """The rule that picks the schedule of a decode step's attention (csrc/decode_schedule.h), compiled and run on the host: where both schedules were
-measured it takes the faster one, and below eight tiles a unit partials are never halves."""
+measured it takes the faster one, and below eight tiles a unit, where the balanced one's outputs are less exact, it takes chunks."""
 import ctypes
 import os
 import subprocess
@@ -10,8 +10,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "decode_schedule.h"
 extern "C" int chunk(int max_batch, int max_slots) { return mtla::decode_chunk(max_batch, max_slots); }
-extern "C" int schedule(int r, int n_heads, int batch, int max_slots, int chunk, int chunk_set, int n_cu) {
-  return mtla::decode_schedule(r, n_heads, batch, max_slots, chunk, chunk_set, n_cu);
+extern "C" int balanced(int r, int n_heads, int batch, int max_slots, int chunk, int chunk_set, int n_cu) {
+  return mtla::decode_balanced(r, n_heads, batch, max_slots, chunk, chunk_set, n_cu);
 }
 """
 
@@ -26,7 +26,7 @@ def rule(tmp_path_factory):
 
 
 def takes(rule, r, heads, batch, max_batch, max_slots, n_cu=256):
-    return bool(rule.schedule(r, heads, batch, max_slots, rule.chunk(max_batch, max_slots), 0, n_cu))
+    return bool(rule.balanced(r, heads, batch, max_slots, rule.chunk(max_batch, max_slots), 0, n_cu))
 
 
 # r, heads, sequences of the call, of the session, slots, us a step in chunks and balanced (256 units, heads of 64 but where 16 or 32 at r >= 256: 128)
@@ -43,7 +43,7 @@ MEASURED = [
     (256, 8, 96, 96, 1024, 26.8, 24.7), (256, 8, 40, 160, 1024, 20.4, 19.5), (256, 8, 160, 160, 1024, 33.7, 29.9), (256, 8, 24, 128, 2048, 24.0, 21.7),
     (256, 8, 40, 512, 1024, 30.9, 19.0), (256, 8, 90, 512, 1024, 32.6, 25.1), (256, 8, 6, 64, 8192, 31.3, 20.6), (256, 16, 40, 512, 1024, 36.4, 22.6),
     (256, 32, 32, 32, 1024, 29.6, 26.4), (256, 32, 100, 100, 1000, 47.8, 35.2), (256, 20, 40, 512, 1024, 46.7, 24.4),
-    (512, 20, 24, 24, 1000, 31.7, 30.4), (512, 32, 24, 24, 1000, 35.8, 33.9), (512, 32, 8, 8, 2600, 32.2, 30.9), (512, 20, 16, 16, 1024, 24.9, 28.4),
+    (512, 20, 16, 16, 1024, 24.9, 28.4),
     (512, 32, 2, 2, 12000, 36.3, 38.5), (512, 16, 24, 24, 1000, 28.8, 29.0), (256, 32, 24, 24, 1000, 23.2, 24.4),
     (512, 16, 32, 32, 1024, 31.8, 29.1), (512, 16, 24, 128, 2048, 42.4, 32.5), (512, 32, 50, 50, 1000, 72.1, 44.2), (512, 32, 6, 64, 8192, 90.1, 31.8),
 ]
@@ -54,18 +54,15 @@ def test_takes_the_faster_one(rule, r, heads, batch, max_batch, max_slots, chunk
     assert takes(rule, r, heads, batch, max_batch, max_slots) == (balanced < chunks)
 
 
-CHUNKS, BALANCED, BALANCED_F32 = 0, 1, 2
-
-
 @pytest.mark.parametrize("r", [64, 128, 256, 512])
 @pytest.mark.parametrize("heads", [1, 16, 17, 32])
-def test_partials_of_small_calls_stay_in_fp32(rule, r, heads):
-    for batch, max_slots in ((1, 32752), (31, 1040), (127, 256), (2047, 16), (63, 511)):
+def test_small_calls_take_chunks(rule, r, heads):
+    for batch, max_slots in ((1, 32752), (31, 1040), (127, 256), (2047, 16), (63, 511), (24, 1000), (12, 2600), (8, 4000)):
         assert -(-max_slots // 16) * batch < 8 * 256
         for max_batch in (batch, 4 * batch, 65535):
-            assert rule.schedule(r, heads, batch, max_slots, rule.chunk(max_batch, max_slots), 0, 256) in (CHUNKS, BALANCED_F32)
+            assert not rule.balanced(r, heads, batch, max_slots, rule.chunk(max_batch, max_slots), 0, 256)
         for chunk in (32, 1024):
-            assert not rule.schedule(r, heads, batch, max_slots, chunk, 1, 256)
+            assert not rule.balanced(r, heads, batch, max_slots, chunk, 1, 256)
 
 
 @pytest.mark.parametrize("r", [64, 128, 256, 512])
@@ -74,12 +71,12 @@ def test_border(rule, r, n_cu):
     # r = 64, and any chunk of the caller's: eight tiles a unit, with nothing else asked
     for batch in (8 * n_cu - 1, 8 * n_cu, 8 * n_cu + 1, 64 * n_cu):
         for chunk in (32, 64, 4096):
-            assert bool(rule.schedule(r, 8, batch, 16, chunk, 1, n_cu)) == (batch >= 8 * n_cu)
-        assert bool(rule.schedule(64, 8, batch, 16, 64, 0, n_cu)) == (batch >= 8 * n_cu)
+            assert bool(rule.balanced(r, 8, batch, 16, chunk, 1, n_cu)) == (batch >= 8 * n_cu)
+        assert bool(rule.balanced(64, 8, batch, 16, 64, 0, n_cu)) == (batch >= 8 * n_cu)
 
 
 def test_sizes_at_the_limits(rule):
     assert rule.chunk(1, 1) == 64 and rule.chunk(512, 64) == 64 and rule.chunk(513, 64) == 128 and rule.chunk(65535, 2 ** 31 - 1) == 1024
     for r in (64, 128, 256, 512):
-        assert rule.schedule(r, 8, 65535, 2 ** 31 - 1, 1024, 0, 256) in (CHUNKS, BALANCED) 
-        assert rule.schedule(r, 32, 65535, 2 ** 31 - 1, 32, 1, 256) == BALANCED
+        assert rule.balanced(r, 8, 65535, 2 ** 31 - 1, 1024, 0, 256) == 1
+        assert rule.balanced(r, 32, 65535, 2 ** 31 - 1, 32, 1, 256) == 1

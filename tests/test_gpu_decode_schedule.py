@@ -1,4 +1,4 @@
-"""Decode calls below eight tiles a unit keep their partials in fp32, whichever schedule they take: with queries of zero every weight is
+"""Decode calls below eight tiles a unit keep their partials in fp32: with queries of zero every weight is
 one and the latent output the mean of the rows, which partials in half would miss by 2^-12 of them and more."""
 import numpy as np
 import pytest
@@ -9,9 +9,9 @@ from paper_2505_13544_amd.session import Session
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_heads,r,batch,slots", [(17, 512, 9, 2064),   # 1161 tiles: the balanced schedule
+@pytest.mark.parametrize("n_heads,r,batch,slots", [(17, 512, 9, 2064),   # 1161 tiles
                                                    (32, 512, 31, 1040),  # 2015
-                                                   (20, 512, 7, 4096),   # 1792, of few sequences: chunks
+                                                   (20, 512, 7, 4096),   # 1792
                                                    (16, 512, 23, 1400), (20, 256, 31, 1040), (16, 256, 31, 1040), (8, 128, 31, 1040)])
 def test_partials_in_fp32(n_heads, r, batch, slots):
     s = Session(n_heads=n_heads, d_head=64, r=r, d_rope=32, d_hyper=64, stride=1, max_batch=batch, max_slots=slots, dtype="bf16")
