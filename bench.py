@@ -43,8 +43,8 @@ MEASURED_TRAFFIC_LINE = {"speech_bf16": (2.504e6, 0.991),
                          "speech_b1024_bf16": (0.0, (306855.8 + 4164.1) * 1024 / 304.6e6)}
 # the same for the prefill attention kernel (profiles/prefill_hbm_traffic.md); every launch of a workload
 # is the same work, so the step count does not matter
-MEASURED_PREFILL_TRAFFIC_BYTES = {"prefill_s2": 2.0 * 348713.0 * 1024 + 262204.4 * 1024,
-                                  "prefill_s4": 2.0 * 294004.1 * 1024 + 262164.4 * 1024}
+MEASURED_PREFILL_TRAFFIC_BYTES = {"prefill_s2": 2.0 * 340758.0 * 1024 + 262145.2 * 1024,
+                                  "prefill_s4": 2.0 * 305956.4 * 1024 + 262213.2 * 1024}
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix rate, published
 
 

@@ -101,7 +101,8 @@ __global__ __launch_bounds__(kBlock) void append_step_kernel(AppendArgs a) {
 // for, neither of which needs the other -- the append of the step's token (workgroups below
 // `batch`) and the absorbed queries (the rest, numbered like the absorb kernel's grid) -- in one
 // launch, so a step pays one kernel start and one round trip to memory for both.
-// Four workgroups per unit (128 registers): what a step of 256 sequences launches is then resident at once.
+// Four workgroups per unit (128 registers, and with heads of 128 exactly a quarter of its LDS): what a step of 256 sequences launches is then resident at
+// once.  The whole-layer call's queries are fp32 and take twice the room: heads of 128 come to 48 KB a workgroup, three of them.
 template <int NCH, int KK, typename TC>
 __global__ __launch_bounds__(kBlock, 4) void decode_front_kernel(AppendArgs ap, AbsorbArgs ab, int gx, int gy) {
   extern __shared__ float smem[];

@@ -54,8 +54,8 @@ namespace {
 // left out: the row blocks are those of the sequences' rows in use, one after the other, so what is left over at the
 // end of the launch returns at once.  Where the caller wants zeros in such rows the blocks are the matrix's own.
 //
-// Tiles: large products go to the streams of gemm_wide.hip; here 64 x 64 to 128 x 128 for the small ones (129 rows x 512 columns,
-// K = 512: 17 us in two 256 x 256 tiles, 6 us in 64 x 64 ones), and 256 x 256 (eight wavefronts, one workgroup per CU)
+// Tiles: short prompts' products go to gemm_ring.hip, large ones to the streams of gemm_wide.hip; between them 64 x 64 to 128 x 128 here (1000 rows x 1024
+// columns, K = 512: 4.9 us in 64 x 64 tiles; 2000 x 2048: 9 us in 128 x 128), and 256 x 256 (eight wavefronts, one workgroup per CU)
 // where a contraction that is no multiple of 64 keeps a large one out of the streams.
 template <int BM, int BN>
 struct GemmGeom {
@@ -70,8 +70,7 @@ struct GemmGeom {
   static constexpr int NLW = W_BYTES / 1024 / NWV, NLA = A_BYTES / 1024 / NWV, LOADS = NLW + NLA;  // loads per wavefront and stage
   static constexpr int PER_CU = BM == 256 && BN == 256 ? 1 : 2;
   // Tiles of 64 rows form their angles while their first operands are on the way: a row is a lane, a frequency a wavefront's.  A
-  // launch that writes a table first is 3 us of a short prompt's; the layer over 129 tokens 35.5, now 34.5 us, 1000 tokens 46.0,
-  // now 44.4.  (Where the larger tiles pay there are thousands of rows: each would be turned once per column block, and the table's
+  // launch that writes a table first is 3 us of a prompt's; the layer over 1000 tokens 46.0, now 44.4 us.  (Where the larger tiles pay there are thousands of rows: each would be turned once per column block, and the table's
   // launch is 6 us of 1280.)
   static constexpr bool OWN_ANGLES = gemm_own_angles(BM, BN);
   static_assert(PF >= SPB && 2 * LOADS * SPB <= 63 && NLW >= 1 && NLA >= 1, "buffers, wait counts");
